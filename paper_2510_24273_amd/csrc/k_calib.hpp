@@ -4,22 +4,26 @@
 //                a chunk are therefore transposed once (calib_transpose_kernel, a plain LDS tile transpose) and the
 //                product is then the row-by-row form the matrix-core GEMM of the prompt compression computes,
 //                C += K^T (K^T)^T, with fp32 tile sums added to the fp64 matrix per chunk.
-//   eigenvectors One-sided Jacobi on the rows of G = C: a plane rotation of rows p, q makes them orthogonal.  With R the
-//                product of all rotations, G = R C; once all rows are orthogonal, G G^T = R C^2 R^T is diagonal, so
-//                the normalised rows of G are eigenvectors of C^2, hence of the positive semi-definite C, and the row
-//                norms are the eigenvalues.  A step rotates D/2 disjoint pairs at once (round-robin pairing, D - 1
-//                steps visit every pair: one sweep), one workgroup per pair, all accesses along contiguous rows, fp64
-//                throughout; nothing but G itself is kept.  Rows whose norm is below 1e-13 of the largest stand for
-//                eigenvalues that are zero to working precision and are left alone.
+//   eigenvectors One-sided Jacobi on the rows of G = R, the Cholesky factor of C = R^T R: a plane rotation of rows p, q
+//                makes them orthogonal.  With J the product of all rotations, G = J R keeps G^T G = C; once all rows are
+//                orthogonal, the normalised rows are eigenvectors of C and the squared row norms the eigenvalues, so no
+//                rotation matrix is kept.  (Starting from the rows of C itself, as a first form did, works on C^2: 15 to
+//                32 sweeps instead of about 10, since the off-diagonal part has twice the dynamic range to lose.)
+//                A step takes D / 32 disjoint pairs of 16-row blocks: one launch forms the pairs' 32 x 32 Gram
+//                matrices, a second one rotates them to orthogonality in LDS and applies the accumulated rotations to
+//                the rows with the fp64 matrix instructions; D / 16 - 1 steps (round-robin over the blocks) rotate every
+//                pair of rows once: one sweep.  One launch per row-pair step (D - 1 of them a sweep, each streaming the
+//                whole matrix) was bound by its launches up to D = 1024 and by the stream above.
+//                fp64 throughout.  Rows whose squared norm is below 1e-13 of the largest eigenvalue stand for eigenvalues
+//                that are zero to working precision and are left alone.
 #pragma once
 #include "common.hpp"
 
 namespace sals {
 
 constexpr int kCalTile = 64;        // transpose tile (elements)
-constexpr int kCalThreads = 256;    // Jacobi workgroup
-constexpr int kCalMaxEpt = 32;      // row elements per thread: D <= 8192
-constexpr int kCalMaxD = kCalThreads * kCalMaxEpt;
+constexpr int kCalThreads = 256;    // workgroup of the row kernels (D is a multiple of it)
+constexpr int kCalMaxD = 8192;
 
 // XT[d, t] = X[t, d] for t < n, zero for n <= t < n_pad; X [n, D], XT [D, n_pad]
 template <typename T>
@@ -100,57 +104,304 @@ __device__ __forceinline__ void calib_pair(int n, int s, int k, int* p, int* q)
     *q = (s - k + m) % m;
 }
 
-// One step: workgroup k rotates rows (p, q) of G so that they become orthogonal.
-// conv[k] keeps the largest |tan| of a rotation angle this workgroup slot has applied, since the host cleared it, to a
-// pair with at least one row of norm >= lead (the rows that can still change a leading eigenvector); floor: rows
-// with a smaller norm are left alone.
-__global__ __launch_bounds__(kCalThreads) void calib_jacobi_step_kernel(double* __restrict__ G, int D, int step,
-                                                                        double floor, double lead, double* __restrict__ conv)
+// ---- Cholesky factor ---------------------------------------------------------------------------------------------
+// G holds a copy of C and becomes R (upper triangular, C = R^T R), in panels of kCalPanel rows.  A pivot of at most `thr`
+// stands for a Schur complement that is zero to working precision: its row of R is zero.
+constexpr int kCalPanel = 64;
+
+// Panel at row k0: every workgroup factors the 64 x 64 diagonal block by itself (a row of it per four threads, the pivot
+// row passed through LDS, one barrier per pivot: 64 dependent steps are what the kernel takes, so repeating them beats
+// another launch) and then carries 256 columns of the panel through the triangular solve, one column per thread.  The
+// factored block goes to `diag` (other workgroups still read the original).  grid max(1, ceil((D - k0 - 64) / 256)).
+__global__ __launch_bounds__(256) void calib_chol_panel_kernel(double* __restrict__ G, int D, int k0, double thr,
+                                                               double* __restrict__ diag)
 {
-    __shared__ double red[3][kCalThreads / kWave];
-    int p, q;
-    calib_pair(D, step, blockIdx.x, &p, &q);
-    if (p > q) { const int t = p; p = q; q = t; }
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int ept = D / kCalThreads;  // D is a multiple of kCalThreads
-    double* gp = G + (size_t)p * D; double* gq = G + (size_t)q * D;
-    double a[kCalMaxEpt], b[kCalMaxEpt];
-    double aa = 0.0, bb = 0.0, ab = 0.0;
+    __shared__ double row[2][kCalPanel];
+    __shared__ double Rk[kCalPanel][kCalPanel + 1];
+    __shared__ double invd[kCalPanel];
+    const int tid = threadIdx.x, i = tid >> 2, j0 = (tid & 3) * 16;
+    const int c = k0 + kCalPanel + blockIdx.x * 256 + tid;
+    double a[16];
 #pragma unroll
-    for (int e = 0; e < kCalMaxEpt; ++e) {
-        if (e < ept) {  // uniform
-            a[e] = gp[e * kCalThreads + tid];
-            b[e] = gq[e * kCalThreads + tid];
-        } else {
-            a[e] = 0.0; b[e] = 0.0;
+    for (int e = 0; e < 16; ++e) a[e] = G[(size_t)(k0 + i) * D + k0 + j0 + e];
+    double pv_i = 0.0;
+    for (int k = 0; k < kCalPanel; ++k) {
+        double* rk = row[k & 1];
+        if (i == k) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) rk[j0 + e] = a[e];
+        }
+        __syncthreads();
+        const double pv = rk[k];
+        if (i == k) pv_i = pv;
+        if (i > k) {
+            const double f = pv > thr ? rk[i] / pv : 0.0;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) a[e] -= f * rk[j0 + e];
         }
     }
+    const double inv = pv_i > thr ? rsqrt(pv_i) : 0.0;
+    if ((tid & 3) == 0) invd[i] = inv;
 #pragma unroll
-    for (int e = 0; e < kCalMaxEpt; ++e) { aa += a[e] * a[e]; bb += b[e] * b[e]; ab += a[e] * b[e]; }
-    aa = wave_sum_f64(aa); bb = wave_sum_f64(bb); ab = wave_sum_f64(ab);
-    if (lane == 0) { red[0][wave] = aa; red[1][wave] = bb; red[2][wave] = ab; }
+    for (int e = 0; e < 16; ++e) {
+        a[e] = j0 + e >= i ? a[e] * inv : 0.0;
+        Rk[i][j0 + e] = a[e];
+        if (blockIdx.x == 0) diag[(size_t)(k0 + i) * kCalPanel + j0 + e] = a[e];
+    }
     __syncthreads();
-    aa = 0.0; bb = 0.0; ab = 0.0;
+    if (c >= D) return;
+    // forward substitution R_kk^T x = a, in steps of 16 rows so that the column's values stay in registers
+    double x[kCalPanel];
 #pragma unroll
-    for (int w = 0; w < kCalThreads / kWave; ++w) { aa += red[0][w]; bb += red[1][w]; ab += red[2][w]; }  // same order in every thread
-    const double na = sqrt(aa), nb = sqrt(bb);
-    if (!(fmin(na, nb) > floor)) return;                 // a row that stands for a zero eigenvalue
-    if (!(fabs(ab) > 1e-15 * na * nb)) return;           // orthogonal to working precision
-    // rotation that zeroes g_p . g_q:  t = tan(phi), the smaller root of  t^2 + 2 zeta t - 1 = 0
-    const double zeta = (bb - aa) / (2.0 * ab);
-    const double t = (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-    const double c = 1.0 / sqrt(1.0 + t * t), s = c * t;
-    if (tid == 0 && fmax(na, nb) >= lead) conv[blockIdx.x] = fmax(conv[blockIdx.x], fabs(t));
+    for (int k = 0; k < kCalPanel; ++k) x[k] = G[(size_t)(k0 + k) * D + c];
 #pragma unroll
-    for (int e = 0; e < kCalMaxEpt; ++e) {
-        if (e < ept) {
-            gp[e * kCalThreads + tid] = c * a[e] - s * b[e];
-            gq[e * kCalThreads + tid] = s * a[e] + c * b[e];
+    for (int k = 0; k < kCalPanel; ++k) {
+        x[k] *= invd[k];
+#pragma unroll
+        for (int m = k + 1; m < kCalPanel; ++m) x[m] -= Rk[k][m] * x[k];
+    }
+#pragma unroll
+    for (int k = 0; k < kCalPanel; ++k) G[(size_t)(k0 + k) * D + c] = x[k];
+}
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+// v_mfma_f64_16x16x4: lane holds A[l % 16][l / 16] and B[l / 16][l % 16]; result element i is row l / 16 + 4 i, column l % 16
+__device__ __forceinline__ f64x4 mma_f64(double a, double b, f64x4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+
+// Trailing update behind the panel at k0: A[i, j] -= sum_k R[k, i] R[k, j] over the panel's 64 rows, 64 x 64 tiles that
+// reach the upper triangle.  grid (tiles, tiles)
+__global__ __launch_bounds__(256) void calib_chol_update_kernel(double* __restrict__ G, int D, int k0)
+{
+    if (blockIdx.x < blockIdx.y) return;
+    const int base = k0 + kCalPanel, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l16 = lane & 15, kg = lane >> 4;
+    const int i0 = base + blockIdx.y * 64 + (wave >> 1) * 32, c0 = base + blockIdx.x * 64 + (wave & 1) * 32;
+    f64x4 acc[2][2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) acc[u][v] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int s = 0; s < kCalPanel / 4; ++s) {
+        const double* r = G + (size_t)(k0 + 4 * s + kg) * D + l16;
+        const double a0 = r[i0], a1 = r[i0 + 16], b0 = r[c0], b1 = r[c0 + 16];
+        acc[0][0] = mma_f64(a0, b0, acc[0][0]); acc[0][1] = mma_f64(a0, b1, acc[0][1]);
+        acc[1][0] = mma_f64(a1, b0, acc[1][0]); acc[1][1] = mma_f64(a1, b1, acc[1][1]);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) G[(size_t)(i0 + u * 16 + kg + 4 * e) * D + c0 + v * 16 + l16] -= acc[u][v][e];
+}
+
+// the factored diagonal blocks into place, zeros below the diagonal
+__global__ __launch_bounds__(256) void calib_chol_finish_kernel(double* __restrict__ G, int D, const double* __restrict__ diag)
+{
+    const int i = blockIdx.x, k0 = i / kCalPanel * kCalPanel;
+    for (int j = threadIdx.x; j < k0 + kCalPanel; j += 256)
+        G[(size_t)i * D + j] = j < k0 ? 0.0 : diag[(size_t)i * kCalPanel + j - k0];
+}
+
+// ---- Jacobi step over pairs of row blocks ----------------------------------------------------------------------------
+constexpr int kJacB = 16;               // rows per block
+constexpr int kJacRec = 3 * kJacB * kJacB;  // a pair's Gram matrix: blocks (P,P), (P,Q), (Q,Q)
+
+// Partial Gram matrices of the step's block pairs over one slice of the columns: part[slice][pair][3][16][16].
+// grid (slices, pairs); four waves, each taking every fourth group of 16 columns (a lane reads four consecutive columns
+// of its row, which serve as four contraction steps of the fp64 MFMA for either operand).
+__global__ __launch_bounds__(256) void calib_jacobi_gram_kernel(const double* __restrict__ G, int D, int step, int slice_cols,
+                                                                double* __restrict__ part)
+{
+    __shared__ double red[3][kJacRec];
+    int p, q;
+    calib_pair(D / kJacB, step, blockIdx.y, &p, &q);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, kg = lane >> 4;
+    const double* gp = G + (size_t)(p * kJacB + l16) * D + blockIdx.x * slice_cols + kg * 4;
+    const double* gq = G + (size_t)(q * kJacB + l16) * D + blockIdx.x * slice_cols + kg * 4;
+    f64x4 acc[3];
+#pragma unroll
+    for (int t = 0; t < 3; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+    for (int c = wave * 16; c < slice_cols; c += 64) {
+        const f64x4 a = *reinterpret_cast<const f64x4*>(gp + c), b = *reinterpret_cast<const f64x4*>(gq + c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            acc[0] = mma_f64(a[e], a[e], acc[0]);
+            acc[1] = mma_f64(a[e], b[e], acc[1]);
+            acc[2] = mma_f64(b[e], b[e], acc[2]);
+        }
+    }
+    // the waves' sums, added in wave order
+    if (wave > 0) {
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) red[wave - 1][t * 256 + (kg + 4 * e) * 16 + l16] = acc[t][e];
+    }
+    __syncthreads();
+    if (wave == 0) {
+        double* out = part + ((size_t)blockIdx.x * gridDim.y + blockIdx.y) * kJacRec;
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int at = t * 256 + (kg + 4 * e) * 16 + l16;
+                out[at] = acc[t][e] + red[0][at] + red[1][at] + red[2][at];
+            }
+    }
+}
+
+// cosine and sine of the rotation (g_p, g_q) -> (c g_p - s g_q, s g_p + c g_q) that makes two rows with squared norms aa,
+// bb and inner product ab orthogonal, by the smaller angle: with h = sqrt((bb-aa)^2 + 4 ab^2) the double angle has
+// cosine |bb-aa| / h and sine 2 |ab| / h, so two reciprocal square roots do.  Rows that stand for a zero eigenvalue
+// (squared norm at most floor) and rows orthogonal to working precision are left alone.
+__device__ __forceinline__ bool jac_rotation(double aa, double bb, double ab, double floor, double* c, double* s)
+{
+    const bool ok = fmin(aa, bb) > floor && ab * ab > 1e-30 * (aa * bb);
+    const double d = bb - aa, hi = rsqrt(d * d + 4.0 * ab * ab);
+    const double c2 = 0.5 + 0.5 * fabs(d) * hi, ci = rsqrt(c2);
+    const double sn = (d >= 0.0 ? ab : -ab) * hi * ci;
+    *c = ok ? c2 * ci : 1.0;
+    *s = ok ? sn : 0.0;
+    return ok;
+}
+
+// Rotates the rows of the step's block pairs.  Workgroup (slice, pair) adds up the pair's partial Gram matrices, runs the
+// rotations on the 32 x 32 Gram matrix in LDS (16 rounds of 16 disjoint pairs: every row of P with every row of Q; in the
+// sweep's first step 15 rounds more, the pairs inside the blocks) while accumulating them into a 32 x 32 matrix, and
+// applies that to its slice of the columns on the matrix cores.  Every slice repeats the small problem (the same
+// numbers): a launch between the two would cost more than its 16 dependent rounds.  Thread (i, j) of a round rotates the
+// 2 x 2 block of row pair i and column pair j from one LDS buffer into the other: one barrier per round.
+// conv[pair] keeps the largest |tan| of a rotation, since the host cleared it, that involved a row of squared norm >=
+// lead (the rows that can still change a leading eigenvector).
+__global__ __launch_bounds__(256) void calib_jacobi_rotate_kernel(double* __restrict__ G, int D, int step, int slice_cols,
+                                                                  const double* __restrict__ part, int n_part, double floor,
+                                                                  double lead, double* __restrict__ conv)
+{
+    constexpr int B2 = 2 * kJacB, LD = B2 + 1;
+    __shared__ double Wb[2][B2 * LD], Qb[2][B2 * LD];
+    __shared__ double s_conv[kJacB];
+    __shared__ int s_any;
+    int p, q;
+    calib_pair(D / kJacB, step, blockIdx.y, &p, &q);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, kg = lane >> 4;
+
+    // partial Gram matrices (at most 8) and the first two column tiles of this wave, all requested together
+    double w8[3][8];
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            w8[t][u] = part[((size_t)min(u, n_part - 1) * gridDim.y + blockIdx.y) * kJacRec + t * 256 + tid];
+    double* const gp = G + (size_t)(p * kJacB + kg) * D + blockIdx.x * slice_cols + l16;
+    double* const gq = G + (size_t)(q * kJacB + kg) * D + blockIdx.x * slice_cols + l16;
+    double x[2][8];  // tile u, contraction step s: row 4 s + kg of (P, Q)
+    auto load_tiles = [&](int c0) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int c = min(c0 + 64 * u, slice_cols - 16);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                x[u][s] = gp[(size_t)(4 * s) * D + c];
+                x[u][4 + s] = gq[(size_t)(4 * s) * D + c];
+            }
+        }
+    };
+    load_tiles(wave * 16);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        double v = 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v += u < n_part ? w8[t][u] : 0.0;
+        const int r = (tid >> 4) + (t == 2 ? kJacB : 0), c = (tid & 15) + (t >= 1 ? kJacB : 0);
+        Wb[0][r * LD + c] = v;
+        if (t == 1) Wb[0][c * LD + r] = v;
+    }
+    for (int e = tid; e < B2 * B2; e += 256) Qb[0][(e >> 5) * LD + (e & 31)] = (e >> 5) == (e & 31) ? 1.0 : 0.0;
+    if (tid == 0) s_any = 0;
+    __syncthreads();
+
+    const int i = tid >> 4, j = tid & 15;
+    double tmax = 0.0;
+    bool any = false;
+    int cur = 0;
+    auto round = [&](int pi, int qi, int pj, int qj) {
+        const double* W = Wb[cur]; const double* Q = Qb[cur];
+        double* Wn = Wb[cur ^ 1]; double* Qn = Qb[cur ^ 1];
+        const double aa = W[pi * LD + pi], bb = W[qi * LD + qi], ab = W[pi * LD + qi];
+        const double aj = W[pj * LD + pj], bj = W[qj * LD + qj], abj = W[pj * LD + qj];
+        const double b00 = W[pi * LD + pj], b01 = W[pi * LD + qj], b10 = W[qi * LD + pj], b11 = W[qi * LD + qj];
+        const double x0 = Q[pi * LD + j], y0 = Q[qi * LD + j], x1 = Q[pi * LD + j + kJacB], y1 = Q[qi * LD + j + kJacB];
+        double c, s, cj, sj;
+        const bool ok = jac_rotation(aa, bb, ab, floor, &c, &s);
+        jac_rotation(aj, bj, abj, floor, &cj, &sj);
+        any |= ok;
+        if (ok && fmax(aa, bb) >= lead) tmax = fmax(tmax, fabs(s) / c);
+        const double r00 = c * b00 - s * b10, r01 = c * b01 - s * b11, r10 = s * b00 + c * b10, r11 = s * b01 + c * b11;
+        Wn[pi * LD + pj] = cj * r00 - sj * r01;
+        Wn[pi * LD + qj] = sj * r00 + cj * r01;
+        Wn[qi * LD + pj] = cj * r10 - sj * r11;
+        Wn[qi * LD + qj] = sj * r10 + cj * r11;
+        Qn[pi * LD + j] = c * x0 - s * y0; Qn[qi * LD + j] = s * x0 + c * y0;
+        Qn[pi * LD + j + kJacB] = c * x1 - s * y1; Qn[qi * LD + j + kJacB] = s * x1 + c * y1;
+        __syncthreads();
+        cur ^= 1;
+    };
+    if (step == 0) {
+        auto inside = [&](int t, int k, int* a, int* b) {  // pair k of round t: k < 8 inside P, otherwise inside Q
+            calib_pair(kJacB, t, k & 7, a, b);
+            *a += k < 8 ? 0 : kJacB; *b += k < 8 ? 0 : kJacB;
+        };
+        for (int t = 0; t < kJacB - 1; ++t) {
+            int pi, qi, pj, qj;
+            inside(t, i, &pi, &qi);
+            inside(t, j, &pj, &qj);
+            round(pi, qi, pj, qj);
+        }
+    }
+    for (int t = 0; t < kJacB; ++t) round(i, kJacB + ((i + t) & 15), j, kJacB + ((j + t) & 15));
+    if (j == 0) s_conv[i] = tmax;
+    if (any) s_any = 1;
+    __syncthreads();
+    if (!s_any) return;  // uniform, and the same in every slice of the pair
+    if (tid == 0 && blockIdx.x == 0) {
+        double v = conv[blockIdx.y];
+        for (int k = 0; k < kJacB; ++k) v = fmax(v, s_conv[k]);
+        conv[blockIdx.y] = v;
+    }
+    double qa[2][8];  // the accumulated rotations as MFMA operand: rows m 16 .. +16, contraction step s
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int s = 0; s < 8; ++s) qa[m][s] = Qb[cur][(m * 16 + l16) * LD + 4 * s + kg];
+    for (int c0 = wave * 16; c0 < slice_cols; c0 += 128) {
+        if (c0 != wave * 16) load_tiles(c0);
+        f64x4 acc[2][2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                acc[u][m] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int s = 0; s < 8; ++s) acc[u][m] = mma_f64(qa[m][s], x[u][s], acc[u][m]);
+            }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int c = c0 + 64 * u;
+            if (c < slice_cols) {  // uniform
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    gp[(size_t)(4 * e) * D + c] = acc[u][0][e];
+                    gq[(size_t)(4 * e) * D + c] = acc[u][1][e];
+                }
+            }
         }
     }
 }
 
-// norm of every row (the eigenvalue estimate lambda_i) and the sign that makes the row's largest component positive
+// norm of every row and the sign that makes the row's largest component positive
 __global__ __launch_bounds__(kCalThreads) void calib_rownorm_kernel(const double* __restrict__ G, int D, double* __restrict__ lam,
                                                                     double* __restrict__ sgn)
 {
@@ -185,20 +436,22 @@ __global__ __launch_bounds__(kCalThreads) void calib_rownorm_kernel(const double
     }
 }
 
-// Row i takes rank = number of rows with a larger norm (equal ones by row index); eigval[rank] = lambda_i and, for
-// rank < r, column rank of U [D, r] = sgn_i * row i of G / lambda_i, rounded to the storage type (a zero row gives a
-// zero column).
-template <typename T>
-__global__ __launch_bounds__(kCalThreads) void calib_select_kernel(const double* __restrict__ G, const double* __restrict__ lam,
+// Row i of G takes rank = number of rows with a larger norm (equal ones by row index); eigval[rank] = lambda_i and, for
+// rank < r, column rank of U [D, r] = sgn_i * row i of G / |row i|, rounded to the storage type (a zero row gives a
+// zero column); row i of C = lambda_i times the eigenvector.  ROOT: G is the rotated Cholesky factor (lambda = squared
+// norm); otherwise its rows are C's own, orthogonal as they came (lambda = norm).
+template <typename T, bool ROOT>
+__global__ __launch_bounds__(kCalThreads) void calib_select_kernel(const double* __restrict__ G, const double* __restrict__ norm,
                                                                    const double* __restrict__ sgn, int D, int r,
-                                                                   double* __restrict__ eigval, T* __restrict__ U)
+                                                                   double* __restrict__ eigval, T* __restrict__ U,
+                                                                   double* __restrict__ C)
 {
     __shared__ int cnt[kCalThreads / kWave];
     const int i = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const double li = lam[i];
+    const double li = norm[i];
     int c = 0;
     for (int j = tid; j < D; j += kCalThreads) {
-        const double lj = lam[j];
+        const double lj = norm[j];
         c += (lj > li || (lj == li && j < i)) ? 1 : 0;
     }
 #pragma unroll
@@ -208,10 +461,12 @@ __global__ __launch_bounds__(kCalThreads) void calib_select_kernel(const double*
     int rank = 0;
 #pragma unroll
     for (int w = 0; w < kCalThreads / kWave; ++w) rank += cnt[w];
-    if (tid == 0) eigval[rank] = li;
-    if (rank < r) {
-        const double s = li > 0.0 ? sgn[i] / li : 0.0;
-        for (int d = tid; d < D; d += kCalThreads) elem<T>::store(U + (size_t)d * r + rank, (float)(s * G[(size_t)i * D + d]));
+    if (tid == 0) eigval[rank] = ROOT ? li * li : li;
+    const double s = li > 0.0 ? sgn[i] / li : 0.0;
+    for (int d = tid; d < D; d += kCalThreads) {
+        const double g = G[(size_t)i * D + d];
+        if (rank < r) elem<T>::store(U + (size_t)d * r + rank, (float)(s * g));
+        if (ROOT) C[(size_t)i * D + d] = li * g;
     }
 }
 

@@ -1449,11 +1449,38 @@ sals_status sals_calib_accumulate(int32_t dtype, const void* K, int64_t n_tok, i
     return calib_accumulate_t<float>(K, n_tok, D, C, workspace, st);
 }
 
+namespace {
+// column slices of the two launches of a Jacobi step: as many (at most 8, each a whole number of 64-column groups) as
+// keep the step within about two workgroups per compute unit
+int jac_slices(int D)
+{
+    int s = 1;
+    while (s < 8 && D % (128 * s) == 0 && D / (2 * kJacB) * 2 * s <= 512) s *= 2;
+    return s;
+}
+struct EigWs {  // byte offsets into the workspace
+    size_t G, conv, norm, sgn, diag, part, total;
+};
+EigWs eig_ws(int D)
+{
+    EigWs w{};
+    size_t o = 0;
+    auto take = [&](size_t bytes) { const size_t at = o; o = align_up(o + bytes); return at; };
+    w.G = take((size_t)D * D * 8);               // the rotated factor
+    w.conv = take((size_t)(D / (2 * kJacB)) * 8);  // convergence slots
+    w.norm = take((size_t)D * 8);                // row norms and signs
+    w.sgn = take((size_t)D * 8);
+    w.diag = take((size_t)D * kCalPanel * 8);    // factored diagonal blocks
+    w.part = take((size_t)jac_slices(D) * (D / (2 * kJacB)) * kJacRec * 8);  // partial Gram matrices of a step
+    w.total = o;
+    return w;
+}
+}  // namespace
+
 size_t sals_calib_eigenvectors_workspace_bytes(int32_t D)
 {
     if (D < kCalThreads || D % kCalThreads != 0 || D > kCalMaxD) return 0;
-    // convergence slots [D / 2], row norms and signs [D] each
-    return align_up((size_t)(D / 2) * 8) + 2 * align_up((size_t)D * 8);
+    return eig_ws(D).total;
 }
 
 sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dtype, double* eigval, void* U, void* workspace,
@@ -1467,44 +1494,65 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         return SALS_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     unsigned char* ws = static_cast<unsigned char*>(workspace);
-    double* conv = reinterpret_cast<double*>(ws);
-    double* lam = reinterpret_cast<double*>(ws + align_up((size_t)(D / 2) * 8));
-    double* sgn = reinterpret_cast<double*>(reinterpret_cast<unsigned char*>(lam) + align_up((size_t)D * 8));
-    std::vector<double> h_conv((size_t)D / 2), h_lam((size_t)D);
-    auto row_norms = [&]() -> bool {  // row norms to the host (blocking)
-        hipLaunchKernelGGL(calib_rownorm_kernel, dim3(D), dim3(kCalThreads), 0, st, C, D, lam, sgn);
-        return hipMemcpyAsync(h_lam.data(), lam, (size_t)D * 8, hipMemcpyDeviceToHost, st) == hipSuccess &&
+    const EigWs off = eig_ws(D);
+    auto at = [&](size_t o) { return reinterpret_cast<double*>(ws + o); };
+    double *G = at(off.G), *conv = at(off.conv), *norm = at(off.norm), *sgn = at(off.sgn), *diag = at(off.diag), *part = at(off.part);
+    const int n_pairs = D / (2 * kJacB), n_steps = D / kJacB - 1, slices = jac_slices(D);
+    std::vector<double> h_conv((size_t)n_pairs), h_norm((size_t)D);
+    auto row_norms = [&](const double* M) -> bool {  // row norms to the host (blocking)
+        hipLaunchKernelGGL(calib_rownorm_kernel, dim3(D), dim3(kCalThreads), 0, st, M, D, norm, sgn);
+        return hipMemcpyAsync(h_norm.data(), norm, (size_t)D * 8, hipMemcpyDeviceToHost, st) == hipSuccess &&
                hipStreamSynchronize(st) == hipSuccess;
     };
-    if (!row_norms()) return SALS_ERR_HIP;
-    const double n0 = *std::max_element(h_lam.begin(), h_lam.end());
+    if (!row_norms(C)) return SALS_ERR_HIP;
+    const double n0 = *std::max_element(h_norm.begin(), h_norm.end());  // (between the largest diagonal entry and lambda_0)
     const double floor = 1e-13 * n0;
     double lead = 0.0;  // first sweep: every rotation counts
     int done = 0;
     bool converged = !(n0 > 0.0);  // the zero matrix needs no rotation
-    while (done < max_sweeps && !converged) {
-        if (hipMemsetAsync(conv, 0, (size_t)(D / 2) * 8, st) != hipSuccess) return SALS_ERR_HIP;
-        for (int step = 0; step < D - 1; ++step)
-            hipLaunchKernelGGL(calib_jacobi_step_kernel, dim3(D / 2), dim3(kCalThreads), 0, st, C, D, step, floor, lead, conv);
+    bool rotated = false;
+    if (!converged) {  // G = Cholesky factor
+        if (hipMemcpyAsync(G, C, (size_t)D * D * 8, hipMemcpyDeviceToDevice, st) != hipSuccess) return SALS_ERR_HIP;
+        for (int k0 = 0; k0 < D; k0 += kCalPanel) {
+            const int rest = D - k0 - kCalPanel;
+            hipLaunchKernelGGL(calib_chol_panel_kernel, dim3(std::max(1, ceil_div(rest, 256))), dim3(256), 0, st, G, D, k0,
+                               1e-14 * n0, diag);
+            if (rest > 0)
+                hipLaunchKernelGGL(calib_chol_update_kernel, dim3(rest / 64, rest / 64), dim3(256), 0, st, G, D, k0);
+        }
+        hipLaunchKernelGGL(calib_chol_finish_kernel, dim3(D), dim3(256), 0, st, G, D, diag);
         if (launch_status() != SALS_OK) return SALS_ERR_HIP;
-        if (hipMemcpyAsync(h_conv.data(), conv, (size_t)(D / 2) * 8, hipMemcpyDeviceToHost, st) != hipSuccess) return SALS_ERR_HIP;
-        if (!row_norms()) return SALS_ERR_HIP;
+    }
+    while (done < max_sweeps && !converged) {
+        if (hipMemsetAsync(conv, 0, (size_t)n_pairs * 8, st) != hipSuccess) return SALS_ERR_HIP;
+        for (int step = 0; step < n_steps; ++step) {
+            hipLaunchKernelGGL(calib_jacobi_gram_kernel, dim3(slices, n_pairs), dim3(256), 0, st, G, D, step, D / slices, part);
+            hipLaunchKernelGGL(calib_jacobi_rotate_kernel, dim3(slices, n_pairs), dim3(256), 0, st, G, D, step, D / slices, part,
+                               slices, floor, lead, conv);
+        }
+        if (launch_status() != SALS_OK) return SALS_ERR_HIP;
+        if (hipMemcpyAsync(h_conv.data(), conv, (size_t)n_pairs * 8, hipMemcpyDeviceToHost, st) != hipSuccess) return SALS_ERR_HIP;
+        if (!row_norms(G)) return SALS_ERR_HIP;
         double worst = 0.0;
         for (double v : h_conv) worst = std::max(worst, v);
+        rotated = rotated || worst > 0.0;  // (in the first sweep every rotation is recorded)
         ++done;
         // a rotation by less than 1e-11 no longer moves an eigenvector; only pairs with a row among the r largest
         // (a little below the r-th largest norm, so that the r-th itself is in) are asked to have converged
         converged = worst <= 1e-11;
-        std::vector<double> sorted(h_lam);
-        std::nth_element(sorted.begin(), sorted.begin() + (r - 1), sorted.end(), std::greater<double>());
-        lead = 0.999 * sorted[(size_t)r - 1];
+        std::nth_element(h_norm.begin(), h_norm.begin() + (r - 1), h_norm.end(), std::greater<double>());
+        const double nr = h_norm[(size_t)r - 1];
+        lead = 0.999 * nr * nr;
     }
-    if (dtype == SALS_BF16)
-        hipLaunchKernelGGL((calib_select_kernel<bf16_t>), dim3(D), dim3(kCalThreads), 0, st, C, lam, sgn, D, r, eigval,
-                           static_cast<bf16_t*>(U));
-    else
-        hipLaunchKernelGGL((calib_select_kernel<float>), dim3(D), dim3(kCalThreads), 0, st, C, lam, sgn, D, r, eigval,
-                           static_cast<float*>(U));
+    // A matrix whose factor needed no rotation is diagonal (R R^T is diagonal for an upper triangular R only if R is): its
+    // own rows are the answer, without the detour through the square roots.
+    if (!rotated && !row_norms(C)) return SALS_ERR_HIP;
+#define SALS_SELECT(T, ROOT, M)                                                                                              \
+    hipLaunchKernelGGL((calib_select_kernel<T, ROOT>), dim3(D), dim3(kCalThreads), 0, st, M, norm, sgn, D, r, eigval,        \
+                       static_cast<T*>(U), C)
+    if (dtype == SALS_BF16) { if (rotated) SALS_SELECT(bf16_t, true, G); else SALS_SELECT(bf16_t, false, C); }
+    else { if (rotated) SALS_SELECT(float, true, G); else SALS_SELECT(float, false, C); }
+#undef SALS_SELECT
     if (sweeps) *sweeps = converged ? done : -done;
     return launch_status();
 }
