@@ -111,8 +111,9 @@ constexpr int kCalPanel = 64;
 
 // Panel at row k0: every workgroup factors the 64 x 64 diagonal block by itself (a row of it per four threads, the pivot
 // row passed through LDS, one barrier per pivot: 64 dependent steps are what the kernel takes, so repeating them beats
-// another launch) and then carries 256 columns of the panel through the triangular solve, one column per thread.  The
-// factored block goes to `diag` (other workgroups still read the original).  grid max(1, ceil((D - k0 - 64) / 256)).
+// another launch) and then carries 64 columns of the panel through the triangular solve, one column per thread of its first
+// wave (with a column on every thread the four waves' broadcast reads of the factor are bound by the LDS).  The
+// factored block goes to `diag` (other workgroups still read the original).  grid max(1, (D - k0 - 64) / 64).
 __global__ __launch_bounds__(256) void calib_chol_panel_kernel(double* __restrict__ G, int D, int k0, double thr,
                                                                double* __restrict__ diag)
 {
@@ -120,7 +121,7 @@ __global__ __launch_bounds__(256) void calib_chol_panel_kernel(double* __restric
     __shared__ double Rk[kCalPanel][kCalPanel + 1];
     __shared__ double invd[kCalPanel];
     const int tid = threadIdx.x, i = tid >> 2, j0 = (tid & 3) * 16;
-    const int c = k0 + kCalPanel + blockIdx.x * 256 + tid;
+    const int c = k0 + kCalPanel + blockIdx.x * 64 + tid;
     double a[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) a[e] = G[(size_t)(k0 + i) * D + k0 + j0 + e];
@@ -149,8 +150,8 @@ __global__ __launch_bounds__(256) void calib_chol_panel_kernel(double* __restric
         if (blockIdx.x == 0) diag[(size_t)(k0 + i) * kCalPanel + j0 + e] = a[e];
     }
     __syncthreads();
-    if (c >= D) return;
-    // forward substitution R_kk^T x = a, in steps of 16 rows so that the column's values stay in registers
+    if (tid >= 64 || c >= D) return;
+    // forward substitution R_kk^T x = a, the column's values in registers
     double x[kCalPanel];
 #pragma unroll
     for (int k = 0; k < kCalPanel; ++k) x[k] = G[(size_t)(k0 + k) * D + c];
@@ -223,14 +224,23 @@ __global__ __launch_bounds__(256) void calib_jacobi_gram_kernel(const double* __
     f64x4 acc[3];
 #pragma unroll
     for (int t = 0; t < 3; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 2
-    for (int c = wave * 16; c < slice_cols; c += 64) {
-        const f64x4 a = *reinterpret_cast<const f64x4*>(gp + c), b = *reinterpret_cast<const f64x4*>(gq + c);
+    for (int c = wave * 16; c < slice_cols; c += 128) {  // two groups requested together, the second from a clamped column
+        f64x4 a[2], b[2];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            acc[0] = mma_f64(a[e], a[e], acc[0]);
-            acc[1] = mma_f64(a[e], b[e], acc[1]);
-            acc[2] = mma_f64(b[e], b[e], acc[2]);
+        for (int u = 0; u < 2; ++u) {
+            a[u] = *reinterpret_cast<const f64x4*>(gp + min(c + 64 * u, slice_cols - 16));
+            b[u] = *reinterpret_cast<const f64x4*>(gq + min(c + 64 * u, slice_cols - 16));
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (c + 64 * u < slice_cols) {  // uniform
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    acc[0] = mma_f64(a[u][e], a[u][e], acc[0]);
+                    acc[1] = mma_f64(a[u][e], b[u][e], acc[1]);
+                    acc[2] = mma_f64(b[u][e], b[u][e], acc[2]);
+                }
+            }
         }
     }
     // the waves' sums, added in wave order
@@ -253,37 +263,54 @@ __global__ __launch_bounds__(256) void calib_jacobi_gram_kernel(const double* __
     }
 }
 
+// 1 / sqrt(x) for normal x: the hardware's estimate and one third-order step (full precision)
+__device__ __forceinline__ double jac_rsqrt(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x), e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
 // cosine and sine of the rotation (g_p, g_q) -> (c g_p - s g_q, s g_p + c g_q) that makes two rows with squared norms aa,
 // bb and inner product ab orthogonal, by the smaller angle: with h = sqrt((bb-aa)^2 + 4 ab^2) the double angle has
 // cosine |bb-aa| / h and sine 2 |ab| / h, so two reciprocal square roots do.  Rows that stand for a zero eigenvalue
 // (squared norm at most floor) and rows orthogonal to working precision are left alone.
+__device__ __forceinline__ bool jac_open(double aa, double bb, double ab, double floor)
+{
+    return fmin(aa, bb) > floor && ab * ab > 1e-30 * (aa * bb);
+}
 __device__ __forceinline__ bool jac_rotation(double aa, double bb, double ab, double floor, double* c, double* s)
 {
-    const bool ok = fmin(aa, bb) > floor && ab * ab > 1e-30 * (aa * bb);
-    const double d = bb - aa, hi = rsqrt(d * d + 4.0 * ab * ab);
-    const double c2 = 0.5 + 0.5 * fabs(d) * hi, ci = rsqrt(c2);
-    const double sn = (d >= 0.0 ? ab : -ab) * hi * ci;
+    const bool ok = jac_open(aa, bb, ab, floor);
+    const double d = bb - aa, hi = jac_rsqrt(fma(d, d, 4.0 * ab * ab));
+    const double c2 = fma(0.5 * fabs(d), hi, 0.5), ci = jac_rsqrt(c2);
     *c = ok ? c2 * ci : 1.0;
-    *s = ok ? sn : 0.0;
+    *s = ok ? (d >= 0.0 ? ab : -ab) * hi * ci : 0.0;
     return ok;
+}
+// (non-negative doubles are ordered like their bits; nothing waits for the result)
+__device__ __forceinline__ void conv_max(double* at, double v)
+{
+    atomicMax(reinterpret_cast<unsigned long long*>(at), (unsigned long long)__double_as_longlong(v));
 }
 
 // Rotates the rows of the step's block pairs.  Workgroup (slice, pair) adds up the pair's partial Gram matrices, runs the
-// rotations on the 32 x 32 Gram matrix in LDS (16 rounds of 16 disjoint pairs: every row of P with every row of Q; in the
+// rotations on the 32 x 32 Gram matrix (16 rounds of 16 disjoint pairs: every row of P with every row of Q; in the
 // sweep's first step 15 rounds more, the pairs inside the blocks) while accumulating them into a 32 x 32 matrix, and
 // applies that to its slice of the columns on the matrix cores.  Every slice repeats the small problem (the same
-// numbers): a launch between the two would cost more than its 16 dependent rounds.  Thread (i, j) of a round rotates the
-// 2 x 2 block of row pair i and column pair j from one LDS buffer into the other: one barrier per round.
-// conv[pair] keeps the largest |tan| of a rotation, since the host cleared it, that involved a row of squared norm >=
+// numbers): a launch between the two would cost more than its 16 dependent rounds.  In a round thread (i, j) rotates the
+// 2 x 2 block of row pair i and column pair j; what the next round's threads need passes through one of two LDS buffers
+// (one barrier per round), what belongs to a row of P stays with its thread.  A round is a chain of LDS reads, two
+// reciprocal square roots and LDS writes, bound by instruction issue of the one wave per SIMD.
+// (The rounds in fp32, with the accumulated matrix re-orthogonalised in fp64, were no faster: 0.5 against 0.6 us a round.)
+// conv[pair] keeps the largest |sin| of a rotation, since the host cleared it, that involved a row of squared norm >=
 // lead (the rows that can still change a leading eigenvector).
 __global__ __launch_bounds__(256) void calib_jacobi_rotate_kernel(double* __restrict__ G, int D, int step, int slice_cols,
                                                                   const double* __restrict__ part, int n_part, double floor,
                                                                   double lead, double* __restrict__ conv)
 {
-    constexpr int B2 = 2 * kJacB, LD = B2 + 1;
-    __shared__ double Wb[2][B2 * LD], Qb[2][B2 * LD];
-    __shared__ double s_conv[kJacB];
-    __shared__ int s_any;
+    constexpr int B2 = 2 * kJacB, LD = B2 + 1, LB = kJacB + 1;
+    __shared__ double Wb[2][B2 * LD], Qb[2][B2 * LD];   // Gram matrix and accumulated rotations
+    __shared__ double s_diag[B2], s_conv[kJacB];
+    __shared__ int s_any[2];
     int p, q;
     calib_pair(D / kJacB, step, blockIdx.y, &p, &q);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, kg = lane >> 4;
@@ -310,46 +337,34 @@ __global__ __launch_bounds__(256) void calib_jacobi_rotate_kernel(double* __rest
         }
     };
     load_tiles(wave * 16);
+    const int i = tid >> 4, j = tid & 15;
+    if (tid < 2) s_any[tid] = 0;
+    double v[3];
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
-        double v = 0.0;
+        v[t] = 0.0;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v += u < n_part ? w8[t][u] : 0.0;
-        const int r = (tid >> 4) + (t == 2 ? kJacB : 0), c = (tid & 15) + (t >= 1 ? kJacB : 0);
-        Wb[0][r * LD + c] = v;
-        if (t == 1) Wb[0][c * LD + r] = v;
+        for (int u = 0; u < 8; ++u) v[t] += u < n_part ? w8[t][u] : 0.0;
+        const int r = i + (t == 2 ? kJacB : 0), c = j + (t >= 1 ? kJacB : 0);
+        Wb[0][r * LD + c] = v[t];
+        if (t == 1) Wb[0][c * LD + r] = v[t];
+        if (r == c) s_diag[r] = v[t];
     }
     for (int e = tid; e < B2 * B2; e += 256) Qb[0][(e >> 5) * LD + (e & 31)] = (e >> 5) == (e & 31) ? 1.0 : 0.0;
-    if (tid == 0) s_any = 0;
     __syncthreads();
+    // nothing to rotate (most pairs of the last sweeps): the rounds would leave everything as it is
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        const int r = i + (t == 2 ? kJacB : 0), c = j + (t >= 1 ? kJacB : 0);
+        if (r != c && (t == 1 || step == 0) && jac_open(s_diag[r], s_diag[c], v[t], floor)) s_any[0] = 1;
+    }
+    __syncthreads();
+    if (!s_any[0]) return;  // uniform, and the same in every slice of the pair
 
-    const int i = tid >> 4, j = tid & 15;
-    double tmax = 0.0;
+    double smax = 0.0;
     bool any = false;
     int cur = 0;
-    auto round = [&](int pi, int qi, int pj, int qj) {
-        const double* W = Wb[cur]; const double* Q = Qb[cur];
-        double* Wn = Wb[cur ^ 1]; double* Qn = Qb[cur ^ 1];
-        const double aa = W[pi * LD + pi], bb = W[qi * LD + qi], ab = W[pi * LD + qi];
-        const double aj = W[pj * LD + pj], bj = W[qj * LD + qj], abj = W[pj * LD + qj];
-        const double b00 = W[pi * LD + pj], b01 = W[pi * LD + qj], b10 = W[qi * LD + pj], b11 = W[qi * LD + qj];
-        const double x0 = Q[pi * LD + j], y0 = Q[qi * LD + j], x1 = Q[pi * LD + j + kJacB], y1 = Q[qi * LD + j + kJacB];
-        double c, s, cj, sj;
-        const bool ok = jac_rotation(aa, bb, ab, floor, &c, &s);
-        jac_rotation(aj, bj, abj, floor, &cj, &sj);
-        any |= ok;
-        if (ok && fmax(aa, bb) >= lead) tmax = fmax(tmax, fabs(s) / c);
-        const double r00 = c * b00 - s * b10, r01 = c * b01 - s * b11, r10 = s * b00 + c * b10, r11 = s * b01 + c * b11;
-        Wn[pi * LD + pj] = cj * r00 - sj * r01;
-        Wn[pi * LD + qj] = sj * r00 + cj * r01;
-        Wn[qi * LD + pj] = cj * r10 - sj * r11;
-        Wn[qi * LD + qj] = sj * r10 + cj * r11;
-        Qn[pi * LD + j] = c * x0 - s * y0; Qn[qi * LD + j] = s * x0 + c * y0;
-        Qn[pi * LD + j + kJacB] = c * x1 - s * y1; Qn[qi * LD + j + kJacB] = s * x1 + c * y1;
-        __syncthreads();
-        cur ^= 1;
-    };
-    if (step == 0) {
+    if (step == 0) {  // the pairs inside the blocks, on whole matrices
         auto inside = [&](int t, int k, int* a, int* b) {  // pair k of round t: k < 8 inside P, otherwise inside Q
             calib_pair(kJacB, t, k & 7, a, b);
             *a += k < 8 ? 0 : kJacB; *b += k < 8 ? 0 : kJacB;
@@ -358,24 +373,86 @@ __global__ __launch_bounds__(256) void calib_jacobi_rotate_kernel(double* __rest
             int pi, qi, pj, qj;
             inside(t, i, &pi, &qi);
             inside(t, j, &pj, &qj);
-            round(pi, qi, pj, qj);
+            const double* W = Wb[cur]; const double* Q = Qb[cur];
+            double* Wn = Wb[cur ^ 1]; double* Qn = Qb[cur ^ 1];
+            const double aa = W[pi * LD + pi], bb = W[qi * LD + qi];
+            const double b00 = W[pi * LD + pj], b01 = W[pi * LD + qj], b10 = W[qi * LD + pj], b11 = W[qi * LD + qj];
+            const double x0 = Q[pi * LD + j], y0 = Q[qi * LD + j], x1 = Q[pi * LD + j + kJacB], y1 = Q[qi * LD + j + kJacB];
+            double c, s, cj, sj;
+            const bool ok = jac_rotation(aa, bb, W[pi * LD + qi], floor, &c, &s);
+            jac_rotation(W[pj * LD + pj], W[qj * LD + qj], W[pj * LD + qj], floor, &cj, &sj);
+            any |= ok;
+            smax = fmax(aa, bb) >= lead ? fmax(smax, fabs(s)) : smax;
+            const double r00 = c * b00 - s * b10, r01 = c * b01 - s * b11, r10 = s * b00 + c * b10, r11 = s * b01 + c * b11;
+            Wn[pi * LD + pj] = cj * r00 - sj * r01;
+            Wn[pi * LD + qj] = sj * r00 + cj * r01;
+            Wn[qi * LD + pj] = cj * r10 - sj * r11;
+            Wn[qi * LD + qj] = sj * r10 + cj * r11;
+            Qn[pi * LD + j] = c * x0 - s * y0; Qn[qi * LD + j] = s * x0 + c * y0;
+            Qn[pi * LD + j + kJacB] = c * x1 - s * y1; Qn[qi * LD + j + kJacB] = s * x1 + c * y1;
+            __syncthreads();
+            cur ^= 1;
         }
     }
-    for (int t = 0; t < kJacB; ++t) round(i, kJacB + ((i + t) & 15), j, kJacB + ((j + t) & 15));
-    if (j == 0) s_conv[i] = tmax;
-    if (any) s_any = 1;
+    // every row of P with every row of Q: round t pairs row i of P with row (i + t) mod 16 of Q
+    const double* Qd;
+    {
+        double b00 = Wb[cur][i * LD + j];
+        double x0 = Qb[cur][i * LD + j], x1 = Qb[cur][i * LD + j + kJacB];
+        const double b01 = Wb[cur][i * LD + kJacB + j], b11 = Wb[cur][(kJacB + i) * LD + kJacB + j];
+        const double y0 = Qb[cur][(kJacB + i) * LD + j], y1 = Qb[cur][(kJacB + i) * LD + j + kJacB];
+        // the two buffers: (P,Q) block [16][17], (Q,Q) block [16][17], diagonal of P [16], accumulated rows of Q [16][33]
+        constexpr int kPQ = 0, kQQ = kJacB * LB, kDP = 2 * kJacB * LB, kAcc = kDP + kJacB, kBuf = kAcc + kJacB * LD;
+        __shared__ double buf0[2 * kBuf];
+        buf0[kPQ + i * LB + j] = b01;
+        buf0[kQQ + i * LB + j] = b11;
+        if (i == j) buf0[kDP + i] = b00;
+        buf0[kAcc + i * LD + j] = y0; buf0[kAcc + i * LD + j + kJacB] = y1;
+        __syncthreads();
+#pragma unroll 2
+        for (int t = 0; t < kJacB; ++t) {
+            const double* R = buf0 + (t & 1) * kBuf;
+            double* N = buf0 + ((t & 1) ^ 1) * kBuf;
+            const int qi = (i + t) & 15, qj = (j + t) & 15;
+            const double aa = R[kDP + i], bb = R[kQQ + qi * (LB + 1)], ab = R[kPQ + i * LB + qi];
+            const double aj = R[kDP + j], bj = R[kQQ + qj * (LB + 1)], abj = R[kPQ + j * LB + qj];
+            const double w01 = R[kPQ + i * LB + qj], w10 = R[kPQ + j * LB + qi], w11 = R[kQQ + qi * LB + qj];
+            const double v0 = R[kAcc + qi * LD + j], v1 = R[kAcc + qi * LD + j + kJacB];
+            double c, s, cj, sj;
+            any |= jac_rotation(aa, bb, ab, floor, &c, &s);
+            jac_rotation(aj, bj, abj, floor, &cj, &sj);
+            smax = fmax(aa, bb) >= lead ? fmax(smax, fabs(s)) : smax;
+            const double r00 = c * b00 - s * w10, r01 = c * w01 - s * w11, r10 = s * b00 + c * w10, r11 = s * w01 + c * w11;
+            b00 = cj * r00 - sj * r01;
+            N[kPQ + i * LB + qj] = sj * r00 + cj * r01;
+            N[kQQ + qi * LB + qj] = sj * r10 + cj * r11;
+            if (i == j) N[kDP + i] = b00;
+            N[kAcc + qi * LD + j] = s * x0 + c * v0; N[kAcc + qi * LD + j + kJacB] = s * x1 + c * v1;
+            x0 = c * x0 - s * v0; x1 = c * x1 - s * v1;
+            __syncthreads();
+        }
+        // the accumulated rotations as one 32 x 32 matrix
+        double* const Qo = &Qb[0][0];
+        const double* R = buf0;  // (an even number of rounds)
+        static_assert(kJacB % 2 == 0, "the last round wrote the first buffer");
+        Qo[i * LD + j] = x0; Qo[i * LD + j + kJacB] = x1;
+        Qo[(kJacB + i) * LD + j] = R[kAcc + i * LD + j]; Qo[(kJacB + i) * LD + j + kJacB] = R[kAcc + i * LD + j + kJacB];
+        Qd = Qo;
+    }
+    if (j == 0) s_conv[i] = smax;
+    if (any) s_any[1] = 1;
     __syncthreads();
-    if (!s_any) return;  // uniform, and the same in every slice of the pair
+    if (!s_any[1]) return;  // uniform
     if (tid == 0 && blockIdx.x == 0) {
-        double v = conv[blockIdx.y];
-        for (int k = 0; k < kJacB; ++k) v = fmax(v, s_conv[k]);
-        conv[blockIdx.y] = v;
+        double m = 0.0;
+        for (int k = 0; k < kJacB; ++k) m = fmax(m, s_conv[k]);
+        conv_max(conv + blockIdx.y, m);
     }
     double qa[2][8];  // the accumulated rotations as MFMA operand: rows m 16 .. +16, contraction step s
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int s = 0; s < 8; ++s) qa[m][s] = Qb[cur][(m * 16 + l16) * LD + 4 * s + kg];
+        for (int s = 0; s < 8; ++s) qa[m][s] = Qd[(m * 16 + l16) * LD + 4 * s + kg];
     for (int c0 = wave * 16; c0 < slice_cols; c0 += 128) {
         if (c0 != wave * 16) load_tiles(c0);
         f64x4 acc[2][2];

@@ -1515,7 +1515,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         if (hipMemcpyAsync(G, C, (size_t)D * D * 8, hipMemcpyDeviceToDevice, st) != hipSuccess) return SALS_ERR_HIP;
         for (int k0 = 0; k0 < D; k0 += kCalPanel) {
             const int rest = D - k0 - kCalPanel;
-            hipLaunchKernelGGL(calib_chol_panel_kernel, dim3(std::max(1, ceil_div(rest, 256))), dim3(256), 0, st, G, D, k0,
+            hipLaunchKernelGGL(calib_chol_panel_kernel, dim3(std::max(1, rest / 64)), dim3(256), 0, st, G, D, k0,
                                1e-14 * n0, diag);
             if (rest > 0)
                 hipLaunchKernelGGL(calib_chol_update_kernel, dim3(rest / 64, rest / 64), dim3(256), 0, st, G, D, k0);
