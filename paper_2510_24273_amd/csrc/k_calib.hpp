@@ -1,9 +1,10 @@
 // Offline calibration (Sec. 4.2): covariance of the calibration keys, C = K^T K, and its leading eigenvectors.
 //
-//   covariance   The contraction runs over the tokens, the axis along which the keys are NOT contiguous.  The keys of
-//                a chunk are therefore transposed once (calib_transpose_kernel, a plain LDS tile transpose) and the
-//                product is then the row-by-row form the matrix-core GEMM of the prompt compression computes,
-//                C += K^T (K^T)^T, with fp32 tile sums added to the fp64 matrix per chunk.
+//   covariance   The contraction runs over the tokens, the axis along which the keys are NOT contiguous.  bf16: token rows
+//                go to LDS as they lie and the matrix operands come out of transposing LDS reads (calib_cov_kernel).
+//                fp32: the keys of a chunk are transposed once (calib_transpose_kernel, a plain LDS tile transpose) and
+//                the product is then the row-by-row form the matrix-core GEMM of the prompt compression computes,
+//                C += K^T (K^T)^T.  Either way fp32 tile sums over at most 4096 tokens are added to the fp64 matrix.
 //   eigenvectors One-sided Jacobi on the rows of G = R, the Cholesky factor of C = R^T R: a plane rotation of rows p, q
 //                makes them orthogonal.  With J the product of all rotations, G = J R keeps G^T G = C; once all rows are
 //                orthogonal, the normalised rows are eigenvectors of C and the squared row norms the eigenvalues, so no
@@ -18,6 +19,7 @@
 //                that are zero to working precision and are left alone.
 #pragma once
 #include "common.hpp"
+#include "k_gemm.hpp"
 
 namespace sals {
 
@@ -52,6 +54,204 @@ __global__ __launch_bounds__(256) void calib_transpose_kernel(const T* __restric
         const long long t = t0 + tx;
         if (d < D && t < n_pad) XT[(size_t)d * n_pad + t] = tile[tx][ty + i];
     }
+}
+
+// Covariance of bf16 keys, C += X^T X, as tiles of 256 x 256 of the upper triangle: P[slice][tile] = the fp32 tile sums over
+// one slice of the tokens (at most 4096 of them).  grid (tiles * slices), 512 threads, one workgroup per compute unit.
+// Matrix-bound: 1.1 PFLOP/s sustained at D = 4096, 32768 tokens (529 us for 1088 items of 0.54 GFLOP), what the chip's
+// power leaves of its rate on such operands (cutting the last, partly filled round into quarter items changed nothing).
+// With the addition below 633 us; a transposing copy of the keys, 256 x 128 tiles staged through registers and an
+// addition per 4096 tokens took 1395 us.
+//
+// The contraction runs over the tokens, the axis along which the keys are not contiguous: token rows go to LDS as they
+// lie in memory (32 tokens x 256 columns for either side, 16 bytes per lane without passing through registers, four
+// stages) and the MFMA operands are read with the transposing LDS read.  64-byte pieces of a row are stored at their
+// index XOR a number made of token bits that differ among the eight rows one read touches: no bank conflicts.
+// Eight waves of 128 x 64: while the MFMAs of one half step (16 tokens) run, the fragments of the next are read; one
+// barrier per 32 tokens, which also publishes the step after, and the loads of the step three ahead are issued behind it.
+constexpr int kCovTile = 256, kCovStep = 32, kCovStages = 4;
+constexpr int kCovSide = kCovStep * kCovTile * 2;              // bytes of one operand's stage
+constexpr size_t kCovLds = (size_t)kCovStages * 2 * kCovSide;  // 128 KB
+__device__ u32x4 g_cov_zero;                                   // stands in for tokens past the end
+
+__device__ __forceinline__ void cov_tile(int id, int nt, int* row, int* col)  // tiles of the upper triangle, row by row
+{
+    int r = 0;
+    while (id >= nt - r) { id -= nt - r; ++r; }
+    *row = r; *col = r + id;
+}
+
+__global__ __launch_bounds__(512, 2) void calib_cov_kernel(const bf16_t* __restrict__ X, long long n_tok, int D, int nt,
+                                                           int slice_tok, int slices, float* __restrict__ P)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];  // [stage][A | B]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, hi = lane >> 5;
+    const int wm = wave >> 2, wn = wave & 3;
+    // consecutive ids go to different XCDs: each XCD takes a run of the list (slice slowest), so the tiles that share token
+    // rows meet in its L2
+    int tile, slice;
+    {
+        const int n_tiles = nt * (nt + 1) / 2, total = n_tiles * slices;
+        const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds, qn = total / kXcds, rem = total % kXcds;
+        const int w = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + slot;
+        slice = w / n_tiles; tile = w - slice * n_tiles;
+    }
+    int tr, tc;
+    cov_tile(tile, nt, &tr, &tc);
+    const long long t_begin = (long long)slice * slice_tok;
+    const int n_live = (int)min((long long)slice_tok, n_tok - t_begin);   // tokens of this slice (the host gives it some)
+    const int n_steps = (n_live + kCovStep - 1) / kCovStep;
+
+    // This wave's share of a stage: two pieces of 1 KB (two token rows) of either operand.  Lane -> token lane / 32 of the
+    // pair, position lane % 32 of 16 bytes.
+    const uint32_t lds0 = lds_offset(lds);
+    const unsigned char* src[2][2];
+    int tok_in_step[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int t = (wave * 2 + u) * 2 + hi;                       // token within the step
+        const int f = (t & 3) | ((t >> 3) & 1) << 2;
+        const int piece = (((l32 >> 2) ^ f) << 2) | (l32 & 3);       // 16-byte piece of the tile row that lies at position l32
+        tok_in_step[u] = t;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int col = min((s ? tc : tr) * kCovTile + piece * 8, D - 8);  // (columns past D: computed, never used)
+            src[u][s] = reinterpret_cast<const unsigned char*>(X + (size_t)t_begin * D + col);
+        }
+    }
+    const size_t row_bytes = (size_t)D * 2;
+    auto load_step = [&](int step) {
+        const int sc = min(step, n_steps - 1);                       // (past the end: a step that nothing reads any more)
+        const uint32_t st = lds0 + (uint32_t)(step & (kCovStages - 1)) * (2 * kCovSide);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int t = sc * kCovStep + tok_in_step[u];
+            const bool in = t < n_live;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const void* p = in ? static_cast<const void*>(src[u][s] + (size_t)t * row_bytes) : static_cast<const void*>(&g_cov_zero);
+                load_lds16(p, st + s * kCovSide + (wave * 2 + u) * 1024);
+            }
+        }
+    };
+
+    // fragment addresses: 32 columns (one 64-byte slot of a row) x 16 tokens; lane -> column l32, tokens 8 hi .. 8 hi + 7
+    const int tt = (lane & 15) >> 2, cc = lane & 3, half = (lane >> 4) & 1;
+    const int f = tt | hi << 2;
+    uint32_t a_at[4], b_at[2];
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb) a_at[mb] = (hi * 8 + tt) * 512 + (((wm * 4 + mb) ^ f) << 6) + half * 32 + cc * 8;
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) b_at[nb] = kCovSide + (hi * 8 + tt) * 512 + (((wn * 2 + nb) ^ f) << 6) + half * 32 + cc * 8;
+    struct Frags { u32x4 a[4], b[2]; };
+    auto frag = [&](uint32_t at) {
+        const s16x4 x = lds_read_tr(lds + at), y = lds_read_tr(lds + at + 4 * 512);
+        const uint2 lo = __builtin_bit_cast(uint2, x), up = __builtin_bit_cast(uint2, y);
+        return u32x4{lo.x, lo.y, up.x, up.y};
+    };
+    auto read_frags = [&](Frags& F, int stage, int ks) {
+        const uint32_t o = stage * (2 * kCovSide) + ks * (16 * 512);
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) F.b[nb] = frag(b_at[nb] + o);
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb) F.a[mb] = frag(a_at[mb] + o);
+    };
+    f32x16 acc[4][2];
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[mb][nb][v] = 0.f;
+    auto mma_frags = [&](const Frags& F) {
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) mma_op<bf16_t>::run(F.a[mb], F.b[nb], acc[mb][nb]);
+    };
+
+    load_step(0); load_step(1); load_step(2);
+    vm_wait<8>();
+    wg_barrier();
+    Frags F0, F1;
+    read_frags(F0, 0, 0);
+    for (int s0 = 0; s0 < n_steps; s0 += kCovStages) {
+#pragma unroll
+        for (int u = 0; u < kCovStages; ++u) {
+            if (s0 + u < n_steps) {  // uniform
+                // steps up to s + 1 have landed, everywhere; every wave is done with step s - 1
+                vm_wait<4>();
+                wg_barrier();
+                load_step(s0 + u + 3);
+                read_frags(F1, u, 1);
+                mma_frags(F0);
+                read_frags(F0, (u + 1) & (kCovStages - 1), 0);
+                mma_frags(F1);
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+                        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // LDS reads
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    }
+            }
+        }
+    }
+    vm_wait<0>();  // (no load may land in LDS that another workgroup has been given)
+
+    float* out = P + ((size_t)slice * (nt * (nt + 1) / 2) + tile) * (kCovTile * kCovTile);
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int r = wm * 128 + mb * 32 + (v >> 2) * 8 + hi * 4 + (v & 3);
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb)
+                __builtin_nontemporal_store(acc[mb][nb][v], out + r * kCovTile + wn * 64 + nb * 32 + l32);
+        }
+}
+
+// C[i, j] += sum over the slices of P[slice][tile][i, j] in slice order, in fp64, for i <= j, and the same value to C[j, i].
+// One workgroup per 32 x 32 block of the upper triangle's tiles; grid (64, tiles).  A stream: 486 MB in 101 us at D = 4096
+// and eight slices.
+__global__ __launch_bounds__(256) void calib_cov_reduce_kernel(double* __restrict__ C, const float* __restrict__ P, int D, int nt,
+                                                               int slices)
+{
+    __shared__ double t[32][33];
+    int tr, tc;
+    cov_tile(blockIdx.y, nt, &tr, &tc);
+    const int bi = blockIdx.x >> 3, bj = blockIdx.x & 7;
+    const int i0 = tr * kCovTile + bi * 32, j0 = tc * kCovTile + bj * 32;
+    if (i0 >= D || j0 >= D || j0 < i0) return;  // uniform
+    const int tx = threadIdx.x & 7, ty = threadIdx.x >> 3;  // four columns of one row per thread
+    const float* src = P + (size_t)blockIdx.y * (kCovTile * kCovTile) + (bi * 32 + ty) * kCovTile + bj * 32 + tx * 4;
+    const size_t stride = (size_t)gridDim.y * (kCovTile * kCovTile);
+    double* dst = C + (size_t)(i0 + ty) * D + j0 + tx * 4;
+    double s[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] = 0.0;
+    for (int z0 = 0; z0 < slices; z0 += 8) {  // eight slices requested together, from clamped slice numbers
+        f32x4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = ld16_f32_stream(src + (size_t)min(z0 + u, slices - 1) * stride);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (z0 + u < slices) { s[0] += (double)v[u].x; s[1] += (double)v[u].y; s[2] += (double)v[u].z; s[3] += (double)v[u].w; }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const double c = dst[e] + s[e];
+        t[ty][tx * 4 + e] = c;
+        if (i0 < j0 || ty <= tx * 4 + e) dst[e] = c;
+    }
+    __syncthreads();
+    double* mir = C + (size_t)(j0 + ty) * D + i0 + tx * 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (i0 < j0 || ty > tx * 4 + e) mir[e] = t[tx * 4 + e][ty];
 }
 
 // C[i, j] += sum over the slices of P[slice][i, j], for the elements the covariance kernel computed: those of the

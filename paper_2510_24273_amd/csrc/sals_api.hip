@@ -1405,6 +1405,44 @@ sals_status calib_accumulate_t(const void* K, int64_t n_tok, int D, double* C, v
     return launch_status();
 }
 
+int cov_tiles(int D) { const int nt = ceil_div(D, kCovTile); return nt * (nt + 1) / 2; }
+// bf16 keys: slices of the token axis per launch at most (each a separate fp32 output over at most 4096 tokens), so that the
+// tile sums of a launch stay near 280 MB
+int cov_max_slices(int D) { return std::min(64, std::max(2, 1088 / cov_tiles(D))); }
+// ... and of a launch over n tokens: the number with the smallest estimated duration in us (rounds of one workgroup per
+// compute unit, 0.95 us per 32 tokens, 8 us to start and to store a tile; 0.05 us to add a tile up)
+int cov_slices(int D, int64_t n)
+{
+    const int tiles = cov_tiles(D), lo = (int)((n + kCalChunk - 1) / kCalChunk);
+    const int64_t steps = (n + kCovStep - 1) / kCovStep;
+    int best = lo;
+    double best_us = 1e30;
+    for (int s = lo; s <= cov_max_slices(D) && s <= steps; ++s) {
+        const double us = (double)ceil_div(tiles * s, 256) * ((double)((steps + s - 1) / s) * 0.95 + 8.0) + 0.05 * tiles * s;
+        if (us < best_us) { best_us = us; best = s; }
+    }
+    return best;
+}
+sals_status calib_accumulate_bf16(const void* K, int64_t n_tok, int D, double* C, void* ws, hipStream_t st)
+{
+    const bf16_t* X = static_cast<const bf16_t*>(K);
+    float* P = static_cast<float*>(ws);
+    const int nt = ceil_div(D, kCovTile), tiles = cov_tiles(D);
+    const int64_t most = kCalChunk * cov_max_slices(D);
+    for (int64_t t0 = 0; t0 < n_tok; t0 += most) {
+        const int64_t n = std::min(most, n_tok - t0);
+        const int64_t steps = (n + kCovStep - 1) / kCovStep;
+        const int want = cov_slices(D, n);
+        const int slice_tok = (int)((steps + want - 1) / want) * kCovStep;   // (at most 4096: want >= n / 4096)
+        const int slices = (int)((n + slice_tok - 1) / slice_tok);
+        hipLaunchKernelGGL(calib_cov_kernel, dim3(tiles * slices), dim3(512), kCovLds, st, X + (size_t)t0 * D, (long long)n, D, nt,
+                           slice_tok, slices, P);
+        hipLaunchKernelGGL(calib_cov_reduce_kernel, dim3(64, tiles), dim3(256), 0, st, C, P, D, nt, slices);
+        if (launch_status() != SALS_OK) return SALS_ERR_HIP;
+    }
+    return SALS_OK;
+}
+
 template <typename T> sals_status calib_lds_attr()
 {
     static std::mutex m;
@@ -1413,7 +1451,11 @@ template <typename T> sals_status calib_lds_attr()
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SALS_ERR_HIP;
     std::lock_guard<std::mutex> lock(m);
     if (done[dev]) return SALS_OK;
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(prefill_compress_kernel<T, 256, 128, true>),
+    if constexpr (sizeof(T) == 2) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(calib_cov_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)kCovLds) != hipSuccess)
+            return SALS_ERR_HIP;
+    } else if (hipFuncSetAttribute(reinterpret_cast<const void*>(prefill_compress_kernel<T, 256, 128, true>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)prefill_lds_bytes(256, 128)) != hipSuccess ||
         hipFuncSetAttribute(reinterpret_cast<const void*>(prefill_compress_kernel<T, 128, 128, true>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)prefill_lds_bytes(128, 128)) != hipSuccess)
@@ -1428,6 +1470,7 @@ extern "C" {
 size_t sals_calib_accumulate_workspace_bytes(int32_t dtype, int32_t D)
 {
     if ((dtype != SALS_BF16 && dtype != SALS_F32) || D < 128 || D % 128 != 0 || D > kCalMaxD) return 0;
+    if (dtype == SALS_BF16) return align_up((size_t)cov_tiles(D) * cov_max_slices(D) * kCovTile * kCovTile * 4);  // tile sums
     // the transposed keys of a chunk, then the fp32 tile sums of its slices
     return align_up((size_t)D * kCalChunk * cal_es(dtype)) + align_up((size_t)cal_slices(D) * D * D * 4);
 }
@@ -1443,7 +1486,7 @@ sals_status sals_calib_accumulate(int32_t dtype, const void* K, int64_t n_tok, i
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (dtype == SALS_BF16) {
         if (calib_lds_attr<bf16_t>() != SALS_OK) return SALS_ERR_HIP;
-        return calib_accumulate_t<bf16_t>(K, n_tok, D, C, workspace, st);
+        return calib_accumulate_bf16(K, n_tok, D, C, workspace, st);
     }
     if (calib_lds_attr<float>() != SALS_OK) return SALS_ERR_HIP;
     return calib_accumulate_t<float>(K, n_tok, D, C, workspace, st);

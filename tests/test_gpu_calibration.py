@@ -50,6 +50,24 @@ def test_covariance_matches_the_oracle(dtype, D, n):
     _check_cov(C, X)
 
 
+@pytest.mark.parametrize("D,n", [(384, 33), (128, 4097), (1152, 31), (8192, 8250)])
+def test_covariance_tile_and_slice_remainders(D, n):
+    """Widths that are no whole number of tiles, token counts one past a step or a slice, more tokens than one launch
+    takes; against fp64 products on the device."""
+    print(f"[case] covariance remainders D={D} n={n}", flush=True)
+    g = torch.Generator(device=gu.DEV)
+    g.manual_seed(D + n)
+    X = torch.randn(n, D, generator=g, device=gu.DEV, dtype=torch.bfloat16)
+    C = torch.randn(D, D, generator=g, device=gu.DEV, dtype=torch.float64)
+    want = torch.triu(C)
+    want = want + torch.triu(want, 1).T + X.double().T.contiguous() @ X.double()
+    ws = binding.calib_accumulate(X, C)
+    torch.cuda.synchronize()
+    dg = want.diagonal().abs().sqrt()
+    assert bool(((C - want).abs() <= 2e-5 * torch.outer(dg, dg) + 1e-9).all())
+    assert torch.equal(C, C.T)
+
+
 def test_covariance_accumulates_over_calls():
     print("[case] covariance in two calls", flush=True)
     X = synth.make_calibration_keys(7, 6000, 256, "bf16", decay=0.95)
