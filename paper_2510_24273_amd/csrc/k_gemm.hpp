@@ -12,6 +12,11 @@ __device__ __forceinline__ void load_lds16(const void* src, uint32_t lds_base)
 {
     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(src) : "memory");
 }
+// the same from a wave-uniform base and a 32-bit offset per lane
+__device__ __forceinline__ void load_lds16(const void* base, uint32_t offset, uint32_t lds_base)
+{
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(offset), "s"(base) : "memory");
+}
 template <int N> __device__ __forceinline__ void vm_wait() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 __device__ __forceinline__ void wg_barrier()
 {

@@ -13,8 +13,11 @@
 // to the third stage).  fp32 accumulation, one rounding to the storage type at the store, so a row
 // equals the one-token projection of the same token up to the order of the fp32 sum.
 #pragma once
+#include <type_traits>
+
 #include "common.hpp"
 #include "k_attend.hpp"
+#include "k_gemm.hpp"
 #include "k_logits.hpp"
 
 namespace sals {
@@ -182,6 +185,209 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_compress_kernel(Prefill
                     elem<T>::store(cache + (size_t)row * a.r + lat0 + wn * 64 + nb * 32 + l32, acc[mb][nb][v]);
             }
         }
+}
+
+// bf16 prompts: tiles of 128 NBT tokens x 64 NBW latent coordinates (NBT 1 | 2, NBW 1 .. 5), one workgroup per compute unit.
+// Both operands come straight from memory into LDS (64-byte steps of the D axis, four stages, 16-byte pieces at their index
+// XOR row bits) and eight waves of 32 NBT tokens x 32 NBW coordinates read the next half step's fragments under the current
+// one's MFMAs, one barrier per step.  The latent coordinates are the MFMA's rows, so a lane ends up with four consecutive
+// coordinates of a token and stores 8 bytes at a time.
+// Matrix-bound while the whole chip works (22 ns per MFMA and SIMD at the clock its power leaves, 13.4 with few workgroups);
+// what is lost to it is the last round of tiles and 7 to 10 us per round to start and store.  Against the 256 x 128 and
+// 128 x 128 tiles staged through registers, two workgroups per compute unit, that this replaced: 6 ragged prompts of up to
+// 4001 tokens, D = 1024, r = 640 91 -> 75 us; 6000 tokens, D = 4096, r = 1024 127 -> 100 us; 64 tokens, D = 4096 38 -> 15 us.
+// Tiles: without n_new the prompts of a batch are one run of B n_tok rows (a tile may span sequences); with n_new every
+// sequence has tiles of its own and only those that hold tokens are in the list (its length is known on the device only, so
+// the launch covers n_tok everywhere and the workgroups past the end leave at once).
+// One launch may take all tiles, or two launches share them: the first one (kPfBig) as many 256-row tiles as fill whole
+// rounds of the chip with its per_big workgroups each, the second one (kPfTail) the rest in smaller tiles, unless that rest
+// is more than tail_max row tiles (then the first launch takes them too).  Both derive the split from the token counts.
+enum { kPfAll = 0, kPfBig = 1, kPfTail = 2 };
+struct PfPart { int part, per_big, tail_max; };
+template <int NBW, int NBT> struct pf_cfg {
+    static constexpr int TN = 64 * NBW, TM = 128 * NBT;
+    static constexpr int A_BYTES = TN * kLgStep, B_BYTES = TM * kLgStep, STAGE = A_BYTES + B_BYTES;
+    static constexpr size_t LDS = 4 * (size_t)STAGE;
+    static constexpr int PIECES = TN / 16;   // 1 KB pieces of the projector side per step
+};
+template <int NBW, int NBT>
+__global__ __launch_bounds__(kPfThreads, 2) void prefill_tile_kernel(PrefillArgs a, int n_col, PfPart p)
+{
+    typedef pf_cfg<NBW, NBT> C;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];  // [stage][projector rows | token rows]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, hi = lane >> 5;
+    const int wm = wave >> 1, wn = wave & 1;   // token group, latent group
+
+    // ---- work list: (token tile, projection, latent tile), latent tile fastest; each XCD takes a run of it
+    const int per_tile = 2 * n_col;
+    int m0, m_end, proj, col;   // first row of the tile and end of its rows, in the run of B n_tok rows
+    {
+        const int unit = p.part == kPfAll ? C::TM : 256;   // rows the list counts in
+        int n_tiles, t0v = 0, t1v = 0, c0 = 0, c1 = 0;
+        if (a.n_new) {
+            const int n0 = lane < a.B ? min(max(a.n_new[lane], 0), a.n_tok) : 0;
+            const int n1 = lane + 64 < a.B ? min(max(a.n_new[lane + 64], 0), a.n_tok) : 0;
+            t0v = (n0 + unit - 1) / unit; t1v = (n1 + unit - 1) / unit;
+            c0 = (int)wave_incl_scan((uint32_t)t0v);
+            c1 = (int)wave_incl_scan((uint32_t)t1v) + __builtin_amdgcn_readlane(c0, 63);
+            n_tiles = __builtin_amdgcn_readlane(c1, 63);
+        } else {
+            n_tiles = (a.B * a.n_tok + unit - 1) / unit;
+        }
+        // the first launch of two takes whole rounds of the chip, the second one what is left, in its smaller tiles
+        constexpr int SUB = 256 / C::TM;
+        int first = 0, count = n_tiles;
+        if (p.part != kPfAll) {
+            int whole = n_tiles * p.per_big / 256 * 256 / p.per_big;
+            if (n_tiles - whole > p.tail_max) whole = n_tiles;
+            first = p.part == kPfTail ? whole : 0;
+            count = p.part == kPfTail ? (n_tiles - whole) * SUB : whole;
+        }
+        const int total = count * per_tile;
+        if ((int)blockIdx.x >= total) return;  // uniform
+        const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds, qn = total / kXcds, rem = total % kXcds;
+        const int w = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + slot;
+        int tile = w / per_tile;
+        const int rest = w - tile * per_tile;
+        proj = rest / n_col; col = rest - proj * n_col;
+        int sub = 0;
+        if (p.part == kPfTail) { sub = (tile % SUB) * C::TM; tile = first + tile / SUB; }
+        if (a.n_new) {  // the sequence whose tiles include this one
+            const int b = __popcll(__ballot(lane < a.B && c0 <= tile)) + __popcll(__ballot(lane + 64 < a.B && c1 <= tile));
+            const int l = b & 63;
+            const int end = b < 64 ? __builtin_amdgcn_readlane(c0, l) : __builtin_amdgcn_readlane(c1, l);
+            const int mine = b < 64 ? __builtin_amdgcn_readlane(t0v, l) : __builtin_amdgcn_readlane(t1v, l);
+            const int n_b = min(max(a.n_new[b], 0), a.n_tok);
+            m0 = b * a.n_tok + (tile - (end - mine)) * unit + sub;
+            m_end = b * a.n_tok + n_b;
+        } else {
+            m0 = tile * unit + sub;
+            m_end = a.B * a.n_tok;
+        }
+        if (m0 >= m_end) return;  // uniform: an empty part of a sequence's last tile
+    }
+    const int lat0 = col * C::TN;
+    const size_t row_bytes = (size_t)a.D * 2;
+    const unsigned char* X = static_cast<const unsigned char*>(a.X[proj]) + (size_t)m0 * row_bytes;
+    const unsigned char* U = static_cast<const unsigned char*>(a.UT[proj]) + (size_t)lat0 * row_bytes;
+
+    // this wave's 1 KB pieces (16 rows of 64 bytes) of a step: projector side wave, wave + 8, wave + 16, token side wave,
+    // wave + 8.  Lane -> row lane / 4, position lane % 4; rows past the end re-read the last one and are never stored
+    const uint32_t lds0 = lds_offset(lds);
+    const int prow = lane >> 2, ppos = lane & 3;
+    constexpr int NU = (C::PIECES + 7) / 8, NL = NU + NBT;   // loads of a wave per step
+    uint32_t u_off[NU], x_off[NBT];
+#pragma unroll
+    for (int i = 0; i < NU; ++i) {
+        const int row = (wave + 8 * i) * 16 + prow;
+        u_off[i] = (uint32_t)min(row, a.r - 1 - lat0) * (uint32_t)row_bytes + (uint32_t)((ppos ^ ((row >> 2) & 3)) << 4);
+    }
+#pragma unroll
+    for (int i = 0; i < NBT; ++i) {
+        const int row = (wave + 8 * i) * 16 + prow;
+        x_off[i] = (uint32_t)min(row, m_end - 1 - m0) * (uint32_t)row_bytes + (uint32_t)((ppos ^ ((row >> 2) & 3)) << 4);
+    }
+    const bool last_u = wave + 8 * (NU - 1) < C::PIECES;   // (uniform) this wave has the last of its projector pieces
+    const int n_steps = a.D / 32;
+    // load i of a step: token pieces, then projector pieces
+    auto load_piece = [&](int i, int step, int stage) {
+        const size_t at = (size_t)min(step, n_steps - 1) * kLgStep;  // (past the end: a step that nothing reads any more)
+        const uint32_t st = lds0 + (uint32_t)stage * C::STAGE;
+        if (i < NBT) load_lds16(X + at, x_off[i], st + C::A_BYTES + (wave + 8 * i) * 1024);
+        else if (i + 1 < NL || last_u) load_lds16(U + at, u_off[i - NBT], st + (wave + 8 * (i - NBT)) * 1024);
+    };
+    auto load_step = [&](int step, int stage) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) load_piece(i, step, stage);
+    };
+    // waits until all but the newest K steps of this wave's loads have landed
+    auto wait_but = [&](auto k) {
+        constexpr int K = decltype(k)::value;
+        if (last_u) vm_wait<K * NL>(); else vm_wait<K * (NL - 1)>();
+    };
+
+    f32x16 acc[NBW][NBT];
+#pragma unroll
+    for (int mb = 0; mb < NBW; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NBT; ++nb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[mb][nb][v] = 0.f;
+    // fragment addresses: row l32 of a 32-row block, 16-byte piece 2 ks + hi (the row bits of the XOR do not depend on the
+    // block, whose rows start at a multiple of 32)
+    const uint32_t at[2] = {(uint32_t)swz64(l32, hi), (uint32_t)swz64(l32, 2 + hi)};
+    struct Frags { u32x4 a[NBW], b[NBT]; };
+    const unsigned char* pa = lds + wn * NBW * 32 * kLgStep;
+    const unsigned char* pb = lds + C::A_BYTES + wm * NBT * 32 * kLgStep;
+    auto read_frag = [&](Frags& F, int i, int stage, int ks) {
+        if (i < NBT) F.b[i] = *reinterpret_cast<const u32x4*>(pb + at[ks] + stage * C::STAGE + i * 32 * kLgStep);
+        else F.a[i - NBT] = *reinterpret_cast<const u32x4*>(pa + at[ks] + stage * C::STAGE + (i - NBT) * 32 * kLgStep);
+    };
+    // One half step, in this order: the MFMAs of `F`, between them the reads of the next half step's fragments into `N` and
+    // half of this wave's share of a later step's loads.  A load is held at issue while the path from the L2 is busy, so
+    // loads issued together in front of the MFMAs would keep the matrix cores waiting (10 % at D = 4096).
+    auto half_step = [&](const Frags& F, Frags& N, int n_stage, int n_ks, int step, int stage, auto half) {
+        constexpr int NM = NBT * NBW, NR = NBW + NBT, H = decltype(half)::value, L0 = H ? (NL + 1) / 2 : 0, L1 = H ? NL : (NL + 1) / 2;
+#pragma unroll
+        for (int j = 0; j < NM; ++j) {
+            mma_op<bf16_t>::run(F.a[j / NBT], F.b[j % NBT], acc[j / NBT][j % NBT]);
+#pragma unroll
+            for (int i = j * NR / NM; i < (j + 1) * NR / NM; ++i) read_frag(N, i, n_stage, n_ks);
+#pragma unroll
+            for (int i = L0 + j * (L1 - L0) / NM; i < L0 + (j + 1) * (L1 - L0) / NM; ++i) load_piece(i, step, stage);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+    load_step(0, 0); load_step(1, 1); load_step(2, 2);
+    // cache rows of this lane's tokens (null: not stored), found while the first loads are in flight
+    unsigned char* dst[NBT];
+#pragma unroll
+    for (int nb = 0; nb < NBT; ++nb) {
+        const int m = m0 + (wm * NBT + nb) * 32 + l32;
+        const int mc = min(m, m_end - 1), b = mc / a.n_tok, t = mc - b * a.n_tok;
+        const int row0 = a.seq_len[b];
+        const long long row = (long long)row0 + t;
+        const bool ok = m < m_end && row0 >= 0 && row < a.S_max;
+        dst[nb] = ok ? static_cast<unsigned char*>(a.cache[proj]) + (((size_t)b * a.S_max + (size_t)row) * a.r + hi * 4) * 2 : nullptr;
+    }
+    wait_but(std::integral_constant<int, 2>{});
+    wg_barrier();
+    Frags F0, F1;
+#pragma unroll
+    for (int i = 0; i < NBW + NBT; ++i) read_frag(F0, i, 0, 0);
+    for (int s0 = 0; s0 < n_steps; s0 += 4) {  // (n_steps is a multiple of 4)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            // steps up to s + 1 have landed, everywhere; every wave is done with step s - 1
+            wait_but(std::integral_constant<int, 1>{});
+            wg_barrier();
+            half_step(F0, F1, u, 1, s0 + u + 3, (u + 3) & 3, std::integral_constant<int, 0>{});
+            half_step(F1, F0, (u + 1) & 3, 0, s0 + u + 3, (u + 3) & 3, std::integral_constant<int, 1>{});
+        }
+    }
+    vm_wait<0>();  // (no load may land in LDS that another workgroup has been given)
+
+    // acc[mb][nb][4a+c]: latent coordinate wn 32 NBW + mb 32 + 8a + 4hi + c, token wm 32 NBT + nb 32 + l32
+#pragma unroll
+    for (int nb = 0; nb < NBT; ++nb) {
+        if (dst[nb]) {
+#pragma unroll
+            for (int mb = 0; mb < NBW; ++mb) {
+                const int lat = lat0 + (wn * NBW + mb) * 32;
+                if (lat < a.r) {  // uniform (r is a multiple of 64, so of the 32-wide blocks)
+#pragma unroll
+                    for (int v = 0; v < 16; v += 4) {
+                        uint2 w;
+                        w.x = (uint32_t)f32_to_bf16(acc[mb][nb][v]) | ((uint32_t)f32_to_bf16(acc[mb][nb][v + 1]) << 16);
+                        w.y = (uint32_t)f32_to_bf16(acc[mb][nb][v + 2]) | ((uint32_t)f32_to_bf16(acc[mb][nb][v + 3]) << 16);
+                        *reinterpret_cast<uint2*>(dst[nb] + (size_t)(lat + 2 * v) * 2) = w;
+                    }
+                }
+            }
+        }
+    }
 }
 
 // after a bulk append: advance every sequence by its token count (separate launch, so that every cache row

@@ -830,8 +830,46 @@ sals_status sals_compress_append(sals_ctx* ctx, const void* k_new, const void* v
     if (!ctx || bad(k_new) || bad(v_new) || bad(W) || bad(Kc) || bad(Vc) || !seq_len) return SALS_ERR_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     return ctx->d.dtype == SALS_BF16
-               ? launch_project<bf16_t, false>(ctx, W, k_new, v_new, Kc, Vc, seq_len, st)
-               : launch_project<float, false>(ctx, W, k_new, v_new, Kc, Vc, seq_len, st);
+               ? launch_append<bf16_t>(ctx, W, k_new, v_new, Kc, Vc, QuantArgs{}, seq_len, st, true)
+               : launch_append<float>(ctx, W, k_new, v_new, Kc, Vc, QuantArgs{}, seq_len, st, true);
+}
+
+namespace {
+// Tiles of the bf16 prompt compression: the choice with the smallest estimated duration in us, where a round of one workgroup
+// per compute unit takes (64-byte steps of the D axis x measured time per step + start and store of a tile).  A step takes
+// `full` with the whole chip at work (the matrix cores' clock follows the power drawn) and `idle` with few workgroups.
+// The tiles that do not fill a round may go to a second launch with smaller ones (see PfPart), 2 us more.
+struct PrefillTile { int nbw, nbt; double idle, full, over; };
+constexpr PrefillTile kPrefillTiles[] = {
+    {1, 1, 0.105, 0.20, 2.0}, {2, 1, 0.145, 0.286, 3.0}, {3, 1, 0.19, 0.38, 4.0},
+    {2, 2, 0.255, 0.45, 6.0}, {4, 2, 0.475, 0.68, 12.0}, {5, 2, 0.58, 0.82, 13.0}};
+struct PrefillPlan { PrefillTile main, tail; int tail_max; };  // tail_max == 0: one launch
+PrefillPlan plan_prefill(const sals_desc& d, int n_tok)
+{
+    PrefillPlan best{kPrefillTiles[0], kPrefillTiles[0], 0};
+    double best_us = 1e30;
+    const double steps = (double)(d.H_kv * d.d) / 32.0;
+    auto rounds_us = [&](const PrefillTile& t, double tiles) {
+        const double rounds = std::floor(tiles / 256.0), rest = tiles / 256.0 - rounds;
+        return rounds * (steps * t.full + t.over) + (rest > 0.0 ? steps * (t.idle + (t.full - t.idle) * rest) + t.over : 0.0);
+    };
+    auto per_row_tile = [&](const PrefillTile& t) { return ceil_div(d.r, 64 * t.nbw) * 2; };
+    for (const PrefillTile& t : kPrefillTiles) {
+        const long long row_tiles = ((long long)d.B * n_tok + 128 * t.nbt - 1) / (128 * t.nbt);
+        const int per = per_row_tile(t);
+        const double us = rounds_us(t, (double)row_tiles * per);
+        if (us < best_us) { best_us = us; best = PrefillPlan{t, t, 0}; }
+        if (t.nbt != 2) continue;
+        const long long whole = row_tiles * per / 256 * 256 / per;
+        if (whole == 0 || whole == row_tiles) continue;
+        for (const PrefillTile& u : kPrefillTiles) {
+            if (u.nbt != 1) continue;
+            const double us2 = rounds_us(t, (double)whole * per) + rounds_us(u, (double)(row_tiles - whole) * 2 * per_row_tile(u)) + 2.0;
+            // (the token counts may be smaller than n_tok: the tail is used for any rest up to this one or two thirds of a round)
+            if (us2 < best_us) { best_us = us2; best = PrefillPlan{t, u, std::max((int)(row_tiles - whole), 171 / per)}; }
+        }
+    }
+    return best;
 }
 
 sals_status sals_compress_prefill(sals_ctx* ctx, const void* k_new, const void* v_new, const void* W, void* Kc,
@@ -849,29 +887,30 @@ sals_status sals_compress_prefill(sals_ctx* ctx, const void* k_new, const void* 
     a.n_tok = n_tok; a.D = d.H_kv * d.d; a.r = d.r; a.S_max = d.S_max; a.B = d.B; a.nproj = 2;
     for (int p = 0; p < 2; ++p)
         a.UT[p] = bf ? static_cast<const void*>(w_section<bf16_t>(ctx, W, p)) : static_cast<const void*>(w_section<float>(ctx, W, p));
-    const int nl = d.r % 128 == 0 ? 128 : 64;
-    // 256-token tiles unless they would fill less than three quarters of the chip's 512 workgroup slots
-    const int tok = (nl == 128 && (long long)ceil_div(n_tok, 256) * (d.r / nl) * d.B * 2 < 384) ? 128 : 256;
-    const dim3 grid(ceil_div(n_tok, tok), d.r / nl, d.B * 2);
-    const size_t lds = prefill_lds_bytes(tok, nl);
-#define SALS_PREFILL(T, TOKT, NLT)                                                                                \
-    do {                                                                                                          \
-        auto kern = prefill_compress_kernel<T, TOKT, NLT>;                                                        \
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,  \
-                                (int)lds) != hipSuccess)                                                          \
-            return SALS_ERR_HIP;                                                                                  \
-        hipLaunchKernelGGL(kern, grid, dim3(kPfThreads), lds, st, a);                                             \
-    } while (0)
-#define SALS_PREFILL_T(T)                                                                                         \
-    do {                                                                                                          \
-        if (nl == 64) SALS_PREFILL(T, 256, 64); else if (tok == 128) SALS_PREFILL(T, 128, 128);                   \
-        else SALS_PREFILL(T, 256, 128);                                                                           \
-    } while (0)
-    {
-        ProfScope ps(ctx, SALS_K_PREFILL, st);
-        if (bf) SALS_PREFILL_T(bf16_t); else SALS_PREFILL_T(float);
-    }
-#undef SALS_PREFILL_T
+    auto allow = [](const void* kern, size_t lds) {
+        return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
+    };
+    ProfScope ps(ctx, SALS_K_PREFILL, st);
+    if (bf) {
+        const PrefillPlan P = plan_prefill(d, n_tok);
+        for (int pass = 0; pass < (P.tail_max ? 2 : 1); ++pass) {
+            const PrefillTile t = pass ? P.tail : P.main;
+            const int n_col = ceil_div(d.r, 64 * t.nbw), tm = 128 * t.nbt;
+            const PfPart part{P.tail_max ? (pass ? kPfTail : kPfBig) : kPfAll, 2 * ceil_div(d.r, 64 * P.main.nbw), P.tail_max};
+            // every token tile a batch of these sizes can have in this launch (workgroups past the tiles that hold tokens leave)
+            const int all = n_new ? d.B * ceil_div(n_tok, tm) : (int)(((long long)d.B * n_tok + tm - 1) / tm);
+            const int n_tiles = pass ? std::min(all, P.tail_max * (256 / tm)) : all;
+#define SALS_PREFILL(N, T)                                                                                              \
+            else if (t.nbw == N && t.nbt == T) {                                                                        \
+                auto kern = prefill_tile_kernel<N, T>;                                                                  \
+                constexpr size_t lds = pf_cfg<N, T>::LDS;                                                               \
+                if (!allow(reinterpret_cast<const void*>(kern), lds)) return SALS_ERR_HIP;                              \
+                hipLaunchKernelGGL(kern, dim3(n_tiles * 2 * n_col), dim3(kPfThreads), lds, st, a, n_col, part);          \
+            }
+            if (false) {}
+            SALS_PREFILL(1, 1) SALS_PREFILL(2, 1) SALS_PREFILL(3, 1) SALS_PREFILL(2, 2) SALS_PREFILL(4, 2) SALS_PREFILL(5, 2)
+            if (launch_status() != SALS_OK) return SALS_ERR_HIP;
+        }
 #undef SALS_PREFILL
     if (launch_status() != SALS_OK) return SALS_ERR_HIP;
     hipLaunchKernelGGL(advance_seq_len_kernel, dim3(ceil_div(d.B, 128)), dim3(128), 0, st, seq_len, n_new, n_tok, d.B, d.S_max);
@@ -896,6 +935,17 @@ namespace {
 // chain the score kernel also leaves its workgroups' key ranges for it.
 sals_status step_scores(sals_ctx* ctx, const void* q, const void* W, const void* Kc, const int32_t* seq_len,
                         float* scores, hipStream_t st)
+    } else {
+        const int nl = d.r % 128 == 0 ? 128 : 64;
+        // 256-token tiles unless they would fill less than three quarters of the chip's 512 workgroup slots
+        const int tok = (nl == 128 && (long long)ceil_div(n_tok, 256) * (d.r / nl) * d.B * 2 < 384) ? 128 : 256;
+        const dim3 grid(ceil_div(n_tok, tok), d.r / nl, d.B * 2);
+        const size_t lds = prefill_lds_bytes(tok, nl);
+        auto kern = nl == 64 ? prefill_compress_kernel<float, 256, 64>
+                             : (tok == 128 ? prefill_compress_kernel<float, 128, 128> : prefill_compress_kernel<float, 256, 128>);
+        if (!allow(reinterpret_cast<const void*>(kern), lds)) return SALS_ERR_HIP;
+        hipLaunchKernelGGL(kern, grid, dim3(kPfThreads), lds, st, a);
+    }
 {
     if (!ctx || bad(q) || bad(W) || bad(Kc) || !seq_len || bad(scores)) return SALS_ERR_INVALID_ARG;
     sals_status s = ctx->d.dtype == SALS_BF16

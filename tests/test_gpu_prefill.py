@@ -11,7 +11,7 @@ torch = pytest.importorskip("torch")
 if not torch.cuda.is_available():
     pytest.skip("no GPU", allow_module_level=True)
 
-from paper_2510_24273_amd import synth  # noqa: E402
+from paper_2510_24273_amd import binding, synth  # noqa: E402
 from tests import gpu_util as gu  # noqa: E402
 
 SMALL = synth.shrink(synth.CONFIGS["cfg2"], B=3, S=700, r=192, top_k=50, n_layers=1, plant=0)
@@ -109,4 +109,45 @@ def test_prefill_then_decode_matches_token_by_token_append(oracle):
     R = gu.run_stages(ctx, w, G)
     for bb in range(w.B):
         gu.check_sequence(oracle, w, L2, R, bb)
+    ctx.close()
+
+
+@pytest.mark.parametrize("B,n_tok,H_kv,r,lens", [
+    (1, 1, 8, 64, None),                                    # one row, one tile mostly empty
+    (3, 129, 1, 192, None),                                 # tiles that span sequences, shortest D axis
+    (5, 257, 2, 448, [257, 0, 1, 256, 129]),                # a tile of its own per sequence, empty sequence
+    (100, 40, 1, 320, [(7 * i) % 41 for i in range(100)]),  # more sequences than a wave has lanes
+    (6, 4001, 8, 640, [4001, 3334, 3001, 0, 2334, 128]),    # whole rounds of large tiles, the rest in small ones
+    (2, 9000, 8, 1024, None),                               # the same without per-sequence counts
+    (1, 3000, 32, 576, None),
+])
+def test_tile_shapes_and_remainders(B, n_tok, H_kv, r, lens):
+    """Every tile shape the batch compression chooses from, at sizes that leave remainders, into a cache that already
+    holds tokens; against fp32 products on the device."""
+    print(f"[case] prefill tiles B={B} n={n_tok} H_kv={H_kv} r={r}", flush=True)
+    D, dev = 128 * H_kv, gu.DEV
+    S = n_tok + 5
+    ctx = binding.Sals(binding.make_desc(B, S, H_kv, H_kv, 128, r, 1, "bf16"), dev)
+    g = torch.Generator(device=dev)
+    g.manual_seed(B * 1000 + n_tok)
+    U = [(torch.randn(D, r, generator=g, device=dev) * D ** -0.5).to(torch.bfloat16) for _ in range(2)]
+    W = ctx.pack_weights(*U)
+    X = [torch.randn(B, n_tok, D, generator=g, device=dev, dtype=torch.bfloat16) for _ in range(2)]
+    C = [torch.full((B, S, r), 7.0, dtype=torch.bfloat16, device=dev) for _ in range(2)]
+    start = torch.arange(B, device=dev, dtype=torch.int32) % 4
+    seq = start.clone()
+    n_new = None if lens is None else torch.tensor(lens, dtype=torch.int32, device=dev)
+    ctx.compress_prefill(X[0], X[1], W, C[0], C[1], seq, n_tok, n_new)
+    torch.cuda.synchronize()
+    count = torch.full((B,), n_tok, device=dev, dtype=torch.int32) if lens is None else n_new
+    assert torch.equal(seq, start + count)
+    row = torch.arange(S, device=dev)[None, :]
+    live = (row >= start[:, None]) & (row < (start + count)[:, None])
+    at = (row - start[:, None]).clamp(0, n_tok - 1)
+    for x, u, c in zip(X, U, C):
+        ref = (x.view(B * n_tok, D).float() @ u.float()).view(B, n_tok, r)
+        want = torch.gather(ref, 1, at[:, :, None].expand(B, S, r))
+        err = (c.float() - want).abs() - (2.0 ** -8 * want.abs() + 1e-4)
+        assert bool((err[live] <= 0).all()), float(err[live].max())
+        assert bool((c[~live] == 7.0).all()), "a row outside the prompt was written"
     ctx.close()
