@@ -34,10 +34,11 @@ template <> struct mma16_op<float> {   // four v_mfma_f32_16x16x4_f32
     }
 };
 
-constexpr int kProjWaves = 4;
+constexpr int kProjWaves = 4;       // waves of a query projection workgroup
 constexpr int kProjThreads = 64 * kProjWaves;
+constexpr int kAppendWaves = 8;     // ... and at most of an append workgroup, which owns the whole D axis
 constexpr int kProjMaxCols = 128;  // B * (H_q / H_kv) handled per call
-constexpr int kProjBatch = 8;      // row pieces a wave keeps in flight per round
+constexpr int kProjBatch = 8;      // row pieces a wave of a query projection keeps in flight per round
 
 struct ProjArgs {  // (what the first loads need comes first: those 14 words arrive preloaded in scalar registers)
     const void* UT[2];   // transposed projectors [r, D]
@@ -50,13 +51,12 @@ struct ProjArgs {  // (what the first loads need comes first: those 14 words arr
     const int32_t* seq_len;  // append: [B] row to write
 };
 
-template <typename T, bool QUERY>
-__global__ __launch_bounds__(kProjThreads) void project_kernel(ProjArgs a)
+// workgroup of NW waves, NBATCH row pieces and HB column blocks of a wave in flight per round; i0: first latent coordinate
+template <typename T, bool QUERY, int NW, int NBATCH, int HB>
+__device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int slice, int proj)
 {
     constexpr int VEC = elem<T>::vec;
     constexpr int KS = 4 * VEC;  // elements of the D axis per MFMA step
-    const int proj = blockIdx.z, slice = blockIdx.y;
-    const int i0 = blockIdx.x * 16;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, kg = lane >> 4;
     const int G = QUERY ? a.H / a.H_kv : 1;
@@ -67,33 +67,33 @@ __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjArgs a)
     const T* X = static_cast<const T*>(a.X[proj]);
     const T* arow = UT + (size_t)(i0 + l16) * a.D + kg * VEC;
 
-    __shared__ __attribute__((aligned(16))) float red[kProjWaves][64][4];
+    __shared__ __attribute__((aligned(16))) float red[NW][64][4];
     __shared__ float colsum[kProjMaxCols][16];
 
     f32x4v acc[kProjMaxCols / 16];
 #pragma unroll
     for (int nb = 0; nb < kProjMaxCols / 16; ++nb) acc[nb] = f32x4v{0.f, 0.f, 0.f, 0.f};
 
-    // this wave's steps: wave, wave+4, ... ; kProjBatch steps of loads per round
-    for (int ks0 = wave; ks0 < nks; ks0 += kProjWaves * kProjBatch) {
-        u32x4 af[kProjBatch];
+    // this wave's steps: wave, wave+NW, ... ; NBATCH steps of loads per round
+    for (int ks0 = wave; ks0 < nks; ks0 += NW * NBATCH) {
+        u32x4 af[NBATCH];
 #pragma unroll
-        for (int u = 0; u < kProjBatch; ++u) {
-            int ks = ks0 + u * kProjWaves;
+        for (int u = 0; u < NBATCH; ++u) {
+            int ks = ks0 + u * NW;
             af[u] = ks < nks ? ld16(arow + (size_t)(ks_first + ks) * KS) : u32x4{0, 0, 0, 0};
         }
-        // the x operands of two column blocks are requested together, ahead of their products: a round costs
-        // one memory round trip per pair of column blocks
+        // the x operands of HB column blocks are requested together, ahead of their products: a round costs one memory
+        // round trip per HB column blocks
 #pragma unroll
-        for (int nb0 = 0; nb0 < kProjMaxCols / 16; nb0 += 2) {
+        for (int nb0 = 0; nb0 < kProjMaxCols / 16; nb0 += HB) {
             if (nb0 < n_nblk) {  // uniform
-                u32x4 bf[2][kProjBatch];
+                u32x4 bf[HB][NBATCH];
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
+                for (int h = 0; h < HB; ++h) {
                     const int n = (nb0 + h) * 16 + l16;
 #pragma unroll
-                    for (int u = 0; u < kProjBatch; ++u) {
-                        int ks = ks0 + u * kProjWaves;
+                    for (int u = 0; u < NBATCH; ++u) {
+                        int ks = ks0 + u * NW;
                         bf[h][u] = u32x4{0, 0, 0, 0};
                         if (ks < nks && n < ncols) {
                             int c = (ks_first + ks) * KS + kg * VEC;
@@ -110,14 +110,14 @@ __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjArgs a)
                 }
                 asm volatile("" ::: "memory");  // (keeps the loads above from sinking towards their products)
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
+                for (int h = 0; h < HB; ++h)
 #pragma unroll
-                    for (int u = 0; u < kProjBatch; ++u) mma16_op<T>::run(af[u], bf[h][u], acc[nb0 + h]);
+                    for (int u = 0; u < NBATCH; ++u) mma16_op<T>::run(af[u], bf[h][u], acc[nb0 + h]);
             }
         }
     }
 
-    // fold the four waves' sums in wave order; acc[nb][v] is (coordinate 4*kg+v, column nb*16+l16)
+    // fold the waves' sums in wave order; acc[nb][v] is (coordinate 4*kg+v, column nb*16+l16)
 #pragma unroll
     for (int nb = 0; nb < kProjMaxCols / 16; ++nb) {
         if (nb < n_nblk) {  // uniform
@@ -125,19 +125,19 @@ __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjArgs a)
 #pragma unroll
             for (int v = 0; v < 4; ++v) red[wave][lane][v] = acc[nb][v];
             __syncthreads();
-            {
+            if (tid < 256) {
                 int col = tid & 15, rr = tid >> 4;
                 int src_lane = (rr >> 2) * 16 + col, v = rr & 3;
                 float s = 0.f;
 #pragma unroll
-                for (int w = 0; w < kProjWaves; ++w) s += red[w][src_lane][v];
+                for (int w = 0; w < NW; ++w) s += red[w][src_lane][v];
                 colsum[nb * 16 + col][rr] = s;
             }
         }
     }
     __syncthreads();
     // add the heads of each group and write
-    for (int t = tid; t < a.B * 16; t += kProjThreads) {
+    for (int t = tid; t < a.B * 16; t += 64 * NW) {
         int b = t >> 4, rr = t & 15;
         float s = 0.f;
         for (int m = 0; m < G; ++m) s += colsum[b * G + m][rr];
@@ -151,6 +151,12 @@ __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjArgs a)
                 elem<T>::store(static_cast<T*>(a.cache[proj]) + ((size_t)b * rows + row) * a.r + i0 + rr, s);
         }
     }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kProjThreads) void project_kernel(ProjArgs a)
+{
+    project_block<T, true, kProjWaves, kProjBatch, 2>(a, blockIdx.x * 16, blockIdx.y, blockIdx.z);
 }
 
 // after an append: advance the sequence lengths (separate launch, so that every cache row

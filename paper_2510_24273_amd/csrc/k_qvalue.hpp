@@ -11,7 +11,7 @@
 //
 //   Vq    [B, S_max, D_kv*BITS/8] bytes      Vmeta [B, S_max, D_kv/32, 2] T
 //
-// qv_quantize_kernel writes the new token's row.  attend_qv_kernel evaluates the last step of
+// append_kernel writes the new token's row.  attend_qv_kernel evaluates the last step of
 // Algorithm 1, y[h] = sum_j p[h,j] v^[C_j, g(h)], from the logits and tile statistics the logits
 // kernel left behind: a gather of k rows of D_kv*BITS/8 bytes, no matrix product.  A thread owns
 // 16 channels of one KV head for the whole token range, so the sum over tokens never leaves its
@@ -22,6 +22,7 @@
 
 #include "common.hpp"
 #include "k_attend.hpp"
+#include "k_project.hpp"
 
 namespace sals {
 
@@ -50,21 +51,23 @@ template <> struct qv_meta<bf16_t> {
 };
 
 // One group per 32 lanes: row seq_len[b] of the quantised cache from the new token's value.
-// A sequence whose cache is full is left untouched.  grid (D/32/8, B), 256 threads.
+// A sequence whose cache is full is left untouched.  `group`: this thread's group, of B * D / 32.
 // ring > 0: the cache is a ring of that many rows per sequence (recent window), token t in row t mod ring.
+struct QuantArgs { const void* v_new; void* codes; void* meta; int bits; };
 template <typename T, int BITS>
-__global__ __launch_bounds__(256) void qv_quantize_kernel(const T* __restrict__ v_new, unsigned char* __restrict__ Vq,
-                                                          T* __restrict__ Vmeta, const int32_t* __restrict__ seq_len,
-                                                          int D, int S_max, int ring)
+__device__ __forceinline__ void qv_quantize_group(const QuantArgs& qa, const int32_t* __restrict__ seq_len, int B, int D, int S_max,
+                                                  int ring, int group)
 {
     constexpr float kLevels = (float)((1 << BITS) - 1);
     constexpr int PER = 32 / BITS;  // codes per 32-bit word
-    const int b = blockIdx.y;
-    const int gi = blockIdx.x * 8 + (threadIdx.x >> 5), l = threadIdx.x & 31;
-    const int n_groups = D / kQvGroup;
+    const int n_groups = D / kQvGroup, l = threadIdx.x & 31;
+    const int b = group / n_groups, gi = group - b * n_groups;
+    if (b >= B) return;
     const int row = seq_len[b];
-    if (gi >= n_groups || row < 0 || row >= S_max) return;
-    const float v = elem<T>::load(v_new + (size_t)b * D + gi * kQvGroup + l);
+    if (row < 0 || row >= S_max) return;
+    unsigned char* const Vq = static_cast<unsigned char*>(qa.codes);
+    T* const Vmeta = static_cast<T*>(qa.meta);
+    const float v = elem<T>::load(static_cast<const T*>(qa.v_new) + (size_t)b * D + gi * kQvGroup + l);
     float mn = v, mx = v;
 #pragma unroll
     for (int o = 16; o > 0; o >>= 1) {
@@ -81,6 +84,27 @@ __global__ __launch_bounds__(256) void qv_quantize_kernel(const T* __restrict__ 
     if (l % PER == 0)
         *reinterpret_cast<uint32_t*>(Vq + tok * ((size_t)D * BITS / 8) + (size_t)(gi * kQvGroup + l) * BITS / 8) = w;
     if (l == 0) qv_meta<T>::store(Vmeta + (tok * n_groups + gi) * 2, scale, mn);
+}
+
+// The append of a token in one launch (the lengths are advanced by a second one: letting the last workgroup do it, counted by
+// an atomic, cost 1 us more than that launch).  blockIdx.z: projection of the new key (and value) into the latent caches, 16
+// coordinates per workgroup; QUANT: z = 0 projects the key, z = 1 quantises the new values, 2 NW groups per workgroup.
+// Eight waves with all their pieces in flight where the D axis is long: a workgroup owns 16 coordinates over the whole axis,
+// 128 KB of the projector at D = 4096, and the bytes a compute unit keeps in flight are what it is bound by.  (Batch 16,
+// D = 4096, r = 512, 2-bit values: 12.4 us to project with four waves and 3.9 to quantise in a launch of its own, now 10.7
+// for both.)
+template <typename T, int NW, bool QUANT>
+__global__ __launch_bounds__(64 * NW) void append_kernel(ProjArgs a, QuantArgs qa)
+{
+    if (QUANT && blockIdx.z == 1) {
+        const int group = blockIdx.x * (2 * NW) + (threadIdx.x >> 5);
+        if (qa.bits == 2) qv_quantize_group<T, 2>(qa, a.seq_len, a.B, a.D, a.S_max, a.ring, group);
+        else if (qa.bits == 4) qv_quantize_group<T, 4>(qa, a.seq_len, a.B, a.D, a.S_max, a.ring, group);
+        else qv_quantize_group<T, 8>(qa, a.seq_len, a.B, a.D, a.S_max, a.ring, group);
+        return;
+    }
+    if (QUANT && (int)blockIdx.x * 16 >= a.r) return;  // (the grid covers the longer of the two parts)
+    project_block<T, false, NW, NW == kProjWaves ? kProjBatch : 16, NW == kProjWaves ? 2 : 1>(a, blockIdx.x * 16, 0, blockIdx.z);
 }
 
 struct QvArgs {

@@ -220,29 +220,51 @@ template <typename T> inline const T* w_section(const sals_ctx* c, const void* W
     return static_cast<const T*>(W) + (size_t)sec * c->L.w_section;
 }
 
-// QUERY: x0 = q.  Otherwise x0 / x1 = new key / value rows (x1 may be null: keys only); `bump` advances
-// the sequence lengths afterwards; ring > 0: the caches are rings of that many rows.
-template <typename T, bool QUERY>
-sals_status launch_project(const sals_ctx* c, const void* W, const void* x0, const void* x1, void* cache0,
-                           void* cache1, int32_t* seq_len, hipStream_t st, bool bump = true, int ring = 0)
+// q~ = U_k^T (summed query heads), as partial sums over slices of the D axis
+template <typename T> sals_status launch_project(const sals_ctx* c, const void* W, const void* q, hipStream_t st)
+{
+    const sals_desc& d = c->d;
+    ProjArgs a{};
+    a.UT[0] = w_section<T>(c, W, 0);
+    a.X[0] = q;
+    a.out_f32 = reinterpret_cast<float*>(c->ws + c->L.qt);
+    a.B = d.B; a.D = d.H_kv * d.d; a.r = d.r; a.H = d.H_q; a.H_kv = d.H_kv; a.d = d.d;
+    a.S_max = d.S_max; a.nproj = 1; a.np = c->L.proj_np;
+    ProfScope ps(c, SALS_K_PROJECT, st);
+    hipLaunchKernelGGL((project_kernel<T>), dim3(d.r / 16, a.np), dim3(kProjThreads), 0, st, a);
+    return launch_status();
+}
+
+// One token per sequence: k_new (and v_new, unless null) projected into cache0 (cache1), qa.bits > 0: its value quantised.
+// `bump` advances the sequence lengths; ring > 0: the caches are rings of that many rows.
+template <typename T>
+sals_status launch_append(const sals_ctx* c, const void* W, const void* k_new, const void* v_new, void* cache0, void* cache1,
+                          const QuantArgs& qa, int32_t* seq_len, hipStream_t st, bool bump, int ring = 0)
 {
     const sals_desc& d = c->d;
     ProjArgs a{};
     a.UT[0] = w_section<T>(c, W, 0);
     a.UT[1] = w_section<T>(c, W, 1);
-    a.X[0] = x0; a.X[1] = x1;
+    a.X[0] = k_new; a.X[1] = v_new;
     a.cache[0] = cache0; a.cache[1] = cache1;
-    a.out_f32 = reinterpret_cast<float*>(c->ws + c->L.qt);
     a.seq_len = seq_len;
     a.B = d.B; a.D = d.H_kv * d.d; a.r = d.r; a.H = d.H_q; a.H_kv = d.H_kv; a.d = d.d;
-    a.S_max = d.S_max; a.nproj = (QUERY || x1 == nullptr) ? 1 : 2; a.np = QUERY ? c->L.proj_np : 1;
+    a.S_max = d.S_max; a.nproj = v_new ? 2 : 1; a.np = 1;
     a.ring = ring;
+    const bool wide = a.D / (4 * elem<T>::vec) > kProjWaves * kProjBatch;  // more MFMA steps than four waves request at once
+    const int nw = wide ? kAppendWaves : kProjWaves;
     {
         ProfScope ps(c, SALS_K_PROJECT, st);
-        hipLaunchKernelGGL((project_kernel<T, QUERY>), dim3(d.r / 16, a.np, a.nproj), dim3(kProjThreads), 0, st, a);
+#define SALS_APPEND(NW, QUANT)                                                                                           \
+    hipLaunchKernelGGL((append_kernel<T, NW, QUANT>),                                                                    \
+                       dim3(QUANT ? std::max(d.r / 16, ceil_div(d.B * (a.D / kQvGroup), 2 * nw)) : d.r / 16, 1,          \
+                            QUANT ? 2 : a.nproj), dim3(64 * NW), 0, st, a, qa)
+        if (qa.bits) { if (wide) SALS_APPEND(kAppendWaves, true); else SALS_APPEND(kProjWaves, true); }
+        else { if (wide) SALS_APPEND(kAppendWaves, false); else SALS_APPEND(kProjWaves, false); }
+#undef SALS_APPEND
     }
     if (launch_status() != SALS_OK) return SALS_ERR_HIP;
-    if (!QUERY && bump)
+    if (bump)
         hipLaunchKernelGGL(bump_seq_len_kernel, dim3(ceil_div(d.B, 128)), dim3(128), 0, st, seq_len, d.B, d.S_max);
     return launch_status();
 }
@@ -871,6 +893,7 @@ PrefillPlan plan_prefill(const sals_desc& d, int n_tok)
     }
     return best;
 }
+}  // namespace
 
 sals_status sals_compress_prefill(sals_ctx* ctx, const void* k_new, const void* v_new, const void* W, void* Kc,
                                   void* Vc, int32_t* seq_len, const int32_t* n_new, int32_t n_tok, void* hip_stream)
@@ -912,29 +935,6 @@ sals_status sals_compress_prefill(sals_ctx* ctx, const void* k_new, const void* 
             if (launch_status() != SALS_OK) return SALS_ERR_HIP;
         }
 #undef SALS_PREFILL
-    if (launch_status() != SALS_OK) return SALS_ERR_HIP;
-    hipLaunchKernelGGL(advance_seq_len_kernel, dim3(ceil_div(d.B, 128)), dim3(128), 0, st, seq_len, n_new, n_tok, d.B, d.S_max);
-    return launch_status();
-}
-
-sals_status sals_latent_scores(sals_ctx* ctx, const void* q, const void* W, const void* Kc,
-                               const int32_t* seq_len, float* scores, void* hip_stream)
-{
-    if (!ctx || bad(q) || bad(W) || bad(Kc) || !seq_len || bad(scores)) return SALS_ERR_INVALID_ARG;
-    hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    sals_status s = ctx->d.dtype == SALS_BF16
-                        ? launch_project<bf16_t, true>(ctx, W, q, nullptr, nullptr, nullptr, nullptr, st)
-                        : launch_project<float, true>(ctx, W, q, nullptr, nullptr, nullptr, nullptr, st);
-    if (s != SALS_OK) return s;
-    return ctx->d.dtype == SALS_BF16 ? launch_scores<bf16_t>(ctx, Kc, seq_len, scores, st)
-                                     : launch_scores<float>(ctx, Kc, seq_len, scores, st);
-}
-
-namespace {
-// The score stage inside a decode step: as sals_latent_scores, and for sequences long enough for the selection
-// chain the score kernel also leaves its workgroups' key ranges for it.
-sals_status step_scores(sals_ctx* ctx, const void* q, const void* W, const void* Kc, const int32_t* seq_len,
-                        float* scores, hipStream_t st)
     } else {
         const int nl = d.r % 128 == 0 ? 128 : 64;
         // 256-token tiles unless they would fill less than three quarters of the chip's 512 workgroup slots
@@ -946,11 +946,34 @@ sals_status step_scores(sals_ctx* ctx, const void* q, const void* W, const void*
         if (!allow(reinterpret_cast<const void*>(kern), lds)) return SALS_ERR_HIP;
         hipLaunchKernelGGL(kern, grid, dim3(kPfThreads), lds, st, a);
     }
+    if (launch_status() != SALS_OK) return SALS_ERR_HIP;
+    hipLaunchKernelGGL(advance_seq_len_kernel, dim3(ceil_div(d.B, 128)), dim3(128), 0, st, seq_len, n_new, n_tok, d.B, d.S_max);
+    return launch_status();
+}
+
+sals_status sals_latent_scores(sals_ctx* ctx, const void* q, const void* W, const void* Kc,
+                               const int32_t* seq_len, float* scores, void* hip_stream)
+{
+    if (!ctx || bad(q) || bad(W) || bad(Kc) || !seq_len || bad(scores)) return SALS_ERR_INVALID_ARG;
+    hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    sals_status s = ctx->d.dtype == SALS_BF16
+                        ? launch_project<bf16_t>(ctx, W, q, st)
+                        : launch_project<float>(ctx, W, q, st);
+    if (s != SALS_OK) return s;
+    return ctx->d.dtype == SALS_BF16 ? launch_scores<bf16_t>(ctx, Kc, seq_len, scores, st)
+                                     : launch_scores<float>(ctx, Kc, seq_len, scores, st);
+}
+
+namespace {
+// The score stage inside a decode step: as sals_latent_scores, and for sequences long enough for the selection
+// chain the score kernel also leaves its workgroups' key ranges for it.
+sals_status step_scores(sals_ctx* ctx, const void* q, const void* W, const void* Kc, const int32_t* seq_len,
+                        float* scores, hipStream_t st)
 {
     if (!ctx || bad(q) || bad(W) || bad(Kc) || !seq_len || bad(scores)) return SALS_ERR_INVALID_ARG;
     sals_status s = ctx->d.dtype == SALS_BF16
-                        ? launch_project<bf16_t, true>(ctx, W, q, nullptr, nullptr, nullptr, nullptr, st)
-                        : launch_project<float, true>(ctx, W, q, nullptr, nullptr, nullptr, nullptr, st);
+                        ? launch_project<bf16_t>(ctx, W, q, st)
+                        : launch_project<float>(ctx, W, q, st);
     if (s != SALS_OK) return s;
     uint2* wg_range = ctx->L.tm_chunks > 0 ? reinterpret_cast<uint2*>(ctx->ws + ctx->L.tm_srange) : nullptr;
     return ctx->d.dtype == SALS_BF16 ? launch_scores<bf16_t>(ctx, Kc, seq_len, scores, st, wg_range)
@@ -998,8 +1021,8 @@ sals_status sals_latent_scores_noalloc(const sals_desc* desc, const void* q, con
     if (s != SALS_OK) return s;
     tmp.ws_bytes = SALS_NOALLOC_SCRATCH_BYTES;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    s = desc->dtype == SALS_BF16 ? launch_project<bf16_t, true>(&tmp, W, q, nullptr, nullptr, nullptr, nullptr, st)
-                                 : launch_project<float, true>(&tmp, W, q, nullptr, nullptr, nullptr, nullptr, st);
+    s = desc->dtype == SALS_BF16 ? launch_project<bf16_t>(&tmp, W, q, st)
+                                 : launch_project<float>(&tmp, W, q, st);
     if (s != SALS_OK) return s;
     return desc->dtype == SALS_BF16 ? launch_scores<bf16_t>(&tmp, Kc, seq_len, scores, st)
                                     : launch_scores<float>(&tmp, Kc, seq_len, scores, st);
@@ -1068,23 +1091,9 @@ sals_status sals_compress_append_qv(sals_ctx* ctx, const void* k_new, const void
         return SALS_ERR_INVALID_ARG;
     if (bits != 2 && bits != 4) return SALS_ERR_UNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const sals_desc& d = ctx->d;
-    const bool bf = d.dtype == SALS_BF16;
-    sals_status s = bf ? launch_project<bf16_t, false>(ctx, W, k_new, nullptr, Kc, nullptr, seq_len, st, false)
-                       : launch_project<float, false>(ctx, W, k_new, nullptr, Kc, nullptr, seq_len, st, false);
-    if (s != SALS_OK) return s;
-    const int D = d.H_kv * d.d;
-    const dim3 grid(ceil_div(D / kQvGroup, 8), d.B);
-    unsigned char* codes = static_cast<unsigned char*>(Vq);
-#define SALS_QUANT(T, BITS)                                                                                   \
-    hipLaunchKernelGGL((qv_quantize_kernel<T, BITS>), grid, dim3(256), 0, st, static_cast<const T*>(v_new), codes, \
-                       static_cast<T*>(Vmeta), seq_len, D, d.S_max, 0)
-    if (bf) { if (bits == 4) SALS_QUANT(bf16_t, 4); else SALS_QUANT(bf16_t, 2); }
-    else    { if (bits == 4) SALS_QUANT(float, 4); else SALS_QUANT(float, 2); }
-#undef SALS_QUANT
-    if (launch_status() != SALS_OK) return SALS_ERR_HIP;
-    hipLaunchKernelGGL(bump_seq_len_kernel, dim3(ceil_div(d.B, 128)), dim3(128), 0, st, seq_len, d.B, d.S_max);
-    return launch_status();
+    const QuantArgs qa{v_new, Vq, Vmeta, bits};
+    return ctx->d.dtype == SALS_BF16 ? launch_append<bf16_t>(ctx, W, k_new, nullptr, Kc, nullptr, qa, seq_len, st, true)
+                                     : launch_append<float>(ctx, W, k_new, nullptr, Kc, nullptr, qa, seq_len, st, true);
 }
 
 sals_status sals_sparse_attend_qv(sals_ctx* ctx, const void* q, const int32_t* q_pos, const void* Kc,
@@ -1161,8 +1170,8 @@ sals_status sals_window_append(sals_ctx* win, const void* k_new, const void* v_n
     int32_t* sl = const_cast<int32_t*>(seq_len);  // read only: no length is advanced here
     const int ring = win->d.top_k;
     return win->d.dtype == SALS_BF16
-               ? launch_project<bf16_t, false>(win, W_hi, k_new, v_new, Kw, Vw, sl, st, false, ring)
-               : launch_project<float, false>(win, W_hi, k_new, v_new, Kw, Vw, sl, st, false, ring);
+               ? launch_append<bf16_t>(win, W_hi, k_new, v_new, Kw, Vw, QuantArgs{}, sl, st, false, ring)
+               : launch_append<float>(win, W_hi, k_new, v_new, Kw, Vw, QuantArgs{}, sl, st, false, ring);
 }
 
 namespace {
@@ -1271,21 +1280,10 @@ sals_status sals_window_append_qv(sals_ctx* win, const void* k_new, const void* 
     if (win->d.n_sink != 0 || win->d.n_recent != 0) return SALS_ERR_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     int32_t* sl = const_cast<int32_t*>(seq_len);  // read only: no length is advanced here
-    const sals_desc& d = win->d;
-    const int ring = d.top_k;
-    const bool bf = d.dtype == SALS_BF16;
-    sals_status s = bf ? launch_project<bf16_t, false>(win, W_hi, k_new, nullptr, Kw, nullptr, sl, st, false, ring)
-                       : launch_project<float, false>(win, W_hi, k_new, nullptr, Kw, nullptr, sl, st, false, ring);
-    if (s != SALS_OK) return s;
-    const int D = d.H_kv * d.d;
-    const dim3 grid(ceil_div(D / kQvGroup, 8), d.B);
-    if (bf)
-        hipLaunchKernelGGL((qv_quantize_kernel<bf16_t, 8>), grid, dim3(256), 0, st, static_cast<const bf16_t*>(v_new),
-                           static_cast<unsigned char*>(Vqw), static_cast<bf16_t*>(Vmeta_w), seq_len, D, d.S_max, ring);
-    else
-        hipLaunchKernelGGL((qv_quantize_kernel<float, 8>), grid, dim3(256), 0, st, static_cast<const float*>(v_new),
-                           static_cast<unsigned char*>(Vqw), static_cast<float*>(Vmeta_w), seq_len, D, d.S_max, ring);
-    return launch_status();
+    const QuantArgs qa{v_new, Vqw, Vmeta_w, 8};
+    const int ring = win->d.top_k;
+    return win->d.dtype == SALS_BF16 ? launch_append<bf16_t>(win, W_hi, k_new, nullptr, Kw, nullptr, qa, sl, st, false, ring)
+                                     : launch_append<float>(win, W_hi, k_new, nullptr, Kw, nullptr, qa, sl, st, false, ring);
 }
 
 namespace {
