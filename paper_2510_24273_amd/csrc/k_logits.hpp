@@ -3,16 +3,16 @@
 //   logits[b, h, j] = RoPE(q[b,h], q_pos[b]) . RoPE(U_k[g(h) block] K~[b, C_j], C_j) / sqrt(d)
 //
 // A gathered-row GEMM on the matrix cores: for one sequence, HEADS KV heads and a tile of
-// selected tokens, D[dim, token] = sum_i U_k[dim, i] K~[C_token, i].  Both operands are
-// staged through LDS in 64-byte steps of the latent axis: the packed U_k panel (shared by
-// the waves of a head) and the gathered latent rows (shared by the heads), each loaded
-// with 16 contiguous bytes per lane and written to a swizzled layout that the MFMA
-// fragment reads hit without bank conflicts.  Three LDS stages and two fragment register sets
-// form a software pipeline in which every wave overlaps its own LDS traffic with its MFMAs.
+// selected tokens, D[dim, token] = sum_i U_k[dim, i] K~[C_token, i].  Both operands come straight from memory into LDS
+// in 64-byte steps of the latent axis (16 bytes per lane, no registers in between): the packed U_k panel (shared by
+// the waves of a head) and the gathered latent rows (shared by the heads), in a swizzled layout that the MFMA
+// fragment reads hit without bank conflicts.  Four LDS stages; while the MFMAs of one half step run, the fragments of the
+// next are read and a share of the loads of the step three ahead is issued between them (a load is held at issue while
+// the path from the L2 is busy: issued together in front of the MFMAs, they keep the matrix cores waiting).
 //
-// The reconstructed keys stay in the accumulators.  The epilogue streams the tokens' cos/sin
-// rows through the same LDS buffers, 16 RoPE pairs per pass, rotates the accumulators and
-// dots them with the rotated query, so only logits are written, plus each (head, token
+// The reconstructed keys stay in the accumulators.  The epilogue needs the tokens' cos/sin rows, 16 RoPE pairs per pass:
+// each pass is one stage of LDS, loaded through the same ring as four more steps behind the latent axis.  It rotates the
+// accumulators and dots them with the rotated query, so only logits are written, plus each (head, token
 // tile)'s softmax maximum and normaliser for the value kernel.  The query itself is rotated
 // (fp64-accurate angles) and scaled by 1/sqrt(d) in the prologue, while the first tile loads
 // are in flight.
@@ -22,6 +22,7 @@
 #pragma once
 #include "common.hpp"
 #include "k_attend.hpp"
+#include "k_gemm.hpp"
 
 namespace sals {
 
@@ -47,7 +48,8 @@ template <int HEADS, int NTG, int NB> struct logits_cfg {
     static constexpr int NBP = B_BYTES / 16 / NT;
     static constexpr int CS_BYTES = TOK * kLgChunk;        // cos/sin of 16 pairs for every token
     static constexpr int NCS = CS_BYTES / 16 / NT;
-    static constexpr size_t LDS = 3 * (size_t)STAGE > 2 * (size_t)CS_BYTES ? 3 * (size_t)STAGE : 2 * (size_t)CS_BYTES;
+    static constexpr int SLOT = STAGE > CS_BYTES ? STAGE : CS_BYTES;
+    static constexpr size_t LDS = 4 * (size_t)SLOT;
 };
 
 // GB: query heads of a KV head handled as one block of straight-line code (1, or 4 when the group size is a multiple
@@ -130,10 +132,12 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
         const int32_t* ib = idx + (size_t)seq_of(t) * k_tot;
         return min(max(ib[min(MULTI ? (t & 63) : tok0 + t, k_tot - 1)], 0), S_max - 1);
     };
-    int b_row[NBP];  // gathered rows: piece q = tid + i*NT -> token q/4 of the tile, column q%4
+    // this lane's row in each of the wave's 1 KB pieces (16 rows of 64 bytes) of the gathered side
+    constexpr int NW = NT / 64;
+    int b_row[NBP];
 #pragma unroll
     for (int i = 0; i < NBP; ++i) {
-        const int t = (tid + i * NT) >> 2;
+        const int t = (wave + i * NW) * 16 + (lane >> 2);
         b_row[i] = row_of(t);
         if (ring > 0) b_row[i] %= ring;  // ring cache: token t lies in row t mod ring
         if (MULTI) b_row[i] += (seq_of(t) - b) * rows_per_seq;  // (rows counted from the tile's first sequence)
@@ -153,17 +157,41 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
         qa[u] = elem<T>::load(qrow + pair_first(p, style));
         qb[u] = elem<T>::load(qrow + pair_second(p, style));
     }
-    asm volatile("" ::: "memory");  // (keeps the loads above ahead of the wait for the count)
+    // ---- global sources ----------------------------------------------------------------
+    // U_k panel: the packed layout is [head][step][128 slots][64 B], so a step of a head is 8 KB in one piece and a wave's
+    // load takes 16 slots.  In LDS the 16-byte piece of slot (row) r at position p is piece p ^ ((r >> 2) & 3).
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];  // [4 slots]: [A | B], later cos/sin passes
+    const uint32_t lds0 = lds_offset(lds);
+    const int prow = lane >> 2, ppos = lane & 3;
+    const uint32_t a_off = (uint32_t)(prow * kLgStep + ((ppos ^ ((prow >> 2) & 3)) << 4));
+    const unsigned char* a_base = reinterpret_cast<const unsigned char*>(UkP + (size_t)g0 * kHeadDim * r);
+    const size_t head_bytes = (size_t)kHeadDim * r * ES;
+    // steps of the latent axis: all of them, or this workgroup's slice
+    const int nkc = MULTI ? r * ES / kLgStep / ksplit : r * ES / kLgStep;
+    const int kc_base = MULTI ? kz * nkc : 0;
+    auto slot_at = [&](int step) { return lds0 + (uint32_t)(step & 3) * C::SLOT; };
+    auto load_a = [&](int i, int step) {
+        const int piece = wave + i * NW;  // 8 pieces per head
+        load_lds16(a_base + (size_t)(piece >> 3) * head_bytes + (size_t)(kc_base + step) * (128 * kLgStep) + (piece & 7) * 1024,
+                   a_off, slot_at(step) + piece * 1024);
+    };
+    // the panels of the first three steps depend on nothing
+#pragma unroll
+    for (int st = 0; st < 3; ++st)
+        if (st < nkc) {  // uniform
+#pragma unroll
+            for (int i = 0; i < NA; ++i) load_a(i, st);
+        }
     // MULTI: a token group past the batch has no tokens
     const int n = (MULTI && b + tg >= B) ? 0 : wave_uniform(n_v);
     const int qpos = MULTI ? qpos_v : wave_uniform(qpos_v);
     if (!MULTI && tok0 >= n) {  // no selected token in this tile: neutral statistics
         if (tid < HEADS * G)
             stats[((size_t)b * H + (size_t)g0 * G + tid) * stats_stride + part] = make_float2(-INFINITY, 0.f);
+        vm_wait<0>();  // (no load may land in LDS that another workgroup has been given)
         return;
     }
 
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];  // [3][A | B], later [2][cos/sin]
     __shared__ __attribute__((aligned(16))) float sQ[SQ * HEADS][kMaxGroup][kHeadDim];
     __shared__ float2 sCS[SQ][kPairs];
     __shared__ float2 sStat[HEADS][NTG][kMaxGroup];
@@ -202,23 +230,30 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
         }
     };
 
-    // ---- global sources of this thread's pieces ---------------------------------------
-    // U_k panel: piece q = tid + i*NT -> head q/512, slot (q%512)/4, 16-byte column q%4.  The
-    // packed layout is [head][step][128 slots][64 B]: inside a head the pieces of a step are
-    // contiguous, and a step adds 8 KB.
-    const unsigned char* a_base = reinterpret_cast<const unsigned char*>(UkP + (size_t)g0 * kHeadDim * r);
-    const size_t head_bytes = (size_t)kHeadDim * r * ES;
-    auto a_src = [&](int i, int kc) {
-        const int qd = tid + i * NT;
-        return a_base + (size_t)(qd >> 9) * head_bytes + (size_t)kc * (128 * kLgStep) + (qd & 511) * 16;
+    // gathered rows and, behind the latent axis, the cos/sin passes: token rows of 128 bytes, piece p of row r at position
+    // p ^ ((r >> 1) & 7)
+    const unsigned char* b_src[NBP];
+#pragma unroll
+    for (int i = 0; i < NBP; ++i)
+        b_src[i] = reinterpret_cast<const unsigned char*>(Kc + ((size_t)b * rows_per_seq + b_row[i]) * r) +
+                   (size_t)kc_base * kLgStep + ((ppos ^ ((prow >> 2) & 3)) << 4);
+    auto load_b = [&](int i, int step) {
+        load_lds16(b_src[i] + (size_t)step * kLgStep, slot_at(step) + C::A_BYTES + (wave + i * NW) * 1024);
     };
-    auto a_dst = [&](int i) {
-        const int qd = tid + i * NT;
-        return (qd >> 9) * 128 * kLgStep + swz64((qd >> 2) & 127, qd & 3);
+    const unsigned char* rope_b = reinterpret_cast<const unsigned char*>(rope);
+    uint32_t cs_off[NCS];
+    auto load_cs = [&](int i, int ps) {
+        load_lds16(rope_b + ps * kLgChunk, cs_off[i], slot_at(nkc + ps) + (wave + i * NW) * 1024);
     };
-    const unsigned char* b_base = reinterpret_cast<const unsigned char*>(Kc + (size_t)b * rows_per_seq * r) + (tid & 3) * 16;
-    const size_t row_bytes = (size_t)r * ES;
-    auto b_dst = [&](int i) { return C::A_BYTES + swz64((tid + i * NT) >> 2, tid & 3); };
+    // load i of NL (or NCS) of virtual step `step`
+    constexpr int NL = NA + NBP;
+    auto load_piece = [&](int i, int step) {
+        if (step < nkc) {  // uniform
+            if (i < NA) load_a(i, step); else if (i < NL) load_b(i - NA, step);
+        } else if (i < NCS) {
+            load_cs(i, step - nkc);
+        }
+    };
 
     f32x16 acc[4][NB];
 #pragma unroll
@@ -228,132 +263,82 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[mb][nb][v] = 0.f;
 
-    // steps of the latent axis: all of them, or this workgroup's slice
-    const int nkc = MULTI ? r * ES / kLgStep / ksplit : r * ES / kLgStep;
-    const int kc_base = MULTI ? kz * nkc : 0;
-    struct Regs { u32x4 a[NA]; u32x4 b[NBP]; };
-    auto g_load = [&](Regs& R, int kc) {
-#pragma unroll
-        for (int i = 0; i < NA; ++i) R.a[i] = ld16(a_src(i, kc_base + kc));
-#pragma unroll
-        for (int i = 0; i < NBP; ++i) R.b[i] = ld16(b_base + (size_t)b_row[i] * row_bytes + (size_t)(kc_base + kc) * kLgStep);
-    };
-    auto l_store = [&](const Regs& R, int buf) {
-        unsigned char* base = lds + (size_t)buf * C::STAGE;
-#pragma unroll
-        for (int i = 0; i < NA; ++i) *reinterpret_cast<u32x4*>(base + a_dst(i)) = R.a[i];
-#pragma unroll
-        for (int i = 0; i < NBP; ++i) *reinterpret_cast<u32x4*>(base + b_dst(i)) = R.b[i];
-    };
-    // cos/sin rows of the tile's tokens for the epilogue, 128 bytes (16 pairs) per token and pass
-    const unsigned char* rope_b = reinterpret_cast<const unsigned char*>(rope) + (tid & 7) * 16;
-    size_t cs_off[NCS];  // byte offset of this thread's token rows in the table
-    u32x4 CR[NCS];
-    auto cs_load = [&](int ps) {
-#pragma unroll
-        for (int i = 0; i < NCS; ++i) CR[i] = ld16(rope_b + cs_off[i] + ps * kLgChunk);
-    };
-    auto cs_store = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < NCS; ++i)
-            *reinterpret_cast<u32x4*>(lds + (size_t)buf * C::CS_BYTES + swz((tid + i * NT) >> 3, tid & 7)) = CR[i];
-    };
-
     // MFMA fragments of one half step (32 latent bytes): NB token blocks, 4 head-dim blocks
     struct Frags { u32x4 b[NB]; u32x4 a[4]; };
-    auto read_frags = [&](Frags& F, int buf, int ks) {
-        const unsigned char* pa = lds + (size_t)buf * C::STAGE + hh * 128 * kLgStep;
-        const unsigned char* pb = lds + (size_t)buf * C::STAGE + C::A_BYTES + tg * NB * 32 * kLgStep;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) F.b[nb] = *reinterpret_cast<const u32x4*>(pb + swz64(nb * 32 + l32, ks * 2 + hi));
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb) F.a[mb] = *reinterpret_cast<const u32x4*>(pa + swz64(mb * 32 + l32, ks * 2 + hi));
+    const uint32_t f_at[2] = {(uint32_t)swz64(l32, hi), (uint32_t)swz64(l32, 2 + hi)};
+    const unsigned char* pa = lds + hh * 128 * kLgStep;
+    const unsigned char* pb = lds + C::A_BYTES + tg * NB * 32 * kLgStep;
+    auto read_frag = [&](Frags& F, int i, uint32_t slot, int ks) {
+        if (i < NB) F.b[i] = *reinterpret_cast<const u32x4*>(pb + slot + f_at[ks] + i * 32 * kLgStep);
+        else F.a[i - NB] = *reinterpret_cast<const u32x4*>(pa + slot + f_at[ks] + (i - NB) * 32 * kLgStep);
     };
-    auto mma_frags = [&](const Frags& F) {
+    // One half step: the MFMAs of `F`, between them the reads of the next half step's fragments into `N` and half of this
+    // wave's loads of the step three ahead, in this order.
+    constexpr int NLM = NL > NCS ? NL : NCS;
+    auto half_step = [&](const Frags& F, Frags& N, uint32_t n_slot, int n_ks, int step, auto half) {
+        constexpr int NM = 4 * NB, NR = 4 + NB, H2 = decltype(half)::value;
+        constexpr int L0 = H2 ? (NLM + 1) / 2 : 0, L1 = H2 ? NLM : (NLM + 1) / 2;
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
+        for (int j = 0; j < NM; ++j) {
+            mma_op<T>::run(F.a[j / NB], F.b[j % NB], acc[j / NB][j % NB]);
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) mma_op<T>::run(F.a[mb], F.b[nb], acc[mb][nb]);
-    };
-
-    // Software pipeline over three LDS stages.  After the barrier every wave of the workgroup is
-    // in the same phase, so LDS traffic and MFMAs only overlap if each wave overlaps them itself:
-    // while the MFMAs of one half step run, the fragments of the next half step are being read
-    // (from this stage, then from the next one, which the previous barrier already published),
-    // and the step after that moves from registers to the third stage.  The scheduling fences
-    // keep the compiler from sinking the reads behind the MFMAs that are meant to cover them.
-    {
-        Regs R;
-        Frags F0, F1;
-        {
-            Regs R1;  // second set for the fill only: the first two steps are requested together
-            g_load(R, 0);
-            g_load(R1, min(1, nkc - 1));
-            rotate_query();  // (its barrier also publishes sPos)
+            for (int i = j * NR / NM; i < (j + 1) * NR / NM; ++i) read_frag(N, i, n_slot, n_ks);
 #pragma unroll
-            for (int i = 0; i < NCS; ++i) cs_off[i] = (size_t)sPos[(tid + i * NT) >> 3] * (kPairs * sizeof(float2));
-            cs_load(0);      // cos/sin of the first epilogue pass: in flight during the whole main loop
-            l_store(R, 0);
-            l_store(R1, 1);
+            for (int i = L0 + j * (L1 - L0) / NM; i < L0 + (j + 1) * (L1 - L0) / NM; ++i) load_piece(i, step);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        g_load(R, min(2, nkc - 1));
-        __syncthreads();
-        read_frags(F0, 0, 0);
-        int cur = 0, nxt = 1, third = 2;  // stage of step kc, kc+1, kc+2
-        for (int kc = 0; kc < nkc; ++kc) {
-            read_frags(F1, cur, 1);
-            mma_frags(F0);
-            l_store(R, third);                       // step kc+2 (a copy of the last step past the end)
-            g_load(R, min(kc + 3, nkc - 1));
-            read_frags(F0, nxt, 0);
-            mma_frags(F1);
-            // issue order: LDS and global memory instructions between the MFMAs that cover them
-            {
-                constexpr int NM = 4 * NB;            // MFMAs per half step
-                constexpr int NR = 4 + NB;            // fragment reads per half step
-                constexpr int NW = NA + NBP;          // staging writes = global loads per step
-                static_assert(NR <= NM && NW < NM, "not enough MFMAs to cover the memory instructions");
+    };
+    {
 #pragma unroll
-                for (int i = 0; i < NR; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA (first half step)
-                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // LDS read (second half step)
-                }
-                if constexpr (NM > NR) __builtin_amdgcn_sched_group_barrier(0x008, NM - NR, 0);
+        for (int st = 0; st < 3; ++st)
+            if (st < nkc) {  // uniform
 #pragma unroll
-                for (int i = 0; i < NW; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA (second half step)
-                    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // LDS write (step + 2)
-                    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // global load (step + 3)
-                }
-                constexpr int REM = NM - NW, RPM = (NR + REM - 1) / REM;
-#pragma unroll
-                for (int i = 0; i < REM; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x100, RPM, 0);  // LDS reads (next step, first half)
-                }
+                for (int i = 0; i < NBP; ++i) load_b(i, st);
             }
-            __syncthreads();
-            const int t = cur; cur = nxt; nxt = third; third = t;
+        rotate_query();  // (its barrier also publishes sPos)
+#pragma unroll
+        for (int i = 0; i < NCS; ++i) {
+            const int row = (wave + i * NW) * 8 + (lane >> 3);
+            cs_off[i] = (uint32_t)sPos[row] * (uint32_t)(kPairs * sizeof(float2)) + (uint32_t)(((lane & 7) ^ ((row >> 1) & 7)) << 4);
+        }
+        for (int st = nkc; st < 3; ++st) {  // (fewer than three latent steps)
+#pragma unroll
+            for (int i = 0; i < NCS; ++i) load_cs(i, st - nkc);
+        }
+        Frags F0, F1;
+        vm_wait<(NBP < NCS ? NBP : NCS)>();  // steps 0 and 1 have landed
+        wg_barrier();
+#pragma unroll
+        for (int i = 0; i < 4 + NB; ++i) read_frag(F0, i, 0, 0);
+        for (int kc = 0; kc < nkc; ++kc) {
+            // steps up to kc + 1 have landed, everywhere; every wave is done with step kc - 1
+            if (kc + 2 < nkc) vm_wait<NL>(); else vm_wait<NCS>();
+            wg_barrier();
+            const uint32_t cur = (uint32_t)(kc & 3) * C::SLOT, nxt = (uint32_t)((kc + 1) & 3) * C::SLOT;
+            half_step(F0, F1, cur, 1, kc + 3, std::integral_constant<int, 0>{});
+            half_step(F1, F0, nxt, 0, kc + 3, std::integral_constant<int, 1>{});
         }
     }
 
     // ---- epilogue.  A lane holds, for token l32 of each block, slots mb*32 + 8a + 4hi + c; slot < 64
     // is the first element of pair (slot), slot+64 its partner (mb+2).  Pass ps = 2*ml + ah covers
-    // the pairs ml*32 + ah*16 .. +16: the tokens' 128-byte cos/sin pieces are staged in LDS, double
-    // buffered, with the loads of the next pass in flight. ------------------------------------------
+    // the pairs ml*32 + ah*16 .. +16; the tokens' 128-byte cos/sin pieces of a pass are one slot of LDS, the last of
+    // them loaded once the main loop has left its slot. ------------------------------------------
     float dot[kMaxGroup][NB];
 #pragma unroll
     for (int m = 0; m < kMaxGroup; ++m)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) dot[m][nb] = 0.f;
     {
-        cs_store(0);
-        cs_load(1);
-        __syncthreads();
+        wg_barrier();  // every wave is done with the last step
+#pragma unroll
+        for (int i = 0; i < NCS; ++i) load_cs(i, 3);
 #pragma unroll
         for (int ps = 0; ps < 4; ++ps) {
             const int ml = ps >> 1, ah = ps & 1;
-            const unsigned char* cb = lds + (size_t)(ps & 1) * C::CS_BYTES;
+            if (ps == 1) { vm_wait<NCS>(); wg_barrier(); }  // passes 1 and 2 (pass 0 landed before the last step)
+            if (ps == 3) { vm_wait<0>(); wg_barrier(); }
+            const unsigned char* cb = lds + (size_t)((nkc + ps) & 3) * C::SLOT;
 #pragma unroll
             for (int al = 0; al < 2; ++al) {
                 const int a = 2 * ah + al;
@@ -393,9 +378,6 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
                     }
                 }
             }
-            if (ps + 1 < 4) cs_store((ps + 1) & 1);
-            if (ps + 2 < 4) cs_load(ps + 2);
-            __syncthreads();
         }
     }
 
