@@ -6,12 +6,11 @@
 // into chunks of 8192 scores, one workgroup each, and the selection runs as a chain of small
 // kernels that exchange a few kilobytes:
 //   range    per chunk: minimum and maximum candidate key
-//   hist     per chunk: histogram over 2048 linear bins of the sequence's [min, max], stored as running
-//            counts from the top bin down (entry s = the chunk's scores in bins above s)
+//   hist     per chunk: histogram over 2048 linear bins of the sequence's [min, max], 16-bit counts from the top bin down
 //   place    per chunk: the bin holding the top_k-th score, how many of its members are selected and
 //            where the chunk's output starts (every workgroup of the sequence derives the same
-//            numbers, in two passes over the chunks' running counts: at every 32nd bin, then at the
-//            32 bins of the step that holds the threshold); then the indices of the scores in
+//            numbers: a thread adds up two bins over the chunks, all its loads in flight together, and one block scan
+//            of the totals and of the earlier chunks' counts settles everything); then the indices of the scores in
 //            higher bins go to their final positions (chunk order, then token order) and the
 //            members of the threshold bin to a candidate list
 //   finish   per sequence: ranks the candidates (ties towards the smaller index), writes the
@@ -32,9 +31,8 @@ constexpr int kTmF4 = kTmChunk / (4 * kTopkThreads);  // float4 groups per threa
 constexpr int kTmBins = 2048;
 constexpr int kTmMaxChunks = 128;         // S_max <= 2^20
 constexpr int kTmCand = 512;              // candidates the finish kernel ranks
-constexpr int kTmCoarse = 32;             // bins per coarse step of the threshold search
-constexpr int kTmNC = kTmBins / kTmCoarse;   // coarse steps
-constexpr int kTmCum = kTmBins + 4;       // running counts per chunk: entries 0 .. kTmBins (rows stay 16-byte aligned)
+constexpr int kTmRow = kTmBins / 2;       // 32-bit words of a chunk's histogram: two 16-bit counts each (a chunk has 8192 scores)
+static_assert(kTmChunk < 65536, "a chunk's counts fit in 16 bits");
 
 struct TopkMeta {        // per sequence, written by the place kernel
     uint32_t fallback;   // 1: topk_kernel must redo the sequence
@@ -46,12 +44,13 @@ struct TopkMeta {        // per sequence, written by the place kernel
     uint32_t pad;
 };
 
-// workspace of the chain, per sequence
+// workspace of the chain, per sequence (the kernels take its members as arguments, those that their first loads need and the
+// sizes first: these words arrive preloaded in scalar registers)
 struct TopkMultiWs {
     const uint2* range;  // [B][n_range] (min key, max key) pairs that cover the sequence's candidates: `part`, or the
     int n_range;         //   pairs the score kernel left per workgroup (then over all scores below the length)
     uint2* part;         // [B][n_chunk] (min key, max key) of the chunk's candidates
-    uint32_t* hist;      // [B][n_chunk][kTmCum]: entry s = the chunk's candidates in slots above s (slot 0 = top bin)
+    uint32_t* hist;      // [B][n_chunk][kTmRow]: the chunk's candidates in slots 2w (low half) and 2w + 1 (slot 0 = top bin)
     TopkMeta* meta;      // [B]
     uint2* cand;         // [B][kTmCand] (key, token index)
 };
@@ -133,9 +132,8 @@ __device__ __forceinline__ int tm_slot(uint32_t key, float flo, float scale)
 }
 
 __global__ __launch_bounds__(kTopkThreads) void topk_range_kernel(const float* __restrict__ scores,
-                                                                  const int32_t* __restrict__ seq_len,
-                                                                  TopkMultiWs ws, int S_max, int n_chunk,
-                                                                  int n_sink, int n_recent)
+                                                                  const int32_t* __restrict__ seq_len, int S_max, int n_chunk,
+                                                                  int n_sink, int n_recent, uint2* __restrict__ part)
 {
     __shared__ uint32_t s_min[kTopkWaves], s_max[kTopkWaves];
     const int chunk = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
@@ -152,14 +150,14 @@ __global__ __launch_bounds__(kTopkThreads) void topk_range_kernel(const float* _
     __syncthreads();
     if (tid == 0) {
         for (int w = 0; w < kTopkWaves; ++w) { kmin = min(kmin, s_min[w]); kmax = max(kmax, s_max[w]); }
-        ws.part[(size_t)b * n_chunk + chunk] = make_uint2(kmin, kmax);
+        part[(size_t)b * n_chunk + chunk] = make_uint2(kmin, kmax);
     }
 }
 
 __global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(const float* __restrict__ scores,
                                                                  const int32_t* __restrict__ seq_len,
-                                                                 TopkMultiWs ws, int S_max, int n_chunk,
-                                                                 int n_sink, int n_recent)
+                                                                 const uint2* __restrict__ range, int n_range, int S_max, int n_chunk,
+                                                                 int n_sink, int n_recent, uint32_t* __restrict__ hist_out)
 {
     __shared__ TopkShared sh;  // (its histogram array and scan buffers)
     static_assert(kTmBins == 2 * kTopkThreads && kTmBins <= kTopkBins, "two bins per thread");
@@ -170,135 +168,91 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(const float* __
     tm_load_keys(scores + (size_t)b * S_max, S_max, chunk, n_sink, S - n_recent, keys);
     for (int t = tid; t < kTmBins; t += kTopkThreads) hist[t] = 0u;
     float flo, scale;
-    const bool ok = tm_range(ws.range + (size_t)b * ws.n_range, ws.n_range, sh.cand, &flo, &scale);  // (barrier inside)
+    const bool ok = tm_range(range + (size_t)b * n_range, n_range, sh.cand, &flo, &scale);  // (barrier inside)
     if (ok) {
 #pragma unroll
         for (int i = 0; i < 4 * kTmF4; ++i)
             if (keys[i] != 0u) atomicAdd(&hist[tm_slot(keys[i], flo, scale)], 1u);
     }
     __syncthreads();
-    // running counts from the top: entry s = members of slots 0 .. s-1, entry kTmBins = all of the chunk's candidates
     const uint2 c = *reinterpret_cast<const uint2*>(&hist[2 * tid]);
-    int phase = 0;
-    uint32_t total;
-    const uint32_t above = block_excl_scan(c.x + c.y, sh, phase, &total);
-    uint32_t* out = ws.hist + ((size_t)b * n_chunk + chunk) * kTmCum;
-    *reinterpret_cast<uint2*>(out + 2 * tid) = make_uint2(above, above + c.x);
-    if (tid == 0) out[kTmBins] = total;
+    hist_out[((size_t)b * n_chunk + chunk) * kTmRow + tid] = c.x | (c.y << 16);
 }
 
-// The sequence-level decisions, taken identically by every workgroup of the sequence from the chunks' running
-// counts: threshold bin, selected members, and the first output position / candidate slot of chunk `chunk`.
+// The sequence-level decisions, taken identically by every workgroup of the sequence from the chunks' histograms: threshold
+// bin, selected members, and the first output position / candidate slot of chunk `chunk`.
 // Returns the meta record (fallback set if the chain does not apply).
 struct TmResolveLds {
-    uint32_t coarse[kTmNC];                       // all chunks' candidates above slot 32 (p + 1)
-    uint32_t fine[kTmCoarse + 1];                 // ... above slot 32 P + i
-    uint32_t fv[kTmMaxChunks][kTmCoarse + 1];     // the chunks' own counts at those slots
     uint32_t red[2 * kTopkWaves];
-    int P, I;
+    uint32_t found, t_slot, n_above, members, base_above, base_cand;
 };
-__device__ __forceinline__ TopkMeta tm_resolve(TmResolveLds& L, const TopkMultiWs& ws, int b, int chunk, int S,
-                                               int n_chunk, int top_k, int n_sink, int n_recent,
-                                               uint32_t* base_above, uint32_t* base_cand)
+__device__ __forceinline__ TopkMeta tm_resolve(TmResolveLds& L, TopkShared& sh, int& phase, const uint2* __restrict__ range,
+                                               int n_range, const uint32_t* __restrict__ hist, int b, int chunk,
+                                               int S, int n_chunk, int top_k, int n_sink, int n_recent, uint32_t* base_above,
+                                               uint32_t* base_cand)
 {
     const int tid = threadIdx.x;
     TopkMeta m{};
-    const uint32_t* cum = ws.hist + (size_t)b * n_chunk * kTmCum;
-    // first pass: the counts at every 32nd slot, summed over the chunks (four loads per thread and trip in flight, from
-    // clamped element numbers: no load in a branch)
-    const int n1 = kTmNC * n_chunk;
-    for (int t = tid; t < kTmNC + kTmCoarse + 1; t += kTopkThreads) (t < kTmNC ? L.coarse[t] : L.fine[t - kTmNC]) = 0u;
-    if (tid == 0) { L.P = -1; L.I = -1; }
-    uint32_t v1[4];
+    const uint32_t* h = hist + (size_t)b * n_chunk * kTmRow + tid;
+    // this thread's two bins over all chunks and over the chunks before this one, 16 loads in flight per trip
+    uint32_t tot[2] = {0u, 0u}, bef[2] = {0u, 0u};
+    if (tid == 0) L.found = 0u;
+    uint32_t v[16];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int e = min(tid + u * kTopkThreads, n1 - 1);
-        v1[u] = cum[(size_t)(e / kTmNC) * kTmCum + (e % kTmNC + 1) * kTmCoarse];
-    }
-    const bool ok = tm_range(ws.range + (size_t)b * ws.n_range, ws.n_range, L.red, &m.flo, &m.scale) &&  // (barrier inside)
+    for (int u = 0; u < 16; ++u) v[u] = h[(size_t)min(u, n_chunk - 1) * kTmRow];
+    const bool ok = tm_range(range + (size_t)b * n_range, n_range, L.red, &m.flo, &m.scale) &&  // (barrier inside)
                     S > top_k + n_sink + n_recent && top_k > 0;
     if (!ok) {  // uniform
         m.fallback = 1u;
         return m;
     }
+    for (int c0 = 0;;) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int e = tid + u * kTopkThreads;
-        if (e < n1) atomicAdd(&L.coarse[e % kTmNC], v1[u]);
+        for (int u = 0; u < 16; ++u) {
+            const int c = c0 + u;
+            const uint32_t x = c < n_chunk ? v[u] : 0u, y = c < chunk ? x : 0u;
+            tot[0] += x & 0xffffu; tot[1] += x >> 16;
+            bef[0] += y & 0xffffu; bef[1] += y >> 16;
+        }
+        c0 += 16;
+        if (c0 >= n_chunk) break;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = h[(size_t)min(c0 + u, n_chunk - 1) * kTmRow];
     }
-    for (int e0 = 4 * kTopkThreads; e0 < n1; e0 += 4 * kTopkThreads) {  // (more than 64 chunks)
-        uint32_t v[4];
+    uint32_t above = tot[0] + tot[1], before = bef[0] + bef[1], sum_a, sum_b;
+    block_excl_scan2(above, before, sh, phase, &sum_a, &sum_b);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = min(e0 + tid + u * kTopkThreads, n1 - 1);
-            v[u] = cum[(size_t)(e / kTmNC) * kTmCum + (e % kTmNC + 1) * kTmCoarse];
+    for (int i = 0; i < 2; ++i) {
+        if (above < (uint32_t)top_k && (uint32_t)top_k <= above + tot[i]) {  // (one thread at most)
+            L.found = 1u; L.t_slot = (uint32_t)(2 * tid + i); L.n_above = above; L.members = tot[i];
+            L.base_above = before; L.base_cand = bef[i];
         }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = e0 + tid + u * kTopkThreads;
-            if (e < n1) atomicAdd(&L.coarse[e % kTmNC], v[u]);
-        }
+        above += tot[i];
+        before += bef[i];
     }
     __syncthreads();
-    if (tid < kTmNC) {
-        const uint32_t lo = tid ? L.coarse[tid - 1] : 0u, hi = L.coarse[tid];
-        if (lo < (uint32_t)top_k && (uint32_t)top_k <= hi) L.P = tid;
-    }
-    __syncthreads();
-    const int P = L.P;
-    if (P < 0) {  // uniform: fewer candidates than top_k in the histograms (cannot happen for a valid range)
+    if (!L.found) {  // uniform: fewer candidates than top_k in the histograms (cannot happen for a valid range)
         m.fallback = 1u;
         return m;
     }
-    // second pass: the counts at the 33 slot boundaries of coarse step P, per chunk and summed
-    const int n2 = (kTmCoarse + 1) * n_chunk;
-    for (int e0 = 0; e0 < n2; e0 += 4 * kTopkThreads) {
-        uint32_t v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = min(e0 + tid + u * kTopkThreads, n2 - 1);
-            v[u] = cum[(size_t)(e / (kTmCoarse + 1)) * kTmCum + P * kTmCoarse + e % (kTmCoarse + 1)];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = e0 + tid + u * kTopkThreads;
-            if (e < n2) {
-                L.fv[e / (kTmCoarse + 1)][e % (kTmCoarse + 1)] = v[u];
-                atomicAdd(&L.fine[e % (kTmCoarse + 1)], v[u]);
-            }
-        }
-    }
-    __syncthreads();
-    if (tid < kTmCoarse) {
-        const uint32_t lo = L.fine[tid], hi = L.fine[tid + 1];
-        if (lo < (uint32_t)top_k && (uint32_t)top_k <= hi) L.I = tid;
-    }
-    __syncthreads();
-    const int I = L.I;
-    if (I < 0) {  // uniform (as above)
-        m.fallback = 1u;
-        return m;
-    }
-    m.t_slot = (uint32_t)(P * kTmCoarse + I);
-    m.n_above = L.fine[I];
-    m.members = L.fine[I + 1] - L.fine[I];
+    m.t_slot = L.t_slot;
+    m.n_above = L.n_above;
+    m.members = L.members;
     m.kk = (uint32_t)top_k - m.n_above;
-    uint32_t a = 0u, mm = 0u;
-    for (int c = 0; c < chunk; ++c) {
-        a += L.fv[c][I];
-        mm += L.fv[c][I + 1] - L.fv[c][I];
-    }
-    *base_above = a;
-    *base_cand = mm;
+    // candidates in the threshold bin of earlier chunks, and in the bins above it
+    *base_above = L.base_above;
+    *base_cand = L.base_cand;
     m.fallback = m.members > (uint32_t)kTmCand ? 1u : 0u;
     return m;
 }
 
 __global__ __launch_bounds__(kTopkThreads) void topk_place_kernel(const float* __restrict__ scores,
                                                                   const int32_t* __restrict__ seq_len,
-                                                                  TopkMultiWs ws, int32_t* __restrict__ idx,
-                                                                  int S_max, int n_chunk, int top_k, int n_sink,
-                                                                  int n_recent)
+                                                                  const uint2* __restrict__ range,
+                                                                  const uint32_t* __restrict__ hist, int n_range, int S_max,
+                                                                  int n_chunk, int top_k, int n_sink, int n_recent,
+                                                                  int32_t* __restrict__ idx, TopkMeta* __restrict__ meta,
+                                                                  uint2* __restrict__ cand_out)
 {
     __shared__ TopkShared sh;
     __shared__ TmResolveLds rl;
@@ -307,9 +261,10 @@ __global__ __launch_bounds__(kTopkThreads) void topk_place_kernel(const float* _
     uint32_t keys[4 * kTmF4];
     tm_load_keys(scores + (size_t)b * S_max, S_max, chunk, n_sink, S - n_recent, keys);
     uint32_t base_above = 0u, base_cand = 0u;
-    const TopkMeta m = tm_resolve(rl, ws, b, chunk, wave_uniform(S), n_chunk, top_k, n_sink, n_recent, &base_above,
+    int phase = 0;
+    const TopkMeta m = tm_resolve(rl, sh, phase, range, n_range, hist, b, chunk, wave_uniform(S), n_chunk, top_k, n_sink, n_recent, &base_above,
                                   &base_cand);
-    if (chunk == 0 && threadIdx.x == 0) ws.meta[b] = m;  // for the finish kernel
+    if (chunk == 0 && threadIdx.x == 0) meta[b] = m;  // for the finish kernel
     if (m.fallback) return;
     int slot[4 * kTmF4];
     uint32_t n_ab = 0u, n_eq = 0u;
@@ -319,12 +274,10 @@ __global__ __launch_bounds__(kTopkThreads) void topk_place_kernel(const float* _
         n_ab += slot[i] < (int)m.t_slot;
         n_eq += slot[i] == (int)m.t_slot;
     }
-    int phase = 0;
     uint32_t tot_ab, tot_eq;
-    __syncthreads();
     block_excl_scan2(n_ab, n_eq, sh, phase, &tot_ab, &tot_eq);
     int32_t* out = idx + (size_t)b * (top_k + n_sink + n_recent) + n_sink;
-    uint2* cand = ws.cand + (size_t)b * kTmCand;
+    uint2* cand = cand_out + (size_t)b * kTmCand;
     uint32_t pa = base_above + n_ab, pc = base_cand + n_eq;
 #pragma unroll
     for (int i = 0; i < 4 * kTmF4; ++i) {
@@ -335,22 +288,23 @@ __global__ __launch_bounds__(kTopkThreads) void topk_place_kernel(const float* _
 }
 
 // finish: ranks the candidates; a flagged sequence is selected from scratch by this workgroup
-__global__ __launch_bounds__(kTopkThreads) void topk_finish_kernel(const float* __restrict__ scores,
-                                                                   const int32_t* __restrict__ seq_len,
-                                                                   TopkMultiWs ws, int32_t* __restrict__ idx,
-                                                                   int32_t* __restrict__ n_sel, int S_max, int top_k,
-                                                                   int n_sink, int n_recent, WindowLists wl)
+__global__ __launch_bounds__(kTopkThreads) void topk_finish_kernel(const uint2* __restrict__ cand,
+                                                                   const TopkMeta* __restrict__ meta,
+                                                                   const int32_t* __restrict__ seq_len, int S_max, int top_k,
+                                                                   int n_sink, int n_recent, int32_t* __restrict__ idx,
+                                                                   int32_t* __restrict__ n_sel, const float* __restrict__ scores,
+                                                                   WindowLists wl)
 {
     __shared__ TopkShared sh;
-    __shared__ uint2 s_c[kTmCand];
-    __shared__ uint32_t s_sel[kTmCand];
+    __shared__ __attribute__((aligned(16))) uint2 s_c[kTmCand];
+    __shared__ __attribute__((aligned(16))) uint32_t s_sel[kTmCand];
     const int b = blockIdx.x, tid = threadIdx.x;
     write_window_lists(wl, seq_len, b, S_max, top_k + n_sink + n_recent, kTopkThreads);
     // (the candidate pair, the length and the meta record are requested together; slots past the member count hold
     // stale pairs and are masked)
-    const uint2 me_raw = ws.cand[(size_t)b * kTmCand + min(tid, kTmCand - 1)];
+    const uint2 me_raw = cand[(size_t)b * kTmCand + min(tid, kTmCand - 1)];
     const int S_v = ld_uniform_i32(seq_len + b);
-    const TopkMeta m = ws.meta[b];
+    const TopkMeta m = meta[b];
     if (m.fallback) {  // uniform
         topk_select_sequence<0>(sh, scores, seq_len, idx, n_sel, b, S_max, top_k, n_sink, n_recent);
         return;
@@ -365,19 +319,32 @@ __global__ __launch_bounds__(kTopkThreads) void topk_finish_kernel(const float* 
     const uint2 me = (uint32_t)tid < nm ? me_raw : make_uint2(0u, 0u);
     if (tid < kTmCand) s_c[tid] = me;
     __syncthreads();
-    // rank among the members: larger key first, equal keys by smaller token index
+    // rank among the members: larger key first, equal keys by smaller token index (slots past the members carry key 0 and
+    // rank behind everything); eight members read together
+    const uint32_t nm8 = (nm + 7u) & ~7u;
     uint32_t before = 0u;
     if ((uint32_t)tid < nm)
-        for (uint32_t c = 0; c < nm; ++c) {
-            const uint2 o = s_c[c];
-            before += (o.x > me.x) || (o.x == me.x && o.y < me.y);
+        for (uint32_t c = 0; c < nm8; c += 8) {
+            u32x4 o[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) o[u] = *reinterpret_cast<const u32x4*>(&s_c[c + 2 * u]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                before += (o[u].x > me.x) || (o[u].x == me.x && o[u].y < me.y);
+                before += (o[u].z > me.x) || (o[u].z == me.x && o[u].w < me.y);
+            }
         }
-    const uint32_t sel = ((uint32_t)tid < nm && before < m.kk) ? 1u : 0u;
-    if (tid < kTmCand) s_sel[tid] = sel;
+    const bool sel = (uint32_t)tid < nm && before < m.kk;
+    // selected members in token order: the others' indices are replaced by the largest number
+    if (tid < kTmCand) s_sel[tid] = sel ? me.y : 0xffffffffu;
     __syncthreads();
-    if (sel) {  // position in token order among the selected members
+    if (sel) {
         uint32_t pos = 0u;
-        for (uint32_t c = 0; c < nm; ++c) pos += s_sel[c] && s_c[c].y < me.y;
+        for (uint32_t c = 0; c < nm8; c += 8) {
+            const u32x4 o0 = *reinterpret_cast<const u32x4*>(&s_sel[c]), o1 = *reinterpret_cast<const u32x4*>(&s_sel[c + 4]);
+            pos += (o0.x < me.y) + (o0.y < me.y) + (o0.z < me.y) + (o0.w < me.y);
+            pos += (o1.x < me.y) + (o1.y < me.y) + (o1.z < me.y) + (o1.w < me.y);
+        }
         out[n_sink + m.n_above + pos] = (int32_t)me.y;
     }
 }

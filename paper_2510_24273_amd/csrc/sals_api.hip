@@ -197,7 +197,7 @@ Layout make_layout(const sals_desc& d)
     L.tm_chunks = d.S_max > 32768 ? ceil_div(d.S_max, kTmChunk) : 0;
     if (L.tm_chunks > 0) {
         L.tm_part = take((size_t)d.B * L.tm_chunks * sizeof(uint2));
-        L.tm_hist = take((size_t)d.B * L.tm_chunks * kTmCum * 4);
+        L.tm_hist = take((size_t)d.B * L.tm_chunks * kTmRow * 4);
         L.tm_meta = take((size_t)d.B * sizeof(TopkMeta));
         L.tm_cand = take((size_t)d.B * kTmCand * sizeof(uint2));
         // key ranges the score kernel leaves per workgroup inside a decode step (at least 16 rows per workgroup)
@@ -334,14 +334,14 @@ sals_status launch_topk(const sals_ctx* c, const float* scores, const int32_t* s
             ws.range = reinterpret_cast<const uint2*>(c->ws + L.tm_srange);
             ws.n_range = ceil_div(d.S_max, c->score_rows);
         } else {
-            hipLaunchKernelGGL(topk_range_kernel, cgrid, block, 0, st, scores, seq_len, ws, d.S_max, nc, d.n_sink,
-                               d.n_recent);
+            hipLaunchKernelGGL(topk_range_kernel, cgrid, block, 0, st, scores, seq_len, d.S_max, nc, d.n_sink, d.n_recent, ws.part);
         }
-        hipLaunchKernelGGL(topk_hist_kernel, cgrid, block, 0, st, scores, seq_len, ws, d.S_max, nc, d.n_sink, d.n_recent);
-        hipLaunchKernelGGL(topk_place_kernel, cgrid, block, 0, st, scores, seq_len, ws, idx, d.S_max, nc, d.top_k,
-                           d.n_sink, d.n_recent);
-        hipLaunchKernelGGL(topk_finish_kernel, grid, block, 0, st, scores, seq_len, ws, idx, n_sel, d.S_max, d.top_k,
-                           d.n_sink, d.n_recent, wl);
+        hipLaunchKernelGGL(topk_hist_kernel, cgrid, block, 0, st, scores, seq_len, ws.range, ws.n_range, d.S_max, nc, d.n_sink,
+                           d.n_recent, ws.hist);
+        hipLaunchKernelGGL(topk_place_kernel, cgrid, block, 0, st, scores, seq_len, ws.range, ws.hist, ws.n_range, d.S_max, nc,
+                           d.top_k, d.n_sink, d.n_recent, idx, ws.meta, ws.cand);
+        hipLaunchKernelGGL(topk_finish_kernel, grid, block, 0, st, ws.cand, ws.meta, seq_len, d.S_max, d.top_k, d.n_sink,
+                           d.n_recent, idx, n_sel, scores, wl);
         return launch_status();
     }
 #define SALS_TOPK_W(F4)                                                                                    \
