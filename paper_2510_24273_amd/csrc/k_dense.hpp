@@ -5,11 +5,12 @@
 //
 // K [B, S_max, H_kv, d] holds the keys as a dense model caches them (already rotated at their
 // positions), V [B, S_max, H_kv, d] the values.  A pure HBM stream of 2*S*D_kv elements per
-// sequence: 16 lanes (one DPP row) own a token's head row of K and of V in 16-byte pieces, the
-// dot product is folded with DPP rotations, softmax runs online per 16-lane group, and the rows of
-// the next token are requested before the current ones are consumed.  A workgroup covers one
-// (sequence, KV head, token chunk); its 16 lane groups and then the chunks are merged by
-// log-sum-exp in a fixed order.
+// sequence.  A workgroup covers a token chunk of one sequence and HB neighbouring KV heads: 16 lanes (one DPP row) own a
+// (token, head) row of K and of V in 16-byte pieces, so with two heads a load of a wave is 512 bytes of a token's row in one
+// piece; the dot product is folded with DPP rotations, softmax runs online per 16-lane group over UT tokens at a time, whose
+// rows are requested together and one set ahead.  The lane groups of a head and then the chunks are merged by
+// log-sum-exp in a fixed order.  One workgroup per compute unit streams best (batch 16, 4096 tokens, 32 heads: 7.0 TB/s;
+// one head per workgroup, a token at a time, 256-token chunks: 5.9).  Batch 8, 2048 tokens: 50.7 -> 43.4 us with the merge.
 #pragma once
 #include "common.hpp"
 #include "k_attend.hpp"
@@ -19,48 +20,55 @@ namespace sals {
 constexpr int kDnMaxChunks = 64;  // token chunks per sequence at most
 constexpr int kDnRec = kHeadDim + 2;  // floats per partial record: running max, normaliser, 128 sums
 
-// part [B, H, n_chunks, kDnRec]
-template <typename T, int GMAX>
+// part [B, H, n_chunks, kDnRec]; grid (n_chunks, H_kv / HB, B)
+template <typename T, int GMAX, int HB>
 __global__ __launch_bounds__(256) void dense_attend_kernel(const T* __restrict__ q, const int32_t* __restrict__ q_pos,
                                                            const T* __restrict__ K, const T* __restrict__ V,
-                                                           const int32_t* __restrict__ seq_len,
+                                                           const int32_t* __restrict__ seq_len, int S_max, int H, int H_kv,
+                                                           int n_chunks,
                                                            const float2* __restrict__ rope, InvFreq inv,
-                                                           float* __restrict__ part, int S_max, int H, int H_kv,
-                                                           int n_chunks, int tok_per_chunk, int rope_style,
-                                                           float scale)
+                                                           float* __restrict__ part, int rope_style, float scale)
 {
+    static_assert(HB == 1 || HB == 2 || HB == 4, "heads of a workgroup share its waves' four lane groups");
     constexpr int VEC = elem<T>::vec;
     constexpr int NCH = kHeadDim / (16 * VEC);  // 16-byte pieces per lane and row: 1 (bf16) or 2 (fp32)
-    __shared__ float sQ[GMAX][kHeadDim];
+    constexpr int UT = GMAX > 4 || NCH > 1 ? 2 : 4;
+    constexpr int NS = 16 / HB;                 // token slots of a head
+    __shared__ float sQ[HB][GMAX][kHeadDim];
     __shared__ float2 sCS[kPairs];
     __shared__ float sRed[16][kDnRec + 2];
 
-    const int chunk = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
-    const int tid = threadIdx.x, li = tid & 15, tg = tid >> 4;
+    const int chunk = blockIdx.x, h0 = blockIdx.y * HB, b = blockIdx.z;
+    const int tid = threadIdx.x, li = tid & 15, tg = tid >> 4;   // lane group tg = wave * 4 + DPP row
+    const int hb = (tg & 3) % HB, slot = (tg >> 2) * (4 / HB) + (tg & 3) / HB;
     const int G = H / H_kv;
-    const int S = min(seq_len[b], S_max);
-    const int j0 = chunk * tok_per_chunk, j1 = min(S, j0 + tok_per_chunk);
+    const int S_v = ld_uniform_i32(seq_len + b), qp_v = ld_uniform_i32(q_pos + b);
     const size_t row_stride = (size_t)H_kv * kHeadDim;
-    const T* kb = K + ((size_t)b * S_max * H_kv + kvh) * kHeadDim;
-    const T* vb = V + ((size_t)b * S_max * H_kv + kvh) * kHeadDim;
+    const T* kb = K + ((size_t)b * S_max * H_kv + h0 + hb) * kHeadDim + li * VEC;
+    const T* vb = V + ((size_t)b * S_max * H_kv + h0 + hb) * kHeadDim + li * VEC;
 
-    // every row below S_max is readable, so the first loads do not wait for the sequence length; rows
-    // at or past it are requested at most one step ahead and never used
-    const int j_readable = min(S_max, j0 + tok_per_chunk);
-    auto load_rows = [&](int j, u32x4* kp, u32x4* vp) {
-        const bool live = j < j_readable;
-        const size_t off = (size_t)(live ? j : 0) * row_stride;
+    struct Rows { u32x4 k[UT][NCH], v[UT][NCH]; };
+    // tokens j, j + NS, ... of this lane's slot, from clamped addresses (slots past the end re-read the last row)
+    auto load_rows = [&](Rows& R, int j, int last) {
 #pragma unroll
-        for (int n = 0; n < NCH; ++n) {
-            kp[n] = live ? ld16_stream(kb + off + (li + 16 * n) * VEC) : u32x4{0, 0, 0, 0};
-            vp[n] = live ? ld16_stream(vb + off + (li + 16 * n) * VEC) : u32x4{0, 0, 0, 0};
+        for (int u = 0; u < UT; ++u) {
+            const size_t off = (size_t)min(j + u * NS, last) * row_stride;
+#pragma unroll
+            for (int n = 0; n < NCH; ++n) {
+                R.k[u][n] = ld16_stream(kb + off + 16 * n * VEC);
+                R.v[u][n] = ld16_stream(vb + off + 16 * n * VEC);
+            }
         }
     };
-    u32x4 kc[NCH], vc[NCH], kn[NCH], vn[NCH];
-    load_rows(j0 + tg, kc, vc);
+    // the chunks are shares of the tokens present, not of the capacity (the first loads wait for the length)
+    const int S = min(wave_uniform(S_v), S_max);
+    const int tok_per_chunk = ((max(S, 0) + n_chunks - 1) / n_chunks + 15) & ~15;
+    const int j0 = chunk * tok_per_chunk, j1 = min(S, j0 + tok_per_chunk);
+    Rows R0, R1;
+    load_rows(R0, j0 + slot, max(S - 1, 0));
 
-    // the rotated, pre-scaled query of this KV head's query heads
-    const int qp = q_pos[b];
+    // the rotated, pre-scaled query of these KV heads' query heads
+    const int qp = wave_uniform(qp_v);
     if (tid < kPairs) {
         if (qp >= 0 && qp <= S_max) {
             sCS[tid] = rope[(size_t)qp * kPairs + tid];
@@ -71,14 +79,15 @@ __global__ __launch_bounds__(256) void dense_attend_kernel(const T* __restrict__
         }
     }
     __syncthreads();
-    for (int t = tid; t < G * kPairs; t += 256) {
-        const int p = t & (kPairs - 1), m = t >> 6;
+    for (int t = tid; t < HB * G * kPairs; t += 256) {
+        const int p = t & (kPairs - 1), hm = t >> 6;  // (head of the block, head of its group)
         const int c1 = pair_first(p, rope_style), c2 = pair_second(p, rope_style);
-        const T* qh = q + ((size_t)b * H + kvh * G + m) * kHeadDim;
+        const T* qh = q + ((size_t)b * H + (size_t)h0 * G + hm) * kHeadDim;
         const float a = elem<T>::load(qh + c1), bb = elem<T>::load(qh + c2);
         const float2 cs = sCS[p];
-        sQ[m][c1] = (a * cs.x - bb * cs.y) * scale;
-        sQ[m][c2] = (bb * cs.x + a * cs.y) * scale;
+        float* dst = sQ[hm / G][hm % G];
+        dst[c1] = (a * cs.x - bb * cs.y) * scale;
+        dst[c2] = (bb * cs.x + a * cs.y) * scale;
     }
     __syncthreads();
     float qf[GMAX][NCH][VEC];
@@ -87,7 +96,7 @@ __global__ __launch_bounds__(256) void dense_attend_kernel(const T* __restrict__
 #pragma unroll
         for (int n = 0; n < NCH; ++n)
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) qf[m][n][v] = m < G ? sQ[m][(li + 16 * n) * VEC + v] : 0.f;
+            for (int v = 0; v < VEC; ++v) qf[m][n][v] = m < G ? sQ[hb][m][(li + 16 * n) * VEC + v] : 0.f;
 
     float mx[GMAX], l[GMAX], acc[GMAX][NCH][VEC];
 #pragma unroll
@@ -98,42 +107,64 @@ __global__ __launch_bounds__(256) void dense_attend_kernel(const T* __restrict__
 #pragma unroll
             for (int v = 0; v < VEC; ++v) acc[m][n][v] = 0.f;
     }
-
-    auto consume = [&](const u32x4* kp, const u32x4* vp) {
-        float kf[NCH][VEC], vf[NCH][VEC];
-#pragma unroll
-        for (int n = 0; n < NCH; ++n) { elem<T>::unpack(kp[n], kf[n]); elem<T>::unpack(vp[n], vf[n]); }
+    auto consume = [&](const Rows& R, int j) {
 #pragma unroll
         for (int m = 0; m < GMAX; ++m) {
             if (m < G) {  // uniform
-                float x = 0.f;
+                float x[UT];
 #pragma unroll
-                for (int n = 0; n < NCH; ++n)
+                for (int u = 0; u < UT; ++u) {
+                    x[u] = 0.f;
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) x = fmaf(qf[m][n][v], kf[n][v], x);
-                x = row16_sum(x);
-                const float mn = fmaxf(mx[m], x);
-                const float r = __expf(mx[m] - mn), p = __expf(x - mn);  // exp(-inf) = 0 on the first token
+                    for (int n = 0; n < NCH; ++n) {
+                        float kf[VEC];
+                        elem<T>::unpack(R.k[u][n], kf);
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) x[u] = fmaf(qf[m][n][v], kf[v], x[u]);
+                    }
+                }
+                float mn = mx[m];
+#pragma unroll
+                for (int u = 0; u < UT; ++u) {
+                    x[u] = row16_sum(x[u]);
+                    x[u] = j + u * NS < j1 ? x[u] : -INFINITY;
+                    mn = fmaxf(mn, x[u]);
+                }
+                const float ref = mn > -INFINITY ? mn : 0.f;  // (no token yet)
+                const float r = __expf(mx[m] - ref);
                 mx[m] = mn;
-                l[m] = l[m] * r + p;
+                l[m] *= r;
 #pragma unroll
                 for (int n = 0; n < NCH; ++n)
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) acc[m][n][v] = fmaf(p, vf[n][v], acc[m][n][v] * r);
+                    for (int v = 0; v < VEC; ++v) acc[m][n][v] *= r;
+#pragma unroll
+                for (int u = 0; u < UT; ++u) {
+                    const float p = __expf(x[u] - ref);
+                    l[m] += p;
+#pragma unroll
+                    for (int n = 0; n < NCH; ++n) {
+                        float vf[VEC];
+                        elem<T>::unpack(R.v[u][n], vf);
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) acc[m][n][v] = fmaf(p, vf[v], acc[m][n][v]);
+                    }
+                }
             }
         }
     };
-    // two register sets take turns (a copy between them would wait for the loads it moves)
-    for (int j = j0 + tg; j < j1; j += 32) {
-        load_rows(j + 16, kn, vn);
-        consume(kc, vc);
-        if (j + 16 < j1) {
-            load_rows(j + 32, kc, vc);
-            consume(kn, vn);
+    // two register sets take turns (a copy between them would wait for the loads it moves); trip counts are the chunk's, the
+    // same for every lane group
+    for (int j = j0; j < j1; j += 2 * UT * NS) {
+        if (j + UT * NS < j1) load_rows(R1, j + UT * NS + slot, S - 1);
+        consume(R0, j + slot);
+        if (j + UT * NS < j1) {
+            if (j + 2 * UT * NS < j1) load_rows(R0, j + 2 * UT * NS + slot, S - 1);
+            consume(R1, j + UT * NS + slot);
         }
     }
 
-    // the 16 lane groups of the workgroup, merged in group order by 128 threads (one per channel)
+    // the lane groups of every head, merged in slot order
 #pragma unroll
     for (int m = 0; m < GMAX; ++m) {
         if (m < G) {  // uniform
@@ -144,21 +175,22 @@ __global__ __launch_bounds__(256) void dense_attend_kernel(const T* __restrict__
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) sRed[tg][2 + (li + 16 * n) * VEC + v] = acc[m][n][v];
             __syncthreads();
-            if (tid < kHeadDim) {
-                const int c = tid;
+            for (int t = tid; t < HB * kHeadDim; t += 256) {
+                const int h = t / kHeadDim, c = t % kHeadDim;
+                auto group = [&](int s) { return (s / (4 / HB)) * 4 + (s % (4 / HB)) * HB + h; };
                 float M = -INFINITY;
 #pragma unroll
-                for (int g = 0; g < 16; ++g) M = fmaxf(M, sRed[g][0]);
+                for (int s = 0; s < NS; ++s) M = fmaxf(M, sRed[group(s)][0]);
                 float L = 0.f, A = 0.f;
                 if (M > -INFINITY) {
 #pragma unroll
-                    for (int g = 0; g < 16; ++g) {
-                        const float w = __expf(sRed[g][0] - M);
-                        L = fmaf(sRed[g][1], w, L);
-                        A = fmaf(sRed[g][2 + c], w, A);
+                    for (int s = 0; s < NS; ++s) {
+                        const float w = __expf(sRed[group(s)][0] - M);
+                        L = fmaf(sRed[group(s)][1], w, L);
+                        A = fmaf(sRed[group(s)][2 + c], w, A);
                     }
                 }
-                float* rec = part + (((size_t)b * H + kvh * G + m) * n_chunks + chunk) * kDnRec;
+                float* rec = part + (((size_t)b * H + (size_t)(h0 + h) * G + m) * n_chunks + chunk) * kDnRec;
                 if (c == 0) { rec[0] = M; rec[1] = L; }
                 rec[2 + c] = A;
             }
@@ -166,8 +198,8 @@ __global__ __launch_bounds__(256) void dense_attend_kernel(const T* __restrict__
     }
 }
 
-// out[b,h] = merged chunks / normaliser, rounded once to T.  grid (B*H), 128 threads.  The chunk records are
-// read eight at a time (a loop with one load per round would cost a memory round trip per chunk).
+// out[b,h] = merged chunks / normaliser, rounded once to T.  grid (B*H), 128 threads.  Sixteen chunk records are requested
+// together and merged online (a loop with one load per round would cost a memory round trip per chunk).
 template <typename T>
 __global__ __launch_bounds__(128) void dense_merge_kernel(const float* __restrict__ part, T* __restrict__ out,
                                                           int n_chunks)
@@ -175,29 +207,28 @@ __global__ __launch_bounds__(128) void dense_merge_kernel(const float* __restric
     const size_t bh = blockIdx.x;
     const int c = threadIdx.x;
     const float* rec = part + bh * n_chunks * kDnRec;
-    float M = -INFINITY;
-    for (int k0 = 0; k0 < n_chunks; k0 += 8) {
-        float m8[8];
+    float M = -INFINITY, L = 0.f, A = 0.f;
+    for (int k0 = 0; k0 < n_chunks; k0 += 16) {
+        float m[16], l[16], a[16];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) m8[u] = rec[(size_t)min(k0 + u, n_chunks - 1) * kDnRec];
+        for (int u = 0; u < 16; ++u) {
+            const float* r = rec + (size_t)min(k0 + u, n_chunks - 1) * kDnRec;
+            m[u] = r[0]; l[u] = r[1]; a[u] = r[2 + c];
+        }
+        float mn = M;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) M = fmaxf(M, m8[u]);
-    }
-    float L = 0.f, A = 0.f;
-    if (M > -INFINITY) {
-        for (int k0 = 0; k0 < n_chunks; k0 += 8) {
-            float m8[8], l8[8], a8[8];
+        for (int u = 0; u < 16; ++u) mn = fmaxf(mn, m[u]);  // (a clamped slot repeats the last record)
+        if (mn > -INFINITY) {  // uniform
+            const float w0 = __expf(M - mn);
+            L *= w0;
+            A *= w0;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const float* r = rec + (size_t)min(k0 + u, n_chunks - 1) * kDnRec;
-                m8[u] = r[0]; l8[u] = r[1]; a8[u] = r[2 + c];
+            for (int u = 0; u < 16; ++u) {
+                const float w = k0 + u < n_chunks ? __expf(m[u] - mn) : 0.f;
+                L = fmaf(l[u], w, L);
+                A = fmaf(a[u], w, A);
             }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const float w = k0 + u < n_chunks ? __expf(m8[u] - M) : 0.f;
-                L = fmaf(l8[u], w, L);
-                A = fmaf(a8[u], w, A);
-            }
+            M = mn;
         }
     }
     elem<T>::store(out + bh * kHeadDim + c, L > 0.f ? A / L : 0.f);

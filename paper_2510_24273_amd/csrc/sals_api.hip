@@ -46,7 +46,7 @@ struct Layout {  // byte offsets into the workspace
     int max_parts;               // token tiles per head of the logits kernel, at most
     int pv_tok_per_wg, pv_ntr, pv_waves;  // value-sum token ranges, waves per workgroup (4 | 8)
     int qv_tok_per_wg, qv_ntr;   // quantised-value attention: token ranges
-    int dn_chunks, dn_tok;       // dense baseline: token chunks per sequence, tokens per chunk
+    int dn_chunks, dn_tok;       // dense baseline: token chunks per sequence (overlap score: tokens per chunk)
     int proj_np;                 // D-axis slices of the query projection
     int tm_chunks;               // chunks of the multi-workgroup selection (0: one workgroup per sequence)
     size_t w_section;            // elements per section of the packed weights
@@ -130,6 +130,9 @@ sals_status validate(const sals_desc* d)
     return SALS_OK;
 }
 
+// KV heads per workgroup of the dense baseline (four were no better than two)
+inline int dense_heads(const sals_desc& d) { return d.H_kv % 2 == 0 ? 2 : 1; }
+
 Layout make_layout(const sals_desc& d)
 {
     Layout L{};
@@ -186,9 +189,15 @@ Layout make_layout(const sals_desc& d)
         L.qv_ntr = ceil_div(k_tot, L.qv_tok_per_wg);
         L.qv_part = take((size_t)L.qv_ntr * d.B * d.H_q * kHeadDim * 4);
     }
-    {   // dense baseline: token chunks until about 2048 workgroups stream the cache, 256 tokens at least
-        int n = std::min(kDnMaxChunks, std::max(1, ceil_div(2048, d.B * d.H_kv)));
-        n = std::max(1, std::min(n, d.S_max / 256));
+    {   // dense baseline: token chunks (64 tokens at least) that make whole rounds of one workgroup per compute unit, or of two
+        // where a key is shared by four query heads and more (then the arithmetic wants more waves), as few as do it well
+        const int per = d.B * d.H_kv / dense_heads(d), target = d.H_q / d.H_kv >= 4 ? 512 : 256;
+        int n = 1;
+        double best = 1e30;
+        for (int k = 1; k <= std::min(kDnMaxChunks, std::max(1, d.S_max / 64)); ++k) {
+            const double rounds = (double)k * per / target, cost = std::ceil(rounds) / rounds + 0.01 * k;
+            if (cost < best) { best = cost; n = k; }
+        }
         L.dn_tok = ceil_div(ceil_div(d.S_max, n), 16) * 16;
         L.dn_chunks = ceil_div(d.S_max, L.dn_tok);
         L.dn_part = take((size_t)d.B * d.H_q * L.dn_chunks * kDnRec * 4);
@@ -427,13 +436,20 @@ sals_status launch_dense(const sals_ctx* c, const void* q, const int32_t* q_pos,
     float* part = reinterpret_cast<float*>(c->ws + L.dn_part);
     const float2* rope = reinterpret_cast<const float2*>(c->ws + L.rope);
     const int G = d.H_q / d.H_kv;
-    const dim3 grid(L.dn_chunks, d.H_kv, d.B);
+    const int hb = dense_heads(d);
+    const dim3 grid(L.dn_chunks, d.H_kv / hb, d.B);
     ProfScope ps(c, SALS_K_DENSE, st);
-#define SALS_DENSE(GMAX)                                                                                   \
-    hipLaunchKernelGGL((dense_attend_kernel<T, GMAX>), grid, dim3(256), 0, st, static_cast<const T*>(q), q_pos, \
-                       static_cast<const T*>(K), static_cast<const T*>(V), seq_len, rope, c->inv, part, d.S_max, \
-                       d.H_q, d.H_kv, L.dn_chunks, L.dn_tok, d.rope_style, 1.0f / std::sqrt((float)d.d))
-    if (G <= 1) SALS_DENSE(1); else if (G <= 2) SALS_DENSE(2); else if (G <= 4) SALS_DENSE(4); else SALS_DENSE(8);
+#define SALS_DENSE(GMAX, HB)                                                                               \
+    hipLaunchKernelGGL((dense_attend_kernel<T, GMAX, HB>), grid, dim3(256), 0, st, static_cast<const T*>(q), q_pos, \
+                       static_cast<const T*>(K), static_cast<const T*>(V), seq_len, d.S_max, d.H_q, d.H_kv, L.dn_chunks, \
+                       rope, c->inv, part, d.rope_style, 1.0f / std::sqrt((float)d.d))
+#define SALS_DENSE_G(HB)                                                                                   \
+    do {                                                                                                   \
+        if (G <= 1) SALS_DENSE(1, HB); else if (G <= 2) SALS_DENSE(2, HB);                                  \
+        else if (G <= 4) SALS_DENSE(4, HB); else SALS_DENSE(8, HB);                                        \
+    } while (0)
+    if (hb == 2) SALS_DENSE_G(2); else SALS_DENSE_G(1);
+#undef SALS_DENSE_G
 #undef SALS_DENSE
     if (launch_status() != SALS_OK) return SALS_ERR_HIP;
     hipLaunchKernelGGL((dense_merge_kernel<T>), dim3(d.B * d.H_q), dim3(128), 0, st, part, static_cast<T*>(out),
