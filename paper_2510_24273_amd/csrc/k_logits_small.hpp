@@ -34,7 +34,8 @@ constexpr size_t kLsLds = 2 * (size_t)kLsIterBytes;          // double buffered:
 // FUSED: the kernel also selects.  With one short sequence the selection kernel is a launch of its own that costs more
 // than its work (a dependent launch is worth about 2.3 us, the kernel 4.4 us at 4096 tokens), so here every workgroup
 // of a sequence repeats the selection itself from the scores (S_max <= 4096: eight keys per thread, in LDS that the
-// stage buffers only need later) while its first U_k steps are in flight, and takes its tile from the list; the
+// stage buffers only need later) while its first U_k steps are in flight (requested behind the scores and in three lots:
+// requested first they held up the scores, 7.4 -> 6.1 us to the end of the selection), and takes its tile from the list; the
 // workgroups of KV head 0 write the list and the count to `idx` / `n_sel` for the stages that follow.  The list is the
 // one topk_kernel would have written, entry for entry.
 struct FusedSelect {
@@ -141,15 +142,21 @@ __global__ __launch_bounds__(kLsThreads) void attend_logits_small_kernel(
     // U_k steps requested before the row indices arrive (all of them when the selection runs here first: it takes
     // longer than a load of the list)
     constexpr int EARLY = FUSED ? NST : (NST < 4 ? NST : 4);
+    if constexpr (!FUSED) {
 #pragma unroll
-    for (int s = 0; s < EARLY; ++s) load_a(0, s);
+        for (int s = 0; s < EARLY; ++s) load_a(0, s);
+    }
     if constexpr (FUSED) {
         // the selection, in LDS that the stage buffers take over afterwards
         TopkShared& sh = *reinterpret_cast<TopkShared*>(lds);
         int32_t* s_idx = reinterpret_cast<int32_t*>(lds + ((sizeof(TopkShared) + 255) & ~(size_t)255));  // [k_tot], then the count
         topk_select_sequence<kLsFusedMaxS / (4 * kLsThreads), kLsThreads, true>(
             sh, fs.scores + (size_t)b * S_max, fs.seq_len + b, s_idx, s_idx + kLsFusedMaxK, 0, S_max, fs.top_k, fs.n_sink,
-            fs.n_recent);
+            fs.n_recent, [&](int place) {
+#pragma unroll
+                for (int s = 0; s < NST; ++s)
+                    if (s * 3 / NST == place) load_a(0, s);
+            });
         __syncthreads();
         n_v = s_idx[kLsFusedMaxK];
         idx_my = s_idx[min(my_slot, k_tot - 1)]; idx_e = s_idx[min(e_slot, k_tot - 1)]; idx_0 = s_idx[0];

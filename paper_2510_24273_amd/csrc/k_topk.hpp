@@ -80,11 +80,16 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, TopkShared& sh, 
 // 4*(c*NTH + t) .. +3): with it, selected indices come out in token order inside each score class whatever NTH is,
 // i.e. in the order the 1024-thread kernel with one group per thread produces.
 // `idx` / `n_sel` may point to LDS (the caller reads them after a barrier of its own).
-template <int F4, int NTH = kTopkThreads, bool CONSEC = false>
+// `meanwhile(0)`, `(1)`, `(2)` run once each, in this order, at three places of the selection: loads that the caller issues
+// there arrive while the selection works.  The first place is behind the arrival of the scores, and the loads are spread,
+// because what a compute unit has requested is delivered in order and a wave stands still while its requests queue up.
+struct TopkNoWork { __device__ void operator()(int) const {} };
+template <int F4, int NTH = kTopkThreads, bool CONSEC = false, typename Meanwhile = TopkNoWork>
 __device__ __forceinline__ void topk_select_sequence(TopkShared& sh, const float* __restrict__ scores,
                                                      const int32_t* __restrict__ seq_len,
                                                      int32_t* __restrict__ idx, int32_t* __restrict__ n_sel,
-                                                     int b, int S_max, int top_k, int n_sink, int n_recent)
+                                                     int b, int S_max, int top_k, int n_sink, int n_recent,
+                                                     Meanwhile meanwhile = Meanwhile())
 {
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const int k_tot = top_k + n_sink + n_recent;
@@ -134,18 +139,25 @@ __device__ __forceinline__ void topk_select_sequence(TopkShared& sh, const float
             for (int c = 0; c < (F4 > 0 ? F4 : 1); ++c) load_group(c, raw + 4 * c);
         }
     }
+    // (cleared while the scores are on their way)
+#pragma unroll
+    for (int t = 0; t < kTopkBins / 4; t += NTH)
+        if (kTopkBins / 4 % NTH == 0 || t + tid < kTopkBins / 4) *reinterpret_cast<u32x4*>(&sh.hist[(t + tid) * 4]) = u32x4{0, 0, 0, 0};
+    if (tid < kTopkCand) sh.cand[tid] = 0u;  // key 0 ranks below every candidate
+    if (tid == 0) sh.n_cand = 0u;
     const int S = min(wave_uniform(S_in_v), S_max);
 
     if (S <= k_tot) {  // short cache: every token is selected
         for (int t = tid; t < k_tot; t += NTH) out[t] = t < S ? t : 0;
         if (tid == 0) n_sel[b] = S > 0 ? S : 0;
+        meanwhile(0); meanwhile(1); meanwhile(2);
         return;
     }
     const int lo = n_sink, hi = S - n_recent;
     for (int t = tid; t < n_sink; t += NTH) out[t] = t;
     for (int t = tid; t < n_recent; t += NTH) out[n_sink + top_k + t] = hi + t;
     if (tid == 0) n_sel[b] = k_tot;
-    if (top_k <= 0) return;
+    if (top_k <= 0) { meanwhile(0); meanwhile(1); meanwhile(2); return; }
 
     // candidates are the tokens lo <= j < hi; every other slot carries key 0 (below -inf)
     uint32_t keys[NREG];
@@ -188,9 +200,8 @@ __device__ __forceinline__ void topk_select_sequence(TopkShared& sh, const float
         kmin = wave_min_u32(kmin);
         kmax = wave_max_u32(kmax);
         if (lane == 0) { sh.wave_a[wave] = kmin; sh.wave_b[wave] = kmax; }
-        for (uint32_t t = tid; t < kTopkBins; t += NTH) sh.hist[t] = 0u;
-        if (tid < kTopkCand) sh.cand[tid] = 0u;  // key 0 ranks below every candidate
-        if (tid == 0) sh.n_cand = 0u;
+        __builtin_amdgcn_sched_barrier(0);
+        meanwhile(0);
         __syncthreads();
 #pragma unroll
         for (int w = 0; w < NW; ++w) { kmin = min(kmin, sh.wave_a[w]); kmax = max(kmax, sh.wave_b[w]); }
@@ -222,6 +233,8 @@ __device__ __forceinline__ void topk_select_sequence(TopkShared& sh, const float
             } else {
                 for_each_key([&](uint32_t k, int) { if (k != 0u) atomicAdd(&sh.hist[slot_of(k)], 1u); });
             }
+            __builtin_amdgcn_sched_barrier(0);
+            meanwhile(1);
             __syncthreads();
             uint32_t cnt[BPT], mine = 0u;  // this thread's BPT consecutive slots
 #pragma unroll
@@ -273,6 +286,8 @@ __device__ __forceinline__ void topk_select_sequence(TopkShared& sh, const float
                 need_eq = sh.sel_kk;
                 found = true;
             }
+        } else {
+            meanwhile(1);
         }
     }
 
@@ -320,6 +335,7 @@ __device__ __forceinline__ void topk_select_sequence(TopkShared& sh, const float
     // ---- count, then place ----------------------------------------------------------------
     uint32_t pos_gt = 0u, pos_eq = 0u;
     for_each_key([&](uint32_t k, int) { pos_gt += k > tau; pos_eq += k == tau; });
+    meanwhile(2);
     uint32_t tot_gt, tot_eq;
     block_excl_scan2<NW>(pos_gt, pos_eq, sh, phase, &tot_gt, &tot_eq);
 
