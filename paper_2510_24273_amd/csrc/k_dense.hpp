@@ -7,9 +7,9 @@
 // positions), V [B, S_max, H_kv, d] the values.  A pure HBM stream of 2*S*D_kv elements per
 // sequence.  A workgroup covers a token chunk of one sequence and HB neighbouring KV heads: 16 lanes (one DPP row) own a
 // (token, head) row of K and of V in 16-byte pieces, so with two heads a load of a wave is 512 bytes of a token's row in one
-// piece; the dot product is folded with DPP rotations, softmax runs online per 16-lane group over UT tokens at a time, whose
-// rows are requested together and one set ahead.  The lane groups of a head and then the chunks are merged by
-// log-sum-exp in a fixed order.  One workgroup per compute unit streams best (batch 16, 4096 tokens, 32 heads: 7.0 TB/s;
+// piece; the dot product is folded with DPP rotations, softmax runs online per 16-lane group over UT tokens at a time (one in
+// fp32, where rows are twice as long), whose rows are requested together and one set ahead.  The lane groups of a head and
+// then the chunks are merged by log-sum-exp in a fixed order.  One workgroup per compute unit streams best (batch 16, 4096 tokens, 32 heads: 7.0 TB/s;
 // one head per workgroup, a token at a time, 256-token chunks: 5.9).  Batch 8, 2048 tokens: 50.7 -> 43.4 us with the merge.
 #pragma once
 #include "common.hpp"
@@ -29,10 +29,10 @@ __global__ __launch_bounds__(256) void dense_attend_kernel(const T* __restrict__
                                                            const float2* __restrict__ rope, InvFreq inv,
                                                            float* __restrict__ part, int rope_style, float scale)
 {
-    static_assert(HB == 1 || HB == 2 || HB == 4, "heads of a workgroup share its waves' four lane groups");
+    static_assert(HB == 1 || HB == 2, "heads of a workgroup share its waves' four lane groups");
     constexpr int VEC = elem<T>::vec;
     constexpr int NCH = kHeadDim / (16 * VEC);  // 16-byte pieces per lane and row: 1 (bf16) or 2 (fp32)
-    constexpr int UT = GMAX > 4 || NCH > 1 ? 2 : 4;
+    constexpr int UT = NCH > 1 ? 1 : GMAX > 4 ? 2 : 4;
     constexpr int NS = 16 / HB;                 // token slots of a head
     __shared__ float sQ[HB][GMAX][kHeadDim];
     __shared__ float2 sCS[kPairs];

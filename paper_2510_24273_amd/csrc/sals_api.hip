@@ -130,8 +130,13 @@ sals_status validate(const sals_desc* d)
     return SALS_OK;
 }
 
-// KV heads per workgroup of the dense baseline (four were no better than two)
-inline int dense_heads(const sals_desc& d) { return d.H_kv % 2 == 0 ? 2 : 1; }
+// KV heads per workgroup of the dense baseline: two where that makes 512-byte pieces (four were no better) and the stream is
+// the bound.  fp32 rows of one head are 512 bytes already, and with four query heads per KV head the arithmetic wants the
+// waves apart (batch 1, 65536 tokens, 8 KV heads: 54.9 us with one head, 60.0 with two).
+inline int dense_heads(const sals_desc& d)
+{
+    return d.dtype == SALS_BF16 && d.H_q / d.H_kv < 4 && d.H_kv % 2 == 0 ? 2 : 1;
+}
 
 Layout make_layout(const sals_desc& d)
 {
@@ -190,8 +195,9 @@ Layout make_layout(const sals_desc& d)
         L.qv_part = take((size_t)L.qv_ntr * d.B * d.H_q * kHeadDim * 4);
     }
     {   // dense baseline: token chunks (64 tokens at least) that make whole rounds of one workgroup per compute unit, or of two
-        // where a key is shared by four query heads and more (then the arithmetic wants more waves), as few as do it well
-        const int per = d.B * d.H_kv / dense_heads(d), target = d.H_q / d.H_kv >= 4 ? 512 : 256;
+        // where a key is shared by four query heads and more (then the arithmetic wants more waves) and in fp32 (a token at a
+        // time per lane group), as few as do it well
+        const int per = d.B * d.H_kv / dense_heads(d), target = d.dtype != SALS_BF16 || d.H_q / d.H_kv >= 4 ? 512 : 256;
         int n = 1;
         double best = 1e30;
         for (int k = 1; k <= std::min(kDnMaxChunks, std::max(1, d.S_max / 64)); ++k) {
@@ -443,13 +449,13 @@ sals_status launch_dense(const sals_ctx* c, const void* q, const int32_t* q_pos,
     hipLaunchKernelGGL((dense_attend_kernel<T, GMAX, HB>), grid, dim3(256), 0, st, static_cast<const T*>(q), q_pos, \
                        static_cast<const T*>(K), static_cast<const T*>(V), seq_len, d.S_max, d.H_q, d.H_kv, L.dn_chunks, \
                        rope, c->inv, part, d.rope_style, 1.0f / std::sqrt((float)d.d))
-#define SALS_DENSE_G(HB)                                                                                   \
-    do {                                                                                                   \
-        if (G <= 1) SALS_DENSE(1, HB); else if (G <= 2) SALS_DENSE(2, HB);                                  \
-        else if (G <= 4) SALS_DENSE(4, HB); else SALS_DENSE(8, HB);                                        \
-    } while (0)
-    if (hb == 2) SALS_DENSE_G(2); else SALS_DENSE_G(1);
-#undef SALS_DENSE_G
+    if constexpr (sizeof(T) == 2) {
+        if (hb == 2) { if (G <= 1) SALS_DENSE(1, 2); else if (G <= 2) SALS_DENSE(2, 2); else SALS_DENSE(4, 2); }
+    }
+    if (hb == 1) {
+        if (G <= 1) SALS_DENSE(1, 1); else if (G <= 2) SALS_DENSE(2, 1);
+        else if (G <= 4) SALS_DENSE(4, 1); else SALS_DENSE(8, 1);
+    }
 #undef SALS_DENSE
     if (launch_status() != SALS_OK) return SALS_ERR_HIP;
     hipLaunchKernelGGL((dense_merge_kernel<T>), dim3(d.B * d.H_q), dim3(128), 0, st, part, static_cast<T*>(out),
