@@ -28,6 +28,27 @@ constexpr int kMaxRanges = 8;      // token ranges per sequence (the output proj
 constexpr int kPvMaxTok = 4096;    // tokens per workgroup, at most (their cache rows sit in LDS)
 constexpr int kPvDepth = 4;        // token groups whose loads a wave keeps in flight
 
+// The output projection that follows reads all of U_v once, in a launch of a few microseconds that mostly wait for it.  The
+// value sum leaves many compute units idle: extra workgroups there touch every 64 bytes of U_v (its head blocks dealt to the
+// XCDs as that launch deals them), so the projection finds it in its L2.
+template <typename T>
+__device__ __forceinline__ void warm_projector(const T* __restrict__ Uv, int r, int H_kv, int id, int n, int xcd, int n_threads)
+{
+    const int n_slots = n / kXcds, slot = id / kXcds;  // (n is a multiple of kXcds)
+    const int per_head = kHeadDim * r * (int)sizeof(T) / 64;  // 64-byte pieces
+    const int pieces = (H_kv - xcd + kXcds - 1) / kXcds * per_head;
+    const unsigned char* base = reinterpret_cast<const unsigned char*>(Uv);
+    for (int i0 = slot * n_threads + threadIdx.x; i0 < pieces; i0 += 4 * n_slots * n_threads) {
+        uint32_t w[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {  // (from clamped addresses: requested together)
+            const int i = min(i0 + u * n_slots * n_threads, pieces - 1), k = i / per_head;
+            w[u] = *reinterpret_cast<const uint32_t*>(base + ((size_t)(xcd + k * kXcds) * per_head + (i - k * per_head)) * 64);
+        }
+        asm volatile("" :: "v"(w[0] ^ w[1] ^ w[2] ^ w[3]));  // (the values are of no use; the loads must stay)
+    }
+}
+
 // NW waves (4 or 8), MB blocks of 32 heads.  The range's tokens are dealt to the waves in groups of one MFMA
 // contraction step (16 tokens for bf16, 8 for fp32: half of them per half-wave); a wave works through its groups on
 // its own, no barrier inside the loop, and keeps the loads of kPvDepth groups in flight.
@@ -41,7 +62,8 @@ template <typename T, int NW, int MB>
 __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ n_sel, const float2* __restrict__ stats,
     int B, int r, int n_tr, int n_parts, int tok_per_wg, int k_tot, int H, int lk,
-    const T* __restrict__ Vc, const float* __restrict__ logits, float* __restrict__ Tpart, int S_max, int ring)
+    const T* __restrict__ Vc, const float* __restrict__ logits, float* __restrict__ Tpart, int S_max, int ring,
+    const T* __restrict__ Uv, int H_kv)
 {
     static_assert((NW == 4 || NW == 8) && (MB == 1 || MB == 2), "four or eight waves, one or two head blocks");
     constexpr int kPvThreads = NW * 64;
@@ -60,7 +82,11 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
     // the list, so the column blocks of one token range (same indices, logits and statistics, adjacent
     // 128-byte pieces of the same cache rows) meet in one L2.
     const int n_cb = r / kPvCols;
-    const int total = n_cb * n_tr * B;  // = gridDim.x
+    const int total = n_cb * n_tr * B;
+    if ((int)blockIdx.x >= total) {  // (uniform)
+        warm_projector<T>(Uv, r, H_kv, blockIdx.x - total, gridDim.x - total, blockIdx.x % kXcds, kPvThreads);
+        return;
+    }
     const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds, qn = total / kXcds, rem = total % kXcds;
     const int item = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + slot;
     const int cb = item % n_cb, tr = (item / n_cb) % n_tr, b = item / (n_cb * n_tr);
@@ -250,127 +276,156 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
 // ---------------------------------------------------------------------------------
 // output projection: y[(b,h), c] = sum_i T[(b,h), i] U_v[g*128 + c, i]
 //
-// One workgroup per (KV head, 16 output channels, tile of 16 rows): 8 x H_kv x ceil(B*G/16)
-// workgroups, so that the pass over U_v is spread over the whole chip.  16x16 MFMA tiles: rows are the (sequence,
-// head of the group) pairs, columns the channels; the latent axis is split over the four
-// waves, every wave issuing all of its loads as one batch.
+// One workgroup per (KV head, 16 output channels, tile of up to 16 rows): 8 x H_kv x ceil(B*G/16)
+// workgroups, so that the pass over U_v is spread over the whole chip.  16x16 MFMA tiles, columns the channels; the latent
+// axis is dealt to the eight waves.  A row is a (sequence, head of the group) pair; with fewer than 16 of them (R = 1, 2, 4, 8)
+// the tile's rows are the pairs of 16 / R token ranges, whose products the fold adds up: one load then serves that many ranges.
+//
+// A few KB per workgroup: the kernel is one memory round trip if every load is requested before the first is used, and
+// little code (each launch starts with cold instruction caches).  So a wave requests BATCH latent steps of U_v with RPR
+// loads of T each in one batch, from clamped addresses and without a branch (predicated loads were waited for one by one).
+// Inside the launch, one sequence, 32 heads, r = 640, 4 ranges: 5.1 -> 2.6 us (0.8 of it by warm_projector); 16 sequences, one
+// range: 4.7 -> 3.4 us; one sequence, 8 KV heads, 8 ranges: 6.3 -> 3.6 us.
 // ---------------------------------------------------------------------------------
-// BATCH latent steps of loads and RPR token ranges are in flight per round and wave: (8,2) covers any rank, (5,3)
-// and (4,4) merge more ranges per memory round trip when a wave has at most 5 / 4 steps.
-template <typename T, int BATCH, int RPR>
-__global__ __launch_bounds__(256) void attend_out_kernel(const T* __restrict__ Uv, const float* __restrict__ Tpart,
-                                                         T* __restrict__ out,
-                                                         int B, int r, int H, int H_kv, int n_tr,
-                                                         const T* __restrict__ Uv2, const float* __restrict__ Tpart2,
-                                                         int r2, int n_tr2)
+constexpr int kOutWaves = 8;
+// one cache's share of the contraction, as a wave walks it
+template <typename T, int BATCH, int RPR> struct OutPass {
+    static constexpr int VEC = elem<T>::vec, KS = 4 * VEC;  // latent coordinates per MFMA step
+    const T* U;           // the workgroup's first channel row (scalar)
+    const float* Tp;      // range 0 (scalar)
+    uint32_t lane_u, lane_t, tstride;
+    int nks, n_tr, q, sub, ks0, t0;  // q ranges per load; this lane's is number sub of them
+    u32x4 bf[BATCH];
+    f32x4 x[BATCH][RPR][VEC / 4];
+
+    __device__ void start(const T* U_, const float* Tp_, int r, int bh, int BH, int n_tr_, int q_, int sub_, int l16, int kg,
+                          int wave)
+    {
+        U = U_; Tp = Tp_; nks = r / KS; n_tr = n_tr_; q = q_; sub = sub_; ks0 = wave; t0 = 0;
+        lane_u = l16 * r + kg * VEC; lane_t = bh * r + kg * VEC; tstride = (uint32_t)BH * r;
+        load();
+    }
+    __device__ void load()
+    {
+        size_t t_at[RPR];
+#pragma unroll
+        for (int w = 0; w < RPR; ++w) t_at[w] = (size_t)min(t0 + w * q + sub, n_tr - 1) * tstride + lane_t;
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const int kk = min(ks0 + kOutWaves * u, nks - 1) * KS;
+            bf[u] = ld16(U + kk + lane_u);
+#pragma unroll
+            for (int w = 0; w < RPR; ++w)
+#pragma unroll
+                for (int v = 0; v < VEC / 4; ++v)
+                    x[u][w][v] = *reinterpret_cast<const f32x4*>(Tp + kk + 4 * v + t_at[w]);
+        }
+    }
+    // every batch of this pass; the first has been loaded
+    __device__ void run(f32x4v& acc)
+    {
+        for (;;) {
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                f32x4 s[VEC / 4];  // this step of T: the partial sums of this lane's ranges, in range order
+#pragma unroll
+                for (int v = 0; v < VEC / 4; ++v) {
+                    s[v] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int w = 0; w < RPR; ++w) {
+                        const bool use = t0 + w * q + sub < n_tr;
+                        s[v].x += use ? x[u][w][v].x : 0.f; s[v].y += use ? x[u][w][v].y : 0.f;
+                        s[v].z += use ? x[u][w][v].z : 0.f; s[v].w += use ? x[u][w][v].w : 0.f;
+                    }
+                }
+                if (ks0 + kOutWaves * u < nks) {  // uniform
+                    if constexpr (sizeof(T) == 2) {
+                        const float t[8] = {s[0].x, s[0].y, s[0].z, s[0].w, s[1].x, s[1].y, s[1].z, s[1].w};
+                        uint32_t hw[8], lw[8];
+#pragma unroll
+                        for (int v = 0; v < 8; ++v) {
+                            hw[v] = f32_to_bf16(t[v]);
+                            lw[v] = f32_to_bf16(t[v] - bf16_to_f32((bf16_t)hw[v]));
+                        }
+                        mma16_op<T>::run(u32x4{hw[0] | (hw[1] << 16), hw[2] | (hw[3] << 16), hw[4] | (hw[5] << 16),
+                                               hw[6] | (hw[7] << 16)}, bf[u], acc);
+                        mma16_op<T>::run(u32x4{lw[0] | (lw[1] << 16), lw[2] | (lw[3] << 16), lw[4] | (lw[5] << 16),
+                                               lw[6] | (lw[7] << 16)}, bf[u], acc);
+                    } else {
+                        mma16_op<T>::run(u32x4{__float_as_uint(s[0].x), __float_as_uint(s[0].y), __float_as_uint(s[0].z),
+                                               __float_as_uint(s[0].w)}, bf[u], acc);
+                    }
+                }
+            }
+            ks0 += kOutWaves * BATCH;
+            if (ks0 >= nks) {
+                ks0 %= kOutWaves;
+                t0 += RPR * q;
+                if (t0 >= n_tr) break;
+            }
+            load();
+            asm volatile("" ::: "memory");
+        }
+    }
+};
+
+// BATCH2 > 0: two caches of different rank share the output (recent window beside the low-rank cache); the first loads of
+// both are in flight together
+template <typename T, int BATCH, int RPR, int BATCH2>
+__global__ __launch_bounds__(64 * kOutWaves) void attend_out_kernel(const T* __restrict__ Uv, const float* __restrict__ Tpart,
+                                                                    int B, int r, int H, int H_kv, int n_tr, int R, int r2,
+                                                                    int n_tr2, const T* __restrict__ Uv2,
+                                                                    const float* __restrict__ Tpart2, T* __restrict__ out)
 {
-    constexpr int VEC = elem<T>::vec;
-    constexpr int KS = 4 * VEC;  // latent coordinates per MFMA step
-    constexpr bool kSplit = sizeof(T) == 2;
-    __shared__ __attribute__((aligned(16))) float red[3][64][5];
+    constexpr int NW = kOutWaves;
+    __shared__ float red[NW][16][17];  // [wave][row of the tile][channel]
 
     // KV head fastest: workgroup ids are dealt round-robin to the XCDs, so the eight channel blocks of
     // a head (which read the same value sums) share one XCD's L2 whenever H_kv is a multiple of 8
     const int g = blockIdx.x, cb = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, kg = lane >> 4;
     const int G = H / H_kv;
     const int n_rows = B * G;  // (sequence, head of this group) pairs
+    const int row0 = blockIdx.z * R;  // this workgroup's rows: R = 1, 2, 4, 8 or 16 of them
+    const int row = min(row0 + (l16 & (R - 1)), n_rows - 1);  // (rows past the last one repeat it and are not stored)
+    const int bh = row / G * H + g * G + row % G, q = 16 / R, sub = l16 / R;
+    const size_t c0 = (size_t)g * kHeadDim + cb * 16;
 
-    {
-        const int row0 = blockIdx.z * 16;  // this workgroup's tile of 16 rows
-        const int row = row0 + l16;
-        const bool row_ok = row < n_rows;
-        const int bb = row_ok ? row / G : 0, h = row_ok ? g * G + row % G : 0;
-        f32x4v acc = {0.f, 0.f, 0.f, 0.f};
-        // A second pair (value sums of another latent cache, its projector) is added into the same output when
-        // r2 > 0: the recent window's higher-rank cache beside the low-rank one.
-        for (int pass = 0; pass < (r2 > 0 ? 2 : 1); ++pass) {
-        const T* const Uv_p = pass ? Uv2 : Uv;
-        const float* const Tpart_p = pass ? Tpart2 : Tpart;
-        const int r_p = pass ? r2 : r, n_tr_p = pass ? n_tr2 : n_tr;
-        const int nks = r_p / KS;
-        const T* urow = Uv_p + ((size_t)g * kHeadDim + cb * 16 + l16) * r_p + kg * VEC;
-        const size_t tstride = (size_t)B * H * r_p;
-        const size_t trow = ((size_t)bb * H + h) * r_p + kg * VEC;
-        for (int ks0 = wave; ks0 < nks; ks0 += 4 * BATCH) {  // this wave: ks0, ks0+4, ...
-            u32x4 bf[BATCH], ah[BATCH], al[BATCH];
-            float tm[BATCH][VEC];  // T of this lane's row: the token ranges' partial sums, added in range order
+    f32x4v acc = {0.f, 0.f, 0.f, 0.f};
+    OutPass<T, BATCH, RPR> p1;
+    p1.start(Uv + c0 * r, Tpart, r, bh, B * H, n_tr, q, sub, l16, kg, wave);
+    if constexpr (BATCH2 > 0) {
+        OutPass<T, BATCH2, 1> p2;
+        p2.start(Uv2 + c0 * r2, Tpart2, r2, bh, B * H, n_tr2, q, sub, l16, kg, wave);
+        asm volatile("" ::: "memory");  // (keeps the loads above from being sunk towards their first use)
+        p1.run(acc);
+        p2.run(acc);
+    } else {
+        asm volatile("" ::: "memory");
+        p1.run(acc);
+    }
+    // acc[v] is tile row 4*kg+v, channel l16: add the rows that are ranges of one pair (they differ by a multiple of R) ...
+    if (R <= 8)
 #pragma unroll
-            for (int u = 0; u < BATCH; ++u) {
-                const int ks = ks0 + 4 * u;
-                bf[u] = ks < nks ? ld16(urow + ks * KS) : u32x4{0, 0, 0, 0};
+        for (int v = 0; v < 4; ++v) acc[v] += __shfl_xor(acc[v], 32, kWave);
+    if (R <= 4)
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) tm[u][v] = 0.f;
-            }
-            // RPR ranges per round, the loads of all BATCH steps in flight together
-            for (int t0 = 0; t0 < n_tr_p; t0 += RPR) {
-                f32x4 x[BATCH][RPR][VEC / 4];
+        for (int v = 0; v < 4; ++v) acc[v] += __shfl_xor(acc[v], 16, kWave);
+    if (R <= 2) { acc[0] += acc[2]; acc[1] += acc[3]; }
+    if (R == 1) acc[0] += acc[1];
+    // ... and the waves' latent shares, in order
 #pragma unroll
-                for (int u = 0; u < BATCH; ++u) {
-                    const int ks = ks0 + 4 * u;
+    for (int v = 0; v < 4; ++v) red[wave][kg * 4 + v][l16] = acc[v];
+    __syncthreads();
+    if (tid < R * 16) {
+        const int m = tid >> 4, c = tid & 15, orow = row0 + m;
+        float y = red[0][m][c];
 #pragma unroll
-                    for (int w = 0; w < RPR; ++w)
-#pragma unroll
-                        for (int v = 0; v < VEC / 4; ++v)
-                            x[u][w][v] = (ks < nks && row_ok && t0 + w < n_tr_p)
-                                             ? *reinterpret_cast<const f32x4*>(Tpart_p + (size_t)(t0 + w) * tstride + trow +
-                                                                               ks * KS + 4 * v)
-                                             : f32x4{0.f, 0.f, 0.f, 0.f};
-                }
-#pragma unroll
-                for (int u = 0; u < BATCH; ++u)
-#pragma unroll
-                    for (int w = 0; w < RPR; ++w)
-#pragma unroll
-                        for (int v = 0; v < VEC / 4; ++v) {
-                            tm[u][4 * v] += x[u][w][v].x; tm[u][4 * v + 1] += x[u][w][v].y;
-                            tm[u][4 * v + 2] += x[u][w][v].z; tm[u][4 * v + 3] += x[u][w][v].w;
-                        }
-            }
-#pragma unroll
-            for (int u = 0; u < BATCH; ++u) {
-                if constexpr (kSplit) {
-                    uint32_t hw[8], lw[8];
-#pragma unroll
-                    for (int v = 0; v < 8; ++v) {
-                        bf16_t ph = f32_to_bf16(tm[u][v]);
-                        hw[v] = ph;
-                        lw[v] = f32_to_bf16(tm[u][v] - bf16_to_f32(ph));
-                    }
-                    ah[u] = u32x4{hw[0] | (hw[1] << 16), hw[2] | (hw[3] << 16), hw[4] | (hw[5] << 16),
-                                  hw[6] | (hw[7] << 16)};
-                    al[u] = u32x4{lw[0] | (lw[1] << 16), lw[2] | (lw[3] << 16), lw[4] | (lw[5] << 16),
-                                  lw[6] | (lw[7] << 16)};
-                } else {
-                    ah[u] = u32x4{__float_as_uint(tm[u][0]), __float_as_uint(tm[u][1]), __float_as_uint(tm[u][2]),
-                                  __float_as_uint(tm[u][3])};
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < BATCH; ++u) {
-                mma16_op<T>::run(ah[u], bf[u], acc);
-                if constexpr (kSplit) mma16_op<T>::run(al[u], bf[u], acc);
-            }
-        }
-        }
-        // fold the four latent slices (waves) in order; acc[v] is tile row 4*kg+v, channel l16
-        __syncthreads();
-        if (wave > 0) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) red[wave - 1][lane][v] = acc[v];
-        }
-        __syncthreads();
-        if (wave == 0) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                float y = acc[v] + red[0][lane][v] + red[1][lane][v] + red[2][lane][v];
-                int orow = row0 + kg * 4 + v;
-                if (orow < n_rows) {
-                    int ob = orow / G, oh = g * G + orow % G;
-                    elem<T>::store(out + ((size_t)ob * H + oh) * kHeadDim + cb * 16 + l16, y);
-                }
-            }
+        for (int w = 1; w < NW; ++w) y += red[w][m][c];
+        if (orow < n_rows) {
+            const int ob = orow / G, oh = g * G + orow % G;
+            elem<T>::store(out + ((size_t)ob * H + oh) * kHeadDim + cb * 16 + c, y);
         }
     }
 }

@@ -600,6 +600,30 @@ template <typename T> sals_status allow_logits_lds(const LogitsPlan& P, int grou
     return ok ? SALS_OK : SALS_ERR_HIP;
 }
 
+// Output projection.  The loads of a wave (BATCH latent steps x RPR groups of token ranges) follow what there is, so that the
+// usual ranks need one memory round trip and few loads are repeated.  r2 > 0: a second cache of that rank beside the first.
+template <typename T>
+void launch_out(hipStream_t st, const sals_desc& d, int n_tr, const T* Uv, const float* tpart, int r2, int n_tr2, const T* Uv2,
+                const float* tpart2, void* out)
+{
+    const int n_rows = d.B * (d.H_q / d.H_kv);
+    int R = 1;
+    while (R < 16 && R < n_rows) R *= 2;
+    const int spw = ceil_div(d.r / (4 * elem<T>::vec), kOutWaves), loads = ceil_div(n_tr, 16 / R);
+    const dim3 grid(d.H_kv, kHeadDim / 16, ceil_div(n_rows, R));
+#define SALS_OUT(BATCH, RPR, BATCH2)                                                                                      \
+    hipLaunchKernelGGL((attend_out_kernel<T, BATCH, RPR, BATCH2>), grid, dim3(64 * kOutWaves), 0, st, Uv, tpart, d.B, d.r, \
+                       d.H_q, d.H_kv, n_tr, R, r2, n_tr2, Uv2, tpart2, static_cast<T*>(out))
+#define SALS_OUT_L(BATCH, BATCH2)                                                                                         \
+    do { if (loads > 1) SALS_OUT(BATCH, 2, BATCH2); else SALS_OUT(BATCH, 1, BATCH2); } while (0)
+    if (r2 > 0) SALS_OUT_L(3, 8);
+    else if (spw <= 2) SALS_OUT_L(2, 0);
+    else if (spw <= 3) SALS_OUT_L(3, 0);
+    else SALS_OUT_L(4, 0);
+#undef SALS_OUT_L
+#undef SALS_OUT
+}
+
 template <typename T>
 sals_status launch_attend(const sals_ctx* c, const void* q, const int32_t* q_pos, const void* Kc,
                           const void* Vc, const void* W, const int32_t* idx, const int32_t* n_sel, void* out,
@@ -709,10 +733,14 @@ sals_status launch_attend(const sals_ctx* c, const void* q, const int32_t* q_pos
     if (phases & kPhaseValue) {
         ProfScope ps(c, SALS_K_ATTEND_PV, st);
         const int n_items = (d.r / kPvCols) * L.pv_ntr * d.B;
+        // idle compute units warm U_v, up to what the launch can read beside its own loads (measured: 5 MB cost it nothing
+        // and save the next launch 0.8 us, 8 MB cost what they save)
+        const size_t uv_bytes = (size_t)d.H_kv * kHeadDim * d.r * sizeof(T);
+        const int n_warm = n_items < 256 && uv_bytes <= (size_t)6 << 20 ? (256 - n_items) / kXcds * kXcds : 0;
 #define SALS_PV(NW, MB)                                                                                            \
-    hipLaunchKernelGGL((attend_pv_kernel<T, NW, MB>), dim3(n_items), dim3(NW * 64), 0, st, idx, n_sel, stats_all, d.B, \
+    hipLaunchKernelGGL((attend_pv_kernel<T, NW, MB>), dim3(n_items + n_warm), dim3(NW * 64), 0, st, idx, n_sel, stats_all, d.B, \
                        d.r, L.pv_ntr, stats_stride, L.pv_tok_per_wg, k_tot, d.H_q, L.lk, static_cast<const T*>(Vc),    \
-                       logits, tpart, d.S_max, ring)
+                       logits, tpart, d.S_max, ring, w_section<T>(c, W, 3), d.H_kv)
         if (d.H_q <= 32) { if (L.pv_waves == 8) SALS_PV(8, 1); else SALS_PV(4, 1); }
         else { if (L.pv_waves == 8) SALS_PV(8, 2); else SALS_PV(4, 2); }
 #undef SALS_PV
@@ -720,18 +748,7 @@ sals_status launch_attend(const sals_ctx* c, const void* q, const int32_t* q_pos
     if (launch_status() != SALS_OK) return SALS_ERR_HIP;
     if (phases & kPhaseOut) {
         ProfScope ps(c, SALS_K_ATTEND_OUT, st);
-        // steps of the latent axis per wave decide how many token ranges fit in one round of loads
-        const int spw = ceil_div(d.r / (4 * elem<T>::vec), 4);
-        const dim3 grid(d.H_kv, kHeadDim / 16, ceil_div(d.B * (d.H_q / d.H_kv), 16));
-#define SALS_OUT(BATCH, RPR)                                                                                     \
-    hipLaunchKernelGGL((attend_out_kernel<T, BATCH, RPR>), grid, dim3(256), 0, st, w_section<T>(c, W, 3), tpart, \
-                       static_cast<T*>(out), d.B, d.r, d.H_q, d.H_kv, L.pv_ntr, static_cast<const T*>(nullptr),     \
-                       static_cast<const float*>(nullptr), 0, 0)
-        if (sizeof(T) == 2 && spw <= 4 && L.pv_ntr > 2) SALS_OUT(4, 4);
-        else if (sizeof(T) == 2 && spw <= 5 && L.pv_ntr > 2) SALS_OUT(5, 3);
-        else SALS_OUT(8, 2);
-#undef SALS_OUT
-
+        launch_out<T>(st, d, L.pv_ntr, w_section<T>(c, W, 3), tpart, 0, 0, nullptr, nullptr, out);
     }
     return launch_status();
 }
@@ -1240,17 +1257,14 @@ sals_status window_attend(sals_ctx* ctx, sals_ctx* win, const void* q, const int
     }
     {
         ProfScope ps(ctx, SALS_K_ATTEND_OUT, st);
-        const dim3 grid(d.H_kv, kHeadDim / 16, ceil_div(d.B * (d.H_q / d.H_kv), 16));
         const float* t_lo = reinterpret_cast<const float*>(ctx->ws + ctx->L.tpart);
         const float* t_hi = reinterpret_cast<const float*>(win->ws + win->L.tpart);
         if (bf)
-            hipLaunchKernelGGL((attend_out_kernel<bf16_t, 8, 2>), grid, dim3(256), 0, st, w_section<bf16_t>(ctx, W, 3), t_lo,
-                               static_cast<bf16_t*>(out), d.B, d.r, d.H_q, d.H_kv, ctx->L.pv_ntr,
-                               w_section<bf16_t>(win, W_hi, 3), t_hi, win->d.r, win->L.pv_ntr);
+            launch_out<bf16_t>(st, d, ctx->L.pv_ntr, w_section<bf16_t>(ctx, W, 3), t_lo, win->d.r, win->L.pv_ntr,
+                               w_section<bf16_t>(win, W_hi, 3), t_hi, out);
         else
-            hipLaunchKernelGGL((attend_out_kernel<float, 8, 2>), grid, dim3(256), 0, st, w_section<float>(ctx, W, 3), t_lo,
-                               static_cast<float*>(out), d.B, d.r, d.H_q, d.H_kv, ctx->L.pv_ntr,
-                               w_section<float>(win, W_hi, 3), t_hi, win->d.r, win->L.pv_ntr);
+            launch_out<float>(st, d, ctx->L.pv_ntr, w_section<float>(ctx, W, 3), t_lo, win->d.r, win->L.pv_ntr,
+                              w_section<float>(win, W_hi, 3), t_hi, out);
     }
     return launch_status();
 }
