@@ -18,7 +18,11 @@
 // are in flight.
 //
 // Wave tile: 128 head dims (4 MFMA row blocks, in RoPE pair order) x 32*NB tokens.
-// Workgroup: HEADS x NTG waves, i.e. HEADS heads x (NTG*32*NB) tokens.
+// Workgroup: HEADS x NTG waves, i.e. HEADS heads x (NTG*32*NB) tokens.  Two shapes: two heads x 256 tokens (8 waves) where that
+// fills the chip: the least operand traffic per product, the matrix cores' power is the bound; one head x 128 tokens
+// (4 waves, two workgroups per compute unit) for the launches in between that and the 64-token kernel, where idle compute
+// units and the feed from the L2 are the bound (one sequence, 32 heads, 1024 tokens, r = 640, attention in all: 26.2 -> 20.6 us;
+// 8 KV heads, 4160 tokens, r = 512: 28.8 -> 26.1; 12 sequences, 8 KV heads, 512 tokens: 29.5 -> 27.5).
 #pragma once
 #include "common.hpp"
 #include "k_attend.hpp"
@@ -56,9 +60,9 @@ template <int HEADS, int NTG, int NB> struct logits_cfg {
 // of 4): the LDS reads and the reductions of a block's heads are in flight together instead of one head after the other.
 // GFIX: the group size when it is known at compile time (1 and 4, the common ones; 0: read from the arguments), which
 // takes the per-block branches out of the epilogue.
-// MULTI: a tile of NTG x 64 tokens is made of the (at most 64 token) selections of NTG consecutive SEQUENCES, one per
-// token group, instead of 256 tokens of one sequence: short selections such as a recent window then share one pass
-// over the head's projector among NTG sequences.  Each token group has its own query, count, index list and cache;
+// MULTI: a tile is made of the (at most 64 token) selections of consecutive SEQUENCES, 64 slots each, instead of as many
+// tokens of one sequence: short selections such as a recent window then share one pass over the head's projector among
+// the sequences of a tile.  Each sequence has its own query, count, index list and cache;
 // the latent axis may be cut into `ksplit` slices (the logit is additive over latent coordinates), whose partial
 // logits go to `plogits` for logits_finish_kernel.
 template <typename T, int HEADS, int NTG, int NB, int GB, int GFIX, bool MULTI = false>
@@ -71,8 +75,9 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
     float* __restrict__ plogits, int ksplit)
 {
     typedef logits_cfg<HEADS, NTG, NB> C;
-    static_assert(!MULTI || (HEADS == 1 && NB * 32 == 64), "a token group is one sequence's 64 slots");
-    constexpr int SQ = MULTI ? NTG : 1;   // sequences per tile
+    static_assert(!MULTI || (HEADS == 1 && NB <= 2), "a sequence's 64 slots are those of one or two waves");
+    constexpr int SQ = MULTI ? C::TOK / 64 : 1;   // sequences per tile
+    constexpr int WT = NB * 32;                   // tokens per wave
     constexpr int NT = C::NT, NA = C::NA, NBP = C::NBP, NCS = C::NCS;
     constexpr int ES = (int)sizeof(T);
     static_assert(C::A_BYTES % (16 * NT) == 0 && C::B_BYTES % (16 * NT) == 0 && C::CS_BYTES % (16 * NT) == 0,
@@ -88,13 +93,13 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
     int b, g0, part, kz = 0;   // MULTI: b is the first sequence of the tile
     if constexpr (MULTI) {
         // list order (head, sequence group, latent slice): an XCD's range keeps a few heads' projector slices
-        const int nb4 = (B + NTG - 1) / NTG, N = nb4 * H_kv * ksplit;
+        const int nsg = (B + SQ - 1) / SQ, N = nsg * H_kv * ksplit;
         const int id = blockIdx.x, xcd = id % kXcds, slot = id / kXcds;
         const int qn = N / kXcds, rem = N % kXcds;
         const int w = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + slot;
-        g0 = w / (nb4 * ksplit);
-        const int rest = w - g0 * (nb4 * ksplit);
-        b = (rest / ksplit) * NTG; kz = rest % ksplit; part = 0;
+        g0 = w / (nsg * ksplit);
+        const int rest = w - g0 * (nsg * ksplit);
+        b = (rest / ksplit) * SQ; kz = rest % ksplit; part = 0;
     } else {
         const int n_y = H_kv / HEADS, N = n_parts * n_y * B;
         const int id = blockIdx.x, xcd = id % kXcds, slot = id / kXcds;
@@ -112,12 +117,12 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hi = lane >> 5;
     const int hh = wave / NTG, tg = wave % NTG;   // head of the tile, token group
-    // sequence of tile token t (MULTI: token group t / 64 is sequence b + t / 64; groups past the batch repeat the last
-    // sequence and get no weight)
+    // sequence of tile token t (MULTI: sequence b + t / 64; sequences past the batch repeat the last one and get no weight)
+    const int sw = MULTI ? tg * WT / 64 : 0;  // this wave's sequence within the tile
     auto seq_of = [&](int t) { return MULTI ? min(b + (t >> 6), B - 1) : b; };
-    // count and query position: of this wave's sequence (MULTI: wave = token group; the position is needed per thread
+    // count and query position: of this wave's sequence (MULTI: the position is needed per thread
     // for the thread's share of the cos/sin rows, see rotate_query)
-    const int n_v = ld_uniform_i32(n_sel + (MULTI ? seq_of(tg * 64) : b));
+    const int n_v = ld_uniform_i32(n_sel + (MULTI ? seq_of(tg * WT) : b));
     const int qpos_v = MULTI ? q_pos[seq_of(tid & ~63)] : ld_uniform_i32(q_pos + b);  // in flight with the loads below
     const int G = GFIX > 0 ? GFIX : H / H_kv;
     const int g = g0 + hh;
@@ -182,8 +187,8 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
 #pragma unroll
             for (int i = 0; i < NA; ++i) load_a(i, st);
         }
-    // MULTI: a token group past the batch has no tokens
-    const int n = (MULTI && b + tg >= B) ? 0 : wave_uniform(n_v);
+    // MULTI: a sequence past the batch has no tokens
+    const int n = (MULTI && b + sw >= B) ? 0 : wave_uniform(n_v);
     const int qpos = MULTI ? qpos_v : wave_uniform(qpos_v);
     if (!MULTI && tok0 >= n) {  // no selected token in this tile: neutral statistics
         if (tid < HEADS * G)
@@ -365,8 +370,8 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
                         f32x4 q1[GB], q2[GB];
 #pragma unroll
                         for (int mi = 0; mi < GB; ++mi) {
-                            q1[mi] = *reinterpret_cast<const f32x4*>(&sQ[MULTI ? tg : hh][m0 + mi][p0]);
-                            q2[mi] = *reinterpret_cast<const f32x4*>(&sQ[MULTI ? tg : hh][m0 + mi][kPairs + p0]);
+                            q1[mi] = *reinterpret_cast<const f32x4*>(&sQ[MULTI ? sw : hh][m0 + mi][p0]);
+                            q2[mi] = *reinterpret_cast<const f32x4*>(&sQ[MULTI ? sw : hh][m0 + mi][kPairs + p0]);
                         }
 #pragma unroll
                         for (int mi = 0; mi < GB; ++mi)
@@ -383,9 +388,9 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
 
     bool ok[NB];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) ok[nb] = (MULTI ? nb * 32 + l32 : tok0 + (tg * NB + nb) * 32 + l32) < n;
-    const int bs = MULTI ? seq_of(tg * 64) : b;          // sequence of this wave's tokens
-    const bool seq_real = !MULTI || b + tg < B;          // (a token group past the batch writes nothing)
+    for (int nb = 0; nb < NB; ++nb) ok[nb] = (MULTI ? (tg * WT & 63) + nb * 32 + l32 : tok0 + (tg * NB + nb) * 32 + l32) < n;
+    const int bs = MULTI ? seq_of(tg * WT) : b;          // sequence of this wave's tokens
+    const bool seq_real = !MULTI || b + sw < B;          // (a sequence past the batch writes nothing)
 #pragma unroll
     for (int m0 = 0; m0 < kGroupEnd; m0 += GB) {
         if (GFIX > 0 || m0 < G) {  // uniform
@@ -397,7 +402,7 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
             for (int mi = 0; mi < GB; ++mi)
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) {
-                    const int slot = MULTI ? nb * 32 + l32 : tok0 + (tg * NB + nb) * 32 + l32;
+                    const int slot = MULTI ? (tg * WT & 63) + nb * 32 + l32 : tok0 + (tg * NB + nb) * 32 + l32;
                     const size_t at = ((size_t)bs * H + g * G + m0 + mi) * lk + slot;
                     if (MULTI && ksplit > 1) {  // uniform: this slice's share of the logit
                         if (hi == 0 && slot < lk && seq_real) plogits[(size_t)kz * B * H * lk + at] = dot[m0 + mi][nb];
@@ -426,24 +431,20 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
             for (int mi = 0; mi < GB; ++mi) se[mi] = wave_sum(se[mi]);
             if (lane == 0) {
 #pragma unroll
-                for (int mi = 0; mi < GB; ++mi) {
-                    if constexpr (MULTI) {  // a token group is the whole (single) tile of its sequence
-                        if (seq_real) stats[((size_t)bs * H + (size_t)g * G + m0 + mi) * stats_stride + part] = make_float2(mx[mi], se[mi]);
-                    } else {
-                        sStat[hh][tg][m0 + mi] = make_float2(mx[mi], se[mi]);
-                    }
-                }
+                for (int mi = 0; mi < GB; ++mi) sStat[hh][tg][m0 + mi] = make_float2(mx[mi], se[mi]);
             }
         }
     }
-    if constexpr (MULTI) return;
+    if (MULTI && ksplit > 1) return;  // uniform
     __syncthreads();
-    if (tid < HEADS * G) {
-        const int h2 = tid / G, m = tid - h2 * G;
-        float2 st = sStat[h2][0][m];
+    // the waves' statistics, merged in wave order: those of a head, or (MULTI) of a sequence, whose single tile this is
+    constexpr int WS = MULTI ? 64 / WT : NTG;  // waves to merge
+    if (tid < (MULTI ? SQ : HEADS) * G) {
+        const int u = tid / G, m = tid - u * G, bt = MULTI ? b + u : b, h2 = MULTI ? 0 : u;
+        float2 st = sStat[h2][MULTI ? u * WS : 0][m];
 #pragma unroll
-        for (int t = 1; t < NTG; ++t) st = stat_merge(st, sStat[h2][t][m]);
-        stats[((size_t)b * H + (size_t)(g0 + h2) * G + m) * stats_stride + part] = st;
+        for (int t = 1; t < WS; ++t) st = stat_merge(st, sStat[h2][(MULTI ? u * WS : 0) + t][m]);
+        if (!MULTI || bt < B) stats[((size_t)bt * H + (size_t)(g0 + h2) * G + m) * stats_stride + part] = st;
     }
 }
 

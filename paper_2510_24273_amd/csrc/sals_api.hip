@@ -57,7 +57,7 @@ struct Layout {  // byte offsets into the workspace
 
 struct ProfRecord { int kernel; hipEvent_t start, stop; };
 
-// which logits kernel a context's shape gets: 1 = 2 heads x 256 tokens, 2 = 1 head x 256 tokens, 3 = 1 head x 64
+// which logits kernel a context's shape gets: 1 = 2 heads x 256 tokens, 2 = 1 head x 128 tokens, 3 = 1 head x 64
 // tokens (then: slices of the latent axis per tile, 128-byte steps loaded ahead); n_parts = token tiles per head
 struct LogitsPlan { int pick, n_parts, ksplit, nst; };
 
@@ -493,19 +493,22 @@ template <typename T> LogitsPlan plan_logits(const sals_desc& d)
     if (allow_split && n_wg1 <= 128)
         for (int ks = kLsMaxSplit; ks >= 2; ks /= 2)
             if (n_wg1 * ks <= 256 && nkc128 % ks == 0 && nkc128 / ks >= 2) { P.ksplit = ks; break; }
-    // Estimated duration of each kernel for this shape, from measured per-step and per-workgroup figures (microseconds):
-    // a 256-token tile walks the latent axis in 64-byte steps of 0.88 us (two heads) or 0.65 us (one head) whatever
-    // part of the tile is filled, workgroups beyond one per compute unit queue up, and the epilogue grows with the
-    // query heads per KV head; a 64-token tile is bound by pulling its operands (the head's projector slice and 64
-    // rows) into the compute unit at about 51 GB/s.
+    // Estimated duration of each kernel for this shape: microseconds per 64-byte step of the latent axis and around the
+    // loop, and G = query heads per KV head in the epilogue, fitted to 70 measured shapes (of 53 in bf16 and 17 in fp32 one
+    // got a kernel that was not its fastest, by 4 %).  Workgroups beyond one per compute unit queue up or share it, which
+    // takes as long.  fp32 is bound by its matrix instructions.
+    constexpr bool bf = sizeof(T) == 2;
+    const double steps = (double)d.r * sizeof(T) / kLgStep, G = (double)(d.H_q / d.H_kv);
+    auto rounds = [](long long n) { return (double)((n + 255) / 256); };
+    auto t_big = [&](long long n) { return rounds(n) * steps * (bf ? 0.65 : 3.5) + 2.1 + 0.7 * G; };  // 2 heads x 256 tokens
+    auto t_mid = [&](long long n, int ks) {  // 1 head x 128 tokens
+        return rounds(n * ks) * steps / ks * (bf ? 0.26 : 0.93) + 3.3 + 0.35 * G + (ks > 1 ? 2.4 : 0.0);
+    };
+    auto t_small = [&](long long n, int ks) {  // 1 head x 64 tokens
+        return rounds(n * ks) * (steps / ks * (bf ? 0.29 : 0.59) + 1.3 + 0.33 * G) + (ks > 1 ? 2.4 : 0.0);
+    };
     {
-        const double steps = (double)d.r * sizeof(T) / kLgStep, G = (double)(d.H_q / d.H_kv);
-        auto rounds = [](long long n) { return (double)((n + 255) / 256); };
-        const double over = 4.0 + 2.2 * G;
-        const double t1 = d.H_kv % 2 == 0 ? rounds(n_wg(2, 256)) * steps * 0.88 + over : 1e30;
-        const double t2 = rounds(n_wg(1, 256)) * steps * 0.65 + over;
-        const double bytes3 = (double)(kHeadDim + kLsTok) * d.r * sizeof(T) / P.ksplit;
-        const double t3 = rounds(n_wg1 * P.ksplit) * (bytes3 / 51e3 + 3.0 + 0.3 * G) + (P.ksplit > 1 ? 3.0 : 0.0);
+        const double t1 = d.H_kv % 2 == 0 ? t_big(n_wg(2, 256)) : 1e30, t2 = t_mid(n_wg(1, 128), 1), t3 = t_small(n_wg1, P.ksplit);
         P.pick = t1 <= t2 && t1 <= t3 ? 1 : (t2 <= t3 ? 2 : 3);
     }
     if (const char* e = std::getenv("SALS_TUNE_LOGITS")) {  // tuning aid: 1 | 2 | 3
@@ -513,31 +516,27 @@ template <typename T> LogitsPlan plan_logits(const sals_desc& d)
         if (v == 1 && d.H_kv % 2 == 0) P.pick = 1;
         if (v == 2 || v == 3) P.pick = v;
     }
-    // A selection of at most 64 tokens per sequence (a recent window) in a batch: tiles of four sequences' selections,
-    // 256 tokens against one pass over the head's projector, the latent axis cut until the launch fills the chip.
-    // Estimated like the one-head 256-token tile (0.57 us per step measured at such shapes, 8 us around the loop, 4 us
-    // for the finishing launch of a split).
+    // A selection of at most 64 tokens per sequence (a recent window) in a batch: tiles of two sequences' selections,
+    // 128 tokens against one pass over the head's projector, the latent axis cut until the launch fills the chip.
     const char* const force = std::getenv("SALS_TUNE_LOGITS");  // tuning aid: "4" asks for these tiles at any batch
     const bool forced4 = force && std::atoi(force) == 4;
-    if (k_tot <= 64 && ((P.pick == 3 && d.B >= 8) || forced4)) {
-        const int steps = d.r * (int)sizeof(T) / kLgStep;
-        const long long tiles = (long long)ceil_div(d.B, 4) * d.H_kv;
+    if (k_tot <= 64 && (d.B >= 8 || forced4)) {
+        const int n_steps = d.r * (int)sizeof(T) / kLgStep;
+        const long long tiles = (long long)ceil_div(d.B, 2) * d.H_kv;
         int ks = 1;
-        while (ks < kLsMaxSplit && tiles * ks < 256 && steps % (2 * ks) == 0 && steps / (2 * ks) >= 8) ks *= 2;
+        // (one workgroup per compute unit, or two where that leaves long slices: 16 sequences, 32 heads, r = 2048: 118 -> 116 us)
+        while (ks < kLsMaxSplit && tiles * ks < 512 && n_steps % (2 * ks) == 0 && n_steps / (2 * ks) >= (tiles * ks < 256 ? 8 : 24)) ks *= 2;
         if (const char* e = std::getenv("SALS_TUNE_MULTI_KSPLIT")) {  // tuning aid: any divisor of the step count up to 8
             const int v = std::atoi(e);
-            if (v >= 1 && v <= kLsMaxSplit && steps % v == 0) ks = v;
+            if (v >= 1 && v <= kLsMaxSplit && n_steps % v == 0) ks = v;
         }
-        const double t4 = (double)((tiles * ks + 255) / 256) * ((double)steps / ks * 0.57 + 8.0) + (ks > 1 ? 4.0 : 0.0);
-        const double bytes3 = (double)(kHeadDim + kLsTok) * d.r * sizeof(T);
-        const double t3 = (double)((n_wg1 + 255) / 256) * (bytes3 / 51e3 + 3.0 + 0.3 * (d.H_q / d.H_kv));
-        if (t4 < t3 || forced4) {
+        if (forced4 || t_mid(tiles, ks) < t_small(n_wg1, P.ksplit)) {
             P.pick = 4; P.n_parts = 1; P.ksplit = ks;
             return P;
         }
     }
     if (P.pick != 3) {
-        P.n_parts = ceil_div(k_tot, 256);
+        P.n_parts = ceil_div(k_tot, P.pick == 2 ? 128 : 256);
         P.ksplit = 1;
         return P;
     }
@@ -591,8 +590,8 @@ template <typename T> sals_status allow_logits_lds(const LogitsPlan& P, int grou
     };
     bool ok = true;
     if (P.pick == 1) ok = allow(reinterpret_cast<const void*>(logits_kernel_for<T, 2, 4, 2>(group)), logits_cfg<2, 4, 2>::LDS);
-    else if (P.pick == 2) ok = allow(reinterpret_cast<const void*>(logits_kernel_for<T, 1, 4, 2>(group)), logits_cfg<1, 4, 2>::LDS);
-    else if (P.pick == 4) ok = allow(reinterpret_cast<const void*>(logits_kernel_for<T, 1, 4, 2, true>(group)), logits_cfg<1, 4, 2>::LDS);
+    else if (P.pick == 2) ok = allow(reinterpret_cast<const void*>(logits_kernel_for<T, 1, 4, 1>(group)), logits_cfg<1, 4, 1>::LDS);
+    else if (P.pick == 4) ok = allow(reinterpret_cast<const void*>(logits_kernel_for<T, 1, 4, 1, true>(group)), logits_cfg<1, 4, 1>::LDS);
     else {
         ok = allow(reinterpret_cast<const void*>(SmallLogits<T>::get(P.nst, false)), kLsLds) &&
              allow(reinterpret_cast<const void*>(SmallLogits<T>::get(P.nst, true)), kLsLds);
@@ -662,12 +661,12 @@ sals_status launch_attend(const sals_ctx* c, const void* q, const int32_t* q_pos
     } while (0)
         const int pick = P.pick;
         if (pick == 1) SALS_LOGITS(2, 4, 2);        // 2 heads x 256 tokens, 8 waves
-        else if (pick == 2) SALS_LOGITS(1, 4, 2);   // 1 head  x 256 tokens
-        else if (pick == 4) {  // four sequences' short selections per 256-token tile, latent axis in P.ksplit slices
-            typedef logits_cfg<1, 4, 2> LC;
-            auto kern = logits_kernel_for<T, 1, 4, 2, true>(d.H_q / d.H_kv);
+        else if (pick == 2) SALS_LOGITS(1, 4, 1);   // 1 head  x 128 tokens
+        else if (pick == 4) {  // two sequences' short selections per 128-token tile, latent axis in P.ksplit slices
+            typedef logits_cfg<1, 4, 1> LC;
+            auto kern = logits_kernel_for<T, 1, 4, 1, true>(d.H_q / d.H_kv);
             float* plogits = reinterpret_cast<float*>(c->ws + L.plogits);
-            hipLaunchKernelGGL(kern, dim3(ceil_div(d.B, 4) * d.H_kv * P.ksplit), dim3(LC::NT), LC::LDS, st,
+            hipLaunchKernelGGL(kern, dim3(ceil_div(d.B, 2) * d.H_kv * P.ksplit), dim3(LC::NT), LC::LDS, st,
                                static_cast<const T*>(Kc), w_section<T>(c, W, 2), idx, n_sel, static_cast<const T*>(q), q_pos,
                                rope, c->inv, logits, stats, d.B, d.S_max, d.r, d.H_q, d.H_kv, k_tot, L.lk, 1, heads_fastest,
                                d.rope_style, 1.0f / std::sqrt((float)d.d), ring, stats_stride, plogits, P.ksplit);

@@ -103,6 +103,15 @@ def test_sixty_four_query_heads(oracle):
         _run(oracle, w, seq_lens=[500, 129], label=f"H=64 H_kv={H_kv}")
 
 
+@pytest.mark.parametrize("dtype,H_kv,top_k", [("bf16", 32, 127), ("bf16", 8, 129), ("bf16", 3, 260), ("f32", 8, 128)])
+def test_logits_tiles_of_128_tokens(oracle, dtype, H_kv, top_k, monkeypatch):
+    """The logits kernel's one-head, 128-token tiles (forced here at a small shape): selections one short of a tile, just
+    past one and several tiles, sequences that fill none, part and all of the last tile, an odd number of heads."""
+    monkeypatch.setenv("SALS_TUNE_LOGITS", "2")
+    w = synth.shrink(SMALL, B=4, S=700, H=4 * H_kv if H_kv < 16 else H_kv, H_kv=H_kv, top_k=top_k, dtype=dtype, plant=0)
+    _run(oracle, w, seq_lens=[700, top_k, 128, 5], label=f"128-token tiles {dtype} H_kv={H_kv} k={top_k}")
+
+
 def test_truncated_scoring_rank(oracle):
     w = synth.shrink(SMALL, r=256, r_score=128, B=2)
     _run(oracle, w, seq_lens=[1000, 500])
