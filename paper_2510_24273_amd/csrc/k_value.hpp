@@ -58,12 +58,20 @@ __device__ __forceinline__ void warm_projector(const T* __restrict__ Uv, int r, 
 // tokens, a half-wave thus a whole 128-byte piece per token, and two byte permutes per token pair turn the eight words
 // into the operand of the even column and the operand of the odd column: the transposition never leaves the
 // registers.  fp32 (two tokens per MFMA, one per half-wave): the loaded words are the operands as they are.
-template <typename T, int NW, int MB>
+//
+// TWO: a second cache under the same softmax (the recent window beside the low-rank cache) takes the workgroups behind the
+// first cache's: two launches of a few dozen workgroups each would follow one another for nothing (one sequence: 10.8 -> 5.7 us).
+// Otherwise the workgroups behind warm the output projection's U_v.
+template <typename T> struct PvSecond {
+    const int32_t* idx; const int32_t* n_sel; const T* Vc; const float* logits; float* Tpart;
+    int r, n_tr, tok_per_wg, k_tot, lk, S_max, ring;
+};
+template <typename T, int NW, int MB, bool TWO>
 __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ n_sel, const float2* __restrict__ stats,
     int B, int r, int n_tr, int n_parts, int tok_per_wg, int k_tot, int H, int lk,
     const T* __restrict__ Vc, const float* __restrict__ logits, float* __restrict__ Tpart, int S_max, int ring,
-    const T* __restrict__ Uv, int H_kv)
+    const T* __restrict__ Uv, int H_kv, PvSecond<T> second)
 {
     static_assert((NW == 4 || NW == 8) && (MB == 1 || MB == 2), "four or eight waves, one or two head blocks");
     constexpr int kPvThreads = NW * 64;
@@ -81,13 +89,20 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
     // Workgroup ids are dealt round-robin to the XCDs; the map below gives each XCD a contiguous run of
     // the list, so the column blocks of one token range (same indices, logits and statistics, adjacent
     // 128-byte pieces of the same cache rows) meet in one L2.
-    const int n_cb = r / kPvCols;
-    const int total = n_cb * n_tr * B;
-    if ((int)blockIdx.x >= total) {  // (uniform)
-        warm_projector<T>(Uv, r, H_kv, blockIdx.x - total, gridDim.x - total, blockIdx.x % kXcds, kPvThreads);
-        return;
+    int n_cb = r / kPvCols, total = n_cb * n_tr * B, id = blockIdx.x;
+    if (id >= total) {  // (uniform)
+        if constexpr (TWO) {
+            id -= total;
+            idx = second.idx; n_sel = second.n_sel; Vc = second.Vc; logits = second.logits; Tpart = second.Tpart;
+            r = second.r; n_tr = second.n_tr; tok_per_wg = second.tok_per_wg; k_tot = second.k_tot; lk = second.lk;
+            S_max = second.S_max; ring = second.ring;
+            n_cb = r / kPvCols; total = n_cb * n_tr * B;
+        } else {
+            warm_projector<T>(Uv, r, H_kv, id - total, gridDim.x - total, id % kXcds, kPvThreads);
+            return;
+        }
     }
-    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds, qn = total / kXcds, rem = total % kXcds;
+    const int xcd = id % kXcds, slot = id / kXcds, qn = total / kXcds, rem = total % kXcds;
     const int item = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + slot;
     const int cb = item % n_cb, tr = (item / n_cb) % n_tr, b = item / (n_cb * n_tr);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -599,6 +599,40 @@ template <typename T> sals_status allow_logits_lds(const LogitsPlan& P, int grou
     return ok ? SALS_OK : SALS_ERR_HIP;
 }
 
+// Value sum over the selected tokens of a cache, and of a second one under the same softmax (the recent window).
+struct PvPass { const sals_ctx* c; const int32_t* idx; const int32_t* n_sel; const void* Vc; int ring; };
+template <typename T>
+void launch_pv(const sals_ctx* c, const float2* stats, int stats_stride, const PvPass& a, const PvPass* b, const T* Uv,
+               hipStream_t st)
+{
+    const sals_desc& d = c->d;
+    ProfScope ps(c, SALS_K_ATTEND_PV, st);
+    auto of = [](const PvPass& p) {
+        const sals_desc& e = p.c->d;
+        const Layout& L = p.c->L;
+        return PvSecond<T>{p.idx, p.n_sel, static_cast<const T*>(p.Vc), reinterpret_cast<const float*>(p.c->ws + L.logits),
+                           reinterpret_cast<float*>(p.c->ws + L.tpart), e.r, L.pv_ntr, L.pv_tok_per_wg,
+                           e.top_k + e.n_sink + e.n_recent, L.lk, e.S_max, p.ring};
+    };
+    const PvSecond<T> f = of(a), g = b ? of(*b) : PvSecond<T>{};
+    const int n_items = f.r / kPvCols * f.n_tr * d.B;
+    // idle compute units warm U_v, up to what the launch can read beside its own loads (measured: 5 MB cost it nothing
+    // and save the next launch 0.8 us, 8 MB cost what they save)
+    const size_t uv_bytes = (size_t)d.H_kv * kHeadDim * d.r * sizeof(T);
+    const int n_more = b ? g.r / kPvCols * g.n_tr * d.B
+                         : (n_items < 256 && uv_bytes <= (size_t)6 << 20 ? (256 - n_items) / kXcds * kXcds : 0);
+#define SALS_PV(NW, MB, TWO)                                                                                              \
+    hipLaunchKernelGGL((attend_pv_kernel<T, NW, MB, TWO>), dim3(n_items + n_more), dim3(NW * 64), 0, st, f.idx, f.n_sel,   \
+                       stats, d.B, f.r, f.n_tr, stats_stride, f.tok_per_wg, f.k_tot, d.H_q, f.lk, f.Vc, f.logits, f.Tpart, \
+                       f.S_max, f.ring, Uv, d.H_kv, g)
+#define SALS_PV_B(NW, MB) do { if (b) SALS_PV(NW, MB, true); else SALS_PV(NW, MB, false); } while (0)
+    const bool w8 = a.c->L.pv_waves == 8 || (b && b->c->L.pv_waves == 8);
+    if (d.H_q <= 32) { if (w8) SALS_PV_B(8, 1); else SALS_PV_B(4, 1); }
+    else { if (w8) SALS_PV_B(8, 2); else SALS_PV_B(4, 2); }
+#undef SALS_PV_B
+#undef SALS_PV
+}
+
 // Output projection.  The loads of a wave (BATCH latent steps x RPR groups of token ranges) follow what there is, so that the
 // usual ranks need one memory round trip and few loads are repeated.  r2 > 0: a second cache of that rank beside the first.
 template <typename T>
@@ -729,21 +763,8 @@ sals_status launch_attend(const sals_ctx* c, const void* q, const int32_t* q_pos
         }
         return launch_status();
     }
-    if (phases & kPhaseValue) {
-        ProfScope ps(c, SALS_K_ATTEND_PV, st);
-        const int n_items = (d.r / kPvCols) * L.pv_ntr * d.B;
-        // idle compute units warm U_v, up to what the launch can read beside its own loads (measured: 5 MB cost it nothing
-        // and save the next launch 0.8 us, 8 MB cost what they save)
-        const size_t uv_bytes = (size_t)d.H_kv * kHeadDim * d.r * sizeof(T);
-        const int n_warm = n_items < 256 && uv_bytes <= (size_t)6 << 20 ? (256 - n_items) / kXcds * kXcds : 0;
-#define SALS_PV(NW, MB)                                                                                            \
-    hipLaunchKernelGGL((attend_pv_kernel<T, NW, MB>), dim3(n_items + n_warm), dim3(NW * 64), 0, st, idx, n_sel, stats_all, d.B, \
-                       d.r, L.pv_ntr, stats_stride, L.pv_tok_per_wg, k_tot, d.H_q, L.lk, static_cast<const T*>(Vc),    \
-                       logits, tpart, d.S_max, ring, w_section<T>(c, W, 3), d.H_kv)
-        if (d.H_q <= 32) { if (L.pv_waves == 8) SALS_PV(8, 1); else SALS_PV(4, 1); }
-        else { if (L.pv_waves == 8) SALS_PV(8, 2); else SALS_PV(4, 2); }
-#undef SALS_PV
-    }
+    if (phases & kPhaseValue)
+        launch_pv<T>(c, stats_all, stats_stride, PvPass{c, idx, n_sel, Vc, ring}, nullptr, w_section<T>(c, W, 3), st);
     if (launch_status() != SALS_OK) return SALS_ERR_HIP;
     if (phases & kPhaseOut) {
         ProfScope ps(c, SALS_K_ATTEND_OUT, st);
@@ -1246,13 +1267,17 @@ sals_status window_attend(sals_ctx* ctx, sals_ctx* win, const void* q, const int
     if (p_lo.n_parts + p_hi.n_parts > ctx->L.max_parts) return SALS_ERR_UNSUPPORTED;
     float2* shared = reinterpret_cast<float2*>(ctx->ws + ctx->L.stats);
     const StatsLink l_lo{shared, p_lo.n_parts + p_hi.n_parts, 0}, l_hi{shared, p_lo.n_parts + p_hi.n_parts, p_lo.n_parts};
-    for (int phase : {(int)kPhaseLogits, (int)kPhaseValue}) {
-        s = bf ? launch_attend<bf16_t>(ctx, q, q_pos, Kc, Vc, W, idx, n_lo, nullptr, st, nullptr, 0, phase, &l_lo)
-               : launch_attend<float>(ctx, q, q_pos, Kc, Vc, W, idx, n_lo, nullptr, st, nullptr, 0, phase, &l_lo);
-        if (s != SALS_OK) return s;
-        s = bf ? launch_attend<bf16_t>(win, q, q_pos, Kw, Vw, W_hi, idx_hi, n_hi, nullptr, st, nullptr, w, phase, &l_hi)
-               : launch_attend<float>(win, q, q_pos, Kw, Vw, W_hi, idx_hi, n_hi, nullptr, st, nullptr, w, phase, &l_hi);
-        if (s != SALS_OK) return s;
+    s = bf ? launch_attend<bf16_t>(ctx, q, q_pos, Kc, Vc, W, idx, n_lo, nullptr, st, nullptr, 0, kPhaseLogits, &l_lo)
+           : launch_attend<float>(ctx, q, q_pos, Kc, Vc, W, idx, n_lo, nullptr, st, nullptr, 0, kPhaseLogits, &l_lo);
+    if (s != SALS_OK) return s;
+    s = bf ? launch_attend<bf16_t>(win, q, q_pos, Kw, Vw, W_hi, idx_hi, n_hi, nullptr, st, nullptr, w, kPhaseLogits, &l_hi)
+           : launch_attend<float>(win, q, q_pos, Kw, Vw, W_hi, idx_hi, n_hi, nullptr, st, nullptr, w, kPhaseLogits, &l_hi);
+    if (s != SALS_OK) return s;
+    {
+        const PvPass lo{ctx, idx, n_lo, Vc, 0}, hi{win, idx_hi, n_hi, Vw, w};
+        if (bf) launch_pv<bf16_t>(ctx, shared, l_lo.stride, lo, &hi, nullptr, st);
+        else launch_pv<float>(ctx, shared, l_lo.stride, lo, &hi, nullptr, st);
+        if (launch_status() != SALS_OK) return SALS_ERR_HIP;
     }
     {
         ProfScope ps(ctx, SALS_K_ATTEND_OUT, st);
