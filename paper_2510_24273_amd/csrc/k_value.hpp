@@ -26,7 +26,6 @@ constexpr int kPvCols = 64;        // latent columns per workgroup
 constexpr int kPvMaxHeads = 64;    // H_q limit of these kernels
 constexpr int kMaxRanges = 8;      // token ranges per sequence (the output projection adds them up)
 constexpr int kPvMaxTok = 4096;    // tokens per workgroup, at most (their cache rows sit in LDS)
-constexpr int kPvDepth = 4;        // token groups whose loads a wave keeps in flight
 
 // The output projection that follows reads all of U_v once, in a launch of a few microseconds that mostly wait for it.  The
 // value sum leaves many compute units idle: extra workgroups there touch every 64 bytes of U_v (its head blocks dealt to the
@@ -51,7 +50,8 @@ __device__ __forceinline__ void warm_projector(const T* __restrict__ Uv, int r, 
 
 // NW waves (4 or 8), MB blocks of 32 heads.  The range's tokens are dealt to the waves in groups of one MFMA
 // contraction step (16 tokens for bf16, 8 for fp32: half of them per half-wave); a wave works through its groups on
-// its own, no barrier inside the loop, and keeps the loads of kPvDepth groups in flight.
+// its own, no barrier inside the loop, and keeps the loads of DEPTH groups in flight (2 or 4, by what a wave has: the first
+// are requested unconditionally, so that waiting for the statistics requested before them does not wait for them too).
 //
 // The MFMA's second operand wants, per lane, consecutive TOKENS of one column, while memory holds consecutive
 // columns of one token.  bf16: lane l32 fetches the 32-bit word (columns 2 l32, 2 l32 + 1) of each of its eight
@@ -66,7 +66,7 @@ template <typename T> struct PvSecond {
     const int32_t* idx; const int32_t* n_sel; const T* Vc; const float* logits; float* Tpart;
     int r, n_tr, tok_per_wg, k_tot, lk, S_max, ring;
 };
-template <typename T, int NW, int MB, bool TWO>
+template <typename T, int NW, int MB, int DEPTH, bool TWO>
 __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ n_sel, const float2* __restrict__ stats,
     int B, int r, int n_tr, int n_parts, int tok_per_wg, int k_tot, int H, int lk,
@@ -83,7 +83,8 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
 
     __shared__ __attribute__((aligned(16))) int sRow[kPvMaxTok];  // cache row of every token of the nominal range
     __shared__ float2 sMZ[kPvMaxHeads];      // per head: softmax maximum, 1 / normaliser
-    __shared__ float red[NW][64][17];        // cross-wave sums, after the loop
+    constexpr int NBR = NW == 4 ? 2 : 1;     // column blocks per pass of the cross-wave sums
+    __shared__ float red[NBR][NW][64][17];   // cross-wave sums, after the loop
 
     // Work items are ordered (sequence, token range, column block) with the column block fastest.
     // Workgroup ids are dealt round-robin to the XCDs; the map below gives each XCD a contiguous run of
@@ -119,12 +120,13 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
         const int pos = min(max(v, 0), S_max - 1);
         sRow[t] = ring > 0 ? pos % ring : pos;  // ring cache: token t lies in row t mod ring
     }
-    const int sh = tid >> 2, sub = tid & 3;     // four lanes share a head's tiles
+    constexpr int LPH = kPvThreads / kPvMaxHeads;   // lanes that share a head's tiles
+    const int sh = tid / LPH, sub = tid % LPH;
     float2 st8[8];
     {
         const float2* sp = stats + ((size_t)b * H + min(sh, H - 1)) * n_parts;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) st8[u] = sub + 4 * u < n_parts ? sp[sub + 4 * u] : make_float2(-INFINITY, 0.f);
+        for (int u = 0; u < 8; ++u) st8[u] = sp[min(sub + LPH * u, n_parts - 1)];  // (clamped: no load in a branch)
     }
     __syncthreads();  // rows of the range in LDS
 
@@ -156,30 +158,36 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
             for (int v = 0; v < VEC / 4; ++v) S.X[mb][v] = *reinterpret_cast<const f32x4*>(lg + off + 4 * v);
         }
     };
-    Stage S[kPvDepth];
+    Stage S[DEPTH];
 #pragma unroll
-    for (int u = 0; u < kPvDepth; ++u)
-        if (wave + NW * u <= g_last) g_load(S[u], wave + NW * u);  // (the count is not known yet: nominal groups)
+    for (int u = 0; u < DEPTH; ++u) g_load(S[u], wave + NW * u);  // (the count is not known yet: nominal groups)
 
     // softmax maximum and normaliser of every head, merged in a fixed order (under the loads above)
     {
-        float2 st = make_float2(-INFINITY, 0.f);
-        if (sh < H) {
+        // (eight at a time: the maximum first, then eight exponentials that do not wait for each other)
+        auto merge8 = [&](float2* e, int t0) {
+            float m = -INFINITY, z = 0.f;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) st = stat_merge(st, st8[u]);
-            const float2* sp = stats + ((size_t)b * H + sh) * n_parts;
-            for (int t0 = sub + 32; t0 < n_parts; t0 += 32) {  // (more than 32 tiles: further rounds of eight loads)
-                float2 e[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    e[u] = t0 + 4 * u < n_parts ? sp[t0 + 4 * u] : make_float2(-INFINITY, 0.f);
-#pragma unroll
-                for (int u = 0; u < 8; ++u) st = stat_merge(st, e[u]);
+            for (int u = 0; u < 8; ++u) {
+                e[u].x = t0 + LPH * u < n_parts ? e[u].x : -INFINITY;
+                m = fmaxf(m, e[u].x);
             }
+            const float ref = m > -INFINITY ? m : 0.f;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) z += e[u].x > -INFINITY ? e[u].y * __expf(e[u].x - ref) : 0.f;
+            return make_float2(m, z);
+        };
+        float2 st = merge8(st8, sub);
+        const float2* sp = stats + ((size_t)b * H + min(sh, H - 1)) * n_parts;
+        for (int t0 = sub + 8 * LPH; t0 - sub < n_parts; t0 += 8 * LPH) {  // (more tiles: further rounds of eight loads)
+            float2 e[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) e[u] = sp[min(t0 + LPH * u, n_parts - 1)];
+            st = stat_merge(st, merge8(e, t0));
         }
-        st = stat_merge(st, make_float2(__shfl_xor(st.x, 1, kWave), __shfl_xor(st.y, 1, kWave)));
-        st = stat_merge(st, make_float2(__shfl_xor(st.x, 2, kWave), __shfl_xor(st.y, 2, kWave)));
-        if (sub == 0 && sh < kPvMaxHeads) sMZ[sh] = make_float2(st.x > -INFINITY ? st.x : 0.f, st.y > 0.f ? 1.f / st.y : 0.f);
+#pragma unroll
+        for (int o = 1; o < LPH; o <<= 1) st = stat_merge(st, make_float2(__shfl_xor(st.x, o, kWave), __shfl_xor(st.y, o, kWave)));
+        if (sub == 0) sMZ[sh] = make_float2(st.x > -INFINITY ? st.x : 0.f, st.y > 0.f ? 1.f / st.y : 0.f);
     }
     __syncthreads();
     float2 mz[MB];
@@ -253,16 +261,16 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
             }
         }
     };
-    for (int i0 = 0; wave + NW * i0 < n_groups; i0 += kPvDepth) {
+    for (int i0 = 0; wave + NW * i0 < n_groups; i0 += DEPTH) {
 #pragma unroll
-        for (int u = 0; u < kPvDepth; ++u) {
+        for (int u = 0; u < DEPTH; ++u) {
             const int g = wave + NW * (i0 + u);  // wave-uniform
             if (g < n_groups) do_group(S[u], g);
-            if (g + NW * kPvDepth < n_groups) g_load(S[u], g + NW * kPvDepth);
+            if (g + NW * DEPTH < n_groups) g_load(S[u], g + NW * DEPTH);
         }
     }
 
-    // The waves' sums, one (head block, column block) at a time, added in wave order; wave w finishes 16 / NW of a
+    // The waves' sums, NBR column blocks of a head block at a time, added in wave order; wave w finishes 16 / NW of a
     // lane's 16 values.  acc[mb][nb][4a+c] is head mb*32 + 8a + 4hi + c; its column is 2 l32 + nb (bf16: even / odd
     // operand) or nb*32 + l32 (fp32).
     float* out_t = Tpart + (((size_t)tr * B + b) * H) * r;
@@ -270,20 +278,25 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-            if (mb + nb > 0) __syncthreads();
+        for (int nb0 = 0; nb0 < 2; nb0 += NBR) {
+            if (mb + nb0 > 0) __syncthreads();
 #pragma unroll
-            for (int v = 0; v < 16; ++v) red[wave][lane][v] = acc[mb][nb][v];
+            for (int k = 0; k < NBR; ++k)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) red[k][wave][lane][v] = acc[mb][nb0 + k][v];
             __syncthreads();
-            const int col = col0 + (kSplit ? 2 * l32 + nb : nb * 32 + l32);
 #pragma unroll
-            for (int c = 0; c < PER; ++c) {
-                const int v = wave * PER + c;
-                const int h = mb * 32 + (v >> 2) * 8 + hi * 4 + (v & 3);
-                float sum = red[0][lane][v];
+            for (int k = 0; k < NBR; ++k) {
+                const int col = col0 + (kSplit ? 2 * l32 + nb0 + k : (nb0 + k) * 32 + l32);
 #pragma unroll
-                for (int w = 1; w < NW; ++w) sum += red[w][lane][v];
-                if (h < H) out_t[(size_t)h * r + col] = sum;
+                for (int c = 0; c < PER; ++c) {
+                    const int v = wave * PER + c;
+                    const int h = mb * 32 + (v >> 2) * 8 + hi * 4 + (v & 3);
+                    float sum = red[k][0][lane][v];
+#pragma unroll
+                    for (int w = 1; w < NW; ++w) sum += red[k][w][lane][v];
+                    if (h < H) out_t[(size_t)h * r + col] = sum;
+                }
             }
         }
 }

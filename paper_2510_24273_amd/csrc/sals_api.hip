@@ -621,14 +621,18 @@ void launch_pv(const sals_ctx* c, const float2* stats, int stats_stride, const P
     const size_t uv_bytes = (size_t)d.H_kv * kHeadDim * d.r * sizeof(T);
     const int n_more = b ? g.r / kPvCols * g.n_tr * d.B
                          : (n_items < 256 && uv_bytes <= (size_t)6 << 20 ? (256 - n_items) / kXcds * kXcds : 0);
-#define SALS_PV(NW, MB, TWO)                                                                                              \
-    hipLaunchKernelGGL((attend_pv_kernel<T, NW, MB, TWO>), dim3(n_items + n_more), dim3(NW * 64), 0, st, f.idx, f.n_sel,   \
-                       stats, d.B, f.r, f.n_tr, stats_stride, f.tok_per_wg, f.k_tot, d.H_q, f.lk, f.Vc, f.logits, f.Tpart, \
-                       f.S_max, f.ring, Uv, d.H_kv, g)
-#define SALS_PV_B(NW, MB) do { if (b) SALS_PV(NW, MB, true); else SALS_PV(NW, MB, false); } while (0)
     const bool w8 = a.c->L.pv_waves == 8 || (b && b->c->L.pv_waves == 8);
-    if (d.H_q <= 32) { if (w8) SALS_PV_B(8, 1); else SALS_PV_B(4, 1); }
-    else { if (w8) SALS_PV_B(8, 2); else SALS_PV_B(4, 2); }
+    // token groups (of 16, in fp32 of 8 tokens) per wave decide how many are loaded ahead
+    const bool deep = ceil_div(std::max(f.tok_per_wg, b ? g.tok_per_wg : 0), 2 * elem<T>::vec) > 2 * (w8 ? 8 : 4);
+#define SALS_PV(NW, MB, DEPTH, TWO)                                                                                       \
+    hipLaunchKernelGGL((attend_pv_kernel<T, NW, MB, DEPTH, TWO>), dim3(n_items + n_more), dim3(NW * 64), 0, st, f.idx,     \
+                       f.n_sel, stats, d.B, f.r, f.n_tr, stats_stride, f.tok_per_wg, f.k_tot, d.H_q, f.lk, f.Vc, f.logits, \
+                       f.Tpart, f.S_max, f.ring, Uv, d.H_kv, g)
+#define SALS_PV_B(NW, MB, DEPTH) do { if (b) SALS_PV(NW, MB, DEPTH, true); else SALS_PV(NW, MB, DEPTH, false); } while (0)
+#define SALS_PV_D(NW, MB) do { if (deep) SALS_PV_B(NW, MB, 4); else SALS_PV_B(NW, MB, 2); } while (0)
+    if (d.H_q <= 32) { if (w8) SALS_PV_D(8, 1); else SALS_PV_D(4, 1); }
+    else { if (w8) SALS_PV_D(8, 2); else SALS_PV_D(4, 2); }
+#undef SALS_PV_D
 #undef SALS_PV_B
 #undef SALS_PV
 }
