@@ -34,6 +34,7 @@ template <> struct mma16_op<float> {   // four v_mfma_f32_16x16x4_f32
     }
 };
 
+constexpr int kScoreMaxParts = 8;   // slices of the D axis the projection may split into
 constexpr int kProjWaves = 4;       // waves of a query projection workgroup
 constexpr int kProjThreads = 64 * kProjWaves;
 constexpr int kAppendWaves = 8;     // ... and at most of an append workgroup, which owns the whole D axis
@@ -47,7 +48,7 @@ struct ProjArgs {  // (what the first loads need comes first: those 14 words arr
     int d, S_max, nproj;
     int ring;            // append: > 0 = the cache is a ring of this many rows, token t in row t mod ring
     void* cache[2];      // append: [B,S_max,r], or [B,ring,r] when ring > 0
-    float* out_f32;      // QUERY: partial q~ [np,B,r], one slice of the D axis each
+    float* out_f32;      // QUERY: partial q~ [np,B,r], one slice of the D axis each; append with np > 1: [nproj,np,B,r]
     const int32_t* seq_len;  // append: [B] row to write
 };
 
@@ -57,7 +58,7 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int sli
 {
     constexpr int VEC = elem<T>::vec;
     constexpr int KS = 4 * VEC;  // elements of the D axis per MFMA step
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, kg = lane >> 4;
     const int G = QUERY ? a.H / a.H_kv : 1;
     const int ncols = a.B * G, n_nblk = (ncols + 15) >> 4;
@@ -74,14 +75,13 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int sli
 #pragma unroll
     for (int nb = 0; nb < kProjMaxCols / 16; ++nb) acc[nb] = f32x4v{0.f, 0.f, 0.f, 0.f};
 
-    // this wave's steps: wave, wave+NW, ... ; NBATCH steps of loads per round
+    // this wave's steps: wave, wave+NW, ... ; NBATCH steps of loads per round.  Branches are wave-uniform (a step that is not
+    // there costs no load), columns past the last one repeat it.
     for (int ks0 = wave; ks0 < nks; ks0 += NW * NBATCH) {
         u32x4 af[NBATCH];
 #pragma unroll
-        for (int u = 0; u < NBATCH; ++u) {
-            int ks = ks0 + u * NW;
-            af[u] = ks < nks ? ld16(arow + (size_t)(ks_first + ks) * KS) : u32x4{0, 0, 0, 0};
-        }
+        for (int u = 0; u < NBATCH; ++u)
+            if (ks0 + u * NW < nks) af[u] = ld16(arow + (size_t)(ks_first + ks0 + u * NW) * KS);
         // the x operands of HB column blocks are requested together, ahead of their products: a round costs one memory
         // round trip per HB column blocks
 #pragma unroll
@@ -90,29 +90,25 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int sli
                 u32x4 bf[HB][NBATCH];
 #pragma unroll
                 for (int h = 0; h < HB; ++h) {
-                    const int n = (nb0 + h) * 16 + l16;
+                    if (nb0 + h < n_nblk) {
+                        const int n = min((nb0 + h) * 16 + l16, ncols - 1), b = n / G;
+                        const T* xrow = X + (QUERY ? ((size_t)b * a.H + n - b * G) * kHeadDim : (size_t)n * a.D) + kg * VEC;
 #pragma unroll
-                    for (int u = 0; u < NBATCH; ++u) {
-                        int ks = ks0 + u * NW;
-                        bf[h][u] = u32x4{0, 0, 0, 0};
-                        if (ks < nks && n < ncols) {
-                            int c = (ks_first + ks) * KS + kg * VEC;
-                            const T* xp;
-                            if (QUERY) {
-                                int b = n / G, m = n - b * G, g = c / a.d;
-                                xp = X + ((size_t)b * a.H + g * G + m) * a.d + (c - g * a.d);
-                            } else {
-                                xp = X + (size_t)n * a.D + c;
+                        for (int u = 0; u < NBATCH; ++u)
+                            if (ks0 + u * NW < nks) {
+                                const int c = (ks_first + ks0 + u * NW) * KS;  // (a step lies within one head)
+                                bf[h][u] = ld16(xrow + (QUERY ? c / kHeadDim * G * kHeadDim + c % kHeadDim : c));
                             }
-                            bf[h][u] = ld16(xp);
-                        }
                     }
                 }
                 asm volatile("" ::: "memory");  // (keeps the loads above from sinking towards their products)
 #pragma unroll
                 for (int h = 0; h < HB; ++h)
+                    if (nb0 + h < n_nblk) {
 #pragma unroll
-                    for (int u = 0; u < NBATCH; ++u) mma16_op<T>::run(af[u], bf[h][u], acc[nb0 + h]);
+                        for (int u = 0; u < NBATCH; ++u)
+                            if (ks0 + u * NW < nks) mma16_op<T>::run(af[u], bf[h][u], acc[nb0 + h]);
+                    }
             }
         }
     }
@@ -141,8 +137,8 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int sli
         int b = t >> 4, rr = t & 15;
         float s = 0.f;
         for (int m = 0; m < G; ++m) s += colsum[b * G + m][rr];
-        if (QUERY) {
-            a.out_f32[((size_t)slice * a.B + b) * a.r + i0 + rr] = s;
+        if (QUERY || a.np > 1) {
+            a.out_f32[((size_t)(proj * a.np + slice) * a.B + b) * a.r + i0 + rr] = s;
         } else {
             const int t_new = a.seq_len[b];
             const int rows = a.ring > 0 ? a.ring : a.S_max;
@@ -157,6 +153,34 @@ template <typename T>
 __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjArgs a)
 {
     project_block<T, true, kProjWaves, kProjBatch, 2>(a, blockIdx.x * 16, blockIdx.y, blockIdx.z);
+}
+
+// Append in slices of the D axis: adds up the slices' partial sums (in slice order) into the new rows and advances the lengths.
+// One workgroup per sequence, which thus reads its length before it advances it.
+template <typename T>
+__global__ __launch_bounds__(256) void append_finish_kernel(ProjArgs a)
+{
+    const int b = blockIdx.x, t_new = a.seq_len[b];
+    if (t_new >= a.S_max) return;  // uniform
+    for (int e = threadIdx.x; e < a.nproj * a.r / 4; e += 256) {
+        const int proj = e / (a.r / 4), i = (e - proj * (a.r / 4)) * 4;
+        f32x4 x[kScoreMaxParts];
+#pragma unroll
+        for (int p = 0; p < kScoreMaxParts; ++p)
+            x[p] = *reinterpret_cast<const f32x4*>(a.out_f32 + ((size_t)(proj * a.np + min(p, a.np - 1)) * a.B + b) * a.r + i);
+        f32x4 s = x[0];
+#pragma unroll
+        for (int p = 1; p < kScoreMaxParts; ++p) {
+            const bool use = p < a.np;
+            s.x += use ? x[p].x : 0.f; s.y += use ? x[p].y : 0.f; s.z += use ? x[p].z : 0.f; s.w += use ? x[p].w : 0.f;
+        }
+        if (t_new >= 0) {
+            T* dst = static_cast<T*>(a.cache[proj]) + ((size_t)b * a.S_max + t_new) * a.r + i;
+            elem<T>::store(dst, s.x); elem<T>::store(dst + 1, s.y); elem<T>::store(dst + 2, s.z); elem<T>::store(dst + 3, s.w);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) const_cast<int32_t*>(a.seq_len)[b] = t_new + 1;
 }
 
 // after an append: advance the sequence lengths (separate launch, so that every cache row

@@ -86,25 +86,26 @@ __device__ __forceinline__ void qv_quantize_group(const QuantArgs& qa, const int
     if (l == 0) qv_meta<T>::store(Vmeta + (tok * n_groups + gi) * 2, scale, mn);
 }
 
-// The append of a token in one launch (the lengths are advanced by a second one: letting the last workgroup do it, counted by
-// an atomic, cost 1 us more than that launch).  blockIdx.z: projection of the new key (and value) into the latent caches, 16
-// coordinates per workgroup; QUANT: z = 0 projects the key, z = 1 quantises the new values, 2 NW groups per workgroup.
-// Eight waves with all their pieces in flight where the D axis is long: a workgroup owns 16 coordinates over the whole axis,
-// 128 KB of the projector at D = 4096, and the bytes a compute unit keeps in flight are what it is bound by.  (Batch 16,
-// D = 4096, r = 512, 2-bit values: 12.4 us to project with four waves and 3.9 to quantise in a launch of its own, now 10.7
-// for both.)
+// The append of a token (the lengths are advanced by a second launch: letting the last workgroup do it, counted by an atomic,
+// cost 1 us more than that launch).  blockIdx.z: projection of the new key (and value) into the latent caches, 16
+// coordinates per workgroup, blockIdx.y: slice of the D axis; QUANT: z = 0 projects the key, z = 1 quantises the new values,
+// 2 NW groups per workgroup.  What binds it is the bytes a compute unit draws: 16 coordinates over the whole axis are 128 KB of
+// the projector and as much of the inputs at D = 4096.  So where a second launch follows anyway the axis is sliced and that
+// launch adds the slices up (append_finish_kernel), and where none does (a recent window) eight waves have all their pieces in
+// flight.  (Batch 16, D = 4096, r = 512, 2-bit values, with the advance: 12.4 + 3.9 + 1.4 us as three launches of four waves,
+// 10.2 + 1.4 with eight waves over the whole axis, 5.1 + 2.6 sliced.)
 template <typename T, int NW, bool QUANT>
 __global__ __launch_bounds__(64 * NW) void append_kernel(ProjArgs a, QuantArgs qa)
 {
     if (QUANT && blockIdx.z == 1) {
-        const int group = blockIdx.x * (2 * NW) + (threadIdx.x >> 5);
+        const int group = (blockIdx.y * gridDim.x + blockIdx.x) * (2 * NW) + (threadIdx.x >> 5);
         if (qa.bits == 2) qv_quantize_group<T, 2>(qa, a.seq_len, a.B, a.D, a.S_max, a.ring, group);
         else if (qa.bits == 4) qv_quantize_group<T, 4>(qa, a.seq_len, a.B, a.D, a.S_max, a.ring, group);
         else qv_quantize_group<T, 8>(qa, a.seq_len, a.B, a.D, a.S_max, a.ring, group);
         return;
     }
     if (QUANT && (int)blockIdx.x * 16 >= a.r) return;  // (the grid covers the longer of the two parts)
-    project_block<T, false, NW, NW == kProjWaves ? kProjBatch : 16, NW == kProjWaves ? 2 : 1>(a, blockIdx.x * 16, 0, blockIdx.z);
+    project_block<T, false, NW, NW == kProjWaves ? kProjBatch : 16, NW == kProjWaves ? 2 : 1>(a, blockIdx.x * 16, blockIdx.y, blockIdx.z);
 }
 
 struct QvArgs {

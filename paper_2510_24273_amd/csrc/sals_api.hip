@@ -41,7 +41,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 struct Layout {  // byte offsets into the workspace
-    size_t qt, scores, idx, n_sel, n_lo, logits, plogits, stats, rope, tpart, qv_part, dn_part, tm_part, tm_hist, tm_meta, tm_cand, tm_srange, total;
+    size_t qt, ap_part, scores, idx, n_sel, n_lo, logits, plogits, stats, rope, tpart, qv_part, dn_part, tm_part, tm_hist, tm_meta, tm_cand, tm_srange, total;
     int lk;                      // logits row stride (floats)
     int max_parts;               // token tiles per head of the logits kernel, at most
     int pv_tok_per_wg, pv_ntr, pv_waves;  // value-sum token ranges, waves per workgroup (4 | 8)
@@ -172,6 +172,7 @@ Layout make_layout(const sals_desc& d)
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes); return at; };
     L.qt = take((size_t)L.proj_np * d.B * d.r * 4);
+    L.ap_part = take((size_t)2 * kScoreMaxParts * d.B * d.r * 4);
     L.scores = take((size_t)d.B * d.S_max * 4);
     L.idx = take((size_t)d.B * k_tot * 4);
     L.n_sel = take((size_t)d.B * 4);
@@ -264,22 +265,31 @@ sals_status launch_append(const sals_ctx* c, const void* W, const void* k_new, c
     a.cache[0] = cache0; a.cache[1] = cache1;
     a.seq_len = seq_len;
     a.B = d.B; a.D = d.H_kv * d.d; a.r = d.r; a.H = d.H_q; a.H_kv = d.H_kv; a.d = d.d;
-    a.S_max = d.S_max; a.nproj = v_new ? 2 : 1; a.np = 1;
+    a.S_max = d.S_max; a.nproj = v_new ? 2 : 1;
     a.ring = ring;
-    const bool wide = a.D / (4 * elem<T>::vec) > kProjWaves * kProjBatch;  // more MFMA steps than four waves request at once
+    // An append that advances the lengths has a second launch anyway: it adds up slices of the D axis, as many (at most 8, of
+    // 32 MFMA steps and more: shorter ones gain less than adding them up costs) as give the projection 128 workgroups.
+    a.np = 1;
+    a.out_f32 = reinterpret_cast<float*>(c->ws + c->L.ap_part);
+    const int nks = a.D / (4 * elem<T>::vec);
+    if (bump)
+        while (a.np < kScoreMaxParts && d.r / 16 * a.nproj * a.np < 128 && nks % (2 * a.np) == 0 && nks / (2 * a.np) >= 32) a.np *= 2;
+    const bool wide = nks / a.np > kProjWaves * kProjBatch;  // more MFMA steps than four waves request at once
     const int nw = wide ? kAppendWaves : kProjWaves;
     {
         ProfScope ps(c, SALS_K_PROJECT, st);
 #define SALS_APPEND(NW, QUANT)                                                                                           \
     hipLaunchKernelGGL((append_kernel<T, NW, QUANT>),                                                                    \
-                       dim3(QUANT ? std::max(d.r / 16, ceil_div(d.B * (a.D / kQvGroup), 2 * nw)) : d.r / 16, 1,          \
+                       dim3(QUANT ? std::max(d.r / 16, ceil_div(d.B * (a.D / kQvGroup), 2 * nw * a.np)) : d.r / 16, a.np, \
                             QUANT ? 2 : a.nproj), dim3(64 * NW), 0, st, a, qa)
         if (qa.bits) { if (wide) SALS_APPEND(kAppendWaves, true); else SALS_APPEND(kProjWaves, true); }
         else { if (wide) SALS_APPEND(kAppendWaves, false); else SALS_APPEND(kProjWaves, false); }
 #undef SALS_APPEND
     }
     if (launch_status() != SALS_OK) return SALS_ERR_HIP;
-    if (bump)
+    if (a.np > 1)
+        hipLaunchKernelGGL((append_finish_kernel<T>), dim3(d.B), dim3(256), 0, st, a);
+    else if (bump)
         hipLaunchKernelGGL(bump_seq_len_kernel, dim3(ceil_div(d.B, 128)), dim3(128), 0, st, seq_len, d.B, d.S_max);
     return launch_status();
 }

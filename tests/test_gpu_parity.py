@@ -318,6 +318,42 @@ def test_compress_append_then_decode(oracle):
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype,H_kv,r,B", [
+    ("bf16", 32, 640, 1),    # two slices of the D axis
+    ("bf16", 32, 128, 5),    # four slices
+    ("bf16", 16, 64, 3),     # slices at their shortest
+    ("f32", 32, 64, 2),      # eight slices
+    ("f32", 12, 192, 2),     # two slices of one and a half rounds of loads
+    ("bf16", 7, 64, 16)])    # no slices
+def test_sliced_append_matches_oracle(oracle, dtype, H_kv, r, B):
+    """Append where the D axis is cut into slices that the length-advancing launch adds up; one sequence is full and must be
+    left alone, no other row may change."""
+    S = 40
+    w = synth.shrink(SMALL, B=B, S=S, top_k=8, H=H_kv, H_kv=H_kv, r=r, plant=0, dtype=dtype)
+    lens = [S if B > 1 and b == B - 1 else (7 * b + 3) % S for b in range(B)]
+    L = synth.make_layer(w, seq_lens=lens)
+    G = gu.upload(L)
+    rng = np.random.default_rng(11)
+    k_new = synth.store(rng.standard_normal((B, w.D_kv)), dtype)
+    v_new = synth.store(rng.standard_normal((B, w.D_kv)), dtype)
+    ctx = gu.make_ctx(w)
+    G["W"] = ctx.pack_weights(G["Uk"], G["Uv"])
+    before = {c: G[c].clone() for c in ("Kc", "Vc")}
+    ctx.compress_append(gu.to_dev(k_new), gu.to_dev(v_new), G["W"], G["Kc"], G["Vc"], G["seq_len"])
+    torch.cuda.synchronize()
+    assert G["seq_len"].tolist() == [min(n + 1, S) for n in lens]
+    for new, U, c in ((k_new, "Uk", "Kc"), (v_new, "Uv", "Vc")):
+        for b, row in enumerate(lens):
+            if row < S:
+                want = oracle.project(synth.widen(new[b]), synth.widen(L[U]))
+                got = gu.from_dev(G[c][b, row])
+                tol = np.abs(want) * 2.0 ** -7 + 1e-6 if dtype == "bf16" else 1e-5
+                assert np.all(np.abs(got - want) <= tol), (c, b)
+                before[c][b, row] = G[c][b, row]
+        assert torch.equal(before[c], G[c])
+    ctx.close()
+
+
 def test_query_position_beyond_the_cache(oracle):
     """q_pos far above S_max: the query's angles are then evaluated in the kernel instead of
     being read from the per-context cos/sin table."""
