@@ -378,12 +378,14 @@ sals_status sals_overlap_score(sals_ctx* ctx, const void* q, const int32_t* q_po
  *   D          multiple of 128, at most 8192 (host)
  *   C          [D, D] fp64 (device)    in/out; the caller zeroes it before the first call
  *   workspace  device, 256-byte aligned, at least sals_calib_accumulate_workspace_bytes(dtype, D) bytes, no contents
- *              kept between calls (it holds the transposed keys of a chunk and the fp32 tile sums of its slices)
+ *              kept between calls (it holds the fp32 tile sums of a launch's token slices and, for fp32 keys, the
+ *              transposed keys of a chunk)
  * Asynchronous on hip_stream.  Errors: SALS_ERR_INVALID_ARG (NULL or misaligned pointer, bad size),
  * SALS_ERR_WORKSPACE, SALS_ERR_HIP.
  *
- * sals_calib_eigenvectors computes the eigen-decomposition of C (symmetric, positive semi-definite) by one-sided
- * Jacobi rotations of its rows in fp64 and returns all eigenvalues in descending order and the r leading eigenvectors:
+ * sals_calib_eigenvectors computes the eigen-decomposition of C (symmetric, positive semi-definite up to the rounding
+ * of its sums) by one-sided Jacobi rotations in fp64, of the rows of the Cholesky factor of C plus a small multiple of
+ * the identity, and returns all eigenvalues in descending order and the r leading eigenvectors:
  *   C          [D, D] fp64 (device)    in; OVERWRITTEN (its rows become eigenvalue times eigenvector)
  *   D          multiple of 256, at most 8192;  r  1 .. D
  *   dtype      storage type T of U
@@ -392,15 +394,18 @@ sals_status sals_overlap_score(sals_ctx* ctx, const void* q, const int32_t* q_po
  *   U          [D, r] T (device)       out: column i is the eigenvector of eigval[i], unit length, signed so that
  *                                      its largest component is positive, rounded once to T; the layout
  *                                      sals_pack_weights takes.  Eigenvalues below 1e-13 of the largest are zero to
- *                                      working precision: their vectors are not resolved (whatever direction the
- *                                      row was left with).
- *   workspace  device, 256-byte aligned, at least sals_calib_eigenvectors_workspace_bytes(D) bytes
+ *                                      working precision: their vectors are not resolved (some direction of the space
+ *                                      they span together); negative ones are returned as zero.
+ *   workspace  device, 256-byte aligned, at least sals_calib_eigenvectors_workspace_bytes(D) bytes (the factor, 8 D^2
+ *              bytes, and some D of scratch)
  *   max_sweeps at least 1 (host): a sweep rotates every pair of rows once; the call stops after the first sweep in
  *              which no rotation that involved one of the r largest rows turned by more than 1e-11, or after
  *              max_sweeps
  *   sweeps     host int32, out (may be NULL): sweeps run; the negative of that number if the limit was reached
- *              before convergence (the results are then the current approximation)
- * BLOCKING: it waits for hip_stream once per sweep to read the convergence measure, so it cannot be captured.
+ *              before convergence (the results are then the current approximation); 0 if there was nothing to
+ *              rotate (C is zero, or not finite: then its rows come back as they are)
+ * BLOCKING: it waits for hip_stream once per sweep to read the convergence measure (and after each factorisation: one,
+ * or a few for a C that rounding has left indefinite), so it cannot be captured.
  * Errors as above. */
 size_t sals_calib_accumulate_workspace_bytes(int32_t dtype, int32_t D);
 sals_status sals_calib_accumulate(int32_t dtype, const void* K, int64_t n_tok, int32_t D, double* C,

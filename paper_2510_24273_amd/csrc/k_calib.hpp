@@ -5,18 +5,18 @@
 //                fp32: the keys of a chunk are transposed once (calib_transpose_kernel, a plain LDS tile transpose) and
 //                the product is then the row-by-row form the matrix-core GEMM of the prompt compression computes,
 //                C += K^T (K^T)^T.  Either way fp32 tile sums over at most 4096 tokens are added to the fp64 matrix.
-//   eigenvectors One-sided Jacobi on the rows of G = R, the Cholesky factor of C = R^T R: a plane rotation of rows p, q
-//                makes them orthogonal.  With J the product of all rotations, G = J R keeps G^T G = C; once all rows are
-//                orthogonal, the normalised rows are eigenvectors of C and the squared row norms the eigenvalues, so no
-//                rotation matrix is kept.  (Starting from the rows of C itself, as a first form did, works on C^2: 15 to
-//                32 sweeps instead of about 10, since the off-diagonal part has twice the dynamic range to lose.)
+//   eigenvectors One-sided Jacobi on the rows of G = R, the Cholesky factor of C + shift I = R^T R: a plane rotation of rows
+//                p, q makes them orthogonal.  With J the product of all rotations, G = J R keeps G^T G = C + shift I; once
+//                all rows are orthogonal, the normalised rows are eigenvectors of C and the squared row norms less the shift
+//                the eigenvalues, so no rotation matrix is kept.  (Starting from the rows of C itself, as a first form did,
+//                works on C^2: 15 to 32 sweeps instead of about 10, since the off-diagonal part has twice the dynamic range
+//                to lose.)
 //                A step takes D / 32 disjoint pairs of 16-row blocks: one launch forms the pairs' 32 x 32 Gram
 //                matrices, a second one rotates them to orthogonality in LDS and applies the accumulated rotations to
 //                the rows with the fp64 matrix instructions; D / 16 - 1 steps (round-robin over the blocks) rotate every
 //                pair of rows once: one sweep.  One launch per row-pair step (D - 1 of them a sweep, each streaming the
 //                whole matrix) was bound by its launches up to D = 1024 and by the stream above.
-//                fp64 throughout.  Rows whose squared norm is below 1e-13 of the largest eigenvalue stand for eigenvalues
-//                that are zero to working precision and are left alone.
+//                fp64 throughout.
 #pragma once
 #include "common.hpp"
 #include "k_gemm.hpp"
@@ -305,8 +305,15 @@ __device__ __forceinline__ void calib_pair(int n, int s, int k, int* p, int* q)
 }
 
 // ---- Cholesky factor ---------------------------------------------------------------------------------------------
-// G holds a copy of C and becomes R (upper triangular, C = R^T R), in panels of kCalPanel rows.  A pivot of at most `thr`
-// stands for a Schur complement that is zero to working precision: its row of R is zero.
+// G holds a copy of C and becomes R (upper triangular, C + shift I = R^T R), in panels of kCalPanel rows.
+//
+// The shift (1e-14 of C's scale at first) keeps the pivots of eigenvalues that are zero to working precision positive, and
+// leaves the eigenvectors as they are.  Dropping rows of small pivots instead is not safe without a search for the largest
+// pivot: the row's other entries may be as large as the square root of the pivot times a later diagonal entry (a channel of
+// little variance ahead of the one it follows: eigenvectors at 1e-8 of the largest eigenvalue came out wrong by 8e-4).  A
+// factorisation whose pivots are all positive is backward stable whatever its pivots are, since the columns of R have the
+// norms sqrt(C_jj + shift); one that meets another pivot (C is indefinite by more than the shift, as the covariance of fewer
+// tokens than channels is by its fp32 sums) sets `fail` and the host starts again with 64 times the shift.
 constexpr int kCalPanel = 64;
 
 // Panel at row k0: every workgroup factors the 64 x 64 diagonal block by itself (a row of it per four threads, the pivot
@@ -314,8 +321,8 @@ constexpr int kCalPanel = 64;
 // another launch) and then carries 64 columns of the panel through the triangular solve, one column per thread of its first
 // wave (with a column on every thread the four waves' broadcast reads of the factor are bound by the LDS).  The
 // factored block goes to `diag` (other workgroups still read the original).  grid max(1, (D - k0 - 64) / 64).
-__global__ __launch_bounds__(256) void calib_chol_panel_kernel(double* __restrict__ G, int D, int k0, double thr,
-                                                               double* __restrict__ diag)
+__global__ __launch_bounds__(256) void calib_chol_panel_kernel(double* __restrict__ G, int D, int k0, double shift,
+                                                               double* __restrict__ diag, int* __restrict__ fail)
 {
     __shared__ double row[2][kCalPanel];
     __shared__ double Rk[kCalPanel][kCalPanel + 1];
@@ -324,7 +331,7 @@ __global__ __launch_bounds__(256) void calib_chol_panel_kernel(double* __restric
     const int c = k0 + kCalPanel + blockIdx.x * 64 + tid;
     double a[16];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) a[e] = G[(size_t)(k0 + i) * D + k0 + j0 + e];
+    for (int e = 0; e < 16; ++e) a[e] = G[(size_t)(k0 + i) * D + k0 + j0 + e] + (j0 + e == i ? shift : 0.0);
     double pv_i = 0.0;
     for (int k = 0; k < kCalPanel; ++k) {
         double* rk = row[k & 1];
@@ -336,12 +343,13 @@ __global__ __launch_bounds__(256) void calib_chol_panel_kernel(double* __restric
         const double pv = rk[k];
         if (i == k) pv_i = pv;
         if (i > k) {
-            const double f = pv > thr ? rk[i] / pv : 0.0;
+            const double f = pv > 0.0 ? rk[i] / pv : 0.0;
 #pragma unroll
             for (int e = 0; e < 16; ++e) a[e] -= f * rk[j0 + e];
         }
     }
-    const double inv = pv_i > thr ? rsqrt(pv_i) : 0.0;
+    const double inv = pv_i > 0.0 ? rsqrt(pv_i) : 0.0;
+    if (!(pv_i > 0.0) && blockIdx.x == 0) *fail = 1;
     if ((tid & 3) == 0) invd[i] = inv;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -471,15 +479,13 @@ __device__ __forceinline__ double jac_rsqrt(double x)
 }
 // cosine and sine of the rotation (g_p, g_q) -> (c g_p - s g_q, s g_p + c g_q) that makes two rows with squared norms aa,
 // bb and inner product ab orthogonal, by the smaller angle: with h = sqrt((bb-aa)^2 + 4 ab^2) the double angle has
-// cosine |bb-aa| / h and sine 2 |ab| / h, so two reciprocal square roots do.  Rows that stand for a zero eigenvalue
-// (squared norm at most floor) and rows orthogonal to working precision are left alone.
-__device__ __forceinline__ bool jac_open(double aa, double bb, double ab, double floor)
+// cosine |bb-aa| / h and sine 2 |ab| / h, so two reciprocal square roots do.  Rows orthogonal to working precision are left
+// alone.  (No row is too small to count: beside a large one, a row of squared norm w left as it is moves the large one's
+// eigenvector by up to w over its eigenvalue.)
+__device__ __forceinline__ bool jac_open(double aa, double bb, double ab) { return ab * ab > 1e-30 * (aa * bb); }
+__device__ __forceinline__ bool jac_rotation(double aa, double bb, double ab, double* c, double* s)
 {
-    return fmin(aa, bb) > floor && ab * ab > 1e-30 * (aa * bb);
-}
-__device__ __forceinline__ bool jac_rotation(double aa, double bb, double ab, double floor, double* c, double* s)
-{
-    const bool ok = jac_open(aa, bb, ab, floor);
+    const bool ok = jac_open(aa, bb, ab);
     const double d = bb - aa, hi = jac_rsqrt(fma(d, d, 4.0 * ab * ab));
     const double c2 = fma(0.5 * fabs(d), hi, 0.5), ci = jac_rsqrt(c2);
     *c = ok ? c2 * ci : 1.0;
@@ -504,8 +510,8 @@ __device__ __forceinline__ void conv_max(double* at, double v)
 // conv[pair] keeps the largest |sin| of a rotation, since the host cleared it, that involved a row of squared norm >=
 // lead (the rows that can still change a leading eigenvector).
 __global__ __launch_bounds__(256) void calib_jacobi_rotate_kernel(double* __restrict__ G, int D, int step, int slice_cols,
-                                                                  const double* __restrict__ part, int n_part, double floor,
-                                                                  double lead, double* __restrict__ conv)
+                                                                  const double* __restrict__ part, int n_part, double lead,
+                                                                  double* __restrict__ conv)
 {
     constexpr int B2 = 2 * kJacB, LD = B2 + 1, LB = kJacB + 1;
     __shared__ double Wb[2][B2 * LD], Qb[2][B2 * LD];   // Gram matrix and accumulated rotations
@@ -556,7 +562,7 @@ __global__ __launch_bounds__(256) void calib_jacobi_rotate_kernel(double* __rest
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
         const int r = i + (t == 2 ? kJacB : 0), c = j + (t >= 1 ? kJacB : 0);
-        if (r != c && (t == 1 || step == 0) && jac_open(s_diag[r], s_diag[c], v[t], floor)) s_any[0] = 1;
+        if (r != c && (t == 1 || step == 0) && jac_open(s_diag[r], s_diag[c], v[t])) s_any[0] = 1;
     }
     __syncthreads();
     if (!s_any[0]) return;  // uniform, and the same in every slice of the pair
@@ -579,8 +585,8 @@ __global__ __launch_bounds__(256) void calib_jacobi_rotate_kernel(double* __rest
             const double b00 = W[pi * LD + pj], b01 = W[pi * LD + qj], b10 = W[qi * LD + pj], b11 = W[qi * LD + qj];
             const double x0 = Q[pi * LD + j], y0 = Q[qi * LD + j], x1 = Q[pi * LD + j + kJacB], y1 = Q[qi * LD + j + kJacB];
             double c, s, cj, sj;
-            const bool ok = jac_rotation(aa, bb, W[pi * LD + qi], floor, &c, &s);
-            jac_rotation(W[pj * LD + pj], W[qj * LD + qj], W[pj * LD + qj], floor, &cj, &sj);
+            const bool ok = jac_rotation(aa, bb, W[pi * LD + qi], &c, &s);
+            jac_rotation(W[pj * LD + pj], W[qj * LD + qj], W[pj * LD + qj], &cj, &sj);
             any |= ok;
             smax = fmax(aa, bb) >= lead ? fmax(smax, fabs(s)) : smax;
             const double r00 = c * b00 - s * b10, r01 = c * b01 - s * b11, r10 = s * b00 + c * b10, r11 = s * b01 + c * b11;
@@ -619,8 +625,8 @@ __global__ __launch_bounds__(256) void calib_jacobi_rotate_kernel(double* __rest
             const double w01 = R[kPQ + i * LB + qj], w10 = R[kPQ + j * LB + qi], w11 = R[kQQ + qi * LB + qj];
             const double v0 = R[kAcc + qi * LD + j], v1 = R[kAcc + qi * LD + j + kJacB];
             double c, s, cj, sj;
-            any |= jac_rotation(aa, bb, ab, floor, &c, &s);
-            jac_rotation(aj, bj, abj, floor, &cj, &sj);
+            any |= jac_rotation(aa, bb, ab, &c, &s);
+            jac_rotation(aj, bj, abj, &cj, &sj);
             smax = fmax(aa, bb) >= lead ? fmax(smax, fabs(s)) : smax;
             const double r00 = c * b00 - s * w10, r01 = c * w01 - s * w11, r10 = s * b00 + c * w10, r11 = s * w01 + c * w11;
             b00 = cj * r00 - sj * r01;
@@ -716,10 +722,10 @@ __global__ __launch_bounds__(kCalThreads) void calib_rownorm_kernel(const double
 // Row i of G takes rank = number of rows with a larger norm (equal ones by row index); eigval[rank] = lambda_i and, for
 // rank < r, column rank of U [D, r] = sgn_i * row i of G / |row i|, rounded to the storage type (a zero row gives a
 // zero column); row i of C = lambda_i times the eigenvector.  ROOT: G is the rotated Cholesky factor (lambda = squared
-// norm); otherwise its rows are C's own, orthogonal as they came (lambda = norm).
+// norm less the shift, at least zero); otherwise its rows are C's own, orthogonal as they came (lambda = norm).
 template <typename T, bool ROOT>
 __global__ __launch_bounds__(kCalThreads) void calib_select_kernel(const double* __restrict__ G, const double* __restrict__ norm,
-                                                                   const double* __restrict__ sgn, int D, int r,
+                                                                   const double* __restrict__ sgn, int D, int r, double shift,
                                                                    double* __restrict__ eigval, T* __restrict__ U,
                                                                    double* __restrict__ C)
 {
@@ -738,12 +744,13 @@ __global__ __launch_bounds__(kCalThreads) void calib_select_kernel(const double*
     int rank = 0;
 #pragma unroll
     for (int w = 0; w < kCalThreads / kWave; ++w) rank += cnt[w];
-    if (tid == 0) eigval[rank] = ROOT ? li * li : li;
-    const double s = li > 0.0 ? sgn[i] / li : 0.0;
+    const double lam = ROOT ? fmax(li * li - shift, 0.0) : li;
+    if (tid == 0) eigval[rank] = lam;
+    const double s = li > 0.0 ? sgn[i] / li : 0.0, to_c = ROOT && li > 0.0 ? lam / li : 0.0;
     for (int d = tid; d < D; d += kCalThreads) {
         const double g = G[(size_t)i * D + d];
         if (rank < r) elem<T>::store(U + (size_t)d * r + rank, (float)(s * g));
-        if (ROOT) C[(size_t)i * D + d] = li * g;
+        if (ROOT) C[(size_t)i * D + d] = to_c * g;
     }
 }
 

@@ -1624,7 +1624,7 @@ int jac_slices(int D)
     return s;
 }
 struct EigWs {  // byte offsets into the workspace
-    size_t G, conv, norm, sgn, diag, part, total;
+    size_t G, fail, conv, norm, sgn, diag, part, total;
 };
 EigWs eig_ws(int D)
 {
@@ -1632,6 +1632,7 @@ EigWs eig_ws(int D)
     size_t o = 0;
     auto take = [&](size_t bytes) { const size_t at = o; o = align_up(o + bytes); return at; };
     w.G = take((size_t)D * D * 8);               // the rotated factor
+    w.fail = take(sizeof(int));                  // a pivot of the factorisation was not positive
     w.conv = take((size_t)(D / (2 * kJacB)) * 8);  // convergence slots
     w.norm = take((size_t)D * 8);                // row norms and signs
     w.sgn = take((size_t)D * 8);
@@ -1662,6 +1663,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     const EigWs off = eig_ws(D);
     auto at = [&](size_t o) { return reinterpret_cast<double*>(ws + o); };
     double *G = at(off.G), *conv = at(off.conv), *norm = at(off.norm), *sgn = at(off.sgn), *diag = at(off.diag), *part = at(off.part);
+    int* fail = reinterpret_cast<int*>(ws + off.fail);
     const int n_pairs = D / (2 * kJacB), n_steps = D / kJacB - 1, slices = jac_slices(D);
     std::vector<double> h_conv((size_t)n_pairs), h_norm((size_t)D);
     auto row_norms = [&](const double* M) -> bool {  // row norms to the host (blocking)
@@ -1671,29 +1673,40 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     };
     if (!row_norms(C)) return SALS_ERR_HIP;
     const double n0 = *std::max_element(h_norm.begin(), h_norm.end());  // (between the largest diagonal entry and lambda_0)
-    const double floor = 1e-13 * n0;
     double lead = 0.0;  // first sweep: every rotation counts
     int done = 0;
-    bool converged = !(n0 > 0.0);  // the zero matrix needs no rotation
+    bool converged = !(n0 > 0.0) || !std::isfinite(n0);  // the zero matrix needs no rotation
     bool rotated = false;
-    if (!converged) {  // G = Cholesky factor
-        if (hipMemcpyAsync(G, C, (size_t)D * D * 8, hipMemcpyDeviceToDevice, st) != hipSuccess) return SALS_ERR_HIP;
-        for (int k0 = 0; k0 < D; k0 += kCalPanel) {
-            const int rest = D - k0 - kCalPanel;
-            hipLaunchKernelGGL(calib_chol_panel_kernel, dim3(std::max(1, rest / 64)), dim3(256), 0, st, G, D, k0,
-                               1e-14 * n0, diag);
-            if (rest > 0)
-                hipLaunchKernelGGL(calib_chol_update_kernel, dim3(rest / 64, rest / 64), dim3(256), 0, st, G, D, k0);
+    // G = Cholesky factor of C + shift I.  No eigenvalue lies below -sqrt(D) n0 (sqrt(D) is at most 90.5), so ten shifts, up to
+    // 180 n0, end with a positive definite matrix unless C is not one of numbers (then its rows are returned as they are).
+    double shift = 0.0;
+    if (!converged) {
+        int failed = 1;
+        for (int t = 0; t < 10 && failed; ++t) {
+            shift = t == 0 ? 1e-14 * n0 : 64.0 * shift;
+            if (hipMemcpyAsync(G, C, (size_t)D * D * 8, hipMemcpyDeviceToDevice, st) != hipSuccess ||
+                hipMemsetAsync(fail, 0, sizeof(int), st) != hipSuccess)
+                return SALS_ERR_HIP;
+            for (int k0 = 0; k0 < D; k0 += kCalPanel) {
+                const int rest = D - k0 - kCalPanel;
+                hipLaunchKernelGGL(calib_chol_panel_kernel, dim3(std::max(1, rest / 64)), dim3(256), 0, st, G, D, k0, shift,
+                                   diag, fail);
+                if (rest > 0)
+                    hipLaunchKernelGGL(calib_chol_update_kernel, dim3(rest / 64, rest / 64), dim3(256), 0, st, G, D, k0);
+            }
+            hipLaunchKernelGGL(calib_chol_finish_kernel, dim3(D), dim3(256), 0, st, G, D, diag);
+            if (launch_status() != SALS_OK || hipMemcpyAsync(&failed, fail, sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess ||
+                hipStreamSynchronize(st) != hipSuccess)
+                return SALS_ERR_HIP;
         }
-        hipLaunchKernelGGL(calib_chol_finish_kernel, dim3(D), dim3(256), 0, st, G, D, diag);
-        if (launch_status() != SALS_OK) return SALS_ERR_HIP;
+        converged = failed != 0;
     }
     while (done < max_sweeps && !converged) {
         if (hipMemsetAsync(conv, 0, (size_t)n_pairs * 8, st) != hipSuccess) return SALS_ERR_HIP;
         for (int step = 0; step < n_steps; ++step) {
             hipLaunchKernelGGL(calib_jacobi_gram_kernel, dim3(slices, n_pairs), dim3(256), 0, st, G, D, step, D / slices, part);
             hipLaunchKernelGGL(calib_jacobi_rotate_kernel, dim3(slices, n_pairs), dim3(256), 0, st, G, D, step, D / slices, part,
-                               slices, floor, lead, conv);
+                               slices, lead, conv);
         }
         if (launch_status() != SALS_OK) return SALS_ERR_HIP;
         if (hipMemcpyAsync(h_conv.data(), conv, (size_t)n_pairs * 8, hipMemcpyDeviceToHost, st) != hipSuccess) return SALS_ERR_HIP;
@@ -1713,7 +1726,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     // own rows are the answer, without the detour through the square roots.
     if (!rotated && !row_norms(C)) return SALS_ERR_HIP;
 #define SALS_SELECT(T, ROOT, M)                                                                                              \
-    hipLaunchKernelGGL((calib_select_kernel<T, ROOT>), dim3(D), dim3(kCalThreads), 0, st, M, norm, sgn, D, r, eigval,        \
+    hipLaunchKernelGGL((calib_select_kernel<T, ROOT>), dim3(D), dim3(kCalThreads), 0, st, M, norm, sgn, D, r, shift, eigval, \
                        static_cast<T*>(U), C)
     if (dtype == SALS_BF16) { if (rotated) SALS_SELECT(bf16_t, true, G); else SALS_SELECT(bf16_t, false, C); }
     else { if (rotated) SALS_SELECT(float, true, G); else SALS_SELECT(float, false, C); }

@@ -174,6 +174,55 @@ def test_rank_deficient_covariance_and_diagonal_input():
         np.testing.assert_array_equal(U[:, i], e)
 
 
+def _channels_of_different_scale(case, D):
+    """Keys whose channels span 1 .. 1e-7 in amplitude (small ones ahead, behind or among the large ones), and keys in
+    which one channel repeats another up to 1e-7 of it.  Their eigenvectors are well determined all the same."""
+    rng = np.random.default_rng(41)
+    mix = np.eye(D) + 0.3 / np.sqrt(D) * rng.standard_normal((D, D))
+    scale = 10.0 ** -np.linspace(0.0, 7.0, D)
+    X = rng.standard_normal((4 * D, D)) @ mix * scale
+    if case == "rising":
+        return X[:, ::-1]
+    if case == "shuffled":
+        return X[:, rng.permutation(D)]
+    if case == "repeated":
+        X[:, 1] = X[:, 0] + 1e-7 * np.std(X[:, 0]) / np.std(X[:, 80]) * X[:, 80]
+    return X
+
+
+@pytest.mark.parametrize("case", ["falling", "rising", "shuffled", "repeated"])
+def test_eigenvectors_with_channels_of_very_different_scale(case):
+    print(f"[case] eigenvectors, channel scales {case}", flush=True)
+    D, r = 256, 180   # the eigenvalues asked for reach down to about 1e-10 of the largest
+    X = _channels_of_different_scale(case, D)
+    _, sv, Vt = np.linalg.svd(X, full_matrices=False)
+    lam, U, sweeps = _eig_gpu(X.T @ X, r)
+    assert sweeps > 0
+    # the matrix in fp64 differs from X^T X by a few hundred 1e-16 of sqrt(C_ii C_jj), which moves an eigenvalue by as much of
+    # itself; the singular vectors are good to 1e-16 sigma_0 / gap, gaps of about 1e-7 sigma_0 among the last; fp32 storage
+    np.testing.assert_allclose(lam[:r], sv[:r] ** 2, rtol=1e-8)
+    _same_up_to_sign(U, Vt[:r].T, 5e-7)
+    np.testing.assert_allclose(U.T @ U, np.eye(r), atol=5e-7)
+
+
+@pytest.mark.parametrize("D,n,r", [(256, 100, 40), (512, 500, 256)])
+def test_eigenvectors_of_fewer_tokens_than_channels(D, n, r):
+    """The covariance the library itself accumulates (fp32 sums) of fewer tokens than channels is indefinite at the
+    level of those sums: the leading eigenvectors are those of the matrix as it is."""
+    print(f"[case] eigenvectors of {n} tokens, D={D}", flush=True)
+    C = _cov_gpu(synth.make_calibration_keys(17, n, D, "bf16", decay=0.97)).cpu().numpy()
+    lam_ref, U_ref = cal.leading_eigenvectors(C, r)
+    assert lam_ref[-1] < -1e-12 * lam_ref[0]   # (the premise)
+    lam, U, sweeps = _eig_gpu(C, r)
+    assert sweeps > 0
+    np.testing.assert_allclose(lam[:r], lam_ref[:r], rtol=0, atol=1e-11 * lam_ref[0])
+    # every column solves the defining equation to fp32 storage, against its own eigenvalue
+    resid = np.linalg.norm(C @ U - U * lam[:r], axis=0)
+    assert np.max(resid / lam_ref[0]) <= 1e-6
+    np.testing.assert_allclose(U.T @ U, np.eye(r), atol=5e-7)
+    assert np.all(lam >= 0.0) and np.all(np.diff(lam) <= 0.0)
+
+
 def test_sweep_limit_is_reported():
     D = 256
     X = synth.widen(synth.make_calibration_keys(13, 1024, D, "f32", decay=0.9))
