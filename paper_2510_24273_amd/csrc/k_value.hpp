@@ -10,7 +10,7 @@
 //               from the per-tile statistics the logits kernel left.  Each token range writes an
 //               fp32 partial sum.
 //   attend_out  y[(b,h), c] = sum_i T[(b,h), i] U_v[g*128 + c, i]  on the matrix cores, after
-//               adding the range partials in range order.
+//               adding the range partials (fp32, in a fixed order).
 //
 // bf16 storage: the fp32 weights p and the fp32 T are split into a bf16 head and a bf16
 // remainder (two MFMAs each), which keeps about 16 mantissa bits.  fp32 storage: fp32 MFMAs.
@@ -307,7 +307,10 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
 // One workgroup per (KV head, 16 output channels, tile of up to 16 rows): 8 x H_kv x ceil(B*G/16)
 // workgroups, so that the pass over U_v is spread over the whole chip.  16x16 MFMA tiles, columns the channels; the latent
 // axis is dealt to the eight waves.  A row is a (sequence, head of the group) pair; with fewer than 16 of them (R = 1, 2, 4, 8)
-// the tile's rows are the pairs of 16 / R token ranges, whose products the fold adds up: one load then serves that many ranges.
+// the lanes of the other rows load the pairs of 16 / R token ranges, so that one load serves that many ranges.  The ranges'
+// sums are added in fp32 across those lanes (DPP shifts, one per halving of the ranges) before T is split into bf16 head and
+// remainder: neighbouring ranges may cancel, which the 16 bits of a split range would not survive (products of the ranges,
+// split one by one and added behind the MFMA: 1 % error where ranges cancel to 1e-4).
 //
 // A few KB per workgroup: the kernel is one memory round trip if every load is requested before the first is used, and
 // little code (each launch starts with cold instruction caches).  So a wave requests BATCH latent steps of U_v with RPR
@@ -322,75 +325,116 @@ template <typename T, int BATCH, int RPR> struct OutPass {
     const T* U;           // the workgroup's first channel row (scalar)
     const float* Tp;      // range 0 (scalar)
     uint32_t lane_u, lane_t, tstride;
-    int nks, n_tr, q, sub, ks0, t0;  // q ranges per load; this lane's is number sub of them
+    int nks, n_tr, q, sub, ks0;  // q ranges per load; this lane's is number sub of them
     u32x4 bf[BATCH];
     f32x4 x[BATCH][RPR][VEC / 4];
 
     __device__ void start(const T* U_, const float* Tp_, int r, int bh, int BH, int n_tr_, int q_, int sub_, int l16, int kg,
                           int wave)
     {
-        U = U_; Tp = Tp_; nks = r / KS; n_tr = n_tr_; q = q_; sub = sub_; ks0 = wave; t0 = 0;
+        U = U_; Tp = Tp_; nks = r / KS; n_tr = n_tr_; q = q_; sub = sub_; ks0 = wave;
         lane_u = l16 * r + kg * VEC; lane_t = bh * r + kg * VEC; tstride = (uint32_t)BH * r;
         load();
     }
+    // latent coordinates of step u, from a clamped step
+    __device__ int at(int u) const { return min(ks0 + kOutWaves * u, nks - 1) * KS; }
     __device__ void load()
     {
         size_t t_at[RPR];
 #pragma unroll
-        for (int w = 0; w < RPR; ++w) t_at[w] = (size_t)min(t0 + w * q + sub, n_tr - 1) * tstride + lane_t;
+        for (int w = 0; w < RPR; ++w) t_at[w] = (size_t)min(w * q + sub, n_tr - 1) * tstride + lane_t;
 #pragma unroll
         for (int u = 0; u < BATCH; ++u) {
-            const int kk = min(ks0 + kOutWaves * u, nks - 1) * KS;
-            bf[u] = ld16(U + kk + lane_u);
+            bf[u] = ld16(U + at(u) + lane_u);
 #pragma unroll
             for (int w = 0; w < RPR; ++w)
 #pragma unroll
                 for (int v = 0; v < VEC / 4; ++v)
-                    x[u][w][v] = *reinterpret_cast<const f32x4*>(Tp + kk + 4 * v + t_at[w]);
+                    x[u][w][v] = *reinterpret_cast<const f32x4*>(Tp + at(u) + 4 * v + t_at[w]);
+        }
+    }
+    // s += the value `DIST` lanes further on in the 16-lane row (zero past its end)
+    template <int DIST> static __device__ void add_lanes(f32x4 (&s)[VEC / 4])
+    {
+#pragma unroll
+        for (int v = 0; v < VEC / 4; ++v)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                s[v][e] += __int_as_float(
+                    __builtin_amdgcn_update_dpp(0, __float_as_int(s[v][e]), 0x100 + DIST, 0xf, 0xf, true));  // row_shl
+    }
+    static __device__ void add(f32x4& s, const f32x4& v, bool use)
+    {
+        s.x += use ? v.x : 0.f; s.y += use ? v.y : 0.f; s.z += use ? v.z : 0.f; s.w += use ? v.w : 0.f;
+    }
+    // the loaded batch, step by step, so that a step does not wait for the loads of the next
+    template <bool FOLD> __device__ void steps(f32x4 (&s)[BATCH][VEC / 4], f32x4v& acc)
+    {
+        const int R = 16 / q, used = min(n_tr, q) * R;  // lanes of a 16-lane row that hold ranges
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            if (ks0 + kOutWaves * u < nks) {  // uniform
+#pragma unroll
+                for (int v = 0; v < VEC / 4; ++v)
+#pragma unroll
+                    for (int w = 0; w < RPR; ++w) add(s[u][v], x[u][w][v], w * q + sub < n_tr);
+                if constexpr (FOLD) {
+                    // the sum of all ranges in the lanes of the tile's first R rows (the others are not used): lane l + R
+                    // holds the range after lane l's
+                    if (used > 8 && R <= 8) add_lanes<8>(s[u]);
+                    if (used > 4 && R <= 4) add_lanes<4>(s[u]);
+                    if (used > 2 && R <= 2) add_lanes<2>(s[u]);
+                    if (used > 1 && R == 1) add_lanes<1>(s[u]);
+                }
+                if constexpr (sizeof(T) == 2) {
+                    uint32_t hw[8], lw[8];
+#pragma unroll
+                    for (int v = 0; v < 8; ++v) {
+                        const float t = s[u][v / 4][v % 4];
+                        hw[v] = f32_to_bf16(t);
+                        lw[v] = f32_to_bf16(t - bf16_to_f32((bf16_t)hw[v]));
+                    }
+                    mma16_op<T>::run(u32x4{hw[0] | (hw[1] << 16), hw[2] | (hw[3] << 16), hw[4] | (hw[5] << 16),
+                                           hw[6] | (hw[7] << 16)}, bf[u], acc);
+                    mma16_op<T>::run(u32x4{lw[0] | (lw[1] << 16), lw[2] | (lw[3] << 16), lw[4] | (lw[5] << 16),
+                                           lw[6] | (lw[7] << 16)}, bf[u], acc);
+                } else {
+                    mma16_op<T>::run(u32x4{__float_as_uint(s[u][0].x), __float_as_uint(s[u][0].y),
+                                           __float_as_uint(s[u][0].z), __float_as_uint(s[u][0].w)}, bf[u], acc);
+                }
+            }
         }
     }
     // every batch of this pass; the first has been loaded
     __device__ void run(f32x4v& acc)
     {
         for (;;) {
+            f32x4 s[BATCH][VEC / 4];
 #pragma unroll
-            for (int u = 0; u < BATCH; ++u) {
-                f32x4 s[VEC / 4];  // this step of T: the partial sums of this lane's ranges, in range order
+            for (int u = 0; u < BATCH; ++u)
 #pragma unroll
-                for (int v = 0; v < VEC / 4; ++v) {
-                    s[v] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int v = 0; v < VEC / 4; ++v) s[u][v] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (n_tr == 1) {  // uniform: one range, no code to jump over between the steps
+                steps<false>(s, acc);
+            } else {
+                // more ranges than one load takes: the further ones first, through registers of their own (reloading x would
+                // cost the usual case, without them, a wait for all of x)
+                for (int t = RPR * q + sub; t - sub < n_tr; t += q) {  // uniform
+                    f32x4 y[BATCH][VEC / 4];
+                    const size_t t_at = (size_t)min(t, n_tr - 1) * tstride + lane_t;
 #pragma unroll
-                    for (int w = 0; w < RPR; ++w) {
-                        const bool use = t0 + w * q + sub < n_tr;
-                        s[v].x += use ? x[u][w][v].x : 0.f; s[v].y += use ? x[u][w][v].y : 0.f;
-                        s[v].z += use ? x[u][w][v].z : 0.f; s[v].w += use ? x[u][w][v].w : 0.f;
-                    }
+                    for (int u = 0; u < BATCH; ++u)
+#pragma unroll
+                        for (int v = 0; v < VEC / 4; ++v) y[u][v] = *reinterpret_cast<const f32x4*>(Tp + at(u) + 4 * v + t_at);
+#pragma unroll
+                    for (int u = 0; u < BATCH; ++u)
+#pragma unroll
+                        for (int v = 0; v < VEC / 4; ++v) add(s[u][v], y[u][v], t < n_tr);
                 }
-                if (ks0 + kOutWaves * u < nks) {  // uniform
-                    if constexpr (sizeof(T) == 2) {
-                        const float t[8] = {s[0].x, s[0].y, s[0].z, s[0].w, s[1].x, s[1].y, s[1].z, s[1].w};
-                        uint32_t hw[8], lw[8];
-#pragma unroll
-                        for (int v = 0; v < 8; ++v) {
-                            hw[v] = f32_to_bf16(t[v]);
-                            lw[v] = f32_to_bf16(t[v] - bf16_to_f32((bf16_t)hw[v]));
-                        }
-                        mma16_op<T>::run(u32x4{hw[0] | (hw[1] << 16), hw[2] | (hw[3] << 16), hw[4] | (hw[5] << 16),
-                                               hw[6] | (hw[7] << 16)}, bf[u], acc);
-                        mma16_op<T>::run(u32x4{lw[0] | (lw[1] << 16), lw[2] | (lw[3] << 16), lw[4] | (lw[5] << 16),
-                                               lw[6] | (lw[7] << 16)}, bf[u], acc);
-                    } else {
-                        mma16_op<T>::run(u32x4{__float_as_uint(s[0].x), __float_as_uint(s[0].y), __float_as_uint(s[0].z),
-                                               __float_as_uint(s[0].w)}, bf[u], acc);
-                    }
-                }
+                steps<true>(s, acc);
             }
             ks0 += kOutWaves * BATCH;
-            if (ks0 >= nks) {
-                ks0 %= kOutWaves;
-                t0 += RPR * q;
-                if (t0 >= n_tr) break;
-            }
+            if (ks0 >= nks) break;
             load();
             asm volatile("" ::: "memory");
         }
@@ -433,16 +477,7 @@ __global__ __launch_bounds__(64 * kOutWaves) void attend_out_kernel(const T* __r
         asm volatile("" ::: "memory");
         p1.run(acc);
     }
-    // acc[v] is tile row 4*kg+v, channel l16: add the rows that are ranges of one pair (they differ by a multiple of R) ...
-    if (R <= 8)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[v] += __shfl_xor(acc[v], 32, kWave);
-    if (R <= 4)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[v] += __shfl_xor(acc[v], 16, kWave);
-    if (R <= 2) { acc[0] += acc[2]; acc[1] += acc[3]; }
-    if (R == 1) acc[0] += acc[1];
-    // ... and the waves' latent shares, in order
+    // the waves' latent shares, in order: acc[v] is tile row 4*kg+v, channel l16
 #pragma unroll
     for (int v = 0; v < 4; ++v) red[wave][kg * 4 + v][l16] = acc[v];
     __syncthreads();

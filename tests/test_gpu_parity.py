@@ -112,6 +112,47 @@ def test_logits_tiles_of_128_tokens(oracle, dtype, H_kv, top_k, monkeypatch):
     _run(oracle, w, seq_lens=[700, top_k, 128, 5], label=f"128-token tiles {dtype} H_kv={H_kv} k={top_k}")
 
 
+@pytest.mark.parametrize("B,H,H_kv,ranges", [(1, 4, 4, 2), (1, 4, 4, 3), (2, 3, 3, 8), (1, 8, 2, 8), (2, 8, 2, 16), (16, 4, 4, 8),
+                                             (40, 2, 2, 2), (1, 4, 4, 16)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_token_ranges_that_cancel(dtype, B, H, H_kv, ranges, monkeypatch):
+    """The value sums of neighbouring token ranges are equal and opposite up to 1e-4: what is left keeps the precision of
+    fp32 sums.  Uniform weights of 1/1024 (zero query) and a projector that copies latent coordinates, so that every output
+    channel is one latent sum."""
+    print(f"[case] cancelling ranges {dtype} B={B} H={H}/{H_kv} ranges={ranges}", flush=True)
+    monkeypatch.setenv("SALS_TUNE_PV_RANGES", str(ranges))
+    n, r, d = 1024, 128, 128
+    dt = gu.out_dtype(synth.shrink(SMALL, dtype=dtype))
+    w = synth.shrink(SMALL, B=B, S=n, H=H, H_kv=H_kv, r=r, top_k=n, dtype=dtype)
+    ctx = gu.make_ctx(w)
+    g = torch.Generator(device=gu.DEV)
+    g.manual_seed(ranges + B)
+
+    def normal(*shape):
+        return torch.randn(*shape, generator=g, device=gu.DEV)
+
+    tok = -(-n // (64 * ranges)) * 64          # tokens of a range (whole 64-token steps)
+    of = torch.arange(n, device=gu.DEV) // tok
+    sign = torch.where(of >= n // tok // 2 * 2, 0.0, 1.0 - 2.0 * (of % 2))   # +, -, +, - ...; 0 without a whole partner
+    Vc = (normal(B, 1, r) * sign[None, :, None]).to(dt)
+    Vc[:, ::tok] = (0.02 * normal(B, Vc[:, ::tok].shape[1], r)).to(dt)       # one token a range holds what does not cancel
+    W = ctx.pack_weights(normal(H_kv * d, r).to(dt), torch.eye(d, r, device=gu.DEV).repeat(H_kv, 1).to(dt).contiguous())
+    out = torch.empty(B, H, d, dtype=dt, device=gu.DEV)
+    at = torch.full((B,), n, dtype=torch.int32, device=gu.DEV)
+    idx = torch.arange(n, dtype=torch.int32, device=gu.DEV).repeat(B, 1).contiguous()
+    ctx.sparse_attend(torch.zeros(B, H, d, dtype=dt, device=gu.DEV), at, normal(B, n, r).to(dt), Vc, W, idx, at, out)
+    torch.cuda.synchronize()
+    want = Vc.double().sum(dim=1)[:, None, :] / n
+    mass = Vc.double().abs().sum(dim=1)[:, None, :] / n
+    # one rounding of the result, and the roundings of the partial sums: products by 1/1024 are exact, and a sum passes
+    # through fewer than 16 additions of partial sums whose magnitudes add up to at most `mass`
+    bound = (2.0 ** -8 if dtype == "bf16" else 2.0 ** -23) * want.abs() + 2.0 ** -20 * mass
+    err = (out.double() - want).abs()
+    print(f"    worst error / bound {float((err / bound).max()):.3f}", flush=True)
+    assert bool((err <= bound).all())
+    ctx.close()
+
+
 def test_truncated_scoring_rank(oracle):
     w = synth.shrink(SMALL, r=256, r_score=128, B=2)
     _run(oracle, w, seq_lens=[1000, 500])
