@@ -107,7 +107,18 @@ __global__ __launch_bounds__(256) void dense_attend_kernel(const T* __restrict__
 #pragma unroll
             for (int v = 0; v < VEC; ++v) acc[m][n][v] = 0.f;
     }
-    auto consume = [&](const Rows& R, int j) {
+    auto consume = [&](Rows& R, int base) {
+        const int j = base + slot;
+        // The value words of slots past the chunk count as zero: the row they re-read is a live one, and its weight of zero
+        // would make a NaN of an infinity.  (The last set of a chunk only; the scores are masked below.)
+        if (base + UT * NS > j1) {  // uniform
+#pragma unroll
+            for (int u = 0; u < UT; ++u)
+#pragma unroll
+                for (int n = 0; n < NCH; ++n)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) R.v[u][n][e] = j + u * NS < j1 ? R.v[u][n][e] : 0u;
+        }
 #pragma unroll
         for (int m = 0; m < GMAX; ++m) {
             if (m < G) {  // uniform
@@ -157,10 +168,10 @@ __global__ __launch_bounds__(256) void dense_attend_kernel(const T* __restrict__
     // same for every lane group
     for (int j = j0; j < j1; j += 2 * UT * NS) {
         if (j + UT * NS < j1) load_rows(R1, j + UT * NS + slot, S - 1);
-        consume(R0, j + slot);
+        consume(R0, j);
         if (j + UT * NS < j1) {
             if (j + 2 * UT * NS < j1) load_rows(R0, j + 2 * UT * NS + slot, S - 1);
-            consume(R1, j + UT * NS + slot);
+            consume(R1, j + UT * NS);
         }
     }
 
@@ -224,9 +235,10 @@ __global__ __launch_bounds__(128) void dense_merge_kernel(const float* __restric
             A *= w0;
 #pragma unroll
             for (int u = 0; u < 16; ++u) {
-                const float w = k0 + u < n_chunks ? __expf(m[u] - mn) : 0.f;
-                L = fmaf(l[u], w, L);
-                A = fmaf(a[u], w, A);
+                const bool live = k0 + u < n_chunks;  // (a repeated record adds nothing, an infinity in it neither)
+                const float w = __expf(m[u] - mn);
+                L = fmaf(live ? l[u] : 0.f, w, L);
+                A = fmaf(live ? a[u] : 0.f, w, A);
             }
             M = mn;
         }

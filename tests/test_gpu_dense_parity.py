@@ -105,3 +105,30 @@ def test_head_blocks_and_short_chunks(oracle, H, H_kv, dtype):
     one past it, and a cache much larger than its sequences."""
     w = synth.shrink(SMALL, B=6, S=2100, H=H, H_kv=H_kv, r=64, dtype=dtype)
     _case(oracle, w, seq_lens=[1, 15, 16, 65, 257, 2100])
+
+
+@pytest.mark.parametrize("H,H_kv,dtype", [(4, 4, "bf16"), (8, 1, "bf16"), (3, 3, "bf16"), (4, 2, "f32")])
+def test_infinite_values_stay_infinite(H, H_kv, dtype):
+    """An infinite value gives an infinite output channel, whatever slots past a chunk or a sequence re-read: every token
+    holds one in its own channel, uniform weights."""
+    w = synth.shrink(SMALL, B=4, S=1000, H=H, H_kv=H_kv, r=64, dtype=dtype)
+    print(f"[case] dense infinities H={H}/{H_kv} {dtype}", flush=True)
+    dt = gu.out_dtype(w)
+    lens = [1000, 513, 100, 37]
+    q = torch.ones((w.B, w.H, w.d), dtype=dt, device=gu.DEV)
+    K = torch.zeros((w.B, w.S, w.H_kv, w.d), dtype=dt, device=gu.DEV)
+    V = torch.ones_like(K)
+    t = torch.arange(w.S, device=gu.DEV)
+    V[:, t, :, t % w.d] = float("inf")
+    sl = torch.tensor(lens, dtype=torch.int32, device=gu.DEV)
+    out = torch.empty((w.B, w.H, w.d), dtype=dt, device=gu.DEV)
+    ctx = gu.make_ctx(w)
+    ctx.dense_attend(q, sl, K, V, sl, out)
+    torch.cuda.synchronize()
+    y = out.float().cpu()
+    for b, n in enumerate(lens):
+        m = min(n, w.d)
+        assert bool(torch.isposinf(y[b, :, :m]).all()), (b, n)
+        # weights of 1/n: their sum to 1 within n roundings, one rounding of the result
+        assert bool(((y[b, :, m:] - 1.0).abs() <= 2.0 ** -8).all()), (b, n)
+    ctx.close()
