@@ -28,11 +28,10 @@ constexpr int kCalThreads = 256;    // workgroup of the row kernels (D is a mult
 constexpr int kCalMaxD = 8192;
 
 // XT[d, t] = X[t, d] for t < n, zero for n <= t < n_pad; X [n, D], XT [D, n_pad]
-template <typename T>
-__global__ __launch_bounds__(256) void calib_transpose_kernel(const T* __restrict__ X, T* __restrict__ XT, long long n, int D,
+__global__ __launch_bounds__(256) void calib_transpose_kernel(const float* __restrict__ X, float* __restrict__ XT, long long n, int D,
                                                               long long n_pad)
 {
-    __shared__ T tile[kCalTile][kCalTile + 2];
+    __shared__ float tile[kCalTile][kCalTile + 2];
     const long long t0 = (long long)blockIdx.x * kCalTile;
     const int d0 = blockIdx.y * kCalTile;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;  // 64 x 4
@@ -40,12 +39,7 @@ __global__ __launch_bounds__(256) void calib_transpose_kernel(const T* __restric
     for (int i = 0; i < kCalTile; i += 4) {
         const long long t = t0 + ty + i;
         const int d = d0 + tx;
-        T v;
-        if (t < n && d < D) v = X[(size_t)t * D + d];
-        else {
-            if constexpr (sizeof(T) == 2) v = 0; else v = 0.f;
-        }
-        tile[ty + i][tx] = v;
+        tile[ty + i][tx] = t < n && d < D ? X[(size_t)t * D + d] : 0.f;
     }
     __syncthreads();
 #pragma unroll

@@ -2,16 +2,13 @@
 // prompt at once):  K~ = K U_k,  V~ = V U_v  for n_tok new tokens per sequence, written to the
 // cache rows seq_len[b] .. seq_len[b] + n_new[b] - 1.
 //
-// A plain GEMM on the matrix cores, [tokens x D_kv] . [D_kv x r], both operands read along their
-// contiguous axis: the token rows as they lie in memory and the TRANSPOSED projector U^T [r x D_kv]
-// (section 0 / 1 of the packed weights, the same rows the one-token projection reads).  One workgroup
-// owns TOK tokens x NL latent coordinates of one sequence and one projection; its eight waves are
-// 4 token groups x 2 latent groups (NL = 128) or 8 token groups (NL = 64), a wave tile being TOK/4 (TOK/8) tokens
-// x 64 latent coordinates.  TOK = 256, or 128 when the larger tile would leave most of the chip without a workgroup.  Both operand tiles walk the D axis in 64-byte steps
-// through three swizzled LDS stages with the software pipeline of the logits kernel (fragments of the
-// next half step are read under the MFMAs of the current one; the step after next moves from registers
-// to the third stage).  fp32 accumulation, one rounding to the storage type at the store, so a row
-// equals the one-token projection of the same token up to the order of the fp32 sum.
+// A plain GEMM on the matrix cores, [tokens x D_kv] . [D_kv x r], both operands read along their contiguous axis: the token
+// rows as they lie in memory and the TRANSPOSED projector U^T [r x D_kv] (section 0 / 1 of the packed weights, the same rows
+// the one-token projection reads).  fp32 accumulation, one rounding to the storage type at the store, so a row equals the
+// one-token projection of the same token up to the order of the fp32 sum.
+//   prefill_tile_kernel       bf16: both operands straight into LDS, tiles of up to 256 x 320, a list of tiles over the batch
+//   prefill_compress_kernel   fp32: operands staged through registers, tiles of up to 256 x 128 of one sequence; also the
+//                             symmetric product of the calibration for fp32 keys
 #pragma once
 #include <type_traits>
 
@@ -36,14 +33,22 @@ struct PrefillArgs {
     int kslice_steps;        // SYRK form only: 64-byte steps of the contraction axis per slice (blockIdx.y = slice)
 };
 
+// fp32 prompts.  One workgroup owns TOK tokens x NL latent coordinates of one sequence and one projection; its eight waves
+// are 4 token groups x 2 latent groups (NL = 128) or 8 token groups (NL = 64), a wave tile being TOK/4 (TOK/8) tokens x 64
+// latent coordinates.  TOK = 256, or 128 when the larger tile would leave most of the chip without a workgroup.  Both operand
+// tiles walk the D axis in 64-byte steps through three swizzled LDS stages: the fragments of the next half step are read
+// under the MFMAs of the current one, and the step after next moves from registers to the third stage.  Bound by the fp32
+// matrix instructions.
+//
 // SYRK: the same tiles and pipeline as a plain product of two row-major operands, out[t, l] = sum_c X[t, c] UT[l, c],
 // whose fp32 tile sums are stored as they are instead of becoming cache rows (the covariance of the offline
 // calibration, Sec. 4.2, with X = UT = the transposed keys and c running over the calibration tokens).  The
 // contraction axis is cut into slices (blockIdx.y), each with its own output matrix, so that narrow matrices still
 // fill the chip; a second kernel adds the slices to the fp64 covariance.
-template <typename T, int TOK, int NL, bool SYRK = false>
+template <int TOK, int NL, bool SYRK = false>
 __global__ __launch_bounds__(kPfThreads, 2) void prefill_compress_kernel(PrefillArgs a)
 {
+    typedef float T;
     static_assert((NL == 128 || NL == 64) && (TOK == 256 || (TOK == 128 && NL == 128)), "tile");
     constexpr int kPfTok = TOK;
     constexpr int ES = (int)sizeof(T);
@@ -182,7 +187,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_compress_kernel(Prefill
             if (t < n_b && row0 >= 0 && row < a.S_max) {
 #pragma unroll
                 for (int nb = 0; nb < 2; ++nb)
-                    elem<T>::store(cache + (size_t)row * a.r + lat0 + wn * 64 + nb * 32 + l32, acc[mb][nb][v]);
+                    cache[(size_t)row * a.r + lat0 + wn * 64 + nb * 32 + l32] = acc[mb][nb][v];
             }
         }
 }

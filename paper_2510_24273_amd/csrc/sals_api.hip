@@ -1014,8 +1014,8 @@ sals_status sals_compress_prefill(sals_ctx* ctx, const void* k_new, const void* 
         const int tok = (nl == 128 && (long long)ceil_div(n_tok, 256) * (d.r / nl) * d.B * 2 < 384) ? 128 : 256;
         const dim3 grid(ceil_div(n_tok, tok), d.r / nl, d.B * 2);
         const size_t lds = prefill_lds_bytes(tok, nl);
-        auto kern = nl == 64 ? prefill_compress_kernel<float, 256, 64>
-                             : (tok == 128 ? prefill_compress_kernel<float, 128, 128> : prefill_compress_kernel<float, 256, 128>);
+        auto kern = nl == 64 ? prefill_compress_kernel<256, 64>
+                             : (tok == 128 ? prefill_compress_kernel<128, 128> : prefill_compress_kernel<256, 128>);
         if (!allow(reinterpret_cast<const void*>(kern), lds)) return SALS_ERR_HIP;
         hipLaunchKernelGGL(kern, grid, dim3(kPfThreads), lds, st, a);
     }
@@ -1475,7 +1475,6 @@ sals_status sals_overlap_score(sals_ctx* ctx, const void* q, const int32_t* q_po
 // ---- offline calibration (Sec. 4.2) ----------------------------------------------------
 namespace {
 constexpr int64_t kCalChunk = 4096;  // tokens whose products are summed in fp32 before they are added to the fp64 matrix
-size_t cal_es(int32_t dtype) { return dtype == SALS_BF16 ? 2 : 4; }
 
 // slices of a chunk's token axis (each a separate fp32 output of the GEMM): as many as bring the launch to about two
 // workgroups per compute unit, at most 8, every slice at least 256 tokens long
@@ -1489,18 +1488,17 @@ int cal_slices(int D)
     return z;
 }
 
-template <typename T>
-sals_status calib_accumulate_t(const void* K, int64_t n_tok, int D, double* C, void* ws, hipStream_t st)
+sals_status calib_accumulate_f32(const void* K, int64_t n_tok, int D, double* C, void* ws, hipStream_t st)
 {
-    const T* X = static_cast<const T*>(K);
-    T* XT = static_cast<T*>(ws);
-    float* P = reinterpret_cast<float*>(static_cast<unsigned char*>(ws) + align_up((size_t)D * kCalChunk * sizeof(T)));
+    const float* X = static_cast<const float*>(K);
+    float* XT = static_cast<float*>(ws);
+    float* P = reinterpret_cast<float*>(static_cast<unsigned char*>(ws) + align_up((size_t)D * kCalChunk * 4));
     const bool big = D % 256 == 0 && D >= 2048;  // (below that the larger tile leaves most of the chip without a workgroup)
-    const int step_tok = kLgStep / (int)sizeof(T);  // tokens per 64-byte step of the contraction axis
+    const int step_tok = kLgStep / 4;  // tokens per 64-byte step of the contraction axis
     for (int64_t t0 = 0; t0 < n_tok; t0 += kCalChunk) {
         const int64_t n = std::min(kCalChunk, n_tok - t0);
         const int64_t n_pad = (n + 63) / 64 * 64;  // whole 64-byte steps of the contraction axis, zero filled
-        hipLaunchKernelGGL((calib_transpose_kernel<T>), dim3((unsigned)(n_pad / kCalTile), (unsigned)ceil_div(D, kCalTile)),
+        hipLaunchKernelGGL(calib_transpose_kernel, dim3((unsigned)(n_pad / kCalTile), (unsigned)ceil_div(D, kCalTile)),
                            dim3(256), 0, st, X + (size_t)t0 * D, XT, (long long)n, D, (long long)n_pad);
         const int steps = (int)(n_pad / step_tok);
         const int per = ceil_div(steps, std::min(cal_slices(D), std::max(1, steps / 2)));  // >= 2 steps per slice
@@ -1511,11 +1509,11 @@ sals_status calib_accumulate_t(const void* K, int64_t n_tok, int D, double* C, v
         // tiles that reach the upper triangle only (the kernel numbers them row by row)
         if (big) {
             const int nt = D / 256;
-            hipLaunchKernelGGL((prefill_compress_kernel<T, 256, 128, true>), dim3(nt * nt + nt, slices, 1), dim3(kPfThreads),
+            hipLaunchKernelGGL((prefill_compress_kernel<256, 128, true>), dim3(nt * nt + nt, slices, 1), dim3(kPfThreads),
                                prefill_lds_bytes(256, 128), st, a);
         } else {
             const int nt = D / 128;
-            hipLaunchKernelGGL((prefill_compress_kernel<T, 128, 128, true>), dim3(nt * (nt + 1) / 2, slices, 1),
+            hipLaunchKernelGGL((prefill_compress_kernel<128, 128, true>), dim3(nt * (nt + 1) / 2, slices, 1),
                                dim3(kPfThreads), prefill_lds_bytes(128, 128), st, a);
         }
         hipLaunchKernelGGL(calib_reduce_kernel, dim3((unsigned)(((size_t)D * D / 4 + 255) / 256)), dim3(256), 0, st, C, P, D,
@@ -1565,25 +1563,22 @@ sals_status calib_accumulate_bf16(const void* K, int64_t n_tok, int D, double* C
     return SALS_OK;
 }
 
-template <typename T> sals_status calib_lds_attr()
+sals_status calib_lds_attr(int32_t dtype)
 {
     static std::mutex m;
-    static bool done[kMaxDevices];
+    static bool done[2][kMaxDevices];
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SALS_ERR_HIP;
     std::lock_guard<std::mutex> lock(m);
-    if (done[dev]) return SALS_OK;
-    if constexpr (sizeof(T) == 2) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(calib_cov_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)kCovLds) != hipSuccess)
-            return SALS_ERR_HIP;
-    } else if (hipFuncSetAttribute(reinterpret_cast<const void*>(prefill_compress_kernel<T, 256, 128, true>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)prefill_lds_bytes(256, 128)) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(prefill_compress_kernel<T, 128, 128, true>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)prefill_lds_bytes(128, 128)) != hipSuccess)
-        return SALS_ERR_HIP;
-    done[dev] = true;
-    return SALS_OK;
+    bool& ok = done[dtype == SALS_BF16][dev];
+    if (ok) return SALS_OK;
+    auto allow = [](const void* kern, size_t bytes) {
+        return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
+    };
+    if (dtype == SALS_BF16) ok = allow(reinterpret_cast<const void*>(calib_cov_kernel), kCovLds);
+    else ok = allow(reinterpret_cast<const void*>(prefill_compress_kernel<256, 128, true>), prefill_lds_bytes(256, 128)) &&
+              allow(reinterpret_cast<const void*>(prefill_compress_kernel<128, 128, true>), prefill_lds_bytes(128, 128));
+    return ok ? SALS_OK : SALS_ERR_HIP;
 }
 }  // namespace
 
@@ -1594,7 +1589,7 @@ size_t sals_calib_accumulate_workspace_bytes(int32_t dtype, int32_t D)
     if ((dtype != SALS_BF16 && dtype != SALS_F32) || D < 128 || D % 128 != 0 || D > kCalMaxD) return 0;
     if (dtype == SALS_BF16) return align_up((size_t)cov_tiles(D) * cov_max_slices(D) * kCovTile * kCovTile * 4);  // tile sums
     // the transposed keys of a chunk, then the fp32 tile sums of its slices
-    return align_up((size_t)D * kCalChunk * cal_es(dtype)) + align_up((size_t)cal_slices(D) * D * D * 4);
+    return align_up((size_t)D * kCalChunk * 4) + align_up((size_t)cal_slices(D) * D * D * 4);
 }
 
 sals_status sals_calib_accumulate(int32_t dtype, const void* K, int64_t n_tok, int32_t D, double* C, void* workspace,
@@ -1606,12 +1601,9 @@ sals_status sals_calib_accumulate(int32_t dtype, const void* K, int64_t n_tok, i
         workspace_bytes < sals_calib_accumulate_workspace_bytes(dtype, D))
         return SALS_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    if (dtype == SALS_BF16) {
-        if (calib_lds_attr<bf16_t>() != SALS_OK) return SALS_ERR_HIP;
-        return calib_accumulate_bf16(K, n_tok, D, C, workspace, st);
-    }
-    if (calib_lds_attr<float>() != SALS_OK) return SALS_ERR_HIP;
-    return calib_accumulate_t<float>(K, n_tok, D, C, workspace, st);
+    if (calib_lds_attr(dtype) != SALS_OK) return SALS_ERR_HIP;
+    if (dtype == SALS_BF16) return calib_accumulate_bf16(K, n_tok, D, C, workspace, st);
+    return calib_accumulate_f32(K, n_tok, D, C, workspace, st);
 }
 
 namespace {
