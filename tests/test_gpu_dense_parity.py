@@ -99,12 +99,13 @@ def test_cfg3b_shape_sampled_sequences(oracle):
     _case(oracle, C["cfg3b"], seqs=[0, 9])
 
 
-@pytest.mark.parametrize("H,H_kv,dtype", [(3, 3, "bf16"), (8, 1, "bf16"), (16, 2, "f32"), (12, 4, "bf16")])
+@pytest.mark.parametrize("H,H_kv,dtype", [(3, 3, "bf16"), (4, 4, "bf16"), (6, 3, "bf16"), (4, 2, "bf16"), (12, 4, "bf16"),
+                                          (8, 2, "bf16"), (8, 1, "bf16"), (16, 2, "f32"), (2, 2, "f32")])
 def test_head_blocks_and_short_chunks(oracle, H, H_kv, dtype):
-    """One and two KV heads per workgroup with every group size, lengths below a trip of the token slots, at its edge and
-    one past it, and a cache much larger than its sequences."""
-    w = synth.shrink(SMALL, B=6, S=2100, H=H, H_kv=H_kv, r=64, dtype=dtype)
-    _case(oracle, w, seq_lens=[1, 15, 16, 65, 257, 2100])
+    """One and two KV heads per workgroup with group sizes of 1, 2, 3, 4 and 8, lengths below a trip of the token slots, chunks
+    of whole trips and of one token set more, and a cache much larger than its sequences."""
+    w = synth.shrink(SMALL, B=10, S=2100, H=H, H_kv=H_kv, r=64, dtype=dtype)
+    _case(oracle, w, seq_lens=[1, 15, 16, 65, 257, 1024, 1025, 2048, 2049, 2100])
 
 
 @pytest.mark.parametrize("H,H_kv,dtype", [(4, 4, "bf16"), (8, 1, "bf16"), (3, 3, "bf16"), (4, 2, "f32")])

@@ -120,6 +120,12 @@ def test_prefill_then_decode_matches_token_by_token_append(oracle):
     (6, 4001, 8, 640, [4001, 3334, 3001, 0, 2334, 128]),    # whole rounds of large tiles, the rest in small ones
     (2, 9000, 8, 1024, None),                               # the same without per-sequence counts
     (1, 3000, 32, 576, None),
+    (1, 4097, 1, 448, None),                                # the smaller tiles alone: 128 x 192,
+    (1, 10001, 1, 256, None),                               # 256 x 128,
+    (1, 12289, 1, 448, None),                               # 256 x 256 and
+    (1, 24577, 1, 320, None),                               # 256 x 320
+    (1, 16385, 2, 256, None),                               # 256 x 128 with the rest in 128 x 64
+    (2, 12289, 1, 704, [12289, 12000]),                     # 256 x 256 with the rest in 128 x 192
 ])
 def test_tile_shapes_and_remainders(B, n_tok, H_kv, r, lens):
     """Every tile shape the batch compression chooses from, at sizes that leave remainders, into a cache that already

@@ -96,7 +96,7 @@ def test_edge_lengths(oracle):
 
 
 def test_windows_of_several_sequences_share_a_tile(oracle, monkeypatch):
-    """The window's logits pass on tiles of four sequences' windows, latent axis in two slices (forced at this size)."""
+    """The window's logits pass on tiles of two sequences' windows, an odd batch, latent axis in two slices (forced at this size)."""
     monkeypatch.setenv("SALS_TUNE_LOGITS", "4")
     monkeypatch.setenv("SALS_TUNE_MULTI_KSPLIT", "2")
     w = synth.shrink(SMALL, B=9, plant=0)

@@ -101,13 +101,13 @@ def test_gqa_interleaved_rope_and_ring_wrap(oracle):
 
 @pytest.mark.parametrize("dtype,ks", [("bf16", 1), ("bf16", 2), ("f32", 4)])
 def test_windows_of_several_sequences_share_a_tile(oracle, dtype, ks, monkeypatch):
-    """The window pass on tiles made of four sequences' windows (chosen by itself for batches of eight and more, see
-    the cfg3a case below; forced here at a small rank), unsplit and with the latent axis in slices: a batch that is no
-    multiple of four, with empty sequences, windows that are not full and full ones."""
+    """The window pass on tiles made of two sequences' windows (chosen by itself for batches of eight and more where it is
+    estimated to be faster, as in the cfg3a case below; forced here at a small rank), unsplit and with the latent axis in
+    slices: an odd batch, with empty sequences, windows that are not full and full ones."""
     monkeypatch.setenv("SALS_TUNE_LOGITS", "4")
     monkeypatch.setenv("SALS_TUNE_MULTI_KSPLIT", str(ks))
-    w = synth.shrink(SMALL, B=10, plant=0, dtype=dtype)
-    _case(oracle, w, seq_lens=[1000, 0, 1, 40, 41, 144, 145, 500, 23, 999])
+    w = synth.shrink(SMALL, B=11, plant=0, dtype=dtype)
+    _case(oracle, w, seq_lens=[1000, 0, 1, 40, 41, 144, 145, 500, 23, 999, 39])
 
 
 def test_shared_tiles_gqa_interleaved_rope_ring_wrap(oracle, monkeypatch):
