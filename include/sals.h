@@ -31,7 +31,8 @@
  *   copies for the projections, a matrix-core tile order for the reconstruction).
  * Asynchrony.  Each call only enqueues kernels on `hip_stream` (a hipStream_t
  *   passed as void*, NULL = the default stream) and returns; nothing synchronises
- *   and no device data is read on the host.  Calls that share one context must be
+ *   and no device data is read on the host, except where a call says so
+ *   (sals_prepare, sals_calib_eigenvectors, sals_profile_collect).  Calls that share one context must be
  *   ordered on one stream (they share the workspace).
  * Errors.  Every call returns a sals_status; nothing throws or aborts.  Argument
  *   and descriptor errors are detected on the host before anything is enqueued.
@@ -99,9 +100,9 @@ sals_status sals_create(const sals_desc* desc, void* d_workspace, size_t workspa
 void sals_destroy(sals_ctx* ctx);
 
 /* One-time device set-up of a context: fills the cos/sin table of the workspace with one
- * kernel on `hip_stream`, WAITS for it (the only call of this library that blocks the host),
- * and raises the LDS limit of the kernels the context will launch.  Afterwards calls on the
- * context may come from any stream and may be captured into HIP graphs.
+ * kernel on `hip_stream`, WAITS for it (only this call, sals_calib_eigenvectors and
+ * sals_profile_collect block the host), and raises the LDS limit of the kernels the
+ * context will launch.  Afterwards calls on the context may come from any stream and may be captured into HIP graphs.
  * A context that was never prepared still works: the first call that needs the table
  * enqueues the fill on its own stream, calls on the same stream follow by stream order and
  * calls on other streams wait for an event; but such a context must not be used under
@@ -417,12 +418,13 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
 
 /* ---- measurement aid --------------------------------------------------------------
  * Per-stage timing for roofline figures.  While enabled, every stage below (one kernel;
- * for the selection of sequences above 32768 tokens a chain of four, for the logits of very
- * short selections two) is bracketed by a
- * pair of HIP events on the call's stream (host-side event objects; no device memory).  sals_profile_collect waits for the recorded events, adds
- * the elapsed milliseconds and launch counts per kernel into total_ms / launches (host
- * arrays of SALS_N_KERNELS entries, overwritten) and forgets the records.  Timing with
- * events serialises neighbouring launches slightly; leave it off in timed runs. */
+ * for the selection of sequences above 32768 tokens a chain of three, or of four on its own,
+ * for logits whose latent axis is split two, for a prompt whose tiles do not fill whole rounds
+ * two) is bracketed by a pair of HIP events on the call's stream (host-side event objects; no
+ * device memory).  sals_profile_collect waits for the recorded events, adds the elapsed
+ * milliseconds and launch counts per kernel into total_ms / launches (host arrays of
+ * SALS_N_KERNELS entries, overwritten) and forgets the records.  Timing with events serialises
+ * neighbouring launches slightly; leave it off in timed runs. */
 enum {
     SALS_K_PROJECT = 0,        /* latent projection (query, or new key/value)  */
     SALS_K_SCORES = 1,         /* latent score stream over the key cache       */

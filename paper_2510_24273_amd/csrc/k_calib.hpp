@@ -52,10 +52,10 @@ __global__ __launch_bounds__(256) void calib_transpose_kernel(const float* __res
 
 // Covariance of bf16 keys, C += X^T X, as tiles of 256 x 256 of the upper triangle: P[slice][tile] = the fp32 tile sums over
 // one slice of the tokens (at most 4096 of them).  grid (tiles * slices), 512 threads, one workgroup per compute unit.
-// Matrix-bound: 1.1 PFLOP/s sustained at D = 4096, 32768 tokens (529 us for 1088 items of 0.54 GFLOP), what the chip's
-// power leaves of its rate on such operands (cutting the last, partly filled round into quarter items changed nothing).
-// With the addition below 633 us; a transposing copy of the keys, 256 x 128 tiles staged through registers and an
-// addition per 4096 tokens took 1395 us.
+// Matrix-bound: 1.04 PFLOP/s sustained at D = 4096, 32768 tokens (560 us for 1088 items of 0.54 GFLOP, 545 to 575 from run
+// to run), what the chip's power leaves of its rate on such operands (cutting the last, partly filled round into quarter items
+// changed nothing).  With the addition below 636 to 650 us a call; a transposing copy of the keys, 256 x 128 tiles staged through
+// registers and an addition per 4096 tokens took 1400 us.
 //
 // The contraction runs over the tokens, the axis along which the keys are not contiguous: token rows go to LDS as they
 // lie in memory (32 tokens x 256 columns for either side, 16 bytes per lane without passing through registers, four

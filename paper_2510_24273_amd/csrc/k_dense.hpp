@@ -9,8 +9,9 @@
 // (token, head) row of K and of V in 16-byte pieces, so with two heads a load of a wave is 512 bytes of a token's row in one
 // piece; the dot product is folded with DPP rotations, softmax runs online per 16-lane group over UT tokens at a time (one in
 // fp32, where rows are twice as long), whose rows are requested together and one set ahead.  The lane groups of a head and
-// then the chunks are merged by log-sum-exp in a fixed order.  One workgroup per compute unit streams best (batch 16, 4096 tokens, 32 heads: 7.0 TB/s;
-// one head per workgroup, a token at a time, 256-token chunks: 5.9).  Batch 8, 2048 tokens: 50.7 -> 43.4 us with the merge.
+// then the chunks are merged by log-sum-exp in a fixed order.  One workgroup per compute unit streams best (batch 16, 4096
+// tokens, 32 heads: 7.1 TB/s with the merge; one head per workgroup, a token at a time, 256-token chunks: 5.9).  Batch 8, 2048
+// tokens: 50.7 -> 43.3 us with the merge.
 #pragma once
 #include "common.hpp"
 #include "k_attend.hpp"

@@ -21,8 +21,10 @@
 // Workgroup: HEADS x NTG waves, i.e. HEADS heads x (NTG*32*NB) tokens.  Two shapes: two heads x 256 tokens (8 waves) where that
 // fills the chip: the least operand traffic per product, the matrix cores' power is the bound; one head x 128 tokens
 // (4 waves, two workgroups per compute unit) for the launches in between that and the 64-token kernel, where idle compute
-// units and the feed from the L2 are the bound (one sequence, 32 heads, 1024 tokens, r = 640, attention in all: 26.2 -> 20.6 us;
-// 8 KV heads, 4160 tokens, r = 512: 28.8 -> 26.1; 12 sequences, 8 KV heads, 512 tokens: 29.5 -> 27.5).
+// units and the feed from the L2 are the bound.  Attention in all (sals_sparse_attend), 256-token tiles / these / the 64-token
+// kernel: one sequence, 32 heads, 1024 tokens, r = 640: 26.3 / 20 / 24.5 us; one sequence, 8 KV heads, 4160 tokens, r = 512:
+// 30.3 / 25.4 / 37.3; 12 sequences, 8 KV heads, 512 tokens, r = 640: 31.1 / 26.3 / 38.2; and 16 sequences, 32 heads, 512 tokens:
+// 54.2 / 69.3 / 156.
 #pragma once
 #include "common.hpp"
 #include "k_attend.hpp"

@@ -198,9 +198,10 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_compress_kernel(Prefill
 // one's MFMAs, one barrier per step.  The latent coordinates are the MFMA's rows, so a lane ends up with four consecutive
 // coordinates of a token and stores 8 bytes at a time.
 // Matrix-bound while the whole chip works (22 ns per MFMA and SIMD at the clock its power leaves, 13.4 with few workgroups);
-// what is lost to it is the last round of tiles and 7 to 10 us per round to start and store.  Against the 256 x 128 and
-// 128 x 128 tiles staged through registers, two workgroups per compute unit, that this replaced: 6 ragged prompts of up to
-// 4001 tokens, D = 1024, r = 640 91 -> 75 us; 6000 tokens, D = 4096, r = 1024 127 -> 100 us; 64 tokens, D = 4096 38 -> 15 us.
+// what is lost to it is the last round of tiles and 2 (smallest tile) to 13 us (largest) per round to start and store.  Whole
+// calls, with the launch that advances the lengths, against the 256 x 128 and 128 x 128 tiles staged through registers, two
+// workgroups per compute unit, that this replaced: 6 ragged prompts of up to 4001 tokens, D = 1024, r = 640 91 -> 78 us;
+// 6000 tokens, D = 4096, r = 1024 125 -> 99 us; 64 tokens, D = 4096 44 -> 20 us.
 // Tiles: without n_new the prompts of a batch are one run of B n_tok rows (a tile may span sequences); with n_new every
 // sequence has tiles of its own and only those that hold tokens are in the list (its length is known on the device only, so
 // the launch covers n_tok everywhere and the workgroups past the end leave at once).

@@ -93,7 +93,7 @@ __device__ __forceinline__ void qv_quantize_group(const QuantArgs& qa, const int
 // the projector and as much of the inputs at D = 4096.  So where a second launch follows anyway the axis is sliced and that
 // launch adds the slices up (append_finish_kernel), and where none does (a recent window) eight waves have all their pieces in
 // flight.  (Batch 16, D = 4096, r = 512, 2-bit values, with the advance: 12.4 + 3.9 + 1.4 us as three launches of four waves,
-// 10.2 + 1.4 with eight waves over the whole axis, 5.1 + 2.6 sliced.)
+// 10.2 + 1.4 with eight waves over the whole axis, 5.3 + 2.8 sliced.)
 template <typename T, int NW, bool QUANT>
 __global__ __launch_bounds__(64 * NW) void append_kernel(ProjArgs a, QuantArgs qa)
 {

@@ -60,7 +60,7 @@ __device__ __forceinline__ void warm_projector(const T* __restrict__ Uv, int r, 
 // registers.  fp32 (two tokens per MFMA, one per half-wave): the loaded words are the operands as they are.
 //
 // TWO: a second cache under the same softmax (the recent window beside the low-rank cache) takes the workgroups behind the
-// first cache's: two launches of a few dozen workgroups each would follow one another for nothing (one sequence: 10.8 -> 5.7 us).
+// first cache's: two launches of a few dozen workgroups each would follow one another for nothing (one sequence: 5.8 + 5.3 -> 5.3 us).
 // Otherwise the workgroups behind warm the output projection's U_v.
 template <typename T> struct PvSecond {
     const int32_t* idx; const int32_t* n_sel; const T* Vc; const float* logits; float* Tpart;
@@ -315,8 +315,9 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
 // A few KB per workgroup: the kernel is one memory round trip if every load is requested before the first is used, and
 // little code (each launch starts with cold instruction caches).  So a wave requests BATCH latent steps of U_v with RPR
 // loads of T each in one batch, from clamped addresses and without a branch (predicated loads were waited for one by one).
-// Inside the launch, one sequence, 32 heads, r = 640, 4 ranges: 5.1 -> 2.6 us (0.8 of it by warm_projector); 16 sequences, one
-// range: 4.7 -> 3.4 us; one sequence, 8 KV heads, 8 ranges: 6.3 -> 3.6 us.
+// Launch durations (kernel trace) before -> now: one sequence, 32 heads, r = 640, 4 ranges 5.9 -> 3.7 us (0.8 of it by
+// warm_projector); 16 sequences, one range 5.4 -> 4.7; one sequence, 8 KV heads, 8 ranges 6.8 -> 4.0; 4 sequences, 6 ranges
+// 7.7 -> 5.1; one sequence with a window of rank 2048 11.7 -> 7.9.
 // ---------------------------------------------------------------------------------
 constexpr int kOutWaves = 8;
 // one cache's share of the contraction, as a wave walks it

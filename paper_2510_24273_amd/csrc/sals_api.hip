@@ -209,7 +209,10 @@ Layout make_layout(const sals_desc& d)
         L.dn_chunks = ceil_div(d.S_max, L.dn_tok);
         L.dn_part = take((size_t)d.B * d.H_q * L.dn_chunks * kDnRec * 4);
     }
-    // long sequences: selection spread over 8192-score chunks
+    // Long sequences: selection spread over 8192-score chunks.  The line lies where topk_kernel's keys no longer fit in
+    // registers.  At it the two are level inside a step (4 x 32768: 15.4 us for the one launch, 16.4 for the chain of three, both
+    // with the gap before a launch) and on its own the one launch is faster (13.4 against 17.9 us for the chain of four; 7.9 at
+    // 16384 scores; the chain takes 18.4 at 131072).
     L.tm_chunks = d.S_max > 32768 ? ceil_div(d.S_max, kTmChunk) : 0;
     if (L.tm_chunks > 0) {
         L.tm_part = take((size_t)d.B * L.tm_chunks * sizeof(uint2));
@@ -534,7 +537,8 @@ template <typename T> LogitsPlan plan_logits(const sals_desc& d)
         const int n_steps = d.r * (int)sizeof(T) / kLgStep;
         const long long tiles = (long long)ceil_div(d.B, 2) * d.H_kv;
         int ks = 1;
-        // (one workgroup per compute unit, or two where that leaves long slices: 16 sequences, 32 heads, r = 2048: 118 -> 116 us)
+        // (one workgroup per compute unit, or two where that leaves long slices.  A step of 16 sequences, 32 heads, r_hi = 2048
+        // with one / two / four slices: 109.3 / 109.2 / 113.5 us; of 8 sequences 82.6 / 79.0 / 76.9)
         while (ks < kLsMaxSplit && tiles * ks < 512 && n_steps % (2 * ks) == 0 && n_steps / (2 * ks) >= (tiles * ks < 256 ? 8 : 24)) ks *= 2;
         if (const char* e = std::getenv("SALS_TUNE_MULTI_KSPLIT")) {  // tuning aid: any divisor of the step count up to 8
             const int v = std::atoi(e);
@@ -583,7 +587,7 @@ bool fused_selection(const sals_ctx* c)
            d.top_k + d.n_sink + d.n_recent <= kLsFusedMaxK && c->fuse_select;
 }
 
-// the instantiation of the 256-token logits kernel for a group size (query heads per KV head)
+// the instantiation of attend_logits_kernel (256- and 128-token tiles) for a group size (query heads per KV head)
 template <typename T, int HEADS, int NTG, int NB, bool MULTI = false> auto logits_kernel_for(int group)
 {
     if (group == 1) return attend_logits_kernel<T, HEADS, NTG, NB, 1, 1, MULTI>;
