@@ -1620,7 +1620,7 @@ int jac_slices(int D)
     return s;
 }
 struct EigWs {  // byte offsets into the workspace
-    size_t G, fail, conv, norm, sgn, diag, part, total;
+    size_t G, conv, norm, sgn, diag, part, total;
 };
 EigWs eig_ws(int D)
 {
@@ -1628,8 +1628,7 @@ EigWs eig_ws(int D)
     size_t o = 0;
     auto take = [&](size_t bytes) { const size_t at = o; o = align_up(o + bytes); return at; };
     w.G = take((size_t)D * D * 8);               // the rotated factor
-    w.fail = take(sizeof(int));                  // a pivot of the factorisation was not positive
-    w.conv = take((size_t)(D / (2 * kJacB)) * 8);  // convergence slots
+    w.conv = take((size_t)(D / (2 * kJacB)) * 8);  // convergence slots; before the sweeps, whether a pivot was not positive
     w.norm = take((size_t)D * 8);                // row norms and signs
     w.sgn = take((size_t)D * 8);
     w.diag = take((size_t)D * kCalPanel * 8);    // factored diagonal blocks
@@ -1659,7 +1658,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     const EigWs off = eig_ws(D);
     auto at = [&](size_t o) { return reinterpret_cast<double*>(ws + o); };
     double *G = at(off.G), *conv = at(off.conv), *norm = at(off.norm), *sgn = at(off.sgn), *diag = at(off.diag), *part = at(off.part);
-    int* fail = reinterpret_cast<int*>(ws + off.fail);
+    int* fail = reinterpret_cast<int*>(ws + off.conv);
     const int n_pairs = D / (2 * kJacB), n_steps = D / kJacB - 1, slices = jac_slices(D);
     std::vector<double> h_conv((size_t)n_pairs), h_norm((size_t)D);
     auto row_norms = [&](const double* M) -> bool {  // row norms to the host (blocking)
