@@ -11,11 +11,10 @@
 //                the eigenvalues, so no rotation matrix is kept.  (Starting from the rows of C itself, as a first form did,
 //                works on C^2: 15 to 32 sweeps instead of about 10, since the off-diagonal part has twice the dynamic range
 //                to lose.)
-//                A step takes D / 32 disjoint pairs of 16-row blocks: one launch forms the pairs' 32 x 32 Gram
-//                matrices, a second one rotates them to orthogonality in LDS and applies the accumulated rotations to
-//                the rows with the fp64 matrix instructions; D / 16 - 1 steps (round-robin over the blocks) rotate every
-//                pair of rows once: one sweep.  One launch per row-pair step (D - 1 of them a sweep, each streaming the
-//                whole matrix) was bound by its launches up to D = 1024 and by the stream above.
+//                A sweep rotates every pair of rows once: a first step inside 32-row blocks, then D / 32 - 1 steps of
+//                disjoint pairs of such blocks (round-robin).  A step is two launches: one forms the pairs' 64 x 64 Gram
+//                matrices, a second one rotates them to orthogonality in LDS and applies the accumulated rotations to the
+//                rows with the fp64 matrix instructions.
 //                fp64 throughout.
 #pragma once
 #include "common.hpp"
@@ -407,62 +406,112 @@ __global__ __launch_bounds__(256) void calib_chol_finish_kernel(double* __restri
         G[(size_t)i * D + j] = j < k0 ? 0.0 : diag[(size_t)i * kCalPanel + j - k0];
 }
 
-// ---- Jacobi step over pairs of row blocks ----------------------------------------------------------------------------
-constexpr int kJacB = 16;               // rows per block
-constexpr int kJacRec = 3 * kJacB * kJacB;  // a pair's Gram matrix: blocks (P,P), (P,Q), (Q,Q)
+// ---- Jacobi steps ------------------------------------------------------------------------------------------------------
+// A sweep rotates every pair of rows once.  Its first step (calib_jacobi_inside) takes the pairs inside 32-row blocks, the
+// others (calib_jacobi_rotate) disjoint pairs (P, Q) of such blocks, every row of P with every row of Q.  What a step costs
+// beside its rotations (two launches, the matrix read twice and written once across the dies' caches, the sums of the partial
+// Gram matrices) is the same for any block height: with 16-row blocks, 63 steps a sweep at D = 1024, it took 13 of the 18.7 us
+// of a step, and at D = 4096 the step was bound by the stream of the matrix.
+constexpr int kJacB = 16;                   // rows of a small block: 16 pairs of rows are rotated side by side
+constexpr int kJacBig = 2 * kJacB;          // rows of a block of the schedule
+constexpr int kJacTile = kJacB * kJacB;
+constexpr int kJacRec = 3 * kJacTile;       // Gram matrix of a 32-row block: small blocks (0,0), (0,1), (1,1)
+// Gram matrix of a pair (P, Q) of blocks, small blocks P0 P1 Q0 Q1 = 0 1 2 3: tiles (0,0) (0,1) (1,1) (0,2) (1,2), (2,2) (2,3)
+// (3,3) (0,3) (1,3)
+constexpr int kJacTiles = 10, kJacBigRec = kJacTiles * kJacTile;
+constexpr int kTile00 = 0, kTile01 = 1, kTile11 = 2, kTile02 = 3, kTile12 = 4, kTile22 = 5, kTile23 = 6, kTile33 = 7, kTile03 = 8;
 
-// Partial Gram matrices of the step's block pairs over one slice of the columns: part[slice][pair][3][16][16].
-// grid (slices, pairs); four waves, each taking every fourth group of 16 columns (a lane reads four consecutive columns
-// of its row, which serve as four contraction steps of the fp64 MFMA for either operand).
-__global__ __launch_bounds__(256) void calib_jacobi_gram_kernel(const double* __restrict__ G, int D, int step, int slice_cols,
-                                                                double* __restrict__ part)
+// first row of small block `sub` (0 .. 3: P0 P1 Q0 Q1) of the blocks p, q
+__device__ __forceinline__ int jac_row(int p, int q, int sub) { return (sub < 2 ? p : q) * kJacBig + (sub & 1) * kJacB; }
+
+// The waves' partial sums of NT 16 x 16 tiles, added in wave order and left by the first wave.
+template <int NT>
+__device__ __forceinline__ void jac_gram_store(const f64x4 (&acc)[NT], double (&red)[3][NT * kJacTile], double* __restrict__ out)
 {
-    __shared__ double red[3][kJacRec];
-    int p, q;
-    calib_pair(D / kJacB, step, blockIdx.y, &p, &q);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, kg = lane >> 4;
-    const double* gp = G + (size_t)(p * kJacB + l16) * D + blockIdx.x * slice_cols + kg * 4;
-    const double* gq = G + (size_t)(q * kJacB + l16) * D + blockIdx.x * slice_cols + kg * 4;
-    f64x4 acc[3];
-#pragma unroll
-    for (int t = 0; t < 3; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-    for (int c = wave * 16; c < slice_cols; c += 128) {  // two groups requested together, the second from a clamped column
-        f64x4 a[2], b[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            a[u] = *reinterpret_cast<const f64x4*>(gp + min(c + 64 * u, slice_cols - 16));
-            b[u] = *reinterpret_cast<const f64x4*>(gq + min(c + 64 * u, slice_cols - 16));
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if (c + 64 * u < slice_cols) {  // uniform
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    acc[0] = mma_f64(a[u][e], a[u][e], acc[0]);
-                    acc[1] = mma_f64(a[u][e], b[u][e], acc[1]);
-                    acc[2] = mma_f64(b[u][e], b[u][e], acc[2]);
-                }
-            }
-        }
-    }
-    // the waves' sums, added in wave order
+    const int lane = lane_id(), wave = threadIdx.x >> 6, l16 = lane & 15, kg = lane >> 4;
     if (wave > 0) {
 #pragma unroll
-        for (int t = 0; t < 3; ++t)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) red[wave - 1][t * 256 + (kg + 4 * e) * 16 + l16] = acc[t][e];
+            for (int e = 0; e < 4; ++e) red[wave - 1][t * kJacTile + (kg + 4 * e) * 16 + l16] = acc[t][e];
     }
     __syncthreads();
     if (wave == 0) {
-        double* out = part + ((size_t)blockIdx.x * gridDim.y + blockIdx.y) * kJacRec;
 #pragma unroll
-        for (int t = 0; t < 3; ++t)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int at = t * 256 + (kg + 4 * e) * 16 + l16;
+                const int at = t * kJacTile + (kg + 4 * e) * 16 + l16;
                 out[at] = acc[t][e] + red[0][at] + red[1][at] + red[2][at];
             }
     }
+}
+
+// Partial Gram matrices of the 32-row blocks over one slice of the columns: part[slice][block][3][16][16].
+// grid (blocks, slices); four waves, each taking every fourth group of 16 columns (a lane reads four consecutive columns
+// of its row, which serve as four contraction steps of the fp64 MFMA for either operand).
+__global__ __launch_bounds__(256) void calib_jacobi_inside_gram_kernel(const double* __restrict__ G, int D, int slice_cols,
+                                                                       double* __restrict__ part)
+{
+    __shared__ double red[3][kJacRec];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kg = lane >> 4;
+    const double* gp = G + (size_t)(blockIdx.x * kJacBig + l16) * D + blockIdx.y * slice_cols + kg * 4;
+    const double* gq = gp + (size_t)kJacB * D;
+    f64x4 acc[3];
+#pragma unroll
+    for (int t = 0; t < 3; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int c = wave * 16; c < slice_cols; c += 64) {
+        const f64x4 a = *reinterpret_cast<const f64x4*>(gp + c), b = *reinterpret_cast<const f64x4*>(gq + c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            acc[0] = mma_f64(a[e], a[e], acc[0]);
+            acc[1] = mma_f64(a[e], b[e], acc[1]);
+            acc[2] = mma_f64(b[e], b[e], acc[2]);
+        }
+    }
+    jac_gram_store(acc, red, part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kJacRec);
+}
+
+// The same for the step's pairs of blocks: part[slice][pair][10][16][16], five tiles per workgroup (grid (pairs, slices, 2)).
+// The pair index runs fastest in both launches of a step, so a pair's sums are written and read on one die.
+__global__ __launch_bounds__(256) void calib_jacobi_gram_kernel(const double* __restrict__ G, int D, int step, int slice_cols,
+                                                                double* __restrict__ part)
+{
+    constexpr int NT = kJacTiles / 2;
+    __shared__ double red[3][NT * kJacTile];
+    int p, q;
+    calib_pair(D / kJacBig, step, blockIdx.x, &p, &q);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kg = lane >> 4;
+    const bool half = blockIdx.z != 0;  // uniform
+    const double* g[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) g[u] = G + (size_t)(jac_row(p, q, u) + l16) * D + blockIdx.y * slice_cols + kg * 4;
+    f64x4 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int c = wave * 16; c < slice_cols; c += 128) {  // two groups requested together, the second from a clamped column
+        f64x4 x[2][4];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x[u][k] = *reinterpret_cast<const f64x4*>(g[k] + min(c + 64 * u, slice_cols - 16));
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (c + 64 * u >= slice_cols) break;  // uniform
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const double p0 = x[u][0][e], p1 = x[u][1][e], q0 = x[u][2][e], q1 = x[u][3][e];
+                // tiles (0,0) (0,1) (1,1) (0,2) (1,2), or (2,2) (2,3) (3,3) (0,3) (1,3)
+                const double a = half ? q0 : p0, b = half ? q1 : p1, last = half ? q1 : q0;
+                acc[0] = mma_f64(a, a, acc[0]);
+                acc[1] = mma_f64(a, b, acc[1]);
+                acc[2] = mma_f64(b, b, acc[2]);
+                acc[3] = mma_f64(p0, last, acc[3]);
+                acc[4] = mma_f64(p1, last, acc[4]);
+            }
+        }
+    }
+    jac_gram_store(acc, red, part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kJacBigRec + (half ? NT * kJacTile : 0));
 }
 
 // 1 / sqrt(x) for normal x: the hardware's estimate and one third-order step (full precision)
@@ -477,14 +526,17 @@ __device__ __forceinline__ double jac_rsqrt(double x)
 // alone.  (No row is too small to count: beside a large one, a row of squared norm w left as it is moves the large one's
 // eigenvector by up to w over its eigenvalue.)
 __device__ __forceinline__ bool jac_open(double aa, double bb, double ab) { return ab * ab > 1e-30 * (aa * bb); }
-__device__ __forceinline__ bool jac_rotation(double aa, double bb, double ab, double* c, double* s)
+__device__ __forceinline__ void jac_rotation(double aa, double bb, double ab, double* c, double* s, double* tan)
 {
     const bool ok = jac_open(aa, bb, ab);
-    const double d = bb - aa, hi = jac_rsqrt(fma(d, d, 4.0 * ab * ab));
+    // (the smallest normal number keeps two zero rows finite)
+    const double d = bb - aa, hi = jac_rsqrt(fma(4.0 * ab, ab, fma(d, d, 2.2250738585072014e-308)));
     const double c2 = fma(0.5 * fabs(d), hi, 0.5), ci = jac_rsqrt(c2);
+    uint2 ab_d = __builtin_bit_cast(uint2, ab);     // ab with its sign turned by d's
+    ab_d.y ^= __builtin_bit_cast(uint2, d).y & 0x80000000u;
     *c = ok ? c2 * ci : 1.0;
-    *s = ok ? (d >= 0.0 ? ab : -ab) * hi * ci : 0.0;
-    return ok;
+    *s = ok ? __builtin_bit_cast(double, ab_d) * hi * ci : 0.0;
+    *tan = *s * ci;
 }
 // (non-negative doubles are ordered like their bits; nothing waits for the result)
 __device__ __forceinline__ void conv_max(double* at, double v)
@@ -492,189 +544,407 @@ __device__ __forceinline__ void conv_max(double* at, double v)
     atomicMax(reinterpret_cast<unsigned long long*>(at), (unsigned long long)__double_as_longlong(v));
 }
 
-// Rotates the rows of the step's block pairs.  Workgroup (slice, pair) adds up the pair's partial Gram matrices, runs the
-// rotations on the 32 x 32 Gram matrix (16 rounds of 16 disjoint pairs: every row of P with every row of Q; in the
-// sweep's first step 15 rounds more, the pairs inside the blocks) while accumulating them into a 32 x 32 matrix, and
-// applies that to its slice of the columns on the matrix cores.  Every slice repeats the small problem (the same
-// numbers): a launch between the two would cost more than its 16 dependent rounds.  In a round thread (i, j) rotates the
-// 2 x 2 block of row pair i and column pair j; what the next round's threads need passes through one of two LDS buffers
-// (one barrier per round), what belongs to a row of P stays with its thread.  A round is a chain of LDS reads, two
-// reciprocal square roots and LDS writes, bound by instruction issue of the one wave per SIMD.
-// (The rounds in fp32, with the accumulated matrix re-orthogonalised in fp64, were no faster: 0.5 against 0.6 us a round.)
-// conv[pair] keeps the largest |sin| of a rotation, since the host cleared it, that involved a row of squared norm >=
-// lead (the rows that can still change a leading eigenvector).
-__global__ __launch_bounds__(256) void calib_jacobi_rotate_kernel(double* __restrict__ G, int D, int step, int slice_cols,
-                                                                  const double* __restrict__ part, int n_part, double lead,
-                                                                  double* __restrict__ conv)
+// value of the next lane of a row of 16 lanes (the last lane gets the first one's)
+__device__ __forceinline__ double row16_next(double v)
 {
-    constexpr int B2 = 2 * kJacB, LD = B2 + 1, LB = kJacB + 1;
-    __shared__ double Wb[2][B2 * LD], Qb[2][B2 * LD];   // Gram matrix and accumulated rotations
-    __shared__ double s_diag[B2], s_conv[kJacB];
-    __shared__ int s_any[2];
-    int p, q;
-    calib_pair(D / kJacB, step, blockIdx.y, &p, &q);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, kg = lane >> 4;
+    const int2 u = __builtin_bit_cast(int2, v);
+    int2 w;
+    w.x = __builtin_amdgcn_update_dpp(u.x, u.x, 0x12f, 0xf, 0xf, false);  // row_ror:15
+    w.y = __builtin_amdgcn_update_dpp(u.y, u.y, 0x12f, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, w);
+}
 
-    // partial Gram matrices (at most 8) and the first two column tiles of this wave, all requested together
-    double w8[3][8];
-#pragma unroll
-    for (int t = 0; t < 3; ++t)
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            w8[t][u] = part[((size_t)min(u, n_part - 1) * gridDim.y + blockIdx.y) * kJacRec + t * 256 + tid];
-    double* const gp = G + (size_t)(p * kJacB + kg) * D + blockIdx.x * slice_cols + l16;
-    double* const gq = G + (size_t)(q * kJacB + kg) * D + blockIdx.x * slice_cols + l16;
-    double x[2][8];  // tile u, contraction step s: row 4 s + kg of (P, Q)
-    auto load_tiles = [&](int c0) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int c = min(c0 + 64 * u, slice_cols - 16);
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                x[u][s] = gp[(size_t)(4 * s) * D + c];
-                x[u][4 + s] = gq[(size_t)(4 * s) * D + c];
-            }
-        }
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+constexpr int kJacLd = 2 * kJacB + 1;   // row pitch of a 32 x 32 matrix in LDS
+constexpr int kJacLt = kJacB + 1;       // of a 16 x 16 tile
+
+// The rotations of two small blocks A, B of rows: every row of A with every row of B, 16 rounds of 16 disjoint pairs on the
+// blocks' Gram matrix, by two waves (jac_solve) while two more accumulate the rotations (jac_accumulate).
+//
+// Round t pairs row i of A with row i + t of B (mod 16).  Thread (i, m), m = 1 .. 8, keeps the 2 x 2 block of row pair i and
+// column pair j = i + m in registers; the blocks of the other m are these transposed, and those of m = 0 are the pairs' own: the
+// squared norms aa, bb and the inner product, zero after the rotation.  i is the lane of a row of 16 lanes, so the threads
+// (i, 1), whose blocks hold the inner product of the pair that comes next, share one wave: it computes the next round's
+// rotations right after its blocks' update.  Going to the next round, (B_i, B_j) moves by one lane (a lane rotation), (A_i, B_j)
+// and (B_i, A_j) pass through LDS.  A round is one LDS round trip, a 2 x 2 block update, one rotation and one barrier: 0.27 us with
+// two groups on a compute unit.  With all 256 blocks, and every wave computing rotations, it took 0.31 us for one group and 0.47
+// for two (instruction issue); with every thread computing both rotations of its block from the whole matrix in LDS 0.6 for one.
+struct JacRounds {
+    f64x2 cs[kJacB + 1][kJacB];          // [round][pair]: cosine and sine
+    f64x2 unused[3 * kJacB];             // (where the other lanes of the wave that computes rotations write)
+    double cross[2][2][8][kJacB];        // [round parity][(A_i, B_j) | (B_i, A_j)][m - 1][i]
+    double zero[2][2][8][kJacB];         // (first row: the product that a round's rotation made zero)
+};
+struct JacPlace { int i, j, m; bool rotates; };
+__device__ __forceinline__ JacPlace jac_place(int w)  // w: the wave's number in its group
+{
+    JacPlace t;
+    t.i = lane_id() & 15; t.m = 1 + w * 4 + (lane_id() >> 4); t.j = (t.i + t.m) & 15; t.rotates = w == 0;
+    return t;
+}
+// In: thread (i, m)'s elements (A_i, A_j), (A_i, B_j), (B_i, A_j), (B_i, B_j) and pair i's squared norms aa, bb and inner product
+// ab.  Out: b00, b11 and, in the threads (i, 1), aa and bb after the rounds (of row i of either block).  17 barriers.
+__device__ __forceinline__ void jac_solve(JacRounds& L, const JacPlace& at, double& b00, double b01, double b10, double& b11, double& aa,
+                                          double& bb, double ab)
+{
+    const int i = at.i, j = at.j, i1 = (i + 1) & 15, half = lane_id() >> 4;
+    // where a round finds (A_i, B_j): thread (i, m + 1)'s, and for m = 8 thread (i + 9, 7)'s (B_i, A_j); and (B_i, A_j): thread
+    // (i + 1, m - 1)'s (of m = 1 it is zero)
+    double* const from01 = at.m < 8 ? &L.cross[0][0][at.m][i] : &L.cross[0][1][6][(i + 9) & 15];
+    double* const from10 = at.m > 1 ? &L.cross[0][1][at.m - 2][i1] : &L.zero[0][0][0][i];
+    double* const to = &L.cross[0][0][at.m - 1][i];
+    constexpr int kParity = 2 * 8 * kJacB;
+    const f64x2 *Ri = &L.cs[0][i], *Rj = &L.cs[0][j];
+    f64x2* out = half == 0 ? &L.cs[0][i] : &L.unused[(half - 1) * kJacB + i];
+    const int step = half == 0 ? kJacB : 0;
+    auto rotation = [&](double abt) {
+        double c, s, tan;
+        jac_rotation(aa, bb, abt, &c, &s, &tan);
+        *out = f64x2{c, s};
+        out += step;
+        aa = fma(-tan, abt, aa);
+        bb = row16_next(fma(tan, abt, bb));   // (the next round's B row)
     };
-    load_tiles(wave * 16);
-    const int i = tid >> 4, j = tid & 15;
-    if (tid < 2) s_any[tid] = 0;
-    double v[3];
-#pragma unroll
-    for (int t = 0; t < 3; ++t) {
-        v[t] = 0.0;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[t] += u < n_part ? w8[t][u] : 0.0;
-        const int r = i + (t == 2 ? kJacB : 0), c = j + (t >= 1 ? kJacB : 0);
-        Wb[0][r * LD + c] = v[t];
-        if (t == 1) Wb[0][c * LD + r] = v[t];
-        if (r == c) s_diag[r] = v[t];
-    }
-    for (int e = tid; e < B2 * B2; e += 256) Qb[0][(e >> 5) * LD + (e & 31)] = (e >> 5) == (e & 31) ? 1.0 : 0.0;
+    auto round = [&](auto parity, bool last) {
+        constexpr int odd = decltype(parity)::value * kParity;
+        const double c = Ri->x, s = Ri->y, cj = Rj->x, sj = Rj->y;
+        Ri += kJacB; Rj += kJacB;
+        b01 = from01[odd];
+        b10 = from10[odd];
+        const double r00 = c * b00 - s * b10, r01 = c * b01 - s * b11, r10 = s * b00 + c * b10, r11 = s * b01 + c * b11;
+        const double n01 = sj * r00 + cj * r01;
+        to[kParity - odd] = n01;
+        to[kParity - odd + 8 * kJacB] = cj * r10 - sj * r11;
+        if (at.rotates && !last) rotation(n01);  // uniform
+        b00 = cj * r00 - sj * r01;
+        b11 = row16_next(sj * r10 + cj * r11);
+        __syncthreads();
+    };
+    // (the first round reads what its threads hold from where a round's threads read)
+    *from01 = b01;
+    if (at.m > 1) *from10 = b10;
+    else from10[0] = b10, from10[kParity] = 0.0;
+    if (at.rotates) rotation(ab);  // uniform
+    __builtin_amdgcn_s_setprio(2);  // (the accumulating waves fill the gaps)
     __syncthreads();
-    // nothing to rotate (most pairs of the last sweeps): the rounds would leave everything as it is
-#pragma unroll
-    for (int t = 0; t < 3; ++t) {
-        const int r = i + (t == 2 ? kJacB : 0), c = j + (t >= 1 ? kJacB : 0);
-        if (r != c && (t == 1 || step == 0) && jac_open(s_diag[r], s_diag[c], v[t])) s_any[0] = 1;
+#pragma unroll 1
+    for (int t = 0; t < kJacB; t += 2) {  // (not unrolled further: every launch starts with cold instruction caches)
+        round(std::integral_constant<int, 0>{}, false);
+        if (t == 0 && at.m == 1) from10[0] = 0.0;
+        round(std::integral_constant<int, 1>{}, t + 2 == kJacB);
     }
-    __syncthreads();
-    if (!s_any[0]) return;  // uniform, and the same in every slice of the pair
-
+    __builtin_amdgcn_s_setprio(0);
+}
+// The largest |sin| of the 256 rotations among those that involved a row of squared norm >= lead (the rows that can still
+// change a leading eigenvector), by the norms the rows of A and B have now (diagonals of pitch `ld`); one wave, every lane
+// gets it.
+__device__ __forceinline__ double jac_largest(const JacRounds& L, const double* A, const double* B, int ld, double lead)
+{
+    const int l16 = lane_id() & 15, kg = lane_id() >> 4;
     double smax = 0.0;
-    bool any = false;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int t = k * 4 + kg;
+        smax = fmax(A[l16 * (ld + 1)], B[((l16 + t) & 15) * (ld + 1)]) >= lead ? fmax(smax, fabs(L.cs[t][l16].y)) : smax;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) smax = fmax(smax, __shfl_xor(smax, o, kWave));
+    return smax;
+}
+// lane l: rows l % 16 of A and B of the accumulated matrix, kJacNc columns; 17 barriers.  (Sixteen moves: every row of B ends
+// in its place.)
+constexpr int kJacNc = 2 * kJacB / 8;   // columns per lane
+__device__ __forceinline__ void jac_accumulate(const JacRounds& L, double (&x)[kJacNc], double (&y)[kJacNc])
+{
+    const int l16 = lane_id() & 15;
+    __syncthreads();
+#pragma unroll 1
+    for (int t = 0; t < kJacB; ++t) {
+        const f64x2 R = L.cs[t][l16];
+#pragma unroll
+        for (int e = 0; e < kJacNc; ++e) {
+            const double xe = x[e], ye = y[e];
+            x[e] = R.x * xe - R.y * ye;
+            y[e] = row16_next(R.y * xe + R.x * ye);
+        }
+        __syncthreads();
+    }
+}
+
+// First step of a sweep: the pairs of rows inside every 32-row block, 15 rounds inside its two small blocks (side by side, on
+// whole matrices in LDS) and the 16 rounds between them; workgroup (block, slice) applies the accumulated rotations to its
+// slice of the columns on the matrix cores.  Every slice repeats the small problem (the same numbers).
+// conv[block] keeps the largest |sin| of a rotation since the host cleared it (see jac_largest).
+constexpr int kJacInsideThreads = 4 * kWave;
+__global__ __launch_bounds__(kJacInsideThreads) void calib_jacobi_inside_kernel(double* __restrict__ G, int D, int slice_cols,
+                                                                                const double* __restrict__ part, int n_part,
+                                                                                double lead, double* __restrict__ conv)
+{
+    constexpr int B2 = 2 * kJacB, LD = kJacLd;
+    __shared__ double Wb[2][B2 * LD], Qb[2][B2 * LD];   // Gram matrix and accumulated rotations
+    __shared__ JacRounds s_rounds;
+    __shared__ double s_conv[kJacB];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, kg = lane >> 4;
+    double* const gp = G + (size_t)(blockIdx.x * kJacBig + kg) * D + blockIdx.y * slice_cols + l16;
+    const int i = tid >> 4, j = tid & 15;
+    {
+        double w8[3][8];
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                w8[t][u] = part[((size_t)min(u, n_part - 1) * gridDim.x + blockIdx.x) * kJacRec + t * kJacTile + tid];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            double v = 0.0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v += u < n_part ? w8[t][u] : 0.0;
+            const int r = i + (t == 2 ? kJacB : 0), c = j + (t >= 1 ? kJacB : 0);
+            Wb[0][r * LD + c] = v;
+            if (t == 1) Wb[0][c * LD + r] = v;
+        }
+        for (int e = tid; e < B2 * B2; e += 256) Qb[0][(e >> 5) * LD + (e & 31)] = (e >> 5) == (e & 31) ? 1.0 : 0.0;
+    }
+    __syncthreads();
     int cur = 0;
-    if (step == 0) {  // the pairs inside the blocks, on whole matrices
-        auto inside = [&](int t, int k, int* a, int* b) {  // pair k of round t: k < 8 inside P, otherwise inside Q
+    {
+        auto inside = [&](int t, int k, int* a, int* b) {  // pair k of round t: k < 8 inside the first small block, otherwise the second
             calib_pair(kJacB, t, k & 7, a, b);
             *a += k < 8 ? 0 : kJacB; *b += k < 8 ? 0 : kJacB;
         };
+        double smax = 0.0;
+#pragma unroll 1
         for (int t = 0; t < kJacB - 1; ++t) {
-            int pi, qi, pj, qj;
-            inside(t, i, &pi, &qi);
-            inside(t, j, &pj, &qj);
-            const double* W = Wb[cur]; const double* Q = Qb[cur];
-            double* Wn = Wb[cur ^ 1]; double* Qn = Qb[cur ^ 1];
-            const double aa = W[pi * LD + pi], bb = W[qi * LD + qi];
-            const double b00 = W[pi * LD + pj], b01 = W[pi * LD + qj], b10 = W[qi * LD + pj], b11 = W[qi * LD + qj];
-            const double x0 = Q[pi * LD + j], y0 = Q[qi * LD + j], x1 = Q[pi * LD + j + kJacB], y1 = Q[qi * LD + j + kJacB];
-            double c, s, cj, sj;
-            const bool ok = jac_rotation(aa, bb, W[pi * LD + qi], &c, &s);
-            jac_rotation(W[pj * LD + pj], W[qj * LD + qj], W[pj * LD + qj], &cj, &sj);
-            any |= ok;
-            smax = fmax(aa, bb) >= lead ? fmax(smax, fabs(s)) : smax;
-            const double r00 = c * b00 - s * b10, r01 = c * b01 - s * b11, r10 = s * b00 + c * b10, r11 = s * b01 + c * b11;
-            Wn[pi * LD + pj] = cj * r00 - sj * r01;
-            Wn[pi * LD + qj] = sj * r00 + cj * r01;
-            Wn[qi * LD + pj] = cj * r10 - sj * r11;
-            Wn[qi * LD + qj] = sj * r10 + cj * r11;
-            Qn[pi * LD + j] = c * x0 - s * y0; Qn[qi * LD + j] = s * x0 + c * y0;
-            Qn[pi * LD + j + kJacB] = c * x1 - s * y1; Qn[qi * LD + j + kJacB] = s * x1 + c * y1;
+            {
+                int pi, qi, pj, qj;
+                inside(t, i, &pi, &qi);
+                inside(t, j, &pj, &qj);
+                const double* W = Wb[cur]; const double* Q = Qb[cur];
+                double* Wn = Wb[cur ^ 1]; double* Qn = Qb[cur ^ 1];
+                const double aa = W[pi * LD + pi], bb = W[qi * LD + qi];
+                const double b00 = W[pi * LD + pj], b01 = W[pi * LD + qj], b10 = W[qi * LD + pj], b11 = W[qi * LD + qj];
+                const double x0 = Q[pi * LD + j], y0 = Q[qi * LD + j], x1 = Q[pi * LD + j + kJacB], y1 = Q[qi * LD + j + kJacB];
+                double c, s, cj, sj, tan;
+                jac_rotation(aa, bb, W[pi * LD + qi], &c, &s, &tan);
+                jac_rotation(W[pj * LD + pj], W[qj * LD + qj], W[pj * LD + qj], &cj, &sj, &tan);
+                smax = fmax(aa, bb) >= lead ? fmax(smax, fabs(s)) : smax;
+                const double r00 = c * b00 - s * b10, r01 = c * b01 - s * b11, r10 = s * b00 + c * b10, r11 = s * b01 + c * b11;
+                Wn[pi * LD + pj] = cj * r00 - sj * r01;
+                Wn[pi * LD + qj] = sj * r00 + cj * r01;
+                Wn[qi * LD + pj] = cj * r10 - sj * r11;
+                Wn[qi * LD + qj] = sj * r10 + cj * r11;
+                Qn[pi * LD + j] = c * x0 - s * y0; Qn[qi * LD + j] = s * x0 + c * y0;
+                Qn[pi * LD + j + kJacB] = c * x1 - s * y1; Qn[qi * LD + j + kJacB] = s * x1 + c * y1;
+            }
             __syncthreads();
             cur ^= 1;
         }
+        if (j == 0) s_conv[i] = smax;
     }
-    // every row of P with every row of Q: round t pairs row i of P with row (i + t) mod 16 of Q
-    const double* Qd;
-    {
-        double b00 = Wb[cur][i * LD + j];
-        double x0 = Qb[cur][i * LD + j], x1 = Qb[cur][i * LD + j + kJacB];
-        const double b01 = Wb[cur][i * LD + kJacB + j], b11 = Wb[cur][(kJacB + i) * LD + kJacB + j];
-        const double y0 = Qb[cur][(kJacB + i) * LD + j], y1 = Qb[cur][(kJacB + i) * LD + j + kJacB];
-        // the two buffers: (P,Q) block [16][17], (Q,Q) block [16][17], diagonal of P [16], accumulated rows of Q [16][33]
-        constexpr int kPQ = 0, kQQ = kJacB * LB, kDP = 2 * kJacB * LB, kAcc = kDP + kJacB, kBuf = kAcc + kJacB * LD;
-        __shared__ double buf0[2 * kBuf];
-        buf0[kPQ + i * LB + j] = b01;
-        buf0[kQQ + i * LB + j] = b11;
-        if (i == j) buf0[kDP + i] = b00;
-        buf0[kAcc + i * LD + j] = y0; buf0[kAcc + i * LD + j + kJacB] = y1;
-        __syncthreads();
-#pragma unroll 2
-        for (int t = 0; t < kJacB; ++t) {
-            const double* R = buf0 + (t & 1) * kBuf;
-            double* N = buf0 + ((t & 1) ^ 1) * kBuf;
-            const int qi = (i + t) & 15, qj = (j + t) & 15;
-            const double aa = R[kDP + i], bb = R[kQQ + qi * (LB + 1)], ab = R[kPQ + i * LB + qi];
-            const double aj = R[kDP + j], bj = R[kQQ + qj * (LB + 1)], abj = R[kPQ + j * LB + qj];
-            const double w01 = R[kPQ + i * LB + qj], w10 = R[kPQ + j * LB + qi], w11 = R[kQQ + qi * LB + qj];
-            const double v0 = R[kAcc + qi * LD + j], v1 = R[kAcc + qi * LD + j + kJacB];
-            double c, s, cj, sj;
-            any |= jac_rotation(aa, bb, ab, &c, &s);
-            jac_rotation(aj, bj, abj, &cj, &sj);
-            smax = fmax(aa, bb) >= lead ? fmax(smax, fabs(s)) : smax;
-            const double r00 = c * b00 - s * w10, r01 = c * w01 - s * w11, r10 = s * b00 + c * w10, r11 = s * w01 + c * w11;
-            b00 = cj * r00 - sj * r01;
-            N[kPQ + i * LB + qj] = sj * r00 + cj * r01;
-            N[kQQ + qi * LB + qj] = sj * r10 + cj * r11;
-            if (i == j) N[kDP + i] = b00;
-            N[kAcc + qi * LD + j] = s * x0 + c * v0; N[kAcc + qi * LD + j + kJacB] = s * x1 + c * v1;
-            x0 = c * x0 - s * v0; x1 = c * x1 - s * v1;
-            __syncthreads();
-        }
-        // the accumulated rotations as one 32 x 32 matrix
-        double* const Qo = &Qb[0][0];
-        const double* R = buf0;  // (an even number of rounds)
-        static_assert(kJacB % 2 == 0, "the last round wrote the first buffer");
-        Qo[i * LD + j] = x0; Qo[i * LD + j + kJacB] = x1;
-        Qo[(kJacB + i) * LD + j] = R[kAcc + i * LD + j]; Qo[(kJacB + i) * LD + j + kJacB] = R[kAcc + i * LD + j + kJacB];
-        Qd = Qo;
+    double* const Qo = Qb[cur];
+    if (wave < 2) {
+        const double* W = Wb[cur];
+        const JacPlace at = jac_place(wave);
+        double b00 = W[at.i * LD + at.j], b11 = W[(kJacB + at.i) * LD + kJacB + at.j];
+        double aa = W[at.i * (LD + 1)], bb = W[(kJacB + at.i) * (LD + 1)];
+        jac_solve(s_rounds, at, b00, W[at.i * LD + kJacB + at.j], W[at.j * LD + kJacB + at.i], b11, aa, bb,
+                  W[at.i * LD + kJacB + at.i]);
+        if (at.m == 1) { Wb[cur ^ 1][at.i * (LD + 1)] = aa; Wb[cur ^ 1][(kJacB + at.i) * (LD + 1)] = bb; }
+    } else {
+        double x[kJacNc], y[kJacNc];
+        const int c0 = ((wave & 1) * 4 + kg) * kJacNc;
+#pragma unroll
+        for (int e = 0; e < kJacNc; ++e) { x[e] = Qo[l16 * LD + c0 + e]; y[e] = Qo[(kJacB + l16) * LD + c0 + e]; }
+        jac_accumulate(s_rounds, x, y);
+#pragma unroll
+        for (int e = 0; e < kJacNc; ++e) { Qo[l16 * LD + c0 + e] = x[e]; Qo[(kJacB + l16) * LD + c0 + e] = y[e]; }
     }
-    if (j == 0) s_conv[i] = smax;
-    if (any) s_any[1] = 1;
     __syncthreads();
-    if (!s_any[1]) return;  // uniform
-    if (tid == 0 && blockIdx.x == 0) {
-        double m = 0.0;
-        for (int k = 0; k < kJacB; ++k) m = fmax(m, s_conv[k]);
-        conv_max(conv + blockIdx.y, m);
+    if (blockIdx.y == 0 && wave == 3) {
+        const double* W = Wb[cur ^ 1];
+        double smax = jac_largest(s_rounds, W, W + kJacB * (LD + 1), LD, lead);
+#pragma unroll
+        for (int k = 0; k < kJacB; ++k) smax = fmax(smax, s_conv[k]);
+        if (lane == 0 && smax > 0.0) conv_max(conv + blockIdx.x, smax);
     }
     double qa[2][8];  // the accumulated rotations as MFMA operand: rows m 16 .. +16, contraction step s
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int s = 0; s < 8; ++s) qa[m][s] = Qd[(m * 16 + l16) * LD + 4 * s + kg];
-    for (int c0 = wave * 16; c0 < slice_cols; c0 += 128) {
-        if (c0 != wave * 16) load_tiles(c0);
-        f64x4 acc[2][2];
+        for (int s = 0; s < 8; ++s) qa[m][s] = Qo[(m * 16 + l16) * LD + 4 * s + kg];
+    for (int c = wave * 16; c < slice_cols; c += 64) {
+        double x[8];  // contraction step s: row 4 s + kg of the block
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int s = 0; s < 8; ++s) x[s] = gp[(size_t)(4 * s) * D + c];
 #pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                acc[u][m] = f64x4{0.0, 0.0, 0.0, 0.0};
+        for (int m = 0; m < 2; ++m) {
+            f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                for (int s = 0; s < 8; ++s) acc[u][m] = mma_f64(qa[m][s], x[u][s], acc[u][m]);
-            }
+            for (int s = 0; s < 8; ++s) acc = mma_f64(qa[m][s], x[s], acc);
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int c = c0 + 64 * u;
-            if (c < slice_cols) {  // uniform
+            for (int e = 0; e < 4; ++e) gp[(size_t)(m * 16 + 4 * e) * D + c] = acc[e];
+        }
+    }
+}
+
+// Rotates the rows of the step's pairs of blocks.  Workgroup (pair, slice) adds up the pair's partial Gram matrices (64 x 64)
+// and rotates P0 with Q0 beside P1 with Q1 and then P0 with Q1 beside P1 with Q0 (jac_solve, a group of four waves each); in
+// between it brings the tiles (P0, Q1) and (P1, Q0) up to date with the accumulated rotations, on the matrix cores, as it
+// applies them to its slice of the columns in the end: two products with 32 x 32 matrices, the first one's result being the
+// second one's operand as it lies in the registers.  Every slice repeats the small problem (the same numbers): a launch between
+// the two would cost more than its 32 dependent rounds.
+// At D = 1024 (256 workgroups of 64 columns) the kernel takes 19.9 us behind 5.7 for the Gram matrices: 8.7 for the rounds, 2.3 for
+// the partial sums, 2.4 for the last products, 1.1 between the halves, the rest for the launch and the matrix's way back to memory.
+// A call at D = 1024, r = 640: 15.4 ms with 16-row blocks, 11.6 with these; at D = 4096 239 and 155.
+constexpr int kJacThreads = 8 * kWave;   // waves 0, 1 and 2, 3: the groups' rounds; 4, 5 and 6, 7: their accumulated rotations
+__global__ __launch_bounds__(kJacThreads) void calib_jacobi_rotate_kernel(double* __restrict__ G, int D, int step, int slice_cols,
+                                                                          const double* __restrict__ part, int n_part, double lead,
+                                                                          double* __restrict__ conv)
+{
+    constexpr int LD = kJacLd, LT = kJacLt;
+    __shared__ double S[kJacTiles][kJacB * LT];          // Gram matrix
+    __shared__ double J[2][2][2 * kJacB * LD];           // [half][group] accumulated rotations
+    __shared__ double T[2][kJacB * LD];
+    __shared__ JacRounds s_rounds[2];
+    __shared__ int s_any;
+    int p, q;
+    calib_pair(D / kJacBig, step, blockIdx.x, &p, &q);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, kg = lane >> 4;
+    const bool solver = wave < 4;   // uniform
+    const int grp = (wave >> 1) & 1;
+    const JacPlace at = jac_place(wave & 1);
+    const int i = at.i, j = at.j;
+
+    // partial Gram matrices (at most 8), two elements per load, and this wave's first column tile, all requested together
+    constexpr int NP = kJacBigRec / 2, NV = (NP + kJacThreads - 1) / kJacThreads;
+    f64x2 w8[NV][8];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    gp[(size_t)(4 * e) * D + c] = acc[u][0][e];
-                    gq[(size_t)(4 * e) * D + c] = acc[u][1][e];
-                }
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            w8[v][u] = *reinterpret_cast<const f64x2*>(part + ((size_t)min(u, n_part - 1) * gridDim.x + blockIdx.x) * kJacBigRec +
+                                                       2 * min(tid + v * kJacThreads, NP - 1));
+    double* g[4];   // small block u, row kg
+#pragma unroll
+    for (int u = 0; u < 4; ++u) g[u] = G + (size_t)(jac_row(p, q, u) + kg) * D + blockIdx.y * slice_cols + l16;
+    double x[4][4];  // small block u, contraction step s: row 4 s + kg
+    auto load_tile = [&](int c) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) x[u][s] = g[u][(size_t)(4 * s) * D + c];
+    };
+    if (wave * 16 < slice_cols) load_tile(wave * 16);  // uniform
+    if (tid == 0) s_any = 0;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int e = 2 * (tid + v * kJacThreads), tile = e / kJacTile, pos = e % kJacTile;
+        f64x2 sum = f64x2{0.0, 0.0};
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            sum.x += u < n_part ? w8[v][u].x : 0.0;
+            sum.y += u < n_part ? w8[v][u].y : 0.0;
+        }
+        if (e < kJacBigRec) {
+            S[tile][(pos >> 4) * LT + (pos & 15)] = sum.x;
+            S[tile][(pos >> 4) * LT + (pos & 15) + 1] = sum.y;
+        }
+    }
+    __syncthreads();
+    // tiles of small blocks P_a and Q_b
+    auto tile_pp = [](int a) { return a ? kTile11 : kTile00; };
+    auto tile_qq = [](int b) { return b ? kTile33 : kTile22; };
+    auto tile_pq = [](int a, int b) { return (b ? kTile03 : kTile02) + a; };
+    // nothing to rotate (most pairs of the last sweeps): the rounds would leave everything as it is
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int a = wave >> 2, r = (tid >> 4) & 15, c = l16;
+        if (jac_open(S[tile_pp(a)][r * (LT + 1)], S[tile_qq(b)][c * (LT + 1)], S[tile_pq(a, b)][r * LT + c])) s_any = 1;
+    }
+    __syncthreads();
+    if (!s_any) return;  // uniform, and the same in every slice of the pair
+
+#pragma unroll 1
+    for (int h = 0; h < 2; ++h) {
+        const int b = h ? 1 - grp : grp;  // group's blocks: P_grp and Q_b
+        double* const A = S[tile_pp(grp)]; double* const C = S[tile_qq(b)];
+        const double* const B = S[tile_pq(grp, b)];
+        if (solver) {
+            double b00 = A[i * LT + j], b11 = C[i * LT + j], aa = A[i * (LT + 1)], bb = C[i * (LT + 1)];
+            jac_solve(s_rounds[grp], at, b00, B[i * LT + j], B[j * LT + i], b11, aa, bb, B[i * (LT + 1)]);
+            A[i * LT + j] = A[j * LT + i] = b00;
+            C[i * LT + j] = C[j * LT + i] = b11;
+            if (at.m == 1) { A[i * (LT + 1)] = aa; C[i * (LT + 1)] = bb; }
+        } else {
+            double xr[kJacNc], yr[kJacNc];
+            const int c0 = ((wave & 1) * 4 + kg) * kJacNc;
+#pragma unroll
+            for (int e = 0; e < kJacNc; ++e) { xr[e] = c0 + e == l16 ? 1.0 : 0.0; yr[e] = c0 + e == kJacB + l16 ? 1.0 : 0.0; }
+            jac_accumulate(s_rounds[grp], xr, yr);
+            double* Jo = J[h][grp];
+#pragma unroll
+            for (int e = 0; e < kJacNc; ++e) { Jo[l16 * LD + c0 + e] = xr[e]; Jo[(kJacB + l16) * LD + c0 + e] = yr[e]; }
+        }
+        __syncthreads();
+        if (!solver && (wave & 1) && blockIdx.y == 0) {
+            const double smax = jac_largest(s_rounds[grp], A, C, LT, lead);
+            if (lane == 0 && smax > 0.0) conv_max(conv + blockIdx.x, smax);
+        }
+        if (h == 1) break;
+        // (P0, Q1) and (Q0, P1) after the first half: rows of J1 W J2^T, W = the Gram matrix between (P0, Q0) and (P1, Q1).
+        // First T[m] = rows m of J1 W, a 16 x 16 tile per wave, then T[m] times the other rows of J2.
+        if (wave < 4) {
+            const int m = wave >> 1, n = wave & 1;
+            f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int s = 0; s < 4; ++s)  // rows 4 s + kg of P0 ...
+                acc = mma_f64(J[0][0][(m * 16 + l16) * LD + 4 * s + kg], S[n ? kTile03 : kTile01][(4 * s + kg) * LT + l16], acc);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)  // ... and of Q0 (the tile (P1, Q0) the other way round)
+                acc = mma_f64(J[0][0][(m * 16 + l16) * LD + kJacB + 4 * s + kg],
+                              n ? S[kTile23][(4 * s + kg) * LT + l16] : S[kTile12][l16 * LT + 4 * s + kg], acc);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) T[m][(kg + 4 * e) * LD + n * 16 + l16] = acc[e];
+        }
+        __syncthreads();
+        if (wave < 2) {
+            const int m = wave;
+            f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+                acc = mma_f64(T[m][l16 * LD + 4 * s + kg], J[0][1][((1 - m) * 16 + l16) * LD + 4 * s + kg], acc);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (m == 0) S[kTile03][(kg + 4 * e) * LT + l16] = acc[e];
+                else S[kTile12][l16 * LT + kg + 4 * e] = acc[e];
             }
         }
+        __syncthreads();
+    }
+    // row of small block u of the result: J[h][group] times the group's two small blocks (A, B), half after half
+    for (int c = wave * 16; c < slice_cols; c += 8 * 16) {
+        if (c != wave * 16) load_tile(c);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                const int u = a, v = 2 + (h ? 1 - a : a);  // small blocks
+                asm volatile("" ::: "memory");  // (the operands of all four products at once do not fit into the registers)
+                f64x4 acc[2];
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    acc[m] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                    for (int s = 0; s < 8; ++s)
+                        acc[m] = mma_f64(J[h][a][(m * 16 + l16) * LD + 4 * s + kg], s < 4 ? x[u][s & 3] : x[v][s & 3], acc[m]);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { x[u][e] = acc[0][e]; x[v][e] = acc[1][e]; }
+            }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) g[u][(size_t)(4 * s) * D + c] = x[u][s];
     }
 }
 

@@ -1611,12 +1611,19 @@ sals_status sals_calib_accumulate(int32_t dtype, const void* K, int64_t n_tok, i
 }
 
 namespace {
-// column slices of the two launches of a Jacobi step: as many (at most 8, each a whole number of 64-column groups) as
-// keep the step within about two workgroups per compute unit
+// Column slices of the launches of a Jacobi step: of the Gram matrices (at most 8: the partial matrices are added up by every
+// workgroup of the rotation) and of the rotation, as many as keep either within about two, or one, workgroups per compute unit
+// (multiples of 16 columns, at least 64 of them).
+int jac_gram_slices(int D)
+{
+    int s = 1;
+    while (s < 8 && D % (32 * s) == 0 && D / (2 * s) >= 64 && D / (2 * kJacBig) * 2 * (2 * s) <= 512) s *= 2;
+    return s;
+}
 int jac_slices(int D)
 {
     int s = 1;
-    while (s < 8 && D % (128 * s) == 0 && D / (2 * kJacB) * 2 * s <= 512) s *= 2;
+    while (D % (32 * s) == 0 && D / (2 * s) >= 64 && D / (2 * kJacBig) * (2 * s) <= 256) s *= 2;
     return s;
 }
 struct EigWs {  // byte offsets into the workspace
@@ -1628,11 +1635,12 @@ EigWs eig_ws(int D)
     size_t o = 0;
     auto take = [&](size_t bytes) { const size_t at = o; o = align_up(o + bytes); return at; };
     w.G = take((size_t)D * D * 8);               // the rotated factor
-    w.conv = take((size_t)(D / (2 * kJacB)) * 8);  // convergence slots; before the sweeps, whether a pivot was not positive
+    w.conv = take((size_t)(D / kJacBig) * 8);    // convergence slots; before the sweeps, whether a pivot was not positive
     w.norm = take((size_t)D * 8);                // row norms and signs
     w.sgn = take((size_t)D * 8);
     w.diag = take((size_t)D * kCalPanel * 8);    // factored diagonal blocks
-    w.part = take((size_t)jac_slices(D) * (D / (2 * kJacB)) * kJacRec * 8);  // partial Gram matrices of a step
+    // partial Gram matrices of a step: of the blocks, or of pairs of them
+    w.part = take((size_t)jac_gram_slices(D) * (D / kJacBig) * std::max(kJacRec, kJacBigRec / 2) * 8);
     w.total = o;
     return w;
 }
@@ -1659,8 +1667,9 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     auto at = [&](size_t o) { return reinterpret_cast<double*>(ws + o); };
     double *G = at(off.G), *conv = at(off.conv), *norm = at(off.norm), *sgn = at(off.sgn), *diag = at(off.diag), *part = at(off.part);
     int* fail = reinterpret_cast<int*>(ws + off.conv);
-    const int n_pairs = D / (2 * kJacB), n_steps = D / kJacB - 1, slices = jac_slices(D);
-    std::vector<double> h_conv((size_t)n_pairs), h_norm((size_t)D);
+    const int n_blocks = D / kJacBig, n_pairs = n_blocks / 2, n_steps = n_blocks - 1;
+    const int n_part = jac_gram_slices(D), slices = jac_slices(D);
+    std::vector<double> h_conv((size_t)n_blocks), h_norm((size_t)D);
     auto row_norms = [&](const double* M) -> bool {  // row norms to the host (blocking)
         hipLaunchKernelGGL(calib_rownorm_kernel, dim3(D), dim3(kCalThreads), 0, st, M, D, norm, sgn);
         return hipMemcpyAsync(h_norm.data(), norm, (size_t)D * 8, hipMemcpyDeviceToHost, st) == hipSuccess &&
@@ -1697,14 +1706,17 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         converged = failed != 0;
     }
     while (done < max_sweeps && !converged) {
-        if (hipMemsetAsync(conv, 0, (size_t)n_pairs * 8, st) != hipSuccess) return SALS_ERR_HIP;
+        if (hipMemsetAsync(conv, 0, (size_t)n_blocks * 8, st) != hipSuccess) return SALS_ERR_HIP;
+        hipLaunchKernelGGL(calib_jacobi_inside_gram_kernel, dim3(n_blocks, n_part), dim3(256), 0, st, G, D, D / n_part, part);
+        hipLaunchKernelGGL(calib_jacobi_inside_kernel, dim3(n_blocks, slices), dim3(kJacInsideThreads), 0, st, G, D, D / slices, part,
+                           n_part, lead, conv);
         for (int step = 0; step < n_steps; ++step) {
-            hipLaunchKernelGGL(calib_jacobi_gram_kernel, dim3(slices, n_pairs), dim3(256), 0, st, G, D, step, D / slices, part);
-            hipLaunchKernelGGL(calib_jacobi_rotate_kernel, dim3(slices, n_pairs), dim3(256), 0, st, G, D, step, D / slices, part,
-                               slices, lead, conv);
+            hipLaunchKernelGGL(calib_jacobi_gram_kernel, dim3(n_pairs, n_part, 2), dim3(256), 0, st, G, D, step, D / n_part, part);
+            hipLaunchKernelGGL(calib_jacobi_rotate_kernel, dim3(n_pairs, slices), dim3(kJacThreads), 0, st, G, D, step, D / slices,
+                               part, n_part, lead, conv);
         }
         if (launch_status() != SALS_OK) return SALS_ERR_HIP;
-        if (hipMemcpyAsync(h_conv.data(), conv, (size_t)n_pairs * 8, hipMemcpyDeviceToHost, st) != hipSuccess) return SALS_ERR_HIP;
+        if (hipMemcpyAsync(h_conv.data(), conv, (size_t)n_blocks * 8, hipMemcpyDeviceToHost, st) != hipSuccess) return SALS_ERR_HIP;
         if (!row_norms(G)) return SALS_ERR_HIP;
         double worst = 0.0;
         for (double v : h_conv) worst = std::max(worst, v);

@@ -112,6 +112,25 @@ def test_eigenvectors_match_the_oracle_on_a_separated_spectrum(D, r, decay):
     assert np.all(big > 0)
 
 
+@pytest.mark.parametrize("D,r", [(256, 256), (768, 300), (1280, 200)])
+def test_eigenvectors_at_widths_of_uneven_column_slices(D, r):
+    """Widths whose 32-row blocks make an uneven number of pairs and whose column slices are not powers of two, with a spectrum
+    that several sweeps work on."""
+    print(f"[case] eigenvectors D={D} r={r}, slow decay", flush=True)
+    rng = np.random.default_rng(D)
+    Q, _ = np.linalg.qr(rng.standard_normal((D, D)))
+    lam_true = 1.0 / np.arange(1, D + 1)
+    C = (Q * lam_true) @ Q.T
+    C = 0.5 * (C + C.T)
+    lam_ref, U_ref = cal.leading_eigenvectors(C, r)
+    lam, U, sweeps = _eig_gpu(C, r)
+    assert 0 < sweeps <= 30, sweeps
+    np.testing.assert_allclose(lam[:r], lam_ref[:r], rtol=0, atol=1e-11 * lam_ref[0])
+    # vectors: half an ulp of fp32, plus 1e-15 lambda_0 over the smallest gap (1 / r^2)
+    _same_up_to_sign(U, U_ref, 2e-7)
+    np.testing.assert_allclose(U.T @ U, np.eye(r), atol=5e-7)
+
+
 def test_eigenvectors_in_bf16_are_the_rounded_fp64_vectors():
     print("[case] eigenvectors bf16", flush=True)
     D, r = 256, 32
