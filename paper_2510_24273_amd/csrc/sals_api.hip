@@ -1728,6 +1728,16 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         std::nth_element(h_norm.begin(), h_norm.begin() + (r - 1), h_norm.end(), std::greater<double>());
         const double nr = h_norm[(size_t)r - 1];
         lead = 0.999 * nr * nr;
+        // Convergence is quadratic: a sweep of small rotations leaves none.  The angles that are left tell (where the sweep's
+        // largest was 1e-5 they are about 1e-12; above 1e-4 a further sweep is due anyway).
+        if (!converged && worst <= 1e-4) {
+            if (hipMemsetAsync(conv, 0, 8, st) != hipSuccess) return SALS_ERR_HIP;
+            hipLaunchKernelGGL(calib_jacobi_check_kernel, dim3(D / 64 * (D / 64 + 1) / 2), dim3(256), 0, st, G, D, norm, lead, conv);
+            if (launch_status() != SALS_OK || hipMemcpyAsync(h_conv.data(), conv, 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
+                hipStreamSynchronize(st) != hipSuccess)
+                return SALS_ERR_HIP;
+            converged = h_conv[0] <= 1e-11;
+        }
     }
     // A matrix whose factor needed no rotation is diagonal (R R^T is diagonal for an upper triangular R only if R is): its
     // own rows are the answer, without the detour through the square roots.
