@@ -54,6 +54,47 @@ __device__ __forceinline__ float2 stat_merge(float2 a, float2 b)
     return make_float2(m, a.y * __expf(a.x - m) + b.y * __expf(b.x - m));
 }
 
+// Logits whose latent axis was split over workgroups (64-token tiles): a slice's workgroup left its partial logits; the sum in
+// slice order and the tile's softmax statistics are one wave's job per (token tile, head).
+constexpr int kLsTok = 64;       // tokens per tile
+constexpr int kLsMaxSplit = 8;   // slices at most
+struct SplitLogits {
+    const float* plogits;    // [ksplit][rows][lk]
+    const int32_t* n_sel;    // [B] tokens of a sequence
+    float* logits;           // [rows][lk]
+    float2* stats;           // [rows][stats_stride], this pass's tiles from record 0 on
+    int ksplit, n_parts, rows, H, lk, stats_stride;   // rows = B * H
+};
+// The job in two halves, so that a kernel that does it on the side requests what it needs early and uses it late.
+struct SplitLogitsJob {
+    float v[kLsMaxSplit];
+    int n, slot, row, part;
+    __device__ __forceinline__ void request(const SplitLogits& f, int row_, int part_)
+    {
+        row = row_; part = part_;
+        slot = part * kLsTok + lane_id();
+#pragma unroll
+        for (int u = 0; u < kLsMaxSplit; ++u)  // all slices requested together, from clamped addresses
+            v[u] = f.plogits[((size_t)min(u, f.ksplit - 1) * f.rows + row) * f.lk + min(slot, f.lk - 1)];
+        n = f.n_sel[row / f.H];
+    }
+    __device__ __forceinline__ void finish(const SplitLogits& f) const
+    {
+        float d = 0.f;
+#pragma unroll
+        for (int u = 0; u < kLsMaxSplit; ++u) d += u < f.ksplit ? v[u] : 0.f;
+        const bool valid = slot < n;
+        if (slot < f.lk) f.logits[(size_t)row * f.lk + slot] = valid ? d : -INFINITY;
+        const float mx = wave_max(valid ? d : -INFINITY);
+        const float se = wave_sum(valid ? __expf(d - mx) : 0.f);
+        if (lane_id() == 0) f.stats[(size_t)row * f.stats_stride + part] = make_float2(mx, se);
+    }
+};
+
+// The recent window's tokens by the sequence length alone: the last min(w, min(length, k_tot)) tokens of the sequence, w the
+// window's own selection size (see write_window_lists, which writes the same list).
+struct WindowByLength { const int32_t* seq_len; int k_tot; };
+
 template <typename T> struct mma_op;
 template <> struct mma_op<bf16_t> {  // one v_mfma_f32_32x32x16_bf16 per 16-byte fragment pair
     static __device__ __forceinline__ void run(const u32x4& a, const u32x4& b, f32x16& c)

@@ -67,16 +67,19 @@ template <int HEADS, int NTG, int NB> struct logits_cfg {
 // the sequences of a tile.  Each sequence has its own query, count, index list and cache;
 // the latent axis may be cut into `ksplit` slices (the logit is additive over latent coordinates), whose partial
 // logits go to `plogits` for logits_finish_kernel.
-template <typename T, int HEADS, int NTG, int NB, int GB, int GFIX, bool MULTI = false>
-__global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void attend_logits_kernel(
-    const T* __restrict__ Kc, const T* __restrict__ UkP, const int32_t* __restrict__ idx,
+// BYLEN (MULTI only): the selections are recent windows given by the sequence lengths (`win`; idx and n_sel are not read).
+// SIDE: `split` names the logits of another pass whose slices are still to be added up, on the side (one job per wave).
+template <typename T, int HEADS, int NTG, int NB, int GB, int GFIX, bool MULTI, bool BYLEN, bool SIDE>
+__device__ __forceinline__ void logits_tile(
+    int block, const T* __restrict__ Kc, const T* __restrict__ UkP, const int32_t* __restrict__ idx,
     const int32_t* __restrict__ n_sel, const T* __restrict__ q, const int32_t* __restrict__ q_pos,
-    const float2* __restrict__ rope, InvFreq inv,
+    const float2* __restrict__ rope, const InvFreq& inv,
     float* __restrict__ logits, float2* __restrict__ stats, int B, int S_max, int r, int H, int H_kv,
     int k_tot, int lk, int n_parts, int heads_fastest, int style, float scale, int ring, int stats_stride,
-    float* __restrict__ plogits, int ksplit)
+    float* __restrict__ plogits, int ksplit, const WindowByLength& win, const SplitLogits& split)
 {
     typedef logits_cfg<HEADS, NTG, NB> C;
+    static_assert(!BYLEN || MULTI, "a window by length fills tiles of several sequences");
     static_assert(!MULTI || (HEADS == 1 && NB <= 2), "a sequence's 64 slots are those of one or two waves");
     constexpr int SQ = MULTI ? C::TOK / 64 : 1;   // sequences per tile
     constexpr int WT = NB * 32;                   // tokens per wave
@@ -96,7 +99,7 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
     if constexpr (MULTI) {
         // list order (head, sequence group, latent slice): an XCD's range keeps a few heads' projector slices
         const int nsg = (B + SQ - 1) / SQ, N = nsg * H_kv * ksplit;
-        const int id = blockIdx.x, xcd = id % kXcds, slot = id / kXcds;
+        const int id = block, xcd = id % kXcds, slot = id / kXcds;
         const int qn = N / kXcds, rem = N % kXcds;
         const int w = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + slot;
         g0 = w / (nsg * ksplit);
@@ -104,7 +107,7 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
         b = (rest / ksplit) * SQ; kz = rest % ksplit; part = 0;
     } else {
         const int n_y = H_kv / HEADS, N = n_parts * n_y * B;
-        const int id = blockIdx.x, xcd = id % kXcds, slot = id / kXcds;
+        const int id = block, xcd = id % kXcds, slot = id / kXcds;
         const int qn = N / kXcds, rem = N % kXcds;
         const int w = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + slot;
         if (heads_fastest) {
@@ -124,7 +127,7 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
     auto seq_of = [&](int t) { return MULTI ? min(b + (t >> 6), B - 1) : b; };
     // count and query position: of this wave's sequence (MULTI: the position is needed per thread
     // for the thread's share of the cos/sin rows, see rotate_query)
-    const int n_v = ld_uniform_i32(n_sel + (MULTI ? seq_of(tg * WT) : b));
+    const int n_v = ld_uniform_i32((BYLEN ? win.seq_len : n_sel) + (MULTI ? seq_of(tg * WT) : b));
     const int qpos_v = MULTI ? q_pos[seq_of(tid & ~63)] : ld_uniform_i32(q_pos + b);  // in flight with the loads below
     const int G = GFIX > 0 ? GFIX : H / H_kv;
     const int g = g0 + hh;
@@ -134,8 +137,22 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
     // read whatever the index array holds there, clamped to a valid row; they get no weight), the raw query
     // pairs of the tile's heads and the query position.
     const int rows_per_seq = ring > 0 ? ring : S_max;
+    SplitLogitsJob job;
+    const int job_id = block * (NT / 64) + wave;
+    const bool has_job = SIDE && job_id < split.rows * split.n_parts;  // uniform
+    auto request_job = [&](int j) { const int row = j / split.n_parts; job.request(split, row, j - row * split.n_parts); };
+    if (has_job) request_job(job_id);
     // cache row (= RoPE position) of tile token t: slot t of the one sequence, or slot t % 64 of sequence b + t / 64
+    auto window_of = [&](int len, int* S) {  // tokens of a window by length
+        *S = min(max(len, 0), S_max);
+        return min(k_tot, min(*S, win.k_tot));
+    };
     auto row_of = [&](int t) {
+        if constexpr (BYLEN) {
+            int S;
+            const int nw = window_of(win.seq_len[seq_of(t)], &S);
+            return min(max(S - nw + ((t & 63) < nw ? t & 63 : 0), 0), S_max - 1);
+        }
         const int32_t* ib = idx + (size_t)seq_of(t) * k_tot;
         return min(max(ib[min(MULTI ? (t & 63) : tok0 + t, k_tot - 1)], 0), S_max - 1);
     };
@@ -190,7 +207,17 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
             for (int i = 0; i < NA; ++i) load_a(i, st);
         }
     // MULTI: a sequence past the batch has no tokens
-    const int n = (MULTI && b + sw >= B) ? 0 : wave_uniform(n_v);
+    int n = wave_uniform(n_v);
+    if constexpr (BYLEN) { int S; n = window_of(n, &S); }
+    if (MULTI && b + sw >= B) n = 0;
+    if (has_job) {
+        job.finish(split);
+        // (the rest, where there are more than waves)
+        for (int j = job_id + (int)gridDim.x * (NT / 64); j < split.rows * split.n_parts; j += (int)gridDim.x * (NT / 64)) {
+            request_job(j);
+            job.finish(split);
+        }
+    }
     const int qpos = MULTI ? qpos_v : wave_uniform(qpos_v);
     if (!MULTI && tok0 >= n) {  // no selected token in this tile: neutral statistics
         if (tid < HEADS * G)
@@ -449,5 +476,28 @@ __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void at
         if (!MULTI || bt < B) stats[((size_t)bt * H + (size_t)(g0 + h2) * G + m) * stats_stride + part] = st;
     }
 }
+
+#define SALS_LG_ARGS                                                                                                     \
+    const T *__restrict__ Kc, const T *__restrict__ UkP, const int32_t *__restrict__ idx, const int32_t *__restrict__ n_sel, \
+        const T *__restrict__ q, const int32_t *__restrict__ q_pos, const float2 *__restrict__ rope, InvFreq inv,         \
+        float *__restrict__ logits, float2 *__restrict__ stats, int B, int S_max, int r, int H, int H_kv, int k_tot,      \
+        int lk, int n_parts, int heads_fastest, int style, float scale, int ring, int stats_stride,                       \
+        float *__restrict__ plogits, int ksplit
+template <typename T, int HEADS, int NTG, int NB, int GB, int GFIX, bool MULTI = false>
+__global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void attend_logits_kernel(SALS_LG_ARGS)
+{
+    logits_tile<T, HEADS, NTG, NB, GB, GFIX, MULTI, false, false>((int)blockIdx.x, Kc, UkP, idx, n_sel, q, q_pos, rope, inv, logits, stats,
+                                                                  B, S_max, r, H, H_kv, k_tot, lk, n_parts, heads_fastest, style, scale,
+                                                                  ring, stats_stride, plogits, ksplit, WindowByLength{}, SplitLogits{});
+}
+// with another pass's split logits on the side
+template <typename T, int HEADS, int NTG, int NB, int GB, int GFIX>
+__global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void attend_logits_side_kernel(SALS_LG_ARGS, SplitLogits split)
+{
+    logits_tile<T, HEADS, NTG, NB, GB, GFIX, false, false, true>((int)blockIdx.x, Kc, UkP, idx, n_sel, q, q_pos, rope, inv, logits, stats,
+                                                                 B, S_max, r, H, H_kv, k_tot, lk, n_parts, heads_fastest, style, scale,
+                                                                 ring, stats_stride, plogits, ksplit, WindowByLength{}, split);
+}
+#undef SALS_LG_ARGS
 
 }  // namespace sals

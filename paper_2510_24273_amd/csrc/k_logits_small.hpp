@@ -25,7 +25,6 @@
 namespace sals {
 
 constexpr int kLsThreads = 512;
-constexpr int kLsTok = 64;                                   // tokens per workgroup
 constexpr int kLsMaxChunk = 10;                              // latent steps loaded ahead, at most
 constexpr int kLsStepBytes = (kHeadDim + kLsTok) * kLgChunk;  // U_k panel + gathered rows: 24 KB
 constexpr int kLsIterBytes = 2 * kLsStepBytes;               // two steps per iteration
@@ -45,16 +44,17 @@ struct FusedSelect {
 };
 constexpr int kLsFusedMaxS = 4096, kLsFusedMaxK = 1024;
 
-template <typename T, int NST, bool FUSED = false>
-__global__ __launch_bounds__(kLsThreads) void attend_logits_small_kernel(
-    // (what the workgroup's first loads need comes first: those 14 words arrive preloaded in scalar registers)
-    const int32_t* __restrict__ idx, const int32_t* __restrict__ n_sel, const T* __restrict__ UkP,
+// BYLEN: the selection is a recent window given by the sequence lengths (`win`; idx and n_sel are not read).
+// SIDE: `split` names the logits of another pass whose slices are still to be added up, on the side (one job per wave).
+template <typename T, int NST, bool FUSED, bool BYLEN, bool SIDE>
+__device__ __forceinline__ void logits_small_tile(
+    int block, const int32_t* __restrict__ idx, const int32_t* __restrict__ n_sel, const T* __restrict__ UkP,
     int B, int H_kv, int n_parts, int heads_fastest, int ksplit, int k_tot, int r, int H,
     const T* __restrict__ Kc, const T* __restrict__ q, const int32_t* __restrict__ q_pos,
-    const float2* __restrict__ rope, InvFreq inv,
+    const float2* __restrict__ rope, const InvFreq& inv,
     float* __restrict__ logits, float2* __restrict__ stats, int S_max,
     int lk, int style, float scale, int ring,
-    float* __restrict__ plogits, int stats_stride, FusedSelect fs)
+    float* __restrict__ plogits, int stats_stride, const FusedSelect& fs, const WindowByLength& win, const SplitLogits& split)
 {
     constexpr int ES = (int)sizeof(T);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kLsThreads) void attend_logits_small_kernel(
     int b, g, part, kz;  // kz: this workgroup's slice of the latent axis (the slices of a tile are neighbours)
     {
         const int N = n_parts * H_kv * B * ksplit;
-        const int id = blockIdx.x, xcd = id % kXcds, slot = id / kXcds;
+        const int id = block, xcd = id % kXcds, slot = id / kXcds;
         const int qn = N / kXcds, rem = N % kXcds;
         const int wk = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + slot;
         const int w = wk / ksplit;
@@ -93,7 +93,23 @@ __global__ __launch_bounds__(kLsThreads) void attend_logits_small_kernel(
     const int e_slot = tok0 + tb * 32 + l32;  // token this lane finishes in the epilogue
     const int32_t* ib = idx + (size_t)b * k_tot;
     int idx_my = 0, idx_e = 0, idx_0 = 0, n_v = 0;
-    if constexpr (!FUSED) {
+    SplitLogitsJob job;
+    const int job_id = block * (kLsThreads / kWave) + wave;
+    const bool has_job = SIDE && job_id < split.rows * split.n_parts;  // uniform
+    auto request_job = [&](int j) { const int row = j / split.n_parts; job.request(split, row, j - row * split.n_parts); };
+    if (has_job) request_job(job_id);
+    auto finish_jobs = [&]() {
+        if (!has_job) return;
+        job.finish(split);
+        // (the rest, where there are more than waves)
+        for (int j = job_id + (int)gridDim.x * (kLsThreads / kWave); j < split.rows * split.n_parts; j += (int)gridDim.x * (kLsThreads / kWave)) {
+            request_job(j);
+            job.finish(split);
+        }
+    };
+    if constexpr (BYLEN) {
+        n_v = ld_uniform_i32(win.seq_len + b);
+    } else if constexpr (!FUSED) {
         idx_my = ib[min(my_slot, k_tot - 1)]; idx_e = ib[min(e_slot, k_tot - 1)]; idx_0 = ib[0];
         n_v = ld_uniform_i32(n_sel + b);
     }
@@ -167,10 +183,17 @@ __global__ __launch_bounds__(kLsThreads) void attend_logits_small_kernel(
         }
         __syncthreads();  // (the list has been read: the stage buffers may be written)
     }
-    const int n = wave_uniform(n_v);
-    if (tok0 >= n) {  // no selected token in this tile: neutral statistics (split tiles: the finishing kernel's job)
+    int n = wave_uniform(n_v);
+    if constexpr (BYLEN) {
+        const int S = min(max(n, 0), S_max);
+        n = min(k_tot, min(S, win.k_tot));
+        idx_0 = S - n;
+        idx_my = idx_0 + my_slot; idx_e = idx_0 + e_slot;
+    }
+    if (tok0 >= n) {  // no selected token in this tile: neutral statistics (split tiles: where they are added up)
         if (tid < G && ksplit == 1)
             stats[((size_t)b * H + (size_t)g * G + tid) * stats_stride + part] = make_float2(-INFINITY, 0.f);
+        if constexpr (SIDE) finish_jobs();
         return;
     }
     // slots past the selected tokens read the first selected row; they get no weight
@@ -306,32 +329,40 @@ __global__ __launch_bounds__(kLsThreads) void attend_logits_small_kernel(
             }
         }
     }
+    if constexpr (SIDE) finish_jobs();
 }
+
+#define SALS_LS_ARGS                                                                                                     \
+    /* (what the workgroup's first loads need comes first: those 14 words arrive preloaded in scalar registers) */        \
+    const int32_t *__restrict__ idx, const int32_t *__restrict__ n_sel, const T *__restrict__ UkP, int B, int H_kv,       \
+        int n_parts, int heads_fastest, int ksplit, int k_tot, int r, int H, const T *__restrict__ Kc,                    \
+        const T *__restrict__ q, const int32_t *__restrict__ q_pos, const float2 *__restrict__ rope, InvFreq inv,         \
+        float *__restrict__ logits, float2 *__restrict__ stats, int S_max, int lk, int style, float scale, int ring,      \
+        float *__restrict__ plogits, int stats_stride
+template <typename T, int NST, bool FUSED>
+__global__ __launch_bounds__(kLsThreads) void attend_logits_small_kernel(SALS_LS_ARGS, FusedSelect fs)
+{
+    logits_small_tile<T, NST, FUSED, false, false>((int)blockIdx.x, idx, n_sel, UkP, B, H_kv, n_parts, heads_fastest, ksplit, k_tot, r, H,
+                                                   Kc, q, q_pos, rope, inv, logits, stats, S_max, lk, style, scale, ring, plogits,
+                                                   stats_stride, fs, WindowByLength{}, SplitLogits{});
+}
+// with another pass's split logits on the side
+template <typename T, int NST>
+__global__ __launch_bounds__(kLsThreads) void attend_logits_small_side_kernel(SALS_LS_ARGS, SplitLogits split)
+{
+    logits_small_tile<T, NST, false, false, true>((int)blockIdx.x, idx, n_sel, UkP, B, H_kv, n_parts, heads_fastest, ksplit, k_tot, r, H,
+                                                  Kc, q, q_pos, rope, inv, logits, stats, S_max, lk, style, scale, ring, plogits,
+                                                  stats_stride, FusedSelect{}, WindowByLength{}, split);
+}
+#undef SALS_LS_ARGS
 
 // Split tiles: logits = sum of the latent slices' partial logits, in slice order, and the tile's softmax
 // statistics.  grid (n_parts, B*H), 64 threads (one per token of the tile).
-constexpr int kLsMaxSplit = 8;
-__global__ __launch_bounds__(64) void logits_finish_kernel(const float* __restrict__ plogits, int ksplit,
-                                                           const int32_t* __restrict__ n_sel,
-                                                           float* __restrict__ logits, float2* __restrict__ stats,
-                                                           int B, int H, int lk, int stats_stride)
+__global__ __launch_bounds__(64) void logits_finish_kernel(SplitLogits f)
 {
-    const int part = blockIdx.x, lane = threadIdx.x;
-    const size_t hrow = blockIdx.y;
-    const int slot = part * kLsTok + lane;
-    float v[kLsMaxSplit];
-#pragma unroll
-    for (int u = 0; u < kLsMaxSplit; ++u)  // all slices requested together, from clamped addresses
-        v[u] = plogits[((size_t)min(u, ksplit - 1) * B * H + hrow) * lk + min(slot, lk - 1)];
-    const int n = n_sel[hrow / H];
-    float d = 0.f;
-#pragma unroll
-    for (int u = 0; u < kLsMaxSplit; ++u) d += u < ksplit ? v[u] : 0.f;
-    const bool valid = slot < n;
-    if (slot < lk) logits[hrow * lk + slot] = valid ? d : -INFINITY;
-    const float mx = wave_max(valid ? d : -INFINITY);
-    const float se = wave_sum(valid ? __expf(d - mx) : 0.f);
-    if (lane == 0) stats[hrow * stats_stride + part] = make_float2(mx, se);
+    SplitLogitsJob job;
+    job.request(f, (int)blockIdx.y, (int)blockIdx.x);
+    job.finish(f);
 }
 
 }  // namespace sals

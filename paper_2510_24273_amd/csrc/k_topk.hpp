@@ -99,7 +99,7 @@ __device__ __forceinline__ void topk_select_sequence(TopkShared& sh, const float
     constexpr int NREG = F4 > 0 ? F4 * 4 : 4;
     constexpr int NW = NTH / kWave;              // waves
     constexpr int BPT = kTopkBins / NTH;         // histogram bins per thread
-    static_assert(NTH % kWave == 0 && NTH >= kTopkCand && NTH <= kTopkThreads && kTopkBins % NTH == 0 && (!CONSEC || F4 > 0),
+    static_assert(NTH % kWave == 0 && NTH <= kTopkThreads && kTopkBins % (4 * NTH) == 0 && (!CONSEC || F4 > 0),
                   "workgroup shape");
     // token of this thread's key i (i = 4*group + element)
     auto token_of = [&](int i) { return CONSEC ? tid * NREG + i : ((((i >> 2) * NTH) + tid) << 2) + (i & 3); };
@@ -143,7 +143,9 @@ __device__ __forceinline__ void topk_select_sequence(TopkShared& sh, const float
 #pragma unroll
     for (int t = 0; t < kTopkBins / 4; t += NTH)
         if (kTopkBins / 4 % NTH == 0 || t + tid < kTopkBins / 4) *reinterpret_cast<u32x4*>(&sh.hist[(t + tid) * 4]) = u32x4{0, 0, 0, 0};
-    if (tid < kTopkCand) sh.cand[tid] = 0u;  // key 0 ranks below every candidate
+#pragma unroll
+    for (int t = 0; t < kTopkCand; t += NTH)  // (key 0 ranks below every candidate)
+        if (kTopkCand % NTH == 0 || t + tid < kTopkCand) sh.cand[t + tid] = 0u;
     if (tid == 0) sh.n_cand = 0u;
     const int S = min(wave_uniform(S_in_v), S_max);
 
@@ -271,8 +273,8 @@ __device__ __forceinline__ void topk_select_sequence(TopkShared& sh, const float
                 }
                 __syncthreads();
                 // the member with  #(greater) < kk <= #(greater or equal)  carries the k-th key
-                if (tid < (int)members) {
-                    const uint32_t mykey = sh.cand[tid];
+                for (int t = tid; t < (int)members; t += NTH) {
+                    const uint32_t mykey = sh.cand[t];
                     uint32_t gt = 0u, ge = 0u;
                     for (uint32_t c = 0; c < members; c += 4) {
                         u32x4 o = *reinterpret_cast<const u32x4*>(&sh.cand[c]);

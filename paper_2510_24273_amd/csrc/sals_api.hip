@@ -435,12 +435,12 @@ sals_status ensure_rope_table(const sals_ctx* cc, hipStream_t st)
 }
 
 // the logits kernels use more than the default 48 KB of dynamic LDS: raised once per context, on first use
-template <typename T> sals_status allow_logits_lds(const LogitsPlan& P, int group);
+template <typename T> sals_status allow_logits_lds(const sals_ctx* c);
 template <typename T> sals_status ensure_lds_attr(const sals_ctx* cc)
 {
     sals_ctx* c = const_cast<sals_ctx*>(cc);
     if (c->lds_allowed) return SALS_OK;
-    if (allow_logits_lds<T>(c->plan, c->d.H_q / c->d.H_kv) != SALS_OK) return SALS_ERR_HIP;
+    if (allow_logits_lds<T>(c) != SALS_OK) return SALS_ERR_HIP;
     c->lds_allowed = true;
     return SALS_OK;
 }
@@ -487,11 +487,21 @@ struct QvCache {
 // qv == nullptr: latent value cache Vc, value sum in latent space and output projection through U_v.
 // Otherwise: values are the de-quantised rows of the quantised cache (Vc unused).
 // ring > 0: Kc, Vc are rings of that many rows per sequence (token t in row t mod ring).
+// other: another pass's split logits, added up by this pass's logits kernel on the side (not by the tiles of several sequences).
 // phases: which of the three launches to enqueue (all of them by default).  link: where the logits kernel leaves
 // its tile statistics and where the value kernel finds the statistics of the whole softmax, when two passes over
 // different caches share one softmax (recent window); by default the context's own array.
 enum { kPhaseLogits = 1, kPhaseValue = 2, kPhaseOut = 4, kPhaseAll = 7 };
 struct StatsLink { float2* stats; int stride; int part0; };  // [B*H][stride] records, this pass's tiles from part0 on
+
+// 128-byte steps that the 64-token logits kernel loads ahead: the largest divisor of a slice's step count
+template <typename T> int steps_ahead(const sals_desc& d, int ksplit)
+{
+    const int nkc = d.r * (int)sizeof(T) / kLgChunk / ksplit;
+    int n = kLsMaxChunk;
+    while (nkc % n != 0) --n;
+    return n;
+}
 
 template <typename T> LogitsPlan plan_logits(const sals_desc& d)
 {
@@ -555,9 +565,7 @@ template <typename T> LogitsPlan plan_logits(const sals_desc& d)
         return P;
     }
     P.n_parts = ceil_div(k_tot, kLsTok);
-    const int nkc = nkc128 / P.ksplit;
-    P.nst = kLsMaxChunk;  // steps loaded ahead: the largest divisor of the step count
-    while (nkc % P.nst != 0) --P.nst;
+    P.nst = steps_ahead<T>(d, P.ksplit);
     return P;
 }
 
@@ -566,6 +574,18 @@ template <typename T> struct SmallLogits {
     typedef void (*Fn)(const int32_t*, const int32_t*, const T*, int, int, int, int, int, int, int, int, const T*, const T*,
                        const int32_t*, const float2*, InvFreq, float*, float2*, int, int, int, float, int, float*, int,
                        FusedSelect);
+    typedef void (*SideFn)(const int32_t*, const int32_t*, const T*, int, int, int, int, int, int, int, int, const T*, const T*,
+                           const int32_t*, const float2*, InvFreq, float*, float2*, int, int, int, float, int, float*, int,
+                           SplitLogits);
+    static SideFn side(int nst)
+    {
+#define SALS_LS(N) case N: return attend_logits_small_side_kernel<T, N>;
+        switch (nst) {
+            SALS_LS(1) SALS_LS(2) SALS_LS(3) SALS_LS(4) SALS_LS(5) SALS_LS(6) SALS_LS(7) SALS_LS(8) SALS_LS(9)
+            default: return attend_logits_small_side_kernel<T, 10>;
+        }
+#undef SALS_LS
+    }
     static Fn get(int nst, bool fused)
     {
 #define SALS_LS(N) case N: return fused ? (Fn)attend_logits_small_kernel<T, N, true> : (Fn)attend_logits_small_kernel<T, N, false>;
@@ -576,6 +596,42 @@ template <typename T> struct SmallLogits {
 #undef SALS_LS
     }
 };
+
+// the window's logits and the step's selection in one launch, for one sequence (64-token form) and for a batch
+template <typename T> struct WindowSelectSmall {
+    typedef void (*Fn)(StepSelect, const T*, int, int, int, int, int, int, int, int, const T*, const T*, const int32_t*, const float2*,
+                       InvFreq, float*, float2*, int, int, int, float, float*, int);
+    static Fn get(int nst)
+    {
+#define SALS_WS(N) case N: return window_select_small_kernel<T, N>;
+        switch (nst) {
+            SALS_WS(1) SALS_WS(2) SALS_WS(3) SALS_WS(4) SALS_WS(5) SALS_WS(6) SALS_WS(7) SALS_WS(8) SALS_WS(9)
+            default: return window_select_small_kernel<T, 10>;
+        }
+#undef SALS_WS
+    }
+};
+template <typename T> auto window_select_for(int group)
+{
+    if (group == 1) return window_select_kernel<T, 1, 1>;
+    if (group == 4) return window_select_kernel<T, 4, 4>;
+    if (group % 4 == 0) return window_select_kernel<T, 4, 0>;
+    return window_select_kernel<T, 1, 0>;
+}
+int select_blocks(const sals_desc& d) { return ceil_div(d.B, kXcds) * kXcds; }
+// Slices of the window's latent axis in the combined launch: the window's own plan, halved while its workgroups fit the chip at
+// once (one per compute unit in the 64-token form, two otherwise) and do not together with the selection's.  (A workgroup too many is a
+// round too many: 16 sequences, r_hi = 2048, two slices 32.0 us and a sum to add, one 30.6; one sequence, eight slices would be
+// 257 workgroups.)
+int window_select_slices(const sals_ctx* win)
+{
+    const LogitsPlan& P = win->plan;
+    const sals_desc& d = win->d;
+    const int tiles = P.pick == 4 ? ceil_div(d.B, 2) * d.H_kv : P.n_parts * d.H_kv * d.B, slots = P.pick == 4 ? 512 : 256;
+    int ks = P.ksplit;
+    while (ks > 1 && tiles * ks <= slots && tiles * ks + d.B > slots) ks /= 2;
+    return ks;
+}
 
 // Whether a whole decode step on this context lets the logits kernel select by itself (no selection launch): the
 // 64-token kernel without a split of the latent axis, a cache of at most 4096 rows whose score rows start 16-byte
@@ -596,8 +652,19 @@ template <typename T, int HEADS, int NTG, int NB, bool MULTI = false> auto logit
     return attend_logits_kernel<T, HEADS, NTG, NB, 1, 0, MULTI>;
 }
 
-template <typename T> sals_status allow_logits_lds(const LogitsPlan& P, int group)
+// the same with another pass's split logits on the side
+template <typename T, int HEADS, int NTG, int NB> auto logits_side_kernel_for(int group)
 {
+    if (group == 1) return attend_logits_side_kernel<T, HEADS, NTG, NB, 1, 1>;
+    if (group == 4) return attend_logits_side_kernel<T, HEADS, NTG, NB, 4, 4>;
+    if (group % 4 == 0) return attend_logits_side_kernel<T, HEADS, NTG, NB, 4, 0>;
+    return attend_logits_side_kernel<T, HEADS, NTG, NB, 1, 0>;
+}
+
+template <typename T> sals_status allow_logits_lds(const sals_ctx* c)
+{
+    const LogitsPlan& P = c->plan;
+    const int group = c->d.H_q / c->d.H_kv;
     auto allow = [](const void* kern, size_t bytes) {
         return bytes <= 48 * 1024 ||
                hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
@@ -610,7 +677,29 @@ template <typename T> sals_status allow_logits_lds(const LogitsPlan& P, int grou
         ok = allow(reinterpret_cast<const void*>(SmallLogits<T>::get(P.nst, false)), kLsLds) &&
              allow(reinterpret_cast<const void*>(SmallLogits<T>::get(P.nst, true)), kLsLds);
     }
+    // (a context with recent tokens may have a window beside it)
+    if (ok && c->d.n_recent > 0) {
+        if (P.pick == 1) ok = allow(reinterpret_cast<const void*>(logits_side_kernel_for<T, 2, 4, 2>(group)), logits_cfg<2, 4, 2>::LDS);
+        if (P.pick == 2) ok = allow(reinterpret_cast<const void*>(logits_side_kernel_for<T, 1, 4, 1>(group)), logits_cfg<1, 4, 1>::LDS);
+        if (P.pick == 3) ok = allow(reinterpret_cast<const void*>(SmallLogits<T>::side(P.nst)), kLsLds);
+    }
+    // (a context without sinks and recent tokens may be a window)
+    if (ok && c->d.n_sink == 0 && c->d.n_recent == 0) {
+        if (P.pick == 4) ok = allow(reinterpret_cast<const void*>(window_select_for<T>(group)), logits_cfg<1, 4, 1>::LDS);
+        if (P.pick == 3) {
+            const int nst = steps_ahead<T>(c->d, window_select_slices(c));
+            ok = allow(reinterpret_cast<const void*>(WindowSelectSmall<T>::get(nst)), kLsLds) &&
+                 allow(reinterpret_cast<const void*>(SmallLogits<T>::get(nst, false)), kLsLds);
+        }
+    }
     return ok ? SALS_OK : SALS_ERR_HIP;
+}
+
+// a context's split logits (see SplitLogits)
+SplitLogits split_logits(const sals_ctx* c, int ksplit, const int32_t* n_sel, float2* stats, int stats_stride)
+{
+    return SplitLogits{reinterpret_cast<const float*>(c->ws + c->L.plogits), n_sel, reinterpret_cast<float*>(c->ws + c->L.logits), stats,
+                       ksplit, c->plan.n_parts, c->d.B * c->d.H_q, c->d.H_q, c->L.lk, stats_stride};
 }
 
 // Value sum over the selected tokens of a cache, and of a second one under the same softmax (the recent window).
@@ -679,13 +768,17 @@ template <typename T>
 sals_status launch_attend(const sals_ctx* c, const void* q, const int32_t* q_pos, const void* Kc,
                           const void* Vc, const void* W, const int32_t* idx, const int32_t* n_sel, void* out,
                           hipStream_t st, const QvCache* qv = nullptr, int ring = 0, int phases = kPhaseAll,
-                          const StatsLink* link = nullptr, const FusedSelect* fs = nullptr)
+                          const StatsLink* link = nullptr, const FusedSelect* fs = nullptr, const SplitLogits* other = nullptr)
 {
     const sals_desc& d = c->d;
     const Layout& L = c->L;
     const int k_tot = d.top_k + d.n_sink + d.n_recent;
     float* logits = reinterpret_cast<float*>(c->ws + L.logits);
-    const LogitsPlan P = c->plan;
+    LogitsPlan P = c->plan;
+    if (ring > 0 && P.pick >= 3) {  // (as in a decode step)
+        P.ksplit = window_select_slices(c);
+        if (P.pick == 3) P.nst = steps_ahead<T>(d, P.ksplit);
+    }
     // tile statistics: written by this pass's logits kernel from record `part0` on, read as a whole by the value kernel
     float2* const stats_all = link ? link->stats : reinterpret_cast<float2*>(c->ws + L.stats);
     float2* const stats = stats_all + (link ? link->part0 : 0);
@@ -701,15 +794,18 @@ sals_status launch_attend(const sals_ctx* c, const void* q, const int32_t* q_pos
         const size_t a_bytes = (size_t)d.H_kv * kHeadDim * d.r, b_bytes = (size_t)d.B * k_tot * d.r;
         const int heads_fastest = a_bytes <= b_bytes ? 1 : 0;
         ProfScope ps(c, SALS_K_ATTEND_LOGITS, st);
+#define SALS_LOGITS_ARGS                                                                                          \
+    static_cast<const T*>(Kc), w_section<T>(c, W, 2), idx, n_sel, static_cast<const T*>(q), q_pos, rope, c->inv,   \
+        logits, stats, d.B, d.S_max, d.r, d.H_q, d.H_kv, k_tot, L.lk, n_parts, heads_fastest, d.rope_style,        \
+        1.0f / std::sqrt((float)d.d), ring, stats_stride, static_cast<float*>(nullptr), 1
 #define SALS_LOGITS(HEADS, NTG, NB)                                                                              \
     do {                                                                                                     \
         typedef logits_cfg<HEADS, NTG, NB> LC;                                                               \
-        auto kern = logits_kernel_for<T, HEADS, NTG, NB>(d.H_q / d.H_kv);                                    \
-        hipLaunchKernelGGL(kern, dim3(n_parts * (d.H_kv / HEADS) * d.B), dim3(LC::NT), LC::LDS, st,          \
-                           static_cast<const T*>(Kc), w_section<T>(c, W, 2), idx, n_sel,                     \
-                           static_cast<const T*>(q), q_pos, rope, c->inv, logits, stats, d.B,                \
-                           d.S_max, d.r, d.H_q, d.H_kv, k_tot, L.lk, n_parts, heads_fastest, d.rope_style,   \
-                           1.0f / std::sqrt((float)d.d), ring, stats_stride, static_cast<float*>(nullptr), 1);       \
+        const dim3 grid(n_parts * (d.H_kv / HEADS) * d.B);                                                   \
+        if (other) hipLaunchKernelGGL((logits_side_kernel_for<T, HEADS, NTG, NB>(d.H_q / d.H_kv)), grid, dim3(LC::NT), LC::LDS, st, \
+                                      SALS_LOGITS_ARGS, *other);                                             \
+        else hipLaunchKernelGGL((logits_kernel_for<T, HEADS, NTG, NB>(d.H_q / d.H_kv)), grid, dim3(LC::NT), LC::LDS, st, \
+                                SALS_LOGITS_ARGS);                                                           \
     } while (0)
         const int pick = P.pick;
         if (pick == 1) SALS_LOGITS(2, 4, 2);        // 2 heads x 256 tokens, 8 waves
@@ -722,30 +818,31 @@ sals_status launch_attend(const sals_ctx* c, const void* q, const int32_t* q_pos
                                static_cast<const T*>(Kc), w_section<T>(c, W, 2), idx, n_sel, static_cast<const T*>(q), q_pos,
                                rope, c->inv, logits, stats, d.B, d.S_max, d.r, d.H_q, d.H_kv, k_tot, L.lk, 1, heads_fastest,
                                d.rope_style, 1.0f / std::sqrt((float)d.d), ring, stats_stride, plogits, P.ksplit);
-            if (P.ksplit > 1) {
-                if (launch_status() != SALS_OK) return SALS_ERR_HIP;
-                hipLaunchKernelGGL(logits_finish_kernel, dim3(1, d.B * d.H_q), dim3(64), 0, st, plogits, P.ksplit, n_sel,
-                                   logits, stats, d.B, d.H_q, L.lk, stats_stride);
-            }
         }
         else {  // few tiles: 1 head x 64 tokens with the whole latent axis loaded ahead
             const int ksplit = P.ksplit, nst = P.nst;
-            // fs: idx / n_sel are outputs of this launch (the kernel selects from fs->scores itself)
-            const typename SmallLogits<T>::Fn kern = SmallLogits<T>::get(nst, fs != nullptr);
-            const FusedSelect fsel = fs ? *fs : FusedSelect{nullptr, nullptr, 0, 0, 0};
             float* plogits = reinterpret_cast<float*>(c->ws + L.plogits);
-            hipLaunchKernelGGL(kern, dim3(n_parts * d.H_kv * d.B * ksplit), dim3(kLsThreads), kLsLds, st,
-                               idx, n_sel, w_section<T>(c, W, 2), d.B, d.H_kv, n_parts, heads_fastest, ksplit, k_tot,
-                               d.r, d.H_q, static_cast<const T*>(Kc), static_cast<const T*>(q), q_pos, rope, c->inv,
-                               logits, stats, d.S_max, L.lk, d.rope_style, 1.0f / std::sqrt((float)d.d), ring,
-                               plogits, stats_stride, fsel);
-            if (ksplit > 1) {
-                if (launch_status() != SALS_OK) return SALS_ERR_HIP;
-                hipLaunchKernelGGL(logits_finish_kernel, dim3(n_parts, d.B * d.H_q), dim3(64), 0, st, plogits, ksplit,
-                                   n_sel, logits, stats, d.B, d.H_q, L.lk, stats_stride);
+            const dim3 grid(n_parts * d.H_kv * d.B * ksplit);
+#define SALS_LS_ARGS                                                                                                      \
+    idx, n_sel, w_section<T>(c, W, 2), d.B, d.H_kv, n_parts, heads_fastest, ksplit, k_tot, d.r, d.H_q,                     \
+        static_cast<const T*>(Kc), static_cast<const T*>(q), q_pos, rope, c->inv, logits, stats, d.S_max, L.lk,            \
+        d.rope_style, 1.0f / std::sqrt((float)d.d), ring, plogits, stats_stride
+            // fs: idx / n_sel are outputs of this launch (the kernel selects from fs->scores itself)
+            if (other) {
+                hipLaunchKernelGGL(SmallLogits<T>::side(nst), grid, dim3(kLsThreads), kLsLds, st, SALS_LS_ARGS, *other);
+            } else {
+                const FusedSelect fsel = fs ? *fs : FusedSelect{nullptr, nullptr, 0, 0, 0};
+                hipLaunchKernelGGL(SmallLogits<T>::get(nst, fs != nullptr), grid, dim3(kLsThreads), kLsLds, st, SALS_LS_ARGS, fsel);
             }
+#undef SALS_LS_ARGS
+        }
+        if (P.ksplit > 1) {
+            if (launch_status() != SALS_OK) return SALS_ERR_HIP;
+            hipLaunchKernelGGL(logits_finish_kernel, dim3(n_parts, d.B * d.H_q), dim3(64), 0, st,
+                               split_logits(c, P.ksplit, n_sel, stats, stats_stride));
         }
 #undef SALS_LOGITS
+#undef SALS_LOGITS_ARGS
         if (launch_status() != SALS_OK) return SALS_ERR_HIP;
     }
     if (qv != nullptr) {
@@ -1251,6 +1348,8 @@ sals_status sals_window_append(sals_ctx* win, const void* k_new, const void* v_n
                : launch_append<float>(win, W_hi, k_new, v_new, Kw, Vw, QuantArgs{}, sl, st, false, ring);
 }
 
+}  // extern "C"
+
 namespace {
 // where the two passes' token lists live: the window's list and count in the window context's workspace, the
 // low-rank pass's count in the main context's
@@ -1260,41 +1359,123 @@ WindowLists window_lists(sals_ctx* ctx, sals_ctx* win)
                        reinterpret_cast<int32_t*>(win->ws + win->L.n_sel), win->d.top_k};
 }
 
-// lists_ready: the selection kernel has already written the two passes' lists (decode step); otherwise they are
-// split off the caller's selection here
+// where the two passes leave their tile statistics: side by side in the main context's array
+StatsLink window_stats(sals_ctx* ctx, sals_ctx* win, bool hi)
+{
+    return StatsLink{reinterpret_cast<float2*>(ctx->ws + ctx->L.stats), ctx->plan.n_parts + win->plan.n_parts, hi ? ctx->plan.n_parts : 0};
+}
+
+// A step's selection together with the window's logits.  Both small: sequences of at most kWsMaxS tokens, windows that fill
+// tiles of one or two sequences.
+bool window_select_fits(const sals_ctx* ctx, const sals_ctx* win)
+{
+    return ctx->d.S_max <= kWsMaxS && (win->plan.pick == 3 || win->plan.pick == 4) && win->fuse_select &&
+           ctx->plan.n_parts + win->plan.n_parts <= ctx->L.max_parts;
+}
+template <typename T>
+sals_status launch_window_select(sals_ctx* ctx, sals_ctx* win, const void* q, const int32_t* q_pos, const void* Kw, const void* W_hi,
+                                 const float* scores, const int32_t* seq_len, int32_t* idx, int32_t* n_sel, hipStream_t st)
+{
+    const sals_desc &d = ctx->d, &e = win->d;
+    const Layout& L = win->L;
+    sals_status s = ensure_rope_table(win, st);
+    if (s == SALS_OK) s = ensure_lds_attr<T>(win);
+    if (s != SALS_OK) return s;
+    const StatsLink link = window_stats(ctx, win, true);
+    const StepSelect sel{scores, seq_len, idx, n_sel, select_blocks(d), d.B, d.S_max, d.top_k, d.n_sink, d.n_recent, window_lists(ctx, win)};
+    const float2* rope = reinterpret_cast<const float2*>(win->ws + L.rope);
+    float* logits = reinterpret_cast<float*>(win->ws + L.logits);
+    float* plogits = reinterpret_cast<float*>(win->ws + L.plogits);
+    const float scale = 1.0f / std::sqrt((float)e.d);
+    const int w = e.top_k, ks = window_select_slices(win);
+    float2* stats = link.stats + link.part0;
+    ProfScope ps(ctx, SALS_K_TOPK, st);
+    if (win->plan.pick == 4) {
+        typedef logits_cfg<1, 4, 1> LC;
+        auto kern = window_select_for<T>(e.H_q / e.H_kv);
+        static_assert(LC::NT == 256 && LC::LDS >= sizeof(TopkShared), "the selection runs in the logits kernel's workgroup");
+        hipLaunchKernelGGL(kern, dim3(sel.n_blocks + ceil_div(e.B, 2) * e.H_kv * ks), dim3(LC::NT), LC::LDS, st, sel,
+                           static_cast<const T*>(Kw), w_section<T>(win, W_hi, 2), static_cast<const T*>(q), q_pos, rope, win->inv, logits,
+                           stats, e.B, e.S_max, e.r, e.H_q, e.H_kv, w, L.lk, e.rope_style, scale, link.stride, plogits, ks);
+    } else {
+        const size_t a_bytes = (size_t)e.H_kv * kHeadDim * e.r, b_bytes = (size_t)e.B * w * e.r;
+        auto kern = WindowSelectSmall<T>::get(steps_ahead<T>(e, ks));
+        hipLaunchKernelGGL(kern, dim3(sel.n_blocks + win->plan.n_parts * e.H_kv * e.B * ks), dim3(kLsThreads), kLsLds, st, sel,
+                           w_section<T>(win, W_hi, 2), e.B, e.H_kv, win->plan.n_parts, a_bytes <= b_bytes ? 1 : 0, ks, w, e.r, e.H_q,
+                           static_cast<const T*>(Kw), static_cast<const T*>(q), q_pos, rope, win->inv, logits, stats, e.S_max, L.lk,
+                           e.rope_style, scale, plogits, link.stride);
+    }
+    return launch_status();
+}
+
+// The two logits passes.  have: what the step's selection has already done.
+enum WindowHave { kWindowNothing, kWindowLists, kWindowLogits };
+template <typename T>
+sals_status window_logits(sals_ctx* ctx, sals_ctx* win, const void* q, const int32_t* q_pos, const void* Kc, const void* W, const void* Kw,
+                          const void* W_hi, const int32_t* idx, const int32_t* n_sel, hipStream_t st, WindowHave have)
+{
+    const sals_desc& d = ctx->d;
+    const WindowLists wl = window_lists(ctx, win);
+    const int w = win->d.top_k;
+    if (ctx->plan.n_parts + win->plan.n_parts > ctx->L.max_parts) return SALS_ERR_UNSUPPORTED;
+    if (have == kWindowNothing) {
+        hipLaunchKernelGGL(window_split_kernel, dim3(d.B), dim3(256), 0, st, idx, n_sel, d.top_k + d.n_sink + d.n_recent, w, wl.idx_hi,
+                           wl.n_lo, wl.n_hi);
+        if (launch_status() != SALS_OK) return SALS_ERR_HIP;
+    }
+    const StatsLink lo = window_stats(ctx, win, false), hi = window_stats(ctx, win, true);
+    SplitLogits split{};
+    if (have == kWindowLogits) {
+        const int ks = window_select_slices(win);
+        if (ks > 1) split = split_logits(win, ks, wl.n_hi, hi.stats + hi.part0, hi.stride);
+        if (ks > 1 && ctx->plan.pick == 4) {  // (tiles of several sequences do not add up on the side)
+            hipLaunchKernelGGL(logits_finish_kernel, dim3(split.n_parts, split.rows), dim3(64), 0, st, split);
+            if (launch_status() != SALS_OK) return SALS_ERR_HIP;
+        }
+    }
+    const sals_status s = launch_attend<T>(ctx, q, q_pos, Kc, nullptr, W, idx, wl.n_lo, nullptr, st, nullptr, 0, kPhaseLogits, &lo,
+                                           nullptr, split.ksplit > 1 && ctx->plan.pick != 4 ? &split : nullptr);
+    if (s != SALS_OK || have == kWindowLogits) return s;
+    return launch_attend<T>(win, q, q_pos, Kw, nullptr, W_hi, wl.idx_hi, wl.n_hi, nullptr, st, nullptr, w, kPhaseLogits, &hi);
+}
+
+// selection of a decode step and, where they go together, the window's logits
+sals_status window_step_select(sals_ctx* ctx, sals_ctx* win, const void* q, const int32_t* q_pos, const void* Kw, const void* W_hi,
+                               const float* scores, const int32_t* seq_len, int32_t* idx, int32_t* n_sel, hipStream_t st, WindowHave* have)
+{
+    if (window_select_fits(ctx, win)) {
+        *have = kWindowLogits;
+        return ctx->d.dtype == SALS_BF16
+                   ? launch_window_select<bf16_t>(ctx, win, q, q_pos, Kw, W_hi, scores, seq_len, idx, n_sel, st)
+                   : launch_window_select<float>(ctx, win, q, q_pos, Kw, W_hi, scores, seq_len, idx, n_sel, st);
+    }
+    // the selection kernel also writes the two passes' token lists (they follow from the sequence lengths)
+    *have = kWindowLists;
+    return launch_topk(ctx, scores, seq_len, idx, n_sel, st, window_lists(ctx, win), ctx->L.tm_chunks > 0);
+}
+
 sals_status window_attend(sals_ctx* ctx, sals_ctx* win, const void* q, const int32_t* q_pos, const void* Kc,
                           const void* Vc, const void* W, const void* Kw, const void* Vw, const void* W_hi,
-                          const int32_t* idx, const int32_t* n_sel, void* out, hipStream_t st, bool lists_ready)
+                          const int32_t* idx, const int32_t* n_sel, void* out, hipStream_t st, WindowHave have)
 {
-    sals_status s = SALS_OK;
     const sals_desc& d = ctx->d;
-    const int k_tot = d.top_k + d.n_sink + d.n_recent, w = win->d.top_k;
+    const int w = win->d.top_k;
     const WindowLists wl = window_lists(ctx, win);
     int32_t* idx_hi = wl.idx_hi;
     int32_t* n_hi = wl.n_hi;
     int32_t* n_lo = wl.n_lo;
-    if (!lists_ready) {
-        hipLaunchKernelGGL(window_split_kernel, dim3(d.B), dim3(256), 0, st, idx, n_sel, k_tot, w, idx_hi, n_lo, n_hi);
-        if (launch_status() != SALS_OK) return SALS_ERR_HIP;
-    }
     // One softmax over both caches: the two logits passes leave their tile statistics side by side in the main
     // context's array, each value pass normalises with the statistics of all tiles, and one output projection adds
     // both passes' value sums through their projectors.
     const bool bf = d.dtype == SALS_BF16;
-    const LogitsPlan p_lo = ctx->plan, p_hi = win->plan;
-    if (p_lo.n_parts + p_hi.n_parts > ctx->L.max_parts) return SALS_ERR_UNSUPPORTED;
-    float2* shared = reinterpret_cast<float2*>(ctx->ws + ctx->L.stats);
-    const StatsLink l_lo{shared, p_lo.n_parts + p_hi.n_parts, 0}, l_hi{shared, p_lo.n_parts + p_hi.n_parts, p_lo.n_parts};
-    s = bf ? launch_attend<bf16_t>(ctx, q, q_pos, Kc, Vc, W, idx, n_lo, nullptr, st, nullptr, 0, kPhaseLogits, &l_lo)
-           : launch_attend<float>(ctx, q, q_pos, Kc, Vc, W, idx, n_lo, nullptr, st, nullptr, 0, kPhaseLogits, &l_lo);
+    const sals_status s = bf ? window_logits<bf16_t>(ctx, win, q, q_pos, Kc, W, Kw, W_hi, idx, n_sel, st, have)
+                             : window_logits<float>(ctx, win, q, q_pos, Kc, W, Kw, W_hi, idx, n_sel, st, have);
     if (s != SALS_OK) return s;
-    s = bf ? launch_attend<bf16_t>(win, q, q_pos, Kw, Vw, W_hi, idx_hi, n_hi, nullptr, st, nullptr, w, kPhaseLogits, &l_hi)
-           : launch_attend<float>(win, q, q_pos, Kw, Vw, W_hi, idx_hi, n_hi, nullptr, st, nullptr, w, kPhaseLogits, &l_hi);
-    if (s != SALS_OK) return s;
+    const StatsLink l_lo = window_stats(ctx, win, false);
     {
         const PvPass lo{ctx, idx, n_lo, Vc, 0}, hi{win, idx_hi, n_hi, Vw, w};
-        if (bf) launch_pv<bf16_t>(ctx, shared, l_lo.stride, lo, &hi, nullptr, st);
-        else launch_pv<float>(ctx, shared, l_lo.stride, lo, &hi, nullptr, st);
+        if (bf) launch_pv<bf16_t>(ctx, l_lo.stats, l_lo.stride, lo, &hi, nullptr, st);
+        else launch_pv<float>(ctx, l_lo.stats, l_lo.stride, lo, &hi, nullptr, st);
         if (launch_status() != SALS_OK) return SALS_ERR_HIP;
     }
     {
@@ -1312,6 +1493,8 @@ sals_status window_attend(sals_ctx* ctx, sals_ctx* win, const void* q, const int
 }
 }  // namespace
 
+extern "C" {
+
 sals_status sals_sparse_attend_window(sals_ctx* ctx, sals_ctx* win, const void* q, const int32_t* q_pos,
                                       const void* Kc, const void* Vc, const void* W, const void* Kw,
                                       const void* Vw, const void* W_hi, const int32_t* idx, const int32_t* n_sel,
@@ -1323,7 +1506,7 @@ sals_status sals_sparse_attend_window(sals_ctx* ctx, sals_ctx* win, const void* 
         bad(out))
         return SALS_ERR_INVALID_ARG;
     return window_attend(ctx, win, q, q_pos, Kc, Vc, W, Kw, Vw, W_hi, idx, n_sel, out, static_cast<hipStream_t>(hip_stream),
-                         false);
+                         kWindowNothing);
 }
 
 sals_status sals_decode_step_window(sals_ctx* ctx, sals_ctx* win, const void* q, const int32_t* q_pos,
@@ -1341,11 +1524,11 @@ sals_status sals_decode_step_window(sals_ctx* ctx, sals_ctx* win, const void* q,
     if (!n_sel) n_sel = reinterpret_cast<int32_t*>(ctx->ws + ctx->L.n_sel);
     s = step_scores(ctx, q, W, Kc, seq_len, scores, static_cast<hipStream_t>(hip_stream));
     if (s != SALS_OK) return s;
-    // the selection kernel also writes the two passes' token lists (they follow from the sequence lengths)
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    s = launch_topk(ctx, scores, seq_len, idx, n_sel, st, window_lists(ctx, win), ctx->L.tm_chunks > 0);
+    WindowHave have;
+    s = window_step_select(ctx, win, q, q_pos, Kw, W_hi, scores, seq_len, idx, n_sel, st, &have);
     if (s != SALS_OK) return s;
-    return window_attend(ctx, win, q, q_pos, Kc, Vc, W, Kw, Vw, W_hi, idx, n_sel, out, st, true);
+    return window_attend(ctx, win, q, q_pos, Kc, Vc, W, Kw, Vw, W_hi, idx, n_sel, out, st, have);
 }
 
 // ---- recent window of the quantised value path: keys in the rank-r_hi ring, values as 8-bit codes ----
@@ -1368,29 +1551,18 @@ namespace {
 sals_status window_attend_qv(sals_ctx* ctx, sals_ctx* win, const void* q, const int32_t* q_pos, const void* Kc,
                              const void* Vq, const void* Vmeta, int bits, const void* W, const void* Kw, const void* Vqw,
                              const void* Vmeta_w, const void* W_hi, const int32_t* idx, const int32_t* n_sel, void* out,
-                             hipStream_t st, bool lists_ready)
+                             hipStream_t st, WindowHave have)
 {
     const sals_desc& d = ctx->d;
-    const int k_tot = d.top_k + d.n_sink + d.n_recent, w = win->d.top_k;
+    const int w = win->d.top_k;
     const WindowLists wl = window_lists(ctx, win);
-    if (!lists_ready) {
-        hipLaunchKernelGGL(window_split_kernel, dim3(d.B), dim3(256), 0, st, idx, n_sel, k_tot, w, wl.idx_hi, wl.n_lo, wl.n_hi);
-        if (launch_status() != SALS_OK) return SALS_ERR_HIP;
-    }
     // two logits passes (low-rank cache, ring) with their tile statistics side by side, then one pass over the values
     // of the whole selection: the tokens before the window from the low-bit cache, the window's from its 8-bit ring
     const bool bf = d.dtype == SALS_BF16;
-    const LogitsPlan p_lo = ctx->plan, p_hi = win->plan;
-    if (p_lo.n_parts + p_hi.n_parts > ctx->L.max_parts) return SALS_ERR_UNSUPPORTED;
-    float2* shared = reinterpret_cast<float2*>(ctx->ws + ctx->L.stats);
-    const int n_all = p_lo.n_parts + p_hi.n_parts;
-    const StatsLink l_lo{shared, n_all, 0}, l_hi{shared, n_all, p_lo.n_parts};
-    sals_status s = bf ? launch_attend<bf16_t>(ctx, q, q_pos, Kc, nullptr, W, idx, wl.n_lo, nullptr, st, nullptr, 0, kPhaseLogits, &l_lo)
-                       : launch_attend<float>(ctx, q, q_pos, Kc, nullptr, W, idx, wl.n_lo, nullptr, st, nullptr, 0, kPhaseLogits, &l_lo);
+    const sals_status s = bf ? window_logits<bf16_t>(ctx, win, q, q_pos, Kc, W, Kw, W_hi, idx, n_sel, st, have)
+                             : window_logits<float>(ctx, win, q, q_pos, Kc, W, Kw, W_hi, idx, n_sel, st, have);
     if (s != SALS_OK) return s;
-    s = bf ? launch_attend<bf16_t>(win, q, q_pos, Kw, nullptr, W_hi, wl.idx_hi, wl.n_hi, nullptr, st, nullptr, w, kPhaseLogits, &l_hi)
-           : launch_attend<float>(win, q, q_pos, Kw, nullptr, W_hi, wl.idx_hi, wl.n_hi, nullptr, st, nullptr, w, kPhaseLogits, &l_hi);
-    if (s != SALS_OK) return s;
+    const StatsLink l_lo = window_stats(ctx, win, false);
     QvCache qv{Vq, Vmeta, bits};
     qv.codes_w = Vqw; qv.meta_w = Vmeta_w;
     qv.logits_w = reinterpret_cast<const float*>(win->ws + win->L.logits);
@@ -1412,7 +1584,7 @@ sals_status sals_sparse_attend_qv_window(sals_ctx* ctx, sals_ctx* win, const voi
         return SALS_ERR_INVALID_ARG;
     if (bits != 2 && bits != 4) return SALS_ERR_UNSUPPORTED;
     return window_attend_qv(ctx, win, q, q_pos, Kc, Vq, Vmeta, bits, W, Kw, Vqw, Vmeta_w, W_hi, idx, n_sel, out,
-                            static_cast<hipStream_t>(hip_stream), false);
+                            static_cast<hipStream_t>(hip_stream), kWindowNothing);
 }
 
 sals_status sals_decode_step_qv_window(sals_ctx* ctx, sals_ctx* win, const void* q, const int32_t* q_pos,
@@ -1434,9 +1606,10 @@ sals_status sals_decode_step_qv_window(sals_ctx* ctx, sals_ctx* win, const void*
     s = step_scores(ctx, q, W, Kc, seq_len, scores, static_cast<hipStream_t>(hip_stream));
     if (s != SALS_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    s = launch_topk(ctx, scores, seq_len, idx, n_sel, st, window_lists(ctx, win), ctx->L.tm_chunks > 0);
+    WindowHave have;
+    s = window_step_select(ctx, win, q, q_pos, Kw, W_hi, scores, seq_len, idx, n_sel, st, &have);
     if (s != SALS_OK) return s;
-    return window_attend_qv(ctx, win, q, q_pos, Kc, Vq, Vmeta, bits, W, Kw, Vqw, Vmeta_w, W_hi, idx, n_sel, out, st, true);
+    return window_attend_qv(ctx, win, q, q_pos, Kc, Vq, Vmeta, bits, W, Kw, Vqw, Vmeta_w, W_hi, idx, n_sel, out, st, have);
 }
 
 // ---- overlap score ----------------------------------------------------------------------------------

@@ -117,6 +117,16 @@ def test_shared_tiles_gqa_interleaved_rope_ring_wrap(oracle, monkeypatch):
     _case(oracle, w, seq_lens=[777, 500, 48, 49, 47, 0, 600, 100, 776])
 
 
+@pytest.mark.parametrize("S,B,tiles", [(4099, 3, "3"), (8192, 3, "3"), (8200, 3, "3"), (5001, 5, "4"), (8192, 3, "4")])
+def test_selection_and_window_logits_in_one_launch(oracle, S, B, tiles, monkeypatch):
+    """Both sides of the sequence lengths at which the selection has one more group of keys per thread (4096) and a launch of its
+    own (8192), rows of the score array that start unaligned, both tile forms of the window: the step against the oracle and
+    against the staged call, whose passes are launches of their own."""
+    monkeypatch.setenv("SALS_TUNE_LOGITS", tiles)
+    w = synth.shrink(SMALL, B=B, S=S, H=4, H_kv=4, r=64, r_hi=128, top_k=150, plant=2)
+    _case(oracle, w, seq_lens=[S, S - 1, 4000, 4097, 70][:B])
+
+
 def test_largest_window_rank(oracle):
     w = synth.shrink(SMALL, B=2, S=600, r=640, r_hi=2048, top_k=200, n_sink=16, n_recent=128, plant=0)
     _case(oracle, w, seq_lens=[600, 345])
