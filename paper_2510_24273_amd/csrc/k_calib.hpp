@@ -309,66 +309,116 @@ __device__ __forceinline__ void calib_pair(int n, int s, int k, int* p, int* q)
 // tokens than channels is by its fp32 sums) sets `fail` and the host starts again with 64 times the shift.
 constexpr int kCalPanel = 64;
 
-// Panel at row k0: every workgroup factors the 64 x 64 diagonal block by itself (a row of it per four threads, the pivot
-// row passed through LDS, one barrier per pivot: 64 dependent steps are what the kernel takes, so repeating them beats
-// another launch) and then carries 64 columns of the panel through the triangular solve, one column per thread of its first
-// wave (with a column on every thread the four waves' broadcast reads of the factor are bound by the LDS).  The
-// factored block goes to `diag` (other workgroups still read the original).  grid max(1, (D - k0 - 64) / 64).
-__global__ __launch_bounds__(256) void calib_chol_panel_kernel(double* __restrict__ G, int D, int k0, double shift,
-                                                               double* __restrict__ diag, int* __restrict__ fail)
-{
-    __shared__ double row[2][kCalPanel];
-    __shared__ double Rk[kCalPanel][kCalPanel + 1];
-    __shared__ double invd[kCalPanel];
-    const int tid = threadIdx.x, i = tid >> 2, j0 = (tid & 3) * 16;
-    const int c = k0 + kCalPanel + blockIdx.x * 64 + tid;
-    double a[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) a[e] = G[(size_t)(k0 + i) * D + k0 + j0 + e] + (j0 + e == i ? shift : 0.0);
-    double pv_i = 0.0;
-    for (int k = 0; k < kCalPanel; ++k) {
-        double* rk = row[k & 1];
-        if (i == k) {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) rk[j0 + e] = a[e];
-        }
-        __syncthreads();
-        const double pv = rk[k];
-        if (i == k) pv_i = pv;
-        if (i > k) {
-            const double f = pv > 0.0 ? rk[i] / pv : 0.0;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) a[e] -= f * rk[j0 + e];
-        }
-    }
-    const double inv = pv_i > 0.0 ? rsqrt(pv_i) : 0.0;
-    if (!(pv_i > 0.0) && blockIdx.x == 0) *fail = 1;
-    if ((tid & 3) == 0) invd[i] = inv;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        a[e] = j0 + e >= i ? a[e] * inv : 0.0;
-        Rk[i][j0 + e] = a[e];
-        if (blockIdx.x == 0) diag[(size_t)(k0 + i) * kCalPanel + j0 + e] = a[e];
-    }
-    __syncthreads();
-    if (tid >= 64 || c >= D) return;
-    // forward substitution R_kk^T x = a, the column's values in registers
-    double x[kCalPanel];
-#pragma unroll
-    for (int k = 0; k < kCalPanel; ++k) x[k] = G[(size_t)(k0 + k) * D + c];
-#pragma unroll
-    for (int k = 0; k < kCalPanel; ++k) {
-        x[k] *= invd[k];
-#pragma unroll
-        for (int m = k + 1; m < kCalPanel; ++m) x[m] -= Rk[k][m] * x[k];
-    }
-#pragma unroll
-    for (int k = 0; k < kCalPanel; ++k) G[(size_t)(k0 + k) * D + c] = x[k];
-}
-
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 // v_mfma_f64_16x16x4: lane holds A[l % 16][l / 16] and B[l / 16][l % 16]; result element i is row l / 16 + 4 i, column l % 16
 __device__ __forceinline__ f64x4 mma_f64(double a, double b, f64x4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+
+// 1 / sqrt(x) for normal x: the hardware's estimate and one third-order step (full precision)
+__device__ __forceinline__ double rsqrt_f64(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x), e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+// Panel at row k0: every workgroup factors the 64 x 64 diagonal block by itself (repeating it beats another launch) and carries
+// 64 columns of the panel along, all in LDS, 16 rows at a time: one wave factors the 16 x 16 diagonal block in registers (a
+// column per lane, the pivot row passed through scalar registers), two waves carry the columns behind it through the
+// triangular solve (a column per thread), and the matrix cores take the 16 rows out of those below.  Bound by the 64 dependent
+// pivots.  20 us at D = 1024; one pivot at a time over the whole block (a barrier and a division each) and a solve of 64 unrolled
+// steps per column took 62.
+// The factored block goes to `diag` (other workgroups still read the original).  grid max(1, (D - k0 - 64) / 64).
+constexpr int kCholLd = 2 * kCalPanel + 2;   // row pitch: the diagonal block's columns, then the workgroup's 64 columns
+__global__ __launch_bounds__(256) void calib_chol_panel_kernel(double* __restrict__ G, int D, int k0, double shift,
+                                                               double* __restrict__ diag, int* __restrict__ fail)
+{
+    __shared__ double M[kCalPanel * kCholLd];
+    __shared__ double invd[kCalPanel];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, kg = lane >> 4;
+    const int c0 = k0 + kCalPanel + blockIdx.x * 64;
+    const bool panel = c0 < D;   // uniform
+    {   // (all loads requested together)
+        double v[2][16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const double* row = G + (size_t)(k0 + u * 4 + wave) * D + lane;
+            v[0][u] = row[k0];
+            v[1][u] = panel ? row[c0] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const int i = u * 4 + wave;
+            M[i * kCholLd + lane] = v[0][u] + (i == lane ? shift : 0.0);
+            M[i * kCholLd + kCalPanel + lane] = v[1][u];
+        }
+    }
+    bool good = true;
+    __syncthreads();
+#pragma unroll 1
+    for (int b = 0; b < kCalPanel; b += 16) {
+        if (wave == 0) {
+            double a[16];   // column l16 of the block
+#pragma unroll
+            for (int r = 0; r < 16; ++r) a[r] = M[(b + r) * kCholLd + b + l16];
+            auto lane_value = [](double x, int from) {
+                const int2 u = __builtin_bit_cast(int2, x);
+                return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(u.x, from), __builtin_amdgcn_readlane(u.y, from)));
+            };
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const double pv = lane_value(a[k], k);
+                good &= pv > 0.0;
+                const double inv = pv > 0.0 ? rsqrt_f64(pv) : 0.0;
+                a[k] *= inv;                                  // row k of the factor
+                if (lane == 0) invd[b + k] = inv;
+#pragma unroll
+                for (int r = k + 1; r < 16; ++r) a[r] -= lane_value(a[k], r) * a[k];
+            }
+            if (kg == 0) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) M[(b + r) * kCholLd + b + l16] = l16 >= r ? a[r] : 0.0;
+            }
+        }
+        __syncthreads();
+        if (wave < 2 && tid >= b + 16) {   // column tid: forward substitution R_bb^T x = a
+            double x[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) x[r] = M[(b + r) * kCholLd + tid];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                x[k] *= invd[b + k];
+#pragma unroll
+                for (int m = k + 1; m < 16; ++m) x[m] -= M[(b + k) * kCholLd + b + m] * x[k];
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) M[(b + r) * kCholLd + tid] = x[r];
+        }
+        __syncthreads();
+        // tiles (row block i, column block j >= i) behind the 16 rows, dealt to the waves
+        int t = 0;
+#pragma unroll 1
+        for (int i = b + 16; i < kCalPanel; i += 16)
+#pragma unroll 1
+            for (int j = i; j < (panel ? 2 : 1) * kCalPanel; j += 16, ++t) {
+                if ((t & 3) != wave) continue;   // uniform
+                f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const double* r = M + (b + 4 * s + kg) * kCholLd + l16;
+                    acc = mma_f64(r[i], r[j], acc);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) M[(i + kg + 4 * e) * kCholLd + j + l16] -= acc[e];
+            }
+        __syncthreads();
+    }
+    if (!good && lane == 0 && wave == 0 && blockIdx.x == 0) *fail = 1;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        const int i = u * 4 + wave;
+        if (blockIdx.x == 0) diag[(size_t)(k0 + i) * kCalPanel + lane] = lane >= i ? M[i * kCholLd + lane] : 0.0;
+        if (panel) G[(size_t)(k0 + i) * D + c0 + lane] = M[i * kCholLd + kCalPanel + lane];
+    }
+}
 
 // Trailing update behind the panel at k0: A[i, j] -= sum_k R[k, i] R[k, j] over the panel's 64 rows, 64 x 64 tiles that
 // reach the upper triangle.  grid (tiles, tiles)
@@ -514,12 +564,6 @@ __global__ __launch_bounds__(256) void calib_jacobi_gram_kernel(const double* __
     jac_gram_store(acc, red, part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kJacBigRec + (half ? NT * kJacTile : 0));
 }
 
-// 1 / sqrt(x) for normal x: the hardware's estimate and one third-order step (full precision)
-__device__ __forceinline__ double jac_rsqrt(double x)
-{
-    const double y = __builtin_amdgcn_rsq(x), e = fma(-x * y, y, 1.0);
-    return fma(y * e, fma(e, 0.375, 0.5), y);
-}
 // cosine and sine of the rotation (g_p, g_q) -> (c g_p - s g_q, s g_p + c g_q) that makes two rows with squared norms aa,
 // bb and inner product ab orthogonal, by the smaller angle: with h = sqrt((bb-aa)^2 + 4 ab^2) the double angle has
 // cosine |bb-aa| / h and sine 2 |ab| / h, so two reciprocal square roots do.  Rows orthogonal to working precision are left
@@ -530,8 +574,8 @@ __device__ __forceinline__ void jac_rotation(double aa, double bb, double ab, do
 {
     const bool ok = jac_open(aa, bb, ab);
     // (the smallest normal number keeps two zero rows finite)
-    const double d = bb - aa, hi = jac_rsqrt(fma(4.0 * ab, ab, fma(d, d, 2.2250738585072014e-308)));
-    const double c2 = fma(0.5 * fabs(d), hi, 0.5), ci = jac_rsqrt(c2);
+    const double d = bb - aa, hi = rsqrt_f64(fma(4.0 * ab, ab, fma(d, d, 2.2250738585072014e-308)));
+    const double c2 = fma(0.5 * fabs(d), hi, 0.5), ci = rsqrt_f64(c2);
     uint2 ab_d = __builtin_bit_cast(uint2, ab);     // ab with its sign turned by d's
     ab_d.y ^= __builtin_bit_cast(uint2, d).y & 0x80000000u;
     *c = ok ? c2 * ci : 1.0;
