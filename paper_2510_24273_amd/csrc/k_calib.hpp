@@ -1027,26 +1027,36 @@ __global__ __launch_bounds__(kCalThreads) void calib_rownorm_kernel(const double
     }
 }
 
-// What the sweeps have left: *worst = the largest angle |ab| / |bb - aa| (first order; at most 1/2) between two rows that are
-// not orthogonal to working precision and of which one has a squared norm >= lead, what a further sweep would turn them by.
-// norm: the rows' norms.  64 x 64 tiles of the upper triangle of G G^T, a quarter per wave, operands straight from memory.
-// At D = 1024 61 us against the 0.8 ms of a sweep that is run only to find that nothing was left to rotate: a call takes 10.9 ms
-// instead of 11.5 (r = 640).
-__global__ __launch_bounds__(256) void calib_jacobi_check_kernel(const double* __restrict__ G, int D, const double* __restrict__ norm,
-                                                                 double lead, double* __restrict__ worst)
+// ---- The last angles -------------------------------------------------------------------------------------------------
+// Convergence is quadratic: behind a sweep whose rotations were at most a few tenths, all angles t_pq = <p, q> / (|q|^2 -
+// |p|^2) between rows are small, and all rotations can be made at once: with E_pq = -t_pq = -E_qp, the rows of exp(E) G are
+// orthogonal up to the square of the angles.  The series is cut behind E^2 or E^4, which leaves a factor that differs from an
+// orthogonal one by |E|^4 / 4 or |E|^6 / 72; the host uses it where that is below the rounding of the sums (Frobenius norm at most
+// 2e-4, or 4e-3).  At D = 1024 a product takes 52 us and the angles 63, a sweep 780: the last one to three of 11 to 13 sweeps are
+// replaced (a call 10.3 to 11.2 ms -> 9.6 to 9.9; D = 4096: 146 -> 140).
+//
+// 64 x 64 tiles of G G^T (upper triangle): E, and per tile {largest |t| (at most 1/2), sum of t^2}, both over pairs that are not
+// orthogonal to working precision and of which one row has a squared norm >= lead; where both have, their cosine counts as
+// well as t (beside a far larger row, t is small long before the smaller row's direction is right).  norm: the rows' norms.
+// Eight waves: (half of the columns) x (quarter of the tile), operands straight from memory.
+__global__ __launch_bounds__(512) void calib_jacobi_angles_kernel(const double* __restrict__ G, int D, const double* __restrict__ norm,
+                                                                  double lead, double* __restrict__ E, f64x2* __restrict__ found)
 {
+    __shared__ double red[4][32 * 33];
+    __shared__ f64x2 s_found[4];
     int tr, tc;
     cov_tile(blockIdx.x, D / 64, &tr, &tc);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kg = lane >> 4;
-    const int r0 = tr * 64 + (wave >> 1) * 32, c0 = tc * 64 + (wave & 1) * 32;
-    const double* ga = G + (size_t)(r0 + l16) * D + kg * 4;
-    const double* gb = G + (size_t)(c0 + l16) * D + kg * 4;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kg = lane >> 4;
+    const int part = wave & 3;
+    const int r0 = tr * 64 + (part >> 1) * 32, c0 = tc * 64 + (part & 1) * 32;
+    const double* ga = G + (size_t)(r0 + l16) * D + (wave >> 2) * (D / 2) + kg * 4;
+    const double* gb = G + (size_t)(c0 + l16) * D + (wave >> 2) * (D / 2) + kg * 4;
     f64x4 acc[2][2];
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
         for (int v = 0; v < 2; ++v) acc[u][v] = f64x4{0.0, 0.0, 0.0, 0.0};
-    for (int c = 0; c < D; c += 32) {  // two groups of 16 columns requested together
+    for (int c = 0; c < D / 2; c += 32) {  // two groups of 16 columns requested together
         f64x4 a[2][2], b[2][2];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
@@ -1064,20 +1074,110 @@ __global__ __launch_bounds__(256) void calib_jacobi_check_kernel(const double* _
 #pragma unroll
                     for (int v = 0; v < 2; ++v) acc[u][v] = mma_f64(a[h][u][e], b[h][v][e], acc[u][v]);
     }
-    double most = 0.0;
+    auto at = [&](int u, int v, int e) { return (u * 16 + kg + 4 * e) * 33 + v * 16 + l16; };
+    double* const t = red[part];
+    if (wave >= 4) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) t[at(u, v, e)] = acc[u][v][e];
+    }
+    __syncthreads();
+    if (wave < 4) {
+        double most = 0.0, sum = 0.0;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = r0 + u * 16 + kg + 4 * e, c = c0 + v * 16 + l16;
+                    const double nr = norm[r], nc = norm[c], aa = nr * nr, bb = nc * nc, ab = acc[u][v][e] + t[at(u, v, e)], d = bb - aa;
+                    const bool counts = r != c && fmax(aa, bb) >= lead && jac_open(aa, bb, ab);
+                    const double th = counts ? ab / d : 0.0;
+                    if (counts && r < c) {
+                        most = fmax(most, fabs(ab) / fmax(fabs(d), 2.0 * fabs(ab)));
+                        if (fmin(aa, bb) >= lead) most = fmax(most, fabs(ab) / (nr * nc));
+                        sum += th * th;
+                    }
+                    E[(size_t)r * D + c] = -th;
+                    t[at(u, v, e)] = th;
+                }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) { most = fmax(most, __shfl_xor(most, o, kWave)); sum += __shfl_xor(sum, o, kWave); }
+        if (lane == 0) s_found[part] = f64x2{most, sum};
+        if (tr != tc) {  // uniform: the other triangle (this wave's own piece of LDS)
+            const int l32 = lane & 31;
+            for (int k = lane >> 5; k < 32; k += 2) E[(size_t)(c0 + k) * D + r0 + l32] = t[l32 * 33 + k];
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        found[blockIdx.x] = f64x2{fmax(fmax(s_found[0].x, s_found[1].x), fmax(s_found[2].x, s_found[3].x)),
+                                  (s_found[0].y + s_found[1].y) + (s_found[2].y + s_found[3].y)};
+}
+
+// Y = G + f E X (Y may be G, X may not).  64 x 64 tiles, eight waves as above; grid (D / 64, D / 64).
+__global__ __launch_bounds__(512) void calib_jacobi_apply_kernel(const double* __restrict__ E, const double* __restrict__ X, const double* G,
+                                                                 double f, double* Y, int D)
+{
+    __shared__ double red[4][16 * 64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kg = lane >> 4;
+    const int part = wave & 3, k0 = (wave >> 2) * (D / 2);
+    const int r0 = blockIdx.y * 64 + (part >> 1) * 32, c0 = blockIdx.x * 64 + (part & 1) * 32;
+    const double* ea = E + (size_t)(r0 + l16) * D + k0 + kg * 4;
+    const double* xb = X + (size_t)(k0 + kg * 4) * D + c0 + l16;
+    f64x4 acc[2][2];
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int v = 0; v < 2; ++v)
+        for (int v = 0; v < 2; ++v) acc[u][v] = f64x4{0.0, 0.0, 0.0, 0.0};
+    struct Terms { f64x4 a[2][2]; double b[2][2][4]; } now, next;   // 32 terms; lane: k + 4 kg .. + 4 of either operand
+    auto load = [&](Terms& x, int k) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int r = r0 + u * 16 + kg + 4 * e, c = c0 + v * 16 + l16;
-                const double nr = norm[r], nc = norm[c], aa = nr * nr, bb = nc * nc, ab = fabs(acc[u][v][e]);
-                if (r < c && fmax(aa, bb) >= lead && jac_open(aa, bb, ab)) most = fmax(most, ab / fmax(fabs(bb - aa), 2.0 * ab));
-            }
+        for (int h = 0; h < 2; ++h) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) most = fmax(most, __shfl_xor(most, o, kWave));
-    if (lane == 0 && most > 0.0) conv_max(worst, most);
+            for (int u = 0; u < 2; ++u) x.a[h][u] = *reinterpret_cast<const f64x4*>(ea + (size_t)(16 * u) * D + k + 16 * h);
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x.b[h][v][e] = xb[(size_t)(k + 16 * h + e) * D + 16 * v];
+        }
+    };
+    auto multiply = [&](const Terms& x) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int v = 0; v < 2; ++v) acc[u][v] = mma_f64(x.a[h][u][e], x.b[h][v][e], acc[u][v]);
+    };
+    load(now, 0);
+    for (int k = 0; k < D / 2; k += 64) {  // (the next terms on their way; past the end: the last ones again)
+        load(next, k + 32);
+        asm volatile("" ::: "memory");  // (keeps the loads here)
+        multiply(now);
+        load(now, min(k + 64, D / 2 - 32));
+        asm volatile("" ::: "memory");
+        multiply(next);
+    }
+    if (wave >= 4) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) red[part][i * 64 + lane] = acc[i >> 3][(i >> 2) & 1][i & 3];
+    }
+    __syncthreads();
+    if (wave < 4) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int u = i >> 3, v = (i >> 2) & 1, e = i & 3;
+            const size_t at = (size_t)(r0 + u * 16 + kg + 4 * e) * D + c0 + v * 16 + l16;
+            Y[at] = fma(f, acc[u][v][e] + red[part][i * 64 + lane], G[at]);
+        }
+    }
 }
 
 // Row i of G takes rank = number of rows with a larger norm (equal ones by row index); eigval[rank] = lambda_i and, for

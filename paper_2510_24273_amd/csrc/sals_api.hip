@@ -4,6 +4,7 @@
 #include "../../include/sals.h"
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -1800,7 +1801,7 @@ int jac_slices(int D)
     return s;
 }
 struct EigWs {  // byte offsets into the workspace
-    size_t G, conv, norm, sgn, diag, part, total;
+    size_t G, conv, norm, sgn, diag, part, E, Y, total;
 };
 EigWs eig_ws(int D)
 {
@@ -1814,6 +1815,8 @@ EigWs eig_ws(int D)
     w.diag = take((size_t)D * kCalPanel * 8);    // factored diagonal blocks
     // partial Gram matrices of a step: of the blocks, or of pairs of them
     w.part = take((size_t)jac_gram_slices(D) * (D / kJacBig) * std::max(kJacRec, kJacBigRec / 2) * 8);
+    w.E = take((size_t)D * D * 8);               // the last angles between the rows
+    w.Y = take((size_t)D * D * 8);               // a partial sum of their series
     w.total = o;
     return w;
 }
@@ -1842,7 +1845,10 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     int* fail = reinterpret_cast<int*>(ws + off.conv);
     const int n_blocks = D / kJacBig, n_pairs = n_blocks / 2, n_steps = n_blocks - 1;
     const int n_part = jac_gram_slices(D), slices = jac_slices(D);
+    const int n_tiles = D / 64 * (D / 64 + 1) / 2;   // of the angles, which lie where the partial Gram matrices do
+    f64x2* const found = reinterpret_cast<f64x2*>(part);
     std::vector<double> h_conv((size_t)n_blocks), h_norm((size_t)D);
+    std::vector<std::array<double, 2>> h_found((size_t)n_tiles);
     auto row_norms = [&](const double* M) -> bool {  // row norms to the host (blocking)
         hipLaunchKernelGGL(calib_rownorm_kernel, dim3(D), dim3(kCalThreads), 0, st, M, D, norm, sgn);
         return hipMemcpyAsync(h_norm.data(), norm, (size_t)D * 8, hipMemcpyDeviceToHost, st) == hipSuccess &&
@@ -1897,19 +1903,35 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         ++done;
         // a rotation by less than 1e-11 no longer moves an eigenvector; only pairs with a row among the r largest
         // (a little below the r-th largest norm, so that the r-th itself is in) are asked to have converged
+        auto leading = [&]() {
+            std::nth_element(h_norm.begin(), h_norm.begin() + (r - 1), h_norm.end(), std::greater<double>());
+            const double nr = h_norm[(size_t)r - 1];
+            return 0.999 * nr * nr;
+        };
         converged = worst <= 1e-11;
-        std::nth_element(h_norm.begin(), h_norm.begin() + (r - 1), h_norm.end(), std::greater<double>());
-        const double nr = h_norm[(size_t)r - 1];
-        lead = 0.999 * nr * nr;
-        // Convergence is quadratic: a sweep of small rotations leaves none.  The angles that are left tell (where the sweep's
-        // largest was 1e-5 they are about 1e-12; above 1e-4 a further sweep is due anyway).
-        if (!converged && worst <= 1e-4) {
-            if (hipMemsetAsync(conv, 0, 8, st) != hipSuccess) return SALS_ERR_HIP;
-            hipLaunchKernelGGL(calib_jacobi_check_kernel, dim3(D / 64 * (D / 64 + 1) / 2), dim3(256), 0, st, G, D, norm, lead, conv);
-            if (launch_status() != SALS_OK || hipMemcpyAsync(h_conv.data(), conv, 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
+        lead = leading();
+        // Behind a sweep of small rotations the angles that are left decide: converged, or all of them at once, or a further sweep.
+        // (Sweeps whose largest rotation was 0.26, 0.07, 0.007 left 4e-5, 1e-3, 4e-6.)
+        for (int pass = 0; !converged && worst <= 0.3 && pass < 4; ++pass) {
+            hipLaunchKernelGGL(calib_jacobi_angles_kernel, dim3(n_tiles), dim3(512), 0, st, G, D, norm, lead, at(off.E), found);
+            if (launch_status() != SALS_OK ||
+                hipMemcpyAsync(h_found.data(), found, h_found.size() * sizeof(h_found[0]), hipMemcpyDeviceToHost, st) != hipSuccess ||
                 hipStreamSynchronize(st) != hipSuccess)
                 return SALS_ERR_HIP;
-            converged = h_conv[0] <= 1e-11;
+            double most = 0.0, square = 0.0;
+            for (const auto& f : h_found) { most = std::max(most, f[0]); square += f[1]; }
+            converged = most <= 1e-11;
+            if (converged || !(square <= 1.6e-5)) break;
+            // exp(E) G from the inside out: G + E (G + E/2 (G + E/3 (G + E/4 G))); C is free until its rows are written
+            double *X = G, *Y = C;
+            for (int k = square <= 4e-8 ? 2 : 4; k >= 1; --k) {
+                if (k == 1) Y = G;
+                hipLaunchKernelGGL(calib_jacobi_apply_kernel, dim3(D / 64, D / 64), dim3(512), 0, st, at(off.E), X, G, 1.0 / k, Y, D);
+                X = Y;
+                Y = X == C ? at(off.Y) : C;
+            }
+            if (!row_norms(G)) return SALS_ERR_HIP;
+            lead = leading();
         }
     }
     // A matrix whose factor needed no rotation is diagonal (R R^T is diagonal for an upper triangular R only if R is): its

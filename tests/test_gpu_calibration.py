@@ -131,6 +131,30 @@ def test_eigenvectors_at_widths_of_uneven_column_slices(D, r):
     np.testing.assert_allclose(U.T @ U, np.eye(r), atol=5e-7)
 
 
+@pytest.mark.parametrize("D,r,decay", [(256, 256, 0.5), (512, 200, 1.0), (768, 768, 0.25)])
+def test_rows_left_behind_are_orthogonal_in_fp64(D, r, decay):
+    """What the call leaves in C, eigenvalue times eigenvector by row, before the vectors are rounded to their storage type:
+    orthogonal and solving the defining equation to fp64, also where the last rotations are made all at once (flat spectra, whose
+    smallest gaps keep the angles large for long)."""
+    print(f"[case] eigenvector rows in fp64, D={D} r={r}", flush=True)
+    rng = np.random.default_rng(2 * D)
+    X = rng.standard_normal((4 * D, D)) * np.arange(1, D + 1) ** -decay
+    C = X.T @ X
+    C = 0.5 * (C + C.T)
+    Cg = gu.to_dev(C)
+    lam, U, sweeps = binding.calib_eigenvectors(Cg, r, torch.float32)
+    torch.cuda.synchronize()
+    assert 0 < sweeps <= 30, sweeps
+    rows = Cg.cpu().numpy()
+    norm = np.linalg.norm(rows, axis=1)
+    lead = np.argsort(-norm)[:r]
+    V = rows[lead] / norm[lead, None]
+    # sums of D products: a few 1e-16 sqrt(D), and the angles the call may leave (1e-11)
+    assert np.max(np.abs(V @ V.T - np.eye(r))) <= 2e-11
+    assert np.max(np.linalg.norm(V @ C - norm[lead, None] * V, axis=1)) <= 2e-11 * norm[lead[0]]
+    np.testing.assert_allclose(norm[lead], lam.cpu().numpy()[:r], rtol=1e-13)
+
+
 def test_eigenvectors_in_bf16_are_the_rounded_fp64_vectors():
     print("[case] eigenvectors bf16", flush=True)
     D, r = 256, 32
