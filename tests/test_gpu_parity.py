@@ -561,3 +561,31 @@ def test_unprepared_context_fills_its_table_lazily_and_refuses_capture(oracle):
     assert torch.equal(o3.view(torch.int16), want["out"].view(torch.int16))
     lib.sals_destroy(h)
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype,H_kv,r,S,top_k,lens", [
+    ("f32", 8, 256, 1000, 100, [1000, 63]), ("f32", 32, 512, 4096, 130, [4093]), ("bf16", 8, 512, 2048, 500, [2048]),
+    ("bf16", 8, 256, 4096, 1000, [4001]), ("bf16", 4, 128, 4, 3, [4, 0])])
+def test_selection_inside_split_logits(dtype, H_kv, r, S, top_k, lens, monkeypatch):
+    """Few tiles, whose latent axis is split over workgroups that each select by themselves: list, count and output equal those of
+    the step with a selection launch, bit for bit (empty tiles and sequences, one tile, a list of the largest length)."""
+    print(f"[case] selection in split logits {dtype} H_kv={H_kv} r={r} S={S} k={top_k}", flush=True)
+    w = synth.shrink(synth.CONFIGS["cfg2"], B=len(lens), S=S, H=32, H_kv=H_kv, r=r, top_k=top_k, n_layers=1, dtype=dtype, plant=0)
+    L = synth.make_layer(w, 0, lens)
+    got = []
+    for fuse in ("1", "0"):
+        monkeypatch.setenv("SALS_TUNE_FUSE_SELECT", fuse)
+        ctx = gu.make_ctx(w)
+        G = gu.upload(L, ctx)
+        out = torch.empty((w.B, w.H, w.d), dtype=gu.out_dtype(w), device=gu.DEV)
+        idx = torch.full((w.B, w.k_tot), -7, dtype=torch.int32, device=gu.DEV)
+        n_sel = torch.full((w.B,), -7, dtype=torch.int32, device=gu.DEV)
+        ctx.decode_step(G["q"], G["q_pos"], G["Kc"], G["Vc"], G["W"], G["seq_len"], out, None, idx, n_sel)
+        torch.cuda.synchronize()
+        got.append((gu.from_dev(out), idx.cpu().numpy(), n_sel.cpu().numpy()))
+        ctx.close()
+    (o1, i1, n1), (o0, i0, n0) = got
+    assert np.array_equal(n1, n0) and n0.tolist() == [min(s, w.k_tot) for s in lens]
+    for b in range(w.B):
+        assert np.array_equal(i1[b, : n1[b]], i0[b, : n0[b]])
+    assert np.array_equal(o1, o0)
