@@ -29,6 +29,7 @@
 #include "common.hpp"
 #include "k_attend.hpp"
 #include "k_gemm.hpp"
+#include "k_topk_multi.hpp"
 
 namespace sals {
 
@@ -69,14 +70,16 @@ template <int HEADS, int NTG, int NB> struct logits_cfg {
 // logits go to `plogits` for logits_finish_kernel.
 // BYLEN (MULTI only): the selections are recent windows given by the sequence lengths (`win`; idx and n_sel are not read).
 // SIDE: `split` names the logits of another pass whose slices are still to be added up, on the side (one job per wave).
-template <typename T, int HEADS, int NTG, int NB, int GB, int GFIX, bool MULTI, bool BYLEN, bool SIDE>
+// RESOLVE: the selection's threshold bin is still to be ranked (`res`): by every workgroup whose tile reaches those entries, those
+// of the first heads leave them in the list.
+template <typename T, int HEADS, int NTG, int NB, int GB, int GFIX, bool MULTI, bool BYLEN, bool SIDE, bool RESOLVE>
 __device__ __forceinline__ void logits_tile(
     int block, const T* __restrict__ Kc, const T* __restrict__ UkP, const int32_t* __restrict__ idx,
     const int32_t* __restrict__ n_sel, const T* __restrict__ q, const int32_t* __restrict__ q_pos,
     const float2* __restrict__ rope, const InvFreq& inv,
     float* __restrict__ logits, float2* __restrict__ stats, int B, int S_max, int r, int H, int H_kv,
     int k_tot, int lk, int n_parts, int heads_fastest, int style, float scale, int ring, int stats_stride,
-    float* __restrict__ plogits, int ksplit, const WindowByLength& win, const SplitLogits& split)
+    float* __restrict__ plogits, int ksplit, const WindowByLength& win, const SplitLogits& split, const TopkResolve& res)
 {
     typedef logits_cfg<HEADS, NTG, NB> C;
     static_assert(!BYLEN || MULTI, "a window by length fills tiles of several sequences");
@@ -131,6 +134,19 @@ __device__ __forceinline__ void logits_tile(
     const int qpos_v = MULTI ? q_pos[seq_of(tid & ~63)] : ld_uniform_i32(q_pos + b);  // in flight with the loads below
     const int G = GFIX > 0 ? GFIX : H / H_kv;
     const int g = g0 + hh;
+    static_assert(!RESOLVE || !MULTI, "a tile of one sequence");
+    uint2 cand[(kTmCand + NT - 1) / NT];
+    u32x4 meta = {1u, 0u, 0u, 0u};   // fallback, threshold slot, selected members, scores above
+    uint32_t members = 0u;
+    if constexpr (RESOLVE) {
+        int zero;
+        asm volatile("v_mov_b32 %0, 0" : "=v"(zero));  // (through the vector memory path, see ld_uniform_i32)
+        const uint32_t* mp = reinterpret_cast<const uint32_t*>(res.meta + b) + zero;
+        meta = ld16(mp);
+        members = mp[4];
+#pragma unroll
+        for (int u = 0; u < (kTmCand + NT - 1) / NT; ++u) cand[u] = res.cand[(size_t)b * kTmCand + min(tid + u * NT, kTmCand - 1)];
+    }
 
     // Everything the prologue needs from memory is requested before anything is waited for, from clamped
     // addresses so that no load sits in a branch: the tile's token rows (slots at or past the selection count
@@ -226,6 +242,25 @@ __device__ __forceinline__ void logits_tile(
         return;
     }
 
+    if constexpr (RESOLVE) {
+        static_assert(C::SLOT >= kTmResolveLds, "the last stage is free until the main loop");
+        const int lo = res.n_sink + wave_uniform((int)meta.w), up = res.n_sink + res.top_k;
+        if (!wave_uniform((int)meta.x) && lo < tok0 + C::TOK && up > tok0) {  // uniform
+            const int* tok = tm_rank<NT>(lds + 3 * C::SLOT, cand, (uint32_t)wave_uniform((int)members), (uint32_t)wave_uniform((int)meta.z));
+            auto entry = [&](int t, int row) {
+                const int slot = tok0 + t;
+                return slot >= lo && slot < up ? min(max(tok[slot - lo], 0), S_max - 1) : row;
+            };
+#pragma unroll
+            for (int i = 0; i < NBP; ++i) b_row[i] = entry((wave + i * NW) * 16 + (lane >> 2), b_row[i]);
+#pragma unroll
+            for (int u = 0; u < NSP; ++u) pos_reg[u] = entry(min(tid + u * NT, C::TOK - 1), pos_reg[u]);
+            if (g0 == 0) {
+                for (int t = tid; t < C::TOK; t += NT)
+                    if (tok0 + t >= lo && tok0 + t < up) res.idx[(size_t)b * k_tot + tok0 + t] = tok[tok0 + t - lo];
+            }
+        }
+    }
     __shared__ __attribute__((aligned(16))) float sQ[SQ * HEADS][kMaxGroup][kHeadDim];
     __shared__ float2 sCS[SQ][kPairs];
     __shared__ float2 sStat[HEADS][NTG][kMaxGroup];
@@ -486,17 +521,28 @@ __device__ __forceinline__ void logits_tile(
 template <typename T, int HEADS, int NTG, int NB, int GB, int GFIX, bool MULTI = false>
 __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void attend_logits_kernel(SALS_LG_ARGS)
 {
-    logits_tile<T, HEADS, NTG, NB, GB, GFIX, MULTI, false, false>((int)blockIdx.x, Kc, UkP, idx, n_sel, q, q_pos, rope, inv, logits, stats,
+    logits_tile<T, HEADS, NTG, NB, GB, GFIX, MULTI, false, false, false>((int)blockIdx.x, Kc, UkP, idx, n_sel, q, q_pos, rope, inv, logits, stats,
                                                                   B, S_max, r, H, H_kv, k_tot, lk, n_parts, heads_fastest, style, scale,
-                                                                  ring, stats_stride, plogits, ksplit, WindowByLength{}, SplitLogits{});
+                                                                  ring, stats_stride, plogits, ksplit, WindowByLength{}, SplitLogits{},
+                                                                  TopkResolve{});
 }
 // with another pass's split logits on the side
 template <typename T, int HEADS, int NTG, int NB, int GB, int GFIX>
 __global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void attend_logits_side_kernel(SALS_LG_ARGS, SplitLogits split)
 {
-    logits_tile<T, HEADS, NTG, NB, GB, GFIX, false, false, true>((int)blockIdx.x, Kc, UkP, idx, n_sel, q, q_pos, rope, inv, logits, stats,
+    logits_tile<T, HEADS, NTG, NB, GB, GFIX, false, false, true, false>((int)blockIdx.x, Kc, UkP, idx, n_sel, q, q_pos, rope, inv, logits, stats,
                                                                  B, S_max, r, H, H_kv, k_tot, lk, n_parts, heads_fastest, style, scale,
-                                                                 ring, stats_stride, plogits, ksplit, WindowByLength{}, split);
+                                                                 ring, stats_stride, plogits, ksplit, WindowByLength{}, split,
+                                                                 TopkResolve{});
+}
+// on a selection whose threshold bin is still to be ranked
+template <typename T, int HEADS, int NTG, int NB, int GB, int GFIX>
+__global__ __launch_bounds__(64 * HEADS * NTG, HEADS * NTG >= 8 ? 2 : 1) void attend_logits_resolve_kernel(SALS_LG_ARGS, TopkResolve res)
+{
+    logits_tile<T, HEADS, NTG, NB, GB, GFIX, false, false, false, true>((int)blockIdx.x, Kc, UkP, idx, n_sel, q, q_pos, rope, inv, logits,
+                                                                        stats, B, S_max, r, H, H_kv, k_tot, lk, n_parts, heads_fastest,
+                                                                        style, scale, ring, stats_stride, plogits, ksplit,
+                                                                        WindowByLength{}, SplitLogits{}, res);
 }
 #undef SALS_LG_ARGS
 

@@ -273,7 +273,10 @@ __device__ __forceinline__ void topk_select_sequence(TopkShared& sh, const float
                 }
                 __syncthreads();
                 // the member with  #(greater) < kk <= #(greater or equal)  carries the k-th key
-                for (int t = tid; t < (int)members; t += NTH) {
+#pragma unroll
+                for (int t0 = 0; t0 < kTopkCand; t0 += NTH) {
+                    const int t = t0 + tid;
+                    if (t >= (int)members) break;
                     const uint32_t mykey = sh.cand[t];
                     uint32_t gt = 0u, ge = 0u;
                     for (uint32_t c = 0; c < members; c += 4) {

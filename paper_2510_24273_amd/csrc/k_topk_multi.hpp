@@ -20,6 +20,9 @@
 // does not cover (a cache no longer than the selection, a degenerate or non-finite score range,
 // more than 512 members in the threshold bin) raise a flag, and the finish kernel's workgroup
 // then selects that sequence from scratch the way topk_kernel does.
+// A decode step whose logits kernel has tiles of one sequence needs no finish launch (3.9 us with the gap before it): the first
+// chunk's place workgroup does all but the ranking (topk_place_kernel<true>), and the logits workgroups whose tiles reach the
+// entries to be ranked do that for themselves, beside the loads of their first panels (TopkResolve; 0.5 - 1 us of theirs).
 #pragma once
 #include "common.hpp"
 #include "k_topk.hpp"
@@ -28,6 +31,7 @@ namespace sals {
 
 constexpr int kTmChunk = 8192;            // scores per workgroup
 constexpr int kTmF4 = kTmChunk / (4 * kTopkThreads);  // float4 groups per thread: 2
+constexpr int kTmStepMin = 16384;         // a decode step uses the chain above this, where its logits kernel can rank (see make_layout)
 constexpr int kTmBins = 2048;
 constexpr int kTmMaxChunks = 128;         // S_max <= 2^20
 constexpr int kTmCand = 512;              // candidates the finish kernel ranks
@@ -246,13 +250,17 @@ __device__ __forceinline__ TopkMeta tm_resolve(TmResolveLds& L, TopkShared& sh, 
     return m;
 }
 
+// LAST: no finish kernel follows.  The first chunk's workgroup also writes the sink and recent entries, the count and the window
+// lists, and selects a flagged sequence from scratch; the members of the threshold bin are ranked by the logits kernel (TopkResolve).
+template <bool LAST>
 __global__ __launch_bounds__(kTopkThreads) void topk_place_kernel(const float* __restrict__ scores,
                                                                   const int32_t* __restrict__ seq_len,
                                                                   const uint2* __restrict__ range,
                                                                   const uint32_t* __restrict__ hist, int n_range, int S_max,
                                                                   int n_chunk, int top_k, int n_sink, int n_recent,
                                                                   int32_t* __restrict__ idx, TopkMeta* __restrict__ meta,
-                                                                  uint2* __restrict__ cand_out)
+                                                                  uint2* __restrict__ cand_out, int32_t* __restrict__ n_sel,
+                                                                  WindowLists wl)
 {
     __shared__ TopkShared sh;
     __shared__ TmResolveLds rl;
@@ -264,7 +272,20 @@ __global__ __launch_bounds__(kTopkThreads) void topk_place_kernel(const float* _
     int phase = 0;
     const TopkMeta m = tm_resolve(rl, sh, phase, range, n_range, hist, b, chunk, wave_uniform(S), n_chunk, top_k, n_sink, n_recent, &base_above,
                                   &base_cand);
-    if (chunk == 0 && threadIdx.x == 0) meta[b] = m;  // for the finish kernel
+    if (chunk == 0 && threadIdx.x == 0) meta[b] = m;  // for the finish kernel, or the logits kernel
+    if (LAST && chunk == 0) {  // uniform
+        write_window_lists(wl, seq_len, b, S_max, top_k + n_sink + n_recent, kTopkThreads);
+        if (m.fallback) {
+            __syncthreads();  // (sh is used anew)
+            topk_select_sequence<0>(sh, scores, seq_len, idx, n_sel, b, S_max, top_k, n_sink, n_recent);
+            return;
+        }
+        int32_t* all = idx + (size_t)b * (top_k + n_sink + n_recent);
+        const int len = wave_uniform(S);
+        for (int t = threadIdx.x; t < n_sink; t += kTopkThreads) all[t] = t;
+        for (int t = threadIdx.x; t < n_recent; t += kTopkThreads) all[n_sink + top_k + t] = len - n_recent + t;
+        if (threadIdx.x == 0) n_sel[b] = top_k + n_sink + n_recent;
+    }
     if (m.fallback) return;
     int slot[4 * kTmF4];
     uint32_t n_ab = 0u, n_eq = 0u;
@@ -287,6 +308,68 @@ __global__ __launch_bounds__(kTopkThreads) void topk_place_kernel(const float* _
     }
 }
 
+// What a kernel needs that reads a selection whose threshold bin has not been ranked (topk_place_kernel<true>): the entries
+// n_sink + n_above .. n_sink + top_k of a sequence's list are the kk first of its `members` candidates, in token order.
+struct TopkResolve {
+    const TopkMeta* meta;    // [B]
+    const uint2* cand;       // [B][kTmCand]
+    int32_t* idx;            // [B][k_tot], the list to complete
+    int n_sink, top_k;
+};
+constexpr int kTmResolveLds = kTmCand * (8 + 4 + 4);
+// Ranks the candidates of a sequence (NT threads; raw[u]: candidate threadIdx.x + u NT) in `lds` (kTmResolveLds bytes, 16-byte
+// aligned); returns the selected tokens in token order, in LDS, readable by all threads.
+template <int NT>
+__device__ __forceinline__ const int* tm_rank(unsigned char* lds, const uint2 (&raw)[(kTmCand + NT - 1) / NT], uint32_t nm, uint32_t kk)
+{
+    constexpr int NC = (kTmCand + NT - 1) / NT;
+    uint64_t* s_c = reinterpret_cast<uint64_t*>(lds);  // key, then the token's complement: a larger number goes first
+    uint32_t* s_sel = reinterpret_cast<uint32_t*>(lds + kTmCand * 8);
+    int* s_tok = reinterpret_cast<int*>(lds + kTmCand * 12);
+    const int tid = threadIdx.x;
+    uint64_t me[NC];
+#pragma unroll
+    for (int u = 0; u < NC; ++u) {
+        me[u] = (uint64_t)raw[u].x << 32 | (uint32_t)~raw[u].y;
+        if (tid + u * NT < kTmCand) s_c[tid + u * NT] = (uint32_t)(tid + u * NT) < nm ? me[u] : 0u;
+    }
+    __syncthreads();
+    // rank among the members: larger key first, equal keys by smaller token index (slots past the members carry key 0 and
+    // rank behind everything); eight members read together
+    const uint32_t nm8 = (nm + 7u) & ~7u;
+    bool sel[NC];
+#pragma unroll
+    for (int u = 0; u < NC; ++u) {
+        const uint32_t e = tid + u * NT;
+        uint32_t before = 0u;
+        if (e < nm)
+            for (uint32_t c = 0; c < nm8; c += 8) {
+                uint64_t o[8];
+#pragma unroll
+                for (int v = 0; v < 8; ++v) o[v] = s_c[c + v];
+#pragma unroll
+                for (int v = 0; v < 8; ++v) before += o[v] > me[u];
+            }
+        sel[u] = e < nm && before < kk;
+        // selected members in token order: the others' indices are replaced by the largest number
+        if (e < (uint32_t)kTmCand) s_sel[e] = sel[u] ? raw[u].y : 0xffffffffu;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NC; ++u)
+        if (sel[u]) {
+            uint32_t pos = 0u;
+            for (uint32_t c = 0; c < nm8; c += 8) {
+                const u32x4 o0 = *reinterpret_cast<const u32x4*>(&s_sel[c]), o1 = *reinterpret_cast<const u32x4*>(&s_sel[c + 4]);
+                pos += (o0.x < raw[u].y) + (o0.y < raw[u].y) + (o0.z < raw[u].y) + (o0.w < raw[u].y);
+                pos += (o1.x < raw[u].y) + (o1.y < raw[u].y) + (o1.z < raw[u].y) + (o1.w < raw[u].y);
+            }
+            s_tok[pos] = (int)raw[u].y;
+        }
+    __syncthreads();
+    return s_tok;
+}
+
 // finish: ranks the candidates; a flagged sequence is selected from scratch by this workgroup
 __global__ __launch_bounds__(kTopkThreads) void topk_finish_kernel(const uint2* __restrict__ cand,
                                                                    const TopkMeta* __restrict__ meta,
@@ -296,13 +379,12 @@ __global__ __launch_bounds__(kTopkThreads) void topk_finish_kernel(const uint2* 
                                                                    WindowLists wl)
 {
     __shared__ TopkShared sh;
-    __shared__ __attribute__((aligned(16))) uint2 s_c[kTmCand];
-    __shared__ __attribute__((aligned(16))) uint32_t s_sel[kTmCand];
+    __shared__ __attribute__((aligned(16))) unsigned char s_rank[kTmResolveLds];
     const int b = blockIdx.x, tid = threadIdx.x;
     write_window_lists(wl, seq_len, b, S_max, top_k + n_sink + n_recent, kTopkThreads);
     // (the candidate pair, the length and the meta record are requested together; slots past the member count hold
     // stale pairs and are masked)
-    const uint2 me_raw = cand[(size_t)b * kTmCand + min(tid, kTmCand - 1)];
+    const uint2 raw[1] = {cand[(size_t)b * kTmCand + min(tid, kTmCand - 1)]};
     const int S_v = ld_uniform_i32(seq_len + b);
     const TopkMeta m = meta[b];
     if (m.fallback) {  // uniform
@@ -315,38 +397,8 @@ __global__ __launch_bounds__(kTopkThreads) void topk_finish_kernel(const uint2* 
     for (int t = tid; t < n_sink; t += kTopkThreads) out[t] = t;
     for (int t = tid; t < n_recent; t += kTopkThreads) out[n_sink + top_k + t] = S - n_recent + t;
     if (tid == 0) n_sel[b] = k_tot;
-    const uint32_t nm = m.members;
-    const uint2 me = (uint32_t)tid < nm ? me_raw : make_uint2(0u, 0u);
-    if (tid < kTmCand) s_c[tid] = me;
-    __syncthreads();
-    // rank among the members: larger key first, equal keys by smaller token index (slots past the members carry key 0 and
-    // rank behind everything); eight members read together
-    const uint32_t nm8 = (nm + 7u) & ~7u;
-    uint32_t before = 0u;
-    if ((uint32_t)tid < nm)
-        for (uint32_t c = 0; c < nm8; c += 8) {
-            u32x4 o[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) o[u] = *reinterpret_cast<const u32x4*>(&s_c[c + 2 * u]);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                before += (o[u].x > me.x) || (o[u].x == me.x && o[u].y < me.y);
-                before += (o[u].z > me.x) || (o[u].z == me.x && o[u].w < me.y);
-            }
-        }
-    const bool sel = (uint32_t)tid < nm && before < m.kk;
-    // selected members in token order: the others' indices are replaced by the largest number
-    if (tid < kTmCand) s_sel[tid] = sel ? me.y : 0xffffffffu;
-    __syncthreads();
-    if (sel) {
-        uint32_t pos = 0u;
-        for (uint32_t c = 0; c < nm8; c += 8) {
-            const u32x4 o0 = *reinterpret_cast<const u32x4*>(&s_sel[c]), o1 = *reinterpret_cast<const u32x4*>(&s_sel[c + 4]);
-            pos += (o0.x < me.y) + (o0.y < me.y) + (o0.z < me.y) + (o0.w < me.y);
-            pos += (o1.x < me.y) + (o1.y < me.y) + (o1.z < me.y) + (o1.w < me.y);
-        }
-        out[n_sink + m.n_above + pos] = (int32_t)me.y;
-    }
+    const int* tok = tm_rank<kTopkThreads>(s_rank, raw, m.members, m.kk);
+    if ((uint32_t)tid < m.kk) out[n_sink + m.n_above + tid] = tok[tid];
 }
 
 }  // namespace sals

@@ -94,10 +94,10 @@ __global__ __launch_bounds__(256, 1) void window_select_kernel(
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     if ((int)blockIdx.x < sel.n_blocks) { step_select<256>(sel, lds); return; }  // uniform
-    logits_tile<T, 1, 4, 1, GB, GFIX, true, true, false>((int)blockIdx.x - sel.n_blocks, Kw, UkP, nullptr, nullptr, q, q_pos, rope, inv, logits,
+    logits_tile<T, 1, 4, 1, GB, GFIX, true, true, false, false>((int)blockIdx.x - sel.n_blocks, Kw, UkP, nullptr, nullptr, q, q_pos, rope, inv, logits,
                                                   stats, B, S_max, r, H, H_kv, w, lk, 1, 0, style, scale, w, stats_stride, plogits,
                                                   ksplit, WindowByLength{sel.seq_len, sel.top_k + sel.n_sink + sel.n_recent},
-                                                  SplitLogits{});
+                                                  SplitLogits{}, TopkResolve{});
 }
 
 }  // namespace sals

@@ -50,6 +50,7 @@ struct Layout {  // byte offsets into the workspace
     int dn_chunks, dn_tok;       // dense baseline: token chunks per sequence (overlap score: tokens per chunk)
     int proj_np;                 // D-axis slices of the query projection
     int tm_chunks;               // chunks of the multi-workgroup selection (0: one workgroup per sequence)
+    int tm_step_chunks;          // the same inside a decode step whose logits kernel ranks the threshold bin
     size_t w_section;            // elements per section of the packed weights
 };
 
@@ -210,14 +211,18 @@ Layout make_layout(const sals_desc& d)
         L.dn_chunks = ceil_div(d.S_max, L.dn_tok);
         L.dn_part = take((size_t)d.B * d.H_q * L.dn_chunks * kDnRec * 4);
     }
-    // Long sequences: selection spread over 8192-score chunks.  The line lies where topk_kernel's keys no longer fit in
-    // registers.  At it the two are level inside a step (4 x 32768: 15.4 us for the one launch, 16.4 for the chain of three, both
-    // with the gap before a launch) and on its own the one launch is faster (13.4 against 17.9 us for the chain of four; 7.9 at
-    // 16384 scores; the chain takes 18.4 at 131072).
+    // Long sequences: selection spread over 8192-score chunks.  On its own from 32769 scores on, where topk_kernel's keys no
+    // longer fit in registers (the one launch takes 13.4 us at 32768 scores and 7.9 at 16384, the chain of four launches 17.9 and,
+    // at 131072, 18.4).  In a decode step the chain has two launches (the score kernel leaves the ranges, the logits kernel ranks
+    // the threshold bin) and is faster from topk_kernel's widest instance on: whole steps of 4 x (2048 of S), H_kv 32, r 1024 take
+    // 145.2 against 145.8 us at S 17408, 152.4 against 153.4 at 24576, 162.4 against 163.0 at 32768; of 1 x (1024 of S) 55.9 against
+    // 56.7, 56.5 against 57.8, 59.7 against 61.4.  Beyond 32768 it saves the finish launch: 170.9 against 173.0 and 63.0 against
+    // 64.7 at 40960, and 1 x (2048 of 131072), H_kv 8 65.0 against 68.2.
     L.tm_chunks = d.S_max > 32768 ? ceil_div(d.S_max, kTmChunk) : 0;
-    if (L.tm_chunks > 0) {
-        L.tm_part = take((size_t)d.B * L.tm_chunks * sizeof(uint2));
-        L.tm_hist = take((size_t)d.B * L.tm_chunks * kTmRow * 4);
+    L.tm_step_chunks = d.S_max > kTmStepMin ? ceil_div(d.S_max, kTmChunk) : 0;
+    if (const int n = L.tm_step_chunks) {
+        L.tm_part = take((size_t)d.B * n * sizeof(uint2));
+        L.tm_hist = take((size_t)d.B * n * kTmRow * 4);
         L.tm_meta = take((size_t)d.B * sizeof(TopkMeta));
         L.tm_cand = take((size_t)d.B * kTmCand * sizeof(uint2));
         // key ranges the score kernel leaves per workgroup inside a decode step (at least 16 rows per workgroup)
@@ -338,12 +343,23 @@ sals_status launch_scores(const sals_ctx* c, const void* Kc, const int32_t* seq_
     return launch_status();
 }
 
+// whether a decode step ranks the threshold bin in its logits kernel (the shapes with tiles of 128 and 256 tokens)
+bool step_resolves(const sals_ctx* c) { return c->L.tm_step_chunks > 0 && (c->plan.pick == 1 || c->plan.pick == 2) && c->fuse_select; }
+// whether a decode step selects by the chunked chain, whose ranges its score kernel leaves
+bool step_chain(const sals_ctx* c) { return c->L.tm_chunks > 0 || step_resolves(c); }
+TopkResolve topk_resolve(const sals_ctx* c, int32_t* idx)
+{
+    return TopkResolve{reinterpret_cast<const TopkMeta*>(c->ws + c->L.tm_meta), reinterpret_cast<const uint2*>(c->ws + c->L.tm_cand), idx,
+                       c->d.n_sink, c->d.top_k};
+}
+
 // wl: also leave the recent-window lists (see WindowLists); by default none
-// score_ranges: the scores were written by this context's score kernel in the same step, which left its workgroups'
-// key ranges in the workspace (the chain then needs no range pass of its own)
+// in_step: the scores were written by this context's score kernel in the same step, which left its workgroups'
+// key ranges in the workspace (the chain then needs no range pass of its own); with step_resolves() the threshold bin is left to the
+// logits kernel
 sals_status launch_topk(const sals_ctx* c, const float* scores, const int32_t* seq_len, int32_t* idx,
                         int32_t* n_sel, hipStream_t st, WindowLists wl = WindowLists{nullptr, nullptr, nullptr, 0},
-                        bool score_ranges = false)
+                        bool in_step = false)
 {
     const sals_desc& d = c->d;
     dim3 grid(d.B), block(kTopkThreads);
@@ -351,15 +367,15 @@ sals_status launch_topk(const sals_ctx* c, const float* scores, const int32_t* s
 #define SALS_TOPK(F4)                                                                                \
     hipLaunchKernelGGL((topk_kernel<F4>), grid, block, 0, st, scores, seq_len, idx, n_sel, d.S_max, \
                        d.top_k, d.n_sink, d.n_recent)
-    if (c->L.tm_chunks > 0) {
+    if (c->L.tm_chunks > 0 || (in_step && step_chain(c))) {
         const Layout& L = c->L;
-        const int nc = L.tm_chunks;
+        const int nc = L.tm_step_chunks;
         TopkMultiWs ws{};
         ws.part = reinterpret_cast<uint2*>(c->ws + L.tm_part); ws.hist = reinterpret_cast<uint32_t*>(c->ws + L.tm_hist);
         ws.meta = reinterpret_cast<TopkMeta*>(c->ws + L.tm_meta); ws.cand = reinterpret_cast<uint2*>(c->ws + L.tm_cand);
         ws.range = ws.part; ws.n_range = nc;
         dim3 cgrid(nc, d.B);
-        if (score_ranges) {
+        if (in_step) {
             ws.range = reinterpret_cast<const uint2*>(c->ws + L.tm_srange);
             ws.n_range = ceil_div(d.S_max, c->score_rows);
         } else {
@@ -367,8 +383,12 @@ sals_status launch_topk(const sals_ctx* c, const float* scores, const int32_t* s
         }
         hipLaunchKernelGGL(topk_hist_kernel, cgrid, block, 0, st, scores, seq_len, ws.range, ws.n_range, d.S_max, nc, d.n_sink,
                            d.n_recent, ws.hist);
-        hipLaunchKernelGGL(topk_place_kernel, cgrid, block, 0, st, scores, seq_len, ws.range, ws.hist, ws.n_range, d.S_max, nc,
-                           d.top_k, d.n_sink, d.n_recent, idx, ws.meta, ws.cand);
+#define SALS_PLACE(LAST)                                                                                          \
+    hipLaunchKernelGGL((topk_place_kernel<LAST>), cgrid, block, 0, st, scores, seq_len, ws.range, ws.hist, ws.n_range, d.S_max, nc, \
+                       d.top_k, d.n_sink, d.n_recent, idx, ws.meta, ws.cand, n_sel, wl)
+        if (in_step && step_resolves(c)) { SALS_PLACE(true); return launch_status(); }
+        SALS_PLACE(false);
+#undef SALS_PLACE
         hipLaunchKernelGGL(topk_finish_kernel, grid, block, 0, st, ws.cand, ws.meta, seq_len, d.S_max, d.top_k, d.n_sink,
                            d.n_recent, idx, n_sel, scores, wl);
         return launch_status();
@@ -488,6 +508,7 @@ struct QvCache {
 // qv == nullptr: latent value cache Vc, value sum in latent space and output projection through U_v.
 // Otherwise: values are the de-quantised rows of the quantised cache (Vc unused).
 // ring > 0: Kc, Vc are rings of that many rows per sequence (token t in row t mod ring).
+// res: the selection's threshold bin is still to be ranked (see step_resolves).
 // other: another pass's split logits, added up by this pass's logits kernel on the side (not by the tiles of several sequences).
 // phases: which of the three launches to enqueue (all of them by default).  link: where the logits kernel leaves
 // its tile statistics and where the value kernel finds the statistics of the whole softmax, when two passes over
@@ -663,6 +684,15 @@ template <typename T, int HEADS, int NTG, int NB> auto logits_side_kernel_for(in
     return attend_logits_side_kernel<T, HEADS, NTG, NB, 1, 0>;
 }
 
+// the same on a selection whose threshold bin is still to be ranked
+template <typename T, int HEADS, int NTG, int NB> auto logits_resolve_kernel_for(int group)
+{
+    if (group == 1) return attend_logits_resolve_kernel<T, HEADS, NTG, NB, 1, 1>;
+    if (group == 4) return attend_logits_resolve_kernel<T, HEADS, NTG, NB, 4, 4>;
+    if (group % 4 == 0) return attend_logits_resolve_kernel<T, HEADS, NTG, NB, 4, 0>;
+    return attend_logits_resolve_kernel<T, HEADS, NTG, NB, 1, 0>;
+}
+
 template <typename T> sals_status allow_logits_lds(const sals_ctx* c)
 {
     const LogitsPlan& P = c->plan;
@@ -678,6 +708,10 @@ template <typename T> sals_status allow_logits_lds(const sals_ctx* c)
     else {
         ok = allow(reinterpret_cast<const void*>(SmallLogits<T>::get(P.nst, false)), kLsLds) &&
              allow(reinterpret_cast<const void*>(SmallLogits<T>::get(P.nst, true)), kLsLds);
+    }
+    if (ok && step_resolves(c)) {
+        if (P.pick == 1) ok = allow(reinterpret_cast<const void*>(logits_resolve_kernel_for<T, 2, 4, 2>(group)), logits_cfg<2, 4, 2>::LDS);
+        if (P.pick == 2) ok = allow(reinterpret_cast<const void*>(logits_resolve_kernel_for<T, 1, 4, 1>(group)), logits_cfg<1, 4, 1>::LDS);
     }
     // (a context with recent tokens may have a window beside it)
     if (ok && c->d.n_recent > 0) {
@@ -770,7 +804,8 @@ template <typename T>
 sals_status launch_attend(const sals_ctx* c, const void* q, const int32_t* q_pos, const void* Kc,
                           const void* Vc, const void* W, const int32_t* idx, const int32_t* n_sel, void* out,
                           hipStream_t st, const QvCache* qv = nullptr, int ring = 0, int phases = kPhaseAll,
-                          const StatsLink* link = nullptr, const FusedSelect* fs = nullptr, const SplitLogits* other = nullptr)
+                          const StatsLink* link = nullptr, const FusedSelect* fs = nullptr, const SplitLogits* other = nullptr,
+                          const TopkResolve* res = nullptr)
 {
     const sals_desc& d = c->d;
     const Layout& L = c->L;
@@ -806,6 +841,8 @@ sals_status launch_attend(const sals_ctx* c, const void* q, const int32_t* q_pos
         const dim3 grid(n_parts * (d.H_kv / HEADS) * d.B);                                                   \
         if (other) hipLaunchKernelGGL((logits_side_kernel_for<T, HEADS, NTG, NB>(d.H_q / d.H_kv)), grid, dim3(LC::NT), LC::LDS, st, \
                                       SALS_LOGITS_ARGS, *other);                                             \
+        else if (res) hipLaunchKernelGGL((logits_resolve_kernel_for<T, HEADS, NTG, NB>(d.H_q / d.H_kv)), grid, dim3(LC::NT), LC::LDS, st, \
+                                         SALS_LOGITS_ARGS, *res);                                            \
         else hipLaunchKernelGGL((logits_kernel_for<T, HEADS, NTG, NB>(d.H_q / d.H_kv)), grid, dim3(LC::NT), LC::LDS, st, \
                                 SALS_LOGITS_ARGS);                                                           \
     } while (0)
@@ -1151,7 +1188,7 @@ sals_status step_scores(sals_ctx* ctx, const void* q, const void* W, const void*
                         ? launch_project<bf16_t>(ctx, W, q, st)
                         : launch_project<float>(ctx, W, q, st);
     if (s != SALS_OK) return s;
-    uint2* wg_range = ctx->L.tm_chunks > 0 ? reinterpret_cast<uint2*>(ctx->ws + ctx->L.tm_srange) : nullptr;
+    uint2* wg_range = step_chain(ctx) ? reinterpret_cast<uint2*>(ctx->ws + ctx->L.tm_srange) : nullptr;
     return ctx->d.dtype == SALS_BF16 ? launch_scores<bf16_t>(ctx, Kc, seq_len, scores, st, wg_range)
                                      : launch_scores<float>(ctx, Kc, seq_len, scores, st, wg_range);
 }
@@ -1243,8 +1280,17 @@ sals_status sals_decode_step(sals_ctx* ctx, const void* q, const int32_t* q_pos,
                    : launch_attend<float>(ctx, q, q_pos, Kc, Vc, W, idx, n_sel, out, st, nullptr, 0, kPhaseAll, nullptr, &fs);
     }
     s = launch_topk(ctx, scores, seq_len, idx, n_sel, static_cast<hipStream_t>(hip_stream),
-                    WindowLists{nullptr, nullptr, nullptr, 0}, ctx->L.tm_chunks > 0);
+                    WindowLists{nullptr, nullptr, nullptr, 0}, true);
     if (s != SALS_OK) return s;
+    if (step_resolves(ctx)) {
+        if (bad(Vc)) return SALS_ERR_INVALID_ARG;
+        const TopkResolve res = topk_resolve(ctx, idx);
+        hipStream_t st = static_cast<hipStream_t>(hip_stream);
+        return ctx->d.dtype == SALS_BF16 ? launch_attend<bf16_t>(ctx, q, q_pos, Kc, Vc, W, idx, n_sel, out, st, nullptr, 0, kPhaseAll,
+                                                                 nullptr, nullptr, nullptr, &res)
+                                         : launch_attend<float>(ctx, q, q_pos, Kc, Vc, W, idx, n_sel, out, st, nullptr, 0, kPhaseAll,
+                                                                nullptr, nullptr, nullptr, &res);
+    }
     return sals_sparse_attend(ctx, q, q_pos, Kc, Vc, W, idx, n_sel, out, hip_stream);
 }
 
@@ -1307,8 +1353,17 @@ sals_status sals_decode_step_qv(sals_ctx* ctx, const void* q, const int32_t* q_p
                    : launch_attend<float>(ctx, q, q_pos, Kc, nullptr, W, idx, n_sel, out, st, &qv, 0, kPhaseAll, nullptr, &fs);
     }
     s = launch_topk(ctx, scores, seq_len, idx, n_sel, static_cast<hipStream_t>(hip_stream),
-                    WindowLists{nullptr, nullptr, nullptr, 0}, ctx->L.tm_chunks > 0);
+                    WindowLists{nullptr, nullptr, nullptr, 0}, true);
     if (s != SALS_OK) return s;
+    if (step_resolves(ctx)) {
+        const QvCache qv{Vq, Vmeta, bits};
+        const TopkResolve res = topk_resolve(ctx, idx);
+        hipStream_t st = static_cast<hipStream_t>(hip_stream);
+        return ctx->d.dtype == SALS_BF16 ? launch_attend<bf16_t>(ctx, q, q_pos, Kc, nullptr, W, idx, n_sel, out, st, &qv, 0, kPhaseAll,
+                                                                 nullptr, nullptr, nullptr, &res)
+                                         : launch_attend<float>(ctx, q, q_pos, Kc, nullptr, W, idx, n_sel, out, st, &qv, 0, kPhaseAll,
+                                                                nullptr, nullptr, nullptr, &res);
+    }
     return sals_sparse_attend_qv(ctx, q, q_pos, Kc, Vq, Vmeta, bits, W, idx, n_sel, out, hip_stream);
 }
 
@@ -1411,12 +1466,13 @@ sals_status launch_window_select(sals_ctx* ctx, sals_ctx* win, const void* q, co
 }
 
 // The two logits passes.  have: what the step's selection has already done.
-enum WindowHave { kWindowNothing, kWindowLists, kWindowLogits };
+enum WindowHave { kWindowNothing, kWindowLists, kWindowListsUnranked, kWindowLogits };
 template <typename T>
 sals_status window_logits(sals_ctx* ctx, sals_ctx* win, const void* q, const int32_t* q_pos, const void* Kc, const void* W, const void* Kw,
                           const void* W_hi, const int32_t* idx, const int32_t* n_sel, hipStream_t st, WindowHave have)
 {
     const sals_desc& d = ctx->d;
+    const TopkResolve res = topk_resolve(ctx, const_cast<int32_t*>(idx));  // (the step's own list where it is used)
     const WindowLists wl = window_lists(ctx, win);
     const int w = win->d.top_k;
     if (ctx->plan.n_parts + win->plan.n_parts > ctx->L.max_parts) return SALS_ERR_UNSUPPORTED;
@@ -1436,7 +1492,8 @@ sals_status window_logits(sals_ctx* ctx, sals_ctx* win, const void* q, const int
         }
     }
     const sals_status s = launch_attend<T>(ctx, q, q_pos, Kc, nullptr, W, idx, wl.n_lo, nullptr, st, nullptr, 0, kPhaseLogits, &lo,
-                                           nullptr, split.ksplit > 1 && ctx->plan.pick != 4 ? &split : nullptr);
+                                           nullptr, split.ksplit > 1 && ctx->plan.pick != 4 ? &split : nullptr,
+                                           have == kWindowListsUnranked ? &res : nullptr);
     if (s != SALS_OK || have == kWindowLogits) return s;
     return launch_attend<T>(win, q, q_pos, Kw, nullptr, W_hi, wl.idx_hi, wl.n_hi, nullptr, st, nullptr, w, kPhaseLogits, &hi);
 }
@@ -1452,8 +1509,8 @@ sals_status window_step_select(sals_ctx* ctx, sals_ctx* win, const void* q, cons
                    : launch_window_select<float>(ctx, win, q, q_pos, Kw, W_hi, scores, seq_len, idx, n_sel, st);
     }
     // the selection kernel also writes the two passes' token lists (they follow from the sequence lengths)
-    *have = kWindowLists;
-    return launch_topk(ctx, scores, seq_len, idx, n_sel, st, window_lists(ctx, win), ctx->L.tm_chunks > 0);
+    *have = step_resolves(ctx) ? kWindowListsUnranked : kWindowLists;
+    return launch_topk(ctx, scores, seq_len, idx, n_sel, st, window_lists(ctx, win), true);
 }
 
 sals_status window_attend(sals_ctx* ctx, sals_ctx* win, const void* q, const int32_t* q_pos, const void* Kc,

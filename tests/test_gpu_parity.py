@@ -589,3 +589,40 @@ def test_selection_inside_split_logits(dtype, H_kv, r, S, top_k, lens, monkeypat
     for b in range(w.B):
         assert np.array_equal(i1[b, : n1[b]], i0[b, : n0[b]])
     assert np.array_equal(o1, o0)
+
+
+@pytest.mark.parametrize("pick,dtype,H_kv,r,S,top_k,n_sink,lens,copies", [
+    (1, "bf16", 8, 128, 16388, 700, 4, [16388, 16001], 1),    # the shortest; ranked entries in the last of three tiles
+    (1, "bf16", 2, 256, 33000, 252, 0, [33000], 1),           # entries up to a tile's end
+    (2, "bf16", 8, 512, 20000, 1000, 3, [19999, 700, 0], 3),  # ties; a sequence shorter than the selection, an empty one
+    (2, "f32", 4, 64, 17000, 300, 4, [17000, 371], 37),       # more ties; one token more than the selection
+    (1, "f32", 4, 128, 16400, 130, 1, [16400], 1),
+    (2, "bf16", 4, 128, 20000, 1, 0, [20000], 1),             # one entry
+    (2, "bf16", 4, 128, 20000, 200, 4, [20000, 9000], 1000)]) # more members than are ranked: selected from scratch
+def test_threshold_bin_ranked_by_the_logits_kernel(pick, dtype, H_kv, r, S, top_k, n_sink, lens, copies, monkeypatch):
+    """A step on a long cache leaves the ranking of the threshold bin to its logits kernel: the list is the selection's set on the
+    step's scores, and the output is, bit for bit, what the attention call gives on that list."""
+    print(f"[case] ranked in logits pick={pick} {dtype} H_kv={H_kv} r={r} S={S} k={top_k} lens={lens} copies={copies}", flush=True)
+    monkeypatch.setenv("SALS_TUNE_LOGITS", str(pick))
+    w = synth.shrink(synth.CONFIGS["cfg2"], B=len(lens), S=S, H=8, H_kv=H_kv, r=r, top_k=top_k, n_sink=n_sink, n_recent=64,
+                     n_layers=1, dtype=dtype, plant=0)
+    L = synth.make_layer(w, 0, lens)
+    for b in range(w.B):  # runs of equal rows: equal scores
+        L["Kc"][b] = np.repeat(L["Kc"][b, ::copies], copies, axis=0)[:S]
+    ctx = gu.make_ctx(w)
+    G = gu.upload(L, ctx)
+    out, out2 = (torch.empty((w.B, w.H, w.d), dtype=gu.out_dtype(w), device=gu.DEV) for _ in range(2))
+    scores = torch.empty((w.B, w.S), dtype=torch.float32, device=gu.DEV)
+    idx, idx2 = (torch.full((w.B, w.k_tot), -7, dtype=torch.int32, device=gu.DEV) for _ in range(2))
+    n, n2 = (torch.full((w.B,), -7, dtype=torch.int32, device=gu.DEV) for _ in range(2))
+    for rep in range(2):
+        ctx.decode_step(G["q"], G["q_pos"], G["Kc"], G["Vc"], G["W"], G["seq_len"], out, scores, idx, n)
+        ctx.topk_select(scores, G["seq_len"], idx2, n2)
+        ctx.sparse_attend(G["q"], G["q_pos"], G["Kc"], G["Vc"], G["W"], idx, n, out2)
+        torch.cuda.synchronize()
+        assert n.tolist() == n2.tolist() == [min(s, w.k_tot) for s in lens]
+        for b in range(w.B):
+            k = int(n[b])
+            assert torch.equal(idx[b, :k].sort().values, idx2[b, :k].sort().values)
+        assert torch.equal(out.view(torch.int16), out2.view(torch.int16))
+    ctx.close()

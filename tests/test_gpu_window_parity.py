@@ -127,6 +127,15 @@ def test_selection_and_window_logits_in_one_launch(oracle, S, B, tiles, monkeypa
     _case(oracle, w, seq_lens=[S, S - 1, 4000, 4097, 70][:B])
 
 
+@pytest.mark.parametrize("tiles", ["1", "2"])
+def test_low_rank_pass_ranks_the_threshold_bin(oracle, tiles, monkeypatch):
+    """A cache long enough for the chunked selection, whose last step the low-rank logits kernel takes; one sequence is shorter
+    than the selection."""
+    monkeypatch.setenv("SALS_TUNE_LOGITS", tiles)
+    w = synth.shrink(SMALL, B=2, S=33001, H=4, H_kv=4, r=64, r_hi=128, top_k=150, plant=2)
+    _case(oracle, w, seq_lens=[32999, 100])
+
+
 def test_largest_window_rank(oracle):
     w = synth.shrink(SMALL, B=2, S=600, r=640, r_hi=2048, top_k=200, n_sink=16, n_recent=128, plant=0)
     _case(oracle, w, seq_lens=[600, 345])
