@@ -53,8 +53,10 @@ __global__ __launch_bounds__(256) void calib_transpose_kernel(const float* __res
 // one slice of the tokens (at most 4096 of them).  grid (tiles * slices), 512 threads, one workgroup per compute unit.
 // Matrix-bound: 1.04 PFLOP/s sustained at D = 4096, 32768 tokens (560 us for 1088 items of 0.54 GFLOP, 545 to 575 from run
 // to run), what the chip's power leaves of its rate on such operands (cutting the last, partly filled round into quarter items
-// changed nothing).  With the addition below 636 to 650 us a call; a transposing copy of the keys, 256 x 128 tiles staged through
-// registers and an addition per 4096 tokens took 1400 us.
+// changed nothing).  The additions of the whole rounds' tiles run on the compute units that the last round leaves idle
+// (cov_first_tiles): 588 to 610 us a call against 644 to 665 with all of them behind; 260 against 286 at 12000 tokens, 212
+// against 225 at 8192.  A transposing copy of the keys, 256 x 128 tiles staged through registers and an addition per 4096 tokens
+// took 1400 us.
 //
 // The contraction runs over the tokens, the axis along which the keys are not contiguous: token rows go to LDS as they
 // lie in memory (32 tokens x 256 columns for either side, 16 bytes per lane without passing through registers, four
@@ -74,10 +76,59 @@ __device__ __forceinline__ void cov_tile(int id, int nt, int* row, int* col)  //
     *row = r; *col = r + id;
 }
 
+// C[i, j] += sum over the slices of P[slice][tile][i, j] in slice order, in fp64, for i <= j, and the same value to C[j, i]:
+// one 32 x 32 block of a tile by 256 threads (x), with 32 * 33 doubles of LDS.  Every thread of the workgroup has to come here (barrier).
+__device__ __forceinline__ void cov_add(double* __restrict__ C, const float* __restrict__ P, int D, int nt, int slices, int tile,
+                                        int block, int x, double* __restrict__ t)
+{
+    int tr, tc;
+    cov_tile(tile, nt, &tr, &tc);
+    const int bi = block >> 3, bj = block & 7;
+    const int i0 = tr * kCovTile + bi * 32, j0 = tc * kCovTile + bj * 32;
+    const bool live = i0 < D && j0 < D && j0 >= i0;
+    const int tx = x & 7, ty = x >> 3;  // four columns of one row per thread
+    if (live) {
+        const float* src = P + (size_t)tile * (kCovTile * kCovTile) + (bi * 32 + ty) * kCovTile + bj * 32 + tx * 4;
+        const size_t stride = (size_t)(nt * (nt + 1) / 2) * (kCovTile * kCovTile);
+        double* dst = C + (size_t)(i0 + ty) * D + j0 + tx * 4;
+        double s[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] = 0.0;
+        for (int z0 = 0; z0 < slices; z0 += 8) {  // eight slices requested together, from clamped slice numbers
+            f32x4 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = ld16_f32_stream(src + (size_t)min(z0 + u, slices - 1) * stride);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (z0 + u < slices) { s[0] += (double)v[u].x; s[1] += (double)v[u].y; s[2] += (double)v[u].z; s[3] += (double)v[u].w; }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double c = dst[e] + s[e];
+            t[ty * 33 + tx * 4 + e] = c;
+            if (i0 < j0 || ty <= tx * 4 + e) dst[e] = c;
+        }
+    }
+    __syncthreads();
+    if (live) {
+        double* mir = C + (size_t)(j0 + ty) * D + i0 + tx * 4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (i0 < j0 || ty > tx * 4 + e) mir[e] = t[(tx * 4 + e) * 33 + ty];
+    }
+}
+
+// tiles tile0 .. tile0 + n_tiles; workgroups behind theirs add up tiles 0, 1, ... of an earlier launch (32 workgroups each)
 __global__ __launch_bounds__(512, 2) void calib_cov_kernel(const bf16_t* __restrict__ X, long long n_tok, int D, int nt,
-                                                           int slice_tok, int slices, float* __restrict__ P)
+                                                           int slice_tok, int slices, float* __restrict__ P, int tile0, int n_tiles,
+                                                           double* __restrict__ C)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];  // [stage][A | B]
+    if ((int)blockIdx.x >= n_tiles * slices) {
+        const int id = (int)blockIdx.x - n_tiles * slices, part = (int)threadIdx.x >> 8;
+        cov_add(C, P, D, nt, slices, id >> 5, (id & 31) * 2 + part, threadIdx.x & 255, reinterpret_cast<double*>(lds) + part * (32 * 33));
+        return;
+    }
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hi = lane >> 5;
     const int wm = wave >> 2, wn = wave & 3;
@@ -85,10 +136,10 @@ __global__ __launch_bounds__(512, 2) void calib_cov_kernel(const bf16_t* __restr
     // rows meet in its L2
     int tile, slice;
     {
-        const int n_tiles = nt * (nt + 1) / 2, total = n_tiles * slices;
+        const int total = n_tiles * slices;
         const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds, qn = total / kXcds, rem = total % kXcds;
         const int w = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + slot;
-        slice = w / n_tiles; tile = w - slice * n_tiles;
+        slice = w / n_tiles; tile = tile0 + w - slice * n_tiles;
     }
     int tr, tc;
     cov_tile(tile, nt, &tr, &tc);
@@ -207,44 +258,13 @@ __global__ __launch_bounds__(512, 2) void calib_cov_kernel(const bf16_t* __restr
         }
 }
 
-// C[i, j] += sum over the slices of P[slice][tile][i, j] in slice order, in fp64, for i <= j, and the same value to C[j, i].
-// One workgroup per 32 x 32 block of the upper triangle's tiles; grid (64, tiles).  A stream: 486 MB in 101 us at D = 4096
-// and eight slices.
+// The additions alone, of the tiles from tile0 on: grid (64, tiles).  A stream: 486 MB in 101 us at D = 4096 and eight slices
+// if all are left to it.
 __global__ __launch_bounds__(256) void calib_cov_reduce_kernel(double* __restrict__ C, const float* __restrict__ P, int D, int nt,
-                                                               int slices)
+                                                               int slices, int tile0)
 {
-    __shared__ double t[32][33];
-    int tr, tc;
-    cov_tile(blockIdx.y, nt, &tr, &tc);
-    const int bi = blockIdx.x >> 3, bj = blockIdx.x & 7;
-    const int i0 = tr * kCovTile + bi * 32, j0 = tc * kCovTile + bj * 32;
-    if (i0 >= D || j0 >= D || j0 < i0) return;  // uniform
-    const int tx = threadIdx.x & 7, ty = threadIdx.x >> 3;  // four columns of one row per thread
-    const float* src = P + (size_t)blockIdx.y * (kCovTile * kCovTile) + (bi * 32 + ty) * kCovTile + bj * 32 + tx * 4;
-    const size_t stride = (size_t)gridDim.y * (kCovTile * kCovTile);
-    double* dst = C + (size_t)(i0 + ty) * D + j0 + tx * 4;
-    double s[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) s[e] = 0.0;
-    for (int z0 = 0; z0 < slices; z0 += 8) {  // eight slices requested together, from clamped slice numbers
-        f32x4 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = ld16_f32_stream(src + (size_t)min(z0 + u, slices - 1) * stride);
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (z0 + u < slices) { s[0] += (double)v[u].x; s[1] += (double)v[u].y; s[2] += (double)v[u].z; s[3] += (double)v[u].w; }
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const double c = dst[e] + s[e];
-        t[ty][tx * 4 + e] = c;
-        if (i0 < j0 || ty <= tx * 4 + e) dst[e] = c;
-    }
-    __syncthreads();
-    double* mir = C + (size_t)(j0 + ty) * D + i0 + tx * 4;
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-        if (i0 < j0 || ty > tx * 4 + e) mir[e] = t[tx * 4 + e][ty];
+    __shared__ double t[32 * 33];
+    cov_add(C, P, D, nt, slices, tile0 + blockIdx.y, blockIdx.x, threadIdx.x, t);
 }
 
 // C[i, j] += sum over the slices of P[slice][i, j], for the elements the covariance kernel computed: those of the

@@ -1765,8 +1765,22 @@ int cov_tiles(int D) { const int nt = ceil_div(D, kCovTile); return nt * (nt + 1
 // bf16 keys: slices of the token axis per launch at most (each a separate fp32 output over at most 4096 tokens), so that the
 // tile sums of a launch stay near 280 MB
 int cov_max_slices(int D) { return std::min(64, std::max(2, 1088 / cov_tiles(D))); }
-// ... and of a launch over n tokens: the number with the smallest estimated duration in us (rounds of one workgroup per
-// compute unit, 0.95 us per 32 tokens, 8 us to start and to store a tile; 0.05 us to add a tile up)
+// Tiles of a first launch, which fill the chip (one workgroup per compute unit) a whole number of times: the second launch has
+// the tiles left and, on the compute units that its part of a round leaves idle, the additions of the first.  0: one launch for
+// all.  Estimated durations in us: a round 0.95 per 32 tokens and 8 to start and to store a tile; the additions 0.05 per tile and
+// slice and 0.3 per tile; 12 for the start and the uneven end of another launch.
+int cov_first_tiles(int tiles, int slices, int64_t slice_steps, double* us)
+{
+    const double round = (double)slice_steps * 0.95 + 8.0, add = 0.05 * slices + 0.3;
+    const int whole = tiles * slices / 256, first = whole * 256 / slices, rest = (tiles - first) * slices;
+    *us = ceil_div(tiles * slices, 256) * round + add * tiles;
+    if (first == 0 || rest == 0 || rest >= 256) return 0;
+    const double two = whole * round + std::max(round, add * first * 256 / (256 - rest)) + add * (tiles - first) + 12.0;
+    if (two >= *us) return 0;
+    *us = two;
+    return first;
+}
+// ... and of a batch of n tokens: the number with the smallest estimated duration
 int cov_slices(int D, int64_t n)
 {
     const int tiles = cov_tiles(D), lo = (int)((n + kCalChunk - 1) / kCalChunk);
@@ -1774,7 +1788,8 @@ int cov_slices(int D, int64_t n)
     int best = lo;
     double best_us = 1e30;
     for (int s = lo; s <= cov_max_slices(D) && s <= steps; ++s) {
-        const double us = (double)ceil_div(tiles * s, 256) * ((double)((steps + s - 1) / s) * 0.95 + 8.0) + 0.05 * tiles * s;
+        double us;
+        cov_first_tiles(tiles, s, (steps + s - 1) / s, &us);
         if (us < best_us) { best_us = us; best = s; }
     }
     return best;
@@ -1791,9 +1806,15 @@ sals_status calib_accumulate_bf16(const void* K, int64_t n_tok, int D, double* C
         const int want = cov_slices(D, n);
         const int slice_tok = (int)((steps + want - 1) / want) * kCovStep;   // (at most 4096: want >= n / 4096)
         const int slices = (int)((n + slice_tok - 1) / slice_tok);
-        hipLaunchKernelGGL(calib_cov_kernel, dim3(tiles * slices), dim3(512), kCovLds, st, X + (size_t)t0 * D, (long long)n, D, nt,
-                           slice_tok, slices, P);
-        hipLaunchKernelGGL(calib_cov_reduce_kernel, dim3(64, tiles), dim3(256), 0, st, C, P, D, nt, slices);
+        double us;
+        const int first = cov_first_tiles(tiles, slices, slice_tok / kCovStep, &us);
+        auto launch = [&](int tile0, int count, int add) {  // tiles' sums, and the additions of the first `add` tiles
+            hipLaunchKernelGGL(calib_cov_kernel, dim3(count * slices + add * 32), dim3(512), kCovLds, st, X + (size_t)t0 * D, (long long)n,
+                               D, nt, slice_tok, slices, P, tile0, count, C);
+        };
+        if (first > 0) launch(0, first, 0);
+        launch(first, tiles - first, first);
+        hipLaunchKernelGGL(calib_cov_reduce_kernel, dim3(64, tiles - first), dim3(256), 0, st, C, P, D, nt, slices, first);
         if (launch_status() != SALS_OK) return SALS_ERR_HIP;
     }
     return SALS_OK;

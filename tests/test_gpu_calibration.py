@@ -68,6 +68,12 @@ def test_covariance_tile_and_slice_remainders(D, n):
     assert torch.equal(C, C.T)
 
 
+@pytest.mark.parametrize("D,n", [(4096, 4096), (3968, 12001), (4096, 9000)])
+def test_covariance_with_additions_beside_the_last_round(D, n):
+    """Batches whose tiles take whole rounds of the chip and a part: the part's launch also adds up the others."""
+    test_covariance_tile_and_slice_remainders(D, n)
+
+
 def test_covariance_accumulates_over_calls():
     print("[case] covariance in two calls", flush=True)
     X = synth.make_calibration_keys(7, 6000, 256, "bf16", decay=0.95)
