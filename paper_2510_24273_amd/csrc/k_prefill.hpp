@@ -200,14 +200,17 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_compress_kernel(Prefill
 // Matrix-bound while the whole chip works (22 ns per MFMA and SIMD at the clock its power leaves, 13.4 with few workgroups);
 // what is lost to it is the last round of tiles and 2 (smallest tile) to 13 us (largest) per round to start and store.  Whole
 // calls, with the launch that advances the lengths, against the 256 x 128 and 128 x 128 tiles staged through registers, two
-// workgroups per compute unit, that this replaced: 6 ragged prompts of up to 4001 tokens, D = 1024, r = 640 91 -> 78 us;
-// 6000 tokens, D = 4096, r = 1024 125 -> 99 us; 64 tokens, D = 4096 44 -> 20 us.
+// workgroups per compute unit, that this replaced: 6 ragged prompts of up to 4001 tokens, D = 1024, r = 640 91 -> 78 us
+// (68 to 73 now, from card to card); 6000 tokens, D = 4096, r = 1024 125 -> 99 us; 64 tokens, D = 4096 44 -> 20 us.
 // Tiles: without n_new the prompts of a batch are one run of B n_tok rows (a tile may span sequences); with n_new every
 // sequence has tiles of its own and only those that hold tokens are in the list (its length is known on the device only, so
 // the launch covers n_tok everywhere and the workgroups past the end leave at once).
-// One launch may take all tiles, or two launches share them: the first one (kPfBig) as many 256-row tiles as fill whole
-// rounds of the chip with its per_big workgroups each, the second one (kPfTail) the rest in smaller tiles, unless that rest
-// is more than tail_max row tiles (then the first launch takes them too).  Both derive the split from the token counts.
+// All tiles alike, or two kinds in a launch (prefill_split_kernel): the first workgroups (kPfBig) as many 256-row tiles as fill
+// whole rounds of the chip with per_big workgroups each, the others (kPfTail) the rest in smaller tiles, unless that rest is more
+// than tail_max row tiles (then the first take them too).  Both derive the split from the token counts.  The smaller tiles start
+// as the compute units get free: in a launch of their own, behind the last of the whole tiles, 6 ragged
+// prompts of up to 4001 tokens (D = 1024, r = 640) took 73 to 74 us instead of 68, 1 x 20000 73.2 instead of 70.2, 4097 tokens of
+// D = 4096, r = 1024 102.5 instead of 98.9.
 enum { kPfAll = 0, kPfBig = 1, kPfTail = 2 };
 struct PfPart { int part, per_big, tail_max; };
 template <int NBW, int NBT> struct pf_cfg {
@@ -217,7 +220,7 @@ template <int NBW, int NBT> struct pf_cfg {
     static constexpr int PIECES = TN / 16;   // 1 KB pieces of the projector side per step
 };
 template <int NBW, int NBT>
-__global__ __launch_bounds__(kPfThreads, 2) void prefill_tile_kernel(PrefillArgs a, int n_col, PfPart p)
+__device__ __forceinline__ void prefill_tile(const PrefillArgs& a, int block, int n_col, const PfPart& p)
 {
     typedef pf_cfg<NBW, NBT> C;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];  // [stage][projector rows | token rows]
@@ -251,8 +254,8 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_tile_kernel(PrefillArgs
             count = p.part == kPfTail ? (n_tiles - whole) * SUB : whole;
         }
         const int total = count * per_tile;
-        if ((int)blockIdx.x >= total) return;  // uniform
-        const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds, qn = total / kXcds, rem = total % kXcds;
+        if (block >= total) return;  // uniform
+        const int xcd = block % kXcds, slot = block / kXcds, qn = total / kXcds, rem = total % kXcds;
         const int w = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + slot;
         int tile = w / per_tile;
         const int rest = w - tile * per_tile;
@@ -363,6 +366,10 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_tile_kernel(PrefillArgs
     Frags F0, F1;
 #pragma unroll
     for (int i = 0; i < NBW + NBT; ++i) read_frag(F0, i, 0, 0);
+    // With small tiles a step is so short that it is felt where the loop lies in the lines of the instruction cache (64 tokens,
+    // D = 4096, r = 1024: 20.4 us a call at the start of a line, 21.1 to 21.5 elsewhere).  Aligned here, with room for the 24 bytes
+    // that set up the loop of the smallest tiles (a loop alignment given to the compiler is not observed).
+    asm volatile(".p2align 6\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0");
     for (int s0 = 0; s0 < n_steps; s0 += 4) {  // (n_steps is a multiple of 4)
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -394,6 +401,20 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_tile_kernel(PrefillArgs
             }
         }
     }
+}
+
+template <int NBW, int NBT>
+__global__ __launch_bounds__(kPfThreads, 2) void prefill_tile_kernel(PrefillArgs a, int n_col)
+{
+    prefill_tile<NBW, NBT>(a, (int)blockIdx.x, n_col, PfPart{kPfAll, 0, 0});
+}
+// n_big workgroups for the whole rounds of tiles of 256 rows, the others for the rest in tiles of 128 rows x 64 UBW coordinates
+template <int NBW, int UBW>
+__global__ __launch_bounds__(kPfThreads, 2) void prefill_split_kernel(PrefillArgs a, int n_col, int n_big, int n_col_rest, int tail_max)
+{
+    const int per_big = 2 * n_col;
+    if ((int)blockIdx.x < n_big) prefill_tile<NBW, 2>(a, (int)blockIdx.x, n_col, PfPart{kPfBig, per_big, tail_max});
+    else prefill_tile<UBW, 1>(a, (int)blockIdx.x - n_big, n_col_rest, PfPart{kPfTail, per_big, tail_max});
 }
 
 // after a bulk append: advance every sequence by its token count (separate launch, so that every cache row

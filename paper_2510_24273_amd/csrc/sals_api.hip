@@ -1073,12 +1073,12 @@ namespace {
 // Tiles of the bf16 prompt compression: the choice with the smallest estimated duration in us, where a round of one workgroup
 // per compute unit takes (64-byte steps of the D axis x measured time per step + start and store of a tile).  A step takes
 // `full` with the whole chip at work (the matrix cores' clock follows the power drawn) and `idle` with few workgroups.
-// The tiles that do not fill a round may go to a second launch with smaller ones (see PfPart), 2 us more.
+// The tiles that do not fill a round may become smaller ones (see PfPart).
 struct PrefillTile { int nbw, nbt; double idle, full, over; };
 constexpr PrefillTile kPrefillTiles[] = {
     {1, 1, 0.105, 0.20, 2.0}, {2, 1, 0.145, 0.286, 3.0}, {3, 1, 0.19, 0.38, 4.0},
     {2, 2, 0.255, 0.45, 6.0}, {4, 2, 0.475, 0.68, 12.0}, {5, 2, 0.58, 0.82, 13.0}};
-struct PrefillPlan { PrefillTile main, tail; int tail_max; };  // tail_max == 0: one launch
+struct PrefillPlan { PrefillTile main, tail; int tail_max; };  // tail_max == 0: all tiles alike
 PrefillPlan plan_prefill(const sals_desc& d, int n_tok)
 {
     PrefillPlan best{kPrefillTiles[0], kPrefillTiles[0], 0};
@@ -1099,7 +1099,7 @@ PrefillPlan plan_prefill(const sals_desc& d, int n_tok)
         if (whole == 0 || whole == row_tiles) continue;
         for (const PrefillTile& u : kPrefillTiles) {
             if (u.nbt != 1) continue;
-            const double us2 = rounds_us(t, (double)whole * per) + rounds_us(u, (double)(row_tiles - whole) * 2 * per_row_tile(u)) + 2.0;
+            const double us2 = rounds_us(t, (double)whole * per) + rounds_us(u, (double)(row_tiles - whole) * 2 * per_row_tile(u));
             // (the token counts may be smaller than n_tok: the tail is used for any rest up to this one or two thirds of a round)
             if (us2 < best_us) { best_us = us2; best = PrefillPlan{t, u, std::max((int)(row_tiles - whole), 171 / per)}; }
         }
@@ -1129,24 +1129,35 @@ sals_status sals_compress_prefill(sals_ctx* ctx, const void* k_new, const void* 
     ProfScope ps(ctx, SALS_K_PREFILL, st);
     if (bf) {
         const PrefillPlan P = plan_prefill(d, n_tok);
-        for (int pass = 0; pass < (P.tail_max ? 2 : 1); ++pass) {
-            const PrefillTile t = pass ? P.tail : P.main;
-            const int n_col = ceil_div(d.r, 64 * t.nbw), tm = 128 * t.nbt;
-            const PfPart part{P.tail_max ? (pass ? kPfTail : kPfBig) : kPfAll, 2 * ceil_div(d.r, 64 * P.main.nbw), P.tail_max};
-            // every token tile a batch of these sizes can have in this launch (workgroups past the tiles that hold tokens leave)
-            const int all = n_new ? d.B * ceil_div(n_tok, tm) : (int)(((long long)d.B * n_tok + tm - 1) / tm);
-            const int n_tiles = pass ? std::min(all, P.tail_max * (256 / tm)) : all;
+        const PrefillTile t = P.main;
+        const int n_col = ceil_div(d.r, 64 * t.nbw), tm = 128 * t.nbt;
+        // every token tile a batch of these sizes can have (workgroups past the tiles that hold tokens leave)
+        const int n_tiles = n_new ? d.B * ceil_div(n_tok, tm) : (int)(((long long)d.B * n_tok + tm - 1) / tm);
+        if (P.tail_max == 0) {
 #define SALS_PREFILL(N, T)                                                                                              \
-            else if (t.nbw == N && t.nbt == T) {                                                                        \
+            if (t.nbw == N && t.nbt == T) {                                                                             \
                 auto kern = prefill_tile_kernel<N, T>;                                                                  \
                 constexpr size_t lds = pf_cfg<N, T>::LDS;                                                               \
                 if (!allow(reinterpret_cast<const void*>(kern), lds)) return SALS_ERR_HIP;                              \
-                hipLaunchKernelGGL(kern, dim3(n_tiles * 2 * n_col), dim3(kPfThreads), lds, st, a, n_col, part);          \
+                hipLaunchKernelGGL(kern, dim3(n_tiles * 2 * n_col), dim3(kPfThreads), lds, st, a, n_col);                \
             }
-            if (false) {}
             SALS_PREFILL(1, 1) SALS_PREFILL(2, 1) SALS_PREFILL(3, 1) SALS_PREFILL(2, 2) SALS_PREFILL(4, 2) SALS_PREFILL(5, 2)
-            if (launch_status() != SALS_OK) return SALS_ERR_HIP;
+        } else {
+            const int n_col_rest = ceil_div(d.r, 64 * P.tail.nbw), n_rest = std::min(n_tiles, P.tail_max) * 2 * 2 * n_col_rest;
+            const int n_big = ceil_div(n_tiles * 2 * n_col, kXcds) * kXcds;  // (either kind is dealt to the XCDs from the first on)
+#define SALS_PREFILL_SPLIT(N, U)                                                                                        \
+            if (t.nbw == N && P.tail.nbw == U) {                                                                        \
+                auto kern = prefill_split_kernel<N, U>;                                                                 \
+                constexpr size_t lds = std::max(pf_cfg<N, 2>::LDS, pf_cfg<U, 1>::LDS);                                  \
+                if (!allow(reinterpret_cast<const void*>(kern), lds)) return SALS_ERR_HIP;                              \
+                hipLaunchKernelGGL(kern, dim3(n_big + n_rest), dim3(kPfThreads), lds, st, a, n_col, n_big, n_col_rest,   \
+                                   P.tail_max);                                                                         \
+            }
+            SALS_PREFILL_SPLIT(2, 1) SALS_PREFILL_SPLIT(2, 2) SALS_PREFILL_SPLIT(2, 3) SALS_PREFILL_SPLIT(4, 1) SALS_PREFILL_SPLIT(4, 2)
+            SALS_PREFILL_SPLIT(4, 3) SALS_PREFILL_SPLIT(5, 1) SALS_PREFILL_SPLIT(5, 2) SALS_PREFILL_SPLIT(5, 3)
         }
+        if (launch_status() != SALS_OK) return SALS_ERR_HIP;
+#undef SALS_PREFILL_SPLIT
 #undef SALS_PREFILL
     } else {
         const int nl = d.r % 128 == 0 ? 128 : 64;

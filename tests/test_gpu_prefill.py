@@ -157,3 +157,15 @@ def test_tile_shapes_and_remainders(B, n_tok, H_kv, r, lens):
         assert bool((err[live] <= 0).all()), float(err[live].max())
         assert bool((c[~live] == 7.0).all()), "a row outside the prompt was written"
     ctx.close()
+
+
+@pytest.mark.parametrize("B,n_tok,H_kv,r,lens", [
+    (1, 20483, 2, 256, None),                  # 256 x 128, the rest in 128 x 128
+    (1, 16396, 8, 320, None),                  # 256 x 128 and 128 x 192
+    (2, 8198, 8, 448, [8198, 8100]),           # 256 x 256 and 128 x 64
+    (1, 18714, 8, 448, None),                  # 256 x 256 and 128 x 128
+    (1, 10784, 8, 832, None),                  # 256 x 320 and 128 x 64
+    (2, 5911, 8, 832, [5911, 5904]),           # 256 x 320 and 128 x 128
+])
+def test_two_kinds_of_tiles_in_a_launch(B, n_tok, H_kv, r, lens):
+    test_tile_shapes_and_remainders(B, n_tok, H_kv, r, lens)
