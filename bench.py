@@ -242,7 +242,7 @@ def measure_calibration(w, n_tok, steps, torch, binding, roofline):
     lam, U, sweeps = binding.calib_eigenvectors(C, w.r, dt)
     torch.cuda.synchronize()
     eig_ms = (time.perf_counter() - t0) * 1e3
-    n_steps = abs(sweeps) * (D // 16 - 1)   # a step rotates D / 32 disjoint pairs of 16-row blocks
+    n_steps = abs(sweeps) * (D // 32)   # a sweep: one step inside 32-row blocks, D / 32 - 1 steps of disjoint pairs of them
     del X, ws, dirs
     torch.cuda.empty_cache()
     return {"workload": f"calib_{w.name}", "D": D, "r": w.r, "tokens": n_tok, "covariance_us_per_call": round(us, 1),

@@ -419,9 +419,8 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
 
 /* ---- measurement aid --------------------------------------------------------------
  * Per-stage timing for roofline figures.  While enabled, every stage below (one kernel;
- * for the selection of sequences above 32768 tokens a chain of three, or of four on its own,
- * for logits whose latent axis is split two, for a prompt whose tiles do not fill whole rounds
- * two) is bracketed by a pair of HIP events on the call's stream (host-side event objects; no
+ * for the selection of long sequences a chain of two or three, or of four on its own,
+ * for logits whose latent axis is split two) is bracketed by a pair of HIP events on the call's stream (host-side event objects; no
  * device memory).  sals_profile_collect waits for the recorded events, adds the elapsed
  * milliseconds and launch counts per kernel into total_ms / launches (host arrays of
  * SALS_N_KERNELS entries, overwritten) and forgets the records.  Timing with events serialises

@@ -31,7 +31,6 @@ namespace sals {
 
 constexpr int kTmChunk = 8192;            // scores per workgroup
 constexpr int kTmF4 = kTmChunk / (4 * kTopkThreads);  // float4 groups per thread: 2
-constexpr int kTmStepMin = 16384;         // a decode step uses the chain above this, where its logits kernel can rank (see make_layout)
 constexpr int kTmBins = 2048;
 constexpr int kTmMaxChunks = 128;         // S_max <= 2^20
 constexpr int kTmCand = 512;              // candidates the finish kernel ranks

@@ -50,7 +50,6 @@ struct Layout {  // byte offsets into the workspace
     int dn_chunks, dn_tok;       // dense baseline: token chunks per sequence (overlap score: tokens per chunk)
     int proj_np;                 // D-axis slices of the query projection
     int tm_chunks;               // chunks of the multi-workgroup selection (0: one workgroup per sequence)
-    int tm_step_chunks;          // the same inside a decode step whose logits kernel ranks the threshold bin
     size_t w_section;            // elements per section of the packed weights
 };
 
@@ -211,16 +210,14 @@ Layout make_layout(const sals_desc& d)
         L.dn_chunks = ceil_div(d.S_max, L.dn_tok);
         L.dn_part = take((size_t)d.B * d.H_q * L.dn_chunks * kDnRec * 4);
     }
-    // Long sequences: selection spread over 8192-score chunks.  On its own from 32769 scores on, where topk_kernel's keys no
-    // longer fit in registers (the one launch takes 13.4 us at 32768 scores and 7.9 at 16384, the chain of four launches 17.9 and,
-    // at 131072, 18.4).  In a decode step the chain has two launches (the score kernel leaves the ranges, the logits kernel ranks
-    // the threshold bin) and is faster from topk_kernel's widest instance on: whole steps of 4 x (2048 of S), H_kv 32, r 1024 take
-    // 145.2 against 145.8 us at S 17408, 152.4 against 153.4 at 24576, 162.4 against 163.0 at 32768; of 1 x (1024 of S) 55.9 against
-    // 56.7, 56.5 against 57.8, 59.7 against 61.4.  Beyond 32768 it saves the finish launch: 170.9 against 173.0 and 63.0 against
-    // 64.7 at 40960, and 1 x (2048 of 131072), H_kv 8 65.0 against 68.2.
+    // Long sequences: selection spread over 8192-score chunks, from 32769 scores on, where topk_kernel's keys no longer fit in
+    // registers: on its own the one launch takes 13.4 us at 32768 scores and 7.9 at 16384, the chain of four launches 17.9 and, at
+    // 131072, 18.4.  In a decode step the chain has two launches (the score kernel leaves the ranges, the logits kernel ranks the
+    // threshold bin), which beat the one launch from 16385 scores on (whole steps of 1 x (1024 of 32768), H_kv 32, r 1024 59.7
+    // against 61.4 us), but order the list in another way; a step leaves the list that the selection call leaves, so both take the
+    // same line.
     L.tm_chunks = d.S_max > 32768 ? ceil_div(d.S_max, kTmChunk) : 0;
-    L.tm_step_chunks = d.S_max > kTmStepMin ? ceil_div(d.S_max, kTmChunk) : 0;
-    if (const int n = L.tm_step_chunks) {
+    if (const int n = L.tm_chunks) {
         L.tm_part = take((size_t)d.B * n * sizeof(uint2));
         L.tm_hist = take((size_t)d.B * n * kTmRow * 4);
         L.tm_meta = take((size_t)d.B * sizeof(TopkMeta));
@@ -344,9 +341,7 @@ sals_status launch_scores(const sals_ctx* c, const void* Kc, const int32_t* seq_
 }
 
 // whether a decode step ranks the threshold bin in its logits kernel (the shapes with tiles of 128 and 256 tokens)
-bool step_resolves(const sals_ctx* c) { return c->L.tm_step_chunks > 0 && (c->plan.pick == 1 || c->plan.pick == 2) && c->fuse_select; }
-// whether a decode step selects by the chunked chain, whose ranges its score kernel leaves
-bool step_chain(const sals_ctx* c) { return c->L.tm_chunks > 0 || step_resolves(c); }
+bool step_resolves(const sals_ctx* c) { return c->L.tm_chunks > 0 && (c->plan.pick == 1 || c->plan.pick == 2) && c->fuse_select; }
 TopkResolve topk_resolve(const sals_ctx* c, int32_t* idx)
 {
     return TopkResolve{reinterpret_cast<const TopkMeta*>(c->ws + c->L.tm_meta), reinterpret_cast<const uint2*>(c->ws + c->L.tm_cand), idx,
@@ -367,9 +362,9 @@ sals_status launch_topk(const sals_ctx* c, const float* scores, const int32_t* s
 #define SALS_TOPK(F4)                                                                                \
     hipLaunchKernelGGL((topk_kernel<F4>), grid, block, 0, st, scores, seq_len, idx, n_sel, d.S_max, \
                        d.top_k, d.n_sink, d.n_recent)
-    if (c->L.tm_chunks > 0 || (in_step && step_chain(c))) {
+    if (c->L.tm_chunks > 0) {
         const Layout& L = c->L;
-        const int nc = L.tm_step_chunks;
+        const int nc = L.tm_chunks;
         TopkMultiWs ws{};
         ws.part = reinterpret_cast<uint2*>(c->ws + L.tm_part); ws.hist = reinterpret_cast<uint32_t*>(c->ws + L.tm_hist);
         ws.meta = reinterpret_cast<TopkMeta*>(c->ws + L.tm_meta); ws.cand = reinterpret_cast<uint2*>(c->ws + L.tm_cand);
@@ -1199,7 +1194,7 @@ sals_status step_scores(sals_ctx* ctx, const void* q, const void* W, const void*
                         ? launch_project<bf16_t>(ctx, W, q, st)
                         : launch_project<float>(ctx, W, q, st);
     if (s != SALS_OK) return s;
-    uint2* wg_range = step_chain(ctx) ? reinterpret_cast<uint2*>(ctx->ws + ctx->L.tm_srange) : nullptr;
+    uint2* wg_range = ctx->L.tm_chunks > 0 ? reinterpret_cast<uint2*>(ctx->ws + ctx->L.tm_srange) : nullptr;
     return ctx->d.dtype == SALS_BF16 ? launch_scores<bf16_t>(ctx, Kc, seq_len, scores, st, wg_range)
                                      : launch_scores<float>(ctx, Kc, seq_len, scores, st, wg_range);
 }

@@ -592,15 +592,15 @@ def test_selection_inside_split_logits(dtype, H_kv, r, S, top_k, lens, monkeypat
 
 
 @pytest.mark.parametrize("pick,dtype,H_kv,r,S,top_k,n_sink,lens,copies", [
-    (1, "bf16", 8, 128, 16388, 700, 4, [16388, 16001], 1),    # the shortest; ranked entries in the last of three tiles
+    (1, "bf16", 8, 128, 32772, 700, 4, [32772, 32001], 1),    # the shortest; ranked entries in the last of three tiles
     (1, "bf16", 2, 256, 33000, 252, 0, [33000], 1),           # entries up to a tile's end
-    (2, "bf16", 8, 512, 20000, 1000, 3, [19999, 700, 0], 3),  # ties; a sequence shorter than the selection, an empty one
-    (2, "f32", 4, 64, 17000, 300, 4, [17000, 371], 37),       # more ties; one token more than the selection
-    (1, "f32", 4, 128, 16400, 130, 1, [16400], 1),
-    (2, "bf16", 4, 128, 20000, 1, 0, [20000], 1),             # one entry
-    (2, "bf16", 4, 128, 20000, 200, 4, [20000, 9000], 1000)]) # more members than are ranked: selected from scratch
+    (2, "bf16", 8, 512, 40000, 1000, 3, [39999, 700, 0], 3),  # ties; a sequence shorter than the selection, an empty one
+    (2, "f32", 4, 64, 33000, 300, 4, [33000, 371], 37),       # more ties; one token more than the selection
+    (1, "f32", 4, 128, 41000, 130, 1, [41000], 1),
+    (2, "bf16", 4, 128, 36000, 1, 0, [36000], 1),             # one entry
+    (2, "bf16", 4, 128, 36000, 200, 4, [36000, 9000], 1000)]) # more members than are ranked: selected from scratch
 def test_threshold_bin_ranked_by_the_logits_kernel(pick, dtype, H_kv, r, S, top_k, n_sink, lens, copies, monkeypatch):
-    """A step on a long cache leaves the ranking of the threshold bin to its logits kernel: the list is the selection's set on the
+    """A step on a long cache leaves the ranking of the threshold bin to its logits kernel: the list is the selection call's on the
     step's scores, and the output is, bit for bit, what the attention call gives on that list."""
     print(f"[case] ranked in logits pick={pick} {dtype} H_kv={H_kv} r={r} S={S} k={top_k} lens={lens} copies={copies}", flush=True)
     monkeypatch.setenv("SALS_TUNE_LOGITS", str(pick))
@@ -623,6 +623,6 @@ def test_threshold_bin_ranked_by_the_logits_kernel(pick, dtype, H_kv, r, S, top_
         assert n.tolist() == n2.tolist() == [min(s, w.k_tot) for s in lens]
         for b in range(w.B):
             k = int(n[b])
-            assert torch.equal(idx[b, :k].sort().values, idx2[b, :k].sort().values)
+            assert torch.equal(idx[b, :k], idx2[b, :k])
         assert torch.equal(out.view(torch.int16), out2.view(torch.int16))
     ctx.close()
