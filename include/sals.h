@@ -397,12 +397,15 @@ sals_status sals_overlap_score(sals_ctx* ctx, const void* q, const int32_t* q_po
  *                                      sals_pack_weights takes.  Eigenvalues below 1e-13 of the largest are zero to
  *                                      working precision: their vectors are not resolved (some direction of the space
  *                                      they span together); negative ones are returned as zero.
- *   workspace  device, 256-byte aligned, at least sals_calib_eigenvectors_workspace_bytes(D) bytes (the factor, the
- *              last angles between its rows and a partial sum of their series, 8 D^2 bytes each, and some D of scratch)
+ *   workspace  device, 256-byte aligned, sals_calib_eigenvectors_workspace_bytes(D) bytes (the factor and two partial
+ *              sums of a series, 8 D^2 bytes each, and some D of scratch).  Fewer are taken from 8 D^2 + 900 D on
+ *              (SALS_ERR_WORKSPACE below what the sweeps need): the last rotations are then made by one to three
+ *              further sweeps, whose sums are spread over as much of the device as the scratch allows (D = 1024:
+ *              9.9 ms with the full size, 11.2 with 8 D^2 + 4000 D bytes, 16.9 with the least)
  *   max_sweeps at least 1 (host): a sweep rotates every pair of rows once; the call stops when no rotation that
  *              involves one of the r largest rows would turn by more than 1e-11 (found by a sweep, or from the Gram
- *              matrix of all rows behind a sweep of small rotations; the last, smallest rotations are made all at
- *              once), or after max_sweeps
+ *              matrix of all rows behind a sweep of small rotations; with a workspace of the full size the last,
+ *              smallest rotations are made all at once), or after max_sweeps
  *   sweeps     host int32, out (may be NULL): sweeps run; the negative of that number if the limit was reached
  *              before convergence (the results are then the current approximation); 0 if there was nothing to
  *              rotate (C is zero, or not finite: then its rows come back as they are)

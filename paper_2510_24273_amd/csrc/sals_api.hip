@@ -1886,9 +1886,10 @@ int jac_slices(int D)
     return s;
 }
 struct EigWs {  // byte offsets into the workspace
-    size_t G, conv, norm, sgn, diag, part, E, Y, total;
+    size_t G, conv, norm, sgn, diag, part, Y0, Y1, total;
 };
-EigWs eig_ws(int D)
+// `n_part` slices of the Gram matrices; `series`: with the two partial sums that making the last rotations all at once takes.
+EigWs eig_ws(int D, int n_part, bool series)
 {
     EigWs w{};
     size_t o = 0;
@@ -1899,18 +1900,33 @@ EigWs eig_ws(int D)
     w.sgn = take((size_t)D * 8);
     w.diag = take((size_t)D * kCalPanel * 8);    // factored diagonal blocks
     // partial Gram matrices of a step: of the blocks, or of pairs of them
-    w.part = take((size_t)jac_gram_slices(D) * (D / kJacBig) * std::max(kJacRec, kJacBigRec / 2) * 8);
-    w.E = take((size_t)D * D * 8);               // the last angles between the rows
-    w.Y = take((size_t)D * D * 8);               // a partial sum of their series
+    w.part = take((size_t)n_part * (D / kJacBig) * std::max(kJacRec, kJacBigRec / 2) * 8);
+    w.Y0 = take(series ? (size_t)D * D * 8 : 0);
+    w.Y1 = take(series ? (size_t)D * D * 8 : 0);
     w.total = o;
     return w;
+}
+// What a workspace of `bytes` allows: with less than the full size sweeps alone, and as many slices as fit (a slice of the Gram
+// matrices is 320 D bytes: with one of them all of it is less than 8 D^2 + 900 D).
+bool eig_plan(int D, size_t bytes, EigWs* w, int* n_part, bool* series)
+{
+    *n_part = jac_gram_slices(D);
+    *series = true;
+    *w = eig_ws(D, *n_part, true);
+    if (bytes >= w->total) return true;
+    *series = false;
+    for (;; *n_part /= 2) {
+        *w = eig_ws(D, *n_part, false);
+        if (bytes >= w->total) return true;
+        if (*n_part == 1) return false;
+    }
 }
 }  // namespace
 
 size_t sals_calib_eigenvectors_workspace_bytes(int32_t D)
 {
     if (D < kCalThreads || D % kCalThreads != 0 || D > kCalMaxD) return 0;
-    return eig_ws(D).total;
+    return eig_ws(D, jac_gram_slices(D), true).total;
 }
 
 sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dtype, double* eigval, void* U, void* workspace,
@@ -1919,17 +1935,18 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     if ((dtype != SALS_BF16 && dtype != SALS_F32) || bad(C) || !eigval || bad(U) || D < kCalThreads || D % kCalThreads != 0 ||
         D > kCalMaxD || r < 1 || r > D || max_sweeps < 1)
         return SALS_ERR_INVALID_ARG;
-    if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0 ||
-        workspace_bytes < sals_calib_eigenvectors_workspace_bytes(D))
+    EigWs off;
+    int n_part;
+    bool series;
+    if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0 || !eig_plan(D, workspace_bytes, &off, &n_part, &series))
         return SALS_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     unsigned char* ws = static_cast<unsigned char*>(workspace);
-    const EigWs off = eig_ws(D);
     auto at = [&](size_t o) { return reinterpret_cast<double*>(ws + o); };
     double *G = at(off.G), *conv = at(off.conv), *norm = at(off.norm), *sgn = at(off.sgn), *diag = at(off.diag), *part = at(off.part);
     int* fail = reinterpret_cast<int*>(ws + off.conv);
     const int n_blocks = D / kJacBig, n_pairs = n_blocks / 2, n_steps = n_blocks - 1;
-    const int n_part = jac_gram_slices(D), slices = jac_slices(D);
+    const int slices = jac_slices(D);
     const int n_tiles = D / 64 * (D / 64 + 1) / 2;   // of the angles, which lie where the partial Gram matrices do
     f64x2* const found = reinterpret_cast<f64x2*>(part);
     std::vector<double> h_conv((size_t)n_blocks), h_norm((size_t)D);
@@ -1996,9 +2013,10 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         converged = worst <= 1e-11;
         lead = leading();
         // Behind a sweep of small rotations the angles that are left decide: converged, or all of them at once, or a further sweep.
-        // (Sweeps whose largest rotation was 0.26, 0.07, 0.007 left 4e-5, 1e-3, 4e-6.)
+        // (Sweeps whose largest rotation was 0.26, 0.07, 0.007 left 4e-5, 1e-3, 4e-6.)  The angles lie in C, which is free until its
+        // rows are written.
         for (int pass = 0; !converged && worst <= 0.3 && pass < 4; ++pass) {
-            hipLaunchKernelGGL(calib_jacobi_angles_kernel, dim3(n_tiles), dim3(512), 0, st, G, D, norm, lead, at(off.E), found);
+            hipLaunchKernelGGL(calib_jacobi_angles_kernel, dim3(n_tiles), dim3(512), 0, st, G, D, norm, lead, C, found);
             if (launch_status() != SALS_OK ||
                 hipMemcpyAsync(h_found.data(), found, h_found.size() * sizeof(h_found[0]), hipMemcpyDeviceToHost, st) != hipSuccess ||
                 hipStreamSynchronize(st) != hipSuccess)
@@ -2006,14 +2024,14 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             double most = 0.0, square = 0.0;
             for (const auto& f : h_found) { most = std::max(most, f[0]); square += f[1]; }
             converged = most <= 1e-11;
-            if (converged || !(square <= 1.6e-5)) break;
-            // exp(E) G from the inside out: G + E (G + E/2 (G + E/3 (G + E/4 G))); C is free until its rows are written
-            double *X = G, *Y = C;
+            if (converged || !series || !(square <= 1.6e-5)) break;
+            // exp(E) G from the inside out: G + E (G + E/2 (G + E/3 (G + E/4 G)))
+            double *X = G, *Y = at(off.Y0);
             for (int k = square <= 4e-8 ? 2 : 4; k >= 1; --k) {
                 if (k == 1) Y = G;
-                hipLaunchKernelGGL(calib_jacobi_apply_kernel, dim3(D / 64, D / 64), dim3(512), 0, st, at(off.E), X, G, 1.0 / k, Y, D);
+                hipLaunchKernelGGL(calib_jacobi_apply_kernel, dim3(D / 64, D / 64), dim3(512), 0, st, C, X, G, 1.0 / k, Y, D);
                 X = Y;
-                Y = X == C ? at(off.Y) : C;
+                Y = X == at(off.Y0) ? at(off.Y1) : at(off.Y0);
             }
             if (!row_norms(G)) return SALS_ERR_HIP;
             lead = leading();

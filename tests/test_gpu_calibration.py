@@ -161,6 +161,49 @@ def test_rows_left_behind_are_orthogonal_in_fp64(D, r, decay):
     np.testing.assert_allclose(norm[lead], lam.cpu().numpy()[:r], rtol=1e-13)
 
 
+def _eig_with_workspace(C, r, nbytes):
+    """The call on a workspace of `nbytes`, which lies before bytes that must stay as they are."""
+    D = C.shape[0]
+    guard = 4096
+    ws = torch.full((nbytes + guard,), 0xA5, dtype=torch.uint8, device=gu.DEV)
+    lam = torch.empty(D, dtype=torch.float64, device=gu.DEV)
+    U = torch.empty(D, r, dtype=torch.float32, device=gu.DEV)
+    sweeps = ctypes.c_int32(0)
+    st = binding._lib.sals_calib_eigenvectors(C.data_ptr(), D, r, binding.SALS_F32, lam.data_ptr(), U.data_ptr(), ws.data_ptr(), nbytes,
+                                              80, ctypes.byref(sweeps), None)
+    torch.cuda.synchronize()
+    assert bool((ws[nbytes:] == 0xA5).all())
+    return binding.status_string(st), lam.cpu().numpy(), sweeps.value
+
+
+@pytest.mark.parametrize("D,r", [(256, 256), (768, 500), (1024, 256), (1280, 1280)])
+def test_eigenvectors_with_a_small_workspace(D, r):
+    """From 8 D^2 + 900 D bytes on the call sweeps to the end, with fewer slices where all of them do not fit: the same
+    decomposition.  With the full size the last rotations are made at once, which takes fewer sweeps on this spectrum."""
+    print(f"[case] eigenvectors, small workspace, D={D} r={r}", flush=True)
+    rng = np.random.default_rng(3 * D)
+    X = rng.standard_normal((4 * D, D)) * np.arange(1, D + 1) ** -0.5
+    C = X.T @ X
+    C = 0.5 * (C + C.T)
+    lam_ref = np.linalg.eigvalsh(C)[::-1]
+    full = binding._lib.sals_calib_eigenvectors_workspace_bytes(D)
+    assert _eig_with_workspace(gu.to_dev(C), r, 8 * D * D)[0] == "SALS_ERR_WORKSPACE"
+    ran = {}
+    for nbytes in (8 * D * D + 900 * D, 10 * D * D + 2600 * D, full - 1, full):
+        Cg = gu.to_dev(C)
+        status, lam, ran[nbytes] = _eig_with_workspace(Cg, r, nbytes)
+        assert status == "SALS_OK" and 0 < ran[nbytes] <= 30, (nbytes, status, ran)
+        rows = Cg.cpu().numpy()
+        norm = np.linalg.norm(rows, axis=1)
+        lead = np.argsort(-norm)[:r]
+        V = rows[lead] / norm[lead, None]
+        # (the bounds of test_rows_left_behind_are_orthogonal_in_fp64)
+        assert np.max(np.abs(V @ V.T - np.eye(r))) <= 2e-11
+        np.testing.assert_allclose(lam[:r], lam_ref[:r], rtol=0, atol=1e-11 * lam_ref[0])
+    print("    sweeps", ran, flush=True)
+    assert all(ran[full] < n for nbytes, n in ran.items() if nbytes != full)
+
+
 def test_eigenvectors_in_bf16_are_the_rounded_fp64_vectors():
     print("[case] eigenvectors bf16", flush=True)
     D, r = 256, 32
