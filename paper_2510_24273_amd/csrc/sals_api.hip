@@ -139,7 +139,8 @@ inline int dense_heads(const sals_desc& d)
     return d.dtype == SALS_BF16 && d.H_q / d.H_kv < 4 && d.H_kv % 2 == 0 ? 2 : 1;
 }
 
-Layout make_layout(const sals_desc& d)
+// `short_ranges`: fp32 value sums in ranges of one step of 64 tokens (otherwise of two), whose partial sums take more workspace.
+Layout make_layout(const sals_desc& d, bool short_ranges = true)
 {
     Layout L{};
     const int D = d.H_kv * d.d;
@@ -154,13 +155,13 @@ Layout make_layout(const sals_desc& d)
         if (const char* e = std::getenv("SALS_TUNE_PROJ_NP")) { const int v = std::atoi(e); if (v >= 1 && v <= kScoreMaxParts && nks % v == 0) np = v; }  // tuning aid
         L.proj_np = np;
     }
-    // value sum: split the selected tokens into ranges of whole 64-token steps (at least two steps in bf16, one in fp32, at
-    // most kPvMaxTok tokens) as long as every workgroup still gets a CU of its own (measured: a few CUs
+    // value sum: split the selected tokens into ranges of whole 64-token steps (at least two steps in bf16, one in fp32 if the
+    // workspace has room for it, at most kPvMaxTok tokens) as long as every workgroup still gets a CU of its own (measured: a few CUs
     // with two workgroups set the kernel's duration; fp32, 128 tokens, r = 512 on 16 workgroups instead of 8: 31.0 -> 30.1 us a step)
     {
         int blocks = d.r / kPvCols;
         int want = std::max(1, 256 / (blocks * d.B));
-        int n_tr = std::max(1, std::min(std::min(want, kMaxRanges), ceil_div(k_tot, (d.dtype == SALS_BF16 ? 2 : 1) * kPvTJ)));
+        int n_tr = std::max(1, std::min(std::min(want, kMaxRanges), ceil_div(k_tot, (d.dtype == SALS_F32 && short_ranges ? 1 : 2) * kPvTJ)));
         if (const char* e = std::getenv("SALS_TUNE_PV_RANGES")) n_tr = std::max(1, std::min(64, std::atoi(e)));  // tuning aid
         n_tr = std::max(n_tr, ceil_div(k_tot, kPvMaxTok));
         int tok = ceil_div(ceil_div(k_tot, n_tr), kPvTJ) * kPvTJ;
@@ -963,6 +964,7 @@ sals_status sals_create(const sals_desc* desc, void* d_workspace, size_t workspa
     sals_status s = validate(desc);
     if (s != SALS_OK) return s;
     Layout L = make_layout(*desc);
+    if (workspace_bytes < L.total) L = make_layout(*desc, false);
     if (!d_workspace || (reinterpret_cast<uintptr_t>(d_workspace) % kAlign) != 0 || workspace_bytes < L.total)
         return SALS_ERR_WORKSPACE;
     sals_ctx* c = new (std::nothrow) sals_ctx;

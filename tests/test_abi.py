@@ -137,3 +137,20 @@ def test_create_checks_workspace_and_calls_check_pointers(sb):
         lib.sals_destroy(hh)
     lib.sals_destroy(h)
     lib.sals_destroy(None)
+
+
+@pytest.mark.parametrize("kw,nbytes", [
+    (dict(B=1, S_max=64, H_kv=32, r=2048, r_score=1024, top_k=512), 1335296),
+    (dict(B=1, S_max=1000, H_kv=32, r=512, top_k=128), 1014016),
+    (dict(B=2, S_max=700, H_q=8, H_kv=8, r=128, top_k=300), 722688),
+    (dict(B=3, S_max=4096, r=640, top_k=512), 4548096)])
+def test_fp32_context_on_the_workspace_of_long_value_sum_ranges(sb, kw, nbytes):
+    """What an fp32 context needs when its value sum has ranges of 128 tokens is enough (one alignment step less is not);
+    sals_workspace_bytes, which counts ranges of 64, asks for more."""
+    desc = _desc(sb, dtype="f32", **kw)
+    assert sb.workspace_bytes(desc) > nbytes
+    h = ctypes.c_void_p()
+    at = 1 << 20   # (sals_create does not touch the workspace)
+    assert sb._lib.sals_create(ctypes.byref(desc), at, nbytes, ctypes.byref(h)) == sb.SALS_OK
+    sb._lib.sals_destroy(h)
+    assert sb._lib.sals_create(ctypes.byref(desc), at, nbytes - 256, ctypes.byref(h)) == sb.SALS_ERR_WORKSPACE

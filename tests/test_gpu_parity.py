@@ -15,7 +15,7 @@ torch = pytest.importorskip("torch")
 if not torch.cuda.is_available():
     pytest.skip("no GPU", allow_module_level=True)
 
-from paper_2510_24273_amd import synth  # noqa: E402
+from paper_2510_24273_amd import binding, synth  # noqa: E402
 from tests import gpu_util as gu  # noqa: E402
 
 C = synth.CONFIGS
@@ -61,6 +61,14 @@ def test_small_ragged_batch(oracle, dtype):
     w = synth.shrink(SMALL, dtype=dtype)
     # full, odd length, shorter than k_tot
     _run(oracle, w, seq_lens=[1000, 777, 61])
+
+
+def test_fp32_value_sum_in_long_ranges(oracle, monkeypatch):
+    """An fp32 context on a workspace without room for value-sum ranges of 64 tokens: ranges of 128."""
+    w = synth.shrink(SMALL, dtype="f32", B=2, S=700, H=8, H_kv=8, r=128, top_k=300, plant=0)
+    assert binding.workspace_bytes(gu.make_ctx(w).desc) > 722688
+    monkeypatch.setattr(binding, "workspace_bytes", lambda desc: 722688)
+    _run(oracle, w, seq_lens=[700, 301])
 
 
 def test_empty_and_single_token_sequences(oracle):
