@@ -46,12 +46,37 @@ __global__ __launch_bounds__(256) void rope_table_kernel(float2* __restrict__ ta
 
 constexpr int kMaxGroup = 8;                 // query heads per KV head
 
+// The logits kernels exist in many instantiations, and a whole step promises the bits that the staged calls leave, whichever of
+// them either runs: which of two products is rounded by itself and which is fused with the addition is written out below, not left
+// to the compiler (which had chosen otherwise from one instantiation to another: 1.4e-4 of a bf16 output, with the same accuracy).
+__device__ __forceinline__ void rotate_key(float y1, float y2, float c, float s, float& k1, float& k2)
+{
+    k1 = fmaf(y1, c, -(y2 * s));
+    k2 = fmaf(y1, s, y2 * c);
+}
+__device__ __forceinline__ void rotate_query(float x1, float x2, float2 cs, float scale, float& q1, float& q2)
+{
+    q1 = fmaf(x1, cs.x, -(x2 * cs.y)) * scale;
+    q2 = fmaf(x2, cs.x, x1 * cs.y) * scale;
+}
+// four pairs' share of q . k
+__device__ __forceinline__ float dot_pairs(const f32x4& q1, const f32x4& q2, const float (&k1)[4], const float (&k2)[4])
+{
+    float t = fmaf(q1.x, k1[0], q1.y * k1[1]);
+    t = fmaf(q1.z, k1[2], t);
+    t = fmaf(q1.w, k1[3], t);
+    t = fmaf(q2.x, k2[0], t);
+    t = fmaf(q2.y, k2[1], t);
+    t = fmaf(q2.z, k2[2], t);
+    return fmaf(q2.w, k2[3], t);
+}
+
 // softmax statistics of a set of logits: maximum m and sum of exp(x - m)
 __device__ __forceinline__ float2 stat_merge(float2 a, float2 b)
 {
     const float m = fmaxf(a.x, b.x);
     if (m == -INFINITY) return make_float2(-INFINITY, 0.f);
-    return make_float2(m, a.y * __expf(a.x - m) + b.y * __expf(b.x - m));
+    return make_float2(m, fmaf(a.y, __expf(a.x - m), b.y * __expf(b.x - m)));
 }
 
 // Logits whose latent axis was split over workgroups (64-token tiles): a slice's workgroup left its partial logits; the sum in

@@ -129,7 +129,7 @@ __device__ __forceinline__ void logits_tile(
     const int sw = MULTI ? tg * WT / 64 : 0;  // this wave's sequence within the tile
     auto seq_of = [&](int t) { return MULTI ? min(b + (t >> 6), B - 1) : b; };
     // count and query position: of this wave's sequence (MULTI: the position is needed per thread
-    // for the thread's share of the cos/sin rows, see rotate_query)
+    // for the thread's share of the cos/sin rows, see rotate_queries)
     const int n_v = ld_uniform_i32((BYLEN ? win.seq_len : n_sel) + (MULTI ? seq_of(tg * WT) : b));
     const int qpos_v = MULTI ? q_pos[seq_of(tid & ~63)] : ld_uniform_i32(q_pos + b);  // in flight with the loads below
     const int G = GFIX > 0 ? GFIX : H / H_kv;
@@ -274,7 +274,7 @@ __device__ __forceinline__ void logits_tile(
     const bool q_in_table = qpos >= 0 && qpos <= S_max;  // the table holds exactly these positions
     float2 qcs = make_float2(1.f, 0.f);
     if (tid < SQ * kPairs) qcs = rope[(size_t)(q_in_table ? qpos : 0) * kPairs + (tid & (kPairs - 1))];
-    auto rotate_query = [&]() {
+    auto rotate_queries = [&]() {
         if (tid < SQ * kPairs) {
             const int pr = tid & (kPairs - 1);
             if (!q_in_table) {
@@ -293,8 +293,7 @@ __device__ __forceinline__ void logits_tile(
                 const int p = t & (kPairs - 1), hm = t >> 6;
                 const float2 c = sCS[MULTI ? hm / G : 0][p];
                 float* dst = &sQ[0][0][0] + (size_t)((hm / G) * kMaxGroup + hm % G) * kHeadDim;
-                dst[p] = (qa[u] * c.x - qb[u] * c.y) * scale;
-                dst[kPairs + p] = (qb[u] * c.x + qa[u] * c.y) * scale;
+                rotate_query(qa[u], qb[u], c, scale, dst[p], dst[kPairs + p]);
             }
         }
     };
@@ -364,7 +363,7 @@ __device__ __forceinline__ void logits_tile(
 #pragma unroll
                 for (int i = 0; i < NBP; ++i) load_b(i, st);
             }
-        rotate_query();  // (its barrier also publishes sPos)
+        rotate_queries();  // (its barrier also publishes sPos)
 #pragma unroll
         for (int i = 0; i < NCS; ++i) {
             const int row = (wave + i * NW) * 8 + (lane >> 3);
@@ -422,11 +421,8 @@ __device__ __forceinline__ void logits_tile(
                     const f32x4 t1 = *reinterpret_cast<const f32x4*>(cb + swz(row, al * 4 + hi * 2 + 1));  // p0+2, p0+3
                     const float cc[4] = {t0.x, t0.z, t1.x, t1.z}, ss[4] = {t0.y, t0.w, t1.y, t1.w};
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const float x1 = acc[ml][nb][a * 4 + c], x2 = acc[ml + 2][nb][a * 4 + c];
-                        k1[nb][c] = x1 * cc[c] - x2 * ss[c];
-                        k2[nb][c] = x2 * cc[c] + x1 * ss[c];
-                    }
+                    for (int c = 0; c < 4; ++c)
+                        rotate_key(acc[ml][nb][a * 4 + c], acc[ml + 2][nb][a * 4 + c], cc[c], ss[c], k1[nb][c], k2[nb][c]);
                 }
 #pragma unroll
                 for (int m0 = 0; m0 < kGroupEnd; m0 += GB) {
@@ -440,10 +436,7 @@ __device__ __forceinline__ void logits_tile(
 #pragma unroll
                         for (int mi = 0; mi < GB; ++mi)
 #pragma unroll
-                            for (int nb = 0; nb < NB; ++nb)
-                                dot[m0 + mi][nb] += q1[mi].x * k1[nb][0] + q1[mi].y * k1[nb][1] + q1[mi].z * k1[nb][2] +
-                                                    q1[mi].w * k1[nb][3] + q2[mi].x * k2[nb][0] + q2[mi].y * k2[nb][1] +
-                                                    q2[mi].z * k2[nb][2] + q2[mi].w * k2[nb][3];
+                            for (int nb = 0; nb < NB; ++nb) dot[m0 + mi][nb] += dot_pairs(q1[mi], q2[mi], k1[nb], k2[nb]);
                     }
                 }
             }

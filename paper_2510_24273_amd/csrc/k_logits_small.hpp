@@ -255,10 +255,7 @@ __device__ __forceinline__ void logits_small_tile(
         sincos((double)qpos * inv.f[qp], &sn, &c);
         qcs = make_float2((float)c, (float)sn);
     }
-    if (tid < G * kPairs) {
-        sQ[tid >> 6][qp] = (qa * qcs.x - qb * qcs.y) * scale;
-        sQ[tid >> 6][kPairs + qp] = (qb * qcs.x + qa * qcs.y) * scale;
-    }
+    if (tid < G * kPairs) rotate_query(qa, qb, qcs, scale, sQ[tid >> 6][qp], sQ[tid >> 6][kPairs + qp]);
     __syncthreads();  // every product is done: the stage buffers are free
 
     // ---- the two k-step parities exchange halves: parity 0 keeps a in {0,1}, parity 1 a in {2,3}
@@ -287,8 +284,7 @@ __device__ __forceinline__ void logits_small_tile(
                 const int v = aa * 4 + c;
                 const float y1 = x1[v] + theirs[v * 64];
                 const float y2 = x2[v] + theirs[(8 + v) * 64];
-                k1[aa][c] = y1 * cc[c] - y2 * ss[c];
-                k2[aa][c] = y2 * cc[c] + y1 * ss[c];
+                rotate_key(y1, y2, cc[c], ss[c], k1[aa][c], k2[aa][c]);
             }
         }
         // partial dot products over this wave's 16 pairs, per query head of the group
@@ -302,8 +298,7 @@ __device__ __forceinline__ void logits_small_tile(
                     const int p0 = dh * 32 + (2 * ksel + aa) * 8 + hi * 4;
                     const f32x4 q1 = *reinterpret_cast<const f32x4*>(&sQ[m][p0]);
                     const f32x4 q2 = *reinterpret_cast<const f32x4*>(&sQ[m][kPairs + p0]);
-                    d += q1.x * k1[aa][0] + q1.y * k1[aa][1] + q1.z * k1[aa][2] + q1.w * k1[aa][3] +
-                         q2.x * k2[aa][0] + q2.y * k2[aa][1] + q2.z * k2[aa][2] + q2.w * k2[aa][3];
+                    d += dot_pairs(q1, q2, k1[aa], k2[aa]);
                 }
                 d += __shfl_xor(d, 32, kWave);
                 if (hi == 0) sDot[((tb * 4 + dh * 2 + ksel) * kMaxGroup + m) * 32 + l32] = d;
