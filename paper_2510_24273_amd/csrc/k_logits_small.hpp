@@ -96,17 +96,9 @@ __device__ __forceinline__ void logits_small_tile(
     SplitLogitsJob job;
     const int job_id = block * (kLsThreads / kWave) + wave;
     const bool has_job = SIDE && job_id < split.rows * split.n_parts;  // uniform
-    auto request_job = [&](int j) { const int row = j / split.n_parts; job.request(split, row, j - row * split.n_parts); };
-    if (has_job) request_job(job_id);
-    auto finish_jobs = [&]() {
-        if (!has_job) return;
-        job.finish(split);
-        // (the rest, where there are more than waves)
-        for (int j = job_id + (int)gridDim.x * (kLsThreads / kWave); j < split.rows * split.n_parts; j += (int)gridDim.x * (kLsThreads / kWave)) {
-            request_job(j);
-            job.finish(split);
-        }
-    };
+    // (never more jobs than waves: a KV head has at most kMaxGroup rows, and the other pass, over part of this one's list, no more tiles)
+    static_assert(kLsThreads / kWave >= kMaxGroup, "a wave per query head of a tile's KV head");
+    if (has_job) { const int row = job_id / split.n_parts; job.request(split, row, job_id - row * split.n_parts); }
     if constexpr (BYLEN) {
         n_v = ld_uniform_i32(win.seq_len + b);
     } else if constexpr (!FUSED) {
@@ -193,7 +185,7 @@ __device__ __forceinline__ void logits_small_tile(
     if (tok0 >= n) {  // no selected token in this tile: neutral statistics (split tiles: where they are added up)
         if (tid < G && ksplit == 1)
             stats[((size_t)b * H + (size_t)g * G + tid) * stats_stride + part] = make_float2(-INFINITY, 0.f);
-        if constexpr (SIDE) finish_jobs();
+        if (has_job) job.finish(split);
         return;
     }
     // slots past the selected tokens read the first selected row; they get no weight
@@ -324,7 +316,7 @@ __device__ __forceinline__ void logits_small_tile(
             }
         }
     }
-    if constexpr (SIDE) finish_jobs();
+    if (has_job) job.finish(split);
 }
 
 #define SALS_LS_ARGS                                                                                                     \
