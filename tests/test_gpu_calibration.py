@@ -179,7 +179,8 @@ def _eig_with_workspace(C, r, nbytes):
 @pytest.mark.parametrize("D,r", [(256, 256), (768, 500), (1024, 256), (1280, 1280)])
 def test_eigenvectors_with_a_small_workspace(D, r):
     """From 8 D^2 + 900 D bytes on the call sweeps to the end, with fewer slices where all of them do not fit: the same
-    decomposition.  With the full size the last rotations are made at once, which takes fewer sweeps on this spectrum."""
+    decomposition.  With the full size the last rotations are made at once, which takes fewer sweeps on this spectrum and leaves
+    the eigenvalues where sweeps would: what makes the rotations is orthogonal to rounding."""
     print(f"[case] eigenvectors, small workspace, D={D} r={r}", flush=True)
     rng = np.random.default_rng(3 * D)
     X = rng.standard_normal((4 * D, D)) * np.arange(1, D + 1) ** -0.5
@@ -188,7 +189,7 @@ def test_eigenvectors_with_a_small_workspace(D, r):
     lam_ref = np.linalg.eigvalsh(C)[::-1]
     full = binding._lib.sals_calib_eigenvectors_workspace_bytes(D)
     assert _eig_with_workspace(gu.to_dev(C), r, 8 * D * D)[0] == "SALS_ERR_WORKSPACE"
-    ran = {}
+    ran, lams = {}, {}
     for nbytes in (8 * D * D + 900 * D, 10 * D * D + 2600 * D, full - 1, full):
         Cg = gu.to_dev(C)
         status, lam, ran[nbytes] = _eig_with_workspace(Cg, r, nbytes)
@@ -200,7 +201,11 @@ def test_eigenvectors_with_a_small_workspace(D, r):
         # (the bounds of test_rows_left_behind_are_orthogonal_in_fp64)
         assert np.max(np.abs(V @ V.T - np.eye(r))) <= 2e-11
         np.testing.assert_allclose(lam[:r], lam_ref[:r], rtol=0, atol=1e-11 * lam_ref[0])
-    print("    sweeps", ran, flush=True)
+        lams[nbytes] = lam[:r]
+    print("    sweeps", ran, "eigenvalues apart", np.max(np.abs(lams[full] / lams[full - 1] - 1.0)), flush=True)
+    # one or two sweeps more: D / 32 steps each, sums of 64 products (2 sqrt(64) 2^-53 of a squared norm per step at most).  A
+    # series cut one term too early, or used at twice the angles it may be, leaves 1e-11 and more
+    np.testing.assert_allclose(lams[full], lams[full - 1], rtol=2 * D / 32 * 16 * 2.0 ** -53)
     assert all(ran[full] < n for nbytes, n in ran.items() if nbytes != full)
 
 

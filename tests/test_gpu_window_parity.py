@@ -3,6 +3,8 @@ higher-rank ring cache) and of the overlap score (Sec. 3.2) against the oracle, 
 Same bounds as the sparse path: selection bit-exact under the shared rule, outputs within max-abs
 2e-2 (bf16) / 1e-4 (fp32) and the tighter derived bound of tests/gpu_util.py::out_tolerances;
 ring rows written by the append within one unit in the last place of the storage type; overlap scores within 1e-4."""
+import sys
+
 import numpy as np
 import pytest
 
@@ -125,6 +127,26 @@ def test_selection_and_window_logits_in_one_launch(oracle, S, B, tiles, monkeypa
     monkeypatch.setenv("SALS_TUNE_LOGITS", tiles)
     w = synth.shrink(SMALL, B=B, S=S, H=4, H_kv=4, r=64, r_hi=128, top_k=150, plant=2)
     _case(oracle, w, seq_lens=[S, S - 1, 4000, 4097, 70][:B])
+
+
+@pytest.mark.parametrize("tiles,H,H_kv,n_recent,top_k,dtype", [
+    ("1", 32, 4, 40, 100, "bf16"),    # 64 sums (a head's window tile each) for 32 waves
+    ("2", 32, 4, 64, 60, "bf16"),     # 64 for 32
+    ("2", 16, 4, 300, 60, "bf16"),    # 160 for 96: a window of five tiles
+    ("1", 16, 4, 200, 30, "f32"),     # 128 for 32
+    ("2", 32, 4, 130, 30, "f32")])    # 192 for 64
+def test_more_window_sums_than_waves_of_the_low_rank_pass(oracle, tiles, H, H_kv, n_recent, top_k, dtype, monkeypatch):
+    """A window in latent slices, whose sums the low-rank logits kernel makes on the side, one per wave and then the rest: more
+    of them than it has waves."""
+    make = make_win_ctx
+
+    def in_64_token_tiles(w):
+        monkeypatch.setenv("SALS_TUNE_LOGITS", "3")
+        return make(w)
+    monkeypatch.setenv("SALS_TUNE_LOGITS", tiles)
+    monkeypatch.setattr(sys.modules[__name__], "make_win_ctx", in_64_token_tiles)
+    w = synth.shrink(SMALL, B=2, S=1100, H=H, H_kv=H_kv, n_recent=n_recent, top_k=top_k, r_hi=512, dtype=dtype, plant=0)
+    _case(oracle, w, seq_lens=[1100, n_recent + top_k // 2])
 
 
 @pytest.mark.parametrize("tiles", ["1", "2"])
