@@ -4,11 +4,11 @@
 #include "../../include/sals.h"
 
 #include <algorithm>
-#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <functional>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -99,14 +99,22 @@ struct ProfScope {
     {
         if (!on) return;
         rec.kernel = kernel;
-        if (hipEventCreate(&rec.start) != hipSuccess || hipEventCreate(&rec.stop) != hipSuccess) { on = false; return; }
+        on = hipEventCreate(&rec.start) == hipSuccess;
+        if (on && hipEventCreate(&rec.stop) != hipSuccess) { (void)hipEventDestroy(rec.start); on = false; }
+        if (!on) return;
+        try {
+            c->prof.push_back(rec);
+        } catch (const std::bad_alloc&) {  // (this launch is not timed)
+            (void)hipEventDestroy(rec.start);
+            (void)hipEventDestroy(rec.stop);
+            on = false;
+            return;
+        }
         (void)hipEventRecord(rec.start, st);
     }
     ~ProfScope()
     {
-        if (!on) return;
-        (void)hipEventRecord(rec.stop, st);
-        c->prof.push_back(rec);
+        if (on) (void)hipEventRecord(rec.stop, st);
     }
 };
 
@@ -1951,15 +1959,16 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     const int slices = jac_slices(D);
     const int n_tiles = D / 64 * (D / 64 + 1) / 2;   // of the angles, which lie where the partial Gram matrices do
     f64x2* const found = reinterpret_cast<f64x2*>(part);
-    std::vector<double> h_conv((size_t)n_blocks), h_norm((size_t)D);
-    std::vector<std::array<double, 2>> h_found((size_t)n_tiles);
+    const std::unique_ptr<double[]> host(new (std::nothrow) double[(size_t)n_blocks + D + 2 * n_tiles]);
+    if (!host) return SALS_ERR_HIP;
+    double *const h_conv = host.get(), *const h_norm = h_conv + n_blocks, *const h_found = h_norm + D;
     auto row_norms = [&](const double* M) -> bool {  // row norms to the host (blocking)
         hipLaunchKernelGGL(calib_rownorm_kernel, dim3(D), dim3(kCalThreads), 0, st, M, D, norm, sgn);
-        return hipMemcpyAsync(h_norm.data(), norm, (size_t)D * 8, hipMemcpyDeviceToHost, st) == hipSuccess &&
+        return hipMemcpyAsync(h_norm, norm, (size_t)D * 8, hipMemcpyDeviceToHost, st) == hipSuccess &&
                hipStreamSynchronize(st) == hipSuccess;
     };
     if (!row_norms(C)) return SALS_ERR_HIP;
-    const double n0 = *std::max_element(h_norm.begin(), h_norm.end());  // (between the largest diagonal entry and lambda_0)
+    const double n0 = *std::max_element(h_norm, h_norm + D);  // (between the largest diagonal entry and lambda_0)
     double lead = 0.0;  // first sweep: every rotation counts
     int done = 0;
     bool converged = !(n0 > 0.0) || !std::isfinite(n0);  // the zero matrix needs no rotation
@@ -1999,17 +2008,17 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                                part, n_part, lead, conv);
         }
         if (launch_status() != SALS_OK) return SALS_ERR_HIP;
-        if (hipMemcpyAsync(h_conv.data(), conv, (size_t)n_blocks * 8, hipMemcpyDeviceToHost, st) != hipSuccess) return SALS_ERR_HIP;
+        if (hipMemcpyAsync(h_conv, conv, (size_t)n_blocks * 8, hipMemcpyDeviceToHost, st) != hipSuccess) return SALS_ERR_HIP;
         if (!row_norms(G)) return SALS_ERR_HIP;
         double worst = 0.0;
-        for (double v : h_conv) worst = std::max(worst, v);
+        for (int i = 0; i < n_blocks; ++i) worst = std::max(worst, h_conv[i]);
         rotated = rotated || worst > 0.0;  // (in the first sweep every rotation is recorded)
         ++done;
         // a rotation by less than 1e-11 no longer moves an eigenvector; only pairs with a row among the r largest
         // (a little below the r-th largest norm, so that the r-th itself is in) are asked to have converged
         auto leading = [&]() {
-            std::nth_element(h_norm.begin(), h_norm.begin() + (r - 1), h_norm.end(), std::greater<double>());
-            const double nr = h_norm[(size_t)r - 1];
+            std::nth_element(h_norm, h_norm + (r - 1), h_norm + D, std::greater<double>());
+            const double nr = h_norm[r - 1];
             return 0.999 * nr * nr;
         };
         converged = worst <= 1e-11;
@@ -2020,11 +2029,11 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         for (int pass = 0; !converged && worst <= 0.3 && pass < 4; ++pass) {
             hipLaunchKernelGGL(calib_jacobi_angles_kernel, dim3(n_tiles), dim3(512), 0, st, G, D, norm, lead, C, found);
             if (launch_status() != SALS_OK ||
-                hipMemcpyAsync(h_found.data(), found, h_found.size() * sizeof(h_found[0]), hipMemcpyDeviceToHost, st) != hipSuccess ||
+                hipMemcpyAsync(h_found, found, (size_t)n_tiles * sizeof(f64x2), hipMemcpyDeviceToHost, st) != hipSuccess ||
                 hipStreamSynchronize(st) != hipSuccess)
                 return SALS_ERR_HIP;
             double most = 0.0, square = 0.0;
-            for (const auto& f : h_found) { most = std::max(most, f[0]); square += f[1]; }
+            for (int i = 0; i < n_tiles; ++i) { most = std::max(most, h_found[2 * i]); square += h_found[2 * i + 1]; }
             converged = most <= 1e-11;
             if (converged || !series || !(square <= 1.6e-5)) break;
             // exp(E) G from the inside out: G + E (G + E/2 (G + E/3 (G + E/4 G)))

@@ -3,6 +3,8 @@ header declares, and rejects bad descriptors / pointers before touching a device
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -137,6 +139,29 @@ def test_create_checks_workspace_and_calls_check_pointers(sb):
         lib.sals_destroy(hh)
     lib.sals_destroy(h)
     lib.sals_destroy(None)
+
+
+_NO_MEMORY = """
+import ctypes, resource, sys
+from paper_2510_24273_amd import binding as b
+libc = ctypes.CDLL(None)
+libc.malloc.restype, libc.malloc.argtypes = ctypes.c_void_p, [ctypes.c_size_t]
+n = ctypes.c_int32(0)
+args = (1 << 20, 8192, 16, b.SALS_F32, 1 << 20, 1 << 20, 1 << 20, 1 << 40, 5, ctypes.byref(n), None)
+used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used, used))
+for size in (1 << 22, 1 << 18, 1 << 16, 1 << 15):   # what the heap still holds
+    while libc.malloc(size):
+        pass
+sys.exit(b._lib.sals_calib_eigenvectors(*args))
+"""
+
+
+def test_no_host_memory_is_an_error_code(sb):
+    """The call that keeps numbers on the host returns an error where the host has no memory for them; nothing throws out of a C
+    entry point (and, the memory coming first, nothing is enqueued)."""
+    p = subprocess.run([sys.executable, "-c", _NO_MEMORY], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert p.returncode == sb.SALS_ERR_HIP, (p.returncode, p.stderr[-300:])
 
 
 @pytest.mark.parametrize("kw,nbytes", [
