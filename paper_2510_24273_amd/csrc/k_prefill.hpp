@@ -366,10 +366,12 @@ __device__ __forceinline__ void prefill_tile(const PrefillArgs& a, int block, in
     Frags F0, F1;
 #pragma unroll
     for (int i = 0; i < NBW + NBT; ++i) read_frag(F0, i, 0, 0);
-    // With small tiles a step is so short that it is felt where the loop lies in the lines of the instruction cache (64 tokens,
-    // D = 4096, r = 1024: 20.4 us a call at the start of a line, 21.1 to 21.5 elsewhere).  Aligned here, with room for the 24 bytes
-    // that set up the loop of the smallest tiles (a loop alignment given to the compiler is not observed).
-    asm volatile(".p2align 6\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0");
+    // In the smallest tiles a step is so short that it is felt where the loop lies in the lines of the instruction cache (64 tokens,
+    // D = 4096, r = 1024: 20.5 us a call at the start of a line, 21.1 elsewhere; 200 tokens, r = 512: 21.1 and 21.6).  Aligned here,
+    // with room for the instructions that the compiler puts in front of the loop (24 bytes and whole lines): a loop alignment given
+    // to the compiler is not observed, so a test looks where the loop of the built library lies.
+    if constexpr (NBW == 1 && NBT == 1)
+        asm volatile(".p2align 6\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0");
     for (int s0 = 0; s0 < n_steps; s0 += 4) {  // (n_steps is a multiple of 4)
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
