@@ -158,7 +158,7 @@ __device__ __forceinline__ void logits_small_tile(
         // the selection, in LDS that the stage buffers take over afterwards
         TopkShared& sh = *reinterpret_cast<TopkShared*>(lds);
         int32_t* s_idx = reinterpret_cast<int32_t*>(lds + ((sizeof(TopkShared) + 255) & ~(size_t)255));  // [k_tot], then the count
-        topk_select_sequence<kLsFusedMaxS / (4 * kLsThreads), kLsThreads, true>(
+        topk_select_sequence<kLsFusedMaxS / (4 * kLsThreads), kLsThreads>(
             sh, fs.scores + (size_t)b * S_max, fs.seq_len + b, s_idx, s_idx + kLsFusedMaxK, 0, S_max, fs.top_k, fs.n_sink,
             fs.n_recent, [&](int place) {
 #pragma unroll

@@ -76,15 +76,15 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, TopkShared& sh, 
 
 // Selection for sequence b by the calling workgroup (NTH threads, all of them must call).
 // F4 > 0: keys of F4 float4 groups per thread stay in registers.  F4 == 0: stream.
-// CONSEC: a thread's keys are 4*F4 consecutive tokens (otherwise group c of thread t covers tokens
-// 4*(c*NTH + t) .. +3): with it, selected indices come out in token order inside each score class whatever NTH is,
-// i.e. in the order the 1024-thread kernel with one group per thread produces.
+// Of the selection kernel's 1024 threads, thread t holds the groups 4*(c*1024 + t) .. +3 (c = 0, 1, ...), and inside a score class
+// the list has the indices in the order of the threads and of a thread's groups.  A workgroup of NTH < 1024 threads leaves the same
+// list: each of its threads holds the groups of 1024 / NTH consecutive ones of the 1024.
 // `idx` / `n_sel` may point to LDS (the caller reads them after a barrier of its own).
 // `meanwhile(0)`, `(1)`, `(2)` run once each, in this order, at three places of the selection: loads that the caller issues
 // there arrive while the selection works.  The first place is behind the arrival of the scores, and the loads are spread,
 // because what a compute unit has requested is delivered in order and a wave stands still while its requests queue up.
 struct TopkNoWork { __device__ void operator()(int) const {} };
-template <int F4, int NTH = kTopkThreads, bool CONSEC = false, typename Meanwhile = TopkNoWork>
+template <int F4, int NTH = kTopkThreads, typename Meanwhile = TopkNoWork>
 __device__ __forceinline__ void topk_select_sequence(TopkShared& sh, const float* __restrict__ scores,
                                                      const int32_t* __restrict__ seq_len,
                                                      int32_t* __restrict__ idx, int32_t* __restrict__ n_sel,
@@ -99,12 +99,17 @@ __device__ __forceinline__ void topk_select_sequence(TopkShared& sh, const float
     constexpr int NREG = F4 > 0 ? F4 * 4 : 4;
     constexpr int NW = NTH / kWave;              // waves
     constexpr int BPT = kTopkBins / NTH;         // histogram bins per thread
-    static_assert(NTH % kWave == 0 && NTH <= kTopkThreads && kTopkBins % (4 * NTH) == 0 && (!CONSEC || F4 > 0),
+    constexpr int VT = kTopkThreads / NTH;       // threads of the 1024 whose groups a thread holds
+    static_assert(NTH % kWave == 0 && kTopkThreads % NTH == 0 && kTopkBins % (4 * NTH) == 0 && F4 % VT == 0 && (VT == 1 || F4 > 0),
                   "workgroup shape");
+    constexpr int VG = VT > 1 ? F4 / VT : 1;     // groups of each of them
     // token of this thread's key i (i = 4*group + element)
-    auto token_of = [&](int i) { return CONSEC ? tid * NREG + i : ((((i >> 2) * NTH) + tid) << 2) + (i & 3); };
+    auto token_of = [&](int i) {
+        const int c = i >> 2;
+        return (VT == 1 ? c * NTH + tid : c % VG * kTopkThreads + tid * VT + c / VG) * 4 + (i & 3);
+    };
 
-    // group c of this thread covers tokens 4*(c*1024 + tid) .. +3  (coalesced float4 loads);
+    // group c of this thread: four tokens (float4 loads);
     // the loads depend on S_max only, so they are in flight together with the length
     auto load_group = [&](int c, float* f) {
         const int j = token_of(4 * c);

@@ -48,7 +48,7 @@ struct StepSelect {
     WindowLists wl;
 };
 constexpr int kWsMaxS = 8192;  // longer sequences keep the selection kernel of 1024 threads, whose own launch then takes longer than the window pass
-// `lds`: at least sizeof(TopkShared) bytes.  A thread's keys are consecutive tokens: the list comes out in token order.
+// `lds`: at least sizeof(TopkShared) bytes.  The list is the selection kernel's, entry by entry (see topk_select_sequence).
 template <int NTH> __device__ __forceinline__ void step_select(const StepSelect& a, unsigned char* lds)
 {
     static_assert(kWsMaxS % (4 * NTH) == 0, "whole groups of four keys per thread");
@@ -57,10 +57,10 @@ template <int NTH> __device__ __forceinline__ void step_select(const StepSelect&
     TopkShared& sh = *reinterpret_cast<TopkShared*>(lds);
     write_window_lists(a.wl, a.seq_len, b, a.S_max, a.top_k + a.n_sink + a.n_recent, NTH);
     if (a.S_max <= kWsMaxS / 2)
-        topk_select_sequence<kWsMaxS / 2 / (4 * NTH), NTH, true>(sh, a.scores, a.seq_len, a.idx, a.n_sel, b, a.S_max, a.top_k, a.n_sink,
+        topk_select_sequence<kWsMaxS / 2 / (4 * NTH), NTH>(sh, a.scores, a.seq_len, a.idx, a.n_sel, b, a.S_max, a.top_k, a.n_sink,
                                                                  a.n_recent);
     else
-        topk_select_sequence<kWsMaxS / (4 * NTH), NTH, true>(sh, a.scores, a.seq_len, a.idx, a.n_sel, b, a.S_max, a.top_k, a.n_sink,
+        topk_select_sequence<kWsMaxS / (4 * NTH), NTH>(sh, a.scores, a.seq_len, a.idx, a.n_sel, b, a.S_max, a.top_k, a.n_sink,
                                                              a.n_recent);
 }
 

@@ -573,7 +573,8 @@ def test_unprepared_context_fills_its_table_lazily_and_refuses_capture(oracle):
 
 @pytest.mark.parametrize("dtype,H_kv,r,S,top_k,lens", [
     ("f32", 8, 256, 1000, 100, [1000, 63]), ("f32", 32, 512, 4096, 130, [4093]), ("bf16", 8, 512, 2048, 500, [2048]),
-    ("bf16", 8, 256, 4096, 1000, [4001]), ("bf16", 4, 128, 4, 3, [4, 0])])
+    ("bf16", 8, 256, 4096, 1000, [4001]), ("bf16", 4, 128, 4, 3, [4, 0]),
+    ("bf16", 4, 256, 4, 3, [4, 0])])
 def test_selection_inside_split_logits(dtype, H_kv, r, S, top_k, lens, monkeypatch):
     """Few tiles, whose latent axis is split over workgroups that each select by themselves: list, count and output equal those of
     the step with a selection launch, bit for bit (empty tiles and sequences, one tile, a list of the largest length)."""

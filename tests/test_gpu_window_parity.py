@@ -43,10 +43,14 @@ def _case(oracle, w, seq_lens=None, seqs=None, label=""):
     out = torch.empty((w.B, w.H, w.d), dtype=gu.out_dtype(w), device=gu.DEV)
     ctx.decode_step_window(win, G["q"], G["q_pos"], G["Kc"], G["Vc"], G["W"], Gw["Kw"], Gw["Vw"], W_hi,
                            G["seq_len"], out, scores, idx, n_sel)
-    # the staged call on the same selection, and a second whole step, must reproduce it bit for bit
+    # the selection call leaves the same list, entry by entry; the staged call on it, and a second whole step, must reproduce
+    # the step bit for bit
+    idx2, n_sel2 = torch.full_like(idx, -8), torch.full_like(n_sel, -8)
+    ctx.topk_select(scores, G["seq_len"], idx2, n_sel2)
+    assert torch.equal(idx, idx2) and torch.equal(n_sel, n_sel2)
     out2, out3 = torch.empty_like(out), torch.empty_like(out)
-    ctx.sparse_attend_window(win, G["q"], G["q_pos"], G["Kc"], G["Vc"], G["W"], Gw["Kw"], Gw["Vw"], W_hi, idx,
-                             n_sel, out2)
+    ctx.sparse_attend_window(win, G["q"], G["q_pos"], G["Kc"], G["Vc"], G["W"], Gw["Kw"], Gw["Vw"], W_hi, idx2,
+                             n_sel2, out2)
     ctx.decode_step_window(win, G["q"], G["q_pos"], G["Kc"], G["Vc"], G["W"], Gw["Kw"], Gw["Vw"], W_hi,
                            G["seq_len"], out3)
     torch.cuda.synchronize()
@@ -127,6 +131,18 @@ def test_selection_and_window_logits_in_one_launch(oracle, S, B, tiles, monkeypa
     monkeypatch.setenv("SALS_TUNE_LOGITS", tiles)
     w = synth.shrink(SMALL, B=B, S=S, H=4, H_kv=4, r=64, r_hi=128, top_k=150, plant=2)
     _case(oracle, w, seq_lens=[S, S - 1, 4000, 4097, 70][:B])
+
+
+@pytest.mark.parametrize("S,B,tiles,top_k", [
+    (4096, 2, "3", 150), (4099, 3, "3", 150), (8192, 2, "3", 700), (5001, 5, "4", 150), (8192, 9, "4", 300),
+    (700, 9, "4", 20)])     # a low-rank pass of 64 tokens, in the window's tiles
+def test_selection_beside_a_window_in_slices(oracle, S, B, tiles, top_k, monkeypatch):
+    """The same with the window's latent axis in four slices (64-token tiles) or two (tiles of two sequences), whose sums the
+    low-rank logits kernel makes on the side, or a launch of their own where it has tiles of two sequences itself."""
+    monkeypatch.setenv("SALS_TUNE_LOGITS", tiles)
+    monkeypatch.setenv("SALS_TUNE_MULTI_KSPLIT", "2")
+    w = synth.shrink(SMALL, B=B, S=S, H=4, H_kv=4, r=64, r_hi=512, top_k=top_k, plant=2 if top_k > 100 else 0)
+    _case(oracle, w, seq_lens=[S, S - 1, S // 2 + 1, 697, 70, 0, 41, 40, 500][:B])
 
 
 @pytest.mark.parametrize("tiles,H,H_kv,n_recent,top_k,dtype", [
