@@ -660,14 +660,16 @@ int window_select_slices(const sals_ctx* win)
 }
 
 // Whether a whole decode step on this context lets the logits kernel select by itself (no selection launch): the
-// 64-token kernel, a cache of at most 4096 rows whose score rows start 16-byte aligned, a selection that fits the kernel's
-// list.  (Also where the latent axis is split, every slice selecting by itself: one sequence in fp32, 1024 tokens, 128 selected,
-// four slices: 32.1 -> 30.9 us a step; 8 KV heads in bf16, 4096 tokens, 512 selected, two slices: 27.3 -> 26.2.)
+// 64-token kernel in one round of workgroups, a cache of at most 4096 rows whose score rows start 16-byte aligned, a selection that
+// fits the kernel's list.  (Also where the latent axis is split, every slice selecting by itself: one sequence in fp32, 1024 tokens,
+// 128 selected, four slices: 32.1 -> 30.9 us a step; 8 KV heads in bf16, 4096 tokens, 512 selected, two slices: 27.3 -> 26.2.  In two
+// or three rounds, which fp32 has, the selection of each of them costs more than the launch; inside and as a launch: 5 sequences of
+// 4096 tokens, 130 selected, H_kv 32, r 512 74.2 and 73.6 us, 6 sequences, 320 selected, r 256 83.1 and 76.3.)
 bool fused_selection(const sals_ctx* c)
 {
     const sals_desc& d = c->d;
-    return c->plan.pick == 3 && d.S_max <= kLsFusedMaxS && d.S_max % 4 == 0 &&
-           d.top_k + d.n_sink + d.n_recent <= kLsFusedMaxK && c->fuse_select;
+    return c->plan.pick == 3 && (long long)c->plan.n_parts * d.H_kv * d.B * c->plan.ksplit <= 256 && d.S_max <= kLsFusedMaxS &&
+           d.S_max % 4 == 0 && d.top_k + d.n_sink + d.n_recent <= kLsFusedMaxK && c->fuse_select;
 }
 
 // the instantiation of attend_logits_kernel (256- and 128-token tiles) for a group size (query heads per KV head)

@@ -600,6 +600,23 @@ def test_selection_inside_split_logits(dtype, H_kv, r, S, top_k, lens, monkeypat
     assert np.array_equal(o1, o0)
 
 
+@pytest.mark.parametrize("B,launches", [(2, 0), (5, 1)])
+def test_selection_inside_one_round_of_logits_only(B, launches):
+    """64-token logits of 192 workgroups select by themselves; with 480, a second round, the selection is a launch of its own (same
+    list, count and output: the test above compares the two forms)."""
+    print(f"[case] selection in one round of logits B={B}", flush=True)
+    w = synth.shrink(synth.CONFIGS["cfg2"], B=B, S=512, H=32, H_kv=32, r=128, top_k=130, n_layers=1, dtype="f32", plant=0)
+    L = synth.make_layer(w, 0)
+    ctx = gu.make_ctx(w)
+    G = gu.upload(L, ctx)
+    out = torch.empty((w.B, w.H, w.d), dtype=gu.out_dtype(w), device=gu.DEV)
+    ctx.profile(True)
+    ctx.decode_step(G["q"], G["q_pos"], G["Kc"], G["Vc"], G["W"], G["seq_len"], out)
+    torch.cuda.synchronize()
+    assert ctx.profile_collect()["topk"][1] == launches
+    ctx.close()
+
+
 @pytest.mark.parametrize("pick,dtype,H_kv,r,S,top_k,n_sink,lens,copies", [
     (1, "bf16", 8, 128, 32772, 700, 4, [32772, 32001], 1),    # the shortest; ranked entries in the last of three tiles
     (1, "bf16", 2, 256, 33000, 252, 0, [33000], 1),           # entries up to a tile's end
