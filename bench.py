@@ -212,9 +212,8 @@ def measure_prefill(w, steps, torch, binding, roofline):
 def measure_calibration(w, n_tok, steps, torch, binding, roofline):
     """Offline calibration at the key width of configuration w: covariance of n_tok synthetic calibration keys (timed
     with events on the launch stream, against the bf16 matrix peak) and the r leading eigenvectors (wall time of the
-    blocking call; every Jacobi step reads and writes the whole fp64 matrix once, so the figure next to it is that
-    stream's bytes per second: a matrix of up to 4096 rows stays in the 256 MB last-level cache, which is why the
-    figure can exceed what HBM delivers)."""
+    blocking call and its sweeps; the call also has the factorisation, the last rotations all at once and the norms, so
+    the time of a step is the kernel trace's)."""
     dev = "cuda:0"
     dt = torch.bfloat16 if w.dtype == "bf16" else torch.float32
     D = w.D_kv
@@ -242,14 +241,12 @@ def measure_calibration(w, n_tok, steps, torch, binding, roofline):
     lam, U, sweeps = binding.calib_eigenvectors(C, w.r, dt)
     torch.cuda.synchronize()
     eig_ms = (time.perf_counter() - t0) * 1e3
-    n_steps = abs(sweeps) * (D // 32)   # a sweep: one step inside 32-row blocks, D / 32 - 1 steps of disjoint pairs of them
     del X, ws, dirs
     torch.cuda.empty_cache()
     return {"workload": f"calib_{w.name}", "D": D, "r": w.r, "tokens": n_tok, "covariance_us_per_call": round(us, 1),
             "covariance_flops": flops, "covariance_TFLOPs": round(flops / (us * 1e-6) / 1e12, 1),
             "covariance_mfma_frac": round(flops / (us * 1e-6) / 1e12 / peak, 4),
-            "eigenvectors_ms": round(eig_ms, 1), "sweeps": sweeps, "jacobi_steps": n_steps,
-            "jacobi_us_per_step": round(eig_ms * 1e3 / max(n_steps, 1), 2),
+            "eigenvectors_ms": round(eig_ms, 1), "sweeps": sweeps,
             "lambda_ratio_r": float(lam[w.r - 1] / lam[0])}
 
 
@@ -285,16 +282,7 @@ def kernel_table(ls, steps, roofline, wall_us_per_layer_step):
         p1 = ls.ctx.profile_collect()
         prof = p1 if prof is None else {k: (min(prof[k], p1[k], key=lambda mn: mn[0] / max(mn[1], 1))) for k in p1}
     ls.ctx.profile(False)
-    sb, sf = roofline.stage_bytes(w), roofline.stage_flops(w)
-    model = {
-        "project": ("hbm", sb["project"]),
-        "scores": ("hbm", sb["scores"]),
-        "topk": ("hbm", sb["select"] + w.B * w.k_tot * 4),
-        "attend_logits": ("mfma", sf["reconstruct_k"]),
-        "attend_pv": ("hbm", w.B * w.k_tot * w.r * w.esize),
-        "attend_out": ("hbm", w.r * w.D_kv * w.esize),
-        "attend_qv": ("hbm", w.B * w.k_tot * (w.D_kv * max(w.qv_bits, 1) // 8 + w.D_kv // 32 * 2 * w.esize)),
-    }
+    model = roofline.stage_work(w)
     raw = {name: ms * 1e3 / n for name, (ms, n) in prof.items() if n > 0}
     gap = max(0.0, (sum(raw.values()) - wall_us_per_layer_step) / max(1, len(raw)))
     rows = {}

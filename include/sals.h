@@ -433,8 +433,10 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
 enum {
     SALS_K_PROJECT = 0,        /* latent projection (query, or new key/value)  */
     SALS_K_SCORES = 1,         /* latent score stream over the key cache       */
-    SALS_K_TOPK = 2,           /* exact top-k selection                        */
-    SALS_K_ATTEND_LOGITS = 3,  /* MFMA key reconstruction + RoPE + q.K         */
+    SALS_K_TOPK = 2,           /* exact top-k selection; in a decode step with a recent window on caches of at most
+                                  8192 rows also the window's logits, in the same launch */
+    SALS_K_ATTEND_LOGITS = 3,  /* MFMA key reconstruction + RoPE + q.K; in a decode step that may include the
+                                  selection (few tokens; then nothing is recorded as SALS_K_TOPK) or its last part */
     SALS_K_ATTEND_PV = 4,      /* softmax + latent-space value sum             */
     SALS_K_ATTEND_OUT = 5,     /* output projection through U_v                */
     SALS_K_ATTEND_QV = 6,      /* softmax + sum over the quantised value cache */

@@ -22,21 +22,23 @@ def stage_bytes(w, seq_len=None) -> dict:
     e = w.esize
     S = getattr(w, "S_live", w.S) if seq_len is None else seq_len
     n_sel = min(S, w.k_tot)
+    n_win = min(S, w.n_recent) if getattr(w, "r_hi", 0) else 0   # tokens attended in the window's caches, n_low in the main ones
+    n_low = n_sel - n_win
     small = w.B * (w.H * w.d * e * 2 + w.r * 4 + n_sel * 4)   # q, out, q~, idx
     return {
         "project": w.r * w.D_kv * e,                      # U_k, once per batch
         "scores": w.B * (S * w.rs * e + 4 * S),          # K~ stream + score write
         "select": w.B * 4 * S,                            # score read
-        "attend_k": w.B * n_sel * w.r * e + w.r * w.D_kv * e,   # gathered K~ rows + U_k
+        "attend_k": w.B * n_low * w.r * e + w.r * w.D_kv * e,   # gathered K~ rows + U_k
         # gathered V~ rows + U_v, or (quantised value cache) gathered code rows + per-group (scale, zero)
-        "attend_v": (w.B * n_sel * w.r * e + w.r * w.D_kv * e) if not getattr(w, "qv_bits", 0)
-        else w.B * n_sel * (w.D_kv * w.qv_bits // 8 + w.D_kv // 32 * 2 * e),
+        "attend_v": (w.B * n_low * w.r * e + w.r * w.D_kv * e) if not getattr(w, "qv_bits", 0)
+        else w.B * n_low * (w.D_kv * w.qv_bits // 8 + w.D_kv // 32 * 2 * e),
         "small": small,
         # high-precision recent window: ring rows of both caches for the recent tokens + the window's projectors
         # (with the quantised value path the window's values are 8-bit rows and only the key projector is read)
-        "window": 0 if not getattr(w, "r_hi", 0) else
-        (2 * w.B * min(S, w.n_recent) * w.r_hi * e + 2 * w.r_hi * w.D_kv * e) if not getattr(w, "qv_bits", 0) else
-        (w.B * min(S, w.n_recent) * (w.r_hi * e + w.D_kv + w.D_kv // 32 * 2 * e) + w.r_hi * w.D_kv * e),
+        "window": 0 if not n_win else
+        (2 * w.B * n_win * w.r_hi * e + 2 * w.r_hi * w.D_kv * e) if not getattr(w, "qv_bits", 0) else
+        (w.B * n_win * (w.r_hi * e + w.D_kv + w.D_kv // 32 * 2 * e) + w.r_hi * w.D_kv * e),
     }
 
 
@@ -49,14 +51,38 @@ def algorithmic_bytes(w, seq_len=None) -> int:
 def stage_flops(w, seq_len=None) -> dict:
     S = getattr(w, "S_live", w.S) if seq_len is None else seq_len
     n_sel = min(S, w.k_tot)
+    n_win = min(S, w.n_recent) if getattr(w, "r_hi", 0) else 0
     return {
         "project": 2 * w.B * w.r * w.D_kv,
         "scores": 2 * w.B * S * w.rs,
-        "reconstruct_k": 2 * w.B * n_sel * w.r * w.D_kv,
+        "reconstruct_k": 2 * w.B * (n_sel - n_win) * w.r * w.D_kv,
+        "reconstruct_window": 2 * w.B * n_win * getattr(w, "r_hi", 0) * w.D_kv,
         "reconstruct_v_literal": 2 * w.B * n_sel * w.r * w.D_kv,
         "value_reassociated": 2 * w.B * w.H * (n_sel * w.r + w.r * w.d),
         "attention": 4 * w.B * n_sel * w.H * w.d,
     }
+
+
+def stage_work(w) -> dict:
+    """What each timed stage of a decode step on workload w moves or computes: (the bound it is rated against, bytes or flop).
+
+    With a recent window the low-rank logits are those of the tokens before it, and the value stages read both
+    caches.  The window's logits are in the selection's launch on caches of at most 8192 rows, which is then rated by
+    their reconstruction; on longer ones they are a launch that no stage of the main context times."""
+    e, S = w.esize, w.S_live
+    n_sel, n_win = min(S, w.k_tot), min(S, w.n_recent) if w.r_hi else 0
+    n_low, meta = n_sel - n_win, w.D_kv // 32 * 2 * e
+    sb, sf = stage_bytes(w), stage_flops(w)
+    return {
+        "project": ("hbm", sb["project"]),
+        "scores": ("hbm", sb["scores"]),
+        "topk": ("mfma", sf["reconstruct_window"]) if n_win and w.S <= 8192 else ("hbm", sb["select"] + w.B * w.k_tot * 4),
+        "attend_logits": ("mfma", sf["reconstruct_k"]),
+        "attend_pv": ("hbm", w.B * (n_low * w.r + n_win * w.r_hi) * e),
+        "attend_out": ("hbm", (w.r + (w.r_hi if n_win else 0)) * w.D_kv * e),
+        "attend_qv": ("hbm", w.B * (n_low * (w.D_kv * max(w.qv_bits, 1) // 8 + meta) + n_win * (w.D_kv + meta))),
+    }
+
 
 # HBM bytes per launch (read + written) measured with rocprofv3 --pmc FETCH_SIZE and --pmc WRITE_SIZE,
 # each scaled by the same counter's reading for a 64 MiB device-to-device copy in the same run
@@ -65,7 +91,7 @@ def stage_flops(w, seq_len=None) -> dict:
 # a stage that runs as several kernels is the sum of their rows.  The scaling assumes full 128-byte
 # requests, so kernels that fetch 64-byte pieces are over-counted by up to 2x.
 _STAGE_OF_KERNEL = (
-    ("project_kernel", "project"), ("scores_kernel", "scores"), ("topk", "topk"),
+    ("project_kernel", "project"), ("scores_kernel", "scores"), ("topk", "topk"), ("window_select", "topk"),
     ("attend_logits", "attend_logits"), ("logits_finish", "attend_logits"), ("attend_pv", "attend_pv"),
     ("attend_out", "attend_out"), ("attend_qv", "attend_qv"), ("qv_merge", "attend_qv"),
 )

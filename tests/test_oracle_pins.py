@@ -412,6 +412,21 @@ def test_traffic_model_fixture():
         assert abs(2 * s * nd / model - 1.0 / ((r / 2 / nd) / 2 + d_r * k_s)) < 1e-12
 
 
+def test_stage_work_follows_the_launches():
+    """The work that a timed stage is rated by, with a recent window: 64 of 512 tokens reconstructed at the window's rank
+    in the selection's launch, the others in the low-rank logits; the value stages read both caches."""
+    from paper_2510_24273_amd import roofline, synth
+    plain, win = (roofline.stage_work(synth.lookup(n)) for n in ("cfg3a_comp", "cfg3a_win"))
+    D, r, r_hi, B = 4096, 640, 2048, 16
+    assert plain["topk"] == ("hbm", B * 4 * 4096 + B * 512 * 4) and plain["attend_logits"] == ("mfma", 2 * B * 512 * r * D)
+    assert win["topk"] == ("mfma", 2 * B * 64 * r_hi * D) and win["attend_logits"] == ("mfma", 2 * B * 448 * r * D)
+    assert win["attend_pv"] == ("hbm", B * (448 * r + 64 * r_hi) * 2) and win["attend_out"] == ("hbm", (r + r_hi) * D * 2)
+    qv = roofline.stage_work(synth.lookup("cfg2_qvwin"))
+    assert qv["attend_qv"] == ("hbm", 448 * (D // 2 + D // 32 * 4) + 64 * (D + D // 32 * 4))
+    a, b = (roofline.stage_bytes(synth.lookup(n)) for n in ("cfg3a_comp", "cfg3a_win"))
+    assert a["attend_k"] - b["attend_k"] == B * 64 * r * 2 and a["window"] == 0
+
+
 # ---------------------------------------------------------------------------
 # interleaved RoPE pairing (pairs (2i, 2i+1)) through the composed functions:
 # brute force written here with explicit 2x2 rotations, independent of oracle.rope
