@@ -200,17 +200,17 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_compress_kernel(Prefill
 // Matrix-bound while the whole chip works (22 ns per MFMA and SIMD at the clock its power leaves, 13.4 with few workgroups);
 // what is lost to it is the last round of tiles and 2 (smallest tile) to 13 us (largest) per round to start and store.  Whole
 // calls, with the launch that advances the lengths, against the 256 x 128 and 128 x 128 tiles staged through registers, two
-// workgroups per compute unit, that this replaced: 6 ragged prompts of up to 4001 tokens, D = 1024, r = 640 91 -> 78 us
-// (68 to 73 now, from card to card); 6000 tokens, D = 4096, r = 1024 125 -> 99 us; 64 tokens, D = 4096 44 -> 20 us.
+// workgroups per compute unit, that this replaced: 6 ragged prompts of up to 4001 tokens, D = 1024, r = 640 91 -> 78 us;
+// 6000 tokens, D = 4096, r = 1024 125 -> 99 us; 64 tokens, D = 4096 44 -> 20 us.
 // Tiles: without n_new the prompts of a batch are one run of B n_tok rows (a tile may span sequences); with n_new every
 // sequence has tiles of its own and only those that hold tokens are in the list (its length is known on the device only, so
 // the launch covers n_tok everywhere and the workgroups past the end leave at once).
 // All tiles alike, or two kinds in a launch (prefill_split_kernel): the first workgroups (kPfBig) as many 256-row tiles as fill
 // whole rounds of the chip with per_big workgroups each, the others (kPfTail) the rest in smaller tiles, unless that rest is more
 // than tail_max row tiles (then the first take them too).  Both derive the split from the token counts.  The smaller tiles start
-// as the compute units get free: in a launch of their own, behind the last of the whole tiles, 6 ragged
-// prompts of up to 4001 tokens (D = 1024, r = 640) took 73 to 74 us instead of 68, 1 x 20000 73.2 instead of 70.2, 4097 tokens of
-// D = 4096, r = 1024 102.5 instead of 98.9.
+// as the compute units get free.  Whole calls and the copy that sets the lengths back, on one card, with the smaller tiles in a
+// launch of their own behind the last of the whole ones and as here: 6 ragged prompts of up to 4001 tokens (D = 1024, r = 640)
+// 74.5 and 71.7 us, 1 x 20000 74.5 and 72.4, 4097 tokens of D = 4096, r = 1024 102.1 and 99.0.
 enum { kPfAll = 0, kPfBig = 1, kPfTail = 2 };
 struct PfPart { int part, per_big, tail_max; };
 template <int NBW, int NBT> struct pf_cfg {

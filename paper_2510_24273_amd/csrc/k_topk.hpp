@@ -367,7 +367,7 @@ __device__ __forceinline__ void topk_select_sequence(TopkShared& sh, const float
         pos_eq = block_excl_scan<NW>(my_eq, sh, phase, &tot_eq);
     }
 
-    // greater-than keys fill [0, n_gt), ties [n_gt, top_k), each in token order.  (The limits
+    // greater-than keys fill [0, n_gt), ties [n_gt, top_k), each in the order of the threads and their groups.  (The limits
     // only guard against out-of-range writes on malformed scores, e.g. NaN.)
     int32_t* const sel = out + n_sink;
     uint32_t og = pos_gt, oe = n_gt + pos_eq;

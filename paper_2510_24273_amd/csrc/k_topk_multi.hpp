@@ -11,7 +11,7 @@
 //            where the chunk's output starts (every workgroup of the sequence derives the same
 //            numbers: a thread adds up two bins over the chunks, all its loads in flight together, and one block scan
 //            of the totals and of the earlier chunks' counts settles everything); then the indices of the scores in
-//            higher bins go to their final positions (chunk order, then token order) and the
+//            higher bins go to their final positions (chunk order, then the order of a chunk's threads) and the
 //            members of the threshold bin to a candidate list
 //   finish   per sequence: ranks the candidates (ties towards the smaller index), writes the
 //            selected ones in token order, the sink / recent entries and n_sel
