@@ -645,14 +645,21 @@ template <typename T> auto window_select_for(int group)
     return window_select_kernel<T, 1, 0>;
 }
 int select_blocks(const sals_desc& d) { return ceil_div(d.B, kXcds) * kXcds; }
-// Slices of the window's latent axis in the combined launch: the window's own plan, halved while its workgroups fit the chip at
+// Whether a decode step has the window's logits in its selection's launch.  Both small: sequences of at most kWsMaxS tokens,
+// windows that fill tiles of one or two sequences.
+bool window_in_select(const sals_ctx* win)
+{
+    return win->d.S_max <= kWsMaxS && (win->plan.pick == 3 || win->plan.pick == 4) && win->fuse_select;
+}
+// Slices of the window's latent axis: the window's own plan; in the combined launch halved while its workgroups fit the chip at
 // once (one per compute unit in the 64-token form, two otherwise) and do not together with the selection's.  (A workgroup too many is a
 // round too many: 16 sequences, r_hi = 2048, two slices 32.0 us and a sum to add, one 30.6; one sequence, eight slices would be
 // 257 workgroups.)
-int window_select_slices(const sals_ctx* win)
+int window_slices(const sals_ctx* win)
 {
     const LogitsPlan& P = win->plan;
     const sals_desc& d = win->d;
+    if (!window_in_select(win)) return P.ksplit;
     const int tiles = P.pick == 4 ? ceil_div(d.B, 2) * d.H_kv : P.n_parts * d.H_kv * d.B, slots = P.pick == 4 ? 512 : 256;
     int ks = P.ksplit;
     while (ks > 1 && tiles * ks <= slots && tiles * ks + d.B > slots) ks /= 2;
@@ -729,7 +736,7 @@ template <typename T> sals_status allow_logits_lds(const sals_ctx* c)
     if (ok && c->d.n_sink == 0 && c->d.n_recent == 0) {
         if (P.pick == 4) ok = allow(reinterpret_cast<const void*>(window_select_for<T>(group)), logits_cfg<1, 4, 1>::LDS);
         if (P.pick == 3) {
-            const int nst = steps_ahead<T>(c->d, window_select_slices(c));
+            const int nst = steps_ahead<T>(c->d, window_slices(c));
             ok = allow(reinterpret_cast<const void*>(WindowSelectSmall<T>::get(nst)), kLsLds) &&
                  allow(reinterpret_cast<const void*>(SmallLogits<T>::get(nst, false)), kLsLds);
         }
@@ -819,7 +826,7 @@ sals_status launch_attend(const sals_ctx* c, const void* q, const int32_t* q_pos
     float* logits = reinterpret_cast<float*>(c->ws + L.logits);
     LogitsPlan P = c->plan;
     if (ring > 0 && P.pick >= 3) {  // (as in a decode step)
-        P.ksplit = window_select_slices(c);
+        P.ksplit = window_slices(c);
         if (P.pick == 3) P.nst = steps_ahead<T>(d, P.ksplit);
     }
     // tile statistics: written by this pass's logits kernel from record `part0` on, read as a whole by the value kernel
@@ -1440,12 +1447,10 @@ StatsLink window_stats(sals_ctx* ctx, sals_ctx* win, bool hi)
     return StatsLink{reinterpret_cast<float2*>(ctx->ws + ctx->L.stats), ctx->plan.n_parts + win->plan.n_parts, hi ? ctx->plan.n_parts : 0};
 }
 
-// A step's selection together with the window's logits.  Both small: sequences of at most kWsMaxS tokens, windows that fill
-// tiles of one or two sequences.
+// A step's selection together with the window's logits.
 bool window_select_fits(const sals_ctx* ctx, const sals_ctx* win)
 {
-    return ctx->d.S_max <= kWsMaxS && (win->plan.pick == 3 || win->plan.pick == 4) && win->fuse_select &&
-           ctx->plan.n_parts + win->plan.n_parts <= ctx->L.max_parts;
+    return window_in_select(win) && ctx->plan.n_parts + win->plan.n_parts <= ctx->L.max_parts;
 }
 template <typename T>
 sals_status launch_window_select(sals_ctx* ctx, sals_ctx* win, const void* q, const int32_t* q_pos, const void* Kw, const void* W_hi,
@@ -1462,7 +1467,7 @@ sals_status launch_window_select(sals_ctx* ctx, sals_ctx* win, const void* q, co
     float* logits = reinterpret_cast<float*>(win->ws + L.logits);
     float* plogits = reinterpret_cast<float*>(win->ws + L.plogits);
     const float scale = 1.0f / std::sqrt((float)e.d);
-    const int w = e.top_k, ks = window_select_slices(win);
+    const int w = e.top_k, ks = window_slices(win);
     float2* stats = link.stats + link.part0;
     ProfScope ps(ctx, SALS_K_TOPK, st);
     if (win->plan.pick == 4) {
@@ -1502,7 +1507,7 @@ sals_status window_logits(sals_ctx* ctx, sals_ctx* win, const void* q, const int
     const StatsLink lo = window_stats(ctx, win, false), hi = window_stats(ctx, win, true);
     SplitLogits split{};
     if (have == kWindowLogits) {
-        const int ks = window_select_slices(win);
+        const int ks = window_slices(win);
         if (ks > 1) split = split_logits(win, ks, wl.n_hi, hi.stats + hi.part0, hi.stride);
         if (ks > 1 && ctx->plan.pick == 4) {  // (tiles of several sequences do not add up on the side)
             hipLaunchKernelGGL(logits_finish_kernel, dim3(split.n_parts, split.rows), dim3(64), 0, st, split);

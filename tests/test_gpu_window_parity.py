@@ -145,6 +145,42 @@ def test_selection_beside_a_window_in_slices(oracle, S, B, tiles, top_k, monkeyp
     _case(oracle, w, seq_lens=[S, S - 1, S // 2 + 1, 697, 70, 0, 41, 40, 500][:B])
 
 
+@pytest.mark.parametrize("dtype,B,S,slices", [("f32", 1, 8192, 4), ("f32", 1, 8200, 8), ("bf16", 16, 4096, 1), ("bf16", 16, 8200, 2)])
+def test_slices_of_the_windows_latent_axis(dtype, B, S, slices):
+    """A window whose logits share a launch with the selection (caches of at most 8192 rows) has fewer slices than one with a launch
+    of its own.  Seen through a key channel that is 2^30 - 2^30 + 20 along the latent axis, the 20 beside the second term: within
+    a slice the sum is 20, but 0 where a slice begins between the two large terms."""
+    print(f"[case] window slices {dtype} B={B} S={S}", flush=True)
+    H, r, r_hi, w = 32, 64, 2048, 64
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    ctx = binding.Sals(binding.make_desc(B, S, H, H, 128, r, 100, dtype, n_recent=w, n_sink=4), gu.DEV)
+    win = binding.Sals(binding.make_desc(B, S, H, H, 128, r_hi, w, dtype, r_score=1024), gu.DEV)
+    zeros = lambda *s: torch.zeros(s, dtype=dt, device=gu.DEV)
+    Uk, Uv = zeros(H * 128, r_hi), zeros(H * 128, r_hi)
+    Uk[0] = 1.0
+    Uv[0, 0] = 1.0
+    W, W_hi = ctx.pack_weights(zeros(H * 128, r), zeros(H * 128, r)), win.pack_weights(Uk, Uv)
+    Vw, q = zeros(B, w, r_hi), zeros(B, H, 128)
+    Vw[:, 0, 0] = 1.0
+    q[:, 0, 0] = 1.0
+    n = torch.full((B,), 2, dtype=torch.int32, device=gu.DEV)   # two tokens, both in the window; the second one's logit is zero
+    out, out2 = zeros(B, H, 128), zeros(B, H, 128)
+    idx = torch.empty((B, 168), dtype=torch.int32, device=gu.DEV)
+    n_sel = torch.empty((B,), dtype=torch.int32, device=gu.DEV)
+    Kc, pos = zeros(B, S, r), torch.zeros_like(n)
+    for cut in (r_hi // 8, r_hi // 4, r_hi // 2):   # where 8, 4 and 2 slices or more have an edge
+        Kw = zeros(B, w, r_hi)
+        Kw[:, 0, cut - r_hi // 8], Kw[:, 0, cut], Kw[:, 0, cut + r_hi // 16] = 2.0 ** 30, -2.0 ** 30, 20.0
+        ctx.decode_step_window(win, q, pos, Kc, Kc, W, Kw, Vw, W_hi, n, out, None, idx, n_sel)
+        ctx.sparse_attend_window(win, q, pos, Kc, Kc, W, Kw, Vw, W_hi, idx, n_sel, out2)
+        torch.cuda.synchronize()
+        logit = 0.0 if slices * cut >= r_hi else 20.0 / 128 ** 0.5
+        want = 1.0 / (1.0 + np.exp(-logit))
+        assert torch.equal(out, out2)
+        assert np.abs(gu.from_dev(out[:, 0, 0]) - want).max() < 2.0 ** -8, (cut, gu.from_dev(out[:, 0, 0]))
+    ctx.close(); win.close()
+
+
 @pytest.mark.parametrize("tiles,H,H_kv,n_recent,top_k,dtype", [
     ("1", 32, 4, 40, 100, "bf16"),    # 64 sums (a head's window tile each) for 32 waves
     ("2", 32, 4, 64, 60, "bf16"),     # 64 for 32
