@@ -434,7 +434,7 @@ enum {
     SALS_K_PROJECT = 0,        /* latent projection (query, or new key/value)  */
     SALS_K_SCORES = 1,         /* latent score stream over the key cache       */
     SALS_K_TOPK = 2,           /* exact top-k selection; in a decode step with a recent window on caches of at most
-                                  8192 rows also the window's logits, in the same launch */
+                                  8192 rows mostly also the window's logits, in the same launch */
     SALS_K_ATTEND_LOGITS = 3,  /* MFMA key reconstruction + RoPE + q.K; in a decode step that may include the
                                   selection (few tokens; then nothing is recorded as SALS_K_TOPK) or its last part */
     SALS_K_ATTEND_PV = 4,      /* softmax + latent-space value sum             */

@@ -645,26 +645,33 @@ template <typename T> auto window_select_for(int group)
     return window_select_kernel<T, 1, 0>;
 }
 int select_blocks(const sals_desc& d) { return ceil_div(d.B, kXcds) * kXcds; }
-// Whether a decode step has the window's logits in its selection's launch.  Both small: sequences of at most kWsMaxS tokens,
-// windows that fill tiles of one or two sequences.
-bool window_in_select(const sals_ctx* win)
-{
-    return win->d.S_max <= kWsMaxS && (win->plan.pick == 3 || win->plan.pick == 4) && win->fuse_select;
-}
-// Slices of the window's latent axis: the window's own plan; in the combined launch halved while its workgroups fit the chip at
-// once (one per compute unit in the 64-token form, two otherwise) and do not together with the selection's.  (A workgroup too many is a
-// round too many: 16 sequences, r_hi = 2048, two slices 32.0 us and a sum to add, one 30.6; one sequence, eight slices would be
-// 257 workgroups.)
-int window_slices(const sals_ctx* win)
+// Slices of the window's latent axis in the launch that it shares with the selection: the window's own plan, halved while its workgroups
+// fit the chip at once (one per compute unit in the 64-token form, two otherwise) and do not together with the selection's.  (A
+// workgroup too many is a round too many: 16 sequences, r_hi = 2048, two slices 32.0 us and a sum to add, one 30.6; one sequence, eight
+// slices would be 257 workgroups.)
+int window_select_slices(const sals_ctx* win)
 {
     const LogitsPlan& P = win->plan;
     const sals_desc& d = win->d;
-    if (!window_in_select(win)) return P.ksplit;
     const int tiles = P.pick == 4 ? ceil_div(d.B, 2) * d.H_kv : P.n_parts * d.H_kv * d.B, slots = P.pick == 4 ? 512 : 256;
     int ks = P.ksplit;
     while (ks > 1 && tiles * ks <= slots && tiles * ks + d.B > slots) ks /= 2;
     return ks;
 }
+// Whether a decode step has the window's logits in its selection's launch.  Both small: sequences of at most kWsMaxS tokens,
+// windows that fill tiles of one or two sequences; and what halved slices of the 64-token form take longer (a 64-byte step 0.29
+// us, in fp32 0.59) is less than the launches save.  (One fp32 sequence of 1024 and of 8192 tokens, launches of their own and the
+// shared one: r_hi 1280 59.0 and 56.5, 62.1 and 58.3 us a step, r_hi 1536 59.9 and 59.8, 63.0 and 61.1, r_hi 2048 62.9 and 65.0, 66.1
+// and 66.7; four bf16 ones of 1024 tokens: r_hi 1536 47.0 and 46.5, r_hi 2048 49.1 and 50.3.)
+bool window_in_select(const sals_ctx* win)
+{
+    const LogitsPlan& P = win->plan;
+    if (win->d.S_max > kWsMaxS || !win->fuse_select || (P.pick != 3 && P.pick != 4)) return false;
+    const bool bf = win->d.dtype == SALS_BF16;
+    const int steps = win->d.r * (bf ? 2 : 4) / kLgStep;
+    return P.pick == 4 || (steps / window_select_slices(win) - steps / P.ksplit) * (bf ? 0.29 : 0.59) < 8.0;
+}
+int window_slices(const sals_ctx* win) { return window_in_select(win) ? window_select_slices(win) : win->plan.ksplit; }
 
 // Whether a whole decode step on this context lets the logits kernel select by itself (no selection launch): the
 // 64-token kernel in one round of workgroups, a cache of at most 4096 rows whose score rows start 16-byte aligned, a selection that

@@ -145,13 +145,15 @@ def test_selection_beside_a_window_in_slices(oracle, S, B, tiles, top_k, monkeyp
     _case(oracle, w, seq_lens=[S, S - 1, S // 2 + 1, 697, 70, 0, 41, 40, 500][:B])
 
 
-@pytest.mark.parametrize("dtype,B,S,slices", [("f32", 1, 8192, 4), ("f32", 1, 8200, 8), ("bf16", 16, 4096, 1), ("bf16", 16, 8200, 2)])
-def test_slices_of_the_windows_latent_axis(dtype, B, S, slices):
-    """A window whose logits share a launch with the selection (caches of at most 8192 rows) has fewer slices than one with a launch
-    of its own.  Seen through a key channel that is 2^30 - 2^30 + 20 along the latent axis, the 20 beside the second term: within
+@pytest.mark.parametrize("dtype,B,S,r_hi,slices", [
+    ("f32", 1, 8192, 1024, 4), ("f32", 1, 8200, 1024, 8), ("f32", 1, 8192, 2048, 8), ("f32", 1, 8200, 2048, 8), ("bf16", 1, 8192, 2048, 4),
+    ("bf16", 1, 8200, 2048, 8), ("bf16", 16, 4096, 2048, 1), ("bf16", 16, 8200, 2048, 2)])
+def test_slices_of_the_windows_latent_axis(dtype, B, S, r_hi, slices):
+    """A window whose logits share a launch with the selection (caches of at most 8192 rows, ranks whose halved slices do not take
+    longer than the launch saves) has fewer slices than one with a launch of its own.  Seen through a key channel that is 2^30 - 2^30 + 20 along the latent axis, the 20 beside the second term: within
     a slice the sum is 20, but 0 where a slice begins between the two large terms."""
-    print(f"[case] window slices {dtype} B={B} S={S}", flush=True)
-    H, r, r_hi, w = 32, 64, 2048, 64
+    print(f"[case] window slices {dtype} B={B} S={S} r_hi={r_hi}", flush=True)
+    H, r, w = 32, 64, 64
     dt = torch.float32 if dtype == "f32" else torch.bfloat16
     ctx = binding.Sals(binding.make_desc(B, S, H, H, 128, r, 100, dtype, n_recent=w, n_sink=4), gu.DEV)
     win = binding.Sals(binding.make_desc(B, S, H, H, 128, r_hi, w, dtype, r_score=1024), gu.DEV)
