@@ -95,7 +95,7 @@ sals_status sals_workspace_bytes(const sals_desc* desc, size_t* bytes);
  * must not write to it.  Part of it holds a constant table (RoPE cos/sin of every
  * position 0 .. S_max, 512 bytes per position), see sals_prepare.  The launch shapes
  * of every stage are fixed here.  An fp32 context also takes a workspace with room for a value sum in ranges of
- * 128 tokens only, and then uses those (sals_workspace_bytes counts ranges of 64).  Host-only, allocates only host
+ * 128 tokens only, and then uses those (sals_workspace_bytes counts ranges of 64 where they are faster).  Host-only, allocates only host
  * memory. */
 sals_status sals_create(const sals_desc* desc, void* d_workspace, size_t workspace_bytes,
                         sals_ctx** out);

@@ -147,6 +147,15 @@ inline int dense_heads(const sals_desc& d)
     return d.dtype == SALS_BF16 && d.H_q / d.H_kv < 4 && d.H_kv % 2 == 0 ? 2 : 1;
 }
 
+// Rows of an output projection workgroup: the (sequence, query head) pairs of a KV head, 1, 2, 4, 8 or 16 of them.
+constexpr int kOutRows = 16;
+int out_tile_rows(const sals_desc& d)
+{
+    int R = 1;
+    while (R < kOutRows && R < d.B * (d.H_q / d.H_kv)) R *= 2;
+    return R;
+}
+
 // `short_ranges`: fp32 value sums in ranges of one step of 64 tokens (otherwise of two), whose partial sums take more workspace.
 Layout make_layout(const sals_desc& d, bool short_ranges = true)
 {
@@ -163,13 +172,18 @@ Layout make_layout(const sals_desc& d, bool short_ranges = true)
         if (const char* e = std::getenv("SALS_TUNE_PROJ_NP")) { const int v = std::atoi(e); if (v >= 1 && v <= kScoreMaxParts && nks % v == 0) np = v; }  // tuning aid
         L.proj_np = np;
     }
-    // value sum: split the selected tokens into ranges of whole 64-token steps (at least two steps in bf16, one in fp32 if the
-    // workspace has room for it, at most kPvMaxTok tokens) as long as every workgroup still gets a CU of its own (measured: a few CUs
-    // with two workgroups set the kernel's duration; fp32, 128 tokens, r = 512 on 16 workgroups instead of 8: 31.0 -> 30.1 us a step)
+    // value sum: split the selected tokens into ranges of whole 64-token steps (at least two steps, at most kPvMaxTok tokens) as
+    // long as every workgroup still gets a CU of its own (measured: a few CUs with two workgroups set the kernel's duration)
     {
         int blocks = d.r / kPvCols;
-        int want = std::max(1, 256 / (blocks * d.B));
-        int n_tr = std::max(1, std::min(std::min(want, kMaxRanges), ceil_div(k_tot, (d.dtype == SALS_F32 && short_ranges ? 1 : 2) * kPvTJ)));
+        int want = std::min(std::max(1, 256 / (blocks * d.B)), kMaxRanges);
+        int n_tr = std::max(1, std::min(want, ceil_div(k_tot, 2 * kPvTJ)));
+        // fp32, if the workspace has room for it: ranges of one step, as far as the output projection still takes all ranges' sums
+        // with one load (kOutRows lanes hold its rows, and further ranges of them).  128 tokens, r = 512, one sequence of 32 KV heads: 32.7
+        // us a step with one range and 31.7 with two; past that line two loads cost more than the value sum gains: 4 sequences of 32
+        // query and 8 KV heads, 256 tokens, r = 640 45.6 us with two ranges and 48.3 with four, 3 with 512 tokens 57.3 and 61.7.
+        if (d.dtype == SALS_F32 && short_ranges)
+            n_tr = std::max(n_tr, std::min(std::min(want, ceil_div(k_tot, kPvTJ)), kOutRows / out_tile_rows(d)));
         if (const char* e = std::getenv("SALS_TUNE_PV_RANGES")) n_tr = std::max(1, std::min(64, std::atoi(e)));  // tuning aid
         n_tr = std::max(n_tr, ceil_div(k_tot, kPvMaxTok));
         int tok = ceil_div(ceil_div(k_tot, n_tr), kPvTJ) * kPvTJ;
@@ -802,10 +816,8 @@ template <typename T>
 void launch_out(hipStream_t st, const sals_desc& d, int n_tr, const T* Uv, const float* tpart, int r2, int n_tr2, const T* Uv2,
                 const float* tpart2, void* out)
 {
-    const int n_rows = d.B * (d.H_q / d.H_kv);
-    int R = 1;
-    while (R < 16 && R < n_rows) R *= 2;
-    const int spw = ceil_div(d.r / (4 * elem<T>::vec), kOutWaves), loads = ceil_div(n_tr, 16 / R);
+    const int n_rows = d.B * (d.H_q / d.H_kv), R = out_tile_rows(d);
+    const int spw = ceil_div(d.r / (4 * elem<T>::vec), kOutWaves), loads = ceil_div(n_tr, kOutRows / R);
     const dim3 grid(d.H_kv, kHeadDim / 16, ceil_div(n_rows, R));
 #define SALS_OUT(BATCH, RPR, BATCH2)                                                                                      \
     hipLaunchKernelGGL((attend_out_kernel<T, BATCH, RPR, BATCH2>), grid, dim3(64 * kOutWaves), 0, st, Uv, tpart, d.B, d.r, \

@@ -168,7 +168,7 @@ def test_no_host_memory_is_an_error_code(sb):
     (dict(B=1, S_max=64, H_kv=32, r=2048, r_score=1024, top_k=512), 1335296),
     (dict(B=1, S_max=1000, H_kv=32, r=512, top_k=128), 1014016),
     (dict(B=2, S_max=700, H_q=8, H_kv=8, r=128, top_k=300), 722688),
-    (dict(B=3, S_max=4096, r=640, top_k=512), 4548096)])
+    (dict(B=2, S_max=4096, H_kv=32, r=640, top_k=512), 3332096)])
 def test_fp32_context_on_the_workspace_of_long_value_sum_ranges(sb, kw, nbytes):
     """What an fp32 context needs when its value sum has ranges of 128 tokens is enough (one alignment step less is not);
     sals_workspace_bytes, which counts ranges of 64, asks for more."""
@@ -179,3 +179,18 @@ def test_fp32_context_on_the_workspace_of_long_value_sum_ranges(sb, kw, nbytes):
     assert sb._lib.sals_create(ctypes.byref(desc), at, nbytes, ctypes.byref(h)) == sb.SALS_OK
     sb._lib.sals_destroy(h)
     assert sb._lib.sals_create(ctypes.byref(desc), at, nbytes - 256, ctypes.byref(h)) == sb.SALS_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("kw,ranges", [
+    (dict(B=1, H_kv=32, top_k=512), 8), (dict(B=2, H_kv=32, top_k=512), 8), (dict(B=4, H_kv=32, top_k=512), 4),
+    (dict(B=3, H_kv=32, top_k=200), 4), (dict(B=8, H_kv=32, top_k=128), 2), (dict(B=1, top_k=500), 4), (dict(B=2, top_k=128), 2),
+    (dict(B=2, top_k=256), 2), (dict(B=3, top_k=128), 1), (dict(B=4, top_k=256), 2), (dict(B=8, top_k=100), 1)])
+def test_fp32_value_sum_ranges_of_one_output_load(sb, kw, ranges, monkeypatch):
+    """fp32 value sums have ranges of 64 tokens as far as one load of the output projection takes all of them (16 rows of
+    sequences x query heads x ranges), and ranges of 128 otherwise: seen through the workspace that their sums take."""
+    desc = _desc(sb, dtype="f32", r=256, **kw)
+    got = sb.workspace_bytes(desc)
+    monkeypatch.setenv("SALS_TUNE_PV_RANGES", str(ranges))
+    assert got == sb.workspace_bytes(desc)
+    monkeypatch.setenv("SALS_TUNE_PV_RANGES", str(2 * ranges))
+    assert got < sb.workspace_bytes(desc) or 2 * ranges > -(-kw["top_k"] // 64)
