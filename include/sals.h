@@ -388,7 +388,8 @@ sals_status sals_overlap_score(sals_ctx* ctx, const void* q, const int32_t* q_po
  *
  * sals_calib_eigenvectors computes the eigen-decomposition of C (symmetric, positive semi-definite up to the rounding
  * of its sums) by one-sided Jacobi rotations in fp64, of the rows of the Cholesky factor of C plus a small multiple of
- * the identity, and returns all eigenvalues in descending order and the r leading eigenvectors:
+ * the identity (with a workspace of the full size and D up to 1536 also by orthogonal transformations of all rows at once,
+ * which are applied in fp64), and returns all eigenvalues in descending order and the r leading eigenvectors:
  *   C          [D, D] fp64 (device)    in; OVERWRITTEN (its rows become eigenvalue times eigenvector)
  *   D          multiple of 256, at most 8192;  r  1 .. D
  *   dtype      storage type T of U
@@ -401,17 +402,18 @@ sals_status sals_overlap_score(sals_ctx* ctx, const void* q, const int32_t* q_po
  *                                      they span together); negative ones are returned as zero.
  *   workspace  device, 256-byte aligned, sals_calib_eigenvectors_workspace_bytes(D) bytes (the factor and two partial
  *              sums of a series, 8 D^2 bytes each, and some D of scratch).  Fewer are taken from 8 D^2 + 900 D on
- *              (SALS_ERR_WORKSPACE below what the sweeps need): the last rotations are then made by one to three
- *              further sweeps, whose sums are spread over as much of the device as the scratch allows (D = 1024:
- *              9.9 ms with the full size, 11.2 with 8 D^2 + 4000 D bytes, 16.9 with the least)
- *   max_sweeps at least 1 (host): a sweep rotates every pair of rows once; the call stops when no rotation that
+ *              (SALS_ERR_WORKSPACE below what the sweeps need): all rotations are then made by sweeps, whose
+ *              sums are spread over as much of the device as the scratch allows (D = 1024: 6.3 ms with the full size,
+ *              11.2 with 8 D^2 + 4000 D bytes, 16.9 with the least)
+ *   max_sweeps at least 1 (host): a sweep rotates every pair of rows once (a transformation of all rows counts as
+ *              one); the call stops when no rotation that
  *              involves one of the r largest rows would turn by more than 1e-11 (found by a sweep, or from the Gram
  *              matrix of all rows behind a sweep of small rotations; with a workspace of the full size the last,
  *              smallest rotations are made all at once), or after max_sweeps
  *   sweeps     host int32, out (may be NULL): sweeps run; the negative of that number if the limit was reached
  *              before convergence (the results are then the current approximation); 0 if there was nothing to
  *              rotate (C is zero, or not finite: then its rows come back as they are)
- * BLOCKING: it waits for hip_stream once per sweep to read the convergence measure (and after each factorisation: one,
+ * BLOCKING: it waits for hip_stream at least once per sweep to read the convergence measure (and after each factorisation: one,
  * or a few for a C that rounding has left indefinite), so it cannot be captured.
  * Errors as above. */
 size_t sals_calib_accumulate_workspace_bytes(int32_t dtype, int32_t D);

@@ -14,8 +14,9 @@
 //                A sweep rotates every pair of rows once: a first step inside 32-row blocks, then D / 32 - 1 steps of
 //                disjoint pairs of such blocks (round-robin).  A step is two launches: one forms the pairs' 64 x 64 Gram
 //                matrices, a second one rotates them to orthogonality in LDS and applies the accumulated rotations to the
-//                rows with the fp64 matrix instructions.
-//                fp64 throughout.
+//                rows with the fp64 matrix instructions.  Where that is faster, orthogonal transformations of all rows at
+//                once take the place of most sweeps (k_calib_all.hpp).
+//                Rows, Gram matrices and everything that is applied to the rows: fp64 throughout.
 #pragma once
 #include "common.hpp"
 #include "k_gemm.hpp"
@@ -542,6 +543,15 @@ __global__ __launch_bounds__(256) void calib_jacobi_inside_gram_kernel(const dou
     jac_gram_store(acc, red, part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kJacRec);
 }
 
+// Pairs of blocks of a step: those of a sweep, or neighbours
+constexpr int kJacNearEven = -1, kJacNearOdd = -2;   // blocks 2 k, 2 k + 1; 2 k + 1, 2 k + 2 (the last one with the first)
+__device__ __forceinline__ void jac_pair(int n, int step, int k, int* p, int* q)
+{
+    if (step >= 0) { calib_pair(n, step, k, p, q); return; }
+    *p = 2 * k + (step == kJacNearOdd ? 1 : 0);
+    *q = *p + 1 < n ? *p + 1 : 0;
+}
+
 // The same for the step's pairs of blocks: part[slice][pair][10][16][16], five tiles per workgroup (grid (pairs, slices, 2)).
 // The pair index runs fastest in both launches of a step, so a pair's sums are written and read on one die.
 __global__ __launch_bounds__(256) void calib_jacobi_gram_kernel(const double* __restrict__ G, int D, int step, int slice_cols,
@@ -550,7 +560,7 @@ __global__ __launch_bounds__(256) void calib_jacobi_gram_kernel(const double* __
     constexpr int NT = kJacTiles / 2;
     __shared__ double red[3][NT * kJacTile];
     int p, q;
-    calib_pair(D / kJacBig, step, blockIdx.x, &p, &q);
+    jac_pair(D / kJacBig, step, blockIdx.x, &p, &q);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kg = lane >> 4;
     const bool half = blockIdx.z != 0;  // uniform
     const double* g[4];
@@ -602,6 +612,9 @@ __device__ __forceinline__ void jac_rotation(double aa, double bb, double ab, do
     *s = ok ? __builtin_bit_cast(double, ab_d) * hi * ci : 0.0;
     *tan = *s * ci;
 }
+// What is applied to the rows turns by these: c so that c^2 + s^2 = 1 to rounding.  (As computed it is above 1 by 5e-17 on average
+// where the angles are small, ten sweeps of which added 1.8e-13 to every eigenvalue at D = 1024.)
+__device__ __forceinline__ double jac_unit(double c, double s) { return fma(0.5 * c, fma(-s, s, fma(-c, c, 1.0)), c); }
 // (non-negative doubles are ordered like their bits; nothing waits for the result)
 __device__ __forceinline__ void conv_max(double* at, double v)
 {
@@ -725,11 +738,12 @@ __device__ __forceinline__ void jac_accumulate(const JacRounds& L, double (&x)[k
 #pragma unroll 1
     for (int t = 0; t < kJacB; ++t) {
         const f64x2 R = L.cs[t][l16];
+        const double c = jac_unit(R.x, R.y), s = R.y;
 #pragma unroll
         for (int e = 0; e < kJacNc; ++e) {
             const double xe = x[e], ye = y[e];
-            x[e] = R.x * xe - R.y * ye;
-            y[e] = row16_next(R.y * xe + R.x * ye);
+            x[e] = c * xe - s * ye;
+            y[e] = row16_next(s * xe + c * ye);
         }
         __syncthreads();
     }
@@ -797,8 +811,9 @@ __global__ __launch_bounds__(kJacInsideThreads) void calib_jacobi_inside_kernel(
                 Wn[pi * LD + qj] = sj * r00 + cj * r01;
                 Wn[qi * LD + pj] = cj * r10 - sj * r11;
                 Wn[qi * LD + qj] = sj * r10 + cj * r11;
-                Qn[pi * LD + j] = c * x0 - s * y0; Qn[qi * LD + j] = s * x0 + c * y0;
-                Qn[pi * LD + j + kJacB] = c * x1 - s * y1; Qn[qi * LD + j + kJacB] = s * x1 + c * y1;
+                const double cu = jac_unit(c, s);
+                Qn[pi * LD + j] = cu * x0 - s * y0; Qn[qi * LD + j] = s * x0 + cu * y0;
+                Qn[pi * LD + j + kJacB] = cu * x1 - s * y1; Qn[qi * LD + j + kJacB] = s * x1 + cu * y1;
             }
             __syncthreads();
             cur ^= 1;
@@ -872,7 +887,7 @@ __global__ __launch_bounds__(kJacThreads) void calib_jacobi_rotate_kernel(double
     __shared__ JacRounds s_rounds[2];
     __shared__ int s_any;
     int p, q;
-    calib_pair(D / kJacBig, step, blockIdx.x, &p, &q);
+    jac_pair(D / kJacBig, step, blockIdx.x, &p, &q);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, kg = lane >> 4;
     const bool solver = wave < 4;   // uniform
     const int grp = (wave >> 1) & 1;
@@ -1047,157 +1062,24 @@ __global__ __launch_bounds__(kCalThreads) void calib_rownorm_kernel(const double
     }
 }
 
-// ---- The last angles -------------------------------------------------------------------------------------------------
-// Convergence is quadratic: behind a sweep whose rotations were at most a few tenths, all angles t_pq = <p, q> / (|q|^2 -
-// |p|^2) between rows are small, and all rotations can be made at once: with E_pq = -t_pq = -E_qp, the rows of exp(E) G are
-// orthogonal up to the square of the angles.  The series is cut behind E^2 or E^4, which leaves a factor that differs from an
-// orthogonal one by |E|^4 / 4 or |E|^6 / 72; the host uses it where that is below the rounding of the sums (Frobenius norm at most
-// 2e-4, or 4e-3).  At D = 1024 a product takes 52 us and the angles 63, a sweep 780: the last one to three of 11 to 13 sweeps are
-// replaced (a call 10.3 to 11.2 ms -> 9.6 to 9.9; D = 4096: 146 -> 140).
-//
-// 64 x 64 tiles of G G^T (upper triangle): E, and per tile {largest |t| (at most 1/2), sum of t^2}, both over pairs that are not
-// orthogonal to working precision and of which one row has a squared norm >= lead; where both have, their cosine counts as
-// well as t (beside a far larger row, t is small long before the smaller row's direction is right).  norm: the rows' norms.
-// Eight waves: (half of the columns) x (quarter of the tile), operands straight from memory.
-__global__ __launch_bounds__(512) void calib_jacobi_angles_kernel(const double* __restrict__ G, int D, const double* __restrict__ norm,
-                                                                  double lead, double* __restrict__ E, f64x2* __restrict__ found)
+// number of rows with a norm larger than row i's (equal ones by row index), by a whole workgroup
+__device__ __forceinline__ int calib_rank(const double* __restrict__ norm, int D, int i, int (&cnt)[kCalThreads / kWave])
 {
-    __shared__ double red[4][32 * 33];
-    __shared__ f64x2 s_found[4];
-    int tr, tc;
-    cov_tile(blockIdx.x, D / 64, &tr, &tc);
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kg = lane >> 4;
-    const int part = wave & 3;
-    const int r0 = tr * 64 + (part >> 1) * 32, c0 = tc * 64 + (part & 1) * 32;
-    const double* ga = G + (size_t)(r0 + l16) * D + (wave >> 2) * (D / 2) + kg * 4;
-    const double* gb = G + (size_t)(c0 + l16) * D + (wave >> 2) * (D / 2) + kg * 4;
-    f64x4 acc[2][2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int v = 0; v < 2; ++v) acc[u][v] = f64x4{0.0, 0.0, 0.0, 0.0};
-    for (int c = 0; c < D / 2; c += 32) {  // two groups of 16 columns requested together
-        f64x4 a[2][2], b[2][2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                a[h][u] = *reinterpret_cast<const f64x4*>(ga + (size_t)(16 * u) * D + c + 16 * h);
-                b[h][u] = *reinterpret_cast<const f64x4*>(gb + (size_t)(16 * u) * D + c + 16 * h);
-            }
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int v = 0; v < 2; ++v) acc[u][v] = mma_f64(a[h][u][e], b[h][v][e], acc[u][v]);
+    const int tid = threadIdx.x;
+    const double li = norm[i];
+    int c = 0;
+    for (int j = tid; j < D; j += kCalThreads) {
+        const double lj = norm[j];
+        c += (lj > li || (lj == li && j < i)) ? 1 : 0;
     }
-    auto at = [&](int u, int v, int e) { return (u * 16 + kg + 4 * e) * 33 + v * 16 + l16; };
-    double* const t = red[part];
-    if (wave >= 4) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int v = 0; v < 2; ++v)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) t[at(u, v, e)] = acc[u][v][e];
-    }
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, kWave);
+    if ((tid & 63) == 0) cnt[tid >> 6] = c;
     __syncthreads();
-    if (wave < 4) {
-        double most = 0.0, sum = 0.0;
+    int rank = 0;
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int v = 0; v < 2; ++v)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int r = r0 + u * 16 + kg + 4 * e, c = c0 + v * 16 + l16;
-                    const double nr = norm[r], nc = norm[c], aa = nr * nr, bb = nc * nc, ab = acc[u][v][e] + t[at(u, v, e)], d = bb - aa;
-                    const bool counts = r != c && fmax(aa, bb) >= lead && jac_open(aa, bb, ab);
-                    const double th = counts ? ab / d : 0.0;
-                    if (counts && r < c) {
-                        most = fmax(most, fabs(ab) / fmax(fabs(d), 2.0 * fabs(ab)));
-                        if (fmin(aa, bb) >= lead) most = fmax(most, fabs(ab) / (nr * nc));
-                        sum += th * th;
-                    }
-                    E[(size_t)r * D + c] = -th;
-                    t[at(u, v, e)] = th;
-                }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) { most = fmax(most, __shfl_xor(most, o, kWave)); sum += __shfl_xor(sum, o, kWave); }
-        if (lane == 0) s_found[part] = f64x2{most, sum};
-        if (tr != tc) {  // uniform: the other triangle (this wave's own piece of LDS)
-            const int l32 = lane & 31;
-            for (int k = lane >> 5; k < 32; k += 2) E[(size_t)(c0 + k) * D + r0 + l32] = t[l32 * 33 + k];
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0)
-        found[blockIdx.x] = f64x2{fmax(fmax(s_found[0].x, s_found[1].x), fmax(s_found[2].x, s_found[3].x)),
-                                  (s_found[0].y + s_found[1].y) + (s_found[2].y + s_found[3].y)};
-}
-
-// Y = G + f E X (Y may be G, X may not).  64 x 64 tiles, eight waves as above; grid (D / 64, D / 64).
-__global__ __launch_bounds__(512) void calib_jacobi_apply_kernel(const double* __restrict__ E, const double* __restrict__ X, const double* G,
-                                                                 double f, double* Y, int D)
-{
-    __shared__ double red[4][16 * 64];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kg = lane >> 4;
-    const int part = wave & 3, k0 = (wave >> 2) * (D / 2);
-    const int r0 = blockIdx.y * 64 + (part >> 1) * 32, c0 = blockIdx.x * 64 + (part & 1) * 32;
-    const double* ea = E + (size_t)(r0 + l16) * D + k0 + kg * 4;
-    const double* xb = X + (size_t)(k0 + kg * 4) * D + c0 + l16;
-    f64x4 acc[2][2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int v = 0; v < 2; ++v) acc[u][v] = f64x4{0.0, 0.0, 0.0, 0.0};
-    struct Terms { f64x4 a[2][2]; double b[2][2][4]; } now, next;   // 32 terms; lane: k + 4 kg .. + 4 of either operand
-    auto load = [&](Terms& x, int k) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-#pragma unroll
-            for (int u = 0; u < 2; ++u) x.a[h][u] = *reinterpret_cast<const f64x4*>(ea + (size_t)(16 * u) * D + k + 16 * h);
-#pragma unroll
-            for (int v = 0; v < 2; ++v)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x.b[h][v][e] = xb[(size_t)(k + 16 * h + e) * D + 16 * v];
-        }
-    };
-    auto multiply = [&](const Terms& x) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int v = 0; v < 2; ++v) acc[u][v] = mma_f64(x.a[h][u][e], x.b[h][v][e], acc[u][v]);
-    };
-    load(now, 0);
-    for (int k = 0; k < D / 2; k += 64) {  // (the next terms on their way; past the end: the last ones again)
-        load(next, k + 32);
-        asm volatile("" ::: "memory");  // (keeps the loads here)
-        multiply(now);
-        load(now, min(k + 64, D / 2 - 32));
-        asm volatile("" ::: "memory");
-        multiply(next);
-    }
-    if (wave >= 4) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) red[part][i * 64 + lane] = acc[i >> 3][(i >> 2) & 1][i & 3];
-    }
-    __syncthreads();
-    if (wave < 4) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int u = i >> 3, v = (i >> 2) & 1, e = i & 3;
-            const size_t at = (size_t)(r0 + u * 16 + kg + 4 * e) * D + c0 + v * 16 + l16;
-            Y[at] = fma(f, acc[u][v][e] + red[part][i * 64 + lane], G[at]);
-        }
-    }
+    for (int w = 0; w < kCalThreads / kWave; ++w) rank += cnt[w];
+    return rank;
 }
 
 // Row i of G takes rank = number of rows with a larger norm (equal ones by row index); eigval[rank] = lambda_i and, for
@@ -1211,20 +1093,9 @@ __global__ __launch_bounds__(kCalThreads) void calib_select_kernel(const double*
                                                                    double* __restrict__ C)
 {
     __shared__ int cnt[kCalThreads / kWave];
-    const int i = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int i = blockIdx.x, tid = threadIdx.x;
     const double li = norm[i];
-    int c = 0;
-    for (int j = tid; j < D; j += kCalThreads) {
-        const double lj = norm[j];
-        c += (lj > li || (lj == li && j < i)) ? 1 : 0;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, kWave);
-    if (lane == 0) cnt[wave] = c;
-    __syncthreads();
-    int rank = 0;
-#pragma unroll
-    for (int w = 0; w < kCalThreads / kWave; ++w) rank += cnt[w];
+    const int rank = calib_rank(norm, D, i, cnt);
     const double lam = ROOT ? fmax(li * li - shift, 0.0) : li;
     if (tid == 0) eigval[rank] = lam;
     const double s = li > 0.0 ? sgn[i] / li : 0.0, to_c = ROOT && li > 0.0 ? lam / li : 0.0;

@@ -16,6 +16,7 @@
 #include "common.hpp"
 #include "k_attend.hpp"
 #include "k_calib.hpp"
+#include "k_calib_all.hpp"
 #include "k_dense.hpp"
 #include "k_logits.hpp"
 #include "k_logits_small.hpp"
@@ -1959,6 +1960,39 @@ bool eig_plan(int D, size_t bytes, EigWs* w, int* n_part, bool* series)
 }
 }  // namespace
 
+namespace {
+// Transformations of all rows at once (k_calib_all.hpp) in place of sweeps, up to kAllMaxD.  One takes 0.55 ms at D = 1024, where a
+// sweep takes 0.79, and from the Cholesky factor on it brings the rows as far as a sweep does, or further once the angles are below
+// one; its products grow with D^3 and a sweep's steps with D^2, so above 1024 it comes later.  A call, r = 5/8 D, in ms with the
+// transformations behind one, two and three sweeps (and with sweeps alone): D = 256 1.9 / 1.9 / 2.0 (2.2), 512 3.3 / 3.3 / 3.4 (4.4),
+// 1024 6.3 / 6.3 / 6.7 (9.6), 1536 19.2 / 17.8 / 16.6 (18.8), 2048 37.8 / 31.4 / 28.7 (29.2).
+constexpr int kAllMaxD = 1536;
+inline int all_first(int D) { return D <= 1024 ? 1 : 3; }
+// |E| at most: larger angles gain nothing (8 and 12: 6.4 and 6.5 ms at D = 1024), and a smaller limit costs a transformation more (3: 7.0)
+constexpr double kAllCap = 6.0;
+// the series of the exponential: cut behind E^4 it differs from an orthogonal matrix by |E|^6 / 72
+constexpr double kSeriesNorm = 4e-3;
+// the product kernels' dynamic LDS, beyond the default limit for the ones with a row-by-row operand
+sals_status calib_all_lds()
+{
+    auto allow = [](const void* kern, size_t bytes) {
+        return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
+    };
+    constexpr size_t nt = prod_lds<float, float, false>();
+    const bool ok = allow(reinterpret_cast<const void*>(calib_angles_kernel<false>), prod_lds<double, double, false>()) &&
+                    allow(reinterpret_cast<const void*>(calib_angles_kernel<true>), prod_lds<double, double, false>()) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_kernel<0, true>), nt) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_kernel<0, false>), nt) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_kernel<1, false>), nt) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_kernel<2, false>), nt) &&
+                    allow(reinterpret_cast<const void*>(calib_defect_kernel), nt) &&
+                    allow(reinterpret_cast<const void*>(calib_correction_kernel), nt) &&
+                    allow(reinterpret_cast<const void*>(calib_apply_kernel<float, false>), prod_lds<float, double, true>()) &&
+                    allow(reinterpret_cast<const void*>(calib_apply_kernel<double, true>), prod_lds<double, double, true>());
+    return ok ? SALS_OK : SALS_ERR_HIP;
+}
+}  // namespace
+
 size_t sals_calib_eigenvectors_workspace_bytes(int32_t D)
 {
     if (D < kCalThreads || D % kCalThreads != 0 || D > kCalMaxD) return 0;
@@ -1976,6 +2010,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     bool series;
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0 || !eig_plan(D, workspace_bytes, &off, &n_part, &series))
         return SALS_ERR_WORKSPACE;
+    if (calib_all_lds() != SALS_OK) return SALS_ERR_HIP;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     auto at = [&](size_t o) { return reinterpret_cast<double*>(ws + o); };
@@ -1983,9 +2018,13 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     int* fail = reinterpret_cast<int*>(ws + off.conv);
     const int n_blocks = D / kJacBig, n_pairs = n_blocks / 2, n_steps = n_blocks - 1;
     const int slices = jac_slices(D);
-    const int n_tiles = D / 64 * (D / 64 + 1) / 2;   // of the angles, which lie where the partial Gram matrices do
+    const int n_tiles = (D / 64) * (D / 64);   // of the angles, whose results lie where the partial Gram matrices do
     f64x2* const found = reinterpret_cast<f64x2*>(part);
-    const std::unique_ptr<double[]> host(new (std::nothrow) double[(size_t)n_blocks + D + 2 * n_tiles]);
+    double* const square = part + 2 * (size_t)n_tiles;
+    double *rows = G, *other = at(off.Y0), *third = at(off.Y1);   // the rows, and room for two more matrices (`series`)
+    double* const sorted = diag;                                  // (the factored blocks are in place by then)
+    const bool all = series && D <= kAllMaxD;
+    const std::unique_ptr<double[]> host(new (std::nothrow) double[(size_t)n_blocks + D + 3 * n_tiles]);
     if (!host) return SALS_ERR_HIP;
     double *const h_conv = host.get(), *const h_norm = h_conv + n_blocks, *const h_found = h_norm + D;
     auto row_norms = [&](const double* M) -> bool {  // row norms to the host (blocking)
@@ -2023,54 +2062,134 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         }
         converged = failed != 0;
     }
-    while (done < max_sweeps && !converged) {
-        if (hipMemsetAsync(conv, 0, (size_t)n_blocks * 8, st) != hipSuccess) return SALS_ERR_HIP;
-        hipLaunchKernelGGL(calib_jacobi_inside_gram_kernel, dim3(n_blocks, n_part), dim3(256), 0, st, G, D, D / n_part, part);
-        hipLaunchKernelGGL(calib_jacobi_inside_kernel, dim3(n_blocks, slices), dim3(kJacInsideThreads), 0, st, G, D, D / slices, part,
+    // r-th largest squared norm, a little less (so that the r-th row itself is among the leading ones)
+    auto leading = [&]() {
+        std::nth_element(h_norm, h_norm + (r - 1), h_norm + D, std::greater<double>());
+        const double nr = h_norm[r - 1];
+        return 0.999 * nr * nr;
+    };
+    auto block_step = [&](int step) {  // rotates the pairs of blocks of a step of a sweep, or neighbours
+        hipLaunchKernelGGL(calib_jacobi_gram_kernel, dim3(n_pairs, n_part, 2), dim3(256), 0, st, rows, D, step, D / n_part, part);
+        hipLaunchKernelGGL(calib_jacobi_rotate_kernel, dim3(n_pairs, slices), dim3(kJacThreads), 0, st, rows, D, step, D / slices,
+                           part, n_part, lead, conv);
+    };
+    auto inside_step = [&]() {
+        hipLaunchKernelGGL(calib_jacobi_inside_gram_kernel, dim3(n_blocks, n_part), dim3(256), 0, st, rows, D, D / n_part, part);
+        hipLaunchKernelGGL(calib_jacobi_inside_kernel, dim3(n_blocks, slices), dim3(kJacInsideThreads), 0, st, rows, D, D / slices, part,
                            n_part, lead, conv);
-        for (int step = 0; step < n_steps; ++step) {
-            hipLaunchKernelGGL(calib_jacobi_gram_kernel, dim3(n_pairs, n_part, 2), dim3(256), 0, st, G, D, step, D / n_part, part);
-            hipLaunchKernelGGL(calib_jacobi_rotate_kernel, dim3(n_pairs, slices), dim3(kJacThreads), 0, st, G, D, step, D / slices,
-                               part, n_part, lead, conv);
+    };
+    const dim3 tile_grid(D / 64, D / 64), prod(kProdThreads);
+    bool settled = false;
+    double last = 1e300;   // |E| of the transformation before, infinite behind a sweep
+    while (done < max_sweeps && !converged) {
+        double worst = 0.0;   // largest rotation that is known to have been left behind
+        if (all && !settled && done >= all_first(D) && last > 0.0) {
+            // One transformation of all rows.
+            inside_step();
+            block_step(kJacNearEven);
+            block_step(kJacNearOdd);
+            hipLaunchKernelGGL(calib_rownorm_kernel, dim3(D), dim3(kCalThreads), 0, st, rows, D, norm, sgn);
+            hipLaunchKernelGGL(calib_sort_kernel, dim3(D), dim3(kCalThreads), 0, st, rows, norm, D, other, sorted);
+            std::swap(rows, other);
+            float *const E = reinterpret_cast<float*>(third), *const A = E + (size_t)D * D;
+            hipLaunchKernelGGL((calib_angles_kernel<true>), tile_grid, prod, (prod_lds<double, double, false>()), st, rows, D, sorted, r, 0.0, E,
+                               found);
+            hipLaunchKernelGGL((calib_polar_kernel<0, true>), tile_grid, prod, (prod_lds<float, float, false>()), st, E, E, D, 1.f, 0.f, 0.f,
+                               nullptr, 0.f, nullptr, A, square);
+            if (launch_status() != SALS_OK ||
+                hipMemcpyAsync(h_found, found, (size_t)n_tiles * (sizeof(f64x2) + sizeof(double)), hipMemcpyDeviceToHost, st) != hipSuccess ||
+                hipStreamSynchronize(st) != hipSuccess)
+                return SALS_ERR_HIP;
+            ++done;
+            double e2 = 0.0, a2 = 0.0;
+            for (int i = 0; i < n_tiles; ++i) { e2 += h_found[2 * i + 1]; a2 += h_found[2 * n_tiles + i]; }
+            // (a matrix on which the transformations gain little, as with eigenvalues that repeat or rows of very different norms
+            // in no order, gets a sweep in between)
+            const double now = std::sqrt(e2);
+            if (now <= kSeriesNorm) {
+                worst = now;
+                last = 0.0;   // (what the series leaves is for sweeps)
+                settled = true;
+                if (!row_norms(rows)) return SALS_ERR_HIP;
+                lead = leading();
+            } else {
+                last = now < 0.9 * last ? now : 0.0;
+                // |E| is at most the fourth root of the sum of squares of E E^T; beyond kAllCap E is scaled down to it
+                const double bound = std::sqrt(std::sqrt(a2)), tau = std::min(1.0, kAllCap / bound), tb = tau * bound;
+                // singular values of (I + tau E) / top: low .. 1
+                const double top = std::sqrt(1.0 + tb * tb);
+                double low = 1.0 / top;
+                auto scale_of = [&]() {   // of the next step, and its lower bound behind it
+                    const double a = low < 0.9985 ? std::sqrt(3.0 / (1.0 + low + low * low)) : 1.0;
+                    const double x = a * low;
+                    low = 0.5 * x * (3.0 - x * x);
+                    return a;
+                };
+                bool more = low < 0.9985;
+                const double a1 = scale_of(), w = 0.5 * a1 * a1 * a1 / (top * top * top), c1 = 1.5 * a1 / top - w;
+                float *X = reinterpret_cast<float*>(other), *X2 = X + (size_t)D * D, *const Y = E;
+                hipLaunchKernelGGL((calib_polar_kernel<2, false>), tile_grid, prod, (prod_lds<float, float, false>()), st, A, E, D,
+                                   (float)(w * tau * tau * tau), (float)c1, (float)(c1 * tau), E, (float)(-w * tau * tau), A, X, nullptr);
+                while (more) {
+                    more = low < 0.9985;
+                    const double a = scale_of();
+                    hipLaunchKernelGGL((calib_polar_kernel<0, false>), tile_grid, prod, (prod_lds<float, float, false>()), st, X, X, D, 1.f,
+                                       0.f, 0.f, nullptr, 0.f, nullptr, Y, nullptr);
+                    hipLaunchKernelGGL((calib_polar_kernel<1, false>), tile_grid, prod, (prod_lds<float, float, false>()), st, X, Y, D,
+                                       (float)(-0.5 * a * a * a), 0.f, (float)(1.5 * a), X, 0.f, nullptr, X2, nullptr);
+                    std::swap(X, X2);
+                }
+                hipLaunchKernelGGL(calib_defect_kernel, tile_grid, prod, (prod_lds<float, float, false>()), st, X, D, C, X2);
+                hipLaunchKernelGGL(calib_correction_kernel, tile_grid, prod, (prod_lds<float, float, false>()), st, X2, D, C);
+                hipLaunchKernelGGL((calib_apply_kernel<float, false>), tile_grid, prod, (prod_lds<float, double, true>()), st, X, rows, nullptr,
+                                   1.0, third, D);
+                hipLaunchKernelGGL((calib_apply_kernel<double, true>), tile_grid, prod, (prod_lds<double, double, true>()), st, C, third, third,
+                                   1.0, other, D);
+                std::swap(rows, other);
+                if (launch_status() != SALS_OK) return SALS_ERR_HIP;
+                if (done >= max_sweeps && !row_norms(rows)) return SALS_ERR_HIP;
+                continue;
+            }
+        } else {
+            if (hipMemsetAsync(conv, 0, (size_t)n_blocks * 8, st) != hipSuccess) return SALS_ERR_HIP;
+            inside_step();
+            for (int step = 0; step < n_steps; ++step) block_step(step);
+            if (launch_status() != SALS_OK) return SALS_ERR_HIP;
+            if (hipMemcpyAsync(h_conv, conv, (size_t)n_blocks * 8, hipMemcpyDeviceToHost, st) != hipSuccess) return SALS_ERR_HIP;
+            if (!row_norms(rows)) return SALS_ERR_HIP;
+            for (int i = 0; i < n_blocks; ++i) worst = std::max(worst, h_conv[i]);
+            rotated = rotated || worst > 0.0;  // (in the first sweep every rotation is recorded)
+            ++done;
+            last = 1e300;
+            // a rotation by less than 1e-11 no longer moves an eigenvector; only pairs with a row among the r largest are asked to
+            // have converged
+            converged = worst <= 1e-11;
+            lead = leading();
         }
-        if (launch_status() != SALS_OK) return SALS_ERR_HIP;
-        if (hipMemcpyAsync(h_conv, conv, (size_t)n_blocks * 8, hipMemcpyDeviceToHost, st) != hipSuccess) return SALS_ERR_HIP;
-        if (!row_norms(G)) return SALS_ERR_HIP;
-        double worst = 0.0;
-        for (int i = 0; i < n_blocks; ++i) worst = std::max(worst, h_conv[i]);
-        rotated = rotated || worst > 0.0;  // (in the first sweep every rotation is recorded)
-        ++done;
-        // a rotation by less than 1e-11 no longer moves an eigenvector; only pairs with a row among the r largest
-        // (a little below the r-th largest norm, so that the r-th itself is in) are asked to have converged
-        auto leading = [&]() {
-            std::nth_element(h_norm, h_norm + (r - 1), h_norm + D, std::greater<double>());
-            const double nr = h_norm[r - 1];
-            return 0.999 * nr * nr;
-        };
-        converged = worst <= 1e-11;
-        lead = leading();
         // Behind a sweep of small rotations the angles that are left decide: converged, or all of them at once, or a further sweep.
         // (Sweeps whose largest rotation was 0.26, 0.07, 0.007 left 4e-5, 1e-3, 4e-6.)  The angles lie in C, which is free until its
         // rows are written.
         for (int pass = 0; !converged && worst <= 0.3 && pass < 4; ++pass) {
-            hipLaunchKernelGGL(calib_jacobi_angles_kernel, dim3(n_tiles), dim3(512), 0, st, G, D, norm, lead, C, found);
+            hipLaunchKernelGGL((calib_angles_kernel<false>), tile_grid, prod, (prod_lds<double, double, false>()), st, rows, D, norm, r, lead, C,
+                               found);
             if (launch_status() != SALS_OK ||
                 hipMemcpyAsync(h_found, found, (size_t)n_tiles * sizeof(f64x2), hipMemcpyDeviceToHost, st) != hipSuccess ||
                 hipStreamSynchronize(st) != hipSuccess)
                 return SALS_ERR_HIP;
-            double most = 0.0, square = 0.0;
-            for (int i = 0; i < n_tiles; ++i) { most = std::max(most, h_found[2 * i]); square += h_found[2 * i + 1]; }
+            double most = 0.0, square_sum = 0.0;
+            for (int i = 0; i < n_tiles; ++i) { most = std::max(most, h_found[2 * i]); square_sum += h_found[2 * i + 1]; }
             converged = most <= 1e-11;
-            if (converged || !series || !(square <= 1.6e-5)) break;
+            if (converged || !series || !(square_sum <= kSeriesNorm * kSeriesNorm)) break;
             // exp(E) G from the inside out: G + E (G + E/2 (G + E/3 (G + E/4 G)))
-            double *X = G, *Y = at(off.Y0);
-            for (int k = square <= 4e-8 ? 2 : 4; k >= 1; --k) {
-                if (k == 1) Y = G;
-                hipLaunchKernelGGL(calib_jacobi_apply_kernel, dim3(D / 64, D / 64), dim3(512), 0, st, C, X, G, 1.0 / k, Y, D);
+            double *X = rows, *Y = other;
+            for (int k = square_sum <= 4e-8 ? 2 : 4; k >= 1; --k) {
+                if (k == 1) Y = rows;
+                hipLaunchKernelGGL((calib_apply_kernel<double, true>), tile_grid, prod, (prod_lds<double, double, true>()), st, C, X, rows,
+                                   1.0 / k, Y, D);
                 X = Y;
-                Y = X == at(off.Y0) ? at(off.Y1) : at(off.Y0);
+                Y = X == other ? third : other;
             }
-            if (!row_norms(G)) return SALS_ERR_HIP;
+            if (!row_norms(rows)) return SALS_ERR_HIP;
             lead = leading();
         }
     }
@@ -2080,8 +2199,8 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
 #define SALS_SELECT(T, ROOT, M)                                                                                              \
     hipLaunchKernelGGL((calib_select_kernel<T, ROOT>), dim3(D), dim3(kCalThreads), 0, st, M, norm, sgn, D, r, shift, eigval, \
                        static_cast<T*>(U), C)
-    if (dtype == SALS_BF16) { if (rotated) SALS_SELECT(bf16_t, true, G); else SALS_SELECT(bf16_t, false, C); }
-    else { if (rotated) SALS_SELECT(float, true, G); else SALS_SELECT(float, false, C); }
+    if (dtype == SALS_BF16) { if (rotated) SALS_SELECT(bf16_t, true, rows); else SALS_SELECT(bf16_t, false, C); }
+    else { if (rotated) SALS_SELECT(float, true, rows); else SALS_SELECT(float, false, C); }
 #undef SALS_SELECT
     if (sweeps) *sweeps = converged ? done : -done;
     return launch_status();

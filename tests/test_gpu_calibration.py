@@ -161,6 +161,42 @@ def test_rows_left_behind_are_orthogonal_in_fp64(D, r, decay):
     np.testing.assert_allclose(norm[lead], lam.cpu().numpy()[:r], rtol=1e-13)
 
 
+@pytest.mark.parametrize("D,r,kind", [(256, 256, "flat"), (512, 512, "repeated"), (512, 300, "shuffled"), (768, 100, "steep"),
+                                      (1280, 700, "slow"), (1536, 1536, "flat")])
+def test_transformations_of_all_rows_at_once(D, r, kind):
+    """Spectra on which the call transforms all rows at once, from the first sweep on and (D above 1024) later, and such on which the
+    transformations gain little and sweeps take turns with them: eigenvalues that repeat, rows of very different norms in no order."""
+    print(f"[case] transformations of all rows, D={D} r={r} {kind}", flush=True)
+    rng = np.random.default_rng(7 * D + r)
+    if kind == "repeated":
+        Q, _ = np.linalg.qr(rng.standard_normal((D, D)))
+        C = (Q * np.repeat(1.0 / np.arange(1, D // 16 + 1), 16)) @ Q.T
+    else:
+        X = rng.standard_normal((4 * D, D))
+        if kind == "shuffled":
+            X = (X @ (np.eye(D) + 0.3 / np.sqrt(D) * rng.standard_normal((D, D))) * 10.0 ** -np.linspace(0.0, 5.0, D))[:, rng.permutation(D)]
+        else:
+            X = X * np.arange(1, D + 1) ** -{"flat": 0.25, "slow": 0.5, "steep": 1.5}[kind] @ rng.standard_normal((D, D)) / np.sqrt(D)
+        C = X.T @ X
+    C = 0.5 * (C + C.T)
+    lam_ref = np.linalg.eigvalsh(C)[::-1]
+    Cg = gu.to_dev(C)
+    lam, U, sweeps = binding.calib_eigenvectors(Cg, r, torch.float32)
+    torch.cuda.synchronize()
+    assert 0 < sweeps <= 40, sweeps
+    rows = Cg.cpu().numpy()
+    norm = np.linalg.norm(rows, axis=1)
+    lead = np.argsort(-norm)[:r]
+    V = rows[lead] / norm[lead, None]
+    assert np.max(np.abs(V @ V.T - np.eye(r))) <= 2e-11     # (the angles the call may leave, and rounding)
+    # at most 20 transformations of three fp64 products each, sums of D terms: sqrt(D) 2^-53 of a row each time.  What fp32 leaves
+    # of the transformation's orthogonality is 1e-6, its square 1e-12: either of them left in would show.  The eigensolver is off by as
+    # much, and a factor of four covers that and the sweeps.
+    eps = 4 * 60 * np.sqrt(D) * 2.0 ** -53
+    np.testing.assert_allclose(lam.cpu().numpy()[:r], lam_ref[:r], rtol=0, atol=eps * lam_ref[0])
+    assert np.max(np.linalg.norm(V @ C - norm[lead, None] * V, axis=1)) <= (2e-11 + eps) * norm[lead[0]]
+
+
 def _eig_with_workspace(C, r, nbytes):
     """The call on a workspace of `nbytes`, which lies before bytes that must stay as they are."""
     D = C.shape[0]
@@ -179,8 +215,8 @@ def _eig_with_workspace(C, r, nbytes):
 @pytest.mark.parametrize("D,r", [(256, 256), (768, 500), (1024, 256), (1280, 1280)])
 def test_eigenvectors_with_a_small_workspace(D, r):
     """From 8 D^2 + 900 D bytes on the call sweeps to the end, with fewer slices where all of them do not fit: the same
-    decomposition.  With the full size the last rotations are made at once, which takes fewer sweeps on this spectrum and leaves
-    the eigenvalues where sweeps would: what makes the rotations is orthogonal to rounding."""
+    decomposition.  With the full size rows are transformed all at once, which takes fewer sweeps on this spectrum and leaves
+    the eigenvalues where sweeps would: what transforms the rows is orthogonal to rounding."""
     print(f"[case] eigenvectors, small workspace, D={D} r={r}", flush=True)
     rng = np.random.default_rng(3 * D)
     X = rng.standard_normal((4 * D, D)) * np.arange(1, D + 1) ** -0.5
