@@ -11,11 +11,11 @@
 //                  where it is small.  Rows are sorted by norm, so that the pairs with large angles lie near the diagonal; those
 //                  inside and next to a 32-row block are rotated one by one first (three Jacobi steps).
 //
-// The polar factor is found by Newton-Schulz steps in fp32 (X <- a X - b X X^T X, scaled by the bounds of its singular values:
-// J. Chen, E. Chow, "A stable scaling of Newton-Schulz for improving the sign function computation of a Hermitian matrix",
-// 2014), and only *found* there: what is left, delta = X X^T - I (1e-6), is formed in fp64 and taken out to third order,
-// G <- (I - delta / 2 + 3/8 delta^2) X G, with fp64 products.  What a transformation does to G is orthogonal to 1e-16 like a
-// rotation made in fp64, and which transformation is made decides nothing but how fast the rows converge.  (D = 1024, r = 640:
+// The polar factor is found by Newton-Schulz steps in pairs of bf16, the last one in fp32 (X <- a X - b X X^T X, scaled by the
+// bounds of its singular values: J. Chen, E. Chow, "A stable scaling of Newton-Schulz for improving the sign function computation of
+// a Hermitian matrix", 2014), and only *found* there: what is left, delta = X X^T - I (1e-6), is formed in fp64 and taken out to
+// third order, G <- (I - delta / 2 + 3/8 delta^2) X G, with fp64 products.  What a transformation does to G is orthogonal to 1e-16
+// like a rotation made in fp64, and which transformation is made decides nothing but how fast the rows converge.  (D = 1024, r = 640:
 // eigenvalues off by 1.5e-14 of themselves against a 64-bit eigensolver, by 2.0e-14 with sweeps alone.)
 #pragma once
 #include "common.hpp"
@@ -128,6 +128,94 @@ __device__ __forceinline__ void calib_product(const TA* A, const TB* B, int D, F
     }
 }
 
+// Matrices of floats as pairs of bf16, x = hi + lo to 2^-17: one 32-bit word an element, hi in the upper half.
+__device__ __forceinline__ uint32_t pack_pair(float x)
+{
+    const bf16_t hi = f32_to_bf16(x);
+    return (uint32_t)hi << 16 | f32_to_bf16(x - bf16_to_f32(hi));
+}
+__device__ __forceinline__ float pair_value(uint32_t w) { return bf16hi(w) + bf16lo(w); }
+
+// The same for A B^T of such matrices: hi hi + hi lo + lo hi on the bf16 matrix cores, summed in fp32.  A step is 64 elements of a
+// row, 32 for either half of the waves.  Bound by what a compute unit draws, 13 us a product at D = 1024, where fp32 instructions take 22.
+constexpr size_t kPairLds = (size_t)kProdStages * 32768;
+template <typename Finish>
+__device__ __forceinline__ void calib_product_pairs(const uint32_t* A, const uint32_t* B, int D, Finish finish)
+{
+    constexpr int STAGE = 32768, ST = kProdStages;   // [A: two 32-element pieces of 64 rows | B]
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kg = lane >> 4;
+    const int part = wave & 3, ks = wave >> 2;
+    const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
+    const uint32_t lds0 = lds_offset(lds);
+    auto swz128 = [](int row, int pc) { return row * 128 + ((pc ^ ((row >> 1) & 7)) << 4); };
+    const int prow = wave * 8 + (lane >> 3);
+    const uint32_t off = (uint32_t)prow * (uint32_t)D * 4 + (uint32_t)(((lane & 7) ^ ((prow >> 1) & 7)) << 4);
+    const unsigned char* a = reinterpret_cast<const unsigned char*>(A + (size_t)r0 * D);
+    const unsigned char* b = reinterpret_cast<const unsigned char*>(B + (size_t)c0 * D);
+    const int n = D / 64;   // (at least 4)
+    auto load = [&](int s) {
+        const size_t at = (size_t)min(s, n - 1) * 256;   // (past the end: a step that nothing reads any more)
+        const uint32_t st = lds0 + (uint32_t)(s % ST) * STAGE + wave * 1024;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            load_lds16(a + at + 128 * i, off, st + 8192 * i);
+            load_lds16(b + at + 128 * i, off, st + 16384 + 8192 * i);
+        }
+    };
+#pragma unroll
+    for (int s = 0; s < ST - 1; ++s) load(s);
+    f32x4 acc[2][2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) acc[u][v] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int rr = (part >> 1) * 32 + l16, cc = (part & 1) * 32 + l16;
+    struct Pair { u32x4 hi, lo; };
+    auto fragment = [&](const unsigned char* st, int row) {   // eight elements of a row, from 8 kg on
+        const u32x4 x = *reinterpret_cast<const u32x4*>(st + swz128(row, 2 * kg)), y = *reinterpret_cast<const u32x4*>(st + swz128(row, 2 * kg + 1));
+        auto upper = [](uint32_t w0, uint32_t w1) { return __builtin_amdgcn_perm(w1, w0, 0x07060302u); };
+        auto lower = [](uint32_t w0, uint32_t w1) { return __builtin_amdgcn_perm(w1, w0, 0x05040100u); };
+        return Pair{u32x4{upper(x.x, x.y), upper(x.z, x.w), upper(y.x, y.y), upper(y.z, y.w)},
+                    u32x4{lower(x.x, x.y), lower(x.z, x.w), lower(y.x, y.y), lower(y.z, y.w)}};
+    };
+    auto mma = [](const u32x4& x, const u32x4& y, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), c, 0, 0, 0);
+    };
+    for (int s = 0; s < n; ++s) {
+        vm_wait<(ST - 2) * 4>();   // step s has landed, everywhere; every wave is done with step s - 1
+        wg_barrier();
+        load(s + ST - 1);
+        const unsigned char* st = lds + (s % ST) * STAGE + ks * 8192;
+        Pair x[2], y[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) { x[u] = fragment(st, rr + 16 * u); y[u] = fragment(st + 16384, cc + 16 * u); }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                acc[u][v] = mma(x[u].lo, y[v].hi, acc[u][v]);
+                acc[u][v] = mma(x[u].hi, y[v].lo, acc[u][v]);
+                acc[u][v] = mma(x[u].hi, y[v].hi, acc[u][v]);
+            }
+    }
+    vm_wait<0>();
+    wg_barrier();
+    float* red = reinterpret_cast<float*>(lds) + part * 1024;
+    if (ks) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) red[i * 64 + lane] = acc[i >> 3][(i >> 2) & 1][i & 3];
+    }
+    __syncthreads();
+    if (ks == 0) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int u = i >> 3, v = (i >> 2) & 1, e = i & 3;
+            finish(r0 + (part >> 1) * 32 + u * 16 + 4 * kg + e, c0 + (part & 1) * 32 + v * 16 + l16, acc[u][v][e] + red[i * 64 + lane]);
+        }
+    }
+}
+
 // Y = G + f A B (ADD), or f A B.  Y may be G, not B.
 template <typename TA, bool ADD>
 __global__ __launch_bounds__(kProdThreads) void calib_apply_kernel(const TA* A, const double* B, const double* G, double f, double* Y, int D)
@@ -139,40 +227,26 @@ __global__ __launch_bounds__(kProdThreads) void calib_apply_kernel(const TA* A, 
 }
 
 // ---- Angles -----------------------------------------------------------------------------------------------------------
-// From G G^T, rows' norms in `norm`.
-// ALL: E as above (fp32) for the pairs that are not orthogonal to 1e-12 and of which one row has a squared norm of at least a
-// thousandth of the r-th largest one (smaller ones hardly move a leading row); found: per tile {sum of its squares over the pairs with
-// a leading row, largest of them}.  The rows are sorted.
-// Otherwise: E = -t (fp64), t = ab / d, over the pairs that are not orthogonal to working precision and of which one row has a squared
-// norm >= lead; where both have, their cosine counts as well as t (beside a far larger row, t is small long before the smaller
-// row's direction is right); found: per tile {largest |t| (at most 1/2), sum of t^2}.
-constexpr double kAllOpen = 1e-24, kAllTail = 1e-3;
-template <bool ALL>
+// Both forms start from G G^T; `norm`: the rows' norms.
+//
+// The last angles: E = -t (fp64), t = ab / d, over the pairs that are not orthogonal to working precision and of which one row has a
+// squared norm >= lead; where both have, their cosine counts as well as t (beside a far larger row, t is small long before the smaller
+// row's direction is right).  found: per tile {largest |t| (at most 1/2), sum of t^2}.
 __global__ __launch_bounds__(kProdThreads) void calib_angles_kernel(const double* __restrict__ G, int D, const double* __restrict__ norm,
-                                                                    int r, double lead, void* __restrict__ E_out, f64x2* __restrict__ found)
+                                                                    double lead, double* __restrict__ E, f64x2* __restrict__ found)
 {
     __shared__ f64x2 s_found[4];
-    if (ALL) { const double nr = norm[r - 1]; lead = 0.999 * nr * nr; }
     double most = 0.0, sum = 0.0;
     calib_product<double, double, false, double>(G, G, D, [&](int i, int j, double ab) {
-        const double ni = norm[i], nj = norm[j], aa = ni * ni, bb = nj * nj, d = bb - aa, hi = fmax(aa, bb);
-        const size_t at = (size_t)i * D + j;
-        if (ALL) {
-            const bool counts = i != j && hi >= kAllTail * lead && ab * ab > kAllOpen * (aa * bb);
-            const double s = counts ? ab * rsqrt_f64(fma(4.0 * ab, ab, d * d)) : 0.0;
-            const double e = d < 0.0 || (d == 0.0 && i > j) ? s : -s;
-            static_cast<float*>(E_out)[at] = (float)e;
-            if (i < j && hi >= lead) { most = fmax(most, fabs(e)); sum += e * e; }
-        } else {
-            const bool counts = i != j && hi >= lead && jac_open(aa, bb, ab);
-            const double th = counts ? ab / d : 0.0;
-            if (counts && i < j) {
-                most = fmax(most, fabs(ab) / fmax(fabs(d), 2.0 * fabs(ab)));
-                if (fmin(aa, bb) >= lead) most = fmax(most, fabs(ab) / (ni * nj));
-                sum += th * th;
-            }
-            static_cast<double*>(E_out)[at] = -th;
+        const double ni = norm[i], nj = norm[j], aa = ni * ni, bb = nj * nj, d = bb - aa;
+        const bool counts = i != j && fmax(aa, bb) >= lead && jac_open(aa, bb, ab);
+        const double th = counts ? ab / d : 0.0;
+        if (counts && i < j) {
+            most = fmax(most, fabs(ab) / fmax(fabs(d), 2.0 * fabs(ab)));
+            if (fmin(aa, bb) >= lead) most = fmax(most, fabs(ab) / (ni * nj));
+            sum += th * th;
         }
+        E[(size_t)i * D + j] = -th;
     });
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) { most = fmax(most, __shfl_xor(most, o, kWave)); sum += __shfl_xor(sum, o, kWave); }
@@ -184,20 +258,99 @@ __global__ __launch_bounds__(kProdThreads) void calib_angles_kernel(const double
                                                            (s_found[0].y + s_found[1].y) + (s_found[2].y + s_found[3].y)};
 }
 
+// Any angles, of rows sorted by norm, for the pairs that are not orthogonal to 1e-12 and of which one row has a squared norm of at
+// least a thousandth of the r-th largest one (smaller ones hardly move a leading row).  A pair of nearly equal norms is turned far by
+// a small ab, and in vain while the norms still move: row i's squared norm is off by about the sum of ab^2 / h over its pairs, h =
+// sqrt(d^2 + 4 ab^2).  So the entry is ab / sqrt(h^2 + (off_i + off_j)^2), which is as good once the rows are nearly orthogonal and
+// saves a transformation of ten (weights 0, 0.1, 0.3, 1 and 3 of its square: 5.93, 5.17, 5.15, 5.21 and 5.54 ms at D = 1024, r = 640;
+// 6.0, 5.0, 5.3, 6.8 and 7.4 with eigenvalues within 1e-3 of each other).  First the products (fp32) and the tiles' shares of
+// `off`, [column tile][row] ...
+constexpr double kAllDamp = 0.1, kAllOpen = 1e-24, kAllTail = 1e-3;
+struct AllPair { bool counts; double d, h2; };
+__device__ __forceinline__ AllPair all_pair(double ni, double nj, double ab, double least)
+{
+    const double aa = ni * ni, bb = nj * nj, d = bb - aa;
+    return AllPair{fmax(aa, bb) >= least && ab * ab > kAllOpen * (aa * bb), d, fma(4.0 * ab, ab, d * d)};
+}
+__global__ __launch_bounds__(kProdThreads) void calib_gram_kernel(const double* __restrict__ G, int D, const double* __restrict__ norm, int r,
+                                                                  float* __restrict__ W, float* __restrict__ off)
+{
+    __shared__ float s_off[2][64];
+    const double lead = 0.999 * norm[r - 1] * norm[r - 1], least = kAllTail * lead;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    float sum[8];   // of this lane's columns, rows 16 u + kg + 4 e of its wave's half
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sum[i] = 0.f;
+    int n = 0;
+    calib_product<double, double, false, double>(G, G, D, [&](int i, int j, double ab) {
+        W[(size_t)i * D + j] = (float)ab;
+        const AllPair p = all_pair(norm[i], norm[j], ab, least);
+        const int k = n++;   // (a constant, once unrolled)
+        if (i != j && p.counts) sum[(k >> 3) * 4 + (k & 3)] += (float)(ab * ab * rsqrt_f64(p.h2));
+    });
+    if (wave < 4) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float t = row16_sum(sum[i]);
+            if ((lane & 15) == 0) s_off[wave & 1][(wave >> 1) * 32 + (i >> 2) * 16 + (lane >> 4) + 4 * (i & 3)] = t;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) off[(size_t)blockIdx.x * D + blockIdx.y * 64 + threadIdx.x] = s_off[0][threadIdx.x] + s_off[1][threadIdx.x];
+}
+// ... then E (pairs of bf16), kAngleRows rows a workgroup, and per workgroup the sum of squares of ab / h over the pairs with a leading row.
+constexpr int kAngleRows = 4;
+__global__ __launch_bounds__(256) void calib_all_angles_kernel(const float* __restrict__ W, int D, const double* __restrict__ norm, int r,
+                                                               const float* __restrict__ off, uint32_t* __restrict__ E, double* __restrict__ found)
+{
+    __shared__ double s_sum[4];
+    const double lead = 0.999 * norm[r - 1] * norm[r - 1], least = kAllTail * lead;
+    const int i0 = blockIdx.x * kAngleRows, n = D / 64;
+    double sum = 0.0;
+    float off_i[kAngleRows];
+#pragma unroll
+    for (int u = 0; u < kAngleRows; ++u) off_i[u] = 0.f;
+    for (int t = 0; t < n; ++t)
+#pragma unroll
+        for (int u = 0; u < kAngleRows; ++u) off_i[u] += off[(size_t)t * D + i0 + u];
+    for (int j = threadIdx.x; j < D; j += 256) {
+        float off_j = 0.f;
+        for (int t = 0; t < n; ++t) off_j += off[(size_t)t * D + j];
+        const double nj = norm[j];
+#pragma unroll
+        for (int u = 0; u < kAngleRows; ++u) {
+            const int i = i0 + u;
+            const double ab = W[(size_t)i * D + j], ni = norm[i], o = (double)off_i[u] + off_j;
+            const AllPair p = all_pair(ni, nj, ab, least);
+            const bool counts = p.counts && i != j;
+            const double s = counts ? ab * rsqrt_f64(fma(kAllDamp * o, o, p.h2)) : 0.0;
+            E[(size_t)i * D + j] = pack_pair((float)(p.d < 0.0 || (p.d == 0.0 && i > j) ? s : -s));
+            if (counts && i < j && fmax(ni, nj) * fmax(ni, nj) >= lead) sum += ab * ab / p.h2;
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, kWave);
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) found[blockIdx.x] = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
+}
+
 // ---- Polar factor -----------------------------------------------------------------------------------------------------
-// O = d I + s S + t T + f A B^T in fp32 (S, T: N > 0, N > 1).  SQUARE: also the sum of squares of every tile of O.
-template <int N, bool SQUARE>
-__global__ __launch_bounds__(kProdThreads) void calib_polar_kernel(const float* A, const float* B, int D, float f, float d, float s,
-                                                                   const float* S, float t, const float* T, float* O, double* square)
+// O = d I + s S + t T + f A B^T (S, T: N > 0, N > 1) from pairs of bf16, left as such pairs or (LAST) in fp32.  SQUARE: also the sum
+// of squares of every tile of O.
+template <int N, bool SQUARE, bool LAST>
+__global__ __launch_bounds__(kProdThreads) void calib_polar_kernel(const uint32_t* A, const uint32_t* B, int D, float f, float d, float s,
+                                                                   const uint32_t* S, float t, const uint32_t* T, void* O, double* square)
 {
     __shared__ double s_sum[4];
     double sum = 0.0;
-    calib_product<float, float, false, float>(A, B, D, [&](int i, int j, float v) {
+    calib_product_pairs(A, B, D, [&](int i, int j, float v) {
         const size_t at = (size_t)i * D + j;
         float o = f * v;
-        if (N > 0) o = fmaf(s, S[at], o);
-        if (N > 1) { o = fmaf(t, T[at], o); o += i == j ? d : 0.f; }
-        O[at] = o;
+        if (N > 0) o = fmaf(s, pair_value(S[at]), o);
+        if (N > 1) { o = fmaf(t, pair_value(T[at]), o); o += i == j ? d : 0.f; }
+        if (LAST) static_cast<float*>(O)[at] = o;
+        else static_cast<uint32_t*>(O)[at] = pack_pair(o);
         if (SQUARE) sum += (double)o * (double)o;
     });
     if (!SQUARE) return;
@@ -208,19 +361,29 @@ __global__ __launch_bounds__(kProdThreads) void calib_polar_kernel(const float* 
     __syncthreads();
     if (threadIdx.x == 0) square[blockIdx.y * gridDim.x + blockIdx.x] = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
 }
-// delta = X X^T - I, summed in fp64, and its rounding to fp32
-__global__ __launch_bounds__(kProdThreads) void calib_defect_kernel(const float* X, int D, double* delta, float* delta32)
+// The last step: O = f A B^T + s S (ADD) in fp32
+template <bool ADD>
+__global__ __launch_bounds__(kProdThreads) void calib_polar_last_kernel(const float* A, const float* B, int D, float f, float s, const float* S,
+                                                                        float* O)
+{
+    calib_product<float, float, false, float>(A, B, D, [&](int i, int j, float v) {
+        const size_t at = (size_t)i * D + j;
+        O[at] = ADD ? fmaf(s, S[at], f * v) : f * v;
+    });
+}
+// delta = X X^T - I, summed in fp64, and its rounding to pairs of bf16
+__global__ __launch_bounds__(kProdThreads) void calib_defect_kernel(const float* X, int D, double* delta, uint32_t* rounded)
 {
     calib_product<float, float, false, double>(X, X, D, [&](int i, int j, double v) {
         const double o = i == j ? v - 1.0 : v;
         delta[(size_t)i * D + j] = o;
-        delta32[(size_t)i * D + j] = (float)o;
+        rounded[(size_t)i * D + j] = pack_pair((float)o);
     });
 }
-// delta <- -delta / 2 + 3/8 delta^2 (the square, 1e-12, from the fp32 rounding)
-__global__ __launch_bounds__(kProdThreads) void calib_correction_kernel(const float* delta32, int D, double* delta)
+// delta <- -delta / 2 + 3/8 delta^2 (the square, 1e-12, from the rounded one)
+__global__ __launch_bounds__(kProdThreads) void calib_correction_kernel(const uint32_t* rounded, int D, double* delta)
 {
-    calib_product<float, float, false, float>(delta32, delta32, D, [&](int i, int j, float v) {
+    calib_product_pairs(rounded, rounded, D, [&](int i, int j, float v) {
         const size_t at = (size_t)i * D + j;
         delta[at] = fma(0.375, (double)v, -0.5 * delta[at]);
     });

@@ -1961,14 +1961,14 @@ bool eig_plan(int D, size_t bytes, EigWs* w, int* n_part, bool* series)
 }  // namespace
 
 namespace {
-// Transformations of all rows at once (k_calib_all.hpp) in place of sweeps, up to kAllMaxD.  One takes 0.55 ms at D = 1024, where a
-// sweep takes 0.79, and from the Cholesky factor on it brings the rows as far as a sweep does, or further once the angles are below
-// one; its products grow with D^3 and a sweep's steps with D^2, so above 1024 it comes later.  A call, r = 5/8 D, in ms with the
-// transformations behind one, two and three sweeps (and with sweeps alone): D = 256 1.9 / 1.9 / 2.0 (2.2), 512 3.3 / 3.3 / 3.4 (4.4),
-// 1024 6.3 / 6.3 / 6.7 (9.6), 1536 19.2 / 17.8 / 16.6 (18.8), 2048 37.8 / 31.4 / 28.7 (29.2).
-constexpr int kAllMaxD = 1536;
-inline int all_first(int D) { return D <= 1024 ? 1 : 3; }
-// |E| at most: larger angles gain nothing (8 and 12: 6.4 and 6.5 ms at D = 1024), and a smaller limit costs a transformation more (3: 7.0)
+// Transformations of all rows at once (k_calib_all.hpp) in place of sweeps, up to kAllMaxD.  One takes 0.42 ms at D = 1024, where a
+// sweep takes 0.8, and from the Cholesky factor on it brings the rows as far as a sweep does, or further once the angles are below
+// one; its products grow with D^3 and a sweep's steps with D^2, so for large D it comes later.  A call, r = 5/8 D, in ms with the
+// transformations behind one, two and three sweeps (and with sweeps alone): D = 256 1.8 / 1.8 / 1.8 (2.2), 512 2.8 / 2.9 / 3.1 (4.4),
+// 1024 5.1 / 5.5 / 5.9 (9.6), 2048 23.7 / 23.7 / 24.3 (29.2), 3072 76 / 72 / 70 (79), 4096 177 / 165 / 149 (141).
+constexpr int kAllMaxD = 3072;
+inline int all_first(int D) { return D <= 2048 ? 1 : 3; }
+// |E| at most: larger angles gain nothing (4, 6 and 10: 5.13, 5.11 and 5.11 ms at D = 1024; 5.43, 5.25, 5.28 with a spectrum c^-2)
 constexpr double kAllCap = 6.0;
 // the series of the exponential: cut behind E^4 it differs from an orthogonal matrix by |E|^6 / 72
 constexpr double kSeriesNorm = 4e-3;
@@ -1979,14 +1979,18 @@ sals_status calib_all_lds()
         return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
     };
     constexpr size_t nt = prod_lds<float, float, false>();
-    const bool ok = allow(reinterpret_cast<const void*>(calib_angles_kernel<false>), prod_lds<double, double, false>()) &&
-                    allow(reinterpret_cast<const void*>(calib_angles_kernel<true>), prod_lds<double, double, false>()) &&
-                    allow(reinterpret_cast<const void*>(calib_polar_kernel<0, true>), nt) &&
-                    allow(reinterpret_cast<const void*>(calib_polar_kernel<0, false>), nt) &&
-                    allow(reinterpret_cast<const void*>(calib_polar_kernel<1, false>), nt) &&
-                    allow(reinterpret_cast<const void*>(calib_polar_kernel<2, false>), nt) &&
+    const bool ok = allow(reinterpret_cast<const void*>(calib_angles_kernel), prod_lds<double, double, false>()) &&
+                    allow(reinterpret_cast<const void*>(calib_gram_kernel), prod_lds<double, double, false>()) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_kernel<0, true, false>), kPairLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_kernel<0, false, false>), kPairLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_kernel<1, false, false>), kPairLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_kernel<1, false, true>), kPairLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_kernel<2, false, false>), kPairLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_kernel<2, false, true>), kPairLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_last_kernel<false>), nt) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_last_kernel<true>), nt) &&
                     allow(reinterpret_cast<const void*>(calib_defect_kernel), nt) &&
-                    allow(reinterpret_cast<const void*>(calib_correction_kernel), nt) &&
+                    allow(reinterpret_cast<const void*>(calib_correction_kernel), kPairLds) &&
                     allow(reinterpret_cast<const void*>(calib_apply_kernel<float, false>), prod_lds<float, double, true>()) &&
                     allow(reinterpret_cast<const void*>(calib_apply_kernel<double, true>), prod_lds<double, double, true>());
     return ok ? SALS_OK : SALS_ERR_HIP;
@@ -2020,11 +2024,13 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     const int slices = jac_slices(D);
     const int n_tiles = (D / 64) * (D / 64);   // of the angles, whose results lie where the partial Gram matrices do
     f64x2* const found = reinterpret_cast<f64x2*>(part);
-    double* const square = part + 2 * (size_t)n_tiles;
+    const int n_angles = D / kAngleRows;
+    double *const all_found = part, *const square = part + n_angles;
+    float* const row_off = reinterpret_cast<float*>(square + n_tiles);
     double *rows = G, *other = at(off.Y0), *third = at(off.Y1);   // the rows, and room for two more matrices (`series`)
     double* const sorted = diag;                                  // (the factored blocks are in place by then)
     const bool all = series && D <= kAllMaxD;
-    const std::unique_ptr<double[]> host(new (std::nothrow) double[(size_t)n_blocks + D + 3 * n_tiles]);
+    const std::unique_ptr<double[]> host(new (std::nothrow) double[(size_t)n_blocks + D + std::max(2 * n_tiles, n_angles + n_tiles)]);
     if (!host) return SALS_ERR_HIP;
     double *const h_conv = host.get(), *const h_norm = h_conv + n_blocks, *const h_found = h_norm + D;
     auto row_norms = [&](const double* M) -> bool {  // row norms to the host (blocking)
@@ -2053,7 +2059,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                 hipLaunchKernelGGL(calib_chol_panel_kernel, dim3(std::max(1, rest / 64)), dim3(256), 0, st, G, D, k0, shift,
                                    diag, fail);
                 if (rest > 0)
-                    hipLaunchKernelGGL(calib_chol_update_kernel, dim3(rest / 64, rest / 64), dim3(256), 0, st, G, D, k0);
+                    hipLaunchKernelGGL(calib_chol_update_kernel, dim3(rest / 64, rest / 64), dim3(512), 0, st, G, D, k0);
             }
             hipLaunchKernelGGL(calib_chol_finish_kernel, dim3(D), dim3(256), 0, st, G, D, diag);
             if (launch_status() != SALS_OK || hipMemcpyAsync(&failed, fail, sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess ||
@@ -2091,18 +2097,21 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             hipLaunchKernelGGL(calib_rownorm_kernel, dim3(D), dim3(kCalThreads), 0, st, rows, D, norm, sgn);
             hipLaunchKernelGGL(calib_sort_kernel, dim3(D), dim3(kCalThreads), 0, st, rows, norm, D, other, sorted);
             std::swap(rows, other);
-            float *const E = reinterpret_cast<float*>(third), *const A = E + (size_t)D * D;
-            hipLaunchKernelGGL((calib_angles_kernel<true>), tile_grid, prod, (prod_lds<double, double, false>()), st, rows, D, sorted, r, 0.0, E,
-                               found);
-            hipLaunchKernelGGL((calib_polar_kernel<0, true>), tile_grid, prod, (prod_lds<float, float, false>()), st, E, E, D, 1.f, 0.f, 0.f,
-                               nullptr, 0.f, nullptr, A, square);
+            uint32_t *const E = reinterpret_cast<uint32_t*>(third), *const A = E + (size_t)D * D;
+            hipLaunchKernelGGL(calib_gram_kernel, tile_grid, prod, (prod_lds<double, double, false>()), st, rows, D, sorted, r,
+                               reinterpret_cast<float*>(A), row_off);
+            hipLaunchKernelGGL(calib_all_angles_kernel, dim3(n_angles), dim3(256), 0, st, reinterpret_cast<const float*>(A), D, sorted, r, row_off,
+                               E, all_found);
+            hipLaunchKernelGGL((calib_polar_kernel<0, true, false>), tile_grid, prod, kPairLds, st, E, E, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr,
+                               A, square);
             if (launch_status() != SALS_OK ||
-                hipMemcpyAsync(h_found, found, (size_t)n_tiles * (sizeof(f64x2) + sizeof(double)), hipMemcpyDeviceToHost, st) != hipSuccess ||
+                hipMemcpyAsync(h_found, all_found, (size_t)(n_angles + n_tiles) * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
                 hipStreamSynchronize(st) != hipSuccess)
                 return SALS_ERR_HIP;
             ++done;
             double e2 = 0.0, a2 = 0.0;
-            for (int i = 0; i < n_tiles; ++i) { e2 += h_found[2 * i + 1]; a2 += h_found[2 * n_tiles + i]; }
+            for (int i = 0; i < n_angles; ++i) e2 += h_found[i];
+            for (int i = 0; i < n_tiles; ++i) a2 += h_found[n_angles + i];
             // (a matrix on which the transformations gain little, as with eigenvalues that repeat or rows of very different norms
             // in no order, gets a sweep in between)
             const double now = std::sqrt(e2);
@@ -2125,24 +2134,40 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                     low = 0.5 * x * (3.0 - x * x);
                     return a;
                 };
-                bool more = low < 0.9985;
+                // (behind a step that leaves them above 0.9985, or one of angles so small to begin with, one more is the last one)
+                const bool one = low >= 0.9985;
                 const double a1 = scale_of(), w = 0.5 * a1 * a1 * a1 / (top * top * top), c1 = 1.5 * a1 / top - w;
-                float *X = reinterpret_cast<float*>(other), *X2 = X + (size_t)D * D, *const Y = E;
-                hipLaunchKernelGGL((calib_polar_kernel<2, false>), tile_grid, prod, (prod_lds<float, float, false>()), st, A, E, D,
-                                   (float)(w * tau * tau * tau), (float)c1, (float)(c1 * tau), E, (float)(-w * tau * tau), A, X, nullptr);
-                while (more) {
-                    more = low < 0.9985;
+                uint32_t *X = reinterpret_cast<uint32_t*>(other), *X2 = X + (size_t)D * D, *const Y = E;
+                auto polar = [&](auto n, bool last, const uint32_t* L, const uint32_t* R, double f, double d, double s, const uint32_t* S, double t,
+                                 const uint32_t* T, uint32_t* O) {
+                    constexpr int N = decltype(n)::value;
+                    if (last) hipLaunchKernelGGL((calib_polar_kernel<N, false, true>), tile_grid, prod, kPairLds, st, L, R, D, (float)f, (float)d,
+                                                 (float)s, S, (float)t, T, O, nullptr);
+                    else hipLaunchKernelGGL((calib_polar_kernel<N, false, false>), tile_grid, prod, kPairLds, st, L, R, D, (float)f, (float)d,
+                                            (float)s, S, (float)t, T, O, nullptr);
+                };
+                bool last = one || low >= 0.9985;
+                polar(std::integral_constant<int, 2>{}, last, A, E, w * tau * tau * tau, c1, c1 * tau, E, -w * tau * tau, A, X);
+                while (!last) {
                     const double a = scale_of();
-                    hipLaunchKernelGGL((calib_polar_kernel<0, false>), tile_grid, prod, (prod_lds<float, float, false>()), st, X, X, D, 1.f,
-                                       0.f, 0.f, nullptr, 0.f, nullptr, Y, nullptr);
-                    hipLaunchKernelGGL((calib_polar_kernel<1, false>), tile_grid, prod, (prod_lds<float, float, false>()), st, X, Y, D,
-                                       (float)(-0.5 * a * a * a), 0.f, (float)(1.5 * a), X, 0.f, nullptr, X2, nullptr);
+                    last = low >= 0.9985;
+                    polar(std::integral_constant<int, 0>{}, false, X, X, 1.0, 0.0, 0.0, nullptr, 0.0, nullptr, Y);
+                    polar(std::integral_constant<int, 1>{}, last, X, Y, -0.5 * a * a * a, 0.0, 1.5 * a, X, 0.0, nullptr, X2);
                     std::swap(X, X2);
                 }
-                hipLaunchKernelGGL(calib_defect_kernel, tile_grid, prod, (prod_lds<float, float, false>()), st, X, D, C, X2);
-                hipLaunchKernelGGL(calib_correction_kernel, tile_grid, prod, (prod_lds<float, float, false>()), st, X2, D, C);
-                hipLaunchKernelGGL((calib_apply_kernel<float, false>), tile_grid, prod, (prod_lds<float, double, true>()), st, X, rows, nullptr,
-                                   1.0, third, D);
+                if (!one) {
+                    float *const x = reinterpret_cast<float*>(X), *const x2 = reinterpret_cast<float*>(X2), *const y = reinterpret_cast<float*>(Y);
+                    hipLaunchKernelGGL((calib_polar_last_kernel<false>), tile_grid, prod, (prod_lds<float, float, false>()), st, x, x, D, 1.f, 0.f,
+                                       nullptr, y);
+                    hipLaunchKernelGGL((calib_polar_last_kernel<true>), tile_grid, prod, (prod_lds<float, float, false>()), st, x, y, D, -0.5f, 1.5f,
+                                       x, x2);
+                    std::swap(X, X2);
+                }
+                hipLaunchKernelGGL(calib_defect_kernel, tile_grid, prod, (prod_lds<float, float, false>()), st, reinterpret_cast<const float*>(X), D,
+                                   C, X2);
+                hipLaunchKernelGGL(calib_correction_kernel, tile_grid, prod, kPairLds, st, X2, D, C);
+                hipLaunchKernelGGL((calib_apply_kernel<float, false>), tile_grid, prod, (prod_lds<float, double, true>()), st,
+                                   reinterpret_cast<const float*>(X), rows, nullptr, 1.0, third, D);
                 hipLaunchKernelGGL((calib_apply_kernel<double, true>), tile_grid, prod, (prod_lds<double, double, true>()), st, C, third, third,
                                    1.0, other, D);
                 std::swap(rows, other);
@@ -2169,20 +2194,20 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         // Behind a sweep of small rotations the angles that are left decide: converged, or all of them at once, or a further sweep.
         // (Sweeps whose largest rotation was 0.26, 0.07, 0.007 left 4e-5, 1e-3, 4e-6.)  The angles lie in C, which is free until its
         // rows are written.
-        for (int pass = 0; !converged && worst <= 0.3 && pass < 4; ++pass) {
-            hipLaunchKernelGGL((calib_angles_kernel<false>), tile_grid, prod, (prod_lds<double, double, false>()), st, rows, D, norm, r, lead, C,
-                               found);
+        for (int pass = 0; !converged && worst <= 0.3 && pass < 6; ++pass) {
+            hipLaunchKernelGGL(calib_angles_kernel, tile_grid, prod, (prod_lds<double, double, false>()), st, rows, D, norm, lead, C, found);
             if (launch_status() != SALS_OK ||
                 hipMemcpyAsync(h_found, found, (size_t)n_tiles * sizeof(f64x2), hipMemcpyDeviceToHost, st) != hipSuccess ||
                 hipStreamSynchronize(st) != hipSuccess)
                 return SALS_ERR_HIP;
             double most = 0.0, square_sum = 0.0;
             for (int i = 0; i < n_tiles; ++i) { most = std::max(most, h_found[2 * i]); square_sum += h_found[2 * i + 1]; }
+           
             converged = most <= 1e-11;
             if (converged || !series || !(square_sum <= kSeriesNorm * kSeriesNorm)) break;
             // exp(E) G from the inside out: G + E (G + E/2 (G + E/3 (G + E/4 G)))
             double *X = rows, *Y = other;
-            for (int k = square_sum <= 4e-8 ? 2 : 4; k >= 1; --k) {
+            for (int k = square_sum <= 1e-18 ? 1 : square_sum <= 4e-8 ? 2 : 4; k >= 1; --k) {
                 if (k == 1) Y = rows;
                 hipLaunchKernelGGL((calib_apply_kernel<double, true>), tile_grid, prod, (prod_lds<double, double, true>()), st, C, X, rows,
                                    1.0 / k, Y, D);
