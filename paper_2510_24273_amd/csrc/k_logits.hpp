@@ -66,7 +66,7 @@ template <int HEADS, int NTG, int NB> struct logits_cfg {
 // MULTI: a tile is made of the (at most 64 token) selections of consecutive SEQUENCES, 64 slots each, instead of as many
 // tokens of one sequence: short selections such as a recent window then share one pass over the head's projector among
 // the sequences of a tile.  Each sequence has its own query, count, index list and cache;
-// the latent axis may be cut into `ksplit` slices (the logit is additive over latent coordinates), whose partial
+// the latent axis may be cut into `ksplit` slices of whole steps (the logit is additive over latent coordinates), whose partial
 // logits go to `plogits` for logits_finish_kernel.
 // BYLEN (MULTI only): the selections are recent windows given by the sequence lengths (`win`; idx and n_sel are not read).
 // SIDE: `split` names the logits of another pass whose slices are still to be added up, on the side (one job per wave).
@@ -83,7 +83,7 @@ __device__ __forceinline__ void logits_tile(
 {
     typedef logits_cfg<HEADS, NTG, NB> C;
     static_assert(!BYLEN || MULTI, "a window by length fills tiles of several sequences");
-    static_assert(!MULTI || (HEADS == 1 && NB <= 2), "a sequence's 64 slots are those of one or two waves");
+    static_assert(!MULTI || NB <= 2, "a sequence's 64 slots are those of one or two waves");
     constexpr int SQ = MULTI ? C::TOK / 64 : 1;   // sequences per tile
     constexpr int WT = NB * 32;                   // tokens per wave
     constexpr int NT = C::NT, NA = C::NA, NBP = C::NBP, NCS = C::NCS;
@@ -101,12 +101,12 @@ __device__ __forceinline__ void logits_tile(
     int b, g0, part, kz = 0;   // MULTI: b is the first sequence of the tile
     if constexpr (MULTI) {
         // list order (head, sequence group, latent slice): an XCD's range keeps a few heads' projector slices
-        const int nsg = (B + SQ - 1) / SQ, N = nsg * H_kv * ksplit;
+        const int nsg = (B + SQ - 1) / SQ, N = nsg * (H_kv / HEADS) * ksplit;
         const int id = block, xcd = id % kXcds, slot = id / kXcds;
         const int qn = N / kXcds, rem = N % kXcds;
         const int w = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + slot;
-        g0 = w / (nsg * ksplit);
-        const int rest = w - g0 * (nsg * ksplit);
+        const int hb = w / (nsg * ksplit), rest = w - hb * (nsg * ksplit);
+        g0 = hb * HEADS;
         b = (rest / ksplit) * SQ; kz = rest % ksplit; part = 0;
     } else {
         const int n_y = H_kv / HEADS, N = n_parts * n_y * B;
@@ -190,9 +190,9 @@ __device__ __forceinline__ void logits_tile(
     float qa[QP], qb[QP];
 #pragma unroll
     for (int u = 0; u < QP; ++u) {
-        // query pair t: (sequence of the tile, head of the tile's heads, pair)
+        // query pair t: (sequence of the tile, query head of the tile's heads, pair)
         const int t = min(tid + u * NT, SQ * HEADS * G * kPairs - 1), p = t & (kPairs - 1);
-        const int hq = t >> 6, sq = MULTI ? hq / G : 0, hm = MULTI ? hq - sq * G : hq;
+        const int hq = t >> 6, sq = MULTI ? hq / (HEADS * G) : 0, hm = MULTI ? hq - sq * (HEADS * G) : hq;
         const T* qrow = q + ((size_t)seq_of(sq * 64) * H + (size_t)g0 * G + hm) * kHeadDim;
         qa[u] = elem<T>::load(qrow + pair_first(p, style));
         qb[u] = elem<T>::load(qrow + pair_second(p, style));
@@ -207,8 +207,8 @@ __device__ __forceinline__ void logits_tile(
     const unsigned char* a_base = reinterpret_cast<const unsigned char*>(UkP + (size_t)g0 * kHeadDim * r);
     const size_t head_bytes = (size_t)kHeadDim * r * ES;
     // steps of the latent axis: all of them, or this workgroup's slice
-    const int nkc = MULTI ? r * ES / kLgStep / ksplit : r * ES / kLgStep;
-    const int kc_base = MULTI ? kz * nkc : 0;
+    const int kc_base = MULTI ? r * ES / kLgStep * kz / ksplit : 0;
+    const int nkc = MULTI ? r * ES / kLgStep * (kz + 1) / ksplit - kc_base : r * ES / kLgStep;
     auto slot_at = [&](int step) { return lds0 + (uint32_t)(step & 3) * C::SLOT; };
     auto load_a = [&](int i, int step) {
         const int piece = wave + i * NW;  // 8 pieces per head
@@ -261,7 +261,8 @@ __device__ __forceinline__ void logits_tile(
             }
         }
     }
-    __shared__ __attribute__((aligned(16))) float sQ[SQ * HEADS][kMaxGroup][kHeadDim];
+    constexpr int GQ = MULTI && GFIX > 0 ? GFIX : kMaxGroup;   // (eight heads' worth would not fit beside tiles of four sequences)
+    __shared__ __attribute__((aligned(16))) float sQ[SQ * HEADS][GQ][kHeadDim];
     __shared__ float2 sCS[SQ][kPairs];
     __shared__ float2 sStat[HEADS][NTG][kMaxGroup];
     __shared__ int sPos[C::TOK];  // cache row (= RoPE position) of every token of the tile
@@ -289,10 +290,10 @@ __device__ __forceinline__ void logits_tile(
         for (int u = 0; u < QP; ++u) {
             const int t = tid + u * NT;
             if (t < SQ * HEADS * G * kPairs) {
-                // (MULTI: t / 64 = sequence * G + head of the group; otherwise head of the tile * G + head of the group)
+                // (t / 64 = (sequence * heads of the tile + head) * G + head of the group)
                 const int p = t & (kPairs - 1), hm = t >> 6;
-                const float2 c = sCS[MULTI ? hm / G : 0][p];
-                float* dst = &sQ[0][0][0] + (size_t)((hm / G) * kMaxGroup + hm % G) * kHeadDim;
+                const float2 c = sCS[MULTI ? hm / (HEADS * G) : 0][p];
+                float* dst = &sQ[0][0][0] + (size_t)((hm / G) * GQ + hm % G) * kHeadDim;
                 rotate_query(qa[u], qb[u], c, scale, dst[p], dst[kPairs + p]);
             }
         }
@@ -430,8 +431,8 @@ __device__ __forceinline__ void logits_tile(
                         f32x4 q1[GB], q2[GB];
 #pragma unroll
                         for (int mi = 0; mi < GB; ++mi) {
-                            q1[mi] = *reinterpret_cast<const f32x4*>(&sQ[MULTI ? sw : hh][m0 + mi][p0]);
-                            q2[mi] = *reinterpret_cast<const f32x4*>(&sQ[MULTI ? sw : hh][m0 + mi][kPairs + p0]);
+                            q1[mi] = *reinterpret_cast<const f32x4*>(&sQ[MULTI ? sw * HEADS + hh : hh][m0 + mi][p0]);
+                            q2[mi] = *reinterpret_cast<const f32x4*>(&sQ[MULTI ? sw * HEADS + hh : hh][m0 + mi][kPairs + p0]);
                         }
 #pragma unroll
                         for (int mi = 0; mi < GB; ++mi)
@@ -496,11 +497,11 @@ __device__ __forceinline__ void logits_tile(
     __syncthreads();
     // the waves' statistics, merged in wave order: those of a head, or (MULTI) of a sequence, whose single tile this is
     constexpr int WS = MULTI ? 64 / WT : NTG;  // waves to merge
-    if (tid < (MULTI ? SQ : HEADS) * G) {
-        const int u = tid / G, m = tid - u * G, bt = MULTI ? b + u : b, h2 = MULTI ? 0 : u;
-        float2 st = sStat[h2][MULTI ? u * WS : 0][m];
+    if (tid < SQ * HEADS * G) {
+        const int u = tid / G, m = tid - u * G, sq = MULTI ? u / HEADS : 0, bt = b + sq, h2 = u - sq * HEADS;
+        float2 st = sStat[h2][sq * WS][m];
 #pragma unroll
-        for (int t = 1; t < WS; ++t) st = stat_merge(st, sStat[h2][(MULTI ? u * WS : 0) + t][m]);
+        for (int t = 1; t < WS; ++t) st = stat_merge(st, sStat[h2][sq * WS + t][m]);
         if (!MULTI || bt < B) stats[((size_t)bt * H + (size_t)(g0 + h2) * G + m) * stats_stride + part] = st;
     }
 }

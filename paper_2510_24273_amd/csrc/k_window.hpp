@@ -82,22 +82,22 @@ __global__ __launch_bounds__(kLsThreads) void window_select_small_kernel(
                                            WindowByLength{sel.seq_len, sel.top_k + sel.n_sink + sel.n_recent}, SplitLogits{});
 }
 
-// A batch: tiles of two sequences' windows.
-// Step of 16 sequences, 32 heads, 4096 tokens, w = 64, r_hi = 2048: the two launches took 6.7 + 23.0 us (the
-// window's in two slices, 4.7 more to add them up), this one 29 to 31 (one slice): the step 117.1 -> 114.5 us on one
-// card, 111.0 -> 107.7 on another.
-template <typename T, int GB, int GFIX>
-__global__ __launch_bounds__(256, 1) void window_select_kernel(
+// A batch: tiles of one head and two sequences' windows, or (WIDE) of two heads and four sequences'.
+// Bound by the operands a compute unit draws, which the wide tiles halve per product.  Step of 16 sequences, 32 heads, 4096 tokens, w =
+// 64, r_hi = 2048: the two launches took 6.7 + 23.0 us (the window's in two slices, 4.7 more to add them up), this one 30 in tiles of a
+// head (one slice) and 23 in wide ones (three slices, which the low-rank logits kernel adds up on the side): 109.3 -> 104.2 us a step.
+template <typename T, int GB, int GFIX, bool WIDE>
+__global__ __launch_bounds__(WIDE ? 512 : 256, WIDE ? 2 : 1) void window_select_kernel(
     StepSelect sel, const T* __restrict__ Kw, const T* __restrict__ UkP, const T* __restrict__ q, const int32_t* __restrict__ q_pos,
     const float2* __restrict__ rope, InvFreq inv, float* __restrict__ logits, float2* __restrict__ stats, int B, int S_max, int r, int H,
     int H_kv, int w, int lk, int style, float scale, int stats_stride, float* __restrict__ plogits, int ksplit)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    if ((int)blockIdx.x < sel.n_blocks) { step_select<256>(sel, lds); return; }  // uniform
-    logits_tile<T, 1, 4, 1, GB, GFIX, true, true, false, false>((int)blockIdx.x - sel.n_blocks, Kw, UkP, nullptr, nullptr, q, q_pos, rope, inv, logits,
-                                                  stats, B, S_max, r, H, H_kv, w, lk, 1, 0, style, scale, w, stats_stride, plogits,
-                                                  ksplit, WindowByLength{sel.seq_len, sel.top_k + sel.n_sink + sel.n_recent},
-                                                  SplitLogits{}, TopkResolve{});
+    if ((int)blockIdx.x < sel.n_blocks) { step_select<WIDE ? 512 : 256>(sel, lds); return; }  // uniform
+    logits_tile<T, WIDE ? 2 : 1, 4, WIDE ? 2 : 1, GB, GFIX, true, true, false, false>(
+        (int)blockIdx.x - sel.n_blocks, Kw, UkP, nullptr, nullptr, q, q_pos, rope, inv, logits, stats, B, S_max, r, H, H_kv, w, lk, 1, 0, style,
+        scale, w, stats_stride, plogits, ksplit, WindowByLength{sel.seq_len, sel.top_k + sel.n_sink + sel.n_recent}, SplitLogits{},
+        TopkResolve{});
 }
 
 }  // namespace sals

@@ -652,20 +652,36 @@ template <typename T> struct WindowSelectSmall {
 #undef SALS_WS
     }
 };
-template <typename T> auto window_select_for(int group)
+template <typename T> auto window_select_for(int group, bool wide)
 {
-    if (group == 1) return window_select_kernel<T, 1, 1>;
-    if (group == 4) return window_select_kernel<T, 4, 4>;
-    if (group % 4 == 0) return window_select_kernel<T, 4, 0>;
-    return window_select_kernel<T, 1, 0>;
+    if constexpr (sizeof(T) == 2) {
+        if (wide) return window_select_kernel<T, 1, 1, true>;
+    }
+    if (group == 1) return window_select_kernel<T, 1, 1, false>;
+    if (group == 4) return window_select_kernel<T, 4, 4, false>;
+    if (group % 4 == 0) return window_select_kernel<T, 4, 0, false>;
+    return window_select_kernel<T, 1, 0, false>;
 }
 int select_blocks(const sals_desc& d) { return ceil_div(d.B, kXcds) * kXcds; }
 // Slices of the window's latent axis in the launch that it shares with the selection: the window's own plan, halved while its workgroups
 // fit the chip at once (one per compute unit in the 64-token form, two otherwise) and do not together with the selection's.  (A
-// workgroup too many is a round too many: 16 sequences, r_hi = 2048, two slices 32.0 us and a sum to add, one 30.6; one sequence, eight
-// slices would be 257 workgroups.)
+// workgroup too many is a round too many: one sequence, eight slices would be 257 workgroups.)
+// Slices of the window's latent axis where that launch has tiles of two heads and four sequences (0: it has not): as many as fit
+// beside the selection, one workgroup per compute unit, at least two (two rounds of those are shorter than one of the whole axis), of
+// two steps and more.  Such a tile reads half as much per product as one of a head and two sequences, which is what binds those: a step
+// with 2-bit values, 32 heads, r = 512, r_hi = 2048 in us with the latter's slices and with these: 8 sequences 73.2 and 70.6, 12 95.8
+// and 91.7, 16 109.3 and 104.2, 24 152.7 and 142.4, 32 189.4 and 179.5; 16 with r_hi = 1024 88.2 and 85.2.  (fp32 is bound by its
+// matrix instructions.  Four query heads per KV head: r_hi = 2048 as fast, 1024 3 % faster, not worth kernels of their own.)
+int wide_window_slices(const sals_ctx* win)
+{
+    const sals_desc& d = win->d;
+    if (win->plan.pick != 4 || d.dtype != SALS_BF16 || d.H_q != d.H_kv || d.H_kv % 2 != 0) return 0;
+    const int tiles = ceil_div(d.B, 4) * (d.H_kv / 2), steps = d.r * 2 / kLgStep;
+    return std::max(1, std::min({(256 - select_blocks(d)) / tiles > 2 ? (256 - select_blocks(d)) / tiles : 2, kLsMaxSplit, steps / 2}));
+}
 int window_select_slices(const sals_ctx* win)
 {
+    if (const int ks = wide_window_slices(win)) return ks;
     const LogitsPlan& P = win->plan;
     const sals_desc& d = win->d;
     const int tiles = P.pick == 4 ? ceil_div(d.B, 2) * d.H_kv : P.n_parts * d.H_kv * d.B, slots = P.pick == 4 ? 512 : 256;
@@ -756,7 +772,10 @@ template <typename T> sals_status allow_logits_lds(const sals_ctx* c)
     }
     // (a context without sinks and recent tokens may be a window)
     if (ok && c->d.n_sink == 0 && c->d.n_recent == 0) {
-        if (P.pick == 4) ok = allow(reinterpret_cast<const void*>(window_select_for<T>(group)), logits_cfg<1, 4, 1>::LDS);
+        if (P.pick == 4) {
+            const bool wide = wide_window_slices(c) > 0;
+            ok = allow(reinterpret_cast<const void*>(window_select_for<T>(group, wide)), wide ? logits_cfg<2, 4, 2>::LDS : logits_cfg<1, 4, 1>::LDS);
+        }
         if (P.pick == 3) {
             const int nst = steps_ahead<T>(c->d, window_slices(c));
             ok = allow(reinterpret_cast<const void*>(WindowSelectSmall<T>::get(nst)), kLsLds) &&
@@ -1492,9 +1511,12 @@ sals_status launch_window_select(sals_ctx* ctx, sals_ctx* win, const void* q, co
     ProfScope ps(ctx, SALS_K_TOPK, st);
     if (win->plan.pick == 4) {
         typedef logits_cfg<1, 4, 1> LC;
-        auto kern = window_select_for<T>(e.H_q / e.H_kv);
-        static_assert(LC::NT == 256 && LC::LDS >= sizeof(TopkShared), "the selection runs in the logits kernel's workgroup");
-        hipLaunchKernelGGL(kern, dim3(sel.n_blocks + ceil_div(e.B, 2) * e.H_kv * ks), dim3(LC::NT), LC::LDS, st, sel,
+        typedef logits_cfg<2, 4, 2> WC;   // wide tiles
+        const bool wide = wide_window_slices(win) > 0;
+        auto kern = window_select_for<T>(e.H_q / e.H_kv, wide);
+        static_assert(LC::NT == 256 && WC::NT == 512 && LC::LDS >= sizeof(TopkShared), "the selection runs in the logits kernel's workgroup");
+        const int tiles = wide ? ceil_div(e.B, 4) * (e.H_kv / 2) : ceil_div(e.B, 2) * e.H_kv;
+        hipLaunchKernelGGL(kern, dim3(sel.n_blocks + tiles * ks), dim3(wide ? WC::NT : LC::NT), wide ? WC::LDS : LC::LDS, st, sel,
                            static_cast<const T*>(Kw), w_section<T>(win, W_hi, 2), static_cast<const T*>(q), q_pos, rope, win->inv, logits,
                            stats, e.B, e.S_max, e.r, e.H_q, e.H_kv, w, L.lk, e.rope_style, scale, link.stride, plogits, ks);
     } else {

@@ -123,6 +123,16 @@ def test_shared_tiles_gqa_interleaved_rope_ring_wrap(oracle, monkeypatch):
     _case(oracle, w, seq_lens=[777, 500, 48, 49, 47, 0, 600, 100, 776])
 
 
+@pytest.mark.parametrize("B,H,r_hi", [(8, 2, 128), (9, 4, 256), (10, 6, 704), (15, 2, 320), (16, 32, 192)])
+def test_wide_window_tiles(oracle, B, H, r_hi, monkeypatch):
+    """The launch that a step's selection shares with the window's logits on tiles of two heads and four sequences: last tiles of
+    one, two, three and four sequences, slices of two steps, of three and of uneven numbers of them; empty, partial
+    and full windows.  The staged call, bit for bit, runs tiles of one head and two sequences."""
+    monkeypatch.setenv("SALS_TUNE_LOGITS", "4")
+    w = synth.shrink(SMALL, B=B, S=600, H=H, H_kv=H, r=64, r_hi=r_hi, plant=0)
+    _case(oracle, w, seq_lens=[600, 0, 1, 40, 41, 144, 145, 500, 23, 599, 39, 64, 300, 2, 139, 143][:B])
+
+
 @pytest.mark.parametrize("S,B,tiles", [(4099, 3, "3"), (8192, 3, "3"), (8200, 3, "3"), (5001, 5, "4"), (8192, 3, "4")])
 def test_selection_and_window_logits_in_one_launch(oracle, S, B, tiles, monkeypatch):
     """Both sides of the sequence lengths at which the selection has one more group of keys per thread (4096) and a launch of its
