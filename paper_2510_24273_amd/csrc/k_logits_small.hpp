@@ -190,7 +190,7 @@ __device__ __forceinline__ void logits_small_tile(
     }
     // slots past the selected tokens read the first selected row; they get no weight
     const int my_pos = min(max(my_slot < n ? idx_my : idx_0, 0), S_max - 1);
-    const int my_row = ring > 0 ? my_pos % ring : my_pos;  // ring cache: token t lies in row t mod ring
+    const int my_row = ring > 0 ? (unsigned)my_pos % (unsigned)ring : my_pos;  // ring cache: token t lies in row t mod ring
     const unsigned char* b_src =
         reinterpret_cast<const unsigned char*>(Kc + ((size_t)b * (ring > 0 ? ring : S_max) + my_row) * r) + pcol * 16 +
         (size_t)kz * nkc * kLgChunk;
@@ -281,20 +281,18 @@ __device__ __forceinline__ void logits_small_tile(
         }
         // partial dot products over this wave's 16 pairs, per query head of the group
         float* sDot = xch + 8 * 16 * 64;  // [token block 2][wave part 4][kMaxGroup][32]
+#pragma unroll 1  // (little code: see project_block)
+        for (int m = 0; m < G; ++m) {
+            float d = 0.f;
 #pragma unroll
-        for (int m = 0; m < kMaxGroup; ++m) {
-            if (m < G) {  // uniform
-                float d = 0.f;
-#pragma unroll
-                for (int aa = 0; aa < 2; ++aa) {
-                    const int p0 = dh * 32 + (2 * ksel + aa) * 8 + hi * 4;
-                    const f32x4 q1 = *reinterpret_cast<const f32x4*>(&sQ[m][p0]);
-                    const f32x4 q2 = *reinterpret_cast<const f32x4*>(&sQ[m][kPairs + p0]);
-                    d += dot_pairs(q1, q2, k1[aa], k2[aa]);
-                }
-                d += __shfl_xor(d, 32, kWave);
-                if (hi == 0) sDot[((tb * 4 + dh * 2 + ksel) * kMaxGroup + m) * 32 + l32] = d;
+            for (int aa = 0; aa < 2; ++aa) {
+                const int p0 = dh * 32 + (2 * ksel + aa) * 8 + hi * 4;
+                const f32x4 q1 = *reinterpret_cast<const f32x4*>(&sQ[m][p0]);
+                const f32x4 q2 = *reinterpret_cast<const f32x4*>(&sQ[m][kPairs + p0]);
+                d += dot_pairs(q1, q2, k1[aa], k2[aa]);
             }
+            d += __shfl_xor(d, 32, kWave);
+            if (hi == 0) sDot[((tb * 4 + dh * 2 + ksel) * kMaxGroup + m) * 32 + l32] = d;
         }
         __syncthreads();
         // ---- first wave: logits of the 64 tokens and the tile's softmax statistics ---------------

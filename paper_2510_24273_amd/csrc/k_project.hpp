@@ -53,6 +53,15 @@ struct ProjArgs {  // (what the first loads need comes first: those 14 words arr
 };
 
 // workgroup of NW waves, NBATCH row pieces and HB column blocks of a wave in flight per round; i0: first latent coordinate
+//
+// Code size counts here as in every kernel of a decode step: the instruction caches (64 KB for two CUs) keep code from one
+// launch to the next (measured: a launch's first pass through 32 KB is as fast as its second), so a step whose kernels fit
+// together runs from them, and one that exceeds them fetches lines from L2 or, behind large caches, from memory (20-30 ns a line) on
+// every pass: the same kernels of a small step linked in nine orders took 27.7 to 29.1 us.  So the column blocks are a loop and
+// not unrolled over registers of their own (a slice of one round still keeps U^T's pieces for all of them), 12.0 -> 2.4 KB for
+// up to 16 columns.  With the value sum's shorter code, whole steps: 1 x (512 of 4096) 28.0 -> 27.4 us, 12 ragged sequences
+// of 8 KV heads 65.1 -> 62.2 (the projection 5.9 -> 4.8), 32 x 2048 the same way 84 -> 79.5, 64 x 2048 of 32 KV heads 263 -> 255; 128
+// sequences, two rounds of column blocks in the append, 124.3 -> 126.5.
 template <typename T, bool QUERY, int NW, int NBATCH, int HB>
 __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int slice, int proj)
 {
@@ -60,74 +69,75 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int sli
     constexpr int KS = 4 * VEC;  // elements of the D axis per MFMA step
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, kg = lane >> 4;
-    const int G = QUERY ? a.H / a.H_kv : 1;
+    const int G = QUERY ? (unsigned)a.H / (unsigned)a.H_kv : 1;
     const int ncols = a.B * G, n_nblk = (ncols + 15) >> 4;
-    const int nks_all = a.D / KS, nks = nks_all / a.np;   // steps of this workgroup's slice
+    const int nks = (unsigned)a.D / KS / (unsigned)a.np;  // steps of this workgroup's slice
     const int ks_first = slice * nks;
     const T* UT = static_cast<const T*>(a.UT[proj]);
     const T* X = static_cast<const T*>(a.X[proj]);
     const T* arow = UT + (size_t)(i0 + l16) * a.D + kg * VEC;
 
-    __shared__ __attribute__((aligned(16))) float red[NW][64][4];
+    __shared__ __attribute__((aligned(16))) float red[HB][NW][64][4];
     __shared__ float colsum[kProjMaxCols][16];
 
-    f32x4v acc[kProjMaxCols / 16];
+    u32x4 af[NBATCH];
+    for (int nb0 = 0; nb0 < n_nblk; nb0 += HB) {
+        const T* xrow[HB];
 #pragma unroll
-    for (int nb = 0; nb < kProjMaxCols / 16; ++nb) acc[nb] = f32x4v{0.f, 0.f, 0.f, 0.f};
+        for (int h = 0; h < HB; ++h) {  // (columns past the last one repeat it)
+            const int n = min((nb0 + h) * 16 + l16, ncols - 1), b = (unsigned)n / (unsigned)G;
+            xrow[h] = X + (QUERY ? ((size_t)b * a.H + n - b * G) * kHeadDim : (size_t)n * a.D) + kg * VEC;
+        }
+        f32x4v acc[HB];
+#pragma unroll
+        for (int h = 0; h < HB; ++h) acc[h] = f32x4v{0.f, 0.f, 0.f, 0.f};
 
-    // this wave's steps: wave, wave+NW, ... ; NBATCH steps of loads per round.  Branches are wave-uniform (a step that is not
-    // there costs no load), columns past the last one repeat it.
-    for (int ks0 = wave; ks0 < nks; ks0 += NW * NBATCH) {
-        u32x4 af[NBATCH];
+        // this wave's steps: wave, wave+NW, ... ; NBATCH steps of loads per round, those of all its column blocks requested
+        // together, ahead of their products: a round costs one memory round trip.  Branches are wave-uniform (a step that is not
+        // there costs no load: clamped instead, 24 columns of 64 steps took 12.4 us where 8.1 do).
+        for (int ks0 = wave; ks0 < nks; ks0 += NW * NBATCH) {
+            if (nb0 == 0 || nks > NW * NBATCH) {
 #pragma unroll
-        for (int u = 0; u < NBATCH; ++u)
-            if (ks0 + u * NW < nks) af[u] = ld16(arow + (size_t)(ks_first + ks0 + u * NW) * KS);
-        // the x operands of HB column blocks are requested together, ahead of their products: a round costs one memory
-        // round trip per HB column blocks
+                for (int u = 0; u < NBATCH; ++u)
+                    if (ks0 + u * NW < nks) af[u] = ld16(arow + (size_t)(ks_first + ks0 + u * NW) * KS);
+            }
+            u32x4 bf[HB][NBATCH];
 #pragma unroll
-        for (int nb0 = 0; nb0 < kProjMaxCols / 16; nb0 += HB) {
-            if (nb0 < n_nblk) {  // uniform
-                u32x4 bf[HB][NBATCH];
+            for (int h = 0; h < HB; ++h) {
+                if (nb0 + h < n_nblk) {
 #pragma unroll
-                for (int h = 0; h < HB; ++h) {
-                    if (nb0 + h < n_nblk) {
-                        const int n = min((nb0 + h) * 16 + l16, ncols - 1), b = n / G;
-                        const T* xrow = X + (QUERY ? ((size_t)b * a.H + n - b * G) * kHeadDim : (size_t)n * a.D) + kg * VEC;
-#pragma unroll
-                        for (int u = 0; u < NBATCH; ++u)
-                            if (ks0 + u * NW < nks) {
-                                const int c = (ks_first + ks0 + u * NW) * KS;  // (a step lies within one head)
-                                bf[h][u] = ld16(xrow + (QUERY ? c / kHeadDim * G * kHeadDim + c % kHeadDim : c));
-                            }
-                    }
+                    for (int u = 0; u < NBATCH; ++u)
+                        if (ks0 + u * NW < nks) {
+                            const unsigned c = (unsigned)(ks_first + ks0 + u * NW) * KS;  // (a step lies within one head)
+                            bf[h][u] = ld16(xrow[h] + (QUERY ? c / kHeadDim * G * kHeadDim + c % kHeadDim : c));
+                        }
                 }
-                asm volatile("" ::: "memory");  // (keeps the loads above from sinking towards their products)
+            }
+            asm volatile("" ::: "memory");  // (keeps the loads above from sinking towards their products)
 #pragma unroll
-                for (int h = 0; h < HB; ++h)
-                    if (nb0 + h < n_nblk) {
+            for (int h = 0; h < HB; ++h) {
+                if (nb0 + h < n_nblk) {
 #pragma unroll
-                        for (int u = 0; u < NBATCH; ++u)
-                            if (ks0 + u * NW < nks) mma16_op<T>::run(af[u], bf[h][u], acc[nb0 + h]);
-                    }
+                    for (int u = 0; u < NBATCH; ++u)
+                        if (ks0 + u * NW < nks) mma16_op<T>::run(af[u], bf[h][u], acc[h]);
+                }
             }
         }
-    }
 
-    // fold the waves' sums in wave order; acc[nb][v] is (coordinate 4*kg+v, column nb*16+l16)
+        // fold the waves' sums in wave order; acc[h][v] is (coordinate 4*kg+v, column (nb0+h)*16+l16)
+        if (nb0 > 0) __syncthreads();
 #pragma unroll
-    for (int nb = 0; nb < kProjMaxCols / 16; ++nb) {
-        if (nb < n_nblk) {  // uniform
-            __syncthreads();
+        for (int h = 0; h < HB; ++h) *reinterpret_cast<f32x4v*>(red[h][wave][lane]) = acc[h];
+        __syncthreads();
+        if (tid < 256) {
+            const int col = tid & 15, rr = tid >> 4;
+            const int src_lane = (rr >> 2) * 16 + col, v = rr & 3;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) red[wave][lane][v] = acc[nb][v];
-            __syncthreads();
-            if (tid < 256) {
-                int col = tid & 15, rr = tid >> 4;
-                int src_lane = (rr >> 2) * 16 + col, v = rr & 3;
+            for (int h = 0; h < HB; ++h) {
                 float s = 0.f;
 #pragma unroll
-                for (int w = 0; w < NW; ++w) s += red[w][src_lane][v];
-                colsum[nb * 16 + col][rr] = s;
+                for (int w = 0; w < NW; ++w) s += red[h][w][src_lane][v];
+                if (nb0 + h < n_nblk) colsum[(nb0 + h) * 16 + col][rr] = s;
             }
         }
     }
@@ -142,17 +152,21 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int sli
         } else {
             const int t_new = a.seq_len[b];
             const int rows = a.ring > 0 ? a.ring : a.S_max;
-            const int row = a.ring > 0 ? t_new % a.ring : t_new;
-            if (t_new >= 0 && t_new < a.S_max)
+            if (t_new >= 0 && t_new < a.S_max) {
+                const int row = a.ring > 0 ? (unsigned)t_new % (unsigned)a.ring : t_new;
                 elem<T>::store(static_cast<T*>(a.cache[proj]) + ((size_t)b * rows + row) * a.r + i0 + rr, s);
+            }
         }
     }
 }
 
-template <typename T>
+// HB: as many column blocks as there are, up to 4, so that all their operands arrive in one round trip (1 x 48 columns, r = 640, D =
+// 1024: 5.6 us unrolled over all blocks, 7.6 in rounds of two, 5.4 in one of four; eight at once draw on the accumulator
+// registers and are no faster than twice four: 128 columns 9.7 and 9.9, 96 columns 7.4 and 7.1)
+template <typename T, int HB>
 __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjArgs a)
 {
-    project_block<T, true, kProjWaves, kProjBatch, 2>(a, blockIdx.x * 16, blockIdx.y, blockIdx.z);
+    project_block<T, true, kProjWaves, kProjBatch, HB>(a, blockIdx.x * 16, blockIdx.y, blockIdx.z);
 }
 
 // Append in slices of the D axis: adds up the slices' partial sums (in slice order) into the new rows and advances the lengths.

@@ -94,7 +94,7 @@ __device__ __forceinline__ void qv_quantize_group(const QuantArgs& qa, const int
 // launch adds the slices up (append_finish_kernel), and where none does (a recent window) eight waves have all their pieces in
 // flight.  (Batch 16, D = 4096, r = 512, 2-bit values, with the advance: 12.4 + 3.9 + 1.4 us as three launches of four waves,
 // 10.2 + 1.4 with eight waves over the whole axis, 5.3 + 2.8 sliced.)
-template <typename T, int NW, bool QUANT>
+template <typename T, int NW, bool QUANT, int HB>
 __global__ __launch_bounds__(64 * NW) void append_kernel(ProjArgs a, QuantArgs qa)
 {
     if (QUANT && blockIdx.z == 1) {
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(64 * NW) void append_kernel(ProjArgs a, QuantArgs q
         return;
     }
     if (QUANT && (int)blockIdx.x * 16 >= a.r) return;  // (the grid covers the longer of the two parts)
-    project_block<T, false, NW, NW == kProjWaves ? kProjBatch : 16, NW == kProjWaves ? 2 : 1>(a, blockIdx.x * 16, blockIdx.y, blockIdx.z);
+    project_block<T, false, NW, NW == kProjWaves ? kProjBatch : 16, HB>(a, blockIdx.x * 16, blockIdx.y, blockIdx.z);
 }
 
 struct QvArgs {

@@ -41,7 +41,7 @@ __device__ __forceinline__ void warm_projector(const T* __restrict__ Uv, int r, 
         uint32_t w[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {  // (from clamped addresses: requested together)
-            const int i = min(i0 + u * n_slots * n_threads, pieces - 1), k = i / per_head;
+            const int i = min(i0 + u * n_slots * n_threads, pieces - 1), k = (unsigned)i / (unsigned)per_head;
             w[u] = *reinterpret_cast<const uint32_t*>(base + ((size_t)(xcd + k * kXcds) * per_head + (i - k * per_head)) * 64);
         }
         asm volatile("" :: "v"(w[0] ^ w[1] ^ w[2] ^ w[3]));  // (the values are of no use; the loads must stay)
@@ -50,8 +50,13 @@ __device__ __forceinline__ void warm_projector(const T* __restrict__ Uv, int r, 
 
 // NW waves (4 or 8), MB blocks of 32 heads.  The range's tokens are dealt to the waves in groups of one MFMA
 // contraction step (16 tokens for bf16, 8 for fp32: half of them per half-wave); a wave works through its groups on
-// its own, no barrier inside the loop, and keeps the loads of DEPTH groups in flight (2 or 4, by what a wave has: the first
-// are requested unconditionally, so that waiting for the statistics requested before them does not wait for them too).
+// its own, no barrier inside the loop, and keeps the loads of DEPTH groups in flight (the first are requested
+// unconditionally, so that waiting for the statistics requested before them does not wait for them too).  DEPTH is small
+// because the loop is unrolled that often and its code is fetched cold: the eight waves keep a CU's memory path busy by
+// themselves.  bf16, r = 640, 32 heads, behind a copy that empties the caches, four | two | one group ahead: 16 sequences of
+// 512 tokens in one range 8.9 | 7.9 | 7.8 us, 4 of 2048 in six 8.4 | 7.4 | 7.0; fp32 (groups half as long), 4 of 512 in four 6.4 |
+// 5.9 | 5.8, 1 of 512 in two 7.5 | 7.3 | 7.6.  Four waves, one | two ahead: bf16, 256 tokens in two ranges 5.3 | 4.6, fp32, 64
+// tokens 4.9 | 4.6.
 //
 // The MFMA's second operand wants, per lane, consecutive TOKENS of one column, while memory holds consecutive
 // columns of one token.  bf16: lane l32 fetches the 32-bit word (columns 2 l32, 2 l32 + 1) of each of its eight
@@ -66,7 +71,7 @@ template <typename T> struct PvSecond {
     const int32_t* idx; const int32_t* n_sel; const T* Vc; const float* logits; float* Tpart;
     int r, n_tr, tok_per_wg, k_tot, lk, S_max, ring;
 };
-template <typename T, int NW, int MB, int DEPTH, bool TWO>
+template <typename T, int NW, int MB, bool TWO>
 __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ n_sel, const float2* __restrict__ stats,
     int B, int r, int n_tr, int n_parts, int tok_per_wg, int k_tot, int H, int lk,
@@ -79,6 +84,7 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
     constexpr int VEC = elem<T>::vec;        // tokens per lane per group = elements per 16 bytes
     constexpr int KG = 2 * VEC;              // tokens per group (both half-waves)
     constexpr bool kSplit = ES == 2;
+    constexpr int DEPTH = NW == 8 && kSplit ? 1 : 2;
     constexpr int ND = 8;                    // gathered words per lane and group: 8 tokens (bf16) | 4 tokens x 2 column blocks (fp32)
 
     __shared__ __attribute__((aligned(16))) int sRow[kPvMaxTok];  // cache row of every token of the nominal range
@@ -105,7 +111,7 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
     }
     const int xcd = id % kXcds, slot = id / kXcds, qn = total / kXcds, rem = total % kXcds;
     const int item = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + slot;
-    const int cb = item % n_cb, tr = (item / n_cb) % n_tr, b = item / (n_cb * n_tr);
+    const int trb = (unsigned)item / (unsigned)n_cb, cb = item - trb * n_cb, b = (unsigned)trb / (unsigned)n_tr, tr = trb - b * n_tr;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hi = lane >> 5;
     const int col0 = cb * kPvCols;
@@ -118,7 +124,7 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
         const int j = tr * tok_per_wg + t;
         const int v = ib[min(j, k_tot - 1)];
         const int pos = min(max(v, 0), S_max - 1);
-        sRow[t] = ring > 0 ? pos % ring : pos;  // ring cache: token t lies in row t mod ring
+        sRow[t] = ring > 0 ? (unsigned)pos % (unsigned)ring : pos;  // ring cache: token t lies in row t mod ring
     }
     constexpr int LPH = kPvThreads / kPvMaxHeads;   // lanes that share a head's tiles
     const int sh = tid / LPH, sub = tid % LPH;
@@ -132,7 +138,7 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
 
     const unsigned char* vbytes =
         reinterpret_cast<const unsigned char*>(Vc + (size_t)b * (ring > 0 ? ring : S_max) * r + col0) + l32 * 4;
-    const size_t row_bytes = (size_t)r * ES;
+    const uint32_t row_bytes = (uint32_t)r * ES;
     const int g_last = tok_per_wg / KG - 1;  // (the range is a whole number of groups)
     // what a group needs from global memory: the gathered words and this lane's logits
     struct Stage { uint32_t R[ND]; f32x4 X[MB][VEC / 4]; };
@@ -146,7 +152,7 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
         }
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
-            const unsigned char* src = vbytes + (size_t)rows[v] * row_bytes;
+            const unsigned char* src = vbytes + (uint64_t)(uint32_t)rows[v] * row_bytes;  // (one 32 x 32 + 64 bit instruction)
             S.R[v] = *reinterpret_cast<const uint32_t*>(src);
             if constexpr (!kSplit) S.R[VEC + v] = *reinterpret_cast<const uint32_t*>(src + 32 * 4);
         }

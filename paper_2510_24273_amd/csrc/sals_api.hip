@@ -188,8 +188,9 @@ Layout make_layout(const sals_desc& d, bool short_ranges = true)
         if (const char* e = std::getenv("SALS_TUNE_PV_RANGES")) n_tr = std::max(1, std::min(64, std::atoi(e)));  // tuning aid
         n_tr = std::max(n_tr, ceil_div(k_tot, kPvMaxTok));
         int tok = ceil_div(ceil_div(k_tot, n_tr), kPvTJ) * kPvTJ;
-        // eight waves once each of them has two groups of 16 tokens (measured: 128 tokens are 0.5 us faster with four)
-        L.pv_waves = tok >= 4 * kPvTJ ? 8 : 4;
+        // eight waves once each of them has two groups, in bf16 of 16 tokens (measured: 128 tokens are 0.5 us faster with four), in
+        // fp32 of 8 (r = 640, one sequence: 192 tokens 6.5 us with eight and 7.2 with four, 64 tokens 4.8 and 4.6)
+        L.pv_waves = tok >= (d.dtype == SALS_BF16 ? 4 : 2) * kPvTJ ? 8 : 4;
         if (const char* e = std::getenv("SALS_TUNE_PV_WAVES")) L.pv_waves = std::atoi(e) == 4 ? 4 : 8;  // tuning aid
         L.pv_tok_per_wg = tok;
         L.pv_ntr = ceil_div(k_tot, tok);
@@ -277,7 +278,11 @@ template <typename T> sals_status launch_project(const sals_ctx* c, const void* 
     a.B = d.B; a.D = d.H_kv * d.d; a.r = d.r; a.H = d.H_q; a.H_kv = d.H_kv; a.d = d.d;
     a.S_max = d.S_max; a.nproj = 1; a.np = c->L.proj_np;
     ProfScope ps(c, SALS_K_PROJECT, st);
-    hipLaunchKernelGGL((project_kernel<T>), dim3(d.r / 16, a.np), dim3(kProjThreads), 0, st, a);
+    const dim3 grid(d.r / 16, a.np), wg(kProjThreads);
+    const int blocks = ceil_div(d.B * (d.H_q / d.H_kv), 16);
+    if (blocks <= 1) hipLaunchKernelGGL((project_kernel<T, 1>), grid, wg, 0, st, a);
+    else if (blocks <= 2) hipLaunchKernelGGL((project_kernel<T, 2>), grid, wg, 0, st, a);
+    else hipLaunchKernelGGL((project_kernel<T, 4>), grid, wg, 0, st, a);
     return launch_status();
 }
 
@@ -308,12 +313,16 @@ sals_status launch_append(const sals_ctx* c, const void* W, const void* k_new, c
     const int nw = wide ? kAppendWaves : kProjWaves;
     {
         ProfScope ps(c, SALS_K_PROJECT, st);
-#define SALS_APPEND(NW, QUANT)                                                                                           \
-    hipLaunchKernelGGL((append_kernel<T, NW, QUANT>),                                                                    \
+#define SALS_APPEND_H(NW, QUANT, HB)                                                                                     \
+    hipLaunchKernelGGL((append_kernel<T, NW, QUANT, HB>),                                                                \
                        dim3(QUANT ? std::max(d.r / 16, ceil_div(d.B * (a.D / kQvGroup), 2 * nw * a.np)) : d.r / 16, a.np, \
                             QUANT ? 2 : a.nproj), dim3(64 * NW), 0, st, a, qa)
+#define SALS_APPEND(NW, QUANT)                                                                                           \
+    do { if (d.B <= 16) SALS_APPEND_H(NW, QUANT, 1); else if (d.B <= 32 || NW > kProjWaves) SALS_APPEND_H(NW, QUANT, 2); \
+         else SALS_APPEND_H(kProjWaves, QUANT, 4); } while (0)
         if (qa.bits) { if (wide) SALS_APPEND(kAppendWaves, true); else SALS_APPEND(kProjWaves, true); }
         else { if (wide) SALS_APPEND(kAppendWaves, false); else SALS_APPEND(kProjWaves, false); }
+#undef SALS_APPEND_H
 #undef SALS_APPEND
     }
     if (launch_status() != SALS_OK) return SALS_ERR_HIP;
@@ -815,17 +824,13 @@ void launch_pv(const sals_ctx* c, const float2* stats, int stats_stride, const P
     const int n_more = b ? g.r / kPvCols * g.n_tr * d.B
                          : (n_items < 256 && uv_bytes <= (size_t)6 << 20 ? (256 - n_items) / kXcds * kXcds : 0);
     const bool w8 = a.c->L.pv_waves == 8 || (b && b->c->L.pv_waves == 8);
-    // token groups (of 16, in fp32 of 8 tokens) per wave decide how many are loaded ahead
-    const bool deep = ceil_div(std::max(f.tok_per_wg, b ? g.tok_per_wg : 0), 2 * elem<T>::vec) > 2 * (w8 ? 8 : 4);
-#define SALS_PV(NW, MB, DEPTH, TWO)                                                                                       \
-    hipLaunchKernelGGL((attend_pv_kernel<T, NW, MB, DEPTH, TWO>), dim3(n_items + n_more), dim3(NW * 64), 0, st, f.idx,     \
+#define SALS_PV(NW, MB, TWO)                                                                                              \
+    hipLaunchKernelGGL((attend_pv_kernel<T, NW, MB, TWO>), dim3(n_items + n_more), dim3(NW * 64), 0, st, f.idx,            \
                        f.n_sel, stats, d.B, f.r, f.n_tr, stats_stride, f.tok_per_wg, f.k_tot, d.H_q, f.lk, f.Vc, f.logits, \
                        f.Tpart, f.S_max, f.ring, Uv, d.H_kv, g)
-#define SALS_PV_B(NW, MB, DEPTH) do { if (b) SALS_PV(NW, MB, DEPTH, true); else SALS_PV(NW, MB, DEPTH, false); } while (0)
-#define SALS_PV_D(NW, MB) do { if (deep) SALS_PV_B(NW, MB, 4); else SALS_PV_B(NW, MB, 2); } while (0)
-    if (d.H_q <= 32) { if (w8) SALS_PV_D(8, 1); else SALS_PV_D(4, 1); }
-    else { if (w8) SALS_PV_D(8, 2); else SALS_PV_D(4, 2); }
-#undef SALS_PV_D
+#define SALS_PV_B(NW, MB) do { if (b) SALS_PV(NW, MB, true); else SALS_PV(NW, MB, false); } while (0)
+    if (d.H_q <= 32) { if (w8) SALS_PV_B(8, 1); else SALS_PV_B(4, 1); }
+    else { if (w8) SALS_PV_B(8, 2); else SALS_PV_B(4, 2); }
 #undef SALS_PV_B
 #undef SALS_PV
 }

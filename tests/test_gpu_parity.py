@@ -403,6 +403,48 @@ def test_sliced_append_matches_oracle(oracle, dtype, H_kv, r, B):
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype,H,H_kv,r,B", [
+    ("bf16", 8, 2, 128, 4),      # 16 columns of query heads: one block
+    ("bf16", 8, 2, 128, 7),      # two blocks, the second one ragged
+    ("bf16", 16, 2, 192, 6),     # three blocks in a round of four
+    ("bf16", 4, 4, 128, 33),     # appends in rounds of four blocks
+    ("bf16", 12, 12, 64, 20),    # appends of eight waves, a round of two blocks
+    ("bf16", 12, 12, 64, 50),    # two such rounds
+    ("f32", 4, 4, 64, 70),       # two rounds of four blocks, the second of one ragged block
+    ("f32", 32, 32, 1024, 70)])  # the same, with two rounds of loads along the D axis
+def test_projections_in_column_blocks(oracle, dtype, H, H_kv, r, B):
+    """Query projection and append over one to five blocks of 16 columns, and more of them than a round holds: scores
+    and appended rows of the sequences at the blocks' edges against the oracle, one bf16 ulp for the rows as in the tests above
+    (fp32: sums of at most 4096 products of unit normals and 1 / 64 in fp32, below 1e-5)."""
+    S = 24
+    w = synth.shrink(SMALL, B=B, S=S, top_k=8, H=H, H_kv=H_kv, r=r, plant=0, dtype=dtype)
+    lens = [(5 * b + 9) % S for b in range(B)]
+    L = synth.make_layer(w, seq_lens=lens)
+    ctx = gu.make_ctx(w)
+    G = gu.upload(L, ctx)
+    scores = torch.empty((B, S), dtype=torch.float32, device="cuda")
+    ctx.latent_scores(G["q"], G["W"], G["Kc"], G["seq_len"], scores)
+    rng = np.random.default_rng(13)
+    k_new = synth.store(rng.standard_normal((B, w.D_kv)), dtype)
+    v_new = synth.store(rng.standard_normal((B, w.D_kv)), dtype)
+    ctx.compress_append(gu.to_dev(k_new), gu.to_dev(v_new), G["W"], G["Kc"], G["Vc"], G["seq_len"])
+    torch.cuda.synchronize()
+    assert G["seq_len"].tolist() == [n + 1 for n in lens]
+    for b in sorted({0, B // 2, B - 2, B - 1} | {e for e in (15, 16, 31, 32, 63, 64) if e < B}):
+        n = lens[b]
+        qt = oracle.project(oracle.group_sum(synth.widen(L["q"][b]), H_kv), synth.widen(L["Uk"]))
+        K = synth.widen(L["Kc"][b][:n])
+        got = gu.from_dev(scores[b])
+        bound = 2e-5 * np.linalg.norm(qt[:w.rs]) * np.linalg.norm(K[:, :w.rs], axis=1) + 1e-6
+        assert np.all(np.abs(got[:n] - oracle.scores(qt, K, w.rs)) <= bound), b
+        assert np.all(np.isneginf(got[n:])), b
+        for new, U, c in ((k_new, "Uk", "Kc"), (v_new, "Uv", "Vc")):
+            want = oracle.project(synth.widen(new[b]), synth.widen(L[U]))
+            tol = np.abs(want) * 2.0 ** -7 + 1e-6 if dtype == "bf16" else 1e-5
+            assert np.all(np.abs(gu.from_dev(G[c][b, n]) - want) <= tol), (c, b)
+    ctx.close()
+
+
 def test_query_position_beyond_the_cache(oracle):
     """q_pos far above S_max: the query's angles are then evaluated in the kernel instead of
     being read from the per-context cos/sin table."""
