@@ -2041,7 +2041,6 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     bool series;
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0 || !eig_plan(D, workspace_bytes, &off, &n_part, &series))
         return SALS_ERR_WORKSPACE;
-    if (calib_all_lds() != SALS_OK) return SALS_ERR_HIP;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     auto at = [&](size_t o) { return reinterpret_cast<double*>(ws + o); };
@@ -2059,6 +2058,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     const bool all = series && D <= kAllMaxD;
     const std::unique_ptr<double[]> host(new (std::nothrow) double[(size_t)n_blocks + D + std::max(2 * n_tiles, n_angles + n_tiles)]);
     if (!host) return SALS_ERR_HIP;
+    if (series && calib_all_lds() != SALS_OK) return SALS_ERR_HIP;  // (behind the memory: the runtime has no error for a lack of it)
     double *const h_conv = host.get(), *const h_norm = h_conv + n_blocks, *const h_found = h_norm + D;
     auto row_norms = [&](const double* M) -> bool {  // row norms to the host (blocking)
         hipLaunchKernelGGL(calib_rownorm_kernel, dim3(D), dim3(kCalThreads), 0, st, M, D, norm, sgn);
