@@ -7,6 +7,18 @@ namespace sals {
 
 constexpr int kXcds = 8;       // accelerator dies, workgroups are dealt to them round-robin
 
+// n / d for 0 <= n, d < 2^24: numbers of heads, sequences, slices, tiles and work items (a grid has fewer than 2^32 threads, 256 or
+// more of them per workgroup).  A kernel's first loads wait for a chain of these, and 24 bits divide in 12 instructions (one float
+// reciprocal and a correction), 32 signed ones in 26.
+__device__ __forceinline__ int idiv(int n, int d) { return (int)(((unsigned)n & 0xffffffu) / ((unsigned)d & 0xffffffu)); }
+
+// Workgroup `id` of N -> its item, one contiguous range of the list of N items per XCD.
+__device__ __forceinline__ int xcd_item(int id, int N)
+{
+    const int xcd = (unsigned)id % kXcds, slot = (unsigned)id / kXcds, qn = (unsigned)N / kXcds, rem = (unsigned)N % kXcds;
+    return xcd * qn + min(xcd, rem) + slot;
+}
+
 constexpr int kWave = 64;
 constexpr int kHeadDim = 128;        // head width the kernels are written for
 constexpr int kPairs = kHeadDim / 2; // RoPE pairs per head

@@ -42,7 +42,7 @@ __global__ __launch_bounds__(256) void dense_attend_kernel(const T* __restrict__
     const int chunk = blockIdx.x, h0 = blockIdx.y * HB, b = blockIdx.z;
     const int tid = threadIdx.x, li = tid & 15, tg = tid >> 4;   // lane group tg = wave * 4 + DPP row
     const int hb = (tg & 3) % HB, slot = (tg >> 2) * (4 / HB) + (tg & 3) / HB;
-    const int G = H / H_kv;
+    const int G = idiv(H, H_kv);
     const int S_v = ld_uniform_i32(seq_len + b), qp_v = ld_uniform_i32(q_pos + b);
     const size_t row_stride = (size_t)H_kv * kHeadDim;
     const T* kb = K + ((size_t)b * S_max * H_kv + h0 + hb) * kHeadDim + li * VEC;

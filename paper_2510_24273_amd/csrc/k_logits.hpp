@@ -101,24 +101,20 @@ __device__ __forceinline__ void logits_tile(
     int b, g0, part, kz = 0;   // MULTI: b is the first sequence of the tile
     if constexpr (MULTI) {
         // list order (head, sequence group, latent slice): an XCD's range keeps a few heads' projector slices
-        const int nsg = (B + SQ - 1) / SQ, N = nsg * (H_kv / HEADS) * ksplit;
-        const int id = block, xcd = id % kXcds, slot = id / kXcds;
-        const int qn = N / kXcds, rem = N % kXcds;
-        const int w = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + slot;
-        const int hb = w / (nsg * ksplit), rest = w - hb * (nsg * ksplit);
+        const int nsg = (unsigned)(B + SQ - 1) / SQ, N = nsg * ((unsigned)H_kv / HEADS) * ksplit;
+        const int w = xcd_item(block, N);
+        const int hb = idiv(w, nsg * ksplit), rest = w - hb * (nsg * ksplit), sg = idiv(rest, ksplit);
         g0 = hb * HEADS;
-        b = (rest / ksplit) * SQ; kz = rest % ksplit; part = 0;
+        b = sg * SQ; kz = rest - sg * ksplit; part = 0;
     } else {
-        const int n_y = H_kv / HEADS, N = n_parts * n_y * B;
-        const int id = block, xcd = id % kXcds, slot = id / kXcds;
-        const int qn = N / kXcds, rem = N % kXcds;
-        const int w = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + slot;
+        const int n_y = (unsigned)H_kv / HEADS, N = n_parts * n_y * B;
+        const int w = xcd_item(block, N);
         if (heads_fastest) {
-            const int bt = w / n_y;
-            g0 = (w - bt * n_y) * HEADS; b = bt / n_parts; part = bt - b * n_parts;
+            const int bt = idiv(w, n_y);
+            g0 = (w - bt * n_y) * HEADS; b = idiv(bt, n_parts); part = bt - b * n_parts;
         } else {
-            const int hb = w / (n_parts * B), bt = w - hb * (n_parts * B);
-            g0 = hb * HEADS; b = bt / n_parts; part = bt - b * n_parts;
+            const int hb = idiv(w, n_parts * B), bt = w - hb * (n_parts * B);
+            g0 = hb * HEADS; b = idiv(bt, n_parts); part = bt - b * n_parts;
         }
     }
     const int tok0 = part * C::TOK;
@@ -132,7 +128,7 @@ __device__ __forceinline__ void logits_tile(
     // for the thread's share of the cos/sin rows, see rotate_queries)
     const int n_v = ld_uniform_i32((BYLEN ? win.seq_len : n_sel) + (MULTI ? seq_of(tg * WT) : b));
     const int qpos_v = MULTI ? q_pos[seq_of(tid & ~63)] : ld_uniform_i32(q_pos + b);  // in flight with the loads below
-    const int G = GFIX > 0 ? GFIX : H / H_kv;
+    const int G = GFIX > 0 ? GFIX : idiv(H, H_kv);
     const int g = g0 + hh;
     static_assert(!RESOLVE || !MULTI, "a tile of one sequence");
     uint2 cand[(kTmCand + NT - 1) / NT];
@@ -156,7 +152,7 @@ __device__ __forceinline__ void logits_tile(
     SplitLogitsJob job;
     const int job_id = block * (NT / 64) + wave;
     const bool has_job = SIDE && job_id < split.rows * split.n_parts;  // uniform
-    auto request_job = [&](int j) { const int row = j / split.n_parts; job.request(split, row, j - row * split.n_parts); };
+    auto request_job = [&](int j) { const int row = idiv(j, split.n_parts); job.request(split, row, j - row * split.n_parts); };
     if (has_job) request_job(job_id);
     // cache row (= RoPE position) of tile token t: slot t of the one sequence, or slot t % 64 of sequence b + t / 64
     auto window_of = [&](int len, int* S) {  // tokens of a window by length
@@ -192,7 +188,7 @@ __device__ __forceinline__ void logits_tile(
     for (int u = 0; u < QP; ++u) {
         // query pair t: (sequence of the tile, query head of the tile's heads, pair)
         const int t = min(tid + u * NT, SQ * HEADS * G * kPairs - 1), p = t & (kPairs - 1);
-        const int hq = t >> 6, sq = MULTI ? hq / (HEADS * G) : 0, hm = MULTI ? hq - sq * (HEADS * G) : hq;
+        const int hq = t >> 6, sq = MULTI ? idiv(hq, HEADS * G) : 0, hm = MULTI ? hq - sq * (HEADS * G) : hq;
         const T* qrow = q + ((size_t)seq_of(sq * 64) * H + (size_t)g0 * G + hm) * kHeadDim;
         qa[u] = elem<T>::load(qrow + pair_first(p, style));
         qb[u] = elem<T>::load(qrow + pair_second(p, style));
@@ -292,8 +288,9 @@ __device__ __forceinline__ void logits_tile(
             if (t < SQ * HEADS * G * kPairs) {
                 // (t / 64 = (sequence * heads of the tile + head) * G + head of the group)
                 const int p = t & (kPairs - 1), hm = t >> 6;
-                const float2 c = sCS[MULTI ? hm / (HEADS * G) : 0][p];
-                float* dst = &sQ[0][0][0] + (size_t)((hm / G) * GQ + hm % G) * kHeadDim;
+                const float2 c = sCS[MULTI ? idiv(hm, HEADS * G) : 0][p];
+                const int hd = idiv(hm, G);
+                float* dst = &sQ[0][0][0] + (size_t)(hd * GQ + hm - hd * G) * kHeadDim;
                 rotate_query(qa[u], qb[u], c, scale, dst[p], dst[kPairs + p]);
             }
         }
@@ -498,7 +495,7 @@ __device__ __forceinline__ void logits_tile(
     // the waves' statistics, merged in wave order: those of a head, or (MULTI) of a sequence, whose single tile this is
     constexpr int WS = MULTI ? 64 / WT : NTG;  // waves to merge
     if (tid < SQ * HEADS * G) {
-        const int u = tid / G, m = tid - u * G, sq = MULTI ? u / HEADS : 0, bt = b + sq, h2 = u - sq * HEADS;
+        const int u = idiv(tid, G), m = tid - u * G, sq = MULTI ? (unsigned)u / HEADS : 0, bt = b + sq, h2 = u - sq * HEADS;
         float2 st = sStat[h2][sq * WS][m];
 #pragma unroll
         for (int t = 1; t < WS; ++t) st = stat_merge(st, sStat[h2][sq * WS + t][m]);

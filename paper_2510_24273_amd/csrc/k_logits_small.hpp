@@ -60,24 +60,21 @@ __device__ __forceinline__ void logits_small_tile(
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hi = lane >> 5;
     const int ksel = wave & 1, dh = (wave >> 1) & 1, tb = wave >> 2;
-    const int G = H / H_kv;
+    const int G = idiv(H, H_kv);
 
     // workgroup id -> (sequence, token tile, KV head), one contiguous range of the list per XCD
     int b, g, part, kz;  // kz: this workgroup's slice of the latent axis (the slices of a tile are neighbours)
     {
         const int N = n_parts * H_kv * B * ksplit;
-        const int id = block, xcd = id % kXcds, slot = id / kXcds;
-        const int qn = N / kXcds, rem = N % kXcds;
-        const int wk = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + slot;
-        const int w = wk / ksplit;
+        const int wk = xcd_item(block, N), w = ksplit == 1 ? wk : idiv(wk, ksplit);
         kz = wk - w * ksplit;
         if (heads_fastest) {
-            const int bt = w / H_kv;
-            g = w - bt * H_kv; b = bt / n_parts; part = bt - b * n_parts;
+            const int bt = idiv(w, H_kv);
+            g = w - bt * H_kv; b = idiv(bt, n_parts); part = bt - b * n_parts;
         } else {
-            g = w / (n_parts * B);
+            g = idiv(w, n_parts * B);
             const int bt = w - g * (n_parts * B);
-            b = bt / n_parts; part = bt - b * n_parts;
+            b = idiv(bt, n_parts); part = bt - b * n_parts;
         }
     }
     const int tok0 = part * kLsTok;
@@ -98,7 +95,7 @@ __device__ __forceinline__ void logits_small_tile(
     const bool has_job = SIDE && job_id < split.rows * split.n_parts;  // uniform
     // (never more jobs than waves: a KV head has at most kMaxGroup rows, and the other pass, over part of this one's list, no more tiles)
     static_assert(kLsThreads / kWave >= kMaxGroup, "a wave per query head of a tile's KV head");
-    if (has_job) { const int row = job_id / split.n_parts; job.request(split, row, job_id - row * split.n_parts); }
+    if (has_job) { const int row = idiv(job_id, split.n_parts); job.request(split, row, job_id - row * split.n_parts); }
     if constexpr (BYLEN) {
         n_v = ld_uniform_i32(win.seq_len + b);
     } else if constexpr (!FUSED) {
@@ -118,7 +115,7 @@ __device__ __forceinline__ void logits_small_tile(
                                  (pcol >> 2) * (kHeadDim * 64) + prow * 64 + (pcol & 3) * 16;
     const int a_dst0 = swz(prow, pcol), a_dst1 = swz(64 + prow, pcol);
     const int b_dst = kHeadDim * kLgChunk + swz(prow, pcol);
-    const int nkc = r * ES / kLgChunk / ksplit;  // 128-byte steps of this slice (the host makes it a whole number)
+    const int nkc = idiv(r * ES / kLgChunk, ksplit);  // 128-byte steps of this slice (the host makes it a whole number)
     a_src += (size_t)kz * nkc * (kHeadDim * kLgChunk);
 
     f32x16 acc0, acc1;  // slots dh*32 + (8a + 4hi + c) and their pair partners (+64)

@@ -255,11 +255,10 @@ __device__ __forceinline__ void prefill_tile(const PrefillArgs& a, int block, in
         }
         const int total = count * per_tile;
         if (block >= total) return;  // uniform
-        const int xcd = block % kXcds, slot = block / kXcds, qn = total / kXcds, rem = total % kXcds;
-        const int w = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + slot;
-        int tile = w / per_tile;
+        const int w = xcd_item(block, total);
+        int tile = idiv(w, per_tile);
         const int rest = w - tile * per_tile;
-        proj = rest / n_col; col = rest - proj * n_col;
+        proj = idiv(rest, n_col); col = rest - proj * n_col;
         int sub = 0;
         if (p.part == kPfTail) { sub = (tile % SUB) * C::TM; tile = first + tile / SUB; }
         if (a.n_new) {  // the sequence whose tiles include this one
@@ -355,7 +354,7 @@ __device__ __forceinline__ void prefill_tile(const PrefillArgs& a, int block, in
 #pragma unroll
     for (int nb = 0; nb < NBT; ++nb) {
         const int m = m0 + (wm * NBT + nb) * 32 + l32;
-        const int mc = min(m, m_end - 1), b = mc / a.n_tok, t = mc - b * a.n_tok;
+        const int mc = min(m, m_end - 1), b = (unsigned)mc / (unsigned)a.n_tok, t = mc - b * a.n_tok;
         const int row0 = a.seq_len[b];
         const long long row = (long long)row0 + t;
         const bool ok = m < m_end && row0 >= 0 && row < a.S_max;

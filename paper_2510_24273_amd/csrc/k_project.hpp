@@ -69,9 +69,9 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int sli
     constexpr int KS = 4 * VEC;  // elements of the D axis per MFMA step
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, kg = lane >> 4;
-    const int G = QUERY ? (unsigned)a.H / (unsigned)a.H_kv : 1;
+    const int G = QUERY ? idiv(a.H, a.H_kv) : 1;
     const int ncols = a.B * G, n_nblk = (ncols + 15) >> 4;
-    const int nks = (unsigned)a.D / KS / (unsigned)a.np;  // steps of this workgroup's slice
+    const int nks = idiv((unsigned)a.D / KS, a.np);  // steps of this workgroup's slice
     const int ks_first = slice * nks;
     const T* UT = static_cast<const T*>(a.UT[proj]);
     const T* X = static_cast<const T*>(a.X[proj]);
@@ -85,7 +85,7 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int sli
         const T* xrow[HB];
 #pragma unroll
         for (int h = 0; h < HB; ++h) {  // (columns past the last one repeat it)
-            const int n = min((nb0 + h) * 16 + l16, ncols - 1), b = (unsigned)n / (unsigned)G;
+            const int n = min((nb0 + h) * 16 + l16, ncols - 1), b = QUERY ? idiv(n, G) : n;
             xrow[h] = X + (QUERY ? ((size_t)b * a.H + n - b * G) * kHeadDim : (size_t)n * a.D) + kg * VEC;
         }
         f32x4v acc[HB];

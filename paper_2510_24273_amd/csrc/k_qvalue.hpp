@@ -60,8 +60,8 @@ __device__ __forceinline__ void qv_quantize_group(const QuantArgs& qa, const int
 {
     constexpr float kLevels = (float)((1 << BITS) - 1);
     constexpr int PER = 32 / BITS;  // codes per 32-bit word
-    const int n_groups = D / kQvGroup, l = threadIdx.x & 31;
-    const int b = group / n_groups, gi = group - b * n_groups;
+    const int n_groups = (unsigned)D / kQvGroup, l = threadIdx.x & 31;
+    const int b = idiv(group, n_groups), gi = group - b * n_groups;
     if (b >= B) return;
     const int row = seq_len[b];
     if (row < 0 || row >= S_max) return;
@@ -147,12 +147,11 @@ __global__ __launch_bounds__(256) void attend_qv_kernel(QvArgs a)
     int tr, kvh, b;
     {
         const int total = a.B * a.n_tr * a.H_kv;  // = gridDim.x
-        const int xcd = blockIdx.x % kXcds, sl = blockIdx.x / kXcds, qn = total / kXcds, rem = total % kXcds;
-        const int item = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + sl;
-        kvh = item % a.H_kv; tr = (item / a.H_kv) % a.n_tr; b = item / (a.H_kv * a.n_tr);
+        const int item = xcd_item(blockIdx.x, total), bt = idiv(item, a.H_kv);
+        kvh = item - bt * a.H_kv; b = idiv(bt, a.n_tr); tr = bt - b * a.n_tr;
     }
     const int tid = threadIdx.x;
-    const int H = a.H, G = H / a.H_kv;
+    const int H = a.H, G = idiv(H, a.H_kv);
     const int slot = tid / kQvTpt, u = tid % kQvTpt, c0 = u * kQvCh;
     const int32_t* ib = a.idx + (size_t)b * a.k_tot;
 

@@ -33,7 +33,7 @@ constexpr int kPvMaxTok = 4096;    // tokens per workgroup, at most (their cache
 template <typename T>
 __device__ __forceinline__ void warm_projector(const T* __restrict__ Uv, int r, int H_kv, int id, int n, int xcd, int n_threads)
 {
-    const int n_slots = n / kXcds, slot = id / kXcds;  // (n is a multiple of kXcds)
+    const int n_slots = (unsigned)n / kXcds, slot = (unsigned)id / kXcds;  // (n is a multiple of kXcds)
     const int per_head = kHeadDim * r * (int)sizeof(T) / 64;  // 64-byte pieces
     const int pieces = (H_kv - xcd + kXcds - 1) / kXcds * per_head;
     const unsigned char* base = reinterpret_cast<const unsigned char*>(Uv);
@@ -96,22 +96,21 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
     // Workgroup ids are dealt round-robin to the XCDs; the map below gives each XCD a contiguous run of
     // the list, so the column blocks of one token range (same indices, logits and statistics, adjacent
     // 128-byte pieces of the same cache rows) meet in one L2.
-    int n_cb = r / kPvCols, total = n_cb * n_tr * B, id = blockIdx.x;
+    int n_cb = (unsigned)r / kPvCols, total = n_cb * n_tr * B, id = blockIdx.x;
     if (id >= total) {  // (uniform)
         if constexpr (TWO) {
             id -= total;
             idx = second.idx; n_sel = second.n_sel; Vc = second.Vc; logits = second.logits; Tpart = second.Tpart;
             r = second.r; n_tr = second.n_tr; tok_per_wg = second.tok_per_wg; k_tot = second.k_tot; lk = second.lk;
             S_max = second.S_max; ring = second.ring;
-            n_cb = r / kPvCols; total = n_cb * n_tr * B;
+            n_cb = (unsigned)r / kPvCols; total = n_cb * n_tr * B;
         } else {
-            warm_projector<T>(Uv, r, H_kv, id - total, gridDim.x - total, id % kXcds, kPvThreads);
+            warm_projector<T>(Uv, r, H_kv, id - total, gridDim.x - total, (unsigned)id % kXcds, kPvThreads);
             return;
         }
     }
-    const int xcd = id % kXcds, slot = id / kXcds, qn = total / kXcds, rem = total % kXcds;
-    const int item = (xcd < rem ? xcd * (qn + 1) : rem * (qn + 1) + (xcd - rem) * qn) + slot;
-    const int trb = (unsigned)item / (unsigned)n_cb, cb = item - trb * n_cb, b = (unsigned)trb / (unsigned)n_tr, tr = trb - b * n_tr;
+    const int item = xcd_item(id, total);
+    const int trb = idiv(item, n_cb), cb = item - trb * n_cb, b = idiv(trb, n_tr), tr = trb - b * n_tr;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hi = lane >> 5;
     const int col0 = cb * kPvCols;
@@ -377,7 +376,7 @@ template <typename T, int BATCH, int RPR> struct OutPass {
     // the loaded batch, step by step, so that a step does not wait for the loads of the next
     template <bool FOLD> __device__ void steps(f32x4 (&s)[BATCH][VEC / 4], f32x4v& acc)
     {
-        const int R = 16 / q, used = min(n_tr, q) * R;  // lanes of a 16-lane row that hold ranges
+        const int R = 16 >> __builtin_ctz(q), used = min(n_tr, q) * R;  // lanes of a 16-lane row that hold ranges
 #pragma unroll
         for (int u = 0; u < BATCH; ++u) {
             if (ks0 + kOutWaves * u < nks) {  // uniform
@@ -464,11 +463,12 @@ __global__ __launch_bounds__(64 * kOutWaves) void attend_out_kernel(const T* __r
     const int g = blockIdx.x, cb = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, kg = lane >> 4;
-    const int G = H / H_kv;
+    const int G = idiv(H, H_kv);
     const int n_rows = B * G;  // (sequence, head of this group) pairs
     const int row0 = blockIdx.z * R;  // this workgroup's rows: R = 1, 2, 4, 8 or 16 of them
     const int row = min(row0 + (l16 & (R - 1)), n_rows - 1);  // (rows past the last one repeat it and are not stored)
-    const int bh = row / G * H + g * G + row % G, q = 16 / R, sub = l16 / R;
+    const int rb = idiv(row, G), bh = rb * H + g * G + row - rb * G;
+    const int lr = __builtin_ctz(R), q = 16 >> lr, sub = l16 >> lr;  // (R is a power of two)
     const size_t c0 = (size_t)g * kHeadDim + cb * 16;
 
     f32x4v acc = {0.f, 0.f, 0.f, 0.f};
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(64 * kOutWaves) void attend_out_kernel(const T* __r
 #pragma unroll
         for (int w = 1; w < NW; ++w) y += red[w][m][c];
         if (orow < n_rows) {
-            const int ob = orow / G, oh = g * G + orow % G;
+            const int ob = idiv(orow, G), oh = g * G + orow - ob * G;
             elem<T>::store(out + ((size_t)ob * H + oh) * kHeadDim + cb * 16 + c, y);
         }
     }
