@@ -126,6 +126,7 @@ struct QvArgs {
     const int32_t* n_lo;     // [B] tokens of the low-precision pass
     int lk_w, ring;
     int part0, n_tr_all;     // partial outputs: this launch writes ranges part0 .. of n_tr_all (n_tr_all == 1: straight to out)
+    int ksplit;              // kernels with SPLIT: `logits` are that many partial sums, [ksplit, B, H, lk]
 };
 
 constexpr int kQvTpt = kHeadDim / kQvCh;  // threads per token: 8
@@ -136,11 +137,17 @@ constexpr int kQvSlots = 256 / kQvTpt;    // tokens in progress side by side: 32
 // in slot order.  1-D grid of B * n_tr * H_kv workgroups; ids are dealt round-robin to the XCDs and
 // mapped so that each XCD gets a contiguous run of the work list (KV head fastest): the heads of a
 // token range read neighbouring pieces of the same cache rows and meet in one L2.
-template <typename T, int BITS, int GMAX, bool WIN = false>
+//
+// SPLIT (one range of at most kQvSplitTok tokens, no window): the logits are still partial sums over slices of the latent axis;
+// the workgroup adds up those of its query heads, once and for all, and takes maximum and normaliser from them.  A launch of its own
+// for that costs 1.5 to 2 us of a small step and the same bytes.
+constexpr int kQvSplitTok = 1024;
+template <typename T, int BITS, int GMAX, bool WIN = false, bool SPLIT = false>
 __global__ __launch_bounds__(256) void attend_qv_kernel(QvArgs a)
 {
     constexpr int UN = GMAX > 4 ? 4 : 8;  // tokens whose loads are in flight together, per thread
-    __shared__ int sRow[kQvMaxTok];
+    __shared__ int sRow[SPLIT ? kQvSplitTok : kQvMaxTok];
+    __shared__ __attribute__((aligned(16))) float sLg[SPLIT ? GMAX : 1][SPLIT ? kQvSplitTok : 4];
     __shared__ float2 sMZ[kMaxGroup];
     __shared__ __attribute__((aligned(16))) float red[256][kQvCh + 1];
 
@@ -160,9 +167,24 @@ __global__ __launch_bounds__(256) void attend_qv_kernel(QvArgs a)
     // and up to four token indices per thread.  (Whole 8-byte loads: a float2 load would be split and
     // its second half sunk behind the merge's early exit.)
     const int sm = tid >> 5, sub = tid & 31;
-    const float2* sp = a.stats + ((size_t)b * H + kvh * G + min(sm, G - 1)) * a.n_parts;
+    const size_t hrow = (size_t)b * H + kvh * G + min(sm, G - 1);
+    const float2* sp = a.stats + hrow * a.n_parts;
     constexpr unsigned long long kNeutral = 0x00000000ff800000ull;  // (-inf, 0)
-    const unsigned long long st0 = (sm < G && sub < a.n_parts) ? *reinterpret_cast<const unsigned long long*>(sp + sub) : kNeutral;
+    unsigned long long st0 = kNeutral;
+    constexpr int PU = 2;                     // SPLIT: groups of four tokens in flight
+    f32x4 pl[SPLIT ? PU : 1][SPLIT ? kLsMaxSplit : 1];
+    auto request_logits = [&](int j0) {       // groups j0, j0 + 1, ... of this lane: tokens 4 (sub + 32 j)
+#pragma unroll
+        for (int v = 0; v < kLsMaxSplit; ++v)
+            if (v < a.ksplit) {  // uniform
+#pragma unroll
+                for (int e = 0; e < PU; ++e)
+                    pl[SPLIT ? e : 0][SPLIT ? v : 0] = *reinterpret_cast<const f32x4*>(
+                        a.logits + ((size_t)v * a.B * H + hrow) * a.lk + min(4 * (sub + 32 * (j0 + e)), a.lk - 4));
+            }
+    };
+    if constexpr (SPLIT) request_logits(0);
+    else if (sm < G && sub < a.n_parts) st0 = *reinterpret_cast<const unsigned long long*>(sp + sub);
     const int n_v = ld_uniform_i32(a.n_sel + b);  // (vector memory path: in flight with the loads around)
     const int nlo_v = WIN ? ld_uniform_i32(a.n_lo + b) : 0;
     int iv[4];
@@ -190,8 +212,40 @@ __global__ __launch_bounds__(256) void attend_qv_kernel(QvArgs a)
         sRow[t] = row_of(t, ib[tr * a.tok_per_wg + t]);
     {   // softmax maximum and normaliser per query head: the head's tile statistics merged in a fixed order
         float2 st = make_float2(__uint_as_float((uint32_t)st0), __uint_as_float((uint32_t)(st0 >> 32)));
-        if (sm < G)
+        if constexpr (SPLIT) {
+            for (int j0 = 0;; j0 += PU) {
+                f32x4 d[PU];
+                float m = -INFINITY, z = 0.f;
+#pragma unroll
+                for (int e = 0; e < PU; ++e) d[e] = pl[e][0];
+#pragma unroll
+                for (int v = 1; v < kLsMaxSplit; ++v)  // (in slice order)
+                    if (v < a.ksplit) {  // uniform
+#pragma unroll
+                        for (int e = 0; e < PU; ++e) d[e] += pl[e][SPLIT ? v : 0];
+                    }
+#pragma unroll
+                for (int e = 0; e < PU; ++e) {
+                    const int t = 4 * (sub + 32 * (j0 + e));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        d[e][i] = t + i < n ? d[e][i] : -INFINITY;
+                        m = fmaxf(m, d[e][i]);
+                    }
+                    if (sm < G && t < a.k_tot) *reinterpret_cast<f32x4*>(&sLg[SPLIT ? sm : 0][SPLIT ? t : 0]) = d[e];
+                }
+                const float ref = m > -INFINITY ? m : 0.f;
+#pragma unroll
+                for (int e = 0; e < PU; ++e)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) z += d[e][i] > -INFINITY ? __expf(d[e][i] - ref) : 0.f;
+                st = stat_merge(st, make_float2(m, z));
+                if (128 * (j0 + PU) >= a.k_tot) break;  // uniform
+                request_logits(j0 + PU);
+            }
+        } else if (sm < G) {
             for (int t0 = sub + 32; t0 < a.n_parts; t0 += 32) st = stat_merge(st, sp[t0]);
+        }
 #pragma unroll
         for (int o = 1; o < 32; o <<= 1)
             st = stat_merge(st, make_float2(__shfl_xor(st.x, o, kWave), __shfl_xor(st.y, o, kWave)));
@@ -241,7 +295,8 @@ __global__ __launch_bounds__(256) void attend_qv_kernel(QvArgs a)
                 }
                 sz[i] = qv_meta<T>::load(vm + row * n_groups * 2);
 #pragma unroll
-                for (int m = 0; m < GMAX; ++m) x[i][m] = (m < G && t < t_hi) ? lgp[(size_t)m * lk + (tc - t_lo)] : -INFINITY;
+                for (int m = 0; m < GMAX; ++m)
+                    x[i][m] = (m < G && t < t_hi) ? (SPLIT ? sLg[SPLIT ? m : 0][SPLIT ? tc : 0] : lgp[(size_t)m * lk + (tc - t_lo)]) : -INFINITY;
             }
 #pragma unroll
             for (int i = 0; i < UN; ++i) {

@@ -71,12 +71,19 @@ template <typename T> struct PvSecond {
     const int32_t* idx; const int32_t* n_sel; const T* Vc; const float* logits; float* Tpart;
     int r, n_tr, tok_per_wg, k_tot, lk, S_max, ring;
 };
-template <typename T, int NW, int MB, bool TWO>
-__global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
+//
+// SPLIT: the logits are still partial sums over slices of the latent axis (`ksplit` of them).  Every workgroup adds up all of its
+// sequence's (a thread has four tokens of a head at a time, all slices requested together), keeps its range's in LDS and
+// takes maxima and normalisers on the way, under the gathered rows: the launch that would add them up before costs 5 us of a small step
+// and moves the same bytes, from L2, once.
+constexpr int kPvSplitTok = 128;                // tokens of a range, at most
+constexpr size_t kPvSplitBytes = 128 << 10;     // partial logits of a sequence, at most (a workgroup reads them all)
+template <typename T, int NW, int MB, bool TWO, bool SPLIT>
+__device__ __forceinline__ void pv_block(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ n_sel, const float2* __restrict__ stats,
     int B, int r, int n_tr, int n_parts, int tok_per_wg, int k_tot, int H, int lk,
     const T* __restrict__ Vc, const float* __restrict__ logits, float* __restrict__ Tpart, int S_max, int ring,
-    const T* __restrict__ Uv, int H_kv, PvSecond<T> second)
+    const T* __restrict__ Uv, int H_kv, PvSecond<T> second, int ksplit)
 {
     static_assert((NW == 4 || NW == 8) && (MB == 1 || MB == 2), "four or eight waves, one or two head blocks");
     constexpr int kPvThreads = NW * 64;
@@ -87,7 +94,9 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
     constexpr int DEPTH = NW == 8 && kSplit ? 1 : 2;
     constexpr int ND = 8;                    // gathered words per lane and group: 8 tokens (bf16) | 4 tokens x 2 column blocks (fp32)
 
-    __shared__ __attribute__((aligned(16))) int sRow[kPvMaxTok];  // cache row of every token of the nominal range
+    __shared__ __attribute__((aligned(16))) int sRow[SPLIT ? kPvSplitTok : kPvMaxTok];  // cache row of every token of the nominal range
+    constexpr int kLgRow = kPvSplitTok + 4;  // (16 heads' 16 bytes lie in different banks)
+    __shared__ __attribute__((aligned(16))) float sLg[SPLIT ? MB * 32 : 1][SPLIT ? kLgRow : 4];  // the range's logits
     __shared__ float2 sMZ[kPvMaxHeads];      // per head: softmax maximum, 1 / normaliser
     constexpr int NBR = NW == 4 ? 2 : 1;     // column blocks per pass of the cross-wave sums
     __shared__ float red[NBR][NW][64][17];   // cross-wave sums, after the loop
@@ -119,16 +128,36 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
 
     // everything that depends on nothing is requested at once: the count, the range's indices, the tile statistics
     const int n_v = ld_uniform_i32(n_sel + b);
-    for (int t = tid; t < tok_per_wg; t += kPvThreads) {
-        const int j = tr * tok_per_wg + t;
-        const int v = ib[min(j, k_tot - 1)];
-        const int pos = min(max(v, 0), S_max - 1);
-        sRow[t] = ring > 0 ? (unsigned)pos % (unsigned)ring : pos;  // ring cache: token t lies in row t mod ring
-    }
-    constexpr int LPH = kPvThreads / kPvMaxHeads;   // lanes that share a head's tiles
+    constexpr int LPH = kPvThreads / (SPLIT ? MB * 32 : kPvMaxHeads);   // lanes that share a head's tiles (SPLIT: tokens)
     const int sh = tid / LPH, sub = tid % LPH;
     float2 st8[8];
-    {
+    constexpr int PU = 4;                     // SPLIT: groups of four tokens in flight
+    f32x4 pl[SPLIT ? PU : 1][SPLIT ? kLsMaxSplit : 1];
+    auto request_logits = [&](int j0) {       // groups j0, j0 + 1, ... of this lane: tokens 4 (sub + LPH j)
+        const float* p[PU];
+#pragma unroll
+        for (int e = 0; e < PU; ++e)
+            p[e] = logits + ((size_t)b * H + min(sh, H - 1)) * lk + min(4 * (sub + LPH * (j0 + e)), lk - 4);
+#pragma unroll
+        for (int u = 0; u < kLsMaxSplit; ++u)
+            if (u < ksplit) {  // uniform
+#pragma unroll
+                for (int e = 0; e < PU; ++e)
+                    pl[SPLIT ? e : 0][SPLIT ? u : 0] = *reinterpret_cast<const f32x4*>(p[e] + (size_t)u * B * H * lk);
+            }
+    };
+    if constexpr (SPLIT) {
+        const int v = ib[min(tr * tok_per_wg + min(tid, tok_per_wg - 1), k_tot - 1)];
+        request_logits(0);
+        const int pos = min(max(v, 0), S_max - 1);
+        if (tid < tok_per_wg) sRow[tid] = ring > 0 ? (unsigned)pos % (unsigned)ring : pos;
+    } else {
+        for (int t = tid; t < tok_per_wg; t += kPvThreads) {
+            const int j = tr * tok_per_wg + t;
+            const int v = ib[min(j, k_tot - 1)];
+            const int pos = min(max(v, 0), S_max - 1);
+            sRow[t] = ring > 0 ? (unsigned)pos % (unsigned)ring : pos;  // ring cache: token t lies in row t mod ring
+        }
         const float2* sp = stats + ((size_t)b * H + min(sh, H - 1)) * n_parts;
 #pragma unroll
         for (int u = 0; u < 8; ++u) st8[u] = sp[min(sub + LPH * u, n_parts - 1)];  // (clamped: no load in a branch)
@@ -157,6 +186,7 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
         }
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
+            if constexpr (SPLIT) break;
             const int h = min(mb * 32 + l32, H - 1);  // (rows past the last head: any head's logits, never stored)
             const size_t off = (size_t)h * lk + tr * tok_per_wg + t0;
 #pragma unroll
@@ -168,7 +198,43 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
     for (int u = 0; u < DEPTH; ++u) g_load(S[u], wave + NW * u);  // (the count is not known yet: nominal groups)
 
     // softmax maximum and normaliser of every head, merged in a fixed order (under the loads above)
-    {
+    if constexpr (SPLIT) {
+        const int n = n_v, r0 = tr * tok_per_wg;
+        float2 st = make_float2(-INFINITY, 0.f);
+        auto take = [&](int j0) {
+            f32x4 d[PU];
+            float m = -INFINITY, z = 0.f;
+#pragma unroll
+            for (int e = 0; e < PU; ++e) d[e] = pl[e][0];
+#pragma unroll
+            for (int u = 1; u < kLsMaxSplit; ++u)  // (in slice order)
+                if (u < ksplit) {  // uniform
+#pragma unroll
+                    for (int e = 0; e < PU; ++e) d[e] += pl[SPLIT ? e : 0][SPLIT ? u : 0];
+                }
+#pragma unroll
+            for (int e = 0; e < PU; ++e) {
+                const int t = 4 * (sub + LPH * (j0 + e));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    d[e][i] = t + i < n ? d[e][i] : -INFINITY;
+                    m = fmaxf(m, d[e][i]);
+                }
+                if (t >= r0 && t < r0 + tok_per_wg) *reinterpret_cast<f32x4*>(&sLg[sh][t - r0]) = d[e];
+            }
+            const float ref = m > -INFINITY ? m : 0.f;
+#pragma unroll
+            for (int e = 0; e < PU; ++e)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) z += d[e][i] > -INFINITY ? __expf(d[e][i] - ref) : 0.f;
+            st = stat_merge(st, make_float2(m, z));
+        };
+        take(0);
+        for (int j0 = PU; 4 * LPH * j0 < k_tot; j0 += PU) { request_logits(j0); take(j0); }
+#pragma unroll
+        for (int o = 1; o < LPH; o <<= 1) st = stat_merge(st, make_float2(__shfl_xor(st.x, o, kWave), __shfl_xor(st.y, o, kWave)));
+        if (sub == 0) sMZ[sh] = make_float2(st.x > -INFINITY ? st.x : 0.f, st.y > 0.f ? 1.f / st.y : 0.f);
+    } else {
         // (eight at a time: the maximum first, then eight exponentials that do not wait for each other)
         auto merge8 = [&](float2* e, int t0) {
             float m = -INFINITY, z = 0.f;
@@ -237,7 +303,7 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
             float pj[VEC];
 #pragma unroll
             for (int v = 0; v < VEC; v += 4) {
-                const f32x4 x = S.X[mb][v / 4];
+                const f32x4 x = SPLIT ? *reinterpret_cast<const f32x4*>(&sLg[SPLIT ? mb * 32 + l32 : 0][SPLIT ? t0 + v : 0]) : S.X[mb][v / 4];
                 // slots past the range carry no weight (their logits may be unwritten)
                 const int jt = t0 + v;
                 pj[v] = jt < ntok ? __expf(x.x - mz[mb].x) * mz[mb].y : 0.f;
@@ -304,6 +370,26 @@ __global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
                 }
             }
         }
+}
+
+template <typename T, int NW, int MB, bool TWO>
+__global__ __launch_bounds__(NW * 64) void attend_pv_kernel(
+    const int32_t* __restrict__ idx, const int32_t* __restrict__ n_sel, const float2* __restrict__ stats,
+    int B, int r, int n_tr, int n_parts, int tok_per_wg, int k_tot, int H, int lk,
+    const T* __restrict__ Vc, const float* __restrict__ logits, float* __restrict__ Tpart, int S_max, int ring,
+    const T* __restrict__ Uv, int H_kv, PvSecond<T> second)
+{
+    pv_block<T, NW, MB, TWO, false>(idx, n_sel, stats, B, r, n_tr, n_parts, tok_per_wg, k_tot, H, lk, Vc, logits, Tpart, S_max, ring, Uv,
+                                    H_kv, second, 1);
+}
+template <typename T, int NW, int MB>
+__global__ __launch_bounds__(NW * 64) void attend_pv_split_kernel(
+    const int32_t* __restrict__ idx, const int32_t* __restrict__ n_sel, const float* __restrict__ plogits,
+    int B, int r, int n_tr, int ksplit, int tok_per_wg, int k_tot, int H, int lk,
+    const T* __restrict__ Vc, float* __restrict__ Tpart, int S_max, int ring, const T* __restrict__ Uv, int H_kv)
+{
+    pv_block<T, NW, MB, false, true>(idx, n_sel, nullptr, B, r, n_tr, 1, tok_per_wg, k_tot, H, lk, Vc, plogits, Tpart, S_max, ring, Uv,
+                                     H_kv, PvSecond<T>{}, ksplit);
 }
 
 // ---------------------------------------------------------------------------------

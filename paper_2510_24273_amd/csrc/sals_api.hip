@@ -801,11 +801,25 @@ SplitLogits split_logits(const sals_ctx* c, int ksplit, const int32_t* n_sel, fl
                        ksplit, c->plan.n_parts, c->d.B * c->d.H_q, c->d.H_q, c->L.lk, stats_stride};
 }
 
+// Split logits that the value kernel adds up itself, in LDS: quantised values if their kernel has one range (a workgroup then reads
+// its heads' partial sums and no others), latent ones as far as a workgroup may read a whole sequence's (see pv_block).  Whole steps
+// with the launch that adds them up -> without, one sequence unless said: 32 KV heads, 128 tokens 25.6 -> 23.8 us, 2 x 128 26.9 ->
+// 25.0, 3 x 128 of 8 KV heads 27.5 -> 25.9, fp32 256 tokens 41.7 -> 40.7; past the line, 8 KV heads, 512 tokens (256 KB) 26.8 -> 28.6.
+// 4-bit values, 32 KV heads, 256 tokens 30.7 -> 29.2, 8 KV heads, 512 tokens 30.1 -> 28.7, 1000 tokens 40.3 -> 40.1.
+bool value_adds_slices(const sals_ctx* c, int ksplit, bool quantised)
+{
+    const sals_desc& d = c->d;
+    const size_t k_tot = (size_t)d.top_k + d.n_sink + d.n_recent;
+    if (ksplit <= 1) return false;
+    if (quantised) return c->L.qv_ntr == 1 && k_tot <= kQvSplitTok;
+    return c->L.pv_tok_per_wg <= kPvSplitTok && d.H_q * k_tot * ksplit * 4 <= kPvSplitBytes;
+}
+
 // Value sum over the selected tokens of a cache, and of a second one under the same softmax (the recent window).
 struct PvPass { const sals_ctx* c; const int32_t* idx; const int32_t* n_sel; const void* Vc; int ring; };
 template <typename T>
 void launch_pv(const sals_ctx* c, const float2* stats, int stats_stride, const PvPass& a, const PvPass* b, const T* Uv,
-               hipStream_t st)
+               hipStream_t st, int ksplit = 1)  // > 1: the logits of `a` (alone) are still that many partial sums
 {
     const sals_desc& d = c->d;
     ProfScope ps(c, SALS_K_ATTEND_PV, st);
@@ -829,8 +843,17 @@ void launch_pv(const sals_ctx* c, const float2* stats, int stats_stride, const P
                        f.n_sel, stats, d.B, f.r, f.n_tr, stats_stride, f.tok_per_wg, f.k_tot, d.H_q, f.lk, f.Vc, f.logits, \
                        f.Tpart, f.S_max, f.ring, Uv, d.H_kv, g)
 #define SALS_PV_B(NW, MB) do { if (b) SALS_PV(NW, MB, true); else SALS_PV(NW, MB, false); } while (0)
-    if (d.H_q <= 32) { if (w8) SALS_PV_B(8, 1); else SALS_PV_B(4, 1); }
+#define SALS_PV_S(NW, MB)                                                                                                 \
+    hipLaunchKernelGGL((attend_pv_split_kernel<T, NW, MB>), dim3(n_items + n_more), dim3(NW * 64), 0, st, f.idx, f.n_sel,  \
+                       reinterpret_cast<const float*>(c->ws + c->L.plogits), d.B, f.r, f.n_tr, ksplit, f.tok_per_wg, f.k_tot, \
+                       d.H_q, f.lk, f.Vc, f.Tpart, f.S_max, f.ring, Uv, d.H_kv)
+    if (ksplit > 1) {
+        if (d.H_q <= 32) { if (w8) SALS_PV_S(8, 1); else SALS_PV_S(4, 1); }
+        else { if (w8) SALS_PV_S(8, 2); else SALS_PV_S(4, 2); }
+    }
+    else if (d.H_q <= 32) { if (w8) SALS_PV_B(8, 1); else SALS_PV_B(4, 1); }
     else { if (w8) SALS_PV_B(8, 2); else SALS_PV_B(4, 2); }
+#undef SALS_PV_S
 #undef SALS_PV_B
 #undef SALS_PV
 }
@@ -873,6 +896,7 @@ sals_status launch_attend(const sals_ctx* c, const void* q, const int32_t* q_pos
         P.ksplit = window_slices(c);
         if (P.pick == 3) P.nst = steps_ahead<T>(d, P.ksplit);
     }
+    const bool value_adds = phases == kPhaseAll && link == nullptr && (!qv || !qv->codes_w) && value_adds_slices(c, P.ksplit, qv != nullptr);
     // tile statistics: written by this pass's logits kernel from record `part0` on, read as a whole by the value kernel
     float2* const stats_all = link ? link->stats : reinterpret_cast<float2*>(c->ws + L.stats);
     float2* const stats = stats_all + (link ? link->part0 : 0);
@@ -932,7 +956,7 @@ sals_status launch_attend(const sals_ctx* c, const void* q, const int32_t* q_pos
             }
 #undef SALS_LS_ARGS
         }
-        if (P.ksplit > 1) {
+        if (P.ksplit > 1 && !value_adds) {
             if (launch_status() != SALS_OK) return SALS_ERR_HIP;
             hipLaunchKernelGGL(logits_finish_kernel, dim3(n_parts, d.B * d.H_q), dim3(64), 0, st,
                                split_logits(c, P.ksplit, n_sel, stats, stats_stride));
@@ -949,13 +973,15 @@ sals_status launch_attend(const sals_ctx* c, const void* q, const int32_t* q_pos
         a.n_parts = stats_stride; a.B = d.B; a.S_max = d.S_max; a.H = d.H_q; a.H_kv = d.H_kv; a.k_tot = k_tot; a.lk = L.lk;
         a.tok_per_wg = L.qv_tok_per_wg; a.n_tr = L.qv_ntr; a.part0 = 0; a.n_tr_all = L.qv_ntr;
         a.Vq_w = static_cast<const unsigned char*>(qv->codes_w); a.Vmeta_w = qv->meta_w; a.logits_w = qv->logits_w;
-        a.n_lo = qv->n_lo; a.lk_w = qv->lk_w; a.ring = qv->ring;
+        a.n_lo = qv->n_lo; a.lk_w = qv->lk_w; a.ring = qv->ring; a.ksplit = P.ksplit;
+        if (value_adds) a.logits = reinterpret_cast<const float*>(c->ws + L.plogits);
         const bool win = qv->codes_w != nullptr;
         const dim3 grid(L.qv_ntr * d.H_kv * d.B);
         const int G = d.H_q / d.H_kv;
 #define SALS_QV(BITS, GMAX)                                                                             \
     do {                                                                                                \
         if (win) hipLaunchKernelGGL((attend_qv_kernel<T, BITS, GMAX, true>), grid, dim3(256), 0, st, a); \
+        else if (value_adds) hipLaunchKernelGGL((attend_qv_kernel<T, BITS, GMAX, false, true>), grid, dim3(256), 0, st, a); \
         else hipLaunchKernelGGL((attend_qv_kernel<T, BITS, GMAX, false>), grid, dim3(256), 0, st, a);   \
     } while (0)
 #define SALS_QV_G(BITS)                                                                                 \
@@ -975,7 +1001,8 @@ sals_status launch_attend(const sals_ctx* c, const void* q, const int32_t* q_pos
         return launch_status();
     }
     if (phases & kPhaseValue)
-        launch_pv<T>(c, stats_all, stats_stride, PvPass{c, idx, n_sel, Vc, ring}, nullptr, w_section<T>(c, W, 3), st);
+        launch_pv<T>(c, stats_all, stats_stride, PvPass{c, idx, n_sel, Vc, ring}, nullptr, w_section<T>(c, W, 3), st,
+                     value_adds ? P.ksplit : 1);
     if (launch_status() != SALS_OK) return SALS_ERR_HIP;
     if (phases & kPhaseOut) {
         ProfScope ps(c, SALS_K_ATTEND_OUT, st);

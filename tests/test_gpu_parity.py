@@ -445,6 +445,31 @@ def test_projections_in_column_blocks(oracle, dtype, H, H_kv, r, B):
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype,H,H_kv,r,top_k,lens", [
+    ("bf16", 32, 32, 192, 3, [500, 2]),             # less than one group of four tokens
+    ("bf16", 32, 32, 192, 64, [500]),
+    ("bf16", 32, 32, 192, 65, [500, 64, 0]),        # two tiles, ranges past the selection
+    ("bf16", 32, 32, 640, 129, [500]),              # two ranges, the last tile of one token
+    ("bf16", 32, 32, 640, 250, [500]),              # two rounds of loads
+    ("bf16", 32, 8, 256, 255, [500, 131]),          # a workgroup's limit (eight slices would pass it: added up beforehand)
+    ("bf16", 64, 64, 256, 100, [300]),              # two head blocks, rounds of 64 tokens
+    ("bf16", 24, 3, 128, 77, [300, 299, 5]),        # heads that do not fill a block
+    ("f32", 32, 32, 192, 128, [500]),               # ranges of one step
+    ("f32", 32, 32, 128, 200, [500]),
+    ("f32", 64, 8, 128, 61, [300, 60])])
+def test_value_sum_adds_logit_slices(oracle, dtype, H, H_kv, r, top_k, lens, monkeypatch):
+    """Split logits that the value sum adds up: against the oracle, and against the unsplit logits within twice the bound that
+    both keep to it."""
+    w = synth.shrink(SMALL, B=len(lens), S=max(lens), r=r, H=H, H_kv=H_kv, top_k=top_k, plant=0, dtype=dtype)
+    L, R, _ = _run(oracle, w, seq_lens=lens, label=f"added slices {dtype} H={H}/{H_kv} r={r} k={top_k}")
+    monkeypatch.setenv("SALS_TUNE_LOGITS_KSPLIT", "0")
+    _, R1, _ = _run(oracle, w, seq_lens=lens, label="unsplit")
+    assert torch.equal(R["idx"], R1["idx"])
+    y, y1 = gu.from_dev(R["out"]), gu.from_dev(R1["out"])
+    for b in range(w.B):
+        assert np.max(np.abs(y[b] - y1[b])) <= 2 * gu.out_tolerances(w, y1[b])[1]
+
+
 def test_query_position_beyond_the_cache(oracle):
     """q_pos far above S_max: the query's angles are then evaluated in the kernel instead of
     being read from the per-context cos/sin table."""

@@ -82,6 +82,19 @@ def test_gqa_groups(oracle, H_kv, H):
     _attend_case(oracle, synth.shrink(SMALL, B=2, S=600, H=H, H_kv=H_kv, plant=0), 4, seq_lens=[600, 333])
 
 
+@pytest.mark.parametrize("dtype,H,H_kv,r,top_k,lens,bits", [
+    ("bf16", 32, 32, 192, 3, [500, 2], 2),          # less than one group of four tokens
+    ("bf16", 32, 32, 640, 129, [500, 128, 0], 4),   # the last tile of one token
+    ("bf16", 32, 32, 640, 250, [500], 2),
+    ("bf16", 32, 8, 256, 600, [900], 4),            # three rounds of loads
+    ("bf16", 8, 1, 128, 1024, [1500, 1000], 2),     # the longest range that holds its logits, eight heads
+    ("bf16", 8, 1, 128, 1025, [1500], 2),           # one token more: added up beforehand
+    ("f32", 64, 32, 128, 61, [300, 60], 4)])
+def test_split_logits_added_by_the_value_kernel(oracle, dtype, H, H_kv, r, top_k, lens, bits):
+    w = synth.shrink(SMALL, B=len(lens), S=max(lens), r=r, H=H, H_kv=H_kv, top_k=top_k, plant=0, dtype=dtype)
+    _attend_case(oracle, w, bits, seq_lens=lens)
+
+
 def test_many_token_ranges_and_window(oracle):
     w = synth.shrink(SMALL, B=1, S=3000, top_k=700, n_sink=4, n_recent=33, plant=0)
     _attend_case(oracle, w, 2)
