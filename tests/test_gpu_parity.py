@@ -286,6 +286,40 @@ def test_selection_random_shapes(oracle):
         ctx.close()
 
 
+@pytest.mark.parametrize("S,n_thr", [(4093, 1024), (4096, 1024), (9001, 1024), (32768, 1024)])
+@pytest.mark.parametrize("members", [1, 2, 31, 32, 33, 64, 512, 513])
+def test_threshold_bin_sizes(oracle, S, n_thr, members):
+    """The cut lies in a bin of `members` scores (half of them pairwise equal), at its first, a middle and its last one: the set is
+    the oracle's, and above the threshold and at it the list has the order of the threads and of their groups of four."""
+    rng = np.random.default_rng(members * 7 + S)
+    sc = np.concatenate([rng.uniform(0.0, 0.4, S), [0.0, 1.0]])[-S:].astype(np.float32)
+    at = rng.permutation(S - 2)
+    n_above = 40
+    sc[at[:n_above]] = rng.uniform(0.8, 0.9, n_above)
+    inside = 0.6 + np.arange(members) * 1e-7   # (a bin is 2.4e-4 wide; 2460 / 4096 = 0.60059 is the nearest edge)
+    inside[1::4] = inside[0::4][: len(inside[1::4])]
+    sc[at[n_above:n_above + members]] = inside
+    token = np.arange(S)
+    place = np.argsort((token // 4 % n_thr) * S + token, kind="stable")   # thread, group, element
+    rank = np.empty(S, np.int64)
+    rank[place] = np.arange(S)
+    for k_in in sorted({1, (members + 1) // 2, members}):
+        top_k = 1 + n_above + k_in             # (the largest score is the range's end)
+        w = synth.shrink(SMALL, B=1, S=S, top_k=top_k, n_sink=0, n_recent=0, plant=0)
+        ctx = gu.make_ctx(w)
+        idx = torch.full((1, top_k), -7, dtype=torch.int32, device=gu.DEV)
+        n = torch.full((1,), -7, dtype=torch.int32, device=gu.DEV)
+        ctx.topk_select(torch.from_numpy(sc[None]).to(gu.DEV), torch.tensor([S], dtype=torch.int32, device=gu.DEV), idx, n)
+        torch.cuda.synchronize()
+        ctx.close()
+        got = idx[0].cpu().numpy()
+        want = np.sort(oracle.topk(sc.astype(np.float64), top_k, 0, 0))
+        assert np.array_equal(np.sort(got), want), (members, k_in)
+        tau = sc[want].min()
+        gt, eq = want[sc[want] > tau], want[sc[want] == tau]
+        assert got.tolist() == gt[np.argsort(rank[gt])].tolist() + eq[np.argsort(rank[eq])].tolist(), (members, k_in)
+
+
 def test_decode_random_shapes(oracle):
     """Seeded sweep over descriptors: ranks, head layouts, batch sizes, budgets, windows, both storage types
     and both RoPE pairings; every stage of every sequence against the oracle."""
