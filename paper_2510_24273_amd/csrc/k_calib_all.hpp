@@ -128,6 +128,119 @@ __device__ __forceinline__ void calib_product(const TA* A, const TB* B, int D, F
     }
 }
 
+// The symmetric A A^T, each pair of elements once: below the diagonal in halves of tiles, 64 rows x 32 columns, on the diagonal whole
+// tiles less their upper 16 x 16 blocks, 10 blocks instead of 8.  (D / 64)^2 workgroups, so one for every compute unit at D = 1024 as
+// with whole tiles, each with half of the work.  A step is 256 bytes of a row; the eight waves are two groups of blocks x four parts of a
+// step's contraction.  Piece p of row r lies at piece p ^ (r & 15): no bank conflicts.
+// Bound by the matrix cores.  Against whole tiles of the full product, with what is done to the result, D = 1024: fp64 products and
+// the rows' shares 42.5 -> 28.6 us, defect 39.9 -> 27.5, angles 46 -> 30, fp32 21.8 -> 15.4; a call 5.15 -> 4.78 ms (with the launch of
+// the angles below), D = 2048 24.4 -> 21.6 ms.  (Products of pairs are bound by what a compute unit draws and stay whole.)
+// finish(rb, cb, v, both): 16 x 16 block (rb, cb) of the tile, element e of a lane at row 16 rb + mma_tile::row(lane / 16, e), column 16 cb +
+// lane % 16; both: the mirrored elements are this workgroup's too (not so for blocks on the diagonal, which come whole).
+constexpr size_t kSymLds = (size_t)kProdStages * 24576;
+struct SymTile { int row, col, half; __device__ __forceinline__ bool diag() const { return row == col; } };   // in tiles of 64
+__device__ __forceinline__ SymTile sym_tile(int block, int D)
+{
+    const int nb = (unsigned)D / 64, w = xcd_item(block, nb * nb);
+    if (w < nb) return SymTile{w, w, 0};
+    const int t = (w - nb) >> 1;
+    int r = (int)((1.f + sqrtf(1.f + 8.f * (float)t)) * 0.5f);   // t = r (r - 1) / 2 + column
+    while (r * (r - 1) / 2 > t) --r;
+    while (r * (r + 1) / 2 <= t) ++r;
+    return SymTile{r, t - r * (r - 1) / 2, (w - nb) & 1};
+}
+template <typename TA, typename ACC, typename Finish>
+__device__ __forceinline__ void calib_product_sym(const TA* A, int D, const SymTile& tile, Finish finish)
+{
+    constexpr int KS = 256 / (int)sizeof(TA), EPV = 16 / (int)sizeof(TA), STAGE = 24576, ST = kProdStages;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];   // per stage: 64 rows | 32 rows
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kg = lane >> 4;
+    const int part = wave & 1, ks = wave >> 1;
+    const uint32_t lds0 = lds_offset(lds);
+    const size_t row_bytes = (size_t)D * sizeof(TA);
+    auto at = [](int row, int pc) { return row * 256 + ((pc ^ (row & 15)) << 4); };
+    const int prow = wave * 4 + kg;
+    const uint32_t off = (uint32_t)prow * (uint32_t)row_bytes + (uint32_t)((l16 ^ (prow & 15)) << 4);
+    const unsigned char* a = reinterpret_cast<const unsigned char*>(A) + (size_t)tile.row * 64 * row_bytes;
+    const unsigned char* b = reinterpret_cast<const unsigned char*>(A) + ((size_t)tile.col * 64 + tile.half * 32) * row_bytes;
+    const int n = D / KS;   // (at least 4)
+    auto load = [&](int s) {
+        const size_t k = (size_t)min(s, n - 1) * 256;   // (past the end: a step that nothing reads any more)
+        const uint32_t st = lds0 + (uint32_t)(s % ST) * STAGE + wave * 1024;
+        load_lds16(a + k, off, st);
+        load_lds16(a + 32 * row_bytes + k, off, st + 8192);
+        load_lds16(b + k, off, st + 16384);   // (on the diagonal nothing reads it)
+    };
+#pragma unroll
+    for (int s = 0; s < ST - 1; ++s) load(s);
+    typename mma_tile<ACC>::acc acc[5];
+#pragma unroll
+    for (int i = 0; i < 5; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i][e] = 0;
+    typedef TA VA __attribute__((ext_vector_type(EPV)));
+    auto run = [&](auto diag) {
+        constexpr bool DG = decltype(diag)::value;
+        for (int s = 0; s < n; ++s) {
+            vm_wait<(ST - 2) * 3>();   // step s has landed, everywhere; every wave is done with step s - 1
+            wg_barrier();
+            load(s + ST - 1);
+            const unsigned char* st = lds + (s % ST) * STAGE;
+            auto rows = [&](int block) { return *reinterpret_cast<const VA*>(st + at(block * 16 + l16, ks * 4 + kg)); };
+            const VA x0 = rows(2 * part), x1 = rows(2 * part + 1);
+            if (DG) {   // blocks 2 part .. against themselves, block 2 + part against the first two
+                const VA x2 = rows(2 + part), y0 = rows(0), y1 = rows(1);
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) {
+                    acc[0] = mma_step((ACC)x0[e], (ACC)x0[e], acc[0]);
+                    acc[1] = mma_step((ACC)x1[e], (ACC)x0[e], acc[1]);
+                    acc[2] = mma_step((ACC)x1[e], (ACC)x1[e], acc[2]);
+                    acc[3] = mma_step((ACC)x2[e], (ACC)y0[e], acc[3]);
+                    acc[4] = mma_step((ACC)x2[e], (ACC)y1[e], acc[4]);
+                }
+            } else {
+                const VA y0 = rows(4), y1 = rows(5);
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) {
+                    acc[0] = mma_step((ACC)x0[e], (ACC)y0[e], acc[0]);
+                    acc[1] = mma_step((ACC)x1[e], (ACC)y0[e], acc[1]);
+                    acc[2] = mma_step((ACC)x0[e], (ACC)y1[e], acc[2]);
+                    acc[3] = mma_step((ACC)x1[e], (ACC)y1[e], acc[3]);
+                }
+            }
+        }
+    };
+    const bool dg = tile.diag();   // uniform
+    if (dg) run(std::true_type{}); else run(std::false_type{});
+    vm_wait<0>();
+    wg_barrier();
+    // the four parts of the contraction: part b % 4 finishes block b
+    ACC* red = reinterpret_cast<ACC*>(lds) + part * (5 * 4 * 256);
+#pragma unroll
+    for (int i = 0; i < 5; ++i)
+        if ((i & 3) != ks) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) red[((i * 4 + ks) * 4 + e) * 64 + lane] = acc[i][e];
+        }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+        if ((i & 3) == ks && (i < 4 || dg)) {   // uniform
+            typename mma_tile<ACC>::acc v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                ACC sum = 0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) sum += k == (i & 3) ? acc[i][e] : red[((i * 4 + k) * 4 + e) * 64 + lane];
+                v[e] = sum;
+            }
+            if (!dg) finish(2 * part + (i & 1), i >> 1, v, true);
+            else if (i < 3) finish(2 * part + (i + 1) / 2, 2 * part + i / 2, v, i == 1);
+            else finish(2 + part, i - 3, v, true);
+        }
+    }
+}
+
 // Matrices of floats as pairs of bf16, x = hi + lo to 2^-17: one 32-bit word an element, hi in the upper half.
 __device__ __forceinline__ uint32_t pack_pair(float x)
 {
@@ -235,27 +348,37 @@ __global__ __launch_bounds__(kProdThreads) void calib_apply_kernel(const TA* A, 
 __global__ __launch_bounds__(kProdThreads) void calib_angles_kernel(const double* __restrict__ G, int D, const double* __restrict__ norm,
                                                                     double lead, double* __restrict__ E, f64x2* __restrict__ found)
 {
-    __shared__ f64x2 s_found[4];
+    __shared__ f64x2 s_found[8];
     double most = 0.0, sum = 0.0;
-    calib_product<double, double, false, double>(G, G, D, [&](int i, int j, double ab) {
-        const double ni = norm[i], nj = norm[j], aa = ni * ni, bb = nj * nj, d = bb - aa;
-        const bool counts = i != j && fmax(aa, bb) >= lead && jac_open(aa, bb, ab);
-        const double th = counts ? ab / d : 0.0;
-        if (counts && i < j) {
-            most = fmax(most, fabs(ab) / fmax(fabs(d), 2.0 * fabs(ab)));
-            if (fmin(aa, bb) >= lead) most = fmax(most, fabs(ab) / (ni * nj));
-            sum += th * th;
+    const SymTile tile = sym_tile(blockIdx.x, D);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    calib_product_sym<double, double>(G, D, tile, [&](int rb, int cb, const f64x4& v, bool both) {
+        const int j = tile.col * 64 + tile.half * 32 + cb * 16 + (lane & 15);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = tile.row * 64 + rb * 16 + mma_tile<double>::row(lane >> 4, e);
+            const double ab = v[e], ni = norm[i], nj = norm[j], aa = ni * ni, bb = nj * nj, d = bb - aa;
+            const bool counts = i != j && fmax(aa, bb) >= lead && jac_open(aa, bb, ab);
+            const double th = counts ? ab / d : 0.0;
+            if (counts && (both || i < j)) {
+                most = fmax(most, fabs(ab) / fmax(fabs(d), 2.0 * fabs(ab)));
+                if (fmin(aa, bb) >= lead) most = fmax(most, fabs(ab) / (ni * nj));
+                sum += th * th;
+            }
+            E[(size_t)i * D + j] = -th;
+            if (both) E[(size_t)j * D + i] = th;
         }
-        E[(size_t)i * D + j] = -th;
     });
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) { most = fmax(most, __shfl_xor(most, o, kWave)); sum += __shfl_xor(sum, o, kWave); }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0 && wave < 4) s_found[wave] = f64x2{most, sum};
+    if (lane == 0) s_found[wave] = f64x2{most, sum};
     __syncthreads();
-    if (threadIdx.x == 0)
-        found[blockIdx.y * gridDim.x + blockIdx.x] = f64x2{fmax(fmax(s_found[0].x, s_found[1].x), fmax(s_found[2].x, s_found[3].x)),
-                                                           (s_found[0].y + s_found[1].y) + (s_found[2].y + s_found[3].y)};
+    if (threadIdx.x == 0) {
+        f64x2 t = s_found[0];
+#pragma unroll
+        for (int w = 1; w < 8; ++w) t = f64x2{fmax(t.x, s_found[w].x), t.y + s_found[w].y};
+        found[blockIdx.x] = t;
+    }
 }
 
 // Any angles, of rows sorted by norm, for the pairs that are not orthogonal to 1e-12 and of which one row has a squared norm of at
@@ -263,8 +386,8 @@ __global__ __launch_bounds__(kProdThreads) void calib_angles_kernel(const double
 // a small ab, and in vain while the norms still move: row i's squared norm is off by about the sum of ab^2 / h over its pairs, h =
 // sqrt(d^2 + 4 ab^2).  So the entry is ab / sqrt(h^2 + (off_i + off_j)^2), which is as good once the rows are nearly orthogonal and
 // saves a transformation of ten (weights 0, 0.1, 0.3, 1 and 3 of its square: 5.93, 5.17, 5.15, 5.21 and 5.54 ms at D = 1024, r = 640;
-// 6.0, 5.0, 5.3, 6.8 and 7.4 with eigenvalues within 1e-3 of each other).  First the products (fp32) and the tiles' shares of
-// `off`, [column tile][row] ...
+// 6.0, 5.0, 5.3, 6.8 and 7.4 with eigenvalues within 1e-3 of each other).  First the products (fp32) and the workgroups'
+// shares of `off`, [share][row]: a row of tile I has D / 64 + I of them, two from a tile before its own, one from its own and from later ones ...
 constexpr double kAllDamp = 0.1, kAllOpen = 1e-24, kAllTail = 1e-3;
 struct AllPair { bool counts; double d, h2; };
 __device__ __forceinline__ AllPair all_pair(double ni, double nj, double ab, double least)
@@ -275,64 +398,84 @@ __device__ __forceinline__ AllPair all_pair(double ni, double nj, double ab, dou
 __global__ __launch_bounds__(kProdThreads) void calib_gram_kernel(const double* __restrict__ G, int D, const double* __restrict__ norm, int r,
                                                                   float* __restrict__ W, float* __restrict__ off)
 {
-    __shared__ float s_off[2][64];
+    __shared__ float s_off[2][4][64];   // of the tile's rows by 16-column block, of its columns by 16-row block (the diagonal: all the former)
     const double lead = 0.999 * norm[r - 1] * norm[r - 1], least = kAllTail * lead;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float sum[8];   // of this lane's columns, rows 16 u + kg + 4 e of its wave's half
+    const SymTile tile = sym_tile(blockIdx.x, D);
+    const int lane = threadIdx.x & 63, l16 = lane & 15, kg = lane >> 4;
+    const int i0 = tile.row * 64, j0 = tile.col * 64 + tile.half * 32;
+    calib_product_sym<double, double>(G, D, tile, [&](int rb, int cb, const f64x4& v, bool both) {
+        const int j = j0 + cb * 16 + l16;
+        float col = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) sum[i] = 0.f;
-    int n = 0;
-    calib_product<double, double, false, double>(G, G, D, [&](int i, int j, double ab) {
-        W[(size_t)i * D + j] = (float)ab;
-        const AllPair p = all_pair(norm[i], norm[j], ab, least);
-        const int k = n++;   // (a constant, once unrolled)
-        if (i != j && p.counts) sum[(k >> 3) * 4 + (k & 3)] += (float)(ab * ab * rsqrt_f64(p.h2));
-    });
-    if (wave < 4) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float t = row16_sum(sum[i]);
-            if ((lane & 15) == 0) s_off[wave & 1][(wave >> 1) * 32 + (i >> 2) * 16 + (lane >> 4) + 4 * (i & 3)] = t;
+        for (int e = 0; e < 4; ++e) {
+            const int at = rb * 16 + mma_tile<double>::row(kg, e), i = i0 + at;
+            const double ab = v[e];
+            W[(size_t)i * D + j] = (float)ab;
+            if (both) W[(size_t)j * D + i] = (float)ab;
+            const AllPair p = all_pair(norm[i], norm[j], ab, least);
+            const float share = i != j && p.counts ? (float)(ab * ab * rsqrt_f64(p.h2)) : 0.f;
+            col += share;
+            const float t = row16_sum(share);
+            if (l16 == 0) s_off[0][cb][at] = t;
         }
-    }
+        if (both) {
+            col += __shfl_xor(col, 16, kWave);
+            col += __shfl_xor(col, 32, kWave);
+            if (kg == 0) s_off[tile.diag() ? 0 : 1][rb][cb * 16 + l16] = col;
+        }
+    });
     __syncthreads();
-    if (threadIdx.x < 64) off[(size_t)blockIdx.x * D + blockIdx.y * 64 + threadIdx.x] = s_off[0][threadIdx.x] + s_off[1][threadIdx.x];
+    const int t = threadIdx.x;
+    if (tile.diag()) {
+        if (t < 64) off[(size_t)(2 * tile.row) * D + i0 + t] = (s_off[0][0][t] + s_off[0][1][t]) + (s_off[0][2][t] + s_off[0][3][t]);
+    } else if (t < 64) {
+        off[(size_t)(2 * tile.col + tile.half) * D + i0 + t] = s_off[0][0][t] + s_off[0][1][t];
+    } else if (t < 96) {
+        const int c = t - 64;
+        off[(size_t)(tile.col + tile.row) * D + j0 + c] = (s_off[1][0][c] + s_off[1][1][c]) + (s_off[1][2][c] + s_off[1][3][c]);
+    }
 }
-// ... then E (pairs of bf16), kAngleRows rows a workgroup, and per workgroup the sum of squares of ab / h over the pairs with a leading row.
-constexpr int kAngleRows = 4;
+// ... then E (pairs of bf16), kAngleRows rows x 256 columns a workgroup, and per workgroup the sum of squares of ab / h over the pairs with
+// a leading row.  (8.9 us at D = 1024; 26.5 with 256 columns
+// after the other in a workgroup.)
+constexpr int kAngleRows = 8;
 __global__ __launch_bounds__(256) void calib_all_angles_kernel(const float* __restrict__ W, int D, const double* __restrict__ norm, int r,
                                                                const float* __restrict__ off, uint32_t* __restrict__ E, double* __restrict__ found)
 {
+    static_assert(kAngleRows == 8 && kCalThreads == 256, "32 lanes a row; D is a multiple of the columns");
     __shared__ double s_sum[4];
+    __shared__ float s_off[kAngleRows];
     const double lead = 0.999 * norm[r - 1] * norm[r - 1], least = kAllTail * lead;
-    const int i0 = blockIdx.x * kAngleRows, n = D / 64;
+    const int tid = threadIdx.x, i0 = blockIdx.x * kAngleRows, j = blockIdx.y * 256 + tid, nb = D / 64;
+    float w[kAngleRows];
+#pragma unroll
+    for (int u = 0; u < kAngleRows; ++u) w[u] = W[(size_t)(i0 + u) * D + j];
+    float off_j = 0.f, mine = 0.f;
+    for (int t = tid & 31; t < nb + i0 / 64; t += 32) mine += off[(size_t)t * D + i0 + (tid >> 5)];
+    const int n_j = nb + wave_uniform(j / 64);
+#pragma unroll 8
+    for (int t = 0; t < n_j; ++t) off_j += off[(size_t)t * D + j];
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) mine += __shfl_xor(mine, o, kWave);
+    if ((tid & 31) == 0) s_off[tid >> 5] = mine;
+    __syncthreads();
+    const double nj = norm[j];
     double sum = 0.0;
-    float off_i[kAngleRows];
 #pragma unroll
-    for (int u = 0; u < kAngleRows; ++u) off_i[u] = 0.f;
-    for (int t = 0; t < n; ++t)
-#pragma unroll
-        for (int u = 0; u < kAngleRows; ++u) off_i[u] += off[(size_t)t * D + i0 + u];
-    for (int j = threadIdx.x; j < D; j += 256) {
-        float off_j = 0.f;
-        for (int t = 0; t < n; ++t) off_j += off[(size_t)t * D + j];
-        const double nj = norm[j];
-#pragma unroll
-        for (int u = 0; u < kAngleRows; ++u) {
-            const int i = i0 + u;
-            const double ab = W[(size_t)i * D + j], ni = norm[i], o = (double)off_i[u] + off_j;
-            const AllPair p = all_pair(ni, nj, ab, least);
-            const bool counts = p.counts && i != j;
-            const double s = counts ? ab * rsqrt_f64(fma(kAllDamp * o, o, p.h2)) : 0.0;
-            E[(size_t)i * D + j] = pack_pair((float)(p.d < 0.0 || (p.d == 0.0 && i > j) ? s : -s));
-            if (counts && i < j && fmax(ni, nj) * fmax(ni, nj) >= lead) sum += ab * ab / p.h2;
-        }
+    for (int u = 0; u < kAngleRows; ++u) {
+        const int i = i0 + u;
+        const double ab = w[u], ni = norm[i], o = (double)s_off[u] + off_j;
+        const AllPair p = all_pair(ni, nj, ab, least);
+        const bool counts = p.counts && i != j;
+        const double s = counts ? ab * rsqrt_f64(fma(kAllDamp * o, o, p.h2)) : 0.0;
+        E[(size_t)i * D + j] = pack_pair((float)(p.d < 0.0 || (p.d == 0.0 && i > j) ? s : -s));
+        if (counts && i < j && fmax(ni, nj) * fmax(ni, nj) >= lead) sum += ab * ab / p.h2;
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, kWave);
-    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = sum;
+    if ((tid & 63) == 0) s_sum[tid >> 6] = sum;
     __syncthreads();
-    if (threadIdx.x == 0) found[blockIdx.x] = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
+    if (tid == 0) found[blockIdx.y * gridDim.x + blockIdx.x] = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
 }
 
 // ---- Polar factor -----------------------------------------------------------------------------------------------------
@@ -361,23 +504,46 @@ __global__ __launch_bounds__(kProdThreads) void calib_polar_kernel(const uint32_
     __syncthreads();
     if (threadIdx.x == 0) square[blockIdx.y * gridDim.x + blockIdx.x] = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
 }
-// The last step: O = f A B^T + s S (ADD) in fp32
-template <bool ADD>
+// The last step in fp32: O = X X^T ...
+__global__ __launch_bounds__(kProdThreads) void calib_polar_square_kernel(const float* X, int D, float* O)
+{
+    const SymTile tile = sym_tile(blockIdx.x, D);
+    const int lane = threadIdx.x & 63;
+    calib_product_sym<float, float>(X, D, tile, [&](int rb, int cb, const f32x4& v, bool both) {
+        const int j = tile.col * 64 + tile.half * 32 + cb * 16 + (lane & 15);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = tile.row * 64 + rb * 16 + mma_tile<float>::row(lane >> 4, e);
+            O[(size_t)i * D + j] = v[e];
+            if (both) O[(size_t)j * D + i] = v[e];
+        }
+    });
+}
+// ... and O = f A B^T + s S
 __global__ __launch_bounds__(kProdThreads) void calib_polar_last_kernel(const float* A, const float* B, int D, float f, float s, const float* S,
                                                                         float* O)
 {
     calib_product<float, float, false, float>(A, B, D, [&](int i, int j, float v) {
         const size_t at = (size_t)i * D + j;
-        O[at] = ADD ? fmaf(s, S[at], f * v) : f * v;
+        O[at] = fmaf(s, S[at], f * v);
     });
 }
 // delta = X X^T - I, summed in fp64, and its rounding to pairs of bf16
 __global__ __launch_bounds__(kProdThreads) void calib_defect_kernel(const float* X, int D, double* delta, uint32_t* rounded)
 {
-    calib_product<float, float, false, double>(X, X, D, [&](int i, int j, double v) {
-        const double o = i == j ? v - 1.0 : v;
-        delta[(size_t)i * D + j] = o;
-        rounded[(size_t)i * D + j] = pack_pair((float)o);
+    const SymTile tile = sym_tile(blockIdx.x, D);
+    const int lane = threadIdx.x & 63;
+    calib_product_sym<float, double>(X, D, tile, [&](int rb, int cb, const f64x4& v, bool both) {
+        const int j = tile.col * 64 + tile.half * 32 + cb * 16 + (lane & 15);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = tile.row * 64 + rb * 16 + mma_tile<double>::row(lane >> 4, e);
+            const double o = i == j ? v[e] - 1.0 : v[e];
+            const uint32_t pair = pack_pair((float)o);
+            delta[(size_t)i * D + j] = o;
+            rounded[(size_t)i * D + j] = pair;
+            if (both) { delta[(size_t)j * D + i] = o; rounded[(size_t)j * D + i] = pair; }
+        }
     });
 }
 // delta <- -delta / 2 + 3/8 delta^2 (the square, 1e-12, from the rounded one)

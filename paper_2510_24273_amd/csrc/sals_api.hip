@@ -2015,35 +2015,37 @@ bool eig_plan(int D, size_t bytes, EigWs* w, int* n_part, bool* series)
 }  // namespace
 
 namespace {
-// Transformations of all rows at once (k_calib_all.hpp) in place of sweeps, up to kAllMaxD.  One takes 0.42 ms at D = 1024, where a
+// Transformations of all rows at once (k_calib_all.hpp) in place of sweeps, up to kAllMaxD.  One takes 0.37 ms at D = 1024, where a
 // sweep takes 0.8, and from the Cholesky factor on it brings the rows as far as a sweep does, or further once the angles are below
 // one; its products grow with D^3 and a sweep's steps with D^2, so for large D it comes later.  A call, r = 5/8 D, in ms with the
 // transformations behind one, two and three sweeps (and with sweeps alone): D = 256 1.8 / 1.8 / 1.8 (2.2), 512 2.8 / 2.9 / 3.1 (4.4),
-// 1024 5.1 / 5.5 / 5.9 (9.6), 2048 23.7 / 23.7 / 24.3 (29.2), 3072 76 / 72 / 70 (79), 4096 177 / 165 / 149 (141).
+// 1024 5.1 / 5.5 / 5.9 (9.6), 2048 23.7 / 23.7 / 24.3 (29.2), 3072 76 / 72 / 70 (79), 4096 177 / 165 / 149 (141); these with the
+// symmetric products computed whole (1024 4.8, 2048 21.6 with half of them).
 constexpr int kAllMaxD = 3072;
 inline int all_first(int D) { return D <= 2048 ? 1 : 3; }
 // |E| at most: larger angles gain nothing (4, 6 and 10: 5.13, 5.11 and 5.11 ms at D = 1024; 5.43, 5.25, 5.28 with a spectrum c^-2)
 constexpr double kAllCap = 6.0;
 // the series of the exponential: cut behind E^4 it differs from an orthogonal matrix by |E|^6 / 72
 constexpr double kSeriesNorm = 4e-3;
-// the product kernels' dynamic LDS, beyond the default limit for the ones with a row-by-row operand
-sals_status calib_all_lds()
+// the product kernels' dynamic LDS, beyond the default limit
+sals_status calib_all_lds(bool series)
 {
     auto allow = [](const void* kern, size_t bytes) {
         return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
     };
     constexpr size_t nt = prod_lds<float, float, false>();
-    const bool ok = allow(reinterpret_cast<const void*>(calib_angles_kernel), prod_lds<double, double, false>()) &&
-                    allow(reinterpret_cast<const void*>(calib_gram_kernel), prod_lds<double, double, false>()) &&
+    if (!allow(reinterpret_cast<const void*>(calib_angles_kernel), kSymLds)) return SALS_ERR_HIP;
+    if (!series) return SALS_OK;
+    const bool ok = allow(reinterpret_cast<const void*>(calib_gram_kernel), kSymLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<0, true, false>), kPairLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<0, false, false>), kPairLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<1, false, false>), kPairLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<1, false, true>), kPairLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<2, false, false>), kPairLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<2, false, true>), kPairLds) &&
-                    allow(reinterpret_cast<const void*>(calib_polar_last_kernel<false>), nt) &&
-                    allow(reinterpret_cast<const void*>(calib_polar_last_kernel<true>), nt) &&
-                    allow(reinterpret_cast<const void*>(calib_defect_kernel), nt) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_square_kernel), kSymLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_last_kernel), nt) &&
+                    allow(reinterpret_cast<const void*>(calib_defect_kernel), kSymLds) &&
                     allow(reinterpret_cast<const void*>(calib_correction_kernel), kPairLds) &&
                     allow(reinterpret_cast<const void*>(calib_apply_kernel<float, false>), prod_lds<float, double, true>()) &&
                     allow(reinterpret_cast<const void*>(calib_apply_kernel<double, true>), prod_lds<double, double, true>());
@@ -2077,7 +2079,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     const int slices = jac_slices(D);
     const int n_tiles = (D / 64) * (D / 64);   // of the angles, whose results lie where the partial Gram matrices do
     f64x2* const found = reinterpret_cast<f64x2*>(part);
-    const int n_angles = D / kAngleRows;
+    const int n_angles = D / kAngleRows * (D / 256);
     double *const all_found = part, *const square = part + n_angles;
     float* const row_off = reinterpret_cast<float*>(square + n_tiles);
     double *rows = G, *other = at(off.Y0), *third = at(off.Y1);   // the rows, and room for two more matrices (`series`)
@@ -2085,7 +2087,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     const bool all = series && D <= kAllMaxD;
     const std::unique_ptr<double[]> host(new (std::nothrow) double[(size_t)n_blocks + D + std::max(2 * n_tiles, n_angles + n_tiles)]);
     if (!host) return SALS_ERR_HIP;
-    if (series && calib_all_lds() != SALS_OK) return SALS_ERR_HIP;  // (behind the memory: the runtime has no error for a lack of it)
+    if (calib_all_lds(series) != SALS_OK) return SALS_ERR_HIP;  // (behind the memory: the runtime has no error for a lack of it)
     double *const h_conv = host.get(), *const h_norm = h_conv + n_blocks, *const h_found = h_norm + D;
     auto row_norms = [&](const double* M) -> bool {  // row norms to the host (blocking)
         hipLaunchKernelGGL(calib_rownorm_kernel, dim3(D), dim3(kCalThreads), 0, st, M, D, norm, sgn);
@@ -2138,7 +2140,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         hipLaunchKernelGGL(calib_jacobi_inside_kernel, dim3(n_blocks, slices), dim3(kJacInsideThreads), 0, st, rows, D, D / slices, part,
                            n_part, lead, conv);
     };
-    const dim3 tile_grid(D / 64, D / 64), prod(kProdThreads);
+    const dim3 tile_grid(D / 64, D / 64), sym_grid(n_tiles), prod(kProdThreads);
     bool settled = false;
     double last = 1e300;   // |E| of the transformation before, infinite behind a sweep
     while (done < max_sweeps && !converged) {
@@ -2152,9 +2154,9 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             hipLaunchKernelGGL(calib_sort_kernel, dim3(D), dim3(kCalThreads), 0, st, rows, norm, D, other, sorted);
             std::swap(rows, other);
             uint32_t *const E = reinterpret_cast<uint32_t*>(third), *const A = E + (size_t)D * D;
-            hipLaunchKernelGGL(calib_gram_kernel, tile_grid, prod, (prod_lds<double, double, false>()), st, rows, D, sorted, r,
+            hipLaunchKernelGGL(calib_gram_kernel, sym_grid, prod, kSymLds, st, rows, D, sorted, r,
                                reinterpret_cast<float*>(A), row_off);
-            hipLaunchKernelGGL(calib_all_angles_kernel, dim3(n_angles), dim3(256), 0, st, reinterpret_cast<const float*>(A), D, sorted, r, row_off,
+            hipLaunchKernelGGL(calib_all_angles_kernel, dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D, sorted, r, row_off,
                                E, all_found);
             hipLaunchKernelGGL((calib_polar_kernel<0, true, false>), tile_grid, prod, kPairLds, st, E, E, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr,
                                A, square);
@@ -2211,13 +2213,12 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                 }
                 if (!one) {
                     float *const x = reinterpret_cast<float*>(X), *const x2 = reinterpret_cast<float*>(X2), *const y = reinterpret_cast<float*>(Y);
-                    hipLaunchKernelGGL((calib_polar_last_kernel<false>), tile_grid, prod, (prod_lds<float, float, false>()), st, x, x, D, 1.f, 0.f,
-                                       nullptr, y);
-                    hipLaunchKernelGGL((calib_polar_last_kernel<true>), tile_grid, prod, (prod_lds<float, float, false>()), st, x, y, D, -0.5f, 1.5f,
+                    hipLaunchKernelGGL(calib_polar_square_kernel, sym_grid, prod, kSymLds, st, x, D, y);
+                    hipLaunchKernelGGL(calib_polar_last_kernel, tile_grid, prod, (prod_lds<float, float, false>()), st, x, y, D, -0.5f, 1.5f,
                                        x, x2);
                     std::swap(X, X2);
                 }
-                hipLaunchKernelGGL(calib_defect_kernel, tile_grid, prod, (prod_lds<float, float, false>()), st, reinterpret_cast<const float*>(X), D,
+                hipLaunchKernelGGL(calib_defect_kernel, sym_grid, prod, kSymLds, st, reinterpret_cast<const float*>(X), D,
                                    C, X2);
                 hipLaunchKernelGGL(calib_correction_kernel, tile_grid, prod, kPairLds, st, X2, D, C);
                 hipLaunchKernelGGL((calib_apply_kernel<float, false>), tile_grid, prod, (prod_lds<float, double, true>()), st,
@@ -2249,7 +2250,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         // (Sweeps whose largest rotation was 0.26, 0.07, 0.007 left 4e-5, 1e-3, 4e-6.)  The angles lie in C, which is free until its
         // rows are written.
         for (int pass = 0; !converged && worst <= 0.3 && pass < 6; ++pass) {
-            hipLaunchKernelGGL(calib_angles_kernel, tile_grid, prod, (prod_lds<double, double, false>()), st, rows, D, norm, lead, C, found);
+            hipLaunchKernelGGL(calib_angles_kernel, sym_grid, prod, kSymLds, st, rows, D, norm, lead, C, found);
             if (launch_status() != SALS_OK ||
                 hipMemcpyAsync(h_found, found, (size_t)n_tiles * sizeof(f64x2), hipMemcpyDeviceToHost, st) != hipSuccess ||
                 hipStreamSynchronize(st) != hipSuccess)
