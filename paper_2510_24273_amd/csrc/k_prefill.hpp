@@ -196,9 +196,9 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_compress_kernel(Prefill
 // Both operands come straight from memory into LDS (64-byte steps of the D axis, four stages, 16-byte pieces at their index
 // XOR row bits) and eight waves of 32 NBT tokens x 32 NBW coordinates read the next half step's fragments under the current
 // one's MFMAs, one barrier per step.  The latent coordinates are the MFMA's rows, so a lane ends up with four consecutive
-// coordinates of a token and stores 8 bytes at a time.
+// coordinates of a token; the stores go through LDS.
 // Matrix-bound while the whole chip works (22 ns per MFMA and SIMD at the clock its power leaves, 13.4 with few workgroups);
-// what is lost to it is the last round of tiles and 2 (smallest tile) to 13 us (largest) per round to start and store.  Whole
+// what is lost to it is the last round of tiles and 2 (smallest tile) to about 9 us (largest) per round to start and store.  Whole
 // calls, with the launch that advances the lengths, against the 256 x 128 and 128 x 128 tiles staged through registers, two
 // workgroups per compute unit, that this replaced: 6 ragged prompts of up to 4001 tokens, D = 1024, r = 640 91 -> 78 us;
 // 6000 tokens, D = 4096, r = 1024 125 -> 99 us; 64 tokens, D = 4096 44 -> 20 us.
@@ -358,7 +358,7 @@ __device__ __forceinline__ void prefill_tile(const PrefillArgs& a, int block, in
         const int row0 = a.seq_len[b];
         const long long row = (long long)row0 + t;
         const bool ok = m < m_end && row0 >= 0 && row < a.S_max;
-        dst[nb] = ok ? static_cast<unsigned char*>(a.cache[proj]) + (((size_t)b * a.S_max + (size_t)row) * a.r + hi * 4) * 2 : nullptr;
+        dst[nb] = ok ? static_cast<unsigned char*>(a.cache[proj]) + ((size_t)b * a.S_max + (size_t)row) * a.r * 2 : nullptr;
     }
     wait_but(std::integral_constant<int, 2>{});
     wg_barrier();
@@ -381,26 +381,40 @@ __device__ __forceinline__ void prefill_tile(const PrefillArgs& a, int block, in
             half_step(F1, F0, (u + 1) & 3, 0, s0 + u + 3, (u + 3) & 3, std::integral_constant<int, 1>{});
         }
     }
-    vm_wait<0>();  // (no load may land in LDS that another workgroup has been given)
+    vm_wait<0>();  // (no load may land in LDS that another workgroup has been given, nor in the rows below)
+    wg_barrier();
 
-    // acc[mb][nb][4a+c]: latent coordinate wn 32 NBW + mb 32 + 8a + 4hi + c, token wm 32 NBT + nb 32 + l32
+    // acc[mb][nb][4a+c]: latent coordinate wn 32 NBW + mb 32 + 8a + 4hi + c, token wm 32 NBT + nb 32 + l32.  A wave turns 32 tokens at
+    // a time in rows of its own in LDS (its coordinates of a token, the token's cache row behind them), so that consecutive lanes
+    // store consecutive 16-byte pieces of a cache row.  Stored as they lie, 8 bytes a lane, every store reached 32 rows: whole calls
+    // and the copy that sets the lengths back, before and now, 6 ragged prompts of up to 4001 tokens (D = 1024, r = 640) 68.6 and 61.6
+    // us, 1 x 20000 70.7 and 62.8, 1 x 6000 (D = 4096, r = 1024) 98.0 and 96.0, 64 tokens 20.6 and 20.5.
+    constexpr int ROW = NBW * 64 + 16, PPR = NBW * 4;   // bytes and pieces of a row
+    static_assert(8 * 32 * ROW <= (int)C::LDS, "rows of eight waves");
+    unsigned char* rows = lds + wave * (32 * ROW);
+    const int lat_w = lat0 + wn * NBW * 32;
 #pragma unroll
     for (int nb = 0; nb < NBT; ++nb) {
-        if (dst[nb]) {
 #pragma unroll
-            for (int mb = 0; mb < NBW; ++mb) {
-                const int lat = lat0 + (wn * NBW + mb) * 32;
-                if (lat < a.r) {  // uniform (r is a multiple of 64, so of the 32-wide blocks)
+        for (int mb = 0; mb < NBW; ++mb)
 #pragma unroll
-                    for (int v = 0; v < 16; v += 4) {
-                        uint2 w;
-                        w.x = (uint32_t)f32_to_bf16(acc[mb][nb][v]) | ((uint32_t)f32_to_bf16(acc[mb][nb][v + 1]) << 16);
-                        w.y = (uint32_t)f32_to_bf16(acc[mb][nb][v + 2]) | ((uint32_t)f32_to_bf16(acc[mb][nb][v + 3]) << 16);
-                        *reinterpret_cast<uint2*>(dst[nb] + (size_t)(lat + 2 * v) * 2) = w;
-                    }
-                }
+            for (int v = 0; v < 16; v += 4) {
+                uint2 w;
+                w.x = (uint32_t)f32_to_bf16(acc[mb][nb][v]) | ((uint32_t)f32_to_bf16(acc[mb][nb][v + 1]) << 16);
+                w.y = (uint32_t)f32_to_bf16(acc[mb][nb][v + 2]) | ((uint32_t)f32_to_bf16(acc[mb][nb][v + 3]) << 16);
+                *reinterpret_cast<uint2*>(rows + l32 * ROW + (mb * 32 + 2 * v + hi * 4) * 2) = w;
             }
+        if (hi == 0) *reinterpret_cast<unsigned char**>(rows + l32 * ROW + NBW * 64) = dst[nb];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < PPR / 2; ++i) {
+            const int q = i * 64 + lane, t = (unsigned)q / PPR, pc = q - t * PPR;
+            unsigned char* const to = *reinterpret_cast<unsigned char* const*>(rows + t * ROW + NBW * 64);
+            const u32x4 w = *reinterpret_cast<const u32x4*>(rows + t * ROW + pc * 16);
+            // (r is a multiple of 64, so of the pieces' coordinates)
+            if (to && lat_w + pc * 8 < a.r) *reinterpret_cast<u32x4*>(to + (size_t)(lat_w + pc * 8) * 2) = w;
         }
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
