@@ -388,7 +388,9 @@ __device__ __forceinline__ void prefill_tile(const PrefillArgs& a, int block, in
     // a time in rows of its own in LDS (its coordinates of a token, the token's cache row behind them), so that consecutive lanes
     // store consecutive 16-byte pieces of a cache row.  Stored as they lie, 8 bytes a lane, every store reached 32 rows: whole calls
     // and the copy that sets the lengths back, before and now, 6 ragged prompts of up to 4001 tokens (D = 1024, r = 640) 68.6 and 61.6
-    // us, 1 x 20000 70.7 and 62.8, 1 x 6000 (D = 4096, r = 1024) 98.0 and 96.0, 64 tokens 20.6 and 20.5.
+    // us, 1 x 20000 70.7 and 62.8, 1 x 6000 (D = 4096, r = 1024) 98.0 and 96.0, 64 tokens 20.6 and 20.5.  The stores are whole lines that
+    // nothing reads soon, so the caches are told not to keep them: inputs that change from call to call 67.3 -> 62.8, 1 x 6000 96.0 ->
+    // 92.9 (8-byte stores with that hint: twice the time).
     constexpr int ROW = NBW * 64 + 16, PPR = NBW * 4;   // bytes and pieces of a row
     static_assert(8 * 32 * ROW <= (int)C::LDS, "rows of eight waves");
     unsigned char* rows = lds + wave * (32 * ROW);
@@ -412,7 +414,7 @@ __device__ __forceinline__ void prefill_tile(const PrefillArgs& a, int block, in
             unsigned char* const to = *reinterpret_cast<unsigned char* const*>(rows + t * ROW + NBW * 64);
             const u32x4 w = *reinterpret_cast<const u32x4*>(rows + t * ROW + pc * 16);
             // (r is a multiple of 64, so of the pieces' coordinates)
-            if (to && lat_w + pc * 8 < a.r) *reinterpret_cast<u32x4*>(to + (size_t)(lat_w + pc * 8) * 2) = w;
+            if (to && lat_w + pc * 8 < a.r) __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(to + (size_t)(lat_w + pc * 8) * 2));
         }
         __builtin_amdgcn_wave_barrier();
     }
