@@ -1162,11 +1162,19 @@ namespace {
 struct PrefillTile { int nbw, nbt; double idle, full, over; };
 constexpr PrefillTile kPrefillTiles[] = {
     {1, 1, 0.105, 0.20, 2.0}, {2, 1, 0.145, 0.286, 3.0}, {3, 1, 0.19, 0.38, 4.0},
+    {2, 2, 0.27, 0.51, 7.5}, {4, 2, 0.475, 0.68, 10.0}, {5, 2, 0.58, 0.82, 10.0}};
+// Where the sequences' token counts are known on the device only, and may be well below n_tok, large tiles that the whole of n_tok would
+// fill may lie idle; the estimate is then more in favour of 256 x 128 tiles and smaller ones.  Whole calls with the estimates below and
+// above in us: without counts 1 x 4097, D = 4096, r = 1024 96.3 and 77.4, 4 x 1391, r = 832 101.7 and 89.5, 2 x 11255, D = 1024, r = 256
+// 37.7 and 32.1; with counts from a half of n_tok on, 6 x 830, D = 4096, r = 896 76.3 and 80.7, 6 x 1101, D = 1024, r = 576 26.6 and 28.1.
+constexpr PrefillTile kPrefillTilesCounts[] = {
+    {1, 1, 0.105, 0.20, 2.0}, {2, 1, 0.145, 0.286, 3.0}, {3, 1, 0.19, 0.38, 4.0},
     {2, 2, 0.255, 0.45, 6.0}, {4, 2, 0.475, 0.68, 12.0}, {5, 2, 0.58, 0.82, 13.0}};
 struct PrefillPlan { PrefillTile main, tail; int tail_max; };  // tail_max == 0: all tiles alike
-PrefillPlan plan_prefill(const sals_desc& d, int n_tok)
+PrefillPlan plan_prefill(const sals_desc& d, int n_tok, bool counts)
 {
-    PrefillPlan best{kPrefillTiles[0], kPrefillTiles[0], 0};
+    const auto& tiles_of = counts ? kPrefillTilesCounts : kPrefillTiles;
+    PrefillPlan best{tiles_of[0], tiles_of[0], 0};
     double best_us = 1e30;
     const double steps = (double)(d.H_kv * d.d) / 32.0;
     auto rounds_us = [&](const PrefillTile& t, double tiles) {
@@ -1174,7 +1182,7 @@ PrefillPlan plan_prefill(const sals_desc& d, int n_tok)
         return rounds * (steps * t.full + t.over) + (rest > 0.0 ? steps * (t.idle + (t.full - t.idle) * rest) + t.over : 0.0);
     };
     auto per_row_tile = [&](const PrefillTile& t) { return ceil_div(d.r, 64 * t.nbw) * 2; };
-    for (const PrefillTile& t : kPrefillTiles) {
+    for (const PrefillTile& t : tiles_of) {
         const long long row_tiles = ((long long)d.B * n_tok + 128 * t.nbt - 1) / (128 * t.nbt);
         const int per = per_row_tile(t);
         const double us = rounds_us(t, (double)row_tiles * per);
@@ -1182,7 +1190,7 @@ PrefillPlan plan_prefill(const sals_desc& d, int n_tok)
         if (t.nbt != 2) continue;
         const long long whole = row_tiles * per / 256 * 256 / per;
         if (whole == 0 || whole == row_tiles) continue;
-        for (const PrefillTile& u : kPrefillTiles) {
+        for (const PrefillTile& u : tiles_of) {
             if (u.nbt != 1) continue;
             const double us2 = rounds_us(t, (double)whole * per) + rounds_us(u, (double)(row_tiles - whole) * 2 * per_row_tile(u));
             // (the token counts may be smaller than n_tok: the tail is used for any rest up to this one or two thirds of a round)
@@ -1213,7 +1221,7 @@ sals_status sals_compress_prefill(sals_ctx* ctx, const void* k_new, const void* 
     };
     ProfScope ps(ctx, SALS_K_PREFILL, st);
     if (bf) {
-        const PrefillPlan P = plan_prefill(d, n_tok);
+        const PrefillPlan P = plan_prefill(d, n_tok, n_new != nullptr);
         const PrefillTile t = P.main;
         const int n_col = ceil_div(d.r, 64 * t.nbw), tm = 128 * t.nbt;
         // every token tile a batch of these sizes can have (workgroups past the tiles that hold tokens leave)

@@ -169,3 +169,16 @@ def test_tile_shapes_and_remainders(B, n_tok, H_kv, r, lens):
 ])
 def test_two_kinds_of_tiles_in_a_launch(B, n_tok, H_kv, r, lens):
     test_tile_shapes_and_remainders(B, n_tok, H_kv, r, lens)
+
+
+@pytest.mark.parametrize("B,n_tok,H_kv,r,lens", [
+    (1, 20483, 2, 256, [20483]),               # 256 x 128 and 128 x 128: with counts only
+    (1, 16396, 8, 320, [16396]),               # 256 x 128 and 128 x 192: with counts only
+    (1, 16630, 1, 384, None),                  # 256 x 128 and 128 x 192
+    (2, 6180, 1, 448, None),                   # 256 x 256, a last row tile of 72 rows
+    (3, 5468, 1, 320, None),                   # 256 x 320, the same of 20 rows
+    (1, 20837, 1, 448, None),                  # 256 x 256 and 128 x 192
+])
+def test_tiles_with_and_without_counts(B, n_tok, H_kv, r, lens):
+    """The choice of tiles differs where the token counts are known on the device only."""
+    test_tile_shapes_and_remainders(B, n_tok, H_kv, r, lens)
