@@ -2,9 +2,9 @@
 // sink / recent composition of Sec. 5.2.
 //
 // One workgroup per sequence finds the key of the k-th largest candidate exactly and then
-// places every selected index with one block-wide prefix sum.  Scores are handled as
-// order-preserving 32-bit keys, kept in registers when the sequence fits (up to 32 per
-// thread); longer sequences re-read the scores, which sit in L2.
+// places every selected index with one block-wide prefix sum.  Scores stay in registers when
+// the sequence fits (up to 32 per thread); longer sequences re-read them, they sit in L2, as
+// order-preserving 32-bit keys.
 //
 // Finding the k-th key:
 //   fast path  a 4096-bin histogram over the LINEAR range [min, max] of the candidates (a
@@ -81,7 +81,7 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, TopkShared& sh, 
 }
 
 // Selection for sequence b by the calling workgroup (NTH threads, all of them must call).
-// F4 > 0: keys of F4 float4 groups per thread stay in registers.  F4 == 0: stream.
+// F4 > 0: the scores of F4 float4 groups per thread stay in registers.  F4 == 0: stream.
 // Of the selection kernel's 1024 threads, thread t holds the groups 4*(c*1024 + t) .. +3 (c = 0, 1, ...), and inside a score class
 // the list has the indices in the order of the threads and of a thread's groups.  A workgroup of NTH < 1024 threads leaves the same
 // list: each of its threads holds the groups of 1024 / NTH consecutive ones of the 1024.
