@@ -2265,18 +2265,19 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                 return SALS_ERR_HIP;
             double most = 0.0, square_sum = 0.0;
             for (int i = 0; i < n_tiles; ++i) { most = std::max(most, h_found[2 * i]); square_sum += h_found[2 * i + 1]; }
-           
             converged = most <= 1e-11;
             if (converged || !series || !(square_sum <= kSeriesNorm * kSeriesNorm)) break;
-            // exp(E) G from the inside out: G + E (G + E/2 (G + E/3 (G + E/4 G)))
+            // exp(E) G from the inside out: G + E (G + E/2 (G + E/3 (G + E/4 G))).  A product may be written over G, but not over the matrix
+            // it multiplies, whose rows other workgroups still read: one term alone, which multiplies G, goes to the other matrix.
+            const int terms = square_sum <= 1e-18 ? 1 : square_sum <= 4e-8 ? 2 : 4;
             double *X = rows, *Y = other;
-            for (int k = square_sum <= 1e-18 ? 1 : square_sum <= 4e-8 ? 2 : 4; k >= 1; --k) {
-                if (k == 1) Y = rows;
+            for (int k = terms; k >= 1; --k) {
+                Y = k == 1 && X != rows ? rows : X == other ? third : other;
                 hipLaunchKernelGGL((calib_apply_kernel<double, true>), tile_grid, prod, (prod_lds<double, double, true>()), st, C, X, rows,
                                    1.0 / k, Y, D);
                 X = Y;
-                Y = X == other ? third : other;
             }
+            if (terms == 1) std::swap(rows, other);
             if (!row_norms(rows)) return SALS_ERR_HIP;
             lead = leading();
         }
