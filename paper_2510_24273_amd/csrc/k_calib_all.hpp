@@ -388,7 +388,11 @@ __global__ __launch_bounds__(kProdThreads) void calib_angles_kernel(const double
 // saves a transformation of ten (weights 0, 0.1, 0.3, 1 and 3 of its square: 5.93, 5.17, 5.15, 5.21 and 5.54 ms at D = 1024, r = 640;
 // 6.0, 5.0, 5.3, 6.8 and 7.4 with eigenvalues within 1e-3 of each other).  First the products (fp32) and the workgroups'
 // shares of `off`, [share][row]: a row of tile I has D / 64 + I of them, two from a tile before its own, one from its own and from later ones ...
+//
+// Products and norms are scaled by the power of two that takes the largest norm below one: any covariance that fp64 holds has products
+// that floats hold (angles do not depend on the scale).
 constexpr double kAllDamp = 0.1, kAllOpen = 1e-24, kAllTail = 1e-3;
+__device__ __forceinline__ double all_scale(const double* __restrict__ norm) { return ldexp(1.0, -__builtin_amdgcn_frexp_exp(norm[0])); }
 struct AllPair { bool counts; double d, h2; };
 __device__ __forceinline__ AllPair all_pair(double ni, double nj, double ab, double least)
 {
@@ -399,7 +403,7 @@ __global__ __launch_bounds__(kProdThreads) void calib_gram_kernel(const double* 
                                                                   float* __restrict__ W, float* __restrict__ off)
 {
     __shared__ float s_off[2][4][64];   // of the tile's rows by 16-column block, of its columns by 16-row block (the diagonal: all the former)
-    const double lead = 0.999 * norm[r - 1] * norm[r - 1], least = kAllTail * lead;
+    const double unit = all_scale(norm), n_r = norm[r - 1] * unit, lead = 0.999 * n_r * n_r, least = kAllTail * lead;
     const SymTile tile = sym_tile(blockIdx.x, D);
     const int lane = threadIdx.x & 63, l16 = lane & 15, kg = lane >> 4;
     const int i0 = tile.row * 64, j0 = tile.col * 64 + tile.half * 32;
@@ -409,10 +413,10 @@ __global__ __launch_bounds__(kProdThreads) void calib_gram_kernel(const double* 
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int at = rb * 16 + mma_tile<double>::row(kg, e), i = i0 + at;
-            const double ab = v[e];
+            const double ab = v[e] * unit * unit;
             W[(size_t)i * D + j] = (float)ab;
             if (both) W[(size_t)j * D + i] = (float)ab;
-            const AllPair p = all_pair(norm[i], norm[j], ab, least);
+            const AllPair p = all_pair(norm[i] * unit, norm[j] * unit, ab, least);
             const float share = i != j && p.counts ? (float)(ab * ab * rsqrt_f64(p.h2)) : 0.f;
             col += share;
             const float t = row16_sum(share);
@@ -445,7 +449,7 @@ __global__ __launch_bounds__(256) void calib_all_angles_kernel(const float* __re
     static_assert(kAngleRows == 8 && kCalThreads == 256, "32 lanes a row; D is a multiple of the columns");
     __shared__ double s_sum[4];
     __shared__ float s_off[kAngleRows];
-    const double lead = 0.999 * norm[r - 1] * norm[r - 1], least = kAllTail * lead;
+    const double unit = all_scale(norm), n_r = norm[r - 1] * unit, lead = 0.999 * n_r * n_r, least = kAllTail * lead;
     const int tid = threadIdx.x, i0 = blockIdx.x * kAngleRows, j = blockIdx.y * 256 + tid, nb = D / 64;
     float w[kAngleRows];
 #pragma unroll
@@ -459,12 +463,12 @@ __global__ __launch_bounds__(256) void calib_all_angles_kernel(const float* __re
     for (int o = 16; o > 0; o >>= 1) mine += __shfl_xor(mine, o, kWave);
     if ((tid & 31) == 0) s_off[tid >> 5] = mine;
     __syncthreads();
-    const double nj = norm[j];
+    const double nj = norm[j] * unit;
     double sum = 0.0;
 #pragma unroll
     for (int u = 0; u < kAngleRows; ++u) {
         const int i = i0 + u;
-        const double ab = w[u], ni = norm[i], o = (double)s_off[u] + off_j;
+        const double ab = w[u], ni = norm[i] * unit, o = (double)s_off[u] + off_j;
         const AllPair p = all_pair(ni, nj, ab, least);
         const bool counts = p.counts && i != j;
         const double s = counts ? ab * rsqrt_f64(fma(kAllDamp * o, o, p.h2)) : 0.0;

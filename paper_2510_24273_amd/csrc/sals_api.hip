@@ -29,6 +29,7 @@
 #include "k_qvalue.hpp"
 #include "k_value.hpp"
 #include "k_window.hpp"
+#include "polar_plan.hpp"
 
 using namespace sals;
 
@@ -2031,8 +2032,6 @@ namespace {
 // symmetric products computed whole (1024 4.8, 2048 21.6 with half of them).
 constexpr int kAllMaxD = 3072;
 inline int all_first(int D) { return D <= 2048 ? 1 : 3; }
-// |E| at most: larger angles gain nothing (4, 6 and 10: 5.13, 5.11 and 5.11 ms at D = 1024; 5.43, 5.25, 5.28 with a spectrum c^-2)
-constexpr double kAllCap = 6.0;
 // the series of the exponential: cut behind E^4 it differs from an orthogonal matrix by |E|^6 / 72
 constexpr double kSeriesNorm = 4e-3;
 // the product kernels' dynamic LDS, beyond the default limit
@@ -2179,47 +2178,37 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             // (a matrix on which the transformations gain little, as with eigenvalues that repeat or rows of very different norms
             // in no order, gets a sweep in between)
             const double now = std::sqrt(e2);
+            const PolarPlan P = polar_plan(a2);
             if (now <= kSeriesNorm) {
                 worst = now;
                 last = 0.0;   // (what the series leaves is for sweeps)
                 settled = true;
                 if (!row_norms(rows)) return SALS_ERR_HIP;
                 lead = leading();
+            } else if (!std::isfinite(now) || P.n == 0) {
+                last = 0.0;   // (sums that are no numbers: a sweep)
+                if (done >= max_sweeps && !row_norms(rows)) return SALS_ERR_HIP;
+                continue;
             } else {
                 last = now < 0.9 * last ? now : 0.0;
-                // |E| is at most the fourth root of the sum of squares of E E^T; beyond kAllCap E is scaled down to it
-                const double bound = std::sqrt(std::sqrt(a2)), tau = std::min(1.0, kAllCap / bound), tb = tau * bound;
-                // singular values of (I + tau E) / top: low .. 1
-                const double top = std::sqrt(1.0 + tb * tb);
-                double low = 1.0 / top;
-                auto scale_of = [&]() {   // of the next step, and its lower bound behind it
-                    const double a = low < 0.9985 ? std::sqrt(3.0 / (1.0 + low + low * low)) : 1.0;
-                    const double x = a * low;
-                    low = 0.5 * x * (3.0 - x * x);
-                    return a;
-                };
-                // (behind a step that leaves them above 0.9985, or one of angles so small to begin with, one more is the last one)
-                const bool one = low >= 0.9985;
-                const double a1 = scale_of(), w = 0.5 * a1 * a1 * a1 / (top * top * top), c1 = 1.5 * a1 / top - w;
+                const double w = 0.5 * P.a[0] * P.a[0] * P.a[0] / (P.top * P.top * P.top), c1 = 1.5 * P.a[0] / P.top - w;
                 uint32_t *X = reinterpret_cast<uint32_t*>(other), *X2 = X + (size_t)D * D, *const Y = E;
-                auto polar = [&](auto n, bool last, const uint32_t* L, const uint32_t* R, double f, double d, double s, const uint32_t* S, double t,
+                auto polar = [&](auto n, bool fp32, const uint32_t* L, const uint32_t* R, double f, double d, double s, const uint32_t* S, double t,
                                  const uint32_t* T, uint32_t* O) {
                     constexpr int N = decltype(n)::value;
-                    if (last) hipLaunchKernelGGL((calib_polar_kernel<N, false, true>), tile_grid, prod, kPairLds, st, L, R, D, (float)f, (float)d,
+                    if (fp32) hipLaunchKernelGGL((calib_polar_kernel<N, false, true>), tile_grid, prod, kPairLds, st, L, R, D, (float)f, (float)d,
                                                  (float)s, S, (float)t, T, O, nullptr);
                     else hipLaunchKernelGGL((calib_polar_kernel<N, false, false>), tile_grid, prod, kPairLds, st, L, R, D, (float)f, (float)d,
                                             (float)s, S, (float)t, T, O, nullptr);
                 };
-                bool last = one || low >= 0.9985;
-                polar(std::integral_constant<int, 2>{}, last, A, E, w * tau * tau * tau, c1, c1 * tau, E, -w * tau * tau, A, X);
-                while (!last) {
-                    const double a = scale_of();
-                    last = low >= 0.9985;
+                polar(std::integral_constant<int, 2>{}, P.n == 1, A, E, w * P.tau * P.tau * P.tau, c1, c1 * P.tau, E, -w * P.tau * P.tau, A, X);
+                for (int k = 1; k < P.n; ++k) {
+                    const double a = P.a[k];
                     polar(std::integral_constant<int, 0>{}, false, X, X, 1.0, 0.0, 0.0, nullptr, 0.0, nullptr, Y);
-                    polar(std::integral_constant<int, 1>{}, last, X, Y, -0.5 * a * a * a, 0.0, 1.5 * a, X, 0.0, nullptr, X2);
+                    polar(std::integral_constant<int, 1>{}, k == P.n - 1, X, Y, -0.5 * a * a * a, 0.0, 1.5 * a, X, 0.0, nullptr, X2);
                     std::swap(X, X2);
                 }
-                if (!one) {
+                if (P.one_more) {
                     float *const x = reinterpret_cast<float*>(X), *const x2 = reinterpret_cast<float*>(X2), *const y = reinterpret_cast<float*>(Y);
                     hipLaunchKernelGGL(calib_polar_square_kernel, sym_grid, prod, kSymLds, st, x, D, y);
                     hipLaunchKernelGGL(calib_polar_last_kernel, tile_grid, prod, (prod_lds<float, float, false>()), st, x, y, D, -0.5f, 1.5f,

@@ -226,6 +226,20 @@ def test_the_call_repeats_bit_for_bit(D, r, decay, mixed):
         assert torch.equal(lam, first[1]) and torch.equal(U, first[2]) and torch.equal(rows, first[0])
 
 
+@pytest.mark.parametrize("power", [200, -200, 400, -400])
+@pytest.mark.parametrize("D,r,decay,mixed", [(512, 512, 0.25, True), (1024, 200, 1.0, False)])
+def test_scale_of_the_covariance_changes_nothing(D, r, decay, mixed, power):
+    """2^200 C and 2^-200 C, far outside the range of fp32: the same steps, and 2^200 times the eigenvalues, to the last bit (every
+    quantity scales by a power of two)."""
+    print(f"[case] eigenvectors of 2^{power} C, D={D} r={r} decay={decay}", flush=True)
+    C = _spectrum_on_device(D, decay, mixed)
+    lam, U, sweeps = binding.calib_eigenvectors(C.clone(), r, torch.float32)
+    lam2, U2, sweeps2 = binding.calib_eigenvectors(C * 2.0 ** power, r, torch.float32)
+    torch.cuda.synchronize()
+    assert 0 < sweeps2 == sweeps
+    assert torch.equal(lam2, lam * 2.0 ** power) and torch.equal(U2, U)
+
+
 def _eig_with_workspace(C, r, nbytes):
     """The call on a workspace of `nbytes`, which lies before bytes that must stay as they are."""
     D = C.shape[0]
