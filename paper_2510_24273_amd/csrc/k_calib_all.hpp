@@ -11,12 +11,15 @@
 //                  where it is small.  Rows are sorted by norm, so that the pairs with large angles lie near the diagonal; those
 //                  inside and next to a 32-row block are rotated one by one first (three Jacobi steps).
 //
-// The polar factor is found by Newton-Schulz steps in pairs of bf16, the last one in fp32 (X <- a X - b X X^T X, scaled by the
+// The polar factor is found by Newton-Schulz steps in pairs of bf16, the last one in fp32 (X <- a X - b (X X^T) X, scaled by the
 // bounds of its singular values: J. Chen, E. Chow, "A stable scaling of Newton-Schulz for improving the sign function computation of
-// a Hermitian matrix", 2014), and only *found* there: what is left, delta = X X^T - I (1e-6), is formed in fp64 and taken out to
-// third order, G <- (I - delta / 2 + 3/8 delta^2) X G, with fp64 products.  What a transformation does to G is orthogonal to 1e-16
-// like a rotation made in fp64, and which transformation is made decides nothing but how fast the rows converge.  (D = 1024, r = 640:
-// eigenvalues off by 1.5e-14 of themselves against a 64-bit eigensolver, by 2.0e-14 with sweeps alone.)
+// a Hermitian matrix", 2014), and only *found* there: what is left, delta = X X^T - I (at most 1e-5: 6.7e-6 where the last step begins
+// with the smallest singular values it may, and the rounding of fp32; measured 5e-7 to 4e-6), is formed in fp64 and taken out to third
+// order, G <- (I - delta / 2 + 3/8 delta^2) X G, with fp64 products.  The fourth, 5/16 delta^3, is below 4e-16, so what a transformation
+// does to G is orthogonal to the rounding of those products (G^T G changed by 2e-15 to 3e-15 of its norm, D = 256 to 1024), and which transformation is made decides
+// nothing but how fast the rows converge.  (D = 1024, r = 640: eigenvalues off by 1.2e-14 of themselves against a 64-bit
+// eigensolver, by 2.4e-14 with sweeps alone.)  With X (X X^T) in the place of (X X^T) X, which is the same for a normal X only, rounding
+// adds up from step to step: delta 2e-5 to 4e-5, G^T G changed by 1.1e-14 at D = 256.
 #pragma once
 #include "common.hpp"
 #include "k_calib.hpp"
@@ -251,6 +254,7 @@ __device__ __forceinline__ float pair_value(uint32_t w) { return bf16hi(w) + bf1
 
 // The same for A B^T of such matrices: hi hi + hi lo + lo hi on the bf16 matrix cores, summed in fp32.  A step is 64 elements of a
 // row, 32 for either half of the waves.  Bound by what a compute unit draws, 13 us a product at D = 1024, where fp32 instructions take 22.
+// finish(i, j, v): rows i .. i + 3 of column j, by the first four waves.
 constexpr size_t kPairLds = (size_t)kProdStages * 32768;
 template <typename Finish>
 __device__ __forceinline__ void calib_product_pairs(const uint32_t* A, const uint32_t* B, int D, Finish finish)
@@ -322,9 +326,12 @@ __device__ __forceinline__ void calib_product_pairs(const uint32_t* A, const uin
     __syncthreads();
     if (ks == 0) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int u = i >> 3, v = (i >> 2) & 1, e = i & 3;
-            finish(r0 + (part >> 1) * 32 + u * 16 + 4 * kg + e, c0 + (part & 1) * 32 + v * 16 + l16, acc[u][v][e] + red[i * 64 + lane]);
+        for (int i = 0; i < 4; ++i) {
+            const int u = i >> 1, v = i & 1;
+            f32x4 x;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = acc[u][v][e] + red[(i * 4 + e) * 64 + lane];
+            finish(r0 + (part >> 1) * 32 + u * 16 + 4 * kg, c0 + (part & 1) * 32 + v * 16 + l16, x);
         }
     }
 }
@@ -483,22 +490,29 @@ __global__ __launch_bounds__(256) void calib_all_angles_kernel(const float* __re
 }
 
 // ---- Polar factor -----------------------------------------------------------------------------------------------------
-// O = d I + s S + t T + f A B^T (S, T: N > 0, N > 1) from pairs of bf16, left as such pairs or (LAST) in fp32.  SQUARE: also the sum
-// of squares of every tile of O.
+// O = d I + s S + t T + f A B^T (S, T: N > 0, N > 1) from pairs of bf16, left as such pairs or (LAST) in fp32; N > 0: also its transpose,
+// OT (16 bytes a lane).  SQUARE: also the sum of squares of every tile of O.
 template <int N, bool SQUARE, bool LAST>
 __global__ __launch_bounds__(kProdThreads) void calib_polar_kernel(const uint32_t* A, const uint32_t* B, int D, float f, float d, float s,
-                                                                   const uint32_t* S, float t, const uint32_t* T, void* O, double* square)
+                                                                   const uint32_t* S, float t, const uint32_t* T, uint32_t* O, uint32_t* OT,
+                                                                   double* square)
 {
     __shared__ double s_sum[4];
     double sum = 0.0;
-    calib_product_pairs(A, B, D, [&](int i, int j, float v) {
-        const size_t at = (size_t)i * D + j;
-        float o = f * v;
-        if (N > 0) o = fmaf(s, pair_value(S[at]), o);
-        if (N > 1) { o = fmaf(t, pair_value(T[at]), o); o += i == j ? d : 0.f; }
-        if (LAST) static_cast<float*>(O)[at] = o;
-        else static_cast<uint32_t*>(O)[at] = pack_pair(o);
-        if (SQUARE) sum += (double)o * (double)o;
+    calib_product_pairs(A, B, D, [&](int i0, int j, const f32x4& v) {
+        u32x4 w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = i0 + e;
+            const size_t at = (size_t)i * D + j;
+            float o = f * v[e];
+            if (N > 0) o = fmaf(s, pair_value(S[at]), o);
+            if (N > 1) { o = fmaf(t, pair_value(T[at]), o); o += i == j ? d : 0.f; }
+            w[e] = LAST ? __float_as_uint(o) : pack_pair(o);
+            O[at] = w[e];
+            if (SQUARE) sum += (double)o * (double)o;
+        }
+        if (N > 0) *reinterpret_cast<u32x4*>(OT + (size_t)j * D + i0) = w;
     });
     if (!SQUARE) return;
 #pragma unroll
@@ -553,9 +567,12 @@ __global__ __launch_bounds__(kProdThreads) void calib_defect_kernel(const float*
 // delta <- -delta / 2 + 3/8 delta^2 (the square, 1e-12, from the rounded one)
 __global__ __launch_bounds__(kProdThreads) void calib_correction_kernel(const uint32_t* rounded, int D, double* delta)
 {
-    calib_product_pairs(rounded, rounded, D, [&](int i, int j, float v) {
-        const size_t at = (size_t)i * D + j;
-        delta[at] = fma(0.375, (double)v, -0.5 * delta[at]);
+    calib_product_pairs(rounded, rounded, D, [&](int i0, int j, const f32x4& v) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const size_t at = (size_t)(i0 + e) * D + j;
+            delta[at] = fma(0.375, (double)v[e], -0.5 * delta[at]);
+        }
     });
 }
 

@@ -2166,7 +2166,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             hipLaunchKernelGGL(calib_all_angles_kernel, dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D, sorted, r, row_off,
                                E, all_found);
             hipLaunchKernelGGL((calib_polar_kernel<0, true, false>), tile_grid, prod, kPairLds, st, E, E, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr,
-                               A, square);
+                               A, nullptr, square);
             if (launch_status() != SALS_OK ||
                 hipMemcpyAsync(h_found, all_found, (size_t)(n_angles + n_tiles) * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
                 hipStreamSynchronize(st) != hipSuccess)
@@ -2192,27 +2192,31 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             } else {
                 last = now < 0.9 * last ? now : 0.0;
                 const double w = 0.5 * P.a[0] * P.a[0] * P.a[0] / (P.top * P.top * P.top), c1 = 1.5 * P.a[0] / P.top - w;
+                // X and its transpose XT.  The defect of (X X^T) X is quadratic in that of X; X (X X^T) is the same only as long as X
+                // commutes with its transpose, and what rounding takes from that would stay.
                 uint32_t *X = reinterpret_cast<uint32_t*>(other), *X2 = X + (size_t)D * D, *const Y = E;
+                uint32_t *XT = reinterpret_cast<uint32_t*>(C), *XT2 = XT + (size_t)D * D;
                 auto polar = [&](auto n, bool fp32, const uint32_t* L, const uint32_t* R, double f, double d, double s, const uint32_t* S, double t,
-                                 const uint32_t* T, uint32_t* O) {
+                                 const uint32_t* T, uint32_t* O, uint32_t* OT) {
                     constexpr int N = decltype(n)::value;
                     if (fp32) hipLaunchKernelGGL((calib_polar_kernel<N, false, true>), tile_grid, prod, kPairLds, st, L, R, D, (float)f, (float)d,
-                                                 (float)s, S, (float)t, T, O, nullptr);
+                                                 (float)s, S, (float)t, T, O, OT, nullptr);
                     else hipLaunchKernelGGL((calib_polar_kernel<N, false, false>), tile_grid, prod, kPairLds, st, L, R, D, (float)f, (float)d,
-                                            (float)s, S, (float)t, T, O, nullptr);
+                                            (float)s, S, (float)t, T, O, OT, nullptr);
                 };
-                polar(std::integral_constant<int, 2>{}, P.n == 1, A, E, w * P.tau * P.tau * P.tau, c1, c1 * P.tau, E, -w * P.tau * P.tau, A, X);
+                polar(std::integral_constant<int, 2>{}, P.n == 1, A, E, w * P.tau * P.tau * P.tau, c1, c1 * P.tau, E, -w * P.tau * P.tau, A, X, XT);
                 for (int k = 1; k < P.n; ++k) {
                     const double a = P.a[k];
-                    polar(std::integral_constant<int, 0>{}, false, X, X, 1.0, 0.0, 0.0, nullptr, 0.0, nullptr, Y);
-                    polar(std::integral_constant<int, 1>{}, k == P.n - 1, X, Y, -0.5 * a * a * a, 0.0, 1.5 * a, X, 0.0, nullptr, X2);
+                    polar(std::integral_constant<int, 0>{}, false, X, X, 1.0, 0.0, 0.0, nullptr, 0.0, nullptr, Y, nullptr);
+                    polar(std::integral_constant<int, 1>{}, k == P.n - 1, Y, XT, -0.5 * a * a * a, 0.0, 1.5 * a, X, 0.0, nullptr, X2, XT2);
                     std::swap(X, X2);
+                    std::swap(XT, XT2);
                 }
                 if (P.one_more) {
                     float *const x = reinterpret_cast<float*>(X), *const x2 = reinterpret_cast<float*>(X2), *const y = reinterpret_cast<float*>(Y);
                     hipLaunchKernelGGL(calib_polar_square_kernel, sym_grid, prod, kSymLds, st, x, D, y);
-                    hipLaunchKernelGGL(calib_polar_last_kernel, tile_grid, prod, (prod_lds<float, float, false>()), st, x, y, D, -0.5f, 1.5f,
-                                       x, x2);
+                    hipLaunchKernelGGL(calib_polar_last_kernel, tile_grid, prod, (prod_lds<float, float, false>()), st, y,
+                                       reinterpret_cast<const float*>(XT), D, -0.5f, 1.5f, x, x2);
                     std::swap(X, X2);
                 }
                 hipLaunchKernelGGL(calib_defect_kernel, sym_grid, prod, kSymLds, st, reinterpret_cast<const float*>(X), D,

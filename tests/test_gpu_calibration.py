@@ -226,6 +226,38 @@ def test_the_call_repeats_bit_for_bit(D, r, decay, mixed):
         assert torch.equal(lam, first[1]) and torch.equal(U, first[2]) and torch.equal(rows, first[0])
 
 
+@pytest.mark.parametrize("D", [256, 512, 1024])
+def test_a_transformation_is_orthogonal_to_rounding(D):
+    """One sweep and one transformation of all rows, by the matrices they leave in the workspace: the corrected rows Q G (the factor's
+    place), the rows before, G, and the rows X G, X the polar factor as it was found (the two partial sums).  Eigenvalues between 1 and 2,
+    so that G can be divided by."""
+    print(f"[case] a transformation of all rows, D={D}", flush=True)
+    rng = np.random.default_rng(D)
+    V, _ = np.linalg.qr(rng.standard_normal((D, D)))
+    C = (V * np.linspace(1.0, 2.0, D)) @ V.T
+    C = 0.5 * (C + C.T)
+    nbytes = binding._lib.sals_calib_eigenvectors_workspace_bytes(D)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=gu.DEV)
+    lam = torch.empty(D, dtype=torch.float64, device=gu.DEV)
+    U = torch.empty(D, D, dtype=torch.float32, device=gu.DEV)
+    st = binding._lib.sals_calib_eigenvectors(gu.to_dev(C).data_ptr(), D, D, binding.SALS_F32, lam.data_ptr(), U.data_ptr(), ws.data_ptr(),
+                                              nbytes, 2, None, None)
+    torch.cuda.synchronize()
+    assert binding.status_string(st) == "SALS_OK"
+    size = 8 * D * D
+    QG, G, XG = (ws[at:at + size].cpu().numpy().view(np.float64).reshape(D, D) for at in (0, nbytes - 2 * size, nbytes - size))
+    assert np.max(np.abs(G.T @ G - C)) <= 1e-12 and np.max(np.abs(QG - G)) > 1e-2   # (the premise)
+    X = XG @ np.linalg.inv(G)
+    delta, change = np.linalg.norm(X @ X.T - np.eye(D), 2), np.linalg.norm(QG.T @ QG - G.T @ G, 2)
+    print(f"    X X^T - I {delta:.2e}, (Q G)^T Q G - G^T G {change:.2e}", flush=True)
+    # The last step squares what is left of singular values from 0.9985 on, 3/4 (1 - 0.9985^2)^2 = 6.7e-6; its fp32 elements and sums of D
+    # such products leave 2^-24 sqrt(D) each (2e-6 at D = 1024)
+    assert delta <= 6.7e-6 + 2.0 ** -24 * D ** 0.5
+    # three orders of that are taken out (what is left is 2e-16); two fp64 products make the rows and two the comparison, sums of D terms
+    # that leave 2 sqrt(D) 2^-53 each, of a matrix of norm sqrt(2)
+    assert change <= 4 * 2 * D ** 0.5 * 2.0 ** -53
+
+
 @pytest.mark.parametrize("power", [200, -200, 400, -400])
 @pytest.mark.parametrize("D,r,decay,mixed", [(512, 512, 0.25, True), (1024, 200, 1.0, False)])
 def test_scale_of_the_covariance_changes_nothing(D, r, decay, mixed, power):
