@@ -2149,11 +2149,13 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     };
     const dim3 tile_grid(D / 64, D / 64), sym_grid(n_tiles), prod(kProdThreads);
     bool settled = false;
+    bool moved = false;    // `lead` is from before a transformation
     double last = 1e300;   // |E| of the transformation before, infinite behind a sweep
     while (done < max_sweeps && !converged) {
         double worst = 0.0;   // largest rotation that is known to have been left behind
         if (all && !settled && done >= all_first(D) && last > 0.0) {
             // One transformation of all rows.
+            moved = true;
             inside_step();
             block_step(kJacNearEven);
             block_step(kJacNearOdd);
@@ -2185,6 +2187,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                 settled = true;
                 if (!row_norms(rows)) return SALS_ERR_HIP;
                 lead = leading();
+                moved = false;
             } else if (!std::isfinite(now) || P.n == 0) {
                 last = 0.0;   // (sums that are no numbers: a sweep)
                 if (done >= max_sweeps && !row_norms(rows)) return SALS_ERR_HIP;
@@ -2232,6 +2235,11 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                 continue;
             }
         } else {
+            if (moved) {   // (the r-th norm may have fallen far: rows below the old one would not be asked to have converged)
+                if (!row_norms(rows)) return SALS_ERR_HIP;
+                lead = leading();
+                moved = false;
+            }
             if (hipMemsetAsync(conv, 0, (size_t)n_blocks * 8, st) != hipSuccess) return SALS_ERR_HIP;
             inside_step();
             for (int step = 0; step < n_steps; ++step) block_step(step);

@@ -197,6 +197,32 @@ def test_transformations_of_all_rows_at_once(D, r, kind):
     assert np.max(np.linalg.norm(V @ C - norm[lead, None] * V, axis=1)) <= (2e-11 + eps) * norm[lead[0]]
 
 
+@pytest.mark.parametrize("large,width,n_large,r", [(1e5, 1e-11, 2, 3), (1e5, 1e-11, 4, 8), (10.0, 1e-10, 4, 8), (1e3, 1e-10, 4, 12)])
+def test_rows_of_a_tight_cluster_are_asked_to_have_converged(large, width, n_large, r):
+    """A few large eigenvalues and all others within a relative `width`, the r-th among these: its row's norm falls far while the large
+    rows are found, and the call must not stop by what it was then.  (Sweeps and transformations take turns here.)"""
+    print(f"[case] cluster of width {width:g} below {n_large} eigenvalues around {large:g}, r={r}", flush=True)
+    D = 256
+    for seed in range(4):
+        rng = np.random.default_rng(seed)
+        Q, _ = np.linalg.qr(rng.standard_normal((D, D)))
+        C = (Q * np.concatenate([large * (1.0 + rng.random(n_large)), 1.0 + width * rng.random(D - n_large)])) @ Q.T
+        Cg = gu.to_dev(0.5 * (C + C.T))
+        _, _, sweeps = binding.calib_eigenvectors(Cg, r, torch.float32)
+        torch.cuda.synchronize()
+        assert sweeps > 0
+        rows = Cg.cpu().numpy()
+        lam = np.linalg.norm(rows, axis=1)
+        order = np.argsort(-lam)
+        V, lam = rows[order] / lam[order, None], lam[order]
+        cos = np.abs(V[:r] @ V.T)
+        cos[np.arange(r), np.arange(r)] = 0.0
+        ab = cos * np.sqrt(np.outer(lam[:r], lam))
+        turn = ab / np.maximum(np.maximum(np.abs(lam[:r, None] - lam), 2.0 * ab), 1e-300)
+        # rows orthogonal to working precision are not rotated (1e-15 there, and sums of D products here)
+        assert np.max(turn[cos > 4e-15], initial=0.0) <= 1e-11, (seed, sweeps)
+
+
 def _spectrum_on_device(D, decay, mixed, seed=1):
     """A covariance of 4 D keys whose channels decay as c^-decay, along directions that mix all channels if `mixed`."""
     g = torch.Generator(device=gu.DEV)
