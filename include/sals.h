@@ -405,11 +405,11 @@ sals_status sals_overlap_score(sals_ctx* ctx, const void* q, const int32_t* q_po
  *              (SALS_ERR_WORKSPACE below what the sweeps need): all rotations are then made by sweeps, whose
  *              sums are spread over as much of the device as the scratch allows (D = 1024: 5.1 ms with the full size,
  *              11.2 with 8 D^2 + 4000 D bytes, 16.9 with the least)
- *   max_sweeps at least 1 (host): a sweep rotates every pair of rows once (a transformation of all rows counts as
- *              one); the call stops when no rotation that
- *              involves one of the r largest rows would turn by more than 1e-11 (found by a sweep, or from the Gram
- *              matrix of all rows behind a sweep of small rotations; with a workspace of the full size the last,
- *              smallest rotations are made all at once), or after max_sweeps
+ *   max_sweeps at least 1 (host): a sweep rotates every pair of rows once (transformations of all rows, which come
+ *              between sweeps, are not counted); the call stops when no rotation that involves one of the r largest
+ *              rows would turn by more than 1e-11 (found by a sweep, or from the Gram matrix of all rows behind a sweep
+ *              of small rotations; with a workspace of the full size the last, smallest rotations are made all at
+ *              once), or after max_sweeps
  *   sweeps     host int32, out (may be NULL): sweeps run; the negative of that number if the limit was reached
  *              before convergence (the results are then the current approximation); 0 if there was nothing to
  *              rotate (C is zero, or not finite: then its rows come back as they are)

@@ -2151,6 +2151,8 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     bool settled = false;
     bool moved = false;    // `lead` is from before a transformation
     double last = 1e300;   // |E| of the transformation before, infinite behind a sweep
+    // (The limit is one of sweeps, so that one which is enough without transformations is enough with them.  Between two sweeps |E|
+    // falls by a tenth at least with each, from at most D to kSeriesNorm.)
     while (done < max_sweeps && !converged) {
         double worst = 0.0;   // largest rotation that is known to have been left behind
         if (all && !settled && done >= all_first(D) && last > 0.0) {
@@ -2173,7 +2175,6 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                 hipMemcpyAsync(h_found, all_found, (size_t)(n_angles + n_tiles) * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
                 hipStreamSynchronize(st) != hipSuccess)
                 return SALS_ERR_HIP;
-            ++done;
             double e2 = 0.0, a2 = 0.0;
             for (int i = 0; i < n_angles; ++i) e2 += h_found[i];
             for (int i = 0; i < n_tiles; ++i) a2 += h_found[n_angles + i];
@@ -2190,7 +2191,6 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                 moved = false;
             } else if (!std::isfinite(now) || P.n == 0) {
                 last = 0.0;   // (sums that are no numbers: a sweep)
-                if (done >= max_sweeps && !row_norms(rows)) return SALS_ERR_HIP;
                 continue;
             } else {
                 last = now < 0.9 * last ? now : 0.0;
@@ -2231,7 +2231,6 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                                    1.0, other, D);
                 std::swap(rows, other);
                 if (launch_status() != SALS_OK) return SALS_ERR_HIP;
-                if (done >= max_sweeps && !row_norms(rows)) return SALS_ERR_HIP;
                 continue;
             }
         } else {

@@ -253,35 +253,39 @@ def test_the_call_repeats_bit_for_bit(D, r, decay, mixed):
 
 
 @pytest.mark.parametrize("D", [256, 512, 1024])
-def test_a_transformation_is_orthogonal_to_rounding(D):
-    """One sweep and one transformation of all rows, by the matrices they leave in the workspace: the corrected rows Q G (the factor's
-    place), the rows before, G, and the rows X G, X the polar factor as it was found (the two partial sums).  Eigenvalues between 1 and 2,
-    so that G can be divided by."""
-    print(f"[case] a transformation of all rows, D={D}", flush=True)
+def test_transformations_are_orthogonal_to_rounding(D):
+    """What transforms the rows leaves their products G^T G as they are: those behind the first sweep (a call of one sweep leaves its
+    rows in the factor's place) against those at the end, which lie in one of the workspace's three matrices.  Eigenvalues between
+    1 and 2, so that no direction of the rows is too small to show it."""
+    print(f"[case] orthogonality of the transformations, D={D}", flush=True)
     rng = np.random.default_rng(D)
     V, _ = np.linalg.qr(rng.standard_normal((D, D)))
     C = (V * np.linspace(1.0, 2.0, D)) @ V.T
     C = 0.5 * (C + C.T)
-    nbytes = binding._lib.sals_calib_eigenvectors_workspace_bytes(D)
-    ws = torch.empty(nbytes, dtype=torch.uint8, device=gu.DEV)
+    nbytes, size = binding._lib.sals_calib_eigenvectors_workspace_bytes(D), 8 * D * D
     lam = torch.empty(D, dtype=torch.float64, device=gu.DEV)
     U = torch.empty(D, D, dtype=torch.float32, device=gu.DEV)
-    st = binding._lib.sals_calib_eigenvectors(gu.to_dev(C).data_ptr(), D, D, binding.SALS_F32, lam.data_ptr(), U.data_ptr(), ws.data_ptr(),
-                                              nbytes, 2, None, None)
-    torch.cuda.synchronize()
-    assert binding.status_string(st) == "SALS_OK"
-    size = 8 * D * D
-    QG, G, XG = (ws[at:at + size].cpu().numpy().view(np.float64).reshape(D, D) for at in (0, nbytes - 2 * size, nbytes - size))
-    assert np.max(np.abs(G.T @ G - C)) <= 1e-12 and np.max(np.abs(QG - G)) > 1e-2   # (the premise)
-    X = XG @ np.linalg.inv(G)
-    delta, change = np.linalg.norm(X @ X.T - np.eye(D), 2), np.linalg.norm(QG.T @ QG - G.T @ G, 2)
-    print(f"    X X^T - I {delta:.2e}, (Q G)^T Q G - G^T G {change:.2e}", flush=True)
-    # The last step squares what is left of singular values from 0.9985 on, 3/4 (1 - 0.9985^2)^2 = 6.7e-6; its fp32 elements and sums of D
-    # such products leave 2^-24 sqrt(D) each (2e-6 at D = 1024)
-    assert delta <= 6.7e-6 + 2.0 ** -24 * D ** 0.5
-    # three orders of that are taken out (what is left is 2e-16); two fp64 products make the rows and two the comparison, sums of D terms
-    # that leave 2 sqrt(D) 2^-53 each, of a matrix of norm sqrt(2)
-    assert change <= 4 * 2 * D ** 0.5 * 2.0 ** -53
+
+    def products(limit):
+        ws = torch.zeros(nbytes, dtype=torch.uint8, device=gu.DEV)
+        n = ctypes.c_int32(0)
+        st = binding._lib.sals_calib_eigenvectors(gu.to_dev(C).data_ptr(), D, D, binding.SALS_F32, lam.data_ptr(), U.data_ptr(), ws.data_ptr(),
+                                                  nbytes, limit, ctypes.byref(n), None)
+        torch.cuda.synchronize()
+        assert binding.status_string(st) == "SALS_OK"
+        return n.value, [M.T @ M for M in (ws[at:at + size].cpu().numpy().view(np.float64).reshape(D, D)
+                                           for at in (0, nbytes - 2 * size, nbytes - size))]
+
+    n, behind_one = products(1)
+    assert n == -1 and np.max(np.abs(behind_one[0] - C)) <= 1e-12   # (the premise)
+    n, at_end = products(80)
+    assert n == 1                                                   # (no further sweep)
+    change = min(np.linalg.norm(P - behind_one[0], 2) for P in at_end if np.all(np.abs(P) < 10.0))
+    print(f"    G^T G changed by {change:.2e}", flush=True)
+    # A product with an orthogonal matrix, sums of D terms, leaves its elements off by about half a 2^-53 at random, a matrix of norm
+    # sqrt(D) 2^-53, and G^T G off by 2 sqrt(2) times that; two of them in each of at most eight transformations, which add up as squares.
+    # (What an X with X X^T - I = 3e-5 leaves behind three orders of correction is 2e-14 by itself.)
+    assert change <= 4 * 2.0 ** 1.5 * D ** 0.5 * 2.0 ** -53
 
 
 @pytest.mark.parametrize("power", [200, -200, 400, -400])
@@ -298,7 +302,7 @@ def test_scale_of_the_covariance_changes_nothing(D, r, decay, mixed, power):
     assert torch.equal(lam2, lam * 2.0 ** power) and torch.equal(U2, U)
 
 
-def _eig_with_workspace(C, r, nbytes):
+def _eig_with_workspace(C, r, nbytes, max_sweeps=80):
     """The call on a workspace of `nbytes`, which lies before bytes that must stay as they are."""
     D = C.shape[0]
     guard = 4096
@@ -307,7 +311,7 @@ def _eig_with_workspace(C, r, nbytes):
     U = torch.empty(D, r, dtype=torch.float32, device=gu.DEV)
     sweeps = ctypes.c_int32(0)
     st = binding._lib.sals_calib_eigenvectors(C.data_ptr(), D, r, binding.SALS_F32, lam.data_ptr(), U.data_ptr(), ws.data_ptr(), nbytes,
-                                              80, ctypes.byref(sweeps), None)
+                                              max_sweeps, ctypes.byref(sweeps), None)
     torch.cuda.synchronize()
     assert bool((ws[nbytes:] == 0xA5).all())
     return binding.status_string(st), lam.cpu().numpy(), sweeps.value
@@ -344,6 +348,24 @@ def test_eigenvectors_with_a_small_workspace(D, r):
     # series cut one term too early, or used at twice the angles it may be, leaves 1e-11 and more
     np.testing.assert_allclose(lams[full], lams[full - 1], rtol=2 * D / 32 * 16 * 2.0 ** -53)
     assert all(ran[full] < n for nbytes, n in ran.items() if nbytes != full)
+
+
+@pytest.mark.parametrize("D,r,large,width,n_large", [(256, 68, 10.0, 1e-10, 64), (256, 41, 1e4, 0.0, 40), (256, 20, 10.0, 1e-10, 16),
+                                                      (512, 200, 10.0, 1.0, 100)])
+def test_a_limit_of_sweeps_is_enough_with_transformations_too(D, r, large, width, n_large):
+    """The sweeps that a call takes without transformations are enough with them, also where the two take turns."""
+    print(f"[case] limit of sweeps, D={D}, cluster of width {width:g}", flush=True)
+    rng = np.random.default_rng(D + n_large)
+    Q, _ = np.linalg.qr(rng.standard_normal((D, D)))
+    C = (Q * np.concatenate([large * (1.0 + rng.random(n_large)), 1.0 + width * rng.random(D - n_large)])) @ Q.T
+    C = gu.to_dev(0.5 * (C + C.T))
+    full = binding._lib.sals_calib_eigenvectors_workspace_bytes(D)
+    status, alone, limit = _eig_with_workspace(C.clone(), r, full - 1)
+    assert status == "SALS_OK" and limit > 0
+    status, lam, sweeps = _eig_with_workspace(C.clone(), r, full, limit)
+    print(f"    sweeps {sweeps}, without transformations {limit}", flush=True)
+    assert status == "SALS_OK" and 0 < sweeps <= limit
+    np.testing.assert_allclose(lam[:r], alone[:r], rtol=1e-13)
 
 
 def test_eigenvectors_in_bf16_are_the_rounded_fp64_vectors():
