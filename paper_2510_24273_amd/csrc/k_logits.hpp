@@ -446,6 +446,7 @@ __device__ __forceinline__ void logits_tile(
     for (int nb = 0; nb < NB; ++nb) ok[nb] = (MULTI ? (tg * WT & 63) + nb * 32 + l32 : tok0 + (tg * NB + nb) * 32 + l32) < n;
     const int bs = MULTI ? seq_of(tg * WT) : b;          // sequence of this wave's tokens
     const bool seq_real = !MULTI || b + sw < B;          // (a sequence past the batch writes nothing)
+    const bool partial = MULTI && (HEADS > 1 || ksplit > 1);  // (tiles of several heads and sequences always have slices)
 #pragma unroll
     for (int m0 = 0; m0 < kGroupEnd; m0 += GB) {
         if (GFIX > 0 || m0 < G) {  // uniform
@@ -459,13 +460,13 @@ __device__ __forceinline__ void logits_tile(
                 for (int nb = 0; nb < NB; ++nb) {
                     const int slot = MULTI ? (tg * WT & 63) + nb * 32 + l32 : tok0 + (tg * NB + nb) * 32 + l32;
                     const size_t at = ((size_t)bs * H + g * G + m0 + mi) * lk + slot;
-                    if (MULTI && ksplit > 1) {  // uniform: this slice's share of the logit
+                    if (partial) {  // uniform: this slice's share of the logit
                         if (hi == 0 && slot < lk && seq_real) plogits[(size_t)kz * B * H * lk + at] = dot[m0 + mi][nb];
                     } else if (hi == 0 && slot < lk && seq_real) {
                         logits[at] = ok[nb] ? dot[m0 + mi][nb] : -INFINITY;
                     }
                 }
-            if (MULTI && ksplit > 1) continue;  // (statistics are taken when the slices are added up)
+            if (partial) continue;  // (statistics are taken when the slices are added up)
             // softmax statistics of this tile, per head: the waves' (max, sum exp) merged in wave order below
             float mx[GB], se[GB];
 #pragma unroll
@@ -490,15 +491,15 @@ __device__ __forceinline__ void logits_tile(
             }
         }
     }
-    if (MULTI && ksplit > 1) return;  // uniform
+    if (partial) return;  // uniform
     __syncthreads();
     // the waves' statistics, merged in wave order: those of a head, or (MULTI) of a sequence, whose single tile this is
     constexpr int WS = MULTI ? 64 / WT : NTG;  // waves to merge
-    if (tid < SQ * HEADS * G) {
-        const int u = idiv(tid, G), m = tid - u * G, sq = MULTI ? (unsigned)u / HEADS : 0, bt = b + sq, h2 = u - sq * HEADS;
-        float2 st = sStat[h2][sq * WS][m];
+    if (tid < (MULTI ? SQ : HEADS) * G) {
+        const int u = idiv(tid, G), m = tid - u * G, bt = MULTI ? b + u : b, h2 = MULTI ? 0 : u;
+        float2 st = sStat[h2][MULTI ? u * WS : 0][m];
 #pragma unroll
-        for (int t = 1; t < WS; ++t) st = stat_merge(st, sStat[h2][sq * WS + t][m]);
+        for (int t = 1; t < WS; ++t) st = stat_merge(st, sStat[h2][(MULTI ? u * WS : 0) + t][m]);
         if (!MULTI || bt < B) stats[((size_t)bt * H + (size_t)(g0 + h2) * G + m) * stats_stride + part] = st;
     }
 }

@@ -62,7 +62,7 @@ struct ProfRecord { int kernel; hipEvent_t start, stop; };
 
 // which logits kernel a context's shape gets: 1 = 2 heads x 256 tokens, 2 = 1 head x 128 tokens, 3 = 1 head x 64
 // tokens (then: slices of the latent axis per tile, 128-byte steps loaded ahead); n_parts = token tiles per head
-struct LogitsPlan { int pick, n_parts, ksplit, nst; };
+struct LogitsPlan { int pick, n_parts, ksplit, nst, forced = 0; };   // forced: slices that the tuning aid asks for
 
 struct sals_ctx {
     sals_desc d;
@@ -603,7 +603,7 @@ template <typename T> LogitsPlan plan_logits(const sals_desc& d)
         while (ks < kLsMaxSplit && tiles * ks < 512 && n_steps % (2 * ks) == 0 && n_steps / (2 * ks) >= (tiles * ks < 256 ? 8 : 24)) ks *= 2;
         if (const char* e = std::getenv("SALS_TUNE_MULTI_KSPLIT")) {  // tuning aid: any divisor of the step count up to 8
             const int v = std::atoi(e);
-            if (v >= 1 && v <= kLsMaxSplit && n_steps % v == 0) ks = v;
+            if (v >= 1 && v <= kLsMaxSplit && n_steps % v == 0) ks = P.forced = v;
         }
         if (forced4 || t_mid(tiles, ks) < t_small(n_wg1, P.ksplit)) {
             P.pick = 4; P.n_parts = 1; P.ksplit = ks;
@@ -673,22 +673,26 @@ template <typename T> auto window_select_for(int group, bool wide)
     return window_select_kernel<T, 1, 0, false>;
 }
 int select_blocks(const sals_desc& d) { return ceil_div(d.B, kXcds) * kXcds; }
-// Slices of the window's latent axis in the launch that it shares with the selection: the window's own plan, halved while its workgroups
-// fit the chip at once (one per compute unit in the 64-token form, two otherwise) and do not together with the selection's.  (A
-// workgroup too many is a round too many: one sequence, eight slices would be 257 workgroups.)
-// Slices of the window's latent axis where that launch has tiles of two heads and four sequences (0: it has not): as many as fit
-// beside the selection, one workgroup per compute unit, at least two (two rounds of those are shorter than one of the whole axis), of
-// two steps and more.  Such a tile reads half as much per product as one of a head and two sequences, which is what binds those: a step
-// with 2-bit values, 32 heads, r = 512, r_hi = 2048 in us with the latter's slices and with these: 8 sequences 73.2 and 70.6, 12 95.8
-// and 91.7, 16 109.3 and 104.2, 24 152.7 and 142.4, 32 189.4 and 179.5; 16 with r_hi = 1024 88.2 and 85.2.  (fp32 is bound by its
-// matrix instructions.  Four query heads per KV head: r_hi = 2048 as fast, 1024 3 % faster, not worth kernels of their own.)
+// Slices of the window's latent axis where the launch that it shares with the selection has tiles of two heads and four sequences (0: it
+// has not): as many as fit beside the selection, one workgroup per compute unit, at least two (two rounds of those are shorter than
+// one of the whole axis), of two steps and more.  (One slice would leave its statistics itself, in another order than the tiles of a head
+// and two sequences that the window's logits have in a launch of their own: a step and its stages agree bit for bit.)  Such a tile reads
+// half as much per product as one of a head and two sequences, which is what binds those: a step with 2-bit values, 32 heads, r = 512,
+// r_hi = 2048 in us with the latter's slices and with these: 8 sequences 73.2 and 70.6, 12 95.8 and 91.7, 16 109.3 and 104.2, 24 152.7
+// and 142.4, 32 189.4 and 179.5; 16 with r_hi = 1024 88.2 and 85.2.  (fp32 is bound by its matrix instructions.  Four query heads per
+// KV head: r_hi = 2048 as fast, 1024 3 % faster, not worth kernels of their own.)
 int wide_window_slices(const sals_ctx* win)
 {
     const sals_desc& d = win->d;
-    if (win->plan.pick != 4 || d.dtype != SALS_BF16 || d.H_q != d.H_kv || d.H_kv % 2 != 0) return 0;
-    const int tiles = ceil_div(d.B, 4) * (d.H_kv / 2), steps = d.r * 2 / kLgStep;
-    return std::max(1, std::min({(256 - select_blocks(d)) / tiles > 2 ? (256 - select_blocks(d)) / tiles : 2, kLsMaxSplit, steps / 2}));
+    const int steps = d.r * 2 / kLgStep, forced = win->plan.forced;
+    if (win->plan.pick != 4 || d.dtype != SALS_BF16 || d.H_q != d.H_kv || d.H_kv % 2 != 0 || steps < 4 || forced == 1) return 0;
+    if (forced) return forced;
+    const int tiles = ceil_div(d.B, 4) * (d.H_kv / 2);
+    return std::min({std::max(2, (256 - select_blocks(d)) / tiles), kLsMaxSplit, steps / 2});
 }
+// Slices in that launch, wide tiles or not: the window's own plan, halved while its workgroups fit the chip at once (one per compute unit
+// in the 64-token form, two otherwise) and do not together with the selection's.  (A workgroup too many is a round too many: one sequence,
+// eight slices would be 257 workgroups.)
 int window_select_slices(const sals_ctx* win)
 {
     if (const int ks = wide_window_slices(win)) return ks;

@@ -123,11 +123,13 @@ def test_shared_tiles_gqa_interleaved_rope_ring_wrap(oracle, monkeypatch):
     _case(oracle, w, seq_lens=[777, 500, 48, 49, 47, 0, 600, 100, 776])
 
 
-@pytest.mark.parametrize("B,H,r_hi", [(8, 2, 128), (9, 4, 256), (10, 6, 704), (15, 2, 320), (16, 32, 192)])
+@pytest.mark.parametrize("B,H,r_hi", [(8, 2, 128), (9, 4, 256), (10, 6, 704), (15, 2, 320), (16, 32, 192), (9, 3, 256), (12, 1, 128),
+                                      (10, 5, 704)])
 def test_wide_window_tiles(oracle, B, H, r_hi, monkeypatch):
     """The launch that a step's selection shares with the window's logits on tiles of two heads and four sequences: last tiles of
-    one, two, three and four sequences, slices of two steps, of three and of uneven numbers of them; empty, partial
-    and full windows.  The staged call, bit for bit, runs tiles of one head and two sequences."""
+    one, two, three and four sequences, slices of two steps, of three and of uneven numbers of them; empty, partial and full
+    windows.  The staged call, bit for bit, runs tiles of one head and two sequences, as the shared launch does for odd numbers of
+    heads."""
     monkeypatch.setenv("SALS_TUNE_LOGITS", "4")
     w = synth.shrink(SMALL, B=B, S=600, H=H, H_kv=H, r=64, r_hi=r_hi, plant=0)
     _case(oracle, w, seq_lens=[600, 0, 1, 40, 41, 144, 145, 500, 23, 599, 39, 64, 300, 2, 139, 143][:B])
@@ -155,13 +157,18 @@ def test_selection_beside_a_window_in_slices(oracle, S, B, tiles, top_k, monkeyp
     _case(oracle, w, seq_lens=[S, S - 1, S // 2 + 1, 697, 70, 0, 41, 40, 500][:B])
 
 
-@pytest.mark.parametrize("dtype,B,S,r_hi,slices", [
-    ("f32", 1, 8192, 1024, 4), ("f32", 1, 8200, 1024, 8), ("f32", 1, 8192, 2048, 8), ("f32", 1, 8200, 2048, 8), ("bf16", 1, 8192, 2048, 4),
-    ("bf16", 1, 8200, 2048, 8), ("bf16", 16, 4096, 2048, 1), ("bf16", 16, 8200, 2048, 2)])
-def test_slices_of_the_windows_latent_axis(dtype, B, S, r_hi, slices):
-    """A window whose logits share a launch with the selection (caches of at most 8192 rows, ranks whose halved slices do not take
-    longer than the launch saves) has fewer slices than one with a launch of its own.  Seen through a key channel that is 2^30 - 2^30 + 20 along the latent axis, the 20 beside the second term: within
-    a slice the sum is 20, but 0 where a slice begins between the two large terms."""
+@pytest.mark.parametrize("dtype,B,S,r_hi,slices,forced", [
+    ("f32", 1, 8192, 1024, 4, 0), ("f32", 1, 8200, 1024, 8, 0), ("f32", 1, 8192, 2048, 8, 0), ("f32", 1, 8200, 2048, 8, 0),
+    ("bf16", 1, 8192, 2048, 4, 0), ("bf16", 1, 8200, 2048, 8, 0), ("bf16", 16, 4096, 2048, 3, 0), ("bf16", 16, 8200, 2048, 2, 0),
+    ("bf16", 16, 4096, 2048, 1, 1), ("bf16", 16, 4096, 2048, 2, 2), ("bf16", 16, 4096, 2048, 8, 8), ("bf16", 16, 8200, 2048, 1, 1)])
+def test_slices_of_the_windows_latent_axis(dtype, B, S, r_hi, slices, forced, monkeypatch):
+    """A window whose logits share a launch with the selection (caches of at most 8192 rows) has other slices than one with a launch of its
+    own: fewer in 64-token tiles (where halved ones do not take longer than the launch saves), as many as fit beside the selection in
+    tiles of two heads and four sequences; or the number asked for.  Seen through a key channel that is 2^30 - 2^30 + 20 along the
+    latent axis, 256 bytes apart (in 64-token tiles every other piece of 128 is summed apart): within a slice the sum is 20, but 0 where a
+    slice begins between the first two terms (the 20 beside the second is lost)."""
+    if forced:
+        monkeypatch.setenv("SALS_TUNE_MULTI_KSPLIT", str(forced))
     print(f"[case] window slices {dtype} B={B} S={S} r_hi={r_hi}", flush=True)
     H, r, w = 32, 64, 64
     dt = torch.float32 if dtype == "f32" else torch.bfloat16
@@ -180,13 +187,16 @@ def test_slices_of_the_windows_latent_axis(dtype, B, S, r_hi, slices):
     idx = torch.empty((B, 168), dtype=torch.int32, device=gu.DEV)
     n_sel = torch.empty((B,), dtype=torch.int32, device=gu.DEV)
     Kc, pos = zeros(B, S, r), torch.zeros_like(n)
-    for cut in (r_hi // 8, r_hi // 4, r_hi // 2):   # where 8, 4 and 2 slices or more have an edge
+    step = 64 // torch.empty(0, dtype=dt).element_size()   # latent coordinates
+    edges = lambda k: {r_hi // step * i // k for i in range(1, k)}
+    between = lambda a, b: any(a < e <= b for e in edges(slices))   # a slice begins behind step a, at step b at the latest
+    for cut in sorted(edges(2) | edges(3) | edges(4) | edges(8)):
         Kw = zeros(B, w, r_hi)
-        Kw[:, 0, cut - r_hi // 8], Kw[:, 0, cut], Kw[:, 0, cut + r_hi // 16] = 2.0 ** 30, -2.0 ** 30, 20.0
+        Kw[:, 0, (cut - 4) * step], Kw[:, 0, cut * step], Kw[:, 0, (cut + 4) * step] = 2.0 ** 30, -2.0 ** 30, 20.0
         ctx.decode_step_window(win, q, pos, Kc, Kc, W, Kw, Vw, W_hi, n, out, None, idx, n_sel)
         ctx.sparse_attend_window(win, q, pos, Kc, Kc, W, Kw, Vw, W_hi, idx, n_sel, out2)
         torch.cuda.synchronize()
-        logit = 0.0 if slices * cut >= r_hi else 20.0 / 128 ** 0.5
+        logit = 0.0 if between(cut - 4, cut) and not between(cut, cut + 4) else 20.0 / 128 ** 0.5
         want = 1.0 / (1.0 + np.exp(-logit))
         assert torch.equal(out, out2)
         assert np.abs(gu.from_dev(out[:, 0, 0]) - want).max() < 2.0 ** -8, (cut, gu.from_dev(out[:, 0, 0]))
