@@ -52,7 +52,8 @@ struct ProjArgs {  // (what the first loads need comes first: those 14 words arr
     const int32_t* seq_len;  // append: [B] row to write
 };
 
-// workgroup of NW waves, NBATCH row pieces and HB column blocks of a wave in flight per round; i0: first latent coordinate
+// workgroup of NW waves, HB column blocks in a round, of which a wave has NBATCH row pieces of LB at a time in flight; i0: first latent
+// coordinate
 //
 // Code size counts here as in every kernel of a decode step: the instruction caches (64 KB for two CUs) keep code from one
 // launch to the next (measured: a launch's first pass through 32 KB is as fast as its second), so a step whose kernels fit
@@ -60,9 +61,8 @@ struct ProjArgs {  // (what the first loads need comes first: those 14 words arr
 // every pass: the same kernels of a small step linked in nine orders took 27.7 to 29.1 us.  So the column blocks are a loop and
 // not unrolled over registers of their own (a slice of one round still keeps U^T's pieces for all of them), 12.0 -> 2.4 KB for
 // up to 16 columns.  With the value sum's shorter code, whole steps: 1 x (512 of 4096) 28.0 -> 27.4 us, 12 ragged sequences
-// of 8 KV heads 65.1 -> 62.2 (the projection 5.9 -> 4.8), 32 x 2048 the same way 84 -> 79.5, 64 x 2048 of 32 KV heads 263 -> 255; 128
-// sequences, two rounds of column blocks in the append, 124.3 -> 126.5.
-template <typename T, bool QUERY, int NW, int NBATCH, int HB>
+// of 8 KV heads 65.1 -> 62.2 (the projection 5.9 -> 4.8), 32 x 2048 the same way 84 -> 79.5, 64 x 2048 of 32 KV heads 263 -> 255.
+template <typename T, bool QUERY, int NW, int NBATCH, int HB, int LB>
 __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int slice, int proj)
 {
     constexpr int VEC = elem<T>::vec;
@@ -92,8 +92,8 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int sli
 #pragma unroll
         for (int h = 0; h < HB; ++h) acc[h] = f32x4v{0.f, 0.f, 0.f, 0.f};
 
-        // this wave's steps: wave, wave+NW, ... ; NBATCH steps of loads per round, those of all its column blocks requested
-        // together, ahead of their products: a round costs one memory round trip.  Branches are wave-uniform (a step that is not
+        // this wave's steps: wave, wave+NW, ... ; NBATCH steps of loads per round, those of LB column blocks requested
+        // together, ahead of their products: they cost one memory round trip.  Branches are wave-uniform (a step that is not
         // there costs no load: clamped instead, 24 columns of 64 steps took 12.4 us where 8.1 do).
         for (int ks0 = wave; ks0 < nks; ks0 += NW * NBATCH) {
             if (nb0 == 0 || nks > NW * NBATCH) {
@@ -101,25 +101,29 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int sli
                 for (int u = 0; u < NBATCH; ++u)
                     if (ks0 + u * NW < nks) af[u] = ld16(arow + (size_t)(ks_first + ks0 + u * NW) * KS);
             }
-            u32x4 bf[HB][NBATCH];
 #pragma unroll
-            for (int h = 0; h < HB; ++h) {
-                if (nb0 + h < n_nblk) {
+            for (int h0 = 0; h0 < HB; h0 += LB) {
+                if (nb0 + h0 >= n_nblk) continue;
+                u32x4 bf[LB][NBATCH];
 #pragma unroll
-                    for (int u = 0; u < NBATCH; ++u)
-                        if (ks0 + u * NW < nks) {
-                            const unsigned c = (unsigned)(ks_first + ks0 + u * NW) * KS;  // (a step lies within one head)
-                            bf[h][u] = ld16(xrow[h] + (QUERY ? c / kHeadDim * G * kHeadDim + c % kHeadDim : c));
-                        }
+                for (int h = 0; h < LB; ++h) {
+                    if (nb0 + h0 + h < n_nblk) {
+#pragma unroll
+                        for (int u = 0; u < NBATCH; ++u)
+                            if (ks0 + u * NW < nks) {
+                                const unsigned c = (unsigned)(ks_first + ks0 + u * NW) * KS;  // (a step lies within one head)
+                                bf[h][u] = ld16(xrow[h0 + h] + (QUERY ? c / kHeadDim * G * kHeadDim + c % kHeadDim : c));
+                            }
+                    }
                 }
-            }
-            asm volatile("" ::: "memory");  // (keeps the loads above from sinking towards their products)
+                asm volatile("" ::: "memory");  // (keeps the loads above from sinking towards their products)
 #pragma unroll
-            for (int h = 0; h < HB; ++h) {
-                if (nb0 + h < n_nblk) {
+                for (int h = 0; h < LB; ++h) {
+                    if (nb0 + h0 + h < n_nblk) {
 #pragma unroll
-                    for (int u = 0; u < NBATCH; ++u)
-                        if (ks0 + u * NW < nks) mma16_op<T>::run(af[u], bf[h][u], acc[h]);
+                        for (int u = 0; u < NBATCH; ++u)
+                            if (ks0 + u * NW < nks) mma16_op<T>::run(af[u], bf[h][u], acc[h0 + h]);
+                    }
                 }
             }
         }
@@ -160,13 +164,13 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int sli
     }
 }
 
-// HB: as many column blocks as there are, up to 4, so that all their operands arrive in one round trip (1 x 48 columns, r = 640, D =
-// 1024: 5.6 us unrolled over all blocks, 7.6 in rounds of two, 5.4 in one of four; eight at once draw on the accumulator
-// registers and are no faster than twice four: 128 columns 9.7 and 9.9, 96 columns 7.4 and 7.1)
+// HB: as many column blocks as there are (1, 2, 4 or 8), so that all their operands arrive in one round trip (1 x 48 columns, r = 640,
+// D = 1024: 5.6 us unrolled over all blocks, 7.6 in rounds of two, 5.4 in one of four; 128 columns, whole steps of 32 sequences of 8 KV heads,
+// r = 512, behind a copy that empties the caches: two rounds of four 65.0, eight at once 63.4, eight in pairs 64.2)
 template <typename T, int HB>
 __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjArgs a)
 {
-    project_block<T, true, kProjWaves, kProjBatch, HB>(a, blockIdx.x * 16, blockIdx.y, blockIdx.z);
+    project_block<T, true, kProjWaves, kProjBatch, HB, HB>(a, blockIdx.x * 16, blockIdx.y, blockIdx.z);
 }
 
 // Append in slices of the D axis: adds up the slices' partial sums (in slice order) into the new rows and advances the lengths.

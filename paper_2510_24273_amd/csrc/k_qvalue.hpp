@@ -94,6 +94,11 @@ __device__ __forceinline__ void qv_quantize_group(const QuantArgs& qa, const int
 // launch adds the slices up (append_finish_kernel), and where none does (a recent window) eight waves have all their pieces in
 // flight.  (Batch 16, D = 4096, r = 512, 2-bit values, with the advance: 12.4 + 3.9 + 1.4 us as three launches of four waves,
 // 10.2 + 1.4 with eight waves over the whole axis, 5.3 + 2.8 sliced.)
+// HB: column blocks in a round, as many as there are.  Eight of them, whose registers would leave a SIMD one wave, take their loads in
+// pairs (four waves) or one by one (eight waves, 16 pieces each), with the sums folded once.  Appends alone, D = 4096,
+// in us: 128 sequences, r = 640 (eight waves) 25.7 in rounds of two blocks, 23.5 in one of eight (24.0 unrolled over all blocks, each
+// folded by itself); r = 256 (four waves) 17.1 in rounds of four, 17.0 with eight at once, 16.0 in pairs (15.2); 40 sequences, r = 640
+// 13.2, 12.8 (12.8).  Whole steps of 128 sequences, r = 512: 152.9 -> 150.0 (151.7).
 template <typename T, int NW, bool QUANT, int HB>
 __global__ __launch_bounds__(64 * NW) void append_kernel(ProjArgs a, QuantArgs qa)
 {
@@ -105,7 +110,8 @@ __global__ __launch_bounds__(64 * NW) void append_kernel(ProjArgs a, QuantArgs q
         return;
     }
     if (QUANT && (int)blockIdx.x * 16 >= a.r) return;  // (the grid covers the longer of the two parts)
-    project_block<T, false, NW, NW == kProjWaves ? kProjBatch : 16, HB>(a, blockIdx.x * 16, blockIdx.y, blockIdx.z);
+    project_block<T, false, NW, NW == kProjWaves ? kProjBatch : 16, HB, HB < 8 ? HB : NW == kProjWaves ? 2 : 1>(
+        a, blockIdx.x * 16, blockIdx.y, blockIdx.z);
 }
 
 struct QvArgs {

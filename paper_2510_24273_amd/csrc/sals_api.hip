@@ -283,7 +283,8 @@ template <typename T> sals_status launch_project(const sals_ctx* c, const void* 
     const int blocks = ceil_div(d.B * (d.H_q / d.H_kv), 16);
     if (blocks <= 1) hipLaunchKernelGGL((project_kernel<T, 1>), grid, wg, 0, st, a);
     else if (blocks <= 2) hipLaunchKernelGGL((project_kernel<T, 2>), grid, wg, 0, st, a);
-    else hipLaunchKernelGGL((project_kernel<T, 4>), grid, wg, 0, st, a);
+    else if (blocks <= 4) hipLaunchKernelGGL((project_kernel<T, 4>), grid, wg, 0, st, a);
+    else hipLaunchKernelGGL((project_kernel<T, 8>), grid, wg, 0, st, a);
     return launch_status();
 }
 
@@ -319,8 +320,8 @@ sals_status launch_append(const sals_ctx* c, const void* W, const void* k_new, c
                        dim3(QUANT ? std::max(d.r / 16, ceil_div(d.B * (a.D / kQvGroup), 2 * nw * a.np)) : d.r / 16, a.np, \
                             QUANT ? 2 : a.nproj), dim3(64 * NW), 0, st, a, qa)
 #define SALS_APPEND(NW, QUANT)                                                                                           \
-    do { if (d.B <= 16) SALS_APPEND_H(NW, QUANT, 1); else if (d.B <= 32 || NW > kProjWaves) SALS_APPEND_H(NW, QUANT, 2); \
-         else SALS_APPEND_H(kProjWaves, QUANT, 4); } while (0)
+    do { if (d.B <= 16) SALS_APPEND_H(NW, QUANT, 1); else if (d.B <= 32) SALS_APPEND_H(NW, QUANT, 2);                    \
+         else if (d.B <= 64 && NW == kProjWaves) SALS_APPEND_H(kProjWaves, QUANT, 4); else SALS_APPEND_H(NW, QUANT, 8); } while (0)
         if (qa.bits) { if (wide) SALS_APPEND(kAppendWaves, true); else SALS_APPEND(kProjWaves, true); }
         else { if (wide) SALS_APPEND(kAppendWaves, false); else SALS_APPEND(kProjWaves, false); }
 #undef SALS_APPEND_H

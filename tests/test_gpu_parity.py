@@ -442,12 +442,14 @@ def test_sliced_append_matches_oracle(oracle, dtype, H_kv, r, B):
     ("bf16", 8, 2, 128, 7),      # two blocks, the second one ragged
     ("bf16", 16, 2, 192, 6),     # three blocks in a round of four
     ("bf16", 4, 4, 128, 33),     # appends in rounds of four blocks
-    ("bf16", 12, 12, 64, 20),    # appends of eight waves, a round of two blocks
-    ("bf16", 12, 12, 64, 50),    # two such rounds
-    ("f32", 4, 4, 64, 70),       # two rounds of four blocks, the second of one ragged block
-    ("f32", 32, 32, 1024, 70)])  # the same, with two rounds of loads along the D axis
+    ("bf16", 12, 12, 64, 20),    # appends of eight waves, a round of two blocks ...
+    ("bf16", 12, 12, 64, 50),    # ... of eight blocks, half of them there
+    ("f32", 4, 4, 64, 70),       # five blocks of a round of eight, the fifth one ragged
+    ("f32", 32, 32, 1024, 70),   # the same, with two rounds of loads along the D axis
+    ("bf16", 4, 4, 128, 128),    # eight whole blocks
+    ("bf16", 16, 2, 192, 16)])   # the same in the projection alone
 def test_projections_in_column_blocks(oracle, dtype, H, H_kv, r, B):
-    """Query projection and append over one to five blocks of 16 columns, and more of them than a round holds: scores
+    """Query projection and append over one to eight blocks of 16 columns, and more of them than a round holds: scores
     and appended rows of the sequences at the blocks' edges against the oracle, one bf16 ulp for the rows as in the tests above
     (fp32: sums of at most 4096 products of unit normals and 1 / 64 in fp32, below 1e-5)."""
     S = 24
