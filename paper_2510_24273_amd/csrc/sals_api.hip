@@ -2032,11 +2032,11 @@ namespace {
 // Transformations of all rows at once (k_calib_all.hpp) in place of sweeps, up to kAllMaxD.  One takes 0.37 ms at D = 1024, where a
 // sweep takes 0.8, and from the Cholesky factor on it brings the rows as far as a sweep does, or further once the angles are below
 // one; its products grow with D^3 and a sweep's steps with D^2, so for large D it comes later.  A call, r = 5/8 D, in ms with the
-// transformations behind one, two and three sweeps (and with sweeps alone): D = 256 1.8 / 1.8 / 1.8 (2.2), 512 2.8 / 2.9 / 3.1 (4.4),
-// 1024 5.1 / 5.5 / 5.9 (9.6), 2048 23.7 / 23.7 / 24.3 (29.2), 3072 76 / 72 / 70 (79), 4096 177 / 165 / 149 (141); these with the
-// symmetric products computed whole (1024 4.8, 2048 21.6 with half of them).
-constexpr int kAllMaxD = 3072;
-inline int all_first(int D) { return D <= 2048 ? 1 : 3; }
+// transformations behind one, two, three and four sweeps (and with sweeps alone): D = 256 1.8 / 1.9 / 2.0 / 2.0 (2.1), 512 2.8 / 2.8 / 3.0 /
+// 3.2 (4.1), 1024 4.9 / 5.3 / 5.7 / 6.3 (9.4), 1536 12.9 / 13.3 / 13.8 / 14.3 (19.1), 2048 21.2 / 21.5 / 21.8 / 22.5 (28.7), 2560 45.6 / 43.8 /
+// 43.0 / 44.1 (58.9), 3072 67.9 / 68.0 / 66.9 / 63.9 (80.3), 3584 111 / 104 / 102 / 98.6 (109), 4096 159 / 149 / 142 / 140 (141).
+constexpr int kAllMaxD = 3584;
+inline int all_first(int D) { return D <= 2048 ? 1 : D < 3072 ? 3 : 4; }
 // the series of the exponential: cut behind E^4 it differs from an orthogonal matrix by |E|^6 / 72
 constexpr double kSeriesNorm = 4e-3;
 // the product kernels' dynamic LDS, beyond the default limit

@@ -162,7 +162,7 @@ def test_rows_left_behind_are_orthogonal_in_fp64(D, r, decay):
 
 
 @pytest.mark.parametrize("D,r,kind", [(256, 256, "flat"), (512, 512, "repeated"), (512, 300, "shuffled"), (768, 100, "steep"),
-                                      (1280, 700, "slow"), (1536, 1536, "flat"), (2304, 128, "slow")])
+                                      (1280, 700, "slow"), (1536, 1536, "flat"), (2304, 128, "slow"), (3072, 64, "slow"), (3584, 1000, "flat")])
 def test_transformations_of_all_rows_at_once(D, r, kind):
     """Spectra on which the call transforms all rows at once, from the first sweep on and (D above 2048) later, and such on which the
     transformations gain little and sweeps take turns with them: eigenvalues that repeat, rows of very different norms in no order."""
