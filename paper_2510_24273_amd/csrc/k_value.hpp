@@ -71,11 +71,10 @@ template <typename T> struct PvSecond {
     const int32_t* idx; const int32_t* n_sel; const T* Vc; const float* logits; float* Tpart;
     int r, n_tr, tok_per_wg, k_tot, lk, S_max, ring;
 };
-//
 // SPLIT: the logits are still partial sums over slices of the latent axis (`ksplit` of them).  Every workgroup adds up all of its
 // sequence's (a thread has four tokens of a head at a time, all slices requested together), keeps its range's in LDS and
-// takes maxima and normalisers on the way, under the gathered rows: the launch that would add them up before costs 5 us of a small step
-// and moves the same bytes, from L2, once.
+// takes maxima and normalisers on the way, under the gathered rows: the launch that would add them up before moves the same bytes, from
+// L2, once, and costs 1 to 2 us of a small step (see value_adds_slices).
 constexpr int kPvSplitTok = 128;                // tokens of a range, at most
 constexpr size_t kPvSplitBytes = 128 << 10;     // partial logits of a sequence, at most (a workgroup reads them all)
 template <typename T, int NW, int MB, bool TWO, bool SPLIT>
