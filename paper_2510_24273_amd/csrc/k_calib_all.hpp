@@ -15,11 +15,11 @@
 // bounds of its singular values: J. Chen, E. Chow, "A stable scaling of Newton-Schulz for improving the sign function computation of
 // a Hermitian matrix", 2014), and only *found* there: what is left, delta = X X^T - I (at most 1e-5: 6.7e-6 where the last step begins
 // with the smallest singular values it may, and the rounding of fp32; measured 5e-7 to 4e-6), is formed in fp64 and taken out to third
-// order, G <- (I - delta / 2 + 3/8 delta^2) X G, with fp64 products.  The fourth, 5/16 delta^3, is below 4e-16, so what a transformation
-// does to G is orthogonal to the rounding of those products (G^T G changed by 2e-15 to 3e-15 of its norm, D = 256 to 1024), and which transformation is made decides
-// nothing but how fast the rows converge.  (D = 1024, r = 640: eigenvalues off by 1.2e-14 of themselves against a 64-bit
-// eigensolver, by 2.4e-14 with sweeps alone.)  With X (X X^T) in the place of (X X^T) X, which is the same for a normal X only, rounding
-// adds up from step to step: delta 2e-5 to 4e-5, G^T G changed by 1.1e-14 at D = 256.
+// order, G <- (I - delta / 2 + 3/8 delta^2) X G, with fp64 products.  The next term, 5/16 delta^3, is below 4e-16, so what a
+// transformation does to G is orthogonal to the rounding of those products (G^T G changed by 2e-15 to 3e-15 of its norm, D = 256 to 1024),
+// and which transformation is made decides nothing but how fast the rows converge.  (D = 1024, r = 640: eigenvalues off by 1.2e-14 of
+// themselves against a 64-bit eigensolver, by 2.4e-14 with sweeps alone.)  With X (X X^T) in the place of (X X^T) X, which is the same
+// for a normal X only, rounding adds up from step to step: delta 2e-5 to 4e-5, G^T G changed by 1.1e-14 at D = 256.
 #pragma once
 #include "common.hpp"
 #include "k_calib.hpp"

@@ -165,8 +165,8 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int sli
 }
 
 // HB: as many column blocks as there are (1, 2, 4 or 8), so that all their operands arrive in one round trip (1 x 48 columns, r = 640,
-// D = 1024: 5.6 us unrolled over all blocks, 7.6 in rounds of two, 5.4 in one of four; 128 columns, whole steps of 32 sequences of 8 KV heads,
-// r = 512, behind a copy that empties the caches: two rounds of four 65.0, eight at once 63.4, eight in pairs 64.2)
+// D = 1024: 5.6 us unrolled over all blocks, 7.6 in rounds of two, 5.4 in one of four; 128 columns, whole steps of 32 sequences of 8 KV
+// heads, r = 512, behind a copy that empties the caches: two rounds of four 65.0, eight at once 63.4, eight in pairs 64.2)
 template <typename T, int HB>
 __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjArgs a)
 {

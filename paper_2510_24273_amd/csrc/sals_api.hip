@@ -2029,12 +2029,12 @@ bool eig_plan(int D, size_t bytes, EigWs* w, int* n_part, bool* series)
 }  // namespace
 
 namespace {
-// Transformations of all rows at once (k_calib_all.hpp) in place of sweeps, up to kAllMaxD.  One takes 0.37 ms at D = 1024, where a
-// sweep takes 0.8, and from the Cholesky factor on it brings the rows as far as a sweep does, or further once the angles are below
+// Transformations of all rows at once (k_calib_all.hpp) in place of sweeps, up to kAllMaxD.  One takes 0.38 ms at D = 1024, where a
+// sweep takes 0.85, and from the Cholesky factor on it brings the rows as far as a sweep does, or further once the angles are below
 // one; its products grow with D^3 and a sweep's steps with D^2, so for large D it comes later.  A call, r = 5/8 D, in ms with the
-// transformations behind one, two, three and four sweeps (and with sweeps alone): D = 256 1.8 / 1.9 / 2.0 / 2.0 (2.1), 512 2.8 / 2.8 / 3.0 /
-// 3.2 (4.1), 1024 4.9 / 5.3 / 5.7 / 6.3 (9.4), 1536 12.9 / 13.3 / 13.8 / 14.3 (19.1), 2048 21.2 / 21.5 / 21.8 / 22.5 (28.7), 2560 45.6 / 43.8 /
-// 43.0 / 44.1 (58.9), 3072 67.9 / 68.0 / 66.9 / 63.9 (80.3), 3584 111 / 104 / 102 / 98.6 (109), 4096 159 / 149 / 142 / 140 (141).
+// transformations behind one, two, three and four sweeps (and with sweeps alone): D = 256 1.8 / 1.9 / 2.0 / 2.0 (2.1), 512 2.8 / 2.8 /
+// 3.0 / 3.2 (4.1), 1024 4.9 / 5.3 / 5.7 / 6.3 (9.4), 1536 12.9 / 13.3 / 13.8 / 14.3 (19.1), 2048 21.2 / 21.5 / 21.8 / 22.5 (28.7), 2560 45.6 /
+// 43.8 / 43.0 / 44.1 (58.9), 3072 67.9 / 68.0 / 66.9 / 63.9 (80.3), 3584 111 / 104 / 102 / 98.6 (109), 4096 159 / 149 / 142 / 140 (141).
 constexpr int kAllMaxD = 3584;
 inline int all_first(int D) { return D <= 2048 ? 1 : D < 3072 ? 3 : 4; }
 // the series of the exponential: cut behind E^4 it differs from an orthogonal matrix by |E|^6 / 72
