@@ -19,6 +19,11 @@ __device__ __forceinline__ int xcd_item(int id, int N)
     return xcd * qn + min(xcd, rem) + slot;
 }
 
+// Who is the last of a launch's workgroups?  One thread of each calls once, behind everything that must come before what the last one does:
+// it is the one that gets n_wg - 1.  The count is zero between launches (the last arrival wraps it).  Nobody waits for anybody, and what
+// an arrival costs is the round trip of its answer (1 us), which is asked for early and looked at late.
+__device__ __forceinline__ uint32_t arrive(uint32_t* count, uint32_t n_wg) { return atomicInc(count, n_wg - 1); }
+
 constexpr int kWave = 64;
 constexpr int kHeadDim = 128;        // head width the kernels are written for
 constexpr int kPairs = kHeadDim / 2; // RoPE pairs per head

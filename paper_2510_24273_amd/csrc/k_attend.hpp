@@ -35,9 +35,11 @@ __device__ __forceinline__ int slot_to_dim(int slot, int style)
 struct InvFreq { double f[kPairs]; };  // theta^(-2p/d), computed on the host in fp64
 
 // cos/sin of every (position, pair): tab[t][p] = (cos, sin)(t * f_p)
-__global__ __launch_bounds__(256) void rope_table_kernel(float2* __restrict__ tab, InvFreq inv, int rows)
+// (and zero in `count`, unless null, for what counts arrivals)
+__global__ __launch_bounds__(256) void rope_table_kernel(float2* __restrict__ tab, InvFreq inv, int rows, uint32_t* count)
 {
     const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (e == 0 && count) *count = 0u;
     if (e >= (size_t)rows * kPairs) return;
     double sn, c;
     sincos((double)(e / kPairs) * inv.f[e % kPairs], &sn, &c);

@@ -29,9 +29,27 @@ struct PrefillArgs {
     const int32_t* seq_len;  // [B] first row to write
     const int32_t* n_new;    // [B] tokens of each sequence (<= n_tok), or nullptr: n_tok everywhere
     int n_tok, D, r, S_max, B, nproj;
+    uint32_t* arrived;       // not null: the last of the launch's n_wg workgroups to arrive here advances the lengths
+    uint32_t n_wg;
     float* pacc;             // SYRK form only: [slices][n_tok, r] fp32 tile sums of each slice of the contraction axis
     int kslice_steps;        // SYRK form only: 64-byte steps of the contraction axis per slice (blockIdx.y = slice)
 };
+
+// a sequence's length behind the prompt
+__device__ __forceinline__ void pf_advance(int32_t* seq_len, const int32_t* n_new, int n_tok, int b, int S_max)
+{
+    const int n = n_new ? min(max(n_new[b], 0), n_tok) : n_tok;
+    const int s = seq_len[b];
+    if (s >= 0) seq_len[b] = (int)min((long long)s + n, (long long)S_max);
+}
+// thread 0 of a workgroup arrives behind every read of the lengths; the last workgroup advances them before it ends (6 ragged prompts
+// of up to 4001 tokens, D = 1024, r = 640 63.1 us a call with a launch for that behind the stores, 61.8 so)
+__device__ __forceinline__ uint32_t pf_arrive(const PrefillArgs& a) { return a.arrived && threadIdx.x == 0 ? arrive(a.arrived, a.n_wg) : 0u; }
+__device__ __forceinline__ void pf_leave(const PrefillArgs& a, uint32_t order)
+{
+    if (!a.arrived || threadIdx.x >= kWave || (uint32_t)wave_uniform((int)order) != a.n_wg - 1) return;
+    for (int b = lane_id(); b < a.B; b += kWave) pf_advance(const_cast<int32_t*>(a.seq_len), a.n_new, a.n_tok, b, a.S_max);
+}
 
 // fp32 prompts.  One workgroup owns TOK tokens x NL latent coordinates of one sequence and one projection; its eight waves
 // are 4 token groups x 2 latent groups (NL = 128) or 8 token groups (NL = 64), a wave tile being TOK/4 (TOK/8) tokens x 64
@@ -177,6 +195,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_compress_kernel(Prefill
         return;
     }
     const int row0 = wave_uniform(row0_v);
+    const uint32_t order = pf_arrive(a);  // (every wave's length came before its last operands)
     T* cache = static_cast<T*>(a.cache[proj]) + (size_t)b * a.S_max * a.r;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -190,6 +209,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_compress_kernel(Prefill
                     cache[(size_t)row * a.r + lat0 + wn * 64 + nb * 32 + l32] = acc[mb][nb][v];
             }
         }
+    pf_leave(a, order);
 }
 
 // bf16 prompts: tiles of 128 NBT tokens x 64 NBW latent coordinates (NBT 1 | 2, NBW 1 .. 5), one workgroup per compute unit.
@@ -219,8 +239,9 @@ template <int NBW, int NBT> struct pf_cfg {
     static constexpr size_t LDS = 4 * (size_t)STAGE;
     static constexpr int PIECES = TN / 16;   // 1 KB pieces of the projector side per step
 };
+// (returns thread 0's arrival, see pf_arrive)
 template <int NBW, int NBT>
-__device__ __forceinline__ void prefill_tile(const PrefillArgs& a, int block, int n_col, const PfPart& p)
+__device__ __forceinline__ uint32_t prefill_tile(const PrefillArgs& a, int block, int n_col, const PfPart& p)
 {
     typedef pf_cfg<NBW, NBT> C;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];  // [stage][projector rows | token rows]
@@ -254,7 +275,7 @@ __device__ __forceinline__ void prefill_tile(const PrefillArgs& a, int block, in
             count = p.part == kPfTail ? (n_tiles - whole) * SUB : whole;
         }
         const int total = count * per_tile;
-        if (block >= total) return;  // uniform
+        if (block >= total) return pf_arrive(a);  // uniform
         const int w = xcd_item(block, total);
         int tile = idiv(w, per_tile);
         const int rest = w - tile * per_tile;
@@ -273,7 +294,7 @@ __device__ __forceinline__ void prefill_tile(const PrefillArgs& a, int block, in
             m0 = tile * unit + sub;
             m_end = a.B * a.n_tok;
         }
-        if (m0 >= m_end) return;  // uniform: an empty part of a sequence's last tile
+        if (m0 >= m_end) return pf_arrive(a);  // uniform: an empty part of a sequence's last tile
     }
     const int lat0 = col * C::TN;
     const size_t row_bytes = (size_t)a.D * 2;
@@ -383,6 +404,7 @@ __device__ __forceinline__ void prefill_tile(const PrefillArgs& a, int block, in
     }
     vm_wait<0>();  // (no load may land in LDS that another workgroup has been given, nor in the rows below)
     wg_barrier();
+    const uint32_t order = pf_arrive(a);
 
     // acc[mb][nb][4a+c]: latent coordinate wn 32 NBW + mb 32 + 8a + 4hi + c, token wm 32 NBT + nb 32 + l32.  A wave turns 32 tokens at
     // a time in rows of its own in LDS (its coordinates of a token, the token's cache row behind them), so that consecutive lanes
@@ -418,32 +440,31 @@ __device__ __forceinline__ void prefill_tile(const PrefillArgs& a, int block, in
         }
         __builtin_amdgcn_wave_barrier();
     }
+    return order;
 }
 
 template <int NBW, int NBT>
 __global__ __launch_bounds__(kPfThreads, 2) void prefill_tile_kernel(PrefillArgs a, int n_col)
 {
-    prefill_tile<NBW, NBT>(a, (int)blockIdx.x, n_col, PfPart{kPfAll, 0, 0});
+    pf_leave(a, prefill_tile<NBW, NBT>(a, (int)blockIdx.x, n_col, PfPart{kPfAll, 0, 0}));
 }
 // n_big workgroups for the whole rounds of tiles of 256 rows, the others for the rest in tiles of 128 rows x 64 UBW coordinates
 template <int NBW, int UBW>
 __global__ __launch_bounds__(kPfThreads, 2) void prefill_split_kernel(PrefillArgs a, int n_col, int n_big, int n_col_rest, int tail_max)
 {
     const int per_big = 2 * n_col;
-    if ((int)blockIdx.x < n_big) prefill_tile<NBW, 2>(a, (int)blockIdx.x, n_col, PfPart{kPfBig, per_big, tail_max});
-    else prefill_tile<UBW, 1>(a, (int)blockIdx.x - n_big, n_col_rest, PfPart{kPfTail, per_big, tail_max});
+    uint32_t order;
+    if ((int)blockIdx.x < n_big) order = prefill_tile<NBW, 2>(a, (int)blockIdx.x, n_col, PfPart{kPfBig, per_big, tail_max});
+    else order = prefill_tile<UBW, 1>(a, (int)blockIdx.x - n_big, n_col_rest, PfPart{kPfTail, per_big, tail_max});
+    pf_leave(a, order);
 }
 
-// after a bulk append: advance every sequence by its token count (separate launch, so that every cache row
-// has been written before any length changes)
+// after the prompt of a context without a count of arrivals (see arrival_count): advance the lengths
 __global__ void advance_seq_len_kernel(int32_t* __restrict__ seq_len, const int32_t* __restrict__ n_new, int n_tok, int B,
                                        int S_max)
 {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    const int n = n_new ? min(max(n_new[b], 0), n_tok) : n_tok;
-    const int s = seq_len[b];
-    if (s >= 0) seq_len[b] = (int)min((long long)s + n, (long long)S_max);
+    if (b < B) pf_advance(seq_len, n_new, n_tok, b, S_max);
 }
 
 }  // namespace sals

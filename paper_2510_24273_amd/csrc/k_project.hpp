@@ -50,7 +50,19 @@ struct ProjArgs {  // (what the first loads need comes first: those 14 words arr
     void* cache[2];      // append: [B,S_max,r], or [B,ring,r] when ring > 0
     float* out_f32;      // QUERY: partial q~ [np,B,r], one slice of the D axis each; append with np > 1: [nproj,np,B,r]
     const int32_t* seq_len;  // append: [B] row to write
+    uint32_t* arrived;       // append: not null = the last of its n_wg workgroups to arrive here advances the lengths
+    uint32_t n_wg;
 };
+
+// One wave, lane l with the lengths of sequences l and 64 + l and (lane 0) the workgroup's arrival: the last workgroup advances them.
+__device__ __forceinline__ void append_advance(const ProjArgs& a, uint32_t order, int32_t len0, int32_t len1)
+{
+    if ((uint32_t)wave_uniform((int)order) != a.n_wg - 1) return;
+    int32_t* const seq_len = const_cast<int32_t*>(a.seq_len);
+    const int lane = lane_id();
+    if (lane < a.B && len0 < a.S_max) seq_len[lane] = len0 + 1;
+    if (lane + kWave < a.B && len1 < a.S_max) seq_len[lane + kWave] = len1 + 1;
+}
 
 // workgroup of NW waves, HB column blocks in a round, of which a wave has NBATCH row pieces of LB at a time in flight; i0: first latent
 // coordinate
@@ -79,6 +91,12 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int sli
 
     __shared__ __attribute__((aligned(16))) float red[HB][NW][64][4];
     __shared__ float colsum[kProjMaxCols][16];
+    // Append: the first wave requests all lengths ahead of its other loads, for the workgroup's stores, and says that it has them.
+    __shared__ int32_t length[QUERY ? 1 : kProjMaxCols];
+    static_assert(kProjMaxCols == 2 * kWave, "two lengths a lane");
+    int32_t len0 = 0, len1 = 0;
+    uint32_t order = 0;
+    if (!QUERY && wave == 0) { len0 = a.seq_len[min(lane, a.B - 1)]; len1 = a.seq_len[min(lane + kWave, a.B - 1)]; }
 
     u32x4 af[NBATCH];
     for (int nb0 = 0; nb0 < n_nblk; nb0 += HB) {
@@ -117,6 +135,11 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int sli
                     }
                 }
                 asm volatile("" ::: "memory");  // (keeps the loads above from sinking towards their products)
+                if (!QUERY && wave == 0 && nb0 + h0 + ks0 == 0) {  // uniform
+                    length[lane] = len0; length[lane + kWave] = len1;
+                    asm volatile("" ::"v"(len0), "v"(len1) : "memory");
+                    if (a.arrived && lane == 0) order = arrive(a.arrived, a.n_wg);
+                }
 #pragma unroll
                 for (int h = 0; h < LB; ++h) {
                     if (nb0 + h0 + h < n_nblk) {
@@ -154,7 +177,7 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int sli
         if (QUERY || a.np > 1) {
             a.out_f32[((size_t)(proj * a.np + slice) * a.B + b) * a.r + i0 + rr] = s;
         } else {
-            const int t_new = a.seq_len[b];
+            const int t_new = length[b];
             const int rows = a.ring > 0 ? a.ring : a.S_max;
             if (t_new >= 0 && t_new < a.S_max) {
                 const int row = a.ring > 0 ? (unsigned)t_new % (unsigned)a.ring : t_new;
@@ -162,6 +185,7 @@ __device__ __forceinline__ void project_block(const ProjArgs& a, int i0, int sli
             }
         }
     }
+    if (!QUERY && a.arrived && wave == 0) append_advance(a, order, len0, len1);
 }
 
 // HB: as many column blocks as there are (1, 2, 4 or 8), so that all their operands arrive in one round trip (1 x 48 columns, r = 640,
@@ -201,8 +225,7 @@ __global__ __launch_bounds__(256) void append_finish_kernel(ProjArgs a)
     if (threadIdx.x == 0) const_cast<int32_t*>(a.seq_len)[b] = t_new + 1;
 }
 
-// after an append: advance the sequence lengths (separate launch, so that every cache row
-// has been written before any length changes)
+// after an append of a context without a count of arrivals (see arrival_count): advance the sequence lengths
 __global__ void bump_seq_len_kernel(int32_t* __restrict__ seq_len, int B, int S_max)
 {
     int b = blockIdx.x * blockDim.x + threadIdx.x;

@@ -45,6 +45,7 @@ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 struct Layout {  // byte offsets into the workspace
     size_t qt, ap_part, scores, idx, n_sel, n_lo, logits, plogits, stats, rope, tpart, qv_part, dn_part, tm_part, tm_hist, tm_meta, tm_cand, tm_srange, total;
+    size_t arrived;              // 0: no room
     int lk;                      // logits row stride (floats)
     int max_parts;               // token tiles per head of the logits kernel, at most
     int pv_tok_per_wg, pv_ntr, pv_waves;  // value-sum token ranges, waves per workgroup (4 | 8)
@@ -204,6 +205,7 @@ Layout make_layout(const sals_desc& d, bool short_ranges = true)
     L.idx = take((size_t)d.B * k_tot * 4);
     L.n_sel = take((size_t)d.B * 4);
     L.n_lo = take((size_t)d.B * 4);                          // recent-window attention: tokens of the low-rank pass
+    L.arrived = (size_t)d.B * 4 % kAlign ? L.n_lo + (size_t)d.B * 4 : 0;  // (in the padding, if there is any: see arrival_count)
     L.logits = take((size_t)d.B * d.H_q * L.lk * 4);
     // partial logits of the latent slices, for shapes with so few 64-token tiles that the latent axis is split too
     // (also for batches of short selections, whose multi-sequence tiles may split the latent axis)
@@ -268,6 +270,12 @@ template <typename T> inline const T* w_section(const sals_ctx* c, const void* W
     return static_cast<const T*>(W) + (size_t)sec * c->L.w_section;
 }
 
+// The count of arrivals of appends and prompt compressions, for a launch whose last workgroup advances the lengths in place of a
+// second launch: calls of a context are ordered, so one is enough.  Cleared with the cos/sin table, so null until that is known to be
+// filled (sals_prepare).  It lies in padding, of which batches of 64 and 128 sequences have none.
+inline uint32_t* arrival_count(const sals_ctx* c) { return c->L.arrived ? reinterpret_cast<uint32_t*>(c->ws + c->L.arrived) : nullptr; }
+inline uint32_t* arrivals(const sals_ctx* c) { return c->rope_state == 2 ? arrival_count(c) : nullptr; }
+
 // q~ = U_k^T (summed query heads), as partial sums over slices of the D axis
 template <typename T> sals_status launch_project(const sals_ctx* c, const void* W, const void* q, hipStream_t st)
 {
@@ -313,12 +321,12 @@ sals_status launch_append(const sals_ctx* c, const void* W, const void* k_new, c
         while (a.np < kScoreMaxParts && d.r / 16 * a.nproj * a.np < 128 && nks % (2 * a.np) == 0 && nks / (2 * a.np) >= 32) a.np *= 2;
     const bool wide = nks / a.np > kProjWaves * kProjBatch;  // more MFMA steps than four waves request at once
     const int nw = wide ? kAppendWaves : kProjWaves;
+    const dim3 grid(qa.bits ? std::max(d.r / 16, ceil_div(d.B * (a.D / kQvGroup), 2 * nw * a.np)) : d.r / 16, a.np, qa.bits ? 2 : a.nproj);
+    a.arrived = bump && a.np == 1 ? arrivals(c) : nullptr;
+    a.n_wg = grid.x * grid.y * grid.z;
     {
         ProfScope ps(c, SALS_K_PROJECT, st);
-#define SALS_APPEND_H(NW, QUANT, HB)                                                                                     \
-    hipLaunchKernelGGL((append_kernel<T, NW, QUANT, HB>),                                                                \
-                       dim3(QUANT ? std::max(d.r / 16, ceil_div(d.B * (a.D / kQvGroup), 2 * nw * a.np)) : d.r / 16, a.np, \
-                            QUANT ? 2 : a.nproj), dim3(64 * NW), 0, st, a, qa)
+#define SALS_APPEND_H(NW, QUANT, HB) hipLaunchKernelGGL((append_kernel<T, NW, QUANT, HB>), grid, dim3(64 * NW), 0, st, a, qa)
 #define SALS_APPEND(NW, QUANT)                                                                                           \
     do { if (d.B <= 16) SALS_APPEND_H(NW, QUANT, 1); else if (d.B <= 32) SALS_APPEND_H(NW, QUANT, 2);                    \
          else if (d.B <= 64 && NW == kProjWaves) SALS_APPEND_H(kProjWaves, QUANT, 4); else SALS_APPEND_H(NW, QUANT, 8); } while (0)
@@ -330,7 +338,7 @@ sals_status launch_append(const sals_ctx* c, const void* W, const void* k_new, c
     if (launch_status() != SALS_OK) return SALS_ERR_HIP;
     if (a.np > 1)
         hipLaunchKernelGGL((append_finish_kernel<T>), dim3(d.B), dim3(256), 0, st, a);
-    else if (bump)
+    else if (bump && !a.arrived)
         hipLaunchKernelGGL(bump_seq_len_kernel, dim3(ceil_div(d.B, 128)), dim3(128), 0, st, seq_len, d.B, d.S_max);
     return launch_status();
 }
@@ -458,7 +466,7 @@ sals_status enqueue_rope_table(sals_ctx* c, hipStream_t st)
 {
     const size_t n = (size_t)(c->d.S_max + 1) * kPairs;
     hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                       reinterpret_cast<float2*>(c->ws + c->L.rope), c->inv, c->d.S_max + 1);
+                       reinterpret_cast<float2*>(c->ws + c->L.rope), c->inv, c->d.S_max + 1, arrival_count(c));
     if (launch_status() != SALS_OK) return SALS_ERR_HIP;
     if (!c->rope_ev && hipEventCreateWithFlags(&c->rope_ev, hipEventDisableTiming) != hipSuccess) return SALS_ERR_HIP;
     if (hipEventRecord(c->rope_ev, st) != hipSuccess) return SALS_ERR_HIP;
@@ -1225,6 +1233,7 @@ sals_status sals_compress_prefill(sals_ctx* ctx, const void* k_new, const void* 
     auto allow = [](const void* kern, size_t lds) {
         return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
     };
+    a.arrived = arrivals(ctx);
     ProfScope ps(ctx, SALS_K_PREFILL, st);
     if (bf) {
         const PrefillPlan P = plan_prefill(d, n_tok, n_new != nullptr);
@@ -1233,23 +1242,25 @@ sals_status sals_compress_prefill(sals_ctx* ctx, const void* k_new, const void* 
         // every token tile a batch of these sizes can have (workgroups past the tiles that hold tokens leave)
         const int n_tiles = n_new ? d.B * ceil_div(n_tok, tm) : (int)(((long long)d.B * n_tok + tm - 1) / tm);
         if (P.tail_max == 0) {
+            a.n_wg = n_tiles * 2 * n_col;
 #define SALS_PREFILL(N, T)                                                                                              \
             if (t.nbw == N && t.nbt == T) {                                                                             \
                 auto kern = prefill_tile_kernel<N, T>;                                                                  \
                 constexpr size_t lds = pf_cfg<N, T>::LDS;                                                               \
                 if (!allow(reinterpret_cast<const void*>(kern), lds)) return SALS_ERR_HIP;                              \
-                hipLaunchKernelGGL(kern, dim3(n_tiles * 2 * n_col), dim3(kPfThreads), lds, st, a, n_col);                \
+                hipLaunchKernelGGL(kern, dim3(a.n_wg), dim3(kPfThreads), lds, st, a, n_col);                            \
             }
             SALS_PREFILL(1, 1) SALS_PREFILL(2, 1) SALS_PREFILL(3, 1) SALS_PREFILL(2, 2) SALS_PREFILL(4, 2) SALS_PREFILL(5, 2)
         } else {
             const int n_col_rest = ceil_div(d.r, 64 * P.tail.nbw), n_rest = std::min(n_tiles, P.tail_max) * 2 * 2 * n_col_rest;
             const int n_big = ceil_div(n_tiles * 2 * n_col, kXcds) * kXcds;  // (either kind is dealt to the XCDs from the first on)
+            a.n_wg = n_big + n_rest;
 #define SALS_PREFILL_SPLIT(N, U)                                                                                        \
             if (t.nbw == N && P.tail.nbw == U) {                                                                        \
                 auto kern = prefill_split_kernel<N, U>;                                                                 \
                 constexpr size_t lds = std::max(pf_cfg<N, 2>::LDS, pf_cfg<U, 1>::LDS);                                  \
                 if (!allow(reinterpret_cast<const void*>(kern), lds)) return SALS_ERR_HIP;                              \
-                hipLaunchKernelGGL(kern, dim3(n_big + n_rest), dim3(kPfThreads), lds, st, a, n_col, n_big, n_col_rest,   \
+                hipLaunchKernelGGL(kern, dim3(a.n_wg), dim3(kPfThreads), lds, st, a, n_col, n_big, n_col_rest,   \
                                    P.tail_max);                                                                         \
             }
             SALS_PREFILL_SPLIT(2, 1) SALS_PREFILL_SPLIT(2, 2) SALS_PREFILL_SPLIT(2, 3) SALS_PREFILL_SPLIT(4, 1) SALS_PREFILL_SPLIT(4, 2)
@@ -1263,6 +1274,7 @@ sals_status sals_compress_prefill(sals_ctx* ctx, const void* k_new, const void* 
         // 256-token tiles unless they would fill less than three quarters of the chip's 512 workgroup slots
         const int tok = (nl == 128 && (long long)ceil_div(n_tok, 256) * (d.r / nl) * d.B * 2 < 384) ? 128 : 256;
         const dim3 grid(ceil_div(n_tok, tok), d.r / nl, d.B * 2);
+        a.n_wg = grid.x * grid.y * grid.z;
         const size_t lds = prefill_lds_bytes(tok, nl);
         auto kern = nl == 64 ? prefill_compress_kernel<256, 64>
                              : (tok == 128 ? prefill_compress_kernel<128, 128> : prefill_compress_kernel<256, 128>);
@@ -1270,6 +1282,7 @@ sals_status sals_compress_prefill(sals_ctx* ctx, const void* k_new, const void* 
         hipLaunchKernelGGL(kern, grid, dim3(kPfThreads), lds, st, a);
     }
     if (launch_status() != SALS_OK) return SALS_ERR_HIP;
+    if (a.arrived) return SALS_OK;
     hipLaunchKernelGGL(advance_seq_len_kernel, dim3(ceil_div(d.B, 128)), dim3(128), 0, st, seq_len, n_new, n_tok, d.B, d.S_max);
     return launch_status();
 }
