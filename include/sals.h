@@ -388,8 +388,8 @@ sals_status sals_overlap_score(sals_ctx* ctx, const void* q, const int32_t* q_po
  *
  * sals_calib_eigenvectors computes the eigen-decomposition of C (symmetric, positive semi-definite up to the rounding
  * of its sums) by one-sided Jacobi rotations in fp64, of the rows of the Cholesky factor of C plus a small multiple of
- * the identity (with a workspace of the full size and D up to 3584 also by orthogonal transformations of all rows at once,
- * which are applied in fp64), and returns all eigenvalues in descending order and the r leading eigenvectors:
+ * the identity (with a workspace of the full size and D up to 3584 also by orthogonal transformations of all rows at once;
+ * up to D = 2560 the first of these are found in fp32 and applied together, as one matrix that is orthogonal to fp64 rounding), and returns all eigenvalues in descending order and the r leading eigenvectors:
  *   C          [D, D] fp64 (device)    in; OVERWRITTEN (its rows become eigenvalue times eigenvector)
  *   D          multiple of 256, at most 8192;  r  1 .. D
  *   dtype      storage type T of U
@@ -403,10 +403,10 @@ sals_status sals_overlap_score(sals_ctx* ctx, const void* q, const int32_t* q_po
  *   workspace  device, 256-byte aligned, sals_calib_eigenvectors_workspace_bytes(D) bytes (the factor and two partial
  *              sums of a series, 8 D^2 bytes each, and some D of scratch).  Fewer are taken from 8 D^2 + 900 D on
  *              (SALS_ERR_WORKSPACE below what the sweeps need): all rotations are then made by sweeps, whose
- *              sums are spread over as much of the device as the scratch allows (D = 1024: 4.8 ms with the full size,
+ *              sums are spread over as much of the device as the scratch allows (D = 1024: 3.5 ms with the full size,
  *              10.2 with 8 D^2 + 4000 D bytes, 15.4 with the least)
  *   max_sweeps at least 1 (host): a sweep rotates every pair of rows once (transformations of all rows, which come
- *              between sweeps, are not counted); the call stops when no rotation that involves one of the r largest
+ *              between sweeps, are not counted; where they take the place of the first sweep they count as one); the call stops when no rotation that involves one of the r largest
  *              rows would turn by more than 1e-11 (found by a sweep, or from the Gram matrix of all rows behind a sweep
  *              of small rotations; with a workspace of the full size the last, smallest rotations are made all at
  *              once), or after max_sweeps

@@ -333,6 +333,11 @@ constexpr int kCalPanel = 64;
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 // v_mfma_f64_16x16x4: lane holds A[l % 16][l / 16] and B[l / 16][l % 16]; result element i is row l / 16 + 4 i, column l % 16
 __device__ __forceinline__ f64x4 mma_f64(double a, double b, f64x4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ f64x4 mma_step(double a, double b, f64x4 c) { return mma_f64(a, b, c); }
+__device__ __forceinline__ f32x4 mma_step(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+template <typename ACC> struct mma_tile;   // result element e of a 16 x 16 tile: row, column lane % 16
+template <> struct mma_tile<double> { typedef f64x4 acc; static __device__ __forceinline__ int row(int kg, int e) { return kg + 4 * e; } };
+template <> struct mma_tile<float> { typedef f32x4 acc; static __device__ __forceinline__ int row(int kg, int e) { return 4 * kg + e; } };
 
 // 1 / sqrt(x) for normal x: the hardware's estimate and one third-order step (full precision)
 __device__ __forceinline__ double rsqrt_f64(double x)
@@ -500,15 +505,15 @@ constexpr int kTile00 = 0, kTile01 = 1, kTile11 = 2, kTile02 = 3, kTile12 = 4, k
 __device__ __forceinline__ int jac_row(int p, int q, int sub) { return (sub < 2 ? p : q) * kJacBig + (sub & 1) * kJacB; }
 
 // The waves' partial sums of NT 16 x 16 tiles, added in wave order and left by the first wave.
-template <int NT>
-__device__ __forceinline__ void jac_gram_store(const f64x4 (&acc)[NT], double (&red)[3][NT * kJacTile], double* __restrict__ out)
+template <typename T, int NT>
+__device__ __forceinline__ void jac_gram_store(const typename mma_tile<T>::acc (&acc)[NT], T (&red)[3][NT * kJacTile], T* __restrict__ out)
 {
     const int lane = lane_id(), wave = threadIdx.x >> 6, l16 = lane & 15, kg = lane >> 4;
     if (wave > 0) {
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) red[wave - 1][t * kJacTile + (kg + 4 * e) * 16 + l16] = acc[t][e];
+            for (int e = 0; e < 4; ++e) red[wave - 1][t * kJacTile + mma_tile<T>::row(kg, e) * 16 + l16] = acc[t][e];
     }
     __syncthreads();
     if (wave == 0) {
@@ -516,7 +521,7 @@ __device__ __forceinline__ void jac_gram_store(const f64x4 (&acc)[NT], double (&
         for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int at = t * kJacTile + (kg + 4 * e) * 16 + l16;
+                const int at = t * kJacTile + mma_tile<T>::row(kg, e) * 16 + l16;
                 out[at] = acc[t][e] + red[0][at] + red[1][at] + red[2][at];
             }
     }
@@ -525,26 +530,27 @@ __device__ __forceinline__ void jac_gram_store(const f64x4 (&acc)[NT], double (&
 // Partial Gram matrices of the 32-row blocks over one slice of the columns: part[slice][block][3][16][16].
 // grid (blocks, slices); four waves, each taking every fourth group of 16 columns (a lane reads four consecutive columns
 // of its row, which serve as four contraction steps of the fp64 MFMA for either operand).
-__global__ __launch_bounds__(256) void calib_jacobi_inside_gram_kernel(const double* __restrict__ G, int D, int slice_cols,
-                                                                       double* __restrict__ part)
+template <typename T>
+__global__ __launch_bounds__(256) void calib_jacobi_inside_gram_kernel(const T* __restrict__ G, int pitch, int slice_cols, T* __restrict__ part)
 {
-    __shared__ double red[3][kJacRec];
+    typedef typename mma_tile<T>::acc V4;
+    __shared__ T red[3][kJacRec];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kg = lane >> 4;
-    const double* gp = G + (size_t)(blockIdx.x * kJacBig + l16) * D + blockIdx.y * slice_cols + kg * 4;
-    const double* gq = gp + (size_t)kJacB * D;
-    f64x4 acc[3];
+    const T* gp = G + (size_t)(blockIdx.x * kJacBig + l16) * pitch + blockIdx.y * slice_cols + kg * 4;
+    const T* gq = gp + (size_t)kJacB * pitch;
+    V4 acc[3];
 #pragma unroll
-    for (int t = 0; t < 3; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int t = 0; t < 3; ++t) acc[t] = V4{0, 0, 0, 0};
     for (int c = wave * 16; c < slice_cols; c += 64) {
-        const f64x4 a = *reinterpret_cast<const f64x4*>(gp + c), b = *reinterpret_cast<const f64x4*>(gq + c);
+        const V4 a = *reinterpret_cast<const V4*>(gp + c), b = *reinterpret_cast<const V4*>(gq + c);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            acc[0] = mma_f64(a[e], a[e], acc[0]);
-            acc[1] = mma_f64(a[e], b[e], acc[1]);
-            acc[2] = mma_f64(b[e], b[e], acc[2]);
+            acc[0] = mma_step(a[e], a[e], acc[0]);
+            acc[1] = mma_step(a[e], b[e], acc[1]);
+            acc[2] = mma_step(b[e], b[e], acc[2]);
         }
     }
-    jac_gram_store(acc, red, part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kJacRec);
+    jac_gram_store<T, 3>(acc, red, part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kJacRec);
 }
 
 // Pairs of blocks of a step: those of a sweep, or neighbours
@@ -558,44 +564,46 @@ __device__ __forceinline__ void jac_pair(int n, int step, int k, int* p, int* q)
 
 // The same for the step's pairs of blocks: part[slice][pair][10][16][16], five tiles per workgroup (grid (pairs, slices, 2)).
 // The pair index runs fastest in both launches of a step, so a pair's sums are written and read on one die.
-__global__ __launch_bounds__(256) void calib_jacobi_gram_kernel(const double* __restrict__ G, int D, int step, int slice_cols,
-                                                                double* __restrict__ part)
+template <typename T>
+__global__ __launch_bounds__(256) void calib_jacobi_gram_kernel(const T* __restrict__ G, int D, int pitch, int step, int slice_cols,
+                                                                T* __restrict__ part)
 {
+    typedef typename mma_tile<T>::acc V4;
     constexpr int NT = kJacTiles / 2;
-    __shared__ double red[3][NT * kJacTile];
+    __shared__ T red[3][NT * kJacTile];
     int p, q;
     jac_pair(D / kJacBig, step, blockIdx.x, &p, &q);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kg = lane >> 4;
     const bool half = blockIdx.z != 0;  // uniform
-    const double* g[4];
+    const T* g[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) g[u] = G + (size_t)(jac_row(p, q, u) + l16) * D + blockIdx.y * slice_cols + kg * 4;
-    f64x4 acc[NT];
+    for (int u = 0; u < 4; ++u) g[u] = G + (size_t)(jac_row(p, q, u) + l16) * pitch + blockIdx.y * slice_cols + kg * 4;
+    V4 acc[NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int t = 0; t < NT; ++t) acc[t] = V4{0, 0, 0, 0};
     for (int c = wave * 16; c < slice_cols; c += 128) {  // two groups requested together, the second from a clamped column
-        f64x4 x[2][4];
+        V4 x[2][4];
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) x[u][k] = *reinterpret_cast<const f64x4*>(g[k] + min(c + 64 * u, slice_cols - 16));
+            for (int k = 0; k < 4; ++k) x[u][k] = *reinterpret_cast<const V4*>(g[k] + min(c + 64 * u, slice_cols - 16));
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             if (c + 64 * u >= slice_cols) break;  // uniform
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const double p0 = x[u][0][e], p1 = x[u][1][e], q0 = x[u][2][e], q1 = x[u][3][e];
+                const T p0 = x[u][0][e], p1 = x[u][1][e], q0 = x[u][2][e], q1 = x[u][3][e];
                 // tiles (0,0) (0,1) (1,1) (0,2) (1,2), or (2,2) (2,3) (3,3) (0,3) (1,3)
-                const double a = half ? q0 : p0, b = half ? q1 : p1, last = half ? q1 : q0;
-                acc[0] = mma_f64(a, a, acc[0]);
-                acc[1] = mma_f64(a, b, acc[1]);
-                acc[2] = mma_f64(b, b, acc[2]);
-                acc[3] = mma_f64(p0, last, acc[3]);
-                acc[4] = mma_f64(p1, last, acc[4]);
+                const T a = half ? q0 : p0, b = half ? q1 : p1, last = half ? q1 : q0;
+                acc[0] = mma_step(a, a, acc[0]);
+                acc[1] = mma_step(a, b, acc[1]);
+                acc[2] = mma_step(b, b, acc[2]);
+                acc[3] = mma_step(p0, last, acc[3]);
+                acc[4] = mma_step(p1, last, acc[4]);
             }
         }
     }
-    jac_gram_store(acc, red, part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kJacBigRec + (half ? NT * kJacTile : 0));
+    jac_gram_store<T, NT>(acc, red, part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kJacBigRec + (half ? NT * kJacTile : 0));
 }
 
 // cosine and sine of the rotation (g_p, g_q) -> (c g_p - s g_q, s g_p + c g_q) that makes two rows with squared norms aa,
@@ -616,9 +624,20 @@ __device__ __forceinline__ void jac_rotation(double aa, double bb, double ab, do
     *s = ok ? __builtin_bit_cast(double, ab_d) * hi * ci : 0.0;
     *tan = *s * ci;
 }
+__device__ __forceinline__ bool jac_open(float aa, float bb, float ab) { return ab * ab > 1e-14f * (aa * bb); }
+// (rows of norms whose fourth powers floats do not hold are left alone)
+__device__ __forceinline__ void jac_rotation(float aa, float bb, float ab, float* c, float* s, float* tan)
+{
+    const float d = bb - aa, h2 = fmaf(4.f * ab, ab, d * d), hi = __builtin_amdgcn_rsqf(fmaxf(h2, 1e-30f));
+    const bool ok = jac_open(aa, bb, ab) && h2 > 1e-30f;
+    const float c2 = fmaf(0.5f * fabsf(d), hi, 0.5f), ci = __builtin_amdgcn_rsqf(c2);
+    *c = ok ? c2 * ci : 1.f;
+    *s = ok ? __uint_as_float(__float_as_uint(ab) ^ (__float_as_uint(d) & 0x80000000u)) * hi * ci : 0.f;
+    *tan = *s * ci;
+}
 // What is applied to the rows turns by these: c so that c^2 + s^2 = 1 to rounding.  (As computed it is above 1 by 5e-17 on average
 // where the angles are small, ten sweeps of which added 1.8e-13 to every eigenvalue at D = 1024.)
-__device__ __forceinline__ double jac_unit(double c, double s) { return fma(0.5 * c, fma(-s, s, fma(-c, c, 1.0)), c); }
+template <typename T> __device__ __forceinline__ T jac_unit(T c, T s) { return fma((T)0.5 * c, fma(-s, s, fma(-c, c, (T)1)), c); }
 // (non-negative doubles are ordered like their bits; nothing waits for the result)
 __device__ __forceinline__ void conv_max(double* at, double v)
 {
@@ -635,7 +654,17 @@ __device__ __forceinline__ double row16_next(double v)
     return __builtin_bit_cast(double, w);
 }
 
+__device__ __forceinline__ float row16_next(float v)
+{
+    const int u = __float_as_int(v);
+    return __int_as_float(__builtin_amdgcn_update_dpp(u, u, 0x12f, 0xf, 0xf, false));
+}
+
 typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+template <typename T> struct vec2;
+template <> struct vec2<double> { typedef f64x2 type; };
+template <> struct vec2<float> { typedef f32x2 type; };
 constexpr int kJacLd = 2 * kJacB + 1;   // row pitch of a 32 x 32 matrix in LDS
 constexpr int kJacLt = kJacB + 1;       // of a 16 x 16 tile
 
@@ -650,11 +679,12 @@ constexpr int kJacLt = kJacB + 1;       // of a 16 x 16 tile
 // and (B_i, A_j) pass through LDS.  A round is one LDS round trip, a 2 x 2 block update, one rotation and one barrier: 0.27 us with
 // two groups on a compute unit.  With all 256 blocks, and every wave computing rotations, it took 0.31 us for one group and 0.47
 // for two (instruction issue); with every thread computing both rotations of its block from the whole matrix in LDS 0.6 for one.
-struct JacRounds {
-    f64x2 cs[kJacB + 1][kJacB];          // [round][pair]: cosine and sine
-    f64x2 unused[3 * kJacB];             // (where the other lanes of the wave that computes rotations write)
-    double cross[2][2][8][kJacB];        // [round parity][(A_i, B_j) | (B_i, A_j)][m - 1][i]
-    double zero[2][2][8][kJacB];         // (first row: the product that a round's rotation made zero)
+template <typename T> struct JacRounds {
+    typedef typename vec2<T>::type T2;
+    T2 cs[kJacB + 1][kJacB];          // [round][pair]: cosine and sine
+    T2 unused[3 * kJacB];             // (where the other lanes of the wave that computes rotations write)
+    T cross[2][2][8][kJacB];        // [round parity][(A_i, B_j) | (B_i, A_j)][m - 1][i]
+    T zero[2][2][8][kJacB];         // (first row: the product that a round's rotation made zero)
 };
 struct JacPlace { int i, j, m; bool rotates; };
 __device__ __forceinline__ JacPlace jac_place(int w)  // w: the wave's number in its group
@@ -665,35 +695,37 @@ __device__ __forceinline__ JacPlace jac_place(int w)  // w: the wave's number in
 }
 // In: thread (i, m)'s elements (A_i, A_j), (A_i, B_j), (B_i, A_j), (B_i, B_j) and pair i's squared norms aa, bb and inner product
 // ab.  Out: b00, b11 and, in the threads (i, 1), aa and bb after the rounds (of row i of either block).  17 barriers.
-__device__ __forceinline__ void jac_solve(JacRounds& L, const JacPlace& at, double& b00, double b01, double b10, double& b11, double& aa,
-                                          double& bb, double ab)
+template <typename T>
+__device__ __forceinline__ void jac_solve(JacRounds<T>& L, const JacPlace& at, T& b00, T b01, T b10, T& b11, T& aa,
+                                          T& bb, T ab)
 {
+    typedef typename vec2<T>::type T2;
     const int i = at.i, j = at.j, i1 = (i + 1) & 15, half = lane_id() >> 4;
     // where a round finds (A_i, B_j): thread (i, m + 1)'s, and for m = 8 thread (i + 9, 7)'s (B_i, A_j); and (B_i, A_j): thread
     // (i + 1, m - 1)'s (of m = 1 it is zero)
-    double* const from01 = at.m < 8 ? &L.cross[0][0][at.m][i] : &L.cross[0][1][6][(i + 9) & 15];
-    double* const from10 = at.m > 1 ? &L.cross[0][1][at.m - 2][i1] : &L.zero[0][0][0][i];
-    double* const to = &L.cross[0][0][at.m - 1][i];
+    T* const from01 = at.m < 8 ? &L.cross[0][0][at.m][i] : &L.cross[0][1][6][(i + 9) & 15];
+    T* const from10 = at.m > 1 ? &L.cross[0][1][at.m - 2][i1] : &L.zero[0][0][0][i];
+    T* const to = &L.cross[0][0][at.m - 1][i];
     constexpr int kParity = 2 * 8 * kJacB;
-    const f64x2 *Ri = &L.cs[0][i], *Rj = &L.cs[0][j];
-    f64x2* out = half == 0 ? &L.cs[0][i] : &L.unused[(half - 1) * kJacB + i];
+    const T2 *Ri = &L.cs[0][i], *Rj = &L.cs[0][j];
+    T2* out = half == 0 ? &L.cs[0][i] : &L.unused[(half - 1) * kJacB + i];
     const int step = half == 0 ? kJacB : 0;
-    auto rotation = [&](double abt) {
-        double c, s, tan;
+    auto rotation = [&](T abt) {
+        T c, s, tan;
         jac_rotation(aa, bb, abt, &c, &s, &tan);
-        *out = f64x2{c, s};
+        *out = T2{c, s};
         out += step;
         aa = fma(-tan, abt, aa);
         bb = row16_next(fma(tan, abt, bb));   // (the next round's B row)
     };
     auto round = [&](auto parity, bool last) {
         constexpr int odd = decltype(parity)::value * kParity;
-        const double c = Ri->x, s = Ri->y, cj = Rj->x, sj = Rj->y;
+        const T c = Ri->x, s = Ri->y, cj = Rj->x, sj = Rj->y;
         Ri += kJacB; Rj += kJacB;
         b01 = from01[odd];
         b10 = from10[odd];
-        const double r00 = c * b00 - s * b10, r01 = c * b01 - s * b11, r10 = s * b00 + c * b10, r11 = s * b01 + c * b11;
-        const double n01 = sj * r00 + cj * r01;
+        const T r00 = c * b00 - s * b10, r01 = c * b01 - s * b11, r10 = s * b00 + c * b10, r11 = s * b01 + c * b11;
+        const T n01 = sj * r00 + cj * r01;
         to[kParity - odd] = n01;
         to[kParity - odd + 8 * kJacB] = cj * r10 - sj * r11;
         if (at.rotates && !last) rotation(n01);  // uniform
@@ -704,14 +736,14 @@ __device__ __forceinline__ void jac_solve(JacRounds& L, const JacPlace& at, doub
     // (the first round reads what its threads hold from where a round's threads read)
     *from01 = b01;
     if (at.m > 1) *from10 = b10;
-    else from10[0] = b10, from10[kParity] = 0.0;
+    else from10[0] = b10, from10[kParity] = 0;
     if (at.rotates) rotation(ab);  // uniform
     __builtin_amdgcn_s_setprio(2);  // (the accumulating waves fill the gaps)
     __syncthreads();
 #pragma unroll 1
     for (int t = 0; t < kJacB; t += 2) {  // (not unrolled further: every launch starts with cold instruction caches)
         round(std::integral_constant<int, 0>{}, false);
-        if (t == 0 && at.m == 1) from10[0] = 0.0;
+        if (t == 0 && at.m == 1) from10[0] = 0;
         round(std::integral_constant<int, 1>{}, t + 2 == kJacB);
     }
     __builtin_amdgcn_s_setprio(0);
@@ -719,7 +751,7 @@ __device__ __forceinline__ void jac_solve(JacRounds& L, const JacPlace& at, doub
 // The largest |sin| of the 256 rotations among those that involved a row of squared norm >= lead (the rows that can still
 // change a leading eigenvector), by the norms the rows of A and B have now (diagonals of pitch `ld`); one wave, every lane
 // gets it.
-__device__ __forceinline__ double jac_largest(const JacRounds& L, const double* A, const double* B, int ld, double lead)
+__device__ __forceinline__ double jac_largest(const JacRounds<double>& L, const double* A, const double* B, int ld, double lead)
 {
     const int l16 = lane_id() & 15, kg = lane_id() >> 4;
     double smax = 0.0;
@@ -735,17 +767,18 @@ __device__ __forceinline__ double jac_largest(const JacRounds& L, const double* 
 // lane l: rows l % 16 of A and B of the accumulated matrix, kJacNc columns; 17 barriers.  (Sixteen moves: every row of B ends
 // in its place.)
 constexpr int kJacNc = 2 * kJacB / 8;   // columns per lane
-__device__ __forceinline__ void jac_accumulate(const JacRounds& L, double (&x)[kJacNc], double (&y)[kJacNc])
+template <typename T>
+__device__ __forceinline__ void jac_accumulate(const JacRounds<T>& L, T (&x)[kJacNc], T (&y)[kJacNc])
 {
     const int l16 = lane_id() & 15;
     __syncthreads();
 #pragma unroll 1
     for (int t = 0; t < kJacB; ++t) {
-        const f64x2 R = L.cs[t][l16];
-        const double c = jac_unit(R.x, R.y), s = R.y;
+        const typename vec2<T>::type R = L.cs[t][l16];
+        const T c = jac_unit(R.x, R.y), s = R.y;
 #pragma unroll
         for (int e = 0; e < kJacNc; ++e) {
-            const double xe = x[e], ye = y[e];
+            const T xe = x[e], ye = y[e];
             x[e] = c * xe - s * ye;
             y[e] = row16_next(s * xe + c * ye);
         }
@@ -758,19 +791,22 @@ __device__ __forceinline__ void jac_accumulate(const JacRounds& L, double (&x)[k
 // slice of the columns on the matrix cores.  Every slice repeats the small problem (the same numbers).
 // conv[block] keeps the largest |sin| of a rotation since the host cleared it (see jac_largest).
 constexpr int kJacInsideThreads = 4 * kWave;
-__global__ __launch_bounds__(kJacInsideThreads) void calib_jacobi_inside_kernel(double* __restrict__ G, int D, int slice_cols,
-                                                                                const double* __restrict__ part, int n_part,
+template <typename T>
+__global__ __launch_bounds__(kJacInsideThreads) void calib_jacobi_inside_kernel(T* __restrict__ G, int pitch, int slice_cols,
+                                                                                const T* __restrict__ part, int n_part,
                                                                                 double lead, double* __restrict__ conv)
 {
+    constexpr bool kConv = sizeof(T) == 8;   // (in floats nobody asks whether the rows have converged)
+    typedef typename mma_tile<T>::acc V4;
     constexpr int B2 = 2 * kJacB, LD = kJacLd;
-    __shared__ double Wb[2][B2 * LD], Qb[2][B2 * LD];   // Gram matrix and accumulated rotations
-    __shared__ JacRounds s_rounds;
-    __shared__ double s_conv[kJacB];
+    __shared__ T Wb[2][B2 * LD], Qb[2][B2 * LD];   // Gram matrix and accumulated rotations
+    __shared__ JacRounds<T> s_rounds;
+    __shared__ T s_conv[kJacB];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, kg = lane >> 4;
-    double* const gp = G + (size_t)(blockIdx.x * kJacBig + kg) * D + blockIdx.y * slice_cols + l16;
+    T* const gp = G + (size_t)blockIdx.x * kJacBig * pitch + blockIdx.y * slice_cols + l16;
     const int i = tid >> 4, j = tid & 15;
     {
-        double w8[3][8];
+        T w8[3][8];
 #pragma unroll
         for (int t = 0; t < 3; ++t)
 #pragma unroll
@@ -778,14 +814,14 @@ __global__ __launch_bounds__(kJacInsideThreads) void calib_jacobi_inside_kernel(
                 w8[t][u] = part[((size_t)min(u, n_part - 1) * gridDim.x + blockIdx.x) * kJacRec + t * kJacTile + tid];
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
-            double v = 0.0;
+            T v = 0;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v += u < n_part ? w8[t][u] : 0.0;
+            for (int u = 0; u < 8; ++u) v += u < n_part ? w8[t][u] : (T)0;
             const int r = i + (t == 2 ? kJacB : 0), c = j + (t >= 1 ? kJacB : 0);
             Wb[0][r * LD + c] = v;
             if (t == 1) Wb[0][c * LD + r] = v;
         }
-        for (int e = tid; e < B2 * B2; e += 256) Qb[0][(e >> 5) * LD + (e & 31)] = (e >> 5) == (e & 31) ? 1.0 : 0.0;
+        for (int e = tid; e < B2 * B2; e += 256) Qb[0][(e >> 5) * LD + (e & 31)] = (e >> 5) == (e & 31) ? 1 : 0;
     }
     __syncthreads();
     int cur = 0;
@@ -794,78 +830,79 @@ __global__ __launch_bounds__(kJacInsideThreads) void calib_jacobi_inside_kernel(
             calib_pair(kJacB, t, k & 7, a, b);
             *a += k < 8 ? 0 : kJacB; *b += k < 8 ? 0 : kJacB;
         };
-        double smax = 0.0;
+        T smax = 0;
 #pragma unroll 1
         for (int t = 0; t < kJacB - 1; ++t) {
             {
                 int pi, qi, pj, qj;
                 inside(t, i, &pi, &qi);
                 inside(t, j, &pj, &qj);
-                const double* W = Wb[cur]; const double* Q = Qb[cur];
-                double* Wn = Wb[cur ^ 1]; double* Qn = Qb[cur ^ 1];
-                const double aa = W[pi * LD + pi], bb = W[qi * LD + qi];
-                const double b00 = W[pi * LD + pj], b01 = W[pi * LD + qj], b10 = W[qi * LD + pj], b11 = W[qi * LD + qj];
-                const double x0 = Q[pi * LD + j], y0 = Q[qi * LD + j], x1 = Q[pi * LD + j + kJacB], y1 = Q[qi * LD + j + kJacB];
-                double c, s, cj, sj, tan;
+                const T* W = Wb[cur]; const T* Q = Qb[cur];
+                T* Wn = Wb[cur ^ 1]; T* Qn = Qb[cur ^ 1];
+                const T aa = W[pi * LD + pi], bb = W[qi * LD + qi];
+                const T b00 = W[pi * LD + pj], b01 = W[pi * LD + qj], b10 = W[qi * LD + pj], b11 = W[qi * LD + qj];
+                const T x0 = Q[pi * LD + j], y0 = Q[qi * LD + j], x1 = Q[pi * LD + j + kJacB], y1 = Q[qi * LD + j + kJacB];
+                T c, s, cj, sj, tan;
                 jac_rotation(aa, bb, W[pi * LD + qi], &c, &s, &tan);
                 jac_rotation(W[pj * LD + pj], W[qj * LD + qj], W[pj * LD + qj], &cj, &sj, &tan);
-                smax = fmax(aa, bb) >= lead ? fmax(smax, fabs(s)) : smax;
-                const double r00 = c * b00 - s * b10, r01 = c * b01 - s * b11, r10 = s * b00 + c * b10, r11 = s * b01 + c * b11;
+                if (kConv) smax = fmax(aa, bb) >= (T)lead ? fmax(smax, fabs(s)) : smax;
+                const T r00 = c * b00 - s * b10, r01 = c * b01 - s * b11, r10 = s * b00 + c * b10, r11 = s * b01 + c * b11;
                 Wn[pi * LD + pj] = cj * r00 - sj * r01;
                 Wn[pi * LD + qj] = sj * r00 + cj * r01;
                 Wn[qi * LD + pj] = cj * r10 - sj * r11;
                 Wn[qi * LD + qj] = sj * r10 + cj * r11;
-                const double cu = jac_unit(c, s);
+                const T cu = jac_unit(c, s);
                 Qn[pi * LD + j] = cu * x0 - s * y0; Qn[qi * LD + j] = s * x0 + cu * y0;
                 Qn[pi * LD + j + kJacB] = cu * x1 - s * y1; Qn[qi * LD + j + kJacB] = s * x1 + cu * y1;
             }
             __syncthreads();
             cur ^= 1;
         }
-        if (j == 0) s_conv[i] = smax;
+        if (kConv && j == 0) s_conv[i] = smax;
     }
-    double* const Qo = Qb[cur];
+    T* const Qo = Qb[cur];
     if (wave < 2) {
-        const double* W = Wb[cur];
+        const T* W = Wb[cur];
         const JacPlace at = jac_place(wave);
-        double b00 = W[at.i * LD + at.j], b11 = W[(kJacB + at.i) * LD + kJacB + at.j];
-        double aa = W[at.i * (LD + 1)], bb = W[(kJacB + at.i) * (LD + 1)];
-        jac_solve(s_rounds, at, b00, W[at.i * LD + kJacB + at.j], W[at.j * LD + kJacB + at.i], b11, aa, bb,
+        T b00 = W[at.i * LD + at.j], b11 = W[(kJacB + at.i) * LD + kJacB + at.j];
+        T aa = W[at.i * (LD + 1)], bb = W[(kJacB + at.i) * (LD + 1)];
+        jac_solve<T>(s_rounds, at, b00, W[at.i * LD + kJacB + at.j], W[at.j * LD + kJacB + at.i], b11, aa, bb,
                   W[at.i * LD + kJacB + at.i]);
         if (at.m == 1) { Wb[cur ^ 1][at.i * (LD + 1)] = aa; Wb[cur ^ 1][(kJacB + at.i) * (LD + 1)] = bb; }
     } else {
-        double x[kJacNc], y[kJacNc];
+        T x[kJacNc], y[kJacNc];
         const int c0 = ((wave & 1) * 4 + kg) * kJacNc;
 #pragma unroll
         for (int e = 0; e < kJacNc; ++e) { x[e] = Qo[l16 * LD + c0 + e]; y[e] = Qo[(kJacB + l16) * LD + c0 + e]; }
-        jac_accumulate(s_rounds, x, y);
+        jac_accumulate<T>(s_rounds, x, y);
 #pragma unroll
         for (int e = 0; e < kJacNc; ++e) { Qo[l16 * LD + c0 + e] = x[e]; Qo[(kJacB + l16) * LD + c0 + e] = y[e]; }
     }
     __syncthreads();
-    if (blockIdx.y == 0 && wave == 3) {
+    if constexpr (kConv) if (blockIdx.y == 0 && wave == 3) {
         const double* W = Wb[cur ^ 1];
         double smax = jac_largest(s_rounds, W, W + kJacB * (LD + 1), LD, lead);
 #pragma unroll
         for (int k = 0; k < kJacB; ++k) smax = fmax(smax, s_conv[k]);
         if (lane == 0 && smax > 0.0) conv_max(conv + blockIdx.x, smax);
     }
-    double qa[2][8];  // the accumulated rotations as MFMA operand: rows m 16 .. +16, contraction step s
+    auto row_of = [&](int s) { return 16 * (s >> 2) + mma_tile<T>::row(kg, s & 3); };   // of the block, in contraction step s
+    T qa[2][8];  // the accumulated rotations as MFMA operand: rows m 16 .. +16, contraction step s
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int s = 0; s < 8; ++s) qa[m][s] = Qo[(m * 16 + l16) * LD + 4 * s + kg];
+        for (int s = 0; s < 8; ++s) qa[m][s] = Qo[(m * 16 + l16) * LD + row_of(s)];
     for (int c = wave * 16; c < slice_cols; c += 64) {
-        double x[8];  // contraction step s: row 4 s + kg of the block
+        T x[8];
 #pragma unroll
-        for (int s = 0; s < 8; ++s) x[s] = gp[(size_t)(4 * s) * D + c];
+        for (int s = 0; s < 8; ++s) x[s] = gp[(size_t)row_of(s) * pitch + c];
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
-            f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
+            V4 acc = V4{0, 0, 0, 0};
 #pragma unroll
-            for (int s = 0; s < 8; ++s) acc = mma_f64(qa[m][s], x[s], acc);
+            for (int s = 0; s < 8; ++s) acc = mma_step(qa[m][s], x[s], acc);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) gp[(size_t)(m * 16 + 4 * e) * D + c] = acc[e];
+            for (int e = 0; e < 4; ++e) gp[(size_t)row_of(4 * m + e) * pitch + c] = acc[e];
         }
     }
 }
@@ -880,15 +917,18 @@ __global__ __launch_bounds__(kJacInsideThreads) void calib_jacobi_inside_kernel(
 // the partial sums, 2.4 for the last products, 1.1 between the halves, the rest for the launch and the matrix's way back to memory.
 // A call at D = 1024, r = 640: 15.4 ms with 16-row blocks, 11.6 with these; at D = 4096 239 and 155.
 constexpr int kJacThreads = 8 * kWave;   // waves 0, 1 and 2, 3: the groups' rounds; 4, 5 and 6, 7: their accumulated rotations
-__global__ __launch_bounds__(kJacThreads) void calib_jacobi_rotate_kernel(double* __restrict__ G, int D, int step, int slice_cols,
-                                                                          const double* __restrict__ part, int n_part, double lead,
+template <typename T>
+__global__ __launch_bounds__(kJacThreads) void calib_jacobi_rotate_kernel(T* __restrict__ G, int D, int pitch, int step, int slice_cols,
+                                                                          const T* __restrict__ part, int n_part, double lead,
                                                                           double* __restrict__ conv)
 {
     constexpr int LD = kJacLd, LT = kJacLt;
-    __shared__ double S[kJacTiles][kJacB * LT];          // Gram matrix
-    __shared__ double J[2][2][2 * kJacB * LD];           // [half][group] accumulated rotations
-    __shared__ double T[2][kJacB * LD];
-    __shared__ JacRounds s_rounds[2];
+    typedef typename mma_tile<T>::acc V4;
+    typedef typename vec2<T>::type V2;
+    __shared__ T S[kJacTiles][kJacB * LT];          // Gram matrix
+    __shared__ T J[2][2][2 * kJacB * LD];           // [half][group] accumulated rotations
+    __shared__ T H[2][kJacB * LD];
+    __shared__ JacRounds<T> s_rounds[2];
     __shared__ int s_any;
     int p, q;
     jac_pair(D / kJacBig, step, blockIdx.x, &p, &q);
@@ -900,33 +940,33 @@ __global__ __launch_bounds__(kJacThreads) void calib_jacobi_rotate_kernel(double
 
     // partial Gram matrices (at most 8), two elements per load, and this wave's first column tile, all requested together
     constexpr int NP = kJacBigRec / 2, NV = (NP + kJacThreads - 1) / kJacThreads;
-    f64x2 w8[NV][8];
+    V2 w8[NV][8];
 #pragma unroll
     for (int v = 0; v < NV; ++v)
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-            w8[v][u] = *reinterpret_cast<const f64x2*>(part + ((size_t)min(u, n_part - 1) * gridDim.x + blockIdx.x) * kJacBigRec +
+            w8[v][u] = *reinterpret_cast<const V2*>(part + ((size_t)min(u, n_part - 1) * gridDim.x + blockIdx.x) * kJacBigRec +
                                                        2 * min(tid + v * kJacThreads, NP - 1));
-    double* g[4];   // small block u, row kg
+    T* g[4];   // small block u
 #pragma unroll
-    for (int u = 0; u < 4; ++u) g[u] = G + (size_t)(jac_row(p, q, u) + kg) * D + blockIdx.y * slice_cols + l16;
-    double x[4][4];  // small block u, contraction step s: row 4 s + kg
+    for (int u = 0; u < 4; ++u) g[u] = G + (size_t)jac_row(p, q, u) * pitch + blockIdx.y * slice_cols + l16;
+    T x[4][4];  // small block u, contraction step s: row mma_tile::row(kg, s)
     auto load_tile = [&](int c) {
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int s = 0; s < 4; ++s) x[u][s] = g[u][(size_t)(4 * s) * D + c];
+            for (int s = 0; s < 4; ++s) x[u][s] = g[u][(size_t)mma_tile<T>::row(kg, s) * pitch + c];
     };
     if (wave * 16 < slice_cols) load_tile(wave * 16);  // uniform
     if (tid == 0) s_any = 0;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
         const int e = 2 * (tid + v * kJacThreads), tile = e / kJacTile, pos = e % kJacTile;
-        f64x2 sum = f64x2{0.0, 0.0};
+        V2 sum = V2{0, 0};
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            sum.x += u < n_part ? w8[v][u].x : 0.0;
-            sum.y += u < n_part ? w8[v][u].y : 0.0;
+            sum.x += u < n_part ? w8[v][u].x : (T)0;
+            sum.y += u < n_part ? w8[v][u].y : (T)0;
         }
         if (e < kJacBigRec) {
             S[tile][(pos >> 4) * LT + (pos & 15)] = sum.x;
@@ -950,56 +990,56 @@ __global__ __launch_bounds__(kJacThreads) void calib_jacobi_rotate_kernel(double
 #pragma unroll 1
     for (int h = 0; h < 2; ++h) {
         const int b = h ? 1 - grp : grp;  // group's blocks: P_grp and Q_b
-        double* const A = S[tile_pp(grp)]; double* const C = S[tile_qq(b)];
-        const double* const B = S[tile_pq(grp, b)];
+        T* const A = S[tile_pp(grp)]; T* const C = S[tile_qq(b)];
+        const T* const B = S[tile_pq(grp, b)];
         if (solver) {
-            double b00 = A[i * LT + j], b11 = C[i * LT + j], aa = A[i * (LT + 1)], bb = C[i * (LT + 1)];
-            jac_solve(s_rounds[grp], at, b00, B[i * LT + j], B[j * LT + i], b11, aa, bb, B[i * (LT + 1)]);
+            T b00 = A[i * LT + j], b11 = C[i * LT + j], aa = A[i * (LT + 1)], bb = C[i * (LT + 1)];
+            jac_solve<T>(s_rounds[grp], at, b00, B[i * LT + j], B[j * LT + i], b11, aa, bb, B[i * (LT + 1)]);
             A[i * LT + j] = A[j * LT + i] = b00;
             C[i * LT + j] = C[j * LT + i] = b11;
             if (at.m == 1) { A[i * (LT + 1)] = aa; C[i * (LT + 1)] = bb; }
         } else {
-            double xr[kJacNc], yr[kJacNc];
+            T xr[kJacNc], yr[kJacNc];
             const int c0 = ((wave & 1) * 4 + kg) * kJacNc;
 #pragma unroll
-            for (int e = 0; e < kJacNc; ++e) { xr[e] = c0 + e == l16 ? 1.0 : 0.0; yr[e] = c0 + e == kJacB + l16 ? 1.0 : 0.0; }
-            jac_accumulate(s_rounds[grp], xr, yr);
-            double* Jo = J[h][grp];
+            for (int e = 0; e < kJacNc; ++e) { xr[e] = c0 + e == l16 ? 1 : 0; yr[e] = c0 + e == kJacB + l16 ? 1 : 0; }
+            jac_accumulate<T>(s_rounds[grp], xr, yr);
+            T* Jo = J[h][grp];
 #pragma unroll
             for (int e = 0; e < kJacNc; ++e) { Jo[l16 * LD + c0 + e] = xr[e]; Jo[(kJacB + l16) * LD + c0 + e] = yr[e]; }
         }
         __syncthreads();
-        if (!solver && (wave & 1) && blockIdx.y == 0) {
+        if constexpr (sizeof(T) == 8) if (!solver && (wave & 1) && blockIdx.y == 0) {   // (in floats nobody asks)
             const double smax = jac_largest(s_rounds[grp], A, C, LT, lead);
             if (lane == 0 && smax > 0.0) conv_max(conv + blockIdx.x, smax);
         }
         if (h == 1) break;
         // (P0, Q1) and (Q0, P1) after the first half: rows of J1 W J2^T, W = the Gram matrix between (P0, Q0) and (P1, Q1).
-        // First T[m] = rows m of J1 W, a 16 x 16 tile per wave, then T[m] times the other rows of J2.
+        // First H[m] = rows m of J1 W, a 16 x 16 tile per wave, then H[m] times the other rows of J2.
         if (wave < 4) {
             const int m = wave >> 1, n = wave & 1;
-            f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
+            V4 acc = V4{0, 0, 0, 0};
 #pragma unroll
             for (int s = 0; s < 4; ++s)  // rows 4 s + kg of P0 ...
-                acc = mma_f64(J[0][0][(m * 16 + l16) * LD + 4 * s + kg], S[n ? kTile03 : kTile01][(4 * s + kg) * LT + l16], acc);
+                acc = mma_step(J[0][0][(m * 16 + l16) * LD + 4 * s + kg], S[n ? kTile03 : kTile01][(4 * s + kg) * LT + l16], acc);
 #pragma unroll
             for (int s = 0; s < 4; ++s)  // ... and of Q0 (the tile (P1, Q0) the other way round)
-                acc = mma_f64(J[0][0][(m * 16 + l16) * LD + kJacB + 4 * s + kg],
+                acc = mma_step(J[0][0][(m * 16 + l16) * LD + kJacB + 4 * s + kg],
                               n ? S[kTile23][(4 * s + kg) * LT + l16] : S[kTile12][l16 * LT + 4 * s + kg], acc);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) T[m][(kg + 4 * e) * LD + n * 16 + l16] = acc[e];
+            for (int e = 0; e < 4; ++e) H[m][mma_tile<T>::row(kg, e) * LD + n * 16 + l16] = acc[e];
         }
         __syncthreads();
         if (wave < 2) {
             const int m = wave;
-            f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
+            V4 acc = V4{0, 0, 0, 0};
 #pragma unroll
             for (int s = 0; s < 8; ++s)
-                acc = mma_f64(T[m][l16 * LD + 4 * s + kg], J[0][1][((1 - m) * 16 + l16) * LD + 4 * s + kg], acc);
+                acc = mma_step(H[m][l16 * LD + 4 * s + kg], J[0][1][((1 - m) * 16 + l16) * LD + 4 * s + kg], acc);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                if (m == 0) S[kTile03][(kg + 4 * e) * LT + l16] = acc[e];
-                else S[kTile12][l16 * LT + kg + 4 * e] = acc[e];
+                if (m == 0) S[kTile03][mma_tile<T>::row(kg, e) * LT + l16] = acc[e];
+                else S[kTile12][l16 * LT + mma_tile<T>::row(kg, e)] = acc[e];
             }
         }
         __syncthreads();
@@ -1013,13 +1053,13 @@ __global__ __launch_bounds__(kJacThreads) void calib_jacobi_rotate_kernel(double
             for (int a = 0; a < 2; ++a) {
                 const int u = a, v = 2 + (h ? 1 - a : a);  // small blocks
                 asm volatile("" ::: "memory");  // (the operands of all four products at once do not fit into the registers)
-                f64x4 acc[2];
+                V4 acc[2];
 #pragma unroll
                 for (int m = 0; m < 2; ++m) {
-                    acc[m] = f64x4{0.0, 0.0, 0.0, 0.0};
+                    acc[m] = V4{0, 0, 0, 0};
 #pragma unroll
                     for (int s = 0; s < 8; ++s)
-                        acc[m] = mma_f64(J[h][a][(m * 16 + l16) * LD + 4 * s + kg], s < 4 ? x[u][s & 3] : x[v][s & 3], acc[m]);
+                        acc[m] = mma_step(J[h][a][(m * 16 + l16) * LD + 16 * (s >> 2) + mma_tile<T>::row(kg, s & 3)], s < 4 ? x[u][s & 3] : x[v][s & 3], acc[m]);
                 }
 #pragma unroll
                 for (int e = 0; e < 4; ++e) { x[u][e] = acc[0][e]; x[v][e] = acc[1][e]; }
@@ -1027,7 +1067,7 @@ __global__ __launch_bounds__(kJacThreads) void calib_jacobi_rotate_kernel(double
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int s = 0; s < 4; ++s) g[u][(size_t)(4 * s) * D + c] = x[u][s];
+            for (int s = 0; s < 4; ++s) g[u][(size_t)mma_tile<T>::row(kg, s) * pitch + c] = x[u][s];
     }
 }
 

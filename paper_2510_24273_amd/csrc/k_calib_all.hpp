@@ -28,13 +28,7 @@
 namespace sals {
 
 // ---- 64 x 64 tiles of products of [D, D] matrices --------------------------------------------------------------------
-__device__ __forceinline__ f64x4 mma_step(double a, double b, f64x4 c) { return mma_f64(a, b, c); }
-__device__ __forceinline__ f32x4 mma_step(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-template <typename ACC> struct mma_tile;   // result element e of a 16 x 16 tile: row, column lane % 16
-template <> struct mma_tile<double> { typedef f64x4 acc; static __device__ __forceinline__ int row(int kg, int e) { return kg + 4 * e; } };
-template <> struct mma_tile<float> { typedef f32x4 acc; static __device__ __forceinline__ int row(int kg, int e) { return 4 * kg + e; } };
-
-// Tile (blockIdx.y, blockIdx.x) of A B^T (NN: of A B, B in doubles), summed in ACC.  A step is 128 bytes of a row: 32 floats or 16 doubles
+// Tile (blockIdx.y, blockIdx.x) of A B^T (NN: of A B), summed in ACC; rows of A are D apart, those of B ldb.  A step is 128 bytes of a row: 32 floats or 16 doubles
 // of the contraction.  Both operands go from memory straight into LDS, three steps ahead in four stages; eight waves, each half
 // of a step's contraction for a quarter of the tile.  16-byte piece p of row r lies at piece p ^ ((r >> 1) & 7): no bank conflicts.
 // Bound by the matrix cores from D = 2048 on (131 TFLOP/s in fp32, 66 in fp64); at D = 1024, one tile per compute unit, 22 and 38 us
@@ -46,10 +40,10 @@ template <typename TA, typename TB, bool NN> constexpr size_t prod_lds()
     return (size_t)kProdStages * (8192 + (NN ? 128 / sizeof(TA) * 64 * sizeof(TB) : 8192));
 }
 template <typename TA, typename TB, bool NN, typename ACC, typename Finish>
-__device__ __forceinline__ void calib_product(const TA* A, const TB* B, int D, Finish finish)
+__device__ __forceinline__ void calib_product(const TA* A, const TB* B, int D, int ldb, Finish finish)
 {
-    static_assert(NN ? sizeof(TB) == 8 : sizeof(TA) == sizeof(TB), "operand layout");
-    constexpr int KS = 128 / (int)sizeof(TA), EPV = 16 / (int)sizeof(TA), B_BYTES = NN ? KS * 512 : 8192, STAGE = 8192 + B_BYTES, ST = kProdStages;
+    static_assert(NN || sizeof(TA) == sizeof(TB), "operand layout");
+    constexpr int KS = 128 / (int)sizeof(TA), EPV = 16 / (int)sizeof(TA), RB = 64 * (int)sizeof(TB), B_BYTES = NN ? KS * RB : 8192, STAGE = 8192 + B_BYTES, ST = kProdStages;
     constexpr int NB = B_BYTES / 8192, NL = 1 + NB;   // loads of a wave per step
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kg = lane >> 4;
@@ -60,9 +54,14 @@ __device__ __forceinline__ void calib_product(const TA* A, const TB* B, int D, F
     const int prow = wave * 8 + (lane >> 3);
     const uint32_t piece = (uint32_t)(((lane & 7) ^ ((prow >> 1) & 7)) << 4);
     const uint32_t off_a = (uint32_t)prow * (uint32_t)D * sizeof(TA) + piece;
-    const uint32_t off_b = NN ? (uint32_t)(wave * 2 + (lane >> 5)) * (uint32_t)D * 8 + ((lane & 31) << 4) : off_a;
+    // NN: B as it lies, row k of a step in RB bytes; of floats, 16-byte piece p of row k lies at piece p ^ 4 (k / 4 % 4), so that the four
+    // groups of lanes that read four rows apart do not meet
+    constexpr int LPR = RB / 16, RPL = 8 * (64 / LPR);   // lanes a row, rows a load of all waves
+    const int krow = wave * (64 / LPR) + lane / LPR;
+    const uint32_t off_b = NN ? (uint32_t)krow * (uint32_t)ldb * sizeof(TB) + (uint32_t)(((lane % LPR) ^ (sizeof(TB) == 4 ? (krow >> 2 & 3) << 2 : 0)) << 4)
+                              : (uint32_t)prow * (uint32_t)ldb * sizeof(TB) + piece;
     const unsigned char* a = reinterpret_cast<const unsigned char*>(A + (size_t)r0 * D);
-    const unsigned char* b = reinterpret_cast<const unsigned char*>(NN ? B + c0 : B + (size_t)c0 * D);
+    const unsigned char* b = reinterpret_cast<const unsigned char*>(NN ? B + c0 : B + (size_t)c0 * ldb);
     const int n = D / KS;   // (at least 8)
     auto load = [&](int s) {
         const size_t t = (size_t)min(s, n - 1);   // (past the end: a step that nothing reads any more)
@@ -70,7 +69,7 @@ __device__ __forceinline__ void calib_product(const TA* A, const TB* B, int D, F
         load_lds16(a + t * 128, off_a, st);
         if (NN) {
 #pragma unroll
-            for (int i = 0; i < NB; ++i) load_lds16(b + (t * KS + 16 * i) * D * 8, off_b, st + 8192 * (1 + i));
+            for (int i = 0; i < NB; ++i) load_lds16(b + (t * KS + RPL * i) * ldb * sizeof(TB), off_b, st + 8192 * (1 + i));
         } else {
             load_lds16(b + t * 128, off_b, st + 8192);
         }
@@ -99,7 +98,8 @@ __device__ __forceinline__ void calib_product(const TA* A, const TB* B, int D, F
             if (NN) {
 #pragma unroll
                 for (int e = 0; e < EPV; ++e)
-                    y[u][e] = (ACC)*reinterpret_cast<const TB*>(st + 8192 + ((ks * 4 + kg) * EPV + e) * 512 + (cc + 16 * u) * 8);
+                    y[u][e] = (ACC)*reinterpret_cast<const TB*>(st + 8192 + ((ks * 4 + kg) * EPV + e) * RB +
+                                                                ((cc + 16 * u) * (int)sizeof(TB) ^ (sizeof(TB) == 4 ? kg << 6 : 0)));
             } else {
                 const VA t = *reinterpret_cast<const VA*>(st + 8192 + swz128(cc + 16 * u, ks * 4 + kg));
 #pragma unroll
@@ -153,14 +153,14 @@ __device__ __forceinline__ SymTile sym_tile(int block, int D)
     return SymTile{r, t - r * (r - 1) / 2, (w - nb) & 1};
 }
 template <typename TA, typename ACC, typename Finish>
-__device__ __forceinline__ void calib_product_sym(const TA* A, int D, const SymTile& tile, Finish finish)
+__device__ __forceinline__ void calib_product_sym(const TA* A, int D, int pitch, const SymTile& tile, Finish finish)
 {
     constexpr int KS = 256 / (int)sizeof(TA), EPV = 16 / (int)sizeof(TA), STAGE = 24576, ST = kProdStages;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];   // per stage: 64 rows | 32 rows
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kg = lane >> 4;
     const int part = wave & 1, ks = wave >> 1;
     const uint32_t lds0 = lds_offset(lds);
-    const size_t row_bytes = (size_t)D * sizeof(TA);
+    const size_t row_bytes = (size_t)pitch * sizeof(TA);
     auto at = [](int row, int pc) { return row * 256 + ((pc ^ (row & 15)) << 4); };
     const int prow = wave * 4 + kg;
     const uint32_t off = (uint32_t)prow * (uint32_t)row_bytes + (uint32_t)((l16 ^ (prow & 15)) << 4);
@@ -252,11 +252,11 @@ __device__ __forceinline__ uint32_t pack_pair(float x)
 }
 __device__ __forceinline__ float pair_value(uint32_t w) { return bf16hi(w) + bf16lo(w); }
 
-// The same for A B^T of such matrices: hi hi + hi lo + lo hi on the bf16 matrix cores, summed in fp32.  A step is 64 elements of a
+// The same for A B^T (NN: A B) of such matrices: hi hi + hi lo + lo hi on the bf16 matrix cores, summed in fp32.  A step is 64 elements of a
 // row, 32 for either half of the waves.  Bound by what a compute unit draws, 13 us a product at D = 1024, where fp32 instructions take 22.
 // finish(i, j, v): rows i .. i + 3 of column j, by the first four waves.
 constexpr size_t kPairLds = (size_t)kProdStages * 32768;
-template <typename Finish>
+template <bool NN, typename Finish>
 __device__ __forceinline__ void calib_product_pairs(const uint32_t* A, const uint32_t* B, int D, Finish finish)
 {
     constexpr int STAGE = 32768, ST = kProdStages;   // [A: two 32-element pieces of 64 rows | B]
@@ -269,7 +269,10 @@ __device__ __forceinline__ void calib_product_pairs(const uint32_t* A, const uin
     const int prow = wave * 8 + (lane >> 3);
     const uint32_t off = (uint32_t)prow * (uint32_t)D * 4 + (uint32_t)(((lane & 7) ^ ((prow >> 1) & 7)) << 4);
     const unsigned char* a = reinterpret_cast<const unsigned char*>(A + (size_t)r0 * D);
-    const unsigned char* b = reinterpret_cast<const unsigned char*>(B + (size_t)c0 * D);
+    // NN: B as it lies, row k of a step in 256 bytes, 16-byte piece p of row k at piece p ^ 4 (k / 8 % 4)
+    const int krow = wave * 4 + kg;
+    const uint32_t off_b = NN ? (uint32_t)krow * (uint32_t)D * 4 + (uint32_t)((l16 ^ ((krow >> 3 & 3) << 2)) << 4) : off;
+    const unsigned char* b = reinterpret_cast<const unsigned char*>(NN ? B + c0 : B + (size_t)c0 * D);
     const int n = D / 64;   // (at least 4)
     auto load = [&](int s) {
         const size_t at = (size_t)min(s, n - 1) * 256;   // (past the end: a step that nothing reads any more)
@@ -277,7 +280,7 @@ __device__ __forceinline__ void calib_product_pairs(const uint32_t* A, const uin
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             load_lds16(a + at + 128 * i, off, st + 8192 * i);
-            load_lds16(b + at + 128 * i, off, st + 16384 + 8192 * i);
+            load_lds16(NN ? b + (at / 4 + 32 * i) * D * 4 : b + at + 128 * i, off_b, st + 16384 + 8192 * i);
         }
     };
 #pragma unroll
@@ -289,12 +292,21 @@ __device__ __forceinline__ void calib_product_pairs(const uint32_t* A, const uin
         for (int v = 0; v < 2; ++v) acc[u][v] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int rr = (part >> 1) * 32 + l16, cc = (part & 1) * 32 + l16;
     struct Pair { u32x4 hi, lo; };
-    auto fragment = [&](const unsigned char* st, int row) {   // eight elements of a row, from 8 kg on
-        const u32x4 x = *reinterpret_cast<const u32x4*>(st + swz128(row, 2 * kg)), y = *reinterpret_cast<const u32x4*>(st + swz128(row, 2 * kg + 1));
+    auto split = [](const u32x4& x, const u32x4& y) {
         auto upper = [](uint32_t w0, uint32_t w1) { return __builtin_amdgcn_perm(w1, w0, 0x07060302u); };
         auto lower = [](uint32_t w0, uint32_t w1) { return __builtin_amdgcn_perm(w1, w0, 0x05040100u); };
         return Pair{u32x4{upper(x.x, x.y), upper(x.z, x.w), upper(y.x, y.y), upper(y.z, y.w)},
                     u32x4{lower(x.x, x.y), lower(x.z, x.w), lower(y.x, y.y), lower(y.z, y.w)}};
+    };
+    auto fragment = [&](const unsigned char* st, int row) {   // eight elements of a row, from 8 kg on
+        return split(*reinterpret_cast<const u32x4*>(st + swz128(row, 2 * kg)), *reinterpret_cast<const u32x4*>(st + swz128(row, 2 * kg + 1)));
+    };
+    auto column = [&](const unsigned char* st, int col) {   // eight elements of a column, from row 8 kg on
+        const unsigned char* at = st + kg * 2048 + ((col * 4) ^ (kg << 6));
+        uint32_t w[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[e] = *reinterpret_cast<const uint32_t*>(at + e * 256);
+        return split(u32x4{w[0], w[1], w[2], w[3]}, u32x4{w[4], w[5], w[6], w[7]});
     };
     auto mma = [](const u32x4& x, const u32x4& y, f32x4 c) {
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), c, 0, 0, 0);
@@ -306,7 +318,7 @@ __device__ __forceinline__ void calib_product_pairs(const uint32_t* A, const uin
         const unsigned char* st = lds + (s % ST) * STAGE + ks * 8192;
         Pair x[2], y[2];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) { x[u] = fragment(st, rr + 16 * u); y[u] = fragment(st + 16384, cc + 16 * u); }
+        for (int u = 0; u < 2; ++u) { x[u] = fragment(st, rr + 16 * u); y[u] = NN ? column(st + 16384, cc + 16 * u) : fragment(st + 16384, cc + 16 * u); }
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -340,7 +352,7 @@ __device__ __forceinline__ void calib_product_pairs(const uint32_t* A, const uin
 template <typename TA, bool ADD>
 __global__ __launch_bounds__(kProdThreads) void calib_apply_kernel(const TA* A, const double* B, const double* G, double f, double* Y, int D)
 {
-    calib_product<TA, double, true, double>(A, B, D, [&](int r, int c, double v) {
+    calib_product<TA, double, true, double>(A, B, D, D, [&](int r, int c, double v) {
         const size_t at = (size_t)r * D + c;
         Y[at] = ADD ? fma(f, v, G[at]) : f * v;
     });
@@ -359,7 +371,7 @@ __global__ __launch_bounds__(kProdThreads) void calib_angles_kernel(const double
     double most = 0.0, sum = 0.0;
     const SymTile tile = sym_tile(blockIdx.x, D);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    calib_product_sym<double, double>(G, D, tile, [&](int rb, int cb, const f64x4& v, bool both) {
+    calib_product_sym<double, double>(G, D, D, tile, [&](int rb, int cb, const f64x4& v, bool both) {
         const int j = tile.col * 64 + tile.half * 32 + cb * 16 + (lane & 15);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -399,14 +411,16 @@ __global__ __launch_bounds__(kProdThreads) void calib_angles_kernel(const double
 // Products and norms are scaled by the power of two that takes the largest norm below one: any covariance that fp64 holds has products
 // that floats hold (angles do not depend on the scale).
 constexpr double kAllDamp = 0.1, kAllOpen = 1e-24, kAllTail = 1e-3;
+constexpr double kFloatOpen = 1e-13;   // of rows in floats, whose products are off by 1e-7 of the norms
 __device__ __forceinline__ double all_scale(const double* __restrict__ norm) { return ldexp(1.0, -__builtin_amdgcn_frexp_exp(norm[0])); }
 struct AllPair { bool counts; double d, h2; };
-__device__ __forceinline__ AllPair all_pair(double ni, double nj, double ab, double least)
+__device__ __forceinline__ AllPair all_pair(double ni, double nj, double ab, double least, double open)
 {
     const double aa = ni * ni, bb = nj * nj, d = bb - aa;
-    return AllPair{fmax(aa, bb) >= least && ab * ab > kAllOpen * (aa * bb), d, fma(4.0 * ab, ab, d * d)};
+    return AllPair{fmax(aa, bb) >= least && ab * ab > open * (aa * bb), d, fma(4.0 * ab, ab, d * d)};
 }
-__global__ __launch_bounds__(kProdThreads) void calib_gram_kernel(const double* __restrict__ G, int D, const double* __restrict__ norm, int r,
+template <typename T>
+__global__ __launch_bounds__(kProdThreads) void calib_gram_kernel(const T* __restrict__ G, int D, int pitch, const double* __restrict__ norm, int r,
                                                                   float* __restrict__ W, float* __restrict__ off)
 {
     __shared__ float s_off[2][4][64];   // of the tile's rows by 16-column block, of its columns by 16-row block (the diagonal: all the former)
@@ -414,16 +428,16 @@ __global__ __launch_bounds__(kProdThreads) void calib_gram_kernel(const double* 
     const SymTile tile = sym_tile(blockIdx.x, D);
     const int lane = threadIdx.x & 63, l16 = lane & 15, kg = lane >> 4;
     const int i0 = tile.row * 64, j0 = tile.col * 64 + tile.half * 32;
-    calib_product_sym<double, double>(G, D, tile, [&](int rb, int cb, const f64x4& v, bool both) {
+    calib_product_sym<T, T>(G, D, pitch, tile, [&](int rb, int cb, const typename mma_tile<T>::acc& v, bool both) {
         const int j = j0 + cb * 16 + l16;
         float col = 0.f;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int at = rb * 16 + mma_tile<double>::row(kg, e), i = i0 + at;
+            const int at = rb * 16 + mma_tile<T>::row(kg, e), i = i0 + at;
             const double ab = v[e] * unit * unit;
             W[(size_t)i * D + j] = (float)ab;
             if (both) W[(size_t)j * D + i] = (float)ab;
-            const AllPair p = all_pair(norm[i] * unit, norm[j] * unit, ab, least);
+            const AllPair p = all_pair(norm[i] * unit, norm[j] * unit, ab, least, sizeof(T) == 8 ? kAllOpen : kFloatOpen);
             const float share = i != j && p.counts ? (float)(ab * ab * rsqrt_f64(p.h2)) : 0.f;
             col += share;
             const float t = row16_sum(share);
@@ -451,7 +465,8 @@ __global__ __launch_bounds__(kProdThreads) void calib_gram_kernel(const double* 
 // after the other in a workgroup.)
 constexpr int kAngleRows = 8;
 __global__ __launch_bounds__(256) void calib_all_angles_kernel(const float* __restrict__ W, int D, const double* __restrict__ norm, int r,
-                                                               const float* __restrict__ off, uint32_t* __restrict__ E, double* __restrict__ found)
+                                                               const float* __restrict__ off, double open, uint32_t* __restrict__ E,
+                                                               double* __restrict__ found)
 {
     static_assert(kAngleRows == 8 && kCalThreads == 256, "32 lanes a row; D is a multiple of the columns");
     __shared__ double s_sum[4];
@@ -476,7 +491,7 @@ __global__ __launch_bounds__(256) void calib_all_angles_kernel(const float* __re
     for (int u = 0; u < kAngleRows; ++u) {
         const int i = i0 + u;
         const double ab = w[u], ni = norm[i] * unit, o = (double)s_off[u] + off_j;
-        const AllPair p = all_pair(ni, nj, ab, least);
+        const AllPair p = all_pair(ni, nj, ab, least, open);
         const bool counts = p.counts && i != j;
         const double s = counts ? ab * rsqrt_f64(fma(kAllDamp * o, o, p.h2)) : 0.0;
         E[(size_t)i * D + j] = pack_pair((float)(p.d < 0.0 || (p.d == 0.0 && i > j) ? s : -s));
@@ -490,17 +505,15 @@ __global__ __launch_bounds__(256) void calib_all_angles_kernel(const float* __re
 }
 
 // ---- Polar factor -----------------------------------------------------------------------------------------------------
-// O = d I + s S + t T + f A B^T (S, T: N > 0, N > 1) from pairs of bf16, left as such pairs or (LAST) in fp32; N > 0: also its transpose,
-// OT (16 bytes a lane).  SQUARE: also the sum of squares of every tile of O.
+// O = d I + s S + t T + f A B^T (S, T: N > 0, N > 1; N == 1: A B) from pairs of bf16, left as such pairs or (LAST) in fp32.  SQUARE: also
+// the sum of squares of every tile of O.
 template <int N, bool SQUARE, bool LAST>
 __global__ __launch_bounds__(kProdThreads) void calib_polar_kernel(const uint32_t* A, const uint32_t* B, int D, float f, float d, float s,
-                                                                   const uint32_t* S, float t, const uint32_t* T, uint32_t* O, uint32_t* OT,
-                                                                   double* square)
+                                                                   const uint32_t* S, float t, const uint32_t* T, uint32_t* O, double* square)
 {
     __shared__ double s_sum[4];
     double sum = 0.0;
-    calib_product_pairs(A, B, D, [&](int i0, int j, const f32x4& v) {
-        u32x4 w;
+    calib_product_pairs<N == 1>(A, B, D, [&](int i0, int j, const f32x4& v) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int i = i0 + e;
@@ -508,11 +521,9 @@ __global__ __launch_bounds__(kProdThreads) void calib_polar_kernel(const uint32_
             float o = f * v[e];
             if (N > 0) o = fmaf(s, pair_value(S[at]), o);
             if (N > 1) { o = fmaf(t, pair_value(T[at]), o); o += i == j ? d : 0.f; }
-            w[e] = LAST ? __float_as_uint(o) : pack_pair(o);
-            O[at] = w[e];
+            O[at] = LAST ? __float_as_uint(o) : pack_pair(o);
             if (SQUARE) sum += (double)o * (double)o;
         }
-        if (N > 0) *reinterpret_cast<u32x4*>(OT + (size_t)j * D + i0) = w;
     });
     if (!SQUARE) return;
 #pragma unroll
@@ -523,11 +534,11 @@ __global__ __launch_bounds__(kProdThreads) void calib_polar_kernel(const uint32_
     if (threadIdx.x == 0) square[blockIdx.y * gridDim.x + blockIdx.x] = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
 }
 // The last step in fp32: O = X X^T ...
-__global__ __launch_bounds__(kProdThreads) void calib_polar_square_kernel(const float* X, int D, float* O)
+__global__ __launch_bounds__(kProdThreads) void calib_polar_square_kernel(const float* X, int D, int pitch, float* O)
 {
     const SymTile tile = sym_tile(blockIdx.x, D);
     const int lane = threadIdx.x & 63;
-    calib_product_sym<float, float>(X, D, tile, [&](int rb, int cb, const f32x4& v, bool both) {
+    calib_product_sym<float, float>(X, D, pitch, tile, [&](int rb, int cb, const f32x4& v, bool both) {
         const int j = tile.col * 64 + tile.half * 32 + cb * 16 + (lane & 15);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -537,13 +548,12 @@ __global__ __launch_bounds__(kProdThreads) void calib_polar_square_kernel(const 
         }
     });
 }
-// ... and O = f A B^T + s S
-__global__ __launch_bounds__(kProdThreads) void calib_polar_last_kernel(const float* A, const float* B, int D, float f, float s, const float* S,
-                                                                        float* O)
+// ... and O = f A B + s B
+__global__ __launch_bounds__(kProdThreads) void calib_polar_last_kernel(const float* A, const float* B, int D, float f, float s, float* O)
 {
-    calib_product<float, float, false, float>(A, B, D, [&](int i, int j, float v) {
+    calib_product<float, float, true, float>(A, B, D, D, [&](int i, int j, float v) {
         const size_t at = (size_t)i * D + j;
-        O[at] = fmaf(s, S[at], f * v);
+        O[at] = fmaf(s, B[at], f * v);
     });
 }
 // delta = X X^T - I, summed in fp64, and its rounding to pairs of bf16
@@ -551,7 +561,7 @@ __global__ __launch_bounds__(kProdThreads) void calib_defect_kernel(const float*
 {
     const SymTile tile = sym_tile(blockIdx.x, D);
     const int lane = threadIdx.x & 63;
-    calib_product_sym<float, double>(X, D, tile, [&](int rb, int cb, const f64x4& v, bool both) {
+    calib_product_sym<float, double>(X, D, D, tile, [&](int rb, int cb, const f64x4& v, bool both) {
         const int j = tile.col * 64 + tile.half * 32 + cb * 16 + (lane & 15);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -567,12 +577,52 @@ __global__ __launch_bounds__(kProdThreads) void calib_defect_kernel(const float*
 // delta <- -delta / 2 + 3/8 delta^2 (the square, 1e-12, from the rounded one)
 __global__ __launch_bounds__(kProdThreads) void calib_correction_kernel(const uint32_t* rounded, int D, double* delta)
 {
-    calib_product_pairs(rounded, rounded, D, [&](int i0, int j, const f32x4& v) {
+    calib_product_pairs<false>(rounded, rounded, D, [&](int i0, int j, const f32x4& v) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const size_t at = (size_t)(i0 + e) * D + j;
             delta[at] = fma(0.375, (double)v[e], -0.5 * delta[at]);
         }
+    });
+}
+
+// ---- Rows in floats -----------------------------------------------------------------------------------------------------
+// From the factor to nearly orthogonal rows it is as far in floats as in doubles, and most of what is computed on the way only steers.
+// So the rows are taken there in floats, [G | V], D rows of 2 D floats: G = V times the factor (scaled so that its largest norm is about
+// one) and V the orthogonal matrix that all transformations so far amount to.  A transformation is that of above: steps inside and next to
+// blocks (calib_jacobi_*<float>), a polar factor, and one product, of [G | V].  Its polar factor is sloppier (pairs of bf16 to the end, see
+// kFloatPolar): V is made orthogonal behind one of the last transformations and at the end, by one Newton-Schulz step each in fp32, and at
+// last to rounding, in fp64, as it is applied to the factor's doubles: what it cost in bits is some angles of the size of fp32 rounding over the
+// relative distance of two eigenvalues, which the fp64 steps that follow take out.  Fewer fp64 products round the result: eigenvalues off by
+// 1e-15 of the largest one where they were by 3e-15, D = 1024, r = 640.
+// At D = 1024 a transformation takes 0.27 ms (fp64: 0.38), of which the product takes 37 us (131 TFLOP/s, the fp32 matrix cores' rate), the polar
+// factor 100, the steps in blocks 65, the Gram matrix and the angles 26; and no sweep (0.85 ms) comes before them.
+__global__ __launch_bounds__(kCalThreads) void calib_float_rows_kernel(const double* __restrict__ G, int D, double scale, float* __restrict__ GV)
+{
+    const int i = blockIdx.x;
+    for (int d = threadIdx.x; d < D; d += kCalThreads) {
+        GV[(size_t)i * 2 * D + d] = (float)(G[(size_t)i * D + d] * scale);
+        GV[(size_t)i * 2 * D + D + d] = d == i ? 1.f : 0.f;
+    }
+}
+// norms of the rows of G, one wave a row
+__global__ __launch_bounds__(256) void calib_float_norm_kernel(const float* __restrict__ GV, int D, double* __restrict__ norm)
+{
+    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
+    double sum = 0.0;
+    for (int d = lane_id() * 4; d < D; d += 256) {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(GV + (size_t)i * 2 * D + d);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum = fma((double)x[e], (double)x[e], sum);
+    }
+    sum = wave_sum_f64(sum);
+    if (lane_id() == 0) norm[i] = sqrt(sum);
+}
+// Y = f A B + s B; columns of B and Y as the grid has them, rows ldb and ldy apart
+__global__ __launch_bounds__(kProdThreads) void calib_float_apply_kernel(const float* A, const float* B, int D, int ldb, float f, float s, float* Y, int ldy)
+{
+    calib_product<float, float, true, float>(A, B, D, ldb, [&](int i, int j, float v) {
+        Y[(size_t)i * ldy + j] = s != 0.f ? fmaf(s, B[(size_t)i * ldb + j], f * v) : f * v;
     });
 }
 

@@ -22,8 +22,9 @@ struct PolarPlan {
     double tau, top;         // X starts as (I + tau E) / top
     double a[kPolarSteps];   // the steps' scales
 };
-// a2: sum of squares of E E^T, of which the fourth root bounds |E|.  What is no number, or infinite, has no plan.
-inline PolarPlan polar_plan(double a2)
+// a2: sum of squares of E E^T, of which the fourth root bounds |E|.  What is no number, or infinite, has no plan.  The scaled steps end
+// with singular values from `near` on.
+inline PolarPlan polar_plan(double a2, double near = kPolarNear)
 {
     PolarPlan P{};
     if (!std::isfinite(a2) || a2 < 0.0) return P;
@@ -32,13 +33,13 @@ inline PolarPlan polar_plan(double a2)
     const double tb = P.tau * bound;
     P.top = std::sqrt(1.0 + tb * tb);
     double low = 1.0 / P.top;
-    P.one_more = low < kPolarNear;   // (angles so small to begin with are done by the first step)
+    P.one_more = low < near;   // (angles so small to begin with are done by the first step)
     do {
         if (P.n == kPolarSteps) return PolarPlan{};
-        const double a = low < kPolarNear ? std::sqrt(3.0 / (1.0 + low + low * low)) : 1.0, x = a * low;
+        const double a = low < near ? std::sqrt(3.0 / (1.0 + low + low * low)) : 1.0, x = a * low;
         P.a[P.n++] = a;
         low = 0.5 * x * (3.0 - x * x);
-    } while (low < kPolarNear);
+    } while (low < near);
     return P;
 }
 

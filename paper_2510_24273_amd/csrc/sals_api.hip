@@ -2050,6 +2050,19 @@ namespace {
 // 43.8 / 43.0 / 44.1 (58.9), 3072 67.9 / 68.0 / 66.9 / 63.9 (80.3), 3584 111 / 104 / 102 / 98.6 (109), 4096 159 / 149 / 142 / 140 (141).
 constexpr int kAllMaxD = 3584;
 inline int all_first(int D) { return D <= 2048 ? 1 : D < 3072 ? 3 : 4; }
+// Up to kFloatMaxD the long way, in place of the first sweep and of the transformations that follow it, is gone in floats (k_calib_all.hpp):
+// transformations until one has started from |E| <= kFloatLast, V made orthogonal once, in fp32, behind the first one that starts from
+// kFloatPolish or less.  A call, r = 5/8 D, in ms without and with it, D = 256 1.77 / 1.50, 512 2.73 / 2.10, 1024 4.75 / 3.48, 1536 12.8 / 10.6,
+// 2048 21.2 / 18.3, 2560 44.4 / 39.4, 3072 66.3 / 65.9, 3584 99.2 / 100.8; D = 1024 with spectra c^-2 5.5 / 4.0, 10^(-6 c / D) 5.1 / 4.1,
+// sixteenfold eigenvalues 9.6 / 8.2.  kFloatLast 0.3 and 0.03: 3.53 and 3.66 at D = 1024; kFloatPolish 1.5 and 6: 3.68 and 3.43, but 4.24 against
+// 4.01 with a spectrum c^-2; steps next to blocks twice: 3.72.
+// Not begun where the rows of the factor are nearly orthogonal as they are, or of nearly equal norms (kFloatSpread of each other): eigenvalues
+// that close are told apart in fp64 only, and the polar factors' rounding would mix them (eigenvalues within 1e-3: 6.3 ms, and 4.8).
+constexpr int kFloatMaxD = 2560;
+constexpr double kFloatFirst = 0.1, kFloatSpread = 0.9, kFloatLast = 0.1, kFloatPolish = 3.5;
+// singular values of their polar factors: one step further from here on, which leaves 3 e-3 of X X^T - I (as good as 7e-6: 3.6 ms at D = 1024
+// with either, but three steps instead of four; 0.9 takes more transformations)
+constexpr double kFloatPolar = 0.97;
 // the series of the exponential: cut behind E^4 it differs from an orthogonal matrix by |E|^6 / 72
 constexpr double kSeriesNorm = 4e-3;
 // the product kernels' dynamic LDS, beyond the default limit
@@ -2058,10 +2071,12 @@ sals_status calib_all_lds(bool series)
     auto allow = [](const void* kern, size_t bytes) {
         return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
     };
-    constexpr size_t nt = prod_lds<float, float, false>();
+    constexpr size_t nn = prod_lds<float, float, true>();
     if (!allow(reinterpret_cast<const void*>(calib_angles_kernel), kSymLds)) return SALS_ERR_HIP;
     if (!series) return SALS_OK;
-    const bool ok = allow(reinterpret_cast<const void*>(calib_gram_kernel), kSymLds) &&
+    const bool ok = allow(reinterpret_cast<const void*>(calib_gram_kernel<double>), kSymLds) &&
+                    allow(reinterpret_cast<const void*>(calib_gram_kernel<float>), kSymLds) &&
+                    allow(reinterpret_cast<const void*>(calib_float_apply_kernel), nn) &&
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<0, true, false>), kPairLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<0, false, false>), kPairLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<1, false, false>), kPairLds) &&
@@ -2069,7 +2084,7 @@ sals_status calib_all_lds(bool series)
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<2, false, false>), kPairLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<2, false, true>), kPairLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_square_kernel), kSymLds) &&
-                    allow(reinterpret_cast<const void*>(calib_polar_last_kernel), nt) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_last_kernel), nn) &&
                     allow(reinterpret_cast<const void*>(calib_defect_kernel), kSymLds) &&
                     allow(reinterpret_cast<const void*>(calib_correction_kernel), kPairLds) &&
                     allow(reinterpret_cast<const void*>(calib_apply_kernel<float, false>), prod_lds<float, double, true>()) &&
@@ -2156,24 +2171,145 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         return 0.999 * nr * nr;
     };
     auto block_step = [&](int step) {  // rotates the pairs of blocks of a step of a sweep, or neighbours
-        hipLaunchKernelGGL(calib_jacobi_gram_kernel, dim3(n_pairs, n_part, 2), dim3(256), 0, st, rows, D, step, D / n_part, part);
-        hipLaunchKernelGGL(calib_jacobi_rotate_kernel, dim3(n_pairs, slices), dim3(kJacThreads), 0, st, rows, D, step, D / slices,
+        hipLaunchKernelGGL((calib_jacobi_gram_kernel<double>), dim3(n_pairs, n_part, 2), dim3(256), 0, st, rows, D, D, step, D / n_part, part);
+        hipLaunchKernelGGL((calib_jacobi_rotate_kernel<double>), dim3(n_pairs, slices), dim3(kJacThreads), 0, st, rows, D, D, step, D / slices,
                            part, n_part, lead, conv);
     };
     auto inside_step = [&]() {
-        hipLaunchKernelGGL(calib_jacobi_inside_gram_kernel, dim3(n_blocks, n_part), dim3(256), 0, st, rows, D, D / n_part, part);
-        hipLaunchKernelGGL(calib_jacobi_inside_kernel, dim3(n_blocks, slices), dim3(kJacInsideThreads), 0, st, rows, D, D / slices, part,
+        hipLaunchKernelGGL((calib_jacobi_inside_gram_kernel<double>), dim3(n_blocks, n_part), dim3(256), 0, st, rows, D, D / n_part, part);
+        hipLaunchKernelGGL((calib_jacobi_inside_kernel<double>), dim3(n_blocks, slices), dim3(kJacInsideThreads), 0, st, rows, D, D / slices, part,
                            n_part, lead, conv);
     };
     const dim3 tile_grid(D / 64, D / 64), sym_grid(n_tiles), prod(kProdThreads);
-    bool settled = false;
+    // Orthogonal polar factor of I + E in floats, X or X2, from E and A = E E^T (as pairs of bf16), with room for Y (which may be E or A).
+    // `exact`: the last step in fp32 (otherwise in pairs, as all others).
+    // The defect of (X X^T) X is quadratic in that of X; X (X X^T) is the same only as long as X commutes with its transpose, and what
+    // rounding takes from that would stay.
+    auto polar_factor = [&](const PolarPlan& P, const uint32_t* E, const uint32_t* A, uint32_t* Y, uint32_t* X, uint32_t* X2, bool exact) -> const float* {
+        auto step = [&](auto n, bool fp32, const uint32_t* L, const uint32_t* R, double f, double d, double s, const uint32_t* S, double t,
+                        const uint32_t* T, uint32_t* O) {
+            constexpr int N = decltype(n)::value;
+            if (fp32) hipLaunchKernelGGL((calib_polar_kernel<N, false, true>), tile_grid, prod, kPairLds, st, L, R, D, (float)f, (float)d,
+                                         (float)s, S, (float)t, T, O, nullptr);
+            else hipLaunchKernelGGL((calib_polar_kernel<N, false, false>), tile_grid, prod, kPairLds, st, L, R, D, (float)f, (float)d,
+                                    (float)s, S, (float)t, T, O, nullptr);
+        };
+        const double w = 0.5 * P.a[0] * P.a[0] * P.a[0] / (P.top * P.top * P.top), c1 = 1.5 * P.a[0] / P.top - w;
+        const bool more = P.one_more && !exact;   // (the unscaled step in pairs as well)
+        const int n = P.n + (more ? 1 : 0);
+        step(std::integral_constant<int, 2>{}, n == 1, A, E, w * P.tau * P.tau * P.tau, c1, c1 * P.tau, E, -w * P.tau * P.tau, A, X);
+        for (int k = 1; k < n; ++k) {
+            const double a = k < P.n ? P.a[k] : 1.0;
+            step(std::integral_constant<int, 0>{}, false, X, X, 1.0, 0.0, 0.0, nullptr, 0.0, nullptr, Y);
+            step(std::integral_constant<int, 1>{}, k == n - 1, Y, X, -0.5 * a * a * a, 0.0, 1.5 * a, X, 0.0, nullptr, X2);
+            std::swap(X, X2);
+        }
+        if (P.one_more && exact) {
+            float *const x = reinterpret_cast<float*>(X), *const x2 = reinterpret_cast<float*>(X2), *const y = reinterpret_cast<float*>(Y);
+            hipLaunchKernelGGL(calib_polar_square_kernel, sym_grid, prod, kSymLds, st, x, D, D, y);
+            hipLaunchKernelGGL(calib_polar_last_kernel, tile_grid, prod, (prod_lds<float, float, true>()), st, y, x, D, -0.5f, 1.5f, x2);
+            std::swap(X, X2);
+        }
+        return reinterpret_cast<const float*>(X);
+    };
+    // to = X made orthogonal, times `from`, by way of `between` and C; `rounded` is room for a matrix of pairs
+    auto correct_and_apply = [&](const float* X, uint32_t* rounded, const double* from, double* between, double* to) {
+        hipLaunchKernelGGL(calib_defect_kernel, sym_grid, prod, kSymLds, st, X, D, C, rounded);
+        hipLaunchKernelGGL(calib_correction_kernel, tile_grid, prod, kPairLds, st, rounded, D, C);
+        hipLaunchKernelGGL((calib_apply_kernel<float, false>), tile_grid, prod, (prod_lds<float, double, true>()), st, X, from, nullptr, 1.0, between, D);
+        hipLaunchKernelGGL((calib_apply_kernel<double, true>), tile_grid, prod, (prod_lds<double, double, true>()), st, C, between, between, 1.0, to, D);
+    };
+    // The long way in floats: an orthogonal matrix times the factor into `rows`, nearly orthogonal rows mostly; *ok false: the factor is still
+    // there (and C, unless a transformation was begun, which takes rows that are not orthogonal).
+    auto float_rows = [&](bool* ok) -> sals_status {
+        *ok = false;
+        float *cur = reinterpret_cast<float*>(at(off.Y0)), *nxt = reinterpret_cast<float*>(at(off.Y1));
+        uint32_t *const c0 = reinterpret_cast<uint32_t*>(C), *const c1 = c0 + (size_t)D * D;
+        float* const fpart = reinterpret_cast<float*>(part);
+        int expo;
+        std::frexp(std::sqrt(n0), &expo);   // (rows of the factor have norms of at most D^1/4 sqrt(n0))
+        auto near_step = [&](int step) {
+            hipLaunchKernelGGL((calib_jacobi_gram_kernel<float>), dim3(n_pairs, n_part, 2), dim3(256), 0, st, cur, D, 2 * D, step, D / n_part, fpart);
+            hipLaunchKernelGGL((calib_jacobi_rotate_kernel<float>), dim3(n_pairs, slices), dim3(kJacThreads), 0, st, cur, D, 2 * D, step, 2 * D / slices, fpart,
+                               n_part, 0.0, conv);
+        };
+        auto polish = [&]() {   // V <- (3 I - V V^T) V / 2, and G with it
+            float* const O = reinterpret_cast<float*>(c0);
+            hipLaunchKernelGGL(calib_polar_square_kernel, sym_grid, prod, kSymLds, st, cur + D, D, 2 * D, O);
+            hipLaunchKernelGGL(calib_float_apply_kernel, dim3(2 * D / 64, D / 64), prod, (prod_lds<float, float, true>()), st, O, cur, D, 2 * D, -0.5f, 1.5f,
+                               nxt, 2 * D);
+            std::swap(cur, nxt);
+        };
+        hipLaunchKernelGGL(calib_float_rows_kernel, dim3(D), dim3(kCalThreads), 0, st, rows, D, std::ldexp(1.0, -expo), cur);
+        double before = 1e300;
+        bool polished = false, enough = false;
+        for (;;) {
+            hipLaunchKernelGGL((calib_jacobi_inside_gram_kernel<float>), dim3(n_blocks, n_part), dim3(256), 0, st, cur, 2 * D, D / n_part, fpart);
+            hipLaunchKernelGGL((calib_jacobi_inside_kernel<float>), dim3(n_blocks, slices), dim3(kJacInsideThreads), 0, st, cur, 2 * D, 2 * D / slices, fpart, n_part,
+                               0.0, conv);
+            near_step(kJacNearEven);
+            near_step(kJacNearOdd);
+            if (enough) break;
+            hipLaunchKernelGGL(calib_float_norm_kernel, dim3(D / 4), dim3(256), 0, st, cur, D, norm);
+            hipLaunchKernelGGL(calib_sort_kernel, dim3(D), dim3(kCalThreads), 0, st, reinterpret_cast<const double*>(cur), norm, D,
+                               reinterpret_cast<double*>(nxt), sorted);
+            std::swap(cur, nxt);
+            uint32_t *const A = reinterpret_cast<uint32_t*>(nxt), *const E = A + (size_t)D * D;
+            hipLaunchKernelGGL((calib_gram_kernel<float>), sym_grid, prod, kSymLds, st, cur, D, 2 * D, sorted, r, reinterpret_cast<float*>(A), row_off);
+            hipLaunchKernelGGL(calib_all_angles_kernel, dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D, sorted, r,
+                               row_off, kFloatOpen, E, all_found);
+            hipLaunchKernelGGL((calib_polar_kernel<0, true, false>), tile_grid, prod, kPairLds, st, E, E, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr, A, square);
+            const bool first = before == 1e300;
+            if (launch_status() != SALS_OK ||
+                hipMemcpyAsync(h_found, all_found, (size_t)(n_angles + n_tiles) * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
+                (first && hipMemcpyAsync(h_norm, sorted, (size_t)D * 8, hipMemcpyDeviceToHost, st) != hipSuccess) ||
+                hipStreamSynchronize(st) != hipSuccess)
+                return SALS_ERR_HIP;
+            double e2 = 0.0, a2 = 0.0;
+            for (int i = 0; i < n_angles; ++i) e2 += h_found[i];
+            for (int i = 0; i < n_tiles; ++i) a2 += h_found[n_angles + i];
+            const double now = std::sqrt(e2);
+            const PolarPlan P = polar_plan(a2, now <= kFloatLast ? kPolarNear : kFloatPolar);
+            if (!std::isfinite(now) || P.n == 0 || (first && (now <= kFloatFirst || h_norm[D - 1] > kFloatSpread * h_norm[0]))) return SALS_OK;
+            const float* const X = polar_factor(P, E, A, A, c0, c1, false);
+            hipLaunchKernelGGL(calib_float_apply_kernel, dim3(2 * D / 64, D / 64), prod, (prod_lds<float, float, true>()), st, X, cur, D, 2 * D, 1.f, 0.f, nxt,
+                               2 * D);
+            std::swap(cur, nxt);
+            const bool stuck = !(now < (now < 10.0 ? 0.6 : 0.9) * before);   // (few large angles are halved and more)
+            enough = stuck || (now <= kFloatLast && polished);
+            if ((now <= kFloatPolish || stuck) && !polished) { polish(); polished = true; }
+            before = now;
+        }
+        float* const O = reinterpret_cast<float*>(c0);
+        hipLaunchKernelGGL(calib_polar_square_kernel, sym_grid, prod, kSymLds, st, cur + D, D, 2 * D, O);
+        hipLaunchKernelGGL(calib_float_apply_kernel, tile_grid, prod, (prod_lds<float, float, true>()), st, O, cur + D, D, 2 * D, -0.5f, 1.5f, nxt, D);
+        // V, made orthogonal in fp64, times the factor
+        correct_and_apply(nxt, reinterpret_cast<uint32_t*>(nxt) + (size_t)D * D, rows, reinterpret_cast<double*>(cur), rows);
+        if (launch_status() != SALS_OK) return SALS_ERR_HIP;
+        *ok = true;
+        return SALS_OK;
+    };
+    bool settled = false, fresh = false;
+    if (all && D <= kFloatMaxD && !converged) {
+        const sals_status s = float_rows(&fresh);
+        if (s != SALS_OK) return s;
+    }
+    if (fresh) {   // (it takes the place of a sweep, and counts as one)
+        rotated = true;
+        done = 1;
+        if (!row_norms(rows)) return SALS_ERR_HIP;
+        lead = leading();
+    }
     bool moved = false;    // `lead` is from before a transformation
     double last = 1e300;   // |E| of the transformation before, infinite behind a sweep
     // (The limit is one of sweeps, so that one which is enough without transformations is enough with them.  Between two sweeps |E|
     // falls by a tenth at least with each, from at most D to kSeriesNorm.)
     while (done < max_sweeps && !converged) {
         double worst = 0.0;   // largest rotation that is known to have been left behind
-        if (all && !settled && done >= all_first(D) && last > 0.0) {
+        if (fresh) {   // behind the floats: their rest is mostly for the series
+            worst = 0.1;
+            fresh = false;
+        } else if (all && !settled && done >= all_first(D) && last > 0.0) {
             // One transformation of all rows.
             moved = true;
             inside_step();
@@ -2183,12 +2319,12 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             hipLaunchKernelGGL(calib_sort_kernel, dim3(D), dim3(kCalThreads), 0, st, rows, norm, D, other, sorted);
             std::swap(rows, other);
             uint32_t *const E = reinterpret_cast<uint32_t*>(third), *const A = E + (size_t)D * D;
-            hipLaunchKernelGGL(calib_gram_kernel, sym_grid, prod, kSymLds, st, rows, D, sorted, r,
+            hipLaunchKernelGGL((calib_gram_kernel<double>), sym_grid, prod, kSymLds, st, rows, D, D, sorted, r,
                                reinterpret_cast<float*>(A), row_off);
             hipLaunchKernelGGL(calib_all_angles_kernel, dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D, sorted, r, row_off,
-                               E, all_found);
+                               kAllOpen, E, all_found);
             hipLaunchKernelGGL((calib_polar_kernel<0, true, false>), tile_grid, prod, kPairLds, st, E, E, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr,
-                               A, nullptr, square);
+                               A, square);
             if (launch_status() != SALS_OK ||
                 hipMemcpyAsync(h_found, all_found, (size_t)(n_angles + n_tiles) * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
                 hipStreamSynchronize(st) != hipSuccess)
@@ -2212,41 +2348,8 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                 continue;
             } else {
                 last = now < 0.9 * last ? now : 0.0;
-                const double w = 0.5 * P.a[0] * P.a[0] * P.a[0] / (P.top * P.top * P.top), c1 = 1.5 * P.a[0] / P.top - w;
-                // X and its transpose XT.  The defect of (X X^T) X is quadratic in that of X; X (X X^T) is the same only as long as X
-                // commutes with its transpose, and what rounding takes from that would stay.
-                uint32_t *X = reinterpret_cast<uint32_t*>(other), *X2 = X + (size_t)D * D, *const Y = E;
-                uint32_t *XT = reinterpret_cast<uint32_t*>(C), *XT2 = XT + (size_t)D * D;
-                auto polar = [&](auto n, bool fp32, const uint32_t* L, const uint32_t* R, double f, double d, double s, const uint32_t* S, double t,
-                                 const uint32_t* T, uint32_t* O, uint32_t* OT) {
-                    constexpr int N = decltype(n)::value;
-                    if (fp32) hipLaunchKernelGGL((calib_polar_kernel<N, false, true>), tile_grid, prod, kPairLds, st, L, R, D, (float)f, (float)d,
-                                                 (float)s, S, (float)t, T, O, OT, nullptr);
-                    else hipLaunchKernelGGL((calib_polar_kernel<N, false, false>), tile_grid, prod, kPairLds, st, L, R, D, (float)f, (float)d,
-                                            (float)s, S, (float)t, T, O, OT, nullptr);
-                };
-                polar(std::integral_constant<int, 2>{}, P.n == 1, A, E, w * P.tau * P.tau * P.tau, c1, c1 * P.tau, E, -w * P.tau * P.tau, A, X, XT);
-                for (int k = 1; k < P.n; ++k) {
-                    const double a = P.a[k];
-                    polar(std::integral_constant<int, 0>{}, false, X, X, 1.0, 0.0, 0.0, nullptr, 0.0, nullptr, Y, nullptr);
-                    polar(std::integral_constant<int, 1>{}, k == P.n - 1, Y, XT, -0.5 * a * a * a, 0.0, 1.5 * a, X, 0.0, nullptr, X2, XT2);
-                    std::swap(X, X2);
-                    std::swap(XT, XT2);
-                }
-                if (P.one_more) {
-                    float *const x = reinterpret_cast<float*>(X), *const x2 = reinterpret_cast<float*>(X2), *const y = reinterpret_cast<float*>(Y);
-                    hipLaunchKernelGGL(calib_polar_square_kernel, sym_grid, prod, kSymLds, st, x, D, y);
-                    hipLaunchKernelGGL(calib_polar_last_kernel, tile_grid, prod, (prod_lds<float, float, false>()), st, y,
-                                       reinterpret_cast<const float*>(XT), D, -0.5f, 1.5f, x, x2);
-                    std::swap(X, X2);
-                }
-                hipLaunchKernelGGL(calib_defect_kernel, sym_grid, prod, kSymLds, st, reinterpret_cast<const float*>(X), D,
-                                   C, X2);
-                hipLaunchKernelGGL(calib_correction_kernel, tile_grid, prod, kPairLds, st, X2, D, C);
-                hipLaunchKernelGGL((calib_apply_kernel<float, false>), tile_grid, prod, (prod_lds<float, double, true>()), st,
-                                   reinterpret_cast<const float*>(X), rows, nullptr, 1.0, third, D);
-                hipLaunchKernelGGL((calib_apply_kernel<double, true>), tile_grid, prod, (prod_lds<double, double, true>()), st, C, third, third,
-                                   1.0, other, D);
+                const float* const X = polar_factor(P, E, A, E, reinterpret_cast<uint32_t*>(other), reinterpret_cast<uint32_t*>(other) + (size_t)D * D, true);
+                correct_and_apply(X, reinterpret_cast<uint32_t*>(other) + (X == reinterpret_cast<float*>(other) ? (size_t)D * D : 0), rows, third, other);
                 std::swap(rows, other);
                 if (launch_status() != SALS_OK) return SALS_ERR_HIP;
                 continue;

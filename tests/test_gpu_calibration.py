@@ -197,6 +197,34 @@ def test_transformations_of_all_rows_at_once(D, r, kind):
     assert np.max(np.linalg.norm(V @ C - norm[lead, None] * V, axis=1)) <= (2e-11 + eps) * norm[lead[0]]
 
 
+@pytest.mark.parametrize("D,r,kind", [(256, 256, "wide"), (512, 300, "geometric"), (768, 768, "close"), (256, 64, "half zero"),
+                                      (1024, 640, "steps"), (2560, 64, "wide")])
+def test_the_way_in_floats_leaves_no_trace(D, r, kind):
+    """Spectra whose rows go most of the way in floats, or are left to doubles (eigenvalues within 1e-3), or come out of it with
+    angles that floats do not tell apart (eigenvalues in steps): the eigenvalues, and the rows left behind, are those of fp64."""
+    print(f"[case] floats on the way, D={D} r={r} {kind}", flush=True)
+    rng = np.random.default_rng(D)
+    lam = {"wide": np.linspace(2.0, 0.01, D), "geometric": 10.0 ** (-6.0 * np.arange(D) / D), "close": 1.0 + 1e-3 * np.arange(D)[::-1] / D,
+           "half zero": np.where(np.arange(D) < D // 2, 1.0 / (1.0 + np.arange(D)), 0.0), "steps": np.repeat(2.0 ** -np.arange(D // 64), 64)}[kind]
+    Q = torch.linalg.qr(torch.from_numpy(rng.standard_normal((D, D))).to(gu.DEV))[0]
+    C = (Q * gu.to_dev(lam)) @ Q.T.contiguous()
+    C = (0.5 * (C + C.T)).contiguous()
+    rows = C.clone()
+    got, U, sweeps = binding.calib_eigenvectors(rows, r, torch.float32)
+    torch.cuda.synchronize()
+    assert 0 < sweeps <= 20
+    # (the matrix is that of `lam` to the rounding of its products; what the call adds is bounded as for transformations in general)
+    eps = 4 * 60 * np.sqrt(D) * 2.0 ** -53
+    np.testing.assert_allclose(got.cpu().numpy()[:r], lam[:r], rtol=0, atol=eps * lam[0])
+    norm = rows.norm(dim=1)
+    lead = torch.argsort(-norm)[:r]
+    V = rows[lead] / norm[lead, None]
+    keep = got[:r] > 1e-10 * lam[0]        # (eigenvectors of zero are some basis)
+    V, L = V[keep], norm[lead][keep]
+    assert float((V @ V.T.contiguous() - torch.eye(len(L), device=gu.DEV, dtype=torch.float64)).abs().max()) <= 2e-11
+    assert float((V @ C - L[:, None] * V).norm(dim=1).max()) <= (2e-11 + eps) * lam[0]
+
+
 @pytest.mark.parametrize("large,width,n_large,r", [(1e5, 1e-11, 2, 3), (1e5, 1e-11, 4, 8), (10.0, 1e-10, 4, 8), (1e3, 1e-10, 4, 12)])
 def test_rows_of_a_tight_cluster_are_asked_to_have_converged(large, width, n_large, r):
     """A few large eigenvalues and all others within a relative `width`, the r-th among these: its row's norm falls far while the large
