@@ -403,7 +403,7 @@ sals_status sals_overlap_score(sals_ctx* ctx, const void* q, const int32_t* q_po
  *   workspace  device, 256-byte aligned, sals_calib_eigenvectors_workspace_bytes(D) bytes (the factor and two partial
  *              sums of a series, 8 D^2 bytes each, and some D of scratch).  Fewer are taken from 8 D^2 + 900 D on
  *              (SALS_ERR_WORKSPACE below what the sweeps need): all rotations are then made by sweeps, whose
- *              sums are spread over as much of the device as the scratch allows (D = 1024: 3.5 ms with the full size,
+ *              sums are spread over as much of the device as the scratch allows (D = 1024: 3.2 ms with the full size,
  *              10.2 with 8 D^2 + 4000 D bytes, 15.4 with the least)
  *   max_sweeps at least 1 (host): a sweep rotates every pair of rows once (transformations of all rows, which come
  *              between sweeps, are not counted; where they take the place of the first sweep they count as one); the call stops when no rotation that involves one of the r largest

@@ -329,6 +329,7 @@ __device__ __forceinline__ void calib_pair(int n, int s, int k, int* p, int* q)
 // norms sqrt(C_jj + shift); one that meets another pivot (C is indefinite by more than the shift, as the covariance of fewer
 // tokens than channels is by its fp32 sums) sets `fail` and the host starts again with 64 times the shift.
 constexpr int kCalPanel = 64;
+constexpr double kCalShift = 1e-14;
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 // v_mfma_f64_16x16x4: lane holds A[l % 16][l / 16] and B[l / 16][l % 16]; result element i is row l / 16 + 4 i, column l % 16
@@ -354,9 +355,11 @@ __device__ __forceinline__ double rsqrt_f64(double x)
 // steps per column took 62.
 // The factored block goes to `diag` (other workgroups still read the original).  grid max(1, (D - k0 - 64) / 64).
 constexpr int kCholLd = 2 * kCalPanel + 2;   // row pitch: the diagonal block's columns, then the workgroup's 64 columns
-__global__ __launch_bounds__(256) void calib_chol_panel_kernel(double* __restrict__ G, int D, int k0, double shift,
+// The shift is `f` times 1e-14 of `scale` (see calib_scale_kernel).
+__global__ __launch_bounds__(256) void calib_chol_panel_kernel(double* __restrict__ G, int D, int k0, const double* __restrict__ scale, double f,
                                                                double* __restrict__ diag, int* __restrict__ fail)
 {
+    const double shift = kCalShift * *scale * f;
     __shared__ double M[kCalPanel * kCholLd];
     __shared__ double invd[kCalPanel];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, kg = lane >> 4;
@@ -794,9 +797,10 @@ constexpr int kJacInsideThreads = 4 * kWave;
 template <typename T>
 __global__ __launch_bounds__(kJacInsideThreads) void calib_jacobi_inside_kernel(T* __restrict__ G, int pitch, int slice_cols,
                                                                                 const T* __restrict__ part, int n_part,
-                                                                                double lead, double* __restrict__ conv)
+                                                                                const double* __restrict__ lead_at, double* __restrict__ conv)
 {
     constexpr bool kConv = sizeof(T) == 8;   // (in floats nobody asks whether the rows have converged)
+    const double lead = kConv ? *lead_at : 0.0;
     typedef typename mma_tile<T>::acc V4;
     constexpr int B2 = 2 * kJacB, LD = kJacLd;
     __shared__ T Wb[2][B2 * LD], Qb[2][B2 * LD];   // Gram matrix and accumulated rotations
@@ -919,10 +923,11 @@ __global__ __launch_bounds__(kJacInsideThreads) void calib_jacobi_inside_kernel(
 constexpr int kJacThreads = 8 * kWave;   // waves 0, 1 and 2, 3: the groups' rounds; 4, 5 and 6, 7: their accumulated rotations
 template <typename T>
 __global__ __launch_bounds__(kJacThreads) void calib_jacobi_rotate_kernel(T* __restrict__ G, int D, int pitch, int step, int slice_cols,
-                                                                          const T* __restrict__ part, int n_part, double lead,
-                                                                          double* __restrict__ conv)
+                                                                          const T* __restrict__ part, int n_part,
+                                                                          const double* __restrict__ lead_at, double* __restrict__ conv)
 {
     constexpr int LD = kJacLd, LT = kJacLt;
+    const double lead = sizeof(T) == 8 ? *lead_at : 0.0;
     typedef typename mma_tile<T>::acc V4;
     typedef typename vec2<T>::type V2;
     __shared__ T S[kJacTiles][kJacB * LT];          // Gram matrix
@@ -1124,6 +1129,33 @@ __device__ __forceinline__ int calib_rank(const double* __restrict__ norm, int D
 #pragma unroll
     for (int w = 0; w < kCalThreads / kWave; ++w) rank += cnt[w];
     return rank;
+}
+
+// A little less than the square of the r-th largest norm (so that the r-th row itself is among the leading ones), a workgroup a row.  (5
+// us at D = 1024; the host would have to wait for the norms, 22 us, and select among them, 10.)
+__global__ __launch_bounds__(kCalThreads) void calib_lead_kernel(const double* __restrict__ norm, int D, int r, double* __restrict__ lead)
+{
+    __shared__ int cnt[kCalThreads / kWave];
+    const int rank = calib_rank(norm, D, blockIdx.x, cnt);
+    if (threadIdx.x == 0 && rank == r - 1) *lead = 0.999 * norm[blockIdx.x] * norm[blockIdx.x];
+}
+// the largest norm, between the largest diagonal entry and the largest eigenvalue of a covariance (not a number if one of them is not)
+__global__ __launch_bounds__(kCalThreads) void calib_scale_kernel(const double* __restrict__ norm, int D, double* __restrict__ scale)
+{
+    __shared__ double s_most[kCalThreads / kWave];
+    const int tid = threadIdx.x;
+    auto larger = [](double a, double b) { return a != a || a > b ? a : b; };
+    double most = 0.0;
+    for (int i = tid; i < D; i += kCalThreads) most = larger(norm[i], most);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) most = larger(__shfl_xor(most, o, kWave), most);
+    if ((tid & 63) == 0) s_most[tid >> 6] = most;
+    __syncthreads();
+    if (tid == 0) {
+#pragma unroll
+        for (int w = 1; w < kCalThreads / kWave; ++w) most = larger(s_most[w], most);
+        *scale = most;
+    }
 }
 
 // Row i of G takes rank = number of rows with a larger norm (equal ones by row index); eigval[rank] = lambda_i and, for

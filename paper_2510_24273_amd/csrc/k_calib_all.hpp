@@ -365,8 +365,10 @@ __global__ __launch_bounds__(kProdThreads) void calib_apply_kernel(const TA* A, 
 // squared norm >= lead; where both have, their cosine counts as well as t (beside a far larger row, t is small long before the smaller
 // row's direction is right).  found: per tile {largest |t| (at most 1/2), sum of t^2}.
 __global__ __launch_bounds__(kProdThreads) void calib_angles_kernel(const double* __restrict__ G, int D, const double* __restrict__ norm,
-                                                                    double lead, double* __restrict__ E, f64x2* __restrict__ found)
+                                                                    const double* __restrict__ lead_at, double* __restrict__ E,
+                                                                    f64x2* __restrict__ found)
 {
+    const double lead = *lead_at;
     __shared__ f64x2 s_found[8];
     double most = 0.0, sum = 0.0;
     const SymTile tile = sym_tile(blockIdx.x, D);

@@ -2003,6 +2003,42 @@ int jac_slices(int D)
     while (D % (32 * s) == 0 && D / (2 * s) >= 64 && D / (2 * kJacBig) * (2 * s) <= 256) s *= 2;
     return s;
 }
+// Pinned host memory for what a call reads back (a wait for the device and 8 KB from it take 11 us, into other memory 22), for one call at
+// a time.  Making and freeing it takes 25 us and waits for every stream of the process, so up to four blocks are kept from call to call.
+struct PinnedLease {
+    double* p = nullptr;
+    bool idle = false;   // no copy into it is under way
+    explicit PinnedLease(size_t n_) : n(n_)
+    {
+        {
+            const std::lock_guard<std::mutex> hold(lock());
+            for (Block& b : kept())
+                if (b.p && b.n >= n) { p = b.p; n = b.n; b.p = nullptr; return; }
+        }
+        void* q = nullptr;
+        if (hipHostMalloc(&q, n * 8, hipHostMallocPortable) == hipSuccess) p = static_cast<double*>(q);
+        else (void)hipGetLastError();
+    }
+    ~PinnedLease()
+    {
+        if (!p) return;
+        if (idle) {
+            const std::lock_guard<std::mutex> hold(lock());
+            for (Block& b : kept())
+                if (!b.p) { b = Block{p, n}; return; }
+        }
+        (void)hipHostFree(p);
+    }
+    PinnedLease(const PinnedLease&) = delete;
+    PinnedLease& operator=(const PinnedLease&) = delete;
+
+private:
+    struct Block { double* p; size_t n; };
+    typedef Block Blocks[4];
+    static std::mutex& lock() { static std::mutex m; return m; }
+    static Blocks& kept() { static Blocks b = {}; return b; }
+    size_t n;
+};
 struct EigWs {  // byte offsets into the workspace
     size_t G, conv, norm, sgn, diag, part, Y0, Y1, total;
 };
@@ -2125,51 +2161,54 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     double *rows = G, *other = at(off.Y0), *third = at(off.Y1);   // the rows, and room for two more matrices (`series`)
     double* const sorted = diag;                                  // (the factored blocks are in place by then)
     const bool all = series && D <= kAllMaxD;
-    const std::unique_ptr<double[]> host(new (std::nothrow) double[(size_t)n_blocks + D + std::max(2 * n_tiles, n_angles + n_tiles)]);
-    if (!host) return SALS_ERR_HIP;
-    if (calib_all_lds(series) != SALS_OK) return SALS_ERR_HIP;  // (behind the memory: the runtime has no error for a lack of it)
-    double *const h_conv = host.get(), *const h_norm = h_conv + n_blocks, *const h_found = h_norm + D;
-    auto row_norms = [&](const double* M) -> bool {  // row norms to the host (blocking)
-        hipLaunchKernelGGL(calib_rownorm_kernel, dim3(D), dim3(kCalThreads), 0, st, M, D, norm, sgn);
-        return hipMemcpyAsync(h_norm, norm, (size_t)D * 8, hipMemcpyDeviceToHost, st) == hipSuccess &&
-               hipStreamSynchronize(st) == hipSuccess;
+    double *const scale = sgn, *const lead = diag + D;   // (behind the sorted norms; the signs are wanted at the very end only)
+    auto row_norms = [&](const double* M) { hipLaunchKernelGGL(calib_rownorm_kernel, dim3(D), dim3(kCalThreads), 0, st, M, D, norm, sgn); };
+    auto find_lead = [&](const double* M) {   // the squared norm of rows that count
+        row_norms(M);
+        hipLaunchKernelGGL(calib_lead_kernel, dim3(D), dim3(kCalThreads), 0, st, norm, D, r, lead);
     };
-    if (!row_norms(C)) return SALS_ERR_HIP;
-    const double n0 = *std::max_element(h_norm, h_norm + D);  // (between the largest diagonal entry and lambda_0)
-    double lead = 0.0;  // first sweep: every rotation counts
+    auto factor = [&](double f) -> bool {
+        if (hipMemcpyAsync(G, C, (size_t)D * D * 8, hipMemcpyDeviceToDevice, st) != hipSuccess ||
+            hipMemsetAsync(fail, 0, sizeof(int), st) != hipSuccess)
+            return false;
+        for (int k0 = 0; k0 < D; k0 += kCalPanel) {
+            const int rest = D - k0 - kCalPanel;
+            hipLaunchKernelGGL(calib_chol_panel_kernel, dim3(std::max(1, rest / 64)), dim3(256), 0, st, G, D, k0, scale, f, diag, fail);
+            if (rest > 0) hipLaunchKernelGGL(calib_chol_update_kernel, dim3(rest / 64, rest / 64), dim3(512), 0, st, G, D, k0);
+        }
+        hipLaunchKernelGGL(calib_chol_finish_kernel, dim3(D), dim3(256), 0, st, G, D, diag);
+        return launch_status() == SALS_OK;
+    };
+    // G = Cholesky factor of C + shift I, the shift from C's scale, which the host learns with what came of it.
+    row_norms(C);
+    hipLaunchKernelGGL(calib_scale_kernel, dim3(1), dim3(kCalThreads), 0, st, norm, D, scale);
+    const bool begun = factor(1.0);
+    PinnedLease host((size_t)n_blocks + D + std::max(2 * n_tiles, n_angles + n_tiles));
+    if (!host.p) return SALS_ERR_HIP;
+    if (!begun || calib_all_lds(series) != SALS_OK) return SALS_ERR_HIP;
+    double *const h_conv = host.p, *const h_norm = h_conv + n_blocks, *const h_found = h_norm + D;
+    auto read = [&](void* to, const void* from, size_t bytes) { return hipMemcpyAsync(to, from, bytes, hipMemcpyDeviceToHost, st) == hipSuccess; };
+    auto wait = [&]() { return launch_status() == SALS_OK && hipStreamSynchronize(st) == hipSuccess; };
+    if (!read(h_norm, scale, 8) || !read(h_conv, fail, sizeof(int)) || !wait()) return SALS_ERR_HIP;
+    const double n0 = h_norm[0];  // (between the largest diagonal entry and lambda_0)
     int done = 0;
     bool converged = !(n0 > 0.0) || !std::isfinite(n0);  // the zero matrix needs no rotation
     bool rotated = false;
-    // G = Cholesky factor of C + shift I.  No eigenvalue lies below -sqrt(D) n0 (sqrt(D) is at most 90.5), so ten shifts, up to
-    // 180 n0, end with a positive definite matrix unless C is not one of numbers (then its rows are returned as they are).
     double shift = 0.0;
+    // No eigenvalue lies below -sqrt(D) n0 (sqrt(D) is at most 90.5), so ten shifts, up to 180 n0, end with a positive definite matrix
+    // unless C is not one of numbers (then its rows are returned as they are).
     if (!converged) {
-        int failed = 1;
-        for (int t = 0; t < 10 && failed; ++t) {
-            shift = t == 0 ? 1e-14 * n0 : 64.0 * shift;
-            if (hipMemcpyAsync(G, C, (size_t)D * D * 8, hipMemcpyDeviceToDevice, st) != hipSuccess ||
-                hipMemsetAsync(fail, 0, sizeof(int), st) != hipSuccess)
-                return SALS_ERR_HIP;
-            for (int k0 = 0; k0 < D; k0 += kCalPanel) {
-                const int rest = D - k0 - kCalPanel;
-                hipLaunchKernelGGL(calib_chol_panel_kernel, dim3(std::max(1, rest / 64)), dim3(256), 0, st, G, D, k0, shift,
-                                   diag, fail);
-                if (rest > 0)
-                    hipLaunchKernelGGL(calib_chol_update_kernel, dim3(rest / 64, rest / 64), dim3(512), 0, st, G, D, k0);
-            }
-            hipLaunchKernelGGL(calib_chol_finish_kernel, dim3(D), dim3(256), 0, st, G, D, diag);
-            if (launch_status() != SALS_OK || hipMemcpyAsync(&failed, fail, sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess ||
-                hipStreamSynchronize(st) != hipSuccess)
-                return SALS_ERR_HIP;
+        int failed = *reinterpret_cast<int*>(h_conv);
+        double f = 1.0;
+        for (int t = 1; t < 10 && failed; ++t) {
+            f *= 64.0;
+            if (!factor(f) || !read(h_conv, fail, sizeof(int)) || !wait()) return SALS_ERR_HIP;
+            failed = *reinterpret_cast<int*>(h_conv);
         }
+        shift = kCalShift * n0 * f;
         converged = failed != 0;
     }
-    // r-th largest squared norm, a little less (so that the r-th row itself is among the leading ones)
-    auto leading = [&]() {
-        std::nth_element(h_norm, h_norm + (r - 1), h_norm + D, std::greater<double>());
-        const double nr = h_norm[r - 1];
-        return 0.999 * nr * nr;
-    };
+    if (hipMemsetAsync(lead, 0, 8, st) != hipSuccess) return SALS_ERR_HIP;   // first sweep: every rotation counts
     auto block_step = [&](int step) {  // rotates the pairs of blocks of a step of a sweep, or neighbours
         hipLaunchKernelGGL((calib_jacobi_gram_kernel<double>), dim3(n_pairs, n_part, 2), dim3(256), 0, st, rows, D, D, step, D / n_part, part);
         hipLaunchKernelGGL((calib_jacobi_rotate_kernel<double>), dim3(n_pairs, slices), dim3(kJacThreads), 0, st, rows, D, D, step, D / slices,
@@ -2231,7 +2270,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         auto near_step = [&](int step) {
             hipLaunchKernelGGL((calib_jacobi_gram_kernel<float>), dim3(n_pairs, n_part, 2), dim3(256), 0, st, cur, D, 2 * D, step, D / n_part, fpart);
             hipLaunchKernelGGL((calib_jacobi_rotate_kernel<float>), dim3(n_pairs, slices), dim3(kJacThreads), 0, st, cur, D, 2 * D, step, 2 * D / slices, fpart,
-                               n_part, 0.0, conv);
+                               n_part, lead, conv);
         };
         auto polish = [&]() {   // V <- (3 I - V V^T) V / 2, and G with it
             float* const O = reinterpret_cast<float*>(c0);
@@ -2246,7 +2285,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         for (;;) {
             hipLaunchKernelGGL((calib_jacobi_inside_gram_kernel<float>), dim3(n_blocks, n_part), dim3(256), 0, st, cur, 2 * D, D / n_part, fpart);
             hipLaunchKernelGGL((calib_jacobi_inside_kernel<float>), dim3(n_blocks, slices), dim3(kJacInsideThreads), 0, st, cur, 2 * D, 2 * D / slices, fpart, n_part,
-                               0.0, conv);
+                               lead, conv);
             near_step(kJacNearEven);
             near_step(kJacNearOdd);
             if (enough) break;
@@ -2260,10 +2299,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                                row_off, kFloatOpen, E, all_found);
             hipLaunchKernelGGL((calib_polar_kernel<0, true, false>), tile_grid, prod, kPairLds, st, E, E, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr, A, square);
             const bool first = before == 1e300;
-            if (launch_status() != SALS_OK ||
-                hipMemcpyAsync(h_found, all_found, (size_t)(n_angles + n_tiles) * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
-                (first && hipMemcpyAsync(h_norm, sorted, (size_t)D * 8, hipMemcpyDeviceToHost, st) != hipSuccess) ||
-                hipStreamSynchronize(st) != hipSuccess)
+            if (!read(h_found, all_found, (size_t)(n_angles + n_tiles) * 8) || (first && !read(h_norm, sorted, (size_t)D * 8)) || !wait())
                 return SALS_ERR_HIP;
             double e2 = 0.0, a2 = 0.0;
             for (int i = 0; i < n_angles; ++i) e2 += h_found[i];
@@ -2297,8 +2333,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     if (fresh) {   // (it takes the place of a sweep, and counts as one)
         rotated = true;
         done = 1;
-        if (!row_norms(rows)) return SALS_ERR_HIP;
-        lead = leading();
+        find_lead(rows);
     }
     bool moved = false;    // `lead` is from before a transformation
     double last = 1e300;   // |E| of the transformation before, infinite behind a sweep
@@ -2325,10 +2360,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                                kAllOpen, E, all_found);
             hipLaunchKernelGGL((calib_polar_kernel<0, true, false>), tile_grid, prod, kPairLds, st, E, E, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr,
                                A, square);
-            if (launch_status() != SALS_OK ||
-                hipMemcpyAsync(h_found, all_found, (size_t)(n_angles + n_tiles) * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
-                hipStreamSynchronize(st) != hipSuccess)
-                return SALS_ERR_HIP;
+            if (!read(h_found, all_found, (size_t)(n_angles + n_tiles) * 8) || !wait()) return SALS_ERR_HIP;
             double e2 = 0.0, a2 = 0.0;
             for (int i = 0; i < n_angles; ++i) e2 += h_found[i];
             for (int i = 0; i < n_tiles; ++i) a2 += h_found[n_angles + i];
@@ -2340,8 +2372,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                 worst = now;
                 last = 0.0;   // (what the series leaves is for sweeps)
                 settled = true;
-                if (!row_norms(rows)) return SALS_ERR_HIP;
-                lead = leading();
+                find_lead(rows);
                 moved = false;
             } else if (!std::isfinite(now) || P.n == 0) {
                 last = 0.0;   // (sums that are no numbers: a sweep)
@@ -2356,16 +2387,15 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             }
         } else {
             if (moved) {   // (the r-th norm may have fallen far: rows below the old one would not be asked to have converged)
-                if (!row_norms(rows)) return SALS_ERR_HIP;
-                lead = leading();
+                find_lead(rows);
                 moved = false;
             }
             if (hipMemsetAsync(conv, 0, (size_t)n_blocks * 8, st) != hipSuccess) return SALS_ERR_HIP;
             inside_step();
             for (int step = 0; step < n_steps; ++step) block_step(step);
-            if (launch_status() != SALS_OK) return SALS_ERR_HIP;
-            if (hipMemcpyAsync(h_conv, conv, (size_t)n_blocks * 8, hipMemcpyDeviceToHost, st) != hipSuccess) return SALS_ERR_HIP;
-            if (!row_norms(rows)) return SALS_ERR_HIP;
+            if (!read(h_conv, conv, (size_t)n_blocks * 8)) return SALS_ERR_HIP;
+            find_lead(rows);
+            if (!wait()) return SALS_ERR_HIP;
             for (int i = 0; i < n_blocks; ++i) worst = std::max(worst, h_conv[i]);
             rotated = rotated || worst > 0.0;  // (in the first sweep every rotation is recorded)
             ++done;
@@ -2373,17 +2403,13 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             // a rotation by less than 1e-11 no longer moves an eigenvector; only pairs with a row among the r largest are asked to
             // have converged
             converged = worst <= 1e-11;
-            lead = leading();
         }
         // Behind a sweep of small rotations the angles that are left decide: converged, or all of them at once, or a further sweep.
         // (Sweeps whose largest rotation was 0.26, 0.07, 0.007 left 4e-5, 1e-3, 4e-6.)  The angles lie in C, which is free until its
         // rows are written.
         for (int pass = 0; !converged && worst <= 0.3 && pass < 6; ++pass) {
             hipLaunchKernelGGL(calib_angles_kernel, sym_grid, prod, kSymLds, st, rows, D, norm, lead, C, found);
-            if (launch_status() != SALS_OK ||
-                hipMemcpyAsync(h_found, found, (size_t)n_tiles * sizeof(f64x2), hipMemcpyDeviceToHost, st) != hipSuccess ||
-                hipStreamSynchronize(st) != hipSuccess)
-                return SALS_ERR_HIP;
+            if (!read(h_found, found, (size_t)n_tiles * sizeof(f64x2)) || !wait()) return SALS_ERR_HIP;
             double most = 0.0, square_sum = 0.0;
             for (int i = 0; i < n_tiles; ++i) { most = std::max(most, h_found[2 * i]); square_sum += h_found[2 * i + 1]; }
             converged = most <= 1e-11;
@@ -2399,13 +2425,12 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                 X = Y;
             }
             if (terms == 1) std::swap(rows, other);
-            if (!row_norms(rows)) return SALS_ERR_HIP;
-            lead = leading();
+            find_lead(rows);
         }
     }
     // A matrix whose factor needed no rotation is diagonal (R R^T is diagonal for an upper triangular R only if R is): its
     // own rows are the answer, without the detour through the square roots.
-    if (!rotated && !row_norms(C)) return SALS_ERR_HIP;
+    if (!rotated) row_norms(C);
 #define SALS_SELECT(T, ROOT, M)                                                                                              \
     hipLaunchKernelGGL((calib_select_kernel<T, ROOT>), dim3(D), dim3(kCalThreads), 0, st, M, norm, sgn, D, r, shift, eigval, \
                        static_cast<T*>(U), C)
@@ -2413,6 +2438,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     else { if (rotated) SALS_SELECT(float, true, rows); else SALS_SELECT(float, false, C); }
 #undef SALS_SELECT
     if (sweeps) *sweeps = converged ? done : -done;
+    host.idle = true;
     return launch_status();
 }
 
