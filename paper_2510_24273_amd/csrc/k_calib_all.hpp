@@ -244,6 +244,31 @@ __device__ __forceinline__ void calib_product_sym(const TA* A, int D, int pitch,
     }
 }
 
+// Behind the loop of a product of 32 x 32 parts by two halves of the waves: the first half adds up both, finish(u, v, sum).
+template <typename Finish>
+__device__ __forceinline__ void sum_halves(const f32x4 (&acc)[2][2], int ks, int part, unsigned char* lds, Finish finish)
+{
+    const int lane = threadIdx.x & 63;
+    vm_wait<0>();
+    wg_barrier();
+    float* red = reinterpret_cast<float*>(lds) + part * 1024;
+    if (ks) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) red[i * 64 + lane] = acc[i >> 3][(i >> 2) & 1][i & 3];
+    }
+    __syncthreads();
+    if (ks == 0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int u = i >> 1, v = i & 1;
+            f32x4 x;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = acc[u][v][e] + red[(i * 4 + e) * 64 + lane];
+            finish(u, v, x);
+        }
+    }
+}
+
 // Matrices of floats as pairs of bf16, x = hi + lo to 2^-17: one 32-bit word an element, hi in the upper half.
 __device__ __forceinline__ uint32_t pack_pair(float x)
 {
@@ -328,24 +353,67 @@ __device__ __forceinline__ void calib_product_pairs(const uint32_t* A, const uin
                 acc[u][v] = mma(x[u].hi, y[v].hi, acc[u][v]);
             }
     }
-    vm_wait<0>();
-    wg_barrier();
-    float* red = reinterpret_cast<float*>(lds) + part * 1024;
-    if (ks) {
+    sum_halves(acc, ks, part, lds, [&](int u, int v, const f32x4& x) {
+        finish(r0 + (part >> 1) * 32 + u * 16 + 4 * kg, c0 + (part & 1) * 32 + v * 16 + l16, x);
+    });
+}
+
+// The same for A B^T of plain bf16 matrices, summed in fp32.  A step is 128 elements of a row, 64 for either half of the waves.
+constexpr size_t kPlainLds = (size_t)kProdStages * 32768;
+template <typename Finish>
+__device__ __forceinline__ void calib_product_plain(const bf16_t* A, const bf16_t* B, int D, Finish finish)
+{
+    constexpr int STAGE = 32768, ST = kProdStages;   // [A: two 64-element pieces of 64 rows | B]
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kg = lane >> 4;
+    const int part = wave & 3, ks = wave >> 2;
+    const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
+    const uint32_t lds0 = lds_offset(lds);
+    auto swz128 = [](int row, int pc) { return row * 128 + ((pc ^ ((row >> 1) & 7)) << 4); };
+    const int prow = wave * 8 + (lane >> 3);
+    const uint32_t off = (uint32_t)prow * (uint32_t)D * 2 + (uint32_t)(((lane & 7) ^ ((prow >> 1) & 7)) << 4);
+    const unsigned char* a = reinterpret_cast<const unsigned char*>(A + (size_t)r0 * D);
+    const unsigned char* b = reinterpret_cast<const unsigned char*>(B + (size_t)c0 * D);
+    const int n = D / 128;   // (at least 2)
+    auto load = [&](int s) {
+        const size_t at = (size_t)min(s, n - 1) * 256;   // (past the end: a step that nothing reads any more)
+        const uint32_t st = lds0 + (uint32_t)(s % ST) * STAGE + wave * 1024;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) red[i * 64 + lane] = acc[i >> 3][(i >> 2) & 1][i & 3];
-    }
-    __syncthreads();
-    if (ks == 0) {
+        for (int i = 0; i < 2; ++i) {
+            load_lds16(a + at + 128 * i, off, st + 8192 * i);
+            load_lds16(b + at + 128 * i, off, st + 16384 + 8192 * i);
+        }
+    };
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int u = i >> 1, v = i & 1;
-            f32x4 x;
+    for (int s = 0; s < ST - 1; ++s) load(s);
+    f32x4 acc[2][2];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] = acc[u][v][e] + red[(i * 4 + e) * 64 + lane];
-            finish(r0 + (part >> 1) * 32 + u * 16 + 4 * kg, c0 + (part & 1) * 32 + v * 16 + l16, x);
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) acc[u][v] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int rr = (part >> 1) * 32 + l16, cc = (part & 1) * 32 + l16;
+    for (int s = 0; s < n; ++s) {
+        vm_wait<(ST - 2) * 4>();   // step s has landed, everywhere; every wave is done with step s - 1
+        wg_barrier();
+        load(s + ST - 1);
+        const unsigned char* st = lds + (s % ST) * STAGE + ks * 8192;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            bf16x8 x[2], y[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                x[u] = *reinterpret_cast<const bf16x8*>(st + swz128(rr + 16 * u, 4 * k + kg));
+                y[u] = *reinterpret_cast<const bf16x8*>(st + 16384 + swz128(cc + 16 * u, 4 * k + kg));
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int v = 0; v < 2; ++v) acc[u][v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[u], y[v], acc[u][v], 0, 0, 0);
         }
     }
+    sum_halves(acc, ks, part, lds, [&](int u, int v, const f32x4& x) {
+        finish(r0 + (part >> 1) * 32 + u * 16 + 4 * kg, c0 + (part & 1) * 32 + v * 16 + l16, x);
+    });
 }
 
 // Y = G + f A B (ADD), or f A B.  Y may be G, not B.
@@ -462,12 +530,13 @@ __global__ __launch_bounds__(kProdThreads) void calib_gram_kernel(const T* __res
         off[(size_t)(tile.col + tile.row) * D + j0 + c] = (s_off[1][0][c] + s_off[1][1][c]) + (s_off[1][2][c] + s_off[1][3][c]);
     }
 }
-// ... then E (pairs of bf16), kAngleRows rows x 256 columns a workgroup, and per workgroup the sum of squares of ab / h over the pairs with
+// ... then E (pairs of bf16, or plain bf16), kAngleRows rows x 256 columns a workgroup, and per workgroup the sum of squares of ab / h over the pairs with
 // a leading row.  (8.9 us at D = 1024; 26.5 with 256 columns
 // after the other in a workgroup.)
 constexpr int kAngleRows = 8;
+template <typename TE>
 __global__ __launch_bounds__(256) void calib_all_angles_kernel(const float* __restrict__ W, int D, const double* __restrict__ norm, int r,
-                                                               const float* __restrict__ off, double open, uint32_t* __restrict__ E,
+                                                               const float* __restrict__ off, double open, TE* __restrict__ E,
                                                                double* __restrict__ found)
 {
     static_assert(kAngleRows == 8 && kCalThreads == 256, "32 lanes a row; D is a multiple of the columns");
@@ -496,7 +565,8 @@ __global__ __launch_bounds__(256) void calib_all_angles_kernel(const float* __re
         const AllPair p = all_pair(ni, nj, ab, least, open);
         const bool counts = p.counts && i != j;
         const double s = counts ? ab * rsqrt_f64(fma(kAllDamp * o, o, p.h2)) : 0.0;
-        E[(size_t)i * D + j] = pack_pair((float)(p.d < 0.0 || (p.d == 0.0 && i > j) ? s : -s));
+        const float e = (float)(p.d < 0.0 || (p.d == 0.0 && i > j) ? s : -s);
+        E[(size_t)i * D + j] = sizeof(TE) == 2 ? (TE)f32_to_bf16(e) : (TE)pack_pair(e);
         if (counts && i < j && fmax(ni, nj) * fmax(ni, nj) >= lead) sum += ab * ab / p.h2;
     }
 #pragma unroll
@@ -507,6 +577,16 @@ __global__ __launch_bounds__(256) void calib_all_angles_kernel(const float* __re
 }
 
 // ---- Polar factor -----------------------------------------------------------------------------------------------------
+// The first four waves' sums of squares, added up for the tile
+__device__ __forceinline__ void tile_square(double sum, double* s_sum, double* square)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, kWave);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane == 0 && wave < 4) s_sum[wave] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) square[blockIdx.y * gridDim.x + blockIdx.x] = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
+}
 // O = d I + s S + t T + f A B^T (S, T: N > 0, N > 1; N == 1: A B) from pairs of bf16, left as such pairs or (LAST) in fp32.  SQUARE: also
 // the sum of squares of every tile of O.
 template <int N, bool SQUARE, bool LAST>
@@ -528,12 +608,47 @@ __global__ __launch_bounds__(kProdThreads) void calib_polar_kernel(const uint32_
         }
     });
     if (!SQUARE) return;
+    tile_square(sum, s_sum, square);
+}
+// The steps of a polar factor that only steers, in plain bf16 up to the last one: O = f A B^T (N == 0, symmetric), that and s S (N == 1), or
+// d I + s E + t A + f A E^T (N == 2, B = S = E, which is skew).  What is symmetric or skew is read and written by rows for columns, four
+// elements a lane; of what is neither, S and OT are the transposes.  Left as plain bf16, in pairs or in fp32.
+//
+// Bound by what a compute unit draws, of which a pair's half is half: 7 us a product at D = 1024 where pairs take 12 to 15, a call 3300 -> 3110 us
+// (D = 2048 18.5 -> 15.4 ms).  Rounding X to 2^-9 turns the rows by 2^-9 of the angles that are taken out, while these are still large, and what it
+// takes from X's singular values is made good by the last step, in pairs: X X^T - I stays within 4e-3.  Not once V is polished: the last angles
+// are told in pairs.
+enum PolarOut { kOutPlain, kOutPairs, kOutFloat };
+template <int N, bool SQUARE, PolarOut OUT>
+__global__ __launch_bounds__(kProdThreads) void calib_polar_plain_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, int D, float f,
+                                                                         float d, float s, const bf16_t* __restrict__ S, float t,
+                                                                         void* __restrict__ O, bf16_t* __restrict__ OT, double* __restrict__ square)
+{
+    struct alignas(8) Four { bf16_t x[4]; };
+    __shared__ double s_sum[4];
+    double sum = 0.0;
+    calib_product_plain(A, B, D, [&](int i0, int j, const f32x4& v) {
+        const size_t tr = (size_t)j * D + i0;
+        Four add{}, sym{}, out;
+        if (N > 0) add = *reinterpret_cast<const Four*>(S + tr);
+        if (N > 1) sym = *reinterpret_cast<const Four*>(A + tr);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, kWave);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0 && wave < 4) s_sum[wave] = sum;
-    __syncthreads();
-    if (threadIdx.x == 0) square[blockIdx.y * gridDim.x + blockIdx.x] = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
+        for (int e = 0; e < 4; ++e) {
+            const int i = i0 + e;
+            const size_t at = (size_t)i * D + j;
+            float o = f * v[e];
+            if (N == 1) o = fmaf(s, bf16_to_f32(add.x[e]), o);
+            if (N == 2) { o = fmaf(-s, bf16_to_f32(add.x[e]), o); o = fmaf(t, bf16_to_f32(sym.x[e]), o); o += i == j ? d : 0.f; }
+            if (SQUARE) sum += (double)o * (double)o;
+            out.x[e] = f32_to_bf16(o);
+            if (OUT == kOutFloat) static_cast<float*>(O)[at] = o;
+            else if (OUT == kOutPairs) static_cast<uint32_t*>(O)[at] = pack_pair(o);
+            else if (N > 0) static_cast<bf16_t*>(O)[at] = out.x[e];
+        }
+        if (OUT == kOutPlain) *reinterpret_cast<Four*>((N > 0 ? OT : static_cast<bf16_t*>(O)) + tr) = out;
+    });
+    if (!SQUARE) return;
+    tile_square(sum, s_sum, square);
 }
 // The last step in fp32: O = X X^T ...
 __global__ __launch_bounds__(kProdThreads) void calib_polar_square_kernel(const float* X, int D, int pitch, float* O)
@@ -597,8 +712,8 @@ __global__ __launch_bounds__(kProdThreads) void calib_correction_kernel(const ui
 // last to rounding, in fp64, as it is applied to the factor's doubles: what it cost in bits is some angles of the size of fp32 rounding over the
 // relative distance of two eigenvalues, which the fp64 steps that follow take out.  Fewer fp64 products round the result: eigenvalues off by
 // 1e-15 of the largest one where they were by 3e-15, D = 1024, r = 640.
-// At D = 1024 a transformation takes 0.27 ms (fp64: 0.38), of which the product takes 37 us (131 TFLOP/s, the fp32 matrix cores' rate), the polar
-// factor 100, the steps in blocks 65, the Gram matrix and the angles 26; and no sweep (0.85 ms) comes before them.
+// At D = 1024 a transformation takes 0.24 ms (fp64: 0.38), of which the product takes 37 us (131 TFLOP/s, the fp32 matrix cores' rate), the polar
+// factor up to 70, the steps in blocks 65, the Gram matrix and the angles 26; and no sweep (0.85 ms) comes before them.
 __global__ __launch_bounds__(kCalThreads) void calib_float_rows_kernel(const double* __restrict__ G, int D, double scale, float* __restrict__ GV)
 {
     const int i = blockIdx.x;

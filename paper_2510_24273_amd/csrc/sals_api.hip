@@ -2119,6 +2119,13 @@ sals_status calib_all_lds(bool series)
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<1, false, true>), kPairLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<2, false, false>), kPairLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<2, false, true>), kPairLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<0, true, kOutPlain>), kPlainLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<0, false, kOutPlain>), kPlainLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<1, false, kOutPlain>), kPlainLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<1, false, kOutPairs>), kPlainLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<2, false, kOutPlain>), kPlainLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<2, false, kOutPairs>), kPlainLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<2, false, kOutFloat>), kPlainLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_square_kernel), kSymLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_last_kernel), nn) &&
                     allow(reinterpret_cast<const void*>(calib_defect_kernel), kSymLds) &&
@@ -2279,6 +2286,43 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                                nxt, 2 * D);
             std::swap(cur, nxt);
         };
+        // The polar factor in floats, X or X2, with all steps but the last one in plain bf16 (E and A are such matrices, in the lower half of
+        // the room of one in pairs).
+        auto plain_factor = [&](const PolarPlan& P, const uint32_t* E_, uint32_t* A_, uint32_t* X, uint32_t* X2) -> const float* {
+            const bf16_t* const E = reinterpret_cast<const bf16_t*>(E_);
+            bf16_t* const A = reinterpret_cast<bf16_t*>(A_), *const Y = A + (size_t)D * D;
+            auto low = [](uint32_t* M) { return reinterpret_cast<bf16_t*>(M); };
+            auto high = [&](uint32_t* M) { return reinterpret_cast<bf16_t*>(M) + (size_t)D * D; };
+            const int n = P.n + (P.one_more ? 1 : 0);
+            const double w = 0.5 * P.a[0] * P.a[0] * P.a[0] / (P.top * P.top * P.top), c1 = 1.5 * P.a[0] / P.top - w;
+            auto first = [&](auto out) {
+                hipLaunchKernelGGL((calib_polar_plain_kernel<2, false, (PolarOut)decltype(out)::value>), tile_grid, prod, kPlainLds, st, A, E, D,
+                                   (float)(w * P.tau * P.tau * P.tau), (float)c1, (float)(c1 * P.tau), E, (float)(-w * P.tau * P.tau), X, high(X), nullptr);
+            };
+            if (n == 1) first(std::integral_constant<int, kOutFloat>{});
+            else if (n == 2) first(std::integral_constant<int, kOutPairs>{});
+            else first(std::integral_constant<int, kOutPlain>{});
+            for (int k = 1; k < n; ++k) {
+                const double a = k < P.n ? P.a[k] : 1.0;
+                const float f = (float)(-0.5 * a * a * a), s = (float)(1.5 * a);
+                if (k == n - 1) {
+                    hipLaunchKernelGGL((calib_polar_kernel<0, false, false>), tile_grid, prod, kPairLds, st, X, X, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr, A_,
+                                       nullptr);
+                    hipLaunchKernelGGL((calib_polar_kernel<1, false, true>), tile_grid, prod, kPairLds, st, A_, X, D, f, 0.f, s, X, 0.f, nullptr, X2, nullptr);
+                } else {
+                    auto step = [&](auto out) {
+                        hipLaunchKernelGGL((calib_polar_plain_kernel<1, false, (PolarOut)decltype(out)::value>), tile_grid, prod, kPlainLds, st, Y, high(X), D, f,
+                                           0.f, s, high(X), 0.f, X2, high(X2), nullptr);
+                    };
+                    hipLaunchKernelGGL((calib_polar_plain_kernel<0, false, kOutPlain>), tile_grid, prod, kPlainLds, st, low(X), low(X), D, 1.f, 0.f, 0.f, nullptr,
+                                       0.f, Y, nullptr, nullptr);
+                    if (k == n - 2) step(std::integral_constant<int, kOutPairs>{});
+                    else step(std::integral_constant<int, kOutPlain>{});
+                }
+                std::swap(X, X2);
+            }
+            return reinterpret_cast<const float*>(X);
+        };
         hipLaunchKernelGGL(calib_float_rows_kernel, dim3(D), dim3(kCalThreads), 0, st, rows, D, std::ldexp(1.0, -expo), cur);
         double before = 1e300;
         bool polished = false, enough = false;
@@ -2295,9 +2339,18 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             std::swap(cur, nxt);
             uint32_t *const A = reinterpret_cast<uint32_t*>(nxt), *const E = A + (size_t)D * D;
             hipLaunchKernelGGL((calib_gram_kernel<float>), sym_grid, prod, kSymLds, st, cur, D, 2 * D, sorted, r, reinterpret_cast<float*>(A), row_off);
-            hipLaunchKernelGGL(calib_all_angles_kernel, dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D, sorted, r,
-                               row_off, kFloatOpen, E, all_found);
-            hipLaunchKernelGGL((calib_polar_kernel<0, true, false>), tile_grid, prod, kPairLds, st, E, E, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr, A, square);
+            const bool plain = !polished;   // (large angles)
+            if (plain) {
+                hipLaunchKernelGGL((calib_all_angles_kernel<bf16_t>), dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D, sorted,
+                                   r, row_off, kFloatOpen, reinterpret_cast<bf16_t*>(E), all_found);
+                hipLaunchKernelGGL((calib_polar_plain_kernel<0, true, kOutPlain>), tile_grid, prod, kPlainLds, st, reinterpret_cast<const bf16_t*>(E),
+                                   reinterpret_cast<const bf16_t*>(E), D, 1.f, 0.f, 0.f, nullptr, 0.f, A, nullptr, square);
+            } else {
+                hipLaunchKernelGGL((calib_all_angles_kernel<uint32_t>), dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D,
+                                   sorted, r, row_off, kFloatOpen, E, all_found);
+                hipLaunchKernelGGL((calib_polar_kernel<0, true, false>), tile_grid, prod, kPairLds, st, E, E, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr, A,
+                                   square);
+            }
             const bool first = before == 1e300;
             if (!read(h_found, all_found, (size_t)(n_angles + n_tiles) * 8) || (first && !read(h_norm, sorted, (size_t)D * 8)) || !wait())
                 return SALS_ERR_HIP;
@@ -2307,7 +2360,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             const double now = std::sqrt(e2);
             const PolarPlan P = polar_plan(a2, now <= kFloatLast ? kPolarNear : kFloatPolar);
             if (!std::isfinite(now) || P.n == 0 || (first && (now <= kFloatFirst || h_norm[D - 1] > kFloatSpread * h_norm[0]))) return SALS_OK;
-            const float* const X = polar_factor(P, E, A, A, c0, c1, false);
+            const float* const X = plain ? plain_factor(P, E, A, c0, c1) : polar_factor(P, E, A, A, c0, c1, false);
             hipLaunchKernelGGL(calib_float_apply_kernel, dim3(2 * D / 64, D / 64), prod, (prod_lds<float, float, true>()), st, X, cur, D, 2 * D, 1.f, 0.f, nxt,
                                2 * D);
             std::swap(cur, nxt);
@@ -2356,7 +2409,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             uint32_t *const E = reinterpret_cast<uint32_t*>(third), *const A = E + (size_t)D * D;
             hipLaunchKernelGGL((calib_gram_kernel<double>), sym_grid, prod, kSymLds, st, rows, D, D, sorted, r,
                                reinterpret_cast<float*>(A), row_off);
-            hipLaunchKernelGGL(calib_all_angles_kernel, dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D, sorted, r, row_off,
+            hipLaunchKernelGGL((calib_all_angles_kernel<uint32_t>), dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D, sorted, r, row_off,
                                kAllOpen, E, all_found);
             hipLaunchKernelGGL((calib_polar_kernel<0, true, false>), tile_grid, prod, kPairLds, st, E, E, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr,
                                A, square);

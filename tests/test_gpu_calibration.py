@@ -225,6 +225,32 @@ def test_the_way_in_floats_leaves_no_trace(D, r, kind):
     assert float((V @ C - L[:, None] * V).norm(dim=1).max()) <= (2e-11 + eps) * lam[0]
 
 
+@pytest.mark.parametrize("D,r,turn", [(256, 160, 0.3), (512, 512, 0.3), (256, 256, 2.0), (768, 480, 2.0), (256, 100, 12.0), (1280, 64, 12.0)])
+def test_polar_factors_that_steer(D, r, turn):
+    """Eigenvectors turned out of the axes by angles whose squares sum to turn^2: polar factors of one, two and more steps in floats, the
+    smallest width and one that is no power of two.  What they are rounded to must not be seen in the result."""
+    print(f"[case] polar factors, D={D} r={r} turned by {turn:g}", flush=True)
+    rng = np.random.default_rng(D + r)
+    K = torch.from_numpy(np.triu(rng.standard_normal((D, D)), 1)).to(gu.DEV)
+    K = (K - K.T) * (turn / D)
+    Q = torch.linalg.matrix_exp(K)
+    lam = np.linspace(3.0, 0.5, D)
+    C = (Q * gu.to_dev(lam)) @ Q.T.contiguous()
+    C = (0.5 * (C + C.T)).contiguous()
+    rows = C.clone()
+    got, U, sweeps = binding.calib_eigenvectors(rows, r, torch.float32)
+    torch.cuda.synchronize()
+    assert 0 < sweeps <= 20
+    # (bounds as above: the matrix is that of `lam` to the rounding of its products, and at most 20 transformations)
+    eps = 4 * 60 * np.sqrt(D) * 2.0 ** -53
+    np.testing.assert_allclose(got.cpu().numpy()[:r], lam[:r], rtol=0, atol=eps * lam[0])
+    norm = rows.norm(dim=1)
+    lead = torch.argsort(-norm)[:r]
+    V = rows[lead] / norm[lead, None]
+    assert float((V @ V.T.contiguous() - torch.eye(r, device=gu.DEV, dtype=torch.float64)).abs().max()) <= 2e-11
+    assert float((V @ C - norm[lead, None] * V).norm(dim=1).max()) <= (2e-11 + eps) * lam[0]
+
+
 @pytest.mark.parametrize("large,width,n_large,r", [(1e5, 1e-11, 2, 3), (1e5, 1e-11, 4, 8), (10.0, 1e-10, 4, 8), (1e3, 1e-10, 4, 12)])
 def test_rows_of_a_tight_cluster_are_asked_to_have_converged(large, width, n_large, r):
     """A few large eigenvalues and all others within a relative `width`, the r-th among these: its row's norm falls far while the large
