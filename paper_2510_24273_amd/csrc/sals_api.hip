@@ -2112,6 +2112,9 @@ sals_status calib_all_lds(bool series)
     if (!series) return SALS_OK;
     const bool ok = allow(reinterpret_cast<const void*>(calib_gram_kernel<double>), kSymLds) &&
                     allow(reinterpret_cast<const void*>(calib_gram_kernel<float>), kSymLds) &&
+                    allow(reinterpret_cast<const void*>(calib_series_kernel<false>), kSymLds) &&
+                    allow(reinterpret_cast<const void*>(calib_series_kernel<true>), kSymLds) &&
+                    allow(reinterpret_cast<const void*>(calib_series_rest_kernel), prod_lds<float, float, false>()) &&
                     allow(reinterpret_cast<const void*>(calib_float_apply_kernel), nn) &&
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<0, true, false>), kPairLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<0, false, false>), kPairLds) &&
@@ -2467,17 +2470,20 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             for (int i = 0; i < n_tiles; ++i) { most = std::max(most, h_found[2 * i]); square_sum += h_found[2 * i + 1]; }
             converged = most <= 1e-11;
             if (converged || !series || !(square_sum <= kSeriesNorm * kSeriesNorm)) break;
-            // exp(E) G from the inside out: G + E (G + E/2 (G + E/3 (G + E/4 G))).  A product may be written over G, but not over the matrix
-            // it multiplies, whose rows other workgroups still read: one term alone, which multiplies G, goes to the other matrix.
-            const int terms = square_sum <= 1e-18 ? 1 : square_sum <= 4e-8 ? 2 : 4;
-            double *X = rows, *Y = other;
-            for (int k = terms; k >= 1; --k) {
-                Y = k == 1 && X != rows ? rows : X == other ? third : other;
-                hipLaunchKernelGGL((calib_apply_kernel<double, true>), tile_grid, prod, (prod_lds<double, double, true>()), st, C, X, rows,
-                                   1.0 / k, Y, D);
-                X = Y;
+            // exp(E) G = G + (exp(E) - I) G, with as many terms as are above rounding.
+            const double* X = C;
+            if (square_sum > 1e-18) {
+                float* const P = reinterpret_cast<float*>(third), *const L = P + (size_t)D * D;
+                X = other;
+                if (square_sum <= 4e-8) {
+                    hipLaunchKernelGGL((calib_series_kernel<false>), sym_grid, prod, kSymLds, st, C, D, other, P, L);
+                } else {
+                    hipLaunchKernelGGL((calib_series_kernel<true>), sym_grid, prod, kSymLds, st, C, D, other, P, L);
+                    hipLaunchKernelGGL(calib_series_rest_kernel, tile_grid, prod, (prod_lds<float, float, false>()), st, L, P, D, other);
+                }
             }
-            if (terms == 1) std::swap(rows, other);
+            hipLaunchKernelGGL((calib_apply_kernel<double, true>), tile_grid, prod, (prod_lds<double, double, true>()), st, X, rows, rows, 1.0, third, D);
+            std::swap(rows, third);
             find_lead(rows);
         }
     }
