@@ -24,6 +24,7 @@
 #include "common.hpp"
 #include "k_calib.hpp"
 #include "k_gemm.hpp"
+#include "polar_plan.hpp"
 
 namespace sals {
 
@@ -360,8 +361,9 @@ __device__ __forceinline__ void calib_product_pairs(const uint32_t* A, const uin
 
 // The same for A B^T of plain bf16 matrices, summed in fp32.  A step is 128 elements of a row, 64 for either half of the waves.
 constexpr size_t kPlainLds = (size_t)kProdStages * 32768;
-template <typename Finish>
-__device__ __forceinline__ void calib_product_plain(const bf16_t* A, const bf16_t* B, int D, Finish finish)
+// meanwhile(): while the first steps are on their way.
+template <typename Meanwhile, typename Finish>
+__device__ __forceinline__ void calib_product_plain(const bf16_t* A, const bf16_t* B, int D, Meanwhile meanwhile, Finish finish)
 {
     constexpr int STAGE = 32768, ST = kProdStages;   // [A: two 64-element pieces of 64 rows | B]
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -386,6 +388,7 @@ __device__ __forceinline__ void calib_product_plain(const bf16_t* A, const bf16_
     };
 #pragma unroll
     for (int s = 0; s < ST - 1; ++s) load(s);
+    meanwhile();
     f32x4 acc[2][2];
 #pragma unroll
     for (int u = 0; u < 2; ++u)
@@ -642,6 +645,8 @@ __global__ __launch_bounds__(kProdThreads) void calib_polar_kernel(const uint32_
     if (!SQUARE) return;
     tile_square(sum, s_sum, square);
 }
+constexpr int kPolarFound = 4;   // a thread's tiles, of at most (kFloatMaxD / 64)^2
+static_assert((kFloatMaxD / 64) * (kFloatMaxD / 64) <= kPolarFound * kProdThreads, "every tile's sum is read");
 // The steps of a polar factor that only steers, in plain bf16 up to the last one: O = f A B^T (N == 0, symmetric), that and s S (N == 1), or
 // d I + s E + t A + f A E^T (N == 2, B = S = E, which is skew).  What is symmetric or skew is read and written by rows for columns, four
 // elements a lane; of what is neither, S and OT are the transposes.  Left as plain bf16, in pairs or in fp32.
@@ -651,15 +656,40 @@ __global__ __launch_bounds__(kProdThreads) void calib_polar_kernel(const uint32_
 // takes from X's singular values is made good by the last step, in pairs: X X^T - I stays within 4e-3.  Not once V is polished: the last angles
 // are told in pairs.
 enum PolarOut { kOutPlain, kOutPairs, kOutFloat };
-template <int N, bool SQUARE, PolarOut OUT>
+//
+// FIND: the scalars of the first step (N == 2) from the sums of squares of A's tiles, as polar_plan has them, so that the step need not wait for the
+// host to learn them: that costs 12 us of an idle device each time.
+template <int N, bool SQUARE, PolarOut OUT, bool FIND>
 __global__ __launch_bounds__(kProdThreads) void calib_polar_plain_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, int D, float f,
                                                                          float d, float s, const bf16_t* __restrict__ S, float t,
                                                                          void* __restrict__ O, bf16_t* __restrict__ OT, double* __restrict__ square)
 {
     struct alignas(8) Four { bf16_t x[4]; };
-    __shared__ double s_sum[4];
-    double sum = 0.0;
-    calib_product_plain(A, B, D, [&](int i0, int j, const f32x4& v) {
+    static_assert(!FIND || (N == 2 && !SQUARE), "the first step");
+    __shared__ double s_sum[kProdThreads / kWave];
+    double sum = 0.0, found[kPolarFound];
+    const int n_tiles = gridDim.x * gridDim.y;
+    if (FIND) {   // (requested ahead of the operands)
+#pragma unroll
+        for (int u = 0; u < kPolarFound; ++u) found[u] = square[min((int)threadIdx.x + u * kProdThreads, n_tiles - 1)];
+    }
+    auto scalars = [&]() {
+        if (!FIND) return;
+        double a2 = 0.0;
+#pragma unroll
+        for (int u = 0; u < kPolarFound; ++u) a2 += (int)threadIdx.x + u * kProdThreads < n_tiles ? found[u] : 0.0;
+        a2 = wave_sum_f64(a2);
+        if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = a2;
+        __syncthreads();
+        a2 = 0.0;
+#pragma unroll
+        for (int w = 0; w < kProdThreads / kWave; ++w) a2 += s_sum[w];
+        const double bound = sqrt(sqrt(a2)), tau = bound > kAllCap ? kAllCap / bound : 1.0, tb = tau * bound, top = sqrt(1.0 + tb * tb);
+        const double low = 1.0 / top, a = low < kFloatPolar ? sqrt(3.0 / (1.0 + low + low * low)) : 1.0;
+        const double w = 0.5 * a * a * a / (top * top * top), c1 = 1.5 * a / top - w;
+        f = (float)(w * tau * tau * tau); d = (float)c1; s = (float)(c1 * tau); t = (float)(-w * tau * tau);
+    };
+    calib_product_plain(A, B, D, scalars, [&](int i0, int j, const f32x4& v) {
         const size_t tr = (size_t)j * D + i0;
         Four add{}, sym{}, out;
         if (N > 0) add = *reinterpret_cast<const Four*>(S + tr);

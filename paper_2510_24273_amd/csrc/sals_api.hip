@@ -2039,6 +2039,10 @@ private:
     static Blocks& kept() { static Blocks b = {}; return b; }
     size_t n;
 };
+struct Event {
+    hipEvent_t e = nullptr;
+    ~Event() { if (e) (void)hipEventDestroy(e); }
+};
 struct EigWs {  // byte offsets into the workspace
     size_t G, conv, norm, sgn, diag, part, Y0, Y1, total;
 };
@@ -2094,11 +2098,7 @@ inline int all_first(int D) { return D <= 2048 ? 1 : D < 3072 ? 3 : 4; }
 // 4.01 with a spectrum c^-2; steps next to blocks twice: 3.72.
 // Not begun where the rows of the factor are nearly orthogonal as they are, or of nearly equal norms (kFloatSpread of each other): eigenvalues
 // that close are told apart in fp64 only, and the polar factors' rounding would mix them (eigenvalues within 1e-3: 6.3 ms, and 4.8).
-constexpr int kFloatMaxD = 2560;
 constexpr double kFloatFirst = 0.1, kFloatSpread = 0.9, kFloatLast = 0.1, kFloatPolish = 3.5;
-// singular values of their polar factors: one step further from here on, which leaves 3 e-3 of X X^T - I (as good as 7e-6: 3.6 ms at D = 1024
-// with either, but three steps instead of four; 0.9 takes more transformations)
-constexpr double kFloatPolar = 0.97;
 // the series of the exponential: cut behind E^4 it differs from an orthogonal matrix by |E|^6 / 72
 constexpr double kSeriesNorm = 4e-3;
 // the product kernels' dynamic LDS, beyond the default limit
@@ -2122,13 +2122,14 @@ sals_status calib_all_lds(bool series)
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<1, false, true>), kPairLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<2, false, false>), kPairLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_kernel<2, false, true>), kPairLds) &&
-                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<0, true, kOutPlain>), kPlainLds) &&
-                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<0, false, kOutPlain>), kPlainLds) &&
-                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<1, false, kOutPlain>), kPlainLds) &&
-                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<1, false, kOutPairs>), kPlainLds) &&
-                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<2, false, kOutPlain>), kPlainLds) &&
-                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<2, false, kOutPairs>), kPlainLds) &&
-                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<2, false, kOutFloat>), kPlainLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<0, true, kOutPlain, false>), kPlainLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<0, false, kOutPlain, false>), kPlainLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<1, false, kOutPlain, false>), kPlainLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<1, false, kOutPairs, false>), kPlainLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<2, false, kOutPlain, false>), kPlainLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<2, false, kOutPlain, true>), kPlainLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<2, false, kOutPairs, false>), kPlainLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<2, false, kOutFloat, false>), kPlainLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_square_kernel), kSymLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_last_kernel), nn) &&
                     allow(reinterpret_cast<const void*>(calib_defect_kernel), kSymLds) &&
@@ -2290,35 +2291,43 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             std::swap(cur, nxt);
         };
         // The polar factor in floats, X or X2, with all steps but the last one in plain bf16 (E and A are such matrices, in the lower half of
-        // the room of one in pairs).
-        auto plain_factor = [&](const PolarPlan& P, const uint32_t* E_, uint32_t* A_, uint32_t* X, uint32_t* X2) -> const float* {
-            const bf16_t* const E = reinterpret_cast<const bf16_t*>(E_);
-            bf16_t* const A = reinterpret_cast<bf16_t*>(A_), *const Y = A + (size_t)D * D;
-            auto low = [](uint32_t* M) { return reinterpret_cast<bf16_t*>(M); };
-            auto high = [&](uint32_t* M) { return reinterpret_cast<bf16_t*>(M) + (size_t)D * D; };
+        // the room of one in pairs).  Its first step and the square that the next one begins with can be launched before the plan is known; they are
+        // `ahead`, and made again if the plan turns out to have fewer than three steps.
+        auto low = [](uint32_t* M) { return reinterpret_cast<bf16_t*>(M); };
+        auto high = [&](uint32_t* M) { return reinterpret_cast<bf16_t*>(M) + (size_t)D * D; };
+        auto plain_square = [&](uint32_t* X, uint32_t* A) {
+            hipLaunchKernelGGL((calib_polar_plain_kernel<0, false, kOutPlain, false>), tile_grid, prod, kPlainLds, st, low(X), low(X), D, 1.f, 0.f, 0.f, nullptr,
+                               0.f, high(A), nullptr, nullptr);
+        };
+        auto begin_plain = [&](uint32_t* E, uint32_t* A, uint32_t* X) {
+            hipLaunchKernelGGL((calib_polar_plain_kernel<2, false, kOutPlain, true>), tile_grid, prod, kPlainLds, st, low(A), low(E), D, 0.f, 0.f, 0.f, low(E),
+                               0.f, X, high(X), square);
+            plain_square(X, A);
+        };
+        auto plain_factor = [&](const PolarPlan& P, bool ahead, uint32_t* E, uint32_t* A, uint32_t* X, uint32_t* X2) -> const float* {
             const int n = P.n + (P.one_more ? 1 : 0);
             const double w = 0.5 * P.a[0] * P.a[0] * P.a[0] / (P.top * P.top * P.top), c1 = 1.5 * P.a[0] / P.top - w;
+            ahead = ahead && n > 2;
             auto first = [&](auto out) {
-                hipLaunchKernelGGL((calib_polar_plain_kernel<2, false, (PolarOut)decltype(out)::value>), tile_grid, prod, kPlainLds, st, A, E, D,
-                                   (float)(w * P.tau * P.tau * P.tau), (float)c1, (float)(c1 * P.tau), E, (float)(-w * P.tau * P.tau), X, high(X), nullptr);
+                hipLaunchKernelGGL((calib_polar_plain_kernel<2, false, (PolarOut)decltype(out)::value, false>), tile_grid, prod, kPlainLds, st, low(A), low(E),
+                                   D, (float)(w * P.tau * P.tau * P.tau), (float)c1, (float)(c1 * P.tau), low(E), (float)(-w * P.tau * P.tau), X, high(X), nullptr);
             };
             if (n == 1) first(std::integral_constant<int, kOutFloat>{});
             else if (n == 2) first(std::integral_constant<int, kOutPairs>{});
-            else first(std::integral_constant<int, kOutPlain>{});
+            else if (!ahead) first(std::integral_constant<int, kOutPlain>{});
             for (int k = 1; k < n; ++k) {
                 const double a = k < P.n ? P.a[k] : 1.0;
                 const float f = (float)(-0.5 * a * a * a), s = (float)(1.5 * a);
                 if (k == n - 1) {
-                    hipLaunchKernelGGL((calib_polar_kernel<0, false, false>), tile_grid, prod, kPairLds, st, X, X, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr, A_,
+                    hipLaunchKernelGGL((calib_polar_kernel<0, false, false>), tile_grid, prod, kPairLds, st, X, X, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr, A,
                                        nullptr);
-                    hipLaunchKernelGGL((calib_polar_kernel<1, false, true>), tile_grid, prod, kPairLds, st, A_, X, D, f, 0.f, s, X, 0.f, nullptr, X2, nullptr);
+                    hipLaunchKernelGGL((calib_polar_kernel<1, false, true>), tile_grid, prod, kPairLds, st, A, X, D, f, 0.f, s, X, 0.f, nullptr, X2, nullptr);
                 } else {
                     auto step = [&](auto out) {
-                        hipLaunchKernelGGL((calib_polar_plain_kernel<1, false, (PolarOut)decltype(out)::value>), tile_grid, prod, kPlainLds, st, Y, high(X), D, f,
-                                           0.f, s, high(X), 0.f, X2, high(X2), nullptr);
+                        hipLaunchKernelGGL((calib_polar_plain_kernel<1, false, (PolarOut)decltype(out)::value, false>), tile_grid, prod, kPlainLds, st, high(A),
+                                           high(X), D, f, 0.f, s, high(X), 0.f, X2, high(X2), nullptr);
                     };
-                    hipLaunchKernelGGL((calib_polar_plain_kernel<0, false, kOutPlain>), tile_grid, prod, kPlainLds, st, low(X), low(X), D, 1.f, 0.f, 0.f, nullptr,
-                                       0.f, Y, nullptr, nullptr);
+                    if (k > 1 || !ahead) plain_square(X, A);
                     if (k == n - 2) step(std::integral_constant<int, kOutPairs>{});
                     else step(std::integral_constant<int, kOutPlain>{});
                 }
@@ -2327,7 +2336,10 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             return reinterpret_cast<const float*>(X);
         };
         hipLaunchKernelGGL(calib_float_rows_kernel, dim3(D), dim3(kCalThreads), 0, st, rows, D, std::ldexp(1.0, -expo), cur);
+        Event copied;
+        if (hipEventCreateWithFlags(&copied.e, hipEventDisableTiming) != hipSuccess) return SALS_ERR_HIP;
         double before = 1e300;
+        int steps = 0;   // of the last polar factor
         bool polished = false, enough = false;
         for (;;) {
             hipLaunchKernelGGL((calib_jacobi_inside_gram_kernel<float>), dim3(n_blocks, n_part), dim3(256), 0, st, cur, 2 * D, D / n_part, fpart);
@@ -2346,7 +2358,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             if (plain) {
                 hipLaunchKernelGGL((calib_all_angles_kernel<bf16_t>), dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D, sorted,
                                    r, row_off, kFloatOpen, reinterpret_cast<bf16_t*>(E), all_found);
-                hipLaunchKernelGGL((calib_polar_plain_kernel<0, true, kOutPlain>), tile_grid, prod, kPlainLds, st, reinterpret_cast<const bf16_t*>(E),
+                hipLaunchKernelGGL((calib_polar_plain_kernel<0, true, kOutPlain, false>), tile_grid, prod, kPlainLds, st, reinterpret_cast<const bf16_t*>(E),
                                    reinterpret_cast<const bf16_t*>(E), D, 1.f, 0.f, 0.f, nullptr, 0.f, A, nullptr, square);
             } else {
                 hipLaunchKernelGGL((calib_all_angles_kernel<uint32_t>), dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D,
@@ -2355,15 +2367,23 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                                    square);
             }
             const bool first = before == 1e300;
-            if (!read(h_found, all_found, (size_t)(n_angles + n_tiles) * 8) || (first && !read(h_norm, sorted, (size_t)D * 8)) || !wait())
+            if (!read(h_found, all_found, (size_t)(n_angles + n_tiles) * 8) || (first && !read(h_norm, sorted, (size_t)D * 8))) return SALS_ERR_HIP;
+            const bool ahead = plain && steps > 2;   // (not the first time, which may leave C as it is)
+            if (ahead) {
+                if (hipEventRecord(copied.e, st) != hipSuccess) return SALS_ERR_HIP;
+                begin_plain(E, A, c0);
+                if (launch_status() != SALS_OK || hipEventSynchronize(copied.e) != hipSuccess) return SALS_ERR_HIP;
+            } else if (!wait()) {
                 return SALS_ERR_HIP;
+            }
             double e2 = 0.0, a2 = 0.0;
             for (int i = 0; i < n_angles; ++i) e2 += h_found[i];
             for (int i = 0; i < n_tiles; ++i) a2 += h_found[n_angles + i];
             const double now = std::sqrt(e2);
-            const PolarPlan P = polar_plan(a2, now <= kFloatLast ? kPolarNear : kFloatPolar);
+            const PolarPlan P = polar_plan(a2, now <= kFloatLast && polished ? kPolarNear : kFloatPolar);
             if (!std::isfinite(now) || P.n == 0 || (first && (now <= kFloatFirst || h_norm[D - 1] > kFloatSpread * h_norm[0]))) return SALS_OK;
-            const float* const X = plain ? plain_factor(P, E, A, c0, c1) : polar_factor(P, E, A, A, c0, c1, false);
+            steps = P.n + (P.one_more ? 1 : 0);
+            const float* const X = plain ? plain_factor(P, ahead, E, A, c0, c1) : polar_factor(P, E, A, A, c0, c1, false);
             hipLaunchKernelGGL(calib_float_apply_kernel, dim3(2 * D / 64, D / 64), prod, (prod_lds<float, float, true>()), st, X, cur, D, 2 * D, 1.f, 0.f, nxt,
                                2 * D);
             std::swap(cur, nxt);
