@@ -340,6 +340,19 @@ template <typename ACC> struct mma_tile;   // result element e of a 16 x 16 tile
 template <> struct mma_tile<double> { typedef f64x4 acc; static __device__ __forceinline__ int row(int kg, int e) { return kg + 4 * e; } };
 template <> struct mma_tile<float> { typedef f32x4 acc; static __device__ __forceinline__ int row(int kg, int e) { return 4 * kg + e; } };
 
+// x of lane K of the row of 16 lanes
+template <int K> __device__ __forceinline__ double row16_value(double x)
+{
+    const int2 u = __builtin_bit_cast(int2, x);
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_update_dpp(0, u.x, 0x150 + K, 0xf, 0xf, true),
+                                                __builtin_amdgcn_update_dpp(0, u.y, 0x150 + K, 0xf, 0xf, true)));
+}
+template <typename F, int... K> __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, K...>)
+{
+    (f(std::integral_constant<int, K>{}), ...);
+}
+template <int N, typename F> __device__ __forceinline__ void static_for(F&& f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
+
 // 1 / sqrt(x) for normal x: the hardware's estimate and one third-order step (full precision)
 __device__ __forceinline__ double rsqrt_f64(double x)
 {
@@ -348,31 +361,33 @@ __device__ __forceinline__ double rsqrt_f64(double x)
 }
 
 // Panel at row k0: every workgroup factors the 64 x 64 diagonal block by itself (repeating it beats another launch) and carries
-// 64 columns of the panel along, all in LDS, 16 rows at a time: one wave factors the 16 x 16 diagonal block in registers (a
-// column per lane, the pivot row passed through scalar registers), two waves carry the columns behind it through the
-// triangular solve (a column per thread), and the matrix cores take the 16 rows out of those below.  Bound by the 64 dependent
-// pivots.  20 us at D = 1024; one pivot at a time over the whole block (a barrier and a division each) and a solve of 64 unrolled
-// steps per column took 62.
+// 64 columns of the panel along, all in LDS, 16 rows at a time: one wave factors the 16 x 16 diagonal block in registers (a column per
+// lane, the pivot row passed along the lanes), two waves carry the columns behind it through the triangular solve (a column per
+// thread), and the matrix cores take the 16 rows out of those below; of these the first wave takes the next diagonal block alone and
+// factors it while the other waves do the rest.  Bound by the 64 dependent pivots.  15.4 us at D = 1024; 18.8 with the pivot row
+// passed through scalar registers (two reads per element, and what did not fit of them spilled), 20.1 with the factoring behind all tiles as
+// well; one pivot at a time over the whole block (a barrier and a division each) and a solve of 64 unrolled steps per column took 62.
 // The factored block goes to `diag` (other workgroups still read the original).  grid max(1, (D - k0 - 64) / 64).
 constexpr int kCholLd = 2 * kCalPanel + 2;   // row pitch: the diagonal block's columns, then the workgroup's 64 columns
 // The shift is `f` times 1e-14 of `scale` (see calib_scale_kernel).
 __global__ __launch_bounds__(256) void calib_chol_panel_kernel(double* __restrict__ G, int D, int k0, const double* __restrict__ scale, double f,
                                                                double* __restrict__ diag, int* __restrict__ fail)
 {
-    const double shift = kCalShift * *scale * f;
     __shared__ double M[kCalPanel * kCholLd];
     __shared__ double invd[kCalPanel];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, kg = lane >> 4;
     const int c0 = k0 + kCalPanel + blockIdx.x * 64;
     const bool panel = c0 < D;   // uniform
+    double* rows = G + (size_t)(k0 + wave) * D + lane;   // row u 4 + wave of the panel, column `lane` of a block
+    const size_t four = (size_t)4 * D;
     {   // (all loads requested together)
+        const int* const sc = reinterpret_cast<const int*>(scale);
+        const int2 s2 = make_int2(ld_uniform_i32(sc), ld_uniform_i32(sc + 1));
+        const double *block = rows + k0, *column = rows + (panel ? c0 : k0);   // (without a panel: again, and not used)
         double v[2][16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const double* row = G + (size_t)(k0 + u * 4 + wave) * D + lane;
-            v[0][u] = row[k0];
-            v[1][u] = panel ? row[c0] : 0.0;
-        }
+        for (int u = 0; u < 16; ++u) { v[0][u] = *block; v[1][u] = *column; block += four; column += four; }
+        const double shift = kCalShift * __builtin_bit_cast(double, s2) * f;
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
             const int i = u * 4 + wave;
@@ -381,31 +396,56 @@ __global__ __launch_bounds__(256) void calib_chol_panel_kernel(double* __restric
         }
     }
     bool good = true;
+    auto factor_block = [&](int b) {   // by one wave
+        double a[16], mine = 0.0;   // column l16 of the block (in every row of 16 lanes), 1 / pivot l16
+#pragma unroll
+        for (int r = 0; r < 16; ++r) a[r] = M[(b + r) * kCholLd + b + l16];
+        static_for<16>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            const double pv = row16_value<k>(a[k]);
+            good = good && pv > 0.0;
+            const double inv = pv > 0.0 ? rsqrt_f64(pv) : 0.0;
+            a[k] *= inv;                                  // row k of the factor
+            mine = l16 == k ? inv : mine;
+            static_for<15 - k>([&](auto rc) {
+                constexpr int r = k + 1 + decltype(rc)::value;
+                a[r] = fma(-row16_value<r>(a[k]), a[k], a[r]);
+            });
+        });
+        if (kg == 0) {
+            invd[b + l16] = mine;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) M[(b + r) * kCholLd + b + l16] = l16 >= r ? a[r] : 0.0;
+        }
+    };
+    // tile (i, j) less what the 16 rows at b contribute to it, by one wave
+    auto take_out = [&](int b, int i, int j) {
+        f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const double* r = M + (b + 4 * s + kg) * kCholLd + l16;
+            acc = mma_f64(r[i], r[j], acc);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) M[(i + kg + 4 * e) * kCholLd + j + l16] -= acc[e];
+    };
     __syncthreads();
 #pragma unroll 1
     for (int b = 0; b < kCalPanel; b += 16) {
+        // The first wave brings the diagonal block up to date and factors it, the others bring the other tiles (row block i, column block
+        // j >= i) up to date meanwhile
         if (wave == 0) {
-            double a[16];   // column l16 of the block
-#pragma unroll
-            for (int r = 0; r < 16; ++r) a[r] = M[(b + r) * kCholLd + b + l16];
-            auto lane_value = [](double x, int from) {
-                const int2 u = __builtin_bit_cast(int2, x);
-                return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(u.x, from), __builtin_amdgcn_readlane(u.y, from)));
-            };
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const double pv = lane_value(a[k], k);
-                good &= pv > 0.0;
-                const double inv = pv > 0.0 ? rsqrt_f64(pv) : 0.0;
-                a[k] *= inv;                                  // row k of the factor
-                if (lane == 0) invd[b + k] = inv;
-#pragma unroll
-                for (int r = k + 1; r < 16; ++r) a[r] -= lane_value(a[k], r) * a[k];
-            }
-            if (kg == 0) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) M[(b + r) * kCholLd + b + l16] = l16 >= r ? a[r] : 0.0;
-            }
+            if (b > 0) take_out(b - 16, b, b);
+            asm volatile("" ::: "memory");   // (a wave's LDS instructions are carried out in order)
+            __builtin_amdgcn_wave_barrier();
+            factor_block(b);
+        } else if (b > 0) {
+            int t = 0;
+#pragma unroll 1
+            for (int i = b; i < kCalPanel; i += 16)
+#pragma unroll 1
+                for (int j = i == b ? i + 16 : i; j < (panel ? 2 : 1) * kCalPanel; j += 16)
+                    if (t++ % 3 + 1 == wave) take_out(b - 16, i, j);   // uniform
         }
         __syncthreads();
         if (wave < 2 && tid >= b + 16) {   // column tid: forward substitution R_bb^T x = a
@@ -422,30 +462,18 @@ __global__ __launch_bounds__(256) void calib_chol_panel_kernel(double* __restric
             for (int r = 0; r < 16; ++r) M[(b + r) * kCholLd + tid] = x[r];
         }
         __syncthreads();
-        // tiles (row block i, column block j >= i) behind the 16 rows, dealt to the waves
-        int t = 0;
-#pragma unroll 1
-        for (int i = b + 16; i < kCalPanel; i += 16)
-#pragma unroll 1
-            for (int j = i; j < (panel ? 2 : 1) * kCalPanel; j += 16, ++t) {
-                if ((t & 3) != wave) continue;   // uniform
-                f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const double* r = M + (b + 4 * s + kg) * kCholLd + l16;
-                    acc = mma_f64(r[i], r[j], acc);
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) M[(i + kg + 4 * e) * kCholLd + j + l16] -= acc[e];
-            }
-        __syncthreads();
     }
     if (!good && lane == 0 && wave == 0 && blockIdx.x == 0) *fail = 1;
+    if (blockIdx.x == 0) {
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-        const int i = u * 4 + wave;
-        if (blockIdx.x == 0) diag[(size_t)(k0 + i) * kCalPanel + lane] = lane >= i ? M[i * kCholLd + lane] : 0.0;
-        if (panel) G[(size_t)(k0 + i) * D + c0 + lane] = M[i * kCholLd + kCalPanel + lane];
+        for (int u = 0; u < 16; ++u) {
+            const int i = u * 4 + wave;
+            diag[(size_t)(k0 + i) * kCalPanel + lane] = lane >= i ? M[i * kCholLd + lane] : 0.0;
+        }
+    }
+    if (panel) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u) { rows[c0] = M[(u * 4 + wave) * kCholLd + kCalPanel + lane]; rows += four; }
     }
 }
 
