@@ -531,6 +531,10 @@ constexpr int kJacRec = 3 * kJacTile;       // Gram matrix of a 32-row block: sm
 // (3,3) (0,3) (1,3)
 constexpr int kJacTiles = 10, kJacBigRec = kJacTiles * kJacTile;
 constexpr int kTile00 = 0, kTile01 = 1, kTile11 = 2, kTile02 = 3, kTile12 = 4, kTile22 = 5, kTile23 = 6, kTile33 = 7, kTile03 = 8;
+// tile of small blocks u <= v, and the blocks of a tile
+__device__ __forceinline__ int jac_tile_of(int u, int v) { return (int)(0x7000650094208310ull >> (4 * (4 * u + v))) & 15; }
+__device__ __forceinline__ int jac_tile_row(int t) { return (int)(0x1032210100ull >> (4 * t)) & 3; }
+__device__ __forceinline__ int jac_tile_col(int t) { return (int)(0x3333222110ull >> (4 * t)) & 3; }
 
 // first row of small block `sub` (0 .. 3: P0 P1 Q0 Q1) of the blocks p, q
 __device__ __forceinline__ int jac_row(int p, int q, int sub) { return (sub < 2 ? p : q) * kJacBig + (sub & 1) * kJacB; }
@@ -561,9 +565,9 @@ __device__ __forceinline__ void jac_gram_store(const typename mma_tile<T>::acc (
 // Partial Gram matrices of the 32-row blocks over one slice of the columns: part[slice][block][3][16][16].
 // grid (blocks, slices); four waves, each taking every fourth group of 16 columns (a lane reads four consecutive columns
 // of its row, which serve as four contraction steps of the fp64 MFMA for either operand).
-template <typename T>
-__global__ __launch_bounds__(256) void calib_jacobi_inside_gram_kernel(const T* __restrict__ G, int pitch, int slice_cols, T* __restrict__ part)
+__global__ __launch_bounds__(256) void calib_jacobi_inside_gram_kernel(const double* __restrict__ G, int pitch, int slice_cols, double* __restrict__ part)
 {
+    typedef double T;
     typedef typename mma_tile<T>::acc V4;
     __shared__ T red[3][kJacRec];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kg = lane >> 4;
@@ -817,44 +821,24 @@ __device__ __forceinline__ void jac_accumulate(const JacRounds<T>& L, T (&x)[kJa
     }
 }
 
-// First step of a sweep: the pairs of rows inside every 32-row block, 15 rounds inside its two small blocks (side by side, on
-// whole matrices in LDS) and the 16 rounds between them; workgroup (block, slice) applies the accumulated rotations to its
-// slice of the columns on the matrix cores.  Every slice repeats the small problem (the same numbers).
-// conv[block] keeps the largest |sin| of a rotation since the host cleared it (see jac_largest).
-constexpr int kJacInsideThreads = 4 * kWave;
+// The pairs of rows inside a 32-row block, by 256 threads (t): 15 rounds inside its two small blocks (side by side, on whole matrices
+// in LDS) and the 16 rounds between them.  In: the Gram matrix in the first of W.  Out: the accumulated rotations, pitch kJacLd, in turned(), behind
+// a barrier (W is free then).
+// conv: not null: keeps the largest |sin| of a rotation (see jac_largest).
+template <typename T> struct JacInside {
+    static constexpr int N = 2 * kJacB * kJacLd;
+    T W[2 * N], Q[2][N];   // Gram matrix (two of them) and accumulated rotations
+    __device__ T* turned() { return Q[(kJacB - 1) & 1]; }
+    T conv[sizeof(T) == 8 ? kJacB : 1];   // (in floats nobody asks whether the rows have converged)
+};
 template <typename T>
-__global__ __launch_bounds__(kJacInsideThreads) void calib_jacobi_inside_kernel(T* __restrict__ G, int pitch, int slice_cols,
-                                                                                const T* __restrict__ part, int n_part,
-                                                                                const double* __restrict__ lead_at, double* __restrict__ conv)
+__device__ __forceinline__ void jac_inside(JacInside<T>& sh, JacRounds<T>& rounds, int t256, double lead, double* __restrict__ conv)
 {
-    constexpr bool kConv = sizeof(T) == 8;   // (in floats nobody asks whether the rows have converged)
-    const double lead = kConv ? *lead_at : 0.0;
-    typedef typename mma_tile<T>::acc V4;
+    constexpr bool kConv = sizeof(T) == 8;
     constexpr int B2 = 2 * kJacB, LD = kJacLd;
-    __shared__ T Wb[2][B2 * LD], Qb[2][B2 * LD];   // Gram matrix and accumulated rotations
-    __shared__ JacRounds<T> s_rounds;
-    __shared__ T s_conv[kJacB];
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, kg = lane >> 4;
-    T* const gp = G + (size_t)blockIdx.x * kJacBig * pitch + blockIdx.y * slice_cols + l16;
-    const int i = tid >> 4, j = tid & 15;
-    {
-        T w8[3][8];
-#pragma unroll
-        for (int t = 0; t < 3; ++t)
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                w8[t][u] = part[((size_t)min(u, n_part - 1) * gridDim.x + blockIdx.x) * kJacRec + t * kJacTile + tid];
-#pragma unroll
-        for (int t = 0; t < 3; ++t) {
-            T v = 0;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v += u < n_part ? w8[t][u] : (T)0;
-            const int r = i + (t == 2 ? kJacB : 0), c = j + (t >= 1 ? kJacB : 0);
-            Wb[0][r * LD + c] = v;
-            if (t == 1) Wb[0][c * LD + r] = v;
-        }
-        for (int e = tid; e < B2 * B2; e += 256) Qb[0][(e >> 5) * LD + (e & 31)] = (e >> 5) == (e & 31) ? 1 : 0;
-    }
+    const int lane = t256 & 63, wave = __builtin_amdgcn_readfirstlane(t256 >> 6), l16 = lane & 15, kg = lane >> 4;
+    const int i = t256 >> 4, j = t256 & 15;
+    for (int e = t256; e < B2 * B2; e += 256) sh.Q[0][(e >> 5) * LD + (e & 31)] = (e >> 5) == (e & 31) ? 1 : 0;
     __syncthreads();
     int cur = 0;
     {
@@ -869,8 +853,8 @@ __global__ __launch_bounds__(kJacInsideThreads) void calib_jacobi_inside_kernel(
                 int pi, qi, pj, qj;
                 inside(t, i, &pi, &qi);
                 inside(t, j, &pj, &qj);
-                const T* W = Wb[cur]; const T* Q = Qb[cur];
-                T* Wn = Wb[cur ^ 1]; T* Qn = Qb[cur ^ 1];
+                const T* W = sh.W + cur * sh.N; const T* Q = sh.Q[cur];
+                T* Wn = sh.W + (cur ^ 1) * sh.N; T* Qn = sh.Q[cur ^ 1];
                 const T aa = W[pi * LD + pi], bb = W[qi * LD + qi];
                 const T b00 = W[pi * LD + pj], b01 = W[pi * LD + qj], b10 = W[qi * LD + pj], b11 = W[qi * LD + qj];
                 const T x0 = Q[pi * LD + j], y0 = Q[qi * LD + j], x1 = Q[pi * LD + j + kJacB], y1 = Q[qi * LD + j + kJacB];
@@ -890,34 +874,72 @@ __global__ __launch_bounds__(kJacInsideThreads) void calib_jacobi_inside_kernel(
             __syncthreads();
             cur ^= 1;
         }
-        if (kConv && j == 0) s_conv[i] = smax;
+        if (kConv && j == 0) sh.conv[i] = smax;
     }
-    T* const Qo = Qb[cur];
+    T* const Qo = sh.turned();   // (= Q[cur])
     if (wave < 2) {
-        const T* W = Wb[cur];
+        const T* W = sh.W + cur * sh.N;
         const JacPlace at = jac_place(wave);
         T b00 = W[at.i * LD + at.j], b11 = W[(kJacB + at.i) * LD + kJacB + at.j];
         T aa = W[at.i * (LD + 1)], bb = W[(kJacB + at.i) * (LD + 1)];
-        jac_solve<T>(s_rounds, at, b00, W[at.i * LD + kJacB + at.j], W[at.j * LD + kJacB + at.i], b11, aa, bb,
+        jac_solve<T>(rounds, at, b00, W[at.i * LD + kJacB + at.j], W[at.j * LD + kJacB + at.i], b11, aa, bb,
                   W[at.i * LD + kJacB + at.i]);
-        if (at.m == 1) { Wb[cur ^ 1][at.i * (LD + 1)] = aa; Wb[cur ^ 1][(kJacB + at.i) * (LD + 1)] = bb; }
+        if (at.m == 1) { T* const Wn = sh.W + (cur ^ 1) * sh.N; Wn[at.i * (LD + 1)] = aa; Wn[(kJacB + at.i) * (LD + 1)] = bb; }
     } else {
         T x[kJacNc], y[kJacNc];
         const int c0 = ((wave & 1) * 4 + kg) * kJacNc;
 #pragma unroll
         for (int e = 0; e < kJacNc; ++e) { x[e] = Qo[l16 * LD + c0 + e]; y[e] = Qo[(kJacB + l16) * LD + c0 + e]; }
-        jac_accumulate<T>(s_rounds, x, y);
+        jac_accumulate<T>(rounds, x, y);
 #pragma unroll
         for (int e = 0; e < kJacNc; ++e) { Qo[l16 * LD + c0 + e] = x[e]; Qo[(kJacB + l16) * LD + c0 + e] = y[e]; }
     }
     __syncthreads();
-    if constexpr (kConv) if (blockIdx.y == 0 && wave == 3) {
-        const double* W = Wb[cur ^ 1];
-        double smax = jac_largest(s_rounds, W, W + kJacB * (LD + 1), LD, lead);
+    if constexpr (kConv) if (conv && wave == 3) {
+        const double* W = sh.W + (cur ^ 1) * sh.N;
+        double smax = jac_largest(rounds, W, W + kJacB * (LD + 1), LD, lead);
 #pragma unroll
-        for (int k = 0; k < kJacB; ++k) smax = fmax(smax, s_conv[k]);
-        if (lane == 0 && smax > 0.0) conv_max(conv + blockIdx.x, smax);
+        for (int k = 0; k < kJacB; ++k) smax = fmax(smax, sh.conv[k]);
+        if (lane == 0 && smax > 0.0) conv_max(conv, smax);
     }
+}
+
+// First step of a sweep: the pairs of rows inside every 32-row block (jac_inside); workgroup (block, slice) applies the accumulated
+// rotations to its slice of the columns on the matrix cores.  Every slice repeats the small problem (the same numbers).
+// conv[block] keeps the largest |sin| of a rotation since the host cleared it.
+constexpr int kJacInsideThreads = 4 * kWave;
+__global__ __launch_bounds__(kJacInsideThreads) void calib_jacobi_inside_kernel(double* __restrict__ G, int pitch, int slice_cols,
+                                                                                const double* __restrict__ part, int n_part,
+                                                                                const double* __restrict__ lead_at, double* __restrict__ conv)
+{
+    typedef double T;
+    typedef typename mma_tile<T>::acc V4;
+    constexpr int LD = kJacLd;
+    __shared__ JacInside<T> sh;
+    __shared__ JacRounds<T> s_rounds;
+    const double lead = *lead_at;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, kg = lane >> 4;
+    T* const gp = G + (size_t)blockIdx.x * kJacBig * pitch + blockIdx.y * slice_cols + l16;
+    {
+        const int i = tid >> 4, j = tid & 15;
+        T w8[3][8];
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                w8[t][u] = part[((size_t)min(u, n_part - 1) * gridDim.x + blockIdx.x) * kJacRec + t * kJacTile + tid];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            T v = 0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v += u < n_part ? w8[t][u] : (T)0;
+            const int r = i + (t == 2 ? kJacB : 0), c = j + (t >= 1 ? kJacB : 0);
+            sh.W[r * LD + c] = v;
+            if (t == 1) sh.W[c * LD + r] = v;
+        }
+    }
+    jac_inside<T>(sh, s_rounds, tid, lead, blockIdx.y == 0 ? conv + blockIdx.x : nullptr);
+    const T* const Qo = sh.turned();
     auto row_of = [&](int s) { return 16 * (s >> 2) + mma_tile<T>::row(kg, s & 3); };   // of the block, in contraction step s
     T qa[2][8];  // the accumulated rotations as MFMA operand: rows m 16 .. +16, contraction step s
 #pragma unroll
@@ -949,7 +971,11 @@ __global__ __launch_bounds__(kJacInsideThreads) void calib_jacobi_inside_kernel(
 // the partial sums, 2.4 for the last products, 1.1 between the halves, the rest for the launch and the matrix's way back to memory.
 // A call at D = 1024, r = 640: 15.4 ms with 16-row blocks, 11.6 with these; at D = 4096 239 and 155.
 constexpr int kJacThreads = 8 * kWave;   // waves 0, 1 and 2, 3: the groups' rounds; 4, 5 and 6, 7: their accumulated rotations
-template <typename T>
+// INSIDE: the pairs inside the blocks first, in the same launch (rows in floats): group g's 256 threads rotate the pairs inside its block
+// (jac_inside), and the pair's Gram matrix W becomes J W J^T, so that one launch for Gram matrices and one passage of the rows less do: 30
+// us at D = 1024 behind 4 for the Gram matrices, in place of 4.6 + 17 + 4 + 15 us in two launches each.  A call at D = 1024, r = 640 2996 ->
+// 2936 us, 2048 14.49 -> 14.31 ms.
+template <typename T, bool INSIDE = false>
 __global__ __launch_bounds__(kJacThreads) void calib_jacobi_rotate_kernel(T* __restrict__ G, int D, int pitch, int step, int slice_cols,
                                                                           const T* __restrict__ part, int n_part,
                                                                           const double* __restrict__ lead_at, double* __restrict__ conv)
@@ -1011,14 +1037,62 @@ __global__ __launch_bounds__(kJacThreads) void calib_jacobi_rotate_kernel(T* __r
     auto tile_pp = [](int a) { return a ? kTile11 : kTile00; };
     auto tile_qq = [](int b) { return b ? kTile33 : kTile22; };
     auto tile_pq = [](int a, int b) { return (b ? kTile03 : kTile02) + a; };
-    // nothing to rotate (most pairs of the last sweeps): the rounds would leave everything as it is
+    T* Jin[2] = {nullptr, nullptr};   // INSIDE: rotations inside P and Q
+    if constexpr (INSIDE) {
+        __shared__ JacInside<T> s_in[2];
+        const int blk = tid >> 8;
+        {   // small blocks 2 blk and 2 blk + 1
+            const int r = (tid >> 4) & 15, c = l16;
+            T* const W = s_in[blk].W;
+            const T v01 = S[blk ? kTile23 : kTile01][r * LT + c];
+            W[r * LD + c] = S[blk ? kTile22 : kTile00][r * LT + c];
+            W[(kJacB + r) * LD + kJacB + c] = S[blk ? kTile33 : kTile11][r * LT + c];
+            W[r * LD + kJacB + c] = v01;
+            W[(kJacB + c) * LD + r] = v01;
+        }
+        jac_inside<T>(s_in[blk], s_rounds[blk], tid & 255, 0.0, nullptr);
+        Jin[0] = s_in[0].turned();
+        Jin[1] = s_in[1].turned();
+        // rows of J W where the blocks' Gram matrices were (of Q's rows the columns of Q only) ...
+        constexpr int LY = 2 * LD;
+        static_assert(LY >= 4 * kJacB, "64 columns");
+        auto rows_of = [&](int g, int m, int n) {
+            V4 acc = V4{0, 0, 0, 0};
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-        const int a = wave >> 2, r = (tid >> 4) & 15, c = l16;
-        if (jac_open(S[tile_pp(a)][r * (LT + 1)], S[tile_qq(b)][c * (LT + 1)], S[tile_pq(a, b)][r * LT + c])) s_any = 1;
+            for (int s = 0; s < 8; ++s) {
+                const int k = 4 * s + kg, u = 2 * g + (s >> 2), r = k & 15;
+                const int tile = u <= n ? jac_tile_of(u, n) : jac_tile_of(n, u);
+                acc = mma_step(Jin[g][(m * 16 + l16) * LD + k], S[tile][u <= n ? r * LT + l16 : l16 * LT + r], acc);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s_in[g].W[(m * 16 + mma_tile<T>::row(kg, e)) * LY + n * 16 + l16] = acc[e];
+        };
+        rows_of(0, wave >> 2, wave & 3);
+        if (wave < 4) rows_of(1, wave >> 1, 2 + (wave & 1));
+        __syncthreads();
+        // ... and times J^T
+        for (int tile = wave; tile < kJacTiles; tile += 8) {
+            const int u = jac_tile_row(tile), v = jac_tile_col(tile), g = v >> 1;
+            const T* const Y = s_in[u >> 1].W;
+            V4 acc = V4{0, 0, 0, 0};
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+                acc = mma_step(Y[((u & 1) * 16 + l16) * LY + g * 32 + 4 * s + kg], Jin[g][((v & 1) * 16 + l16) * LD + 4 * s + kg], acc);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) S[tile][mma_tile<T>::row(kg, e) * LT + l16] = acc[e];
+        }
+        __syncthreads();
     }
-    __syncthreads();
-    if (!s_any) return;  // uniform, and the same in every slice of the pair
+    // nothing to rotate (most pairs of the last sweeps): the rounds would leave everything as it is
+    if constexpr (!INSIDE) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int a = wave >> 2, r = (tid >> 4) & 15, c = l16;
+            if (jac_open(S[tile_pp(a)][r * (LT + 1)], S[tile_qq(b)][c * (LT + 1)], S[tile_pq(a, b)][r * LT + c])) s_any = 1;
+        }
+        __syncthreads();
+        if (!s_any) return;  // uniform, and the same in every slice of the pair
+    }
 
 #pragma unroll 1
     for (int h = 0; h < 2; ++h) {
@@ -1080,23 +1154,24 @@ __global__ __launch_bounds__(kJacThreads) void calib_jacobi_rotate_kernel(T* __r
     // row of small block u of the result: J[h][group] times the group's two small blocks (A, B), half after half
     for (int c = wave * 16; c < slice_cols; c += 8 * 16) {
         if (c != wave * 16) load_tile(c);
+        auto turn = [&](const T* Jt, T (&A)[4], T (&B)[4]) {
+            asm volatile("" ::: "memory");  // (the operands of all products at once do not fit into the registers)
+            V4 acc[2];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                acc[m] = V4{0, 0, 0, 0};
+#pragma unroll
+                for (int s = 0; s < 8; ++s)
+                    acc[m] = mma_step(Jt[(m * 16 + l16) * LD + 16 * (s >> 2) + mma_tile<T>::row(kg, s & 3)], s < 4 ? A[s & 3] : B[s & 3], acc[m]);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { A[e] = acc[0][e]; B[e] = acc[1][e]; }
+        };
+        if constexpr (INSIDE) { turn(Jin[0], x[0], x[1]); turn(Jin[1], x[2], x[3]); }
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                const int u = a, v = 2 + (h ? 1 - a : a);  // small blocks
-                asm volatile("" ::: "memory");  // (the operands of all four products at once do not fit into the registers)
-                V4 acc[2];
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    acc[m] = V4{0, 0, 0, 0};
-#pragma unroll
-                    for (int s = 0; s < 8; ++s)
-                        acc[m] = mma_step(J[h][a][(m * 16 + l16) * LD + 16 * (s >> 2) + mma_tile<T>::row(kg, s & 3)], s < 4 ? x[u][s & 3] : x[v][s & 3], acc[m]);
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) { x[u][e] = acc[0][e]; x[v][e] = acc[1][e]; }
-            }
+            for (int a = 0; a < 2; ++a) turn(J[h][a], x[a], x[2 + (h ? 1 - a : a)]);
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll

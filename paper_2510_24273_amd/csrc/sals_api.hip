@@ -2226,8 +2226,8 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                            part, n_part, lead, conv);
     };
     auto inside_step = [&]() {
-        hipLaunchKernelGGL((calib_jacobi_inside_gram_kernel<double>), dim3(n_blocks, n_part), dim3(256), 0, st, rows, D, D / n_part, part);
-        hipLaunchKernelGGL((calib_jacobi_inside_kernel<double>), dim3(n_blocks, slices), dim3(kJacInsideThreads), 0, st, rows, D, D / slices, part,
+        hipLaunchKernelGGL(calib_jacobi_inside_gram_kernel, dim3(n_blocks, n_part), dim3(256), 0, st, rows, D, D / n_part, part);
+        hipLaunchKernelGGL(calib_jacobi_inside_kernel, dim3(n_blocks, slices), dim3(kJacInsideThreads), 0, st, rows, D, D / slices, part,
                            n_part, lead, conv);
     };
     const dim3 tile_grid(D / 64, D / 64), sym_grid(n_tiles), prod(kProdThreads);
@@ -2278,10 +2278,11 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         float* const fpart = reinterpret_cast<float*>(part);
         int expo;
         std::frexp(std::sqrt(n0), &expo);   // (rows of the factor have norms of at most D^1/4 sqrt(n0))
-        auto near_step = [&](int step) {
+        auto near_step = [&](int step, auto inside) {
+            constexpr bool kInside = decltype(inside)::value;
             hipLaunchKernelGGL((calib_jacobi_gram_kernel<float>), dim3(n_pairs, n_part, 2), dim3(256), 0, st, cur, D, 2 * D, step, D / n_part, fpart);
-            hipLaunchKernelGGL((calib_jacobi_rotate_kernel<float>), dim3(n_pairs, slices), dim3(kJacThreads), 0, st, cur, D, 2 * D, step, 2 * D / slices, fpart,
-                               n_part, lead, conv);
+            hipLaunchKernelGGL((calib_jacobi_rotate_kernel<float, kInside>), dim3(n_pairs, slices), dim3(kJacThreads), 0, st, cur, D, 2 * D, step,
+                               2 * D / slices, fpart, n_part, lead, conv);
         };
         auto polish = [&]() {   // V <- (3 I - V V^T) V / 2, and G with it
             float* const O = reinterpret_cast<float*>(c0);
@@ -2342,11 +2343,8 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         int steps = 0;   // of the last polar factor
         bool polished = false, enough = false;
         for (;;) {
-            hipLaunchKernelGGL((calib_jacobi_inside_gram_kernel<float>), dim3(n_blocks, n_part), dim3(256), 0, st, cur, 2 * D, D / n_part, fpart);
-            hipLaunchKernelGGL((calib_jacobi_inside_kernel<float>), dim3(n_blocks, slices), dim3(kJacInsideThreads), 0, st, cur, 2 * D, 2 * D / slices, fpart, n_part,
-                               lead, conv);
-            near_step(kJacNearEven);
-            near_step(kJacNearOdd);
+            near_step(kJacNearEven, std::true_type{});
+            near_step(kJacNearOdd, std::false_type{});
             if (enough) break;
             hipLaunchKernelGGL(calib_float_norm_kernel, dim3(D / 4), dim3(256), 0, st, cur, D, norm);
             hipLaunchKernelGGL(calib_sort_kernel, dim3(D), dim3(kCalThreads), 0, st, reinterpret_cast<const double*>(cur), norm, D,

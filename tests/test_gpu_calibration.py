@@ -225,6 +225,32 @@ def test_the_way_in_floats_leaves_no_trace(D, r, kind):
     assert float((V @ C - L[:, None] * V).norm(dim=1).max()) <= (2e-11 + eps) * lam[0]
 
 
+@pytest.mark.parametrize("D,r,width", [(256, 256, 16), (512, 200, 32), (768, 768, 64), (768, 480, 96), (1024, 640, 128)])
+def test_coupled_groups_of_neighbouring_rows(D, r, width):
+    """Groups of `width` neighbouring channels that mix among themselves alone: rotations inside the small blocks of rows, inside blocks, inside
+    pairs of them and across pairs, which the launches that rotate single pairs deal with before any transformation of all rows."""
+    print(f"[case] groups of {width}, D={D} r={r}", flush=True)
+    rng = np.random.default_rng(D + width)
+    lam = np.linspace(2.0, 0.01, D)
+    C = np.zeros((D, D))
+    for a in range(0, D, width):
+        Q = np.linalg.qr(rng.standard_normal((width, width)))[0]
+        C[a:a + width, a:a + width] = (Q * lam[a:a + width]) @ Q.T
+    C = gu.to_dev(0.5 * (C + C.T)).contiguous()
+    rows = C.clone()
+    got, U, sweeps = binding.calib_eigenvectors(rows, r, torch.float32)
+    torch.cuda.synchronize()
+    assert 0 < sweeps <= 20
+    # (bounds as above)
+    eps = 4 * 60 * np.sqrt(D) * 2.0 ** -53
+    np.testing.assert_allclose(got.cpu().numpy()[:r], lam[:r], rtol=0, atol=eps * lam[0])
+    norm = rows.norm(dim=1)
+    lead = torch.argsort(-norm)[:r]
+    V = rows[lead] / norm[lead, None]
+    assert float((V @ V.T.contiguous() - torch.eye(r, device=gu.DEV, dtype=torch.float64)).abs().max()) <= 2e-11
+    assert float((V @ C - norm[lead, None] * V).norm(dim=1).max()) <= (2e-11 + eps) * lam[0]
+
+
 @pytest.mark.parametrize("D,r,turn", [(256, 160, 0.3), (512, 512, 0.3), (256, 256, 2.0), (768, 480, 2.0), (256, 100, 12.0), (1280, 64, 12.0)])
 def test_polar_factors_that_steer(D, r, turn):
     """Eigenvectors turned out of the axes by angles whose squares sum to turn^2: polar factors of one, two and more steps in floats, the
