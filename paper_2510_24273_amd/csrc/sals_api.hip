@@ -2342,10 +2342,9 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         double before = 1e300;
         int steps = 0;   // of the last polar factor
         bool polished = false, enough = false;
-        for (;;) {
+        do {
             near_step(kJacNearEven, std::true_type{});
             near_step(kJacNearOdd, std::false_type{});
-            if (enough) break;
             hipLaunchKernelGGL(calib_float_norm_kernel, dim3(D / 4), dim3(256), 0, st, cur, D, norm);
             hipLaunchKernelGGL(calib_sort_kernel, dim3(D), dim3(kCalThreads), 0, st, reinterpret_cast<const double*>(cur), norm, D,
                                reinterpret_cast<double*>(nxt), sorted);
@@ -2355,12 +2354,12 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             const bool plain = !polished;   // (large angles)
             if (plain) {
                 hipLaunchKernelGGL((calib_all_angles_kernel<bf16_t>), dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D, sorted,
-                                   r, row_off, kFloatOpen, reinterpret_cast<bf16_t*>(E), all_found);
+                                   r, row_off, kFloatOpen, kFloatDamp, reinterpret_cast<bf16_t*>(E), all_found);
                 hipLaunchKernelGGL((calib_polar_plain_kernel<0, true, kOutPlain, false>), tile_grid, prod, kPlainLds, st, reinterpret_cast<const bf16_t*>(E),
                                    reinterpret_cast<const bf16_t*>(E), D, 1.f, 0.f, 0.f, nullptr, 0.f, A, nullptr, square);
             } else {
                 hipLaunchKernelGGL((calib_all_angles_kernel<uint32_t>), dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D,
-                                   sorted, r, row_off, kFloatOpen, E, all_found);
+                                   sorted, r, row_off, kFloatOpen, kFloatDamp, E, all_found);
                 hipLaunchKernelGGL((calib_polar_kernel<0, true, false>), tile_grid, prod, kPairLds, st, E, E, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr, A,
                                    square);
             }
@@ -2389,7 +2388,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             enough = stuck || (now <= kFloatLast && polished);
             if ((now <= kFloatPolish || stuck) && !polished) { polish(); polished = true; }
             before = now;
-        }
+        } while (!enough);
         float* const O = reinterpret_cast<float*>(c0);
         hipLaunchKernelGGL(calib_polar_square_kernel, sym_grid, prod, kSymLds, st, cur + D, D, 2 * D, O);
         hipLaunchKernelGGL(calib_float_apply_kernel, tile_grid, prod, (prod_lds<float, float, true>()), st, O, cur + D, D, 2 * D, -0.5f, 1.5f, nxt, D);
@@ -2407,6 +2406,11 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     if (fresh) {   // (it takes the place of a sweep, and counts as one)
         rotated = true;
         done = 1;
+        // The pairs inside and next to blocks, which floats leave too far from orthogonal for the series half of the time.  (Once more in floats,
+        // the angles, and if they were too large a transformation: 5 % more at D = 1024, 2 at 256 and 512.)
+        inside_step();
+        block_step(kJacNearEven);
+        block_step(kJacNearOdd);
         find_lead(rows);
     }
     bool moved = false;    // `lead` is from before a transformation
@@ -2431,7 +2435,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             hipLaunchKernelGGL((calib_gram_kernel<double>), sym_grid, prod, kSymLds, st, rows, D, D, sorted, r,
                                reinterpret_cast<float*>(A), row_off);
             hipLaunchKernelGGL((calib_all_angles_kernel<uint32_t>), dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D, sorted, r, row_off,
-                               kAllOpen, E, all_found);
+                               kAllOpen, kAllDamp, E, all_found);
             hipLaunchKernelGGL((calib_polar_kernel<0, true, false>), tile_grid, prod, kPairLds, st, E, E, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr,
                                A, square);
             if (!read(h_found, all_found, (size_t)(n_angles + n_tiles) * 8) || !wait()) return SALS_ERR_HIP;
