@@ -651,15 +651,17 @@ __global__ __launch_bounds__(kProdThreads) void calib_polar_kernel(const uint32_
 }
 constexpr int kPolarFound = 4;   // a thread's tiles, of at most (kFloatMaxD / 64)^2
 static_assert((kFloatMaxD / 64) * (kFloatMaxD / 64) <= kPolarFound * kProdThreads, "every tile's sum is read");
-// The steps of a polar factor that only steers, in plain bf16 up to the last one: O = f A B^T (N == 0, symmetric), that and s S (N == 1), or
+// The steps of a polar factor that only steers, in plain bf16: O = d I + f A B^T (N == 0, symmetric), f A B^T + s S (N == 1), or
 // d I + s E + t A + f A E^T (N == 2, B = S = E, which is skew).  What is symmetric or skew is read and written by rows for columns, four
-// elements a lane; of what is neither, S and OT are the transposes.  Left as plain bf16, in pairs or in fp32.
+// elements a lane; of what is neither, S and OT are the transposes.  Left as plain bf16 or in fp32.
 //
 // Bound by what a compute unit draws, of which a pair's half is half: 7 us a product at D = 1024 where pairs take 12 to 15, a call 3300 -> 3110 us
-// (D = 2048 18.5 -> 15.4 ms).  Rounding X to 2^-9 turns the rows by 2^-9 of the angles that are taken out, while these are still large, and what it
-// takes from X's singular values is made good by the last step, in pairs: X X^T - I stays within 4e-3.  Not once V is polished: the last angles
-// are told in pairs.
-enum PolarOut { kOutPlain, kOutPairs, kOutFloat };
+// (D = 2048 18.5 -> 15.4 ms) with all steps but the last one so, and 2824 -> 2667 (13.4 -> 12.4) with that one too.  Rounding X to 2^-9 turns the
+// rows by 2^-9 of the angles that are taken out, while these are still large, and moves its singular values by 2e-3 (noise of 2^-9 / sqrt(3 D) an
+// element), which the last step, the one that leaves fp32, takes to the square of that.  The steps multiply with X X^T - I, whose rounding is a
+// small part of what is still to be made good; the diagonal of X X^T alone would be off by 4e-3.  X X^T - I stays within 4e-3.  Not once V is
+// polished: the last angles are told in pairs.
+enum PolarOut { kOutPlain, kOutFloat };
 //
 // FIND: the scalars of the first step (N == 2) from the sums of squares of A's tiles, as polar_plan has them, so that the step need not wait for the
 // host to learn them: that costs 12 us of an idle device each time.
@@ -703,12 +705,12 @@ __global__ __launch_bounds__(kProdThreads) void calib_polar_plain_kernel(const b
             const int i = i0 + e;
             const size_t at = (size_t)i * D + j;
             float o = f * v[e];
+            if (N == 0) o += i == j ? d : 0.f;
             if (N == 1) o = fmaf(s, bf16_to_f32(add.x[e]), o);
             if (N == 2) { o = fmaf(-s, bf16_to_f32(add.x[e]), o); o = fmaf(t, bf16_to_f32(sym.x[e]), o); o += i == j ? d : 0.f; }
             if (SQUARE) sum += (double)o * (double)o;
             out.x[e] = f32_to_bf16(o);
             if (OUT == kOutFloat) static_cast<float*>(O)[at] = o;
-            else if (OUT == kOutPairs) static_cast<uint32_t*>(O)[at] = pack_pair(o);
             else if (N > 0) static_cast<bf16_t*>(O)[at] = out.x[e];
         }
         if (OUT == kOutPlain) *reinterpret_cast<Four*>((N > 0 ? OT : static_cast<bf16_t*>(O)) + tr) = out;

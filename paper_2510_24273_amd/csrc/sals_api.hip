@@ -2125,10 +2125,9 @@ sals_status calib_all_lds(bool series)
                     allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<0, true, kOutPlain, false>), kPlainLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<0, false, kOutPlain, false>), kPlainLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<1, false, kOutPlain, false>), kPlainLds) &&
-                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<1, false, kOutPairs, false>), kPlainLds) &&
+                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<1, false, kOutFloat, false>), kPlainLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<2, false, kOutPlain, false>), kPlainLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<2, false, kOutPlain, true>), kPlainLds) &&
-                    allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<2, false, kOutPairs, false>), kPlainLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_plain_kernel<2, false, kOutFloat, false>), kPlainLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_square_kernel), kSymLds) &&
                     allow(reinterpret_cast<const void*>(calib_polar_last_kernel), nn) &&
@@ -2291,13 +2290,13 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                                nxt, 2 * D);
             std::swap(cur, nxt);
         };
-        // The polar factor in floats, X or X2, with all steps but the last one in plain bf16 (E and A are such matrices, in the lower half of
-        // the room of one in pairs).  Its first step and the square that the next one begins with can be launched before the plan is known; they are
-        // `ahead`, and made again if the plan turns out to have fewer than three steps.
+        // The polar factor in floats, X or X2, with all steps in plain bf16 (E and A are such matrices, in the lower half of the room of one in
+        // pairs).  Its first step and the square that the next one begins with can be launched before the plan is known; they are `ahead`, and made
+        // again if the plan turns out to have one step only.
         auto low = [](uint32_t* M) { return reinterpret_cast<bf16_t*>(M); };
         auto high = [&](uint32_t* M) { return reinterpret_cast<bf16_t*>(M) + (size_t)D * D; };
         auto plain_square = [&](uint32_t* X, uint32_t* A) {
-            hipLaunchKernelGGL((calib_polar_plain_kernel<0, false, kOutPlain, false>), tile_grid, prod, kPlainLds, st, low(X), low(X), D, 1.f, 0.f, 0.f, nullptr,
+            hipLaunchKernelGGL((calib_polar_plain_kernel<0, false, kOutPlain, false>), tile_grid, prod, kPlainLds, st, low(X), low(X), D, 1.f, -1.f, 0.f, nullptr,
                                0.f, high(A), nullptr, nullptr);
         };
         auto begin_plain = [&](uint32_t* E, uint32_t* A, uint32_t* X) {
@@ -2308,30 +2307,23 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         auto plain_factor = [&](const PolarPlan& P, bool ahead, uint32_t* E, uint32_t* A, uint32_t* X, uint32_t* X2) -> const float* {
             const int n = P.n + (P.one_more ? 1 : 0);
             const double w = 0.5 * P.a[0] * P.a[0] * P.a[0] / (P.top * P.top * P.top), c1 = 1.5 * P.a[0] / P.top - w;
-            ahead = ahead && n > 2;
+            ahead = ahead && n > 1;
             auto first = [&](auto out) {
                 hipLaunchKernelGGL((calib_polar_plain_kernel<2, false, (PolarOut)decltype(out)::value, false>), tile_grid, prod, kPlainLds, st, low(A), low(E),
                                    D, (float)(w * P.tau * P.tau * P.tau), (float)c1, (float)(c1 * P.tau), low(E), (float)(-w * P.tau * P.tau), X, high(X), nullptr);
             };
             if (n == 1) first(std::integral_constant<int, kOutFloat>{});
-            else if (n == 2) first(std::integral_constant<int, kOutPairs>{});
             else if (!ahead) first(std::integral_constant<int, kOutPlain>{});
             for (int k = 1; k < n; ++k) {
                 const double a = k < P.n ? P.a[k] : 1.0;
-                const float f = (float)(-0.5 * a * a * a), s = (float)(1.5 * a);
-                if (k == n - 1) {
-                    hipLaunchKernelGGL((calib_polar_kernel<0, false, false>), tile_grid, prod, kPairLds, st, X, X, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr, A,
-                                       nullptr);
-                    hipLaunchKernelGGL((calib_polar_kernel<1, false, true>), tile_grid, prod, kPairLds, st, A, X, D, f, 0.f, s, X, 0.f, nullptr, X2, nullptr);
-                } else {
-                    auto step = [&](auto out) {
-                        hipLaunchKernelGGL((calib_polar_plain_kernel<1, false, (PolarOut)decltype(out)::value, false>), tile_grid, prod, kPlainLds, st, high(A),
-                                           high(X), D, f, 0.f, s, high(X), 0.f, X2, high(X2), nullptr);
-                    };
-                    if (k > 1 || !ahead) plain_square(X, A);
-                    if (k == n - 2) step(std::integral_constant<int, kOutPairs>{});
-                    else step(std::integral_constant<int, kOutPlain>{});
-                }
+                const float f = (float)(-0.5 * a * a * a), s = (float)(1.5 * a - 0.5 * a * a * a);   // of (X X^T - I) X and X
+                auto step = [&](auto out) {
+                    hipLaunchKernelGGL((calib_polar_plain_kernel<1, false, (PolarOut)decltype(out)::value, false>), tile_grid, prod, kPlainLds, st, high(A),
+                                       high(X), D, f, 0.f, s, high(X), 0.f, X2, high(X2), nullptr);
+                };
+                if (k > 1 || !ahead) plain_square(X, A);
+                if (k == n - 1) step(std::integral_constant<int, kOutFloat>{});
+                else step(std::integral_constant<int, kOutPlain>{});
                 std::swap(X, X2);
             }
             return reinterpret_cast<const float*>(X);
@@ -2365,7 +2357,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             }
             const bool first = before == 1e300;
             if (!read(h_found, all_found, (size_t)(n_angles + n_tiles) * 8) || (first && !read(h_norm, sorted, (size_t)D * 8))) return SALS_ERR_HIP;
-            const bool ahead = plain && steps > 2;   // (not the first time, which may leave C as it is)
+            const bool ahead = plain && steps > 1;   // (not the first time, which may leave C as it is)
             if (ahead) {
                 if (hipEventRecord(copied.e, st) != hipSuccess) return SALS_ERR_HIP;
                 begin_plain(E, A, c0);
@@ -2407,7 +2399,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         rotated = true;
         done = 1;
         // The pairs inside and next to blocks, which floats leave too far from orthogonal for the series half of the time.  (Once more in floats,
-        // the angles, and if they were too large a transformation: 5 % more at D = 1024, 2 at 256 and 512.)
+        // the angles, and if they were too large a transformation: 4 % more at D = 256 and 1024, 2 at 512 and 768.)
         inside_step();
         block_step(kJacNearEven);
         block_step(kJacNearOdd);
