@@ -406,8 +406,9 @@ sals_status sals_overlap_score(sals_ctx* ctx, const void* q, const int32_t* q_po
  *              sums are spread over as much of the device as the scratch allows (D = 1024: 3.2 ms with the full size,
  *              10.2 with 8 D^2 + 4000 D bytes, 15.4 with the least)
  *   max_sweeps at least 1 (host): a sweep rotates every pair of rows once (transformations of all rows, which come
- *              between sweeps, are not counted; where they take the place of the first sweep they count as one); the call stops when no rotation that involves one of the r largest
- *              rows would turn by more than 1e-11 (found by a sweep, or from the Gram matrix of all rows behind a sweep
+ *              between sweeps, are not counted; where they take the place of the first sweep, which they do if the
+ *              limit is more than one, they count as one); the call stops when no rotation that involves one of the r
+ *              largest rows would turn by more than 1e-11 (found by a sweep, or from the Gram matrix of all rows behind a sweep
  *              of small rotations; with a workspace of the full size the last, smallest rotations are made all at
  *              once), or after max_sweeps
  *   sweeps     host int32, out (may be NULL): sweeps run; the negative of that number if the limit was reached

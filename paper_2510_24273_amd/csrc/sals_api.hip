@@ -2391,7 +2391,8 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         return SALS_OK;
     };
     bool settled = false, fresh = false;
-    if (all && D <= kFloatMaxD && !converged) {
+    // (A limit of one is that of one sweep in fp64: behind the floats, which would be all that it allows, some angles are always left.)
+    if (all && D <= kFloatMaxD && max_sweeps > 1 && !converged) {
         const sals_status s = float_rows(&fresh);
         if (s != SALS_OK) return s;
     }

@@ -566,6 +566,33 @@ def test_sweep_limit_is_reported():
     assert sweeps == -1
 
 
+@pytest.mark.parametrize("D,r,angle", [(256, 256, 0.1), (256, 85, 0.03), (512, 512, 0.01), (1024, 341, 0.03)])
+def test_one_sweep_is_enough_where_it_was(D, r, angle):
+    """Channels that mix in pairs far apart, by small angles: one sweep rotates them, so a limit of one sweep does."""
+    print(f"[case] limit of one sweep, D={D} r={r} turned by {angle:g}", flush=True)
+    rng = np.random.default_rng(D + r)
+    lam = np.linspace(2.0, 0.1, D)
+    turn = angle * rng.uniform(0.5, 1.0, D // 2) * rng.choice([-1, 1], D // 2)
+    i, j = np.arange(D // 2), np.arange(D // 2, D)
+    Q = np.zeros((D, D))
+    Q[i, i] = Q[j, j] = np.cos(turn)
+    Q[i, j], Q[j, i] = -np.sin(turn), np.sin(turn)
+    at = rng.permutation(D)
+    C = gu.to_dev((Q * lam[at]) @ Q.T).contiguous()
+    C = (0.5 * (C + C.T)).contiguous()
+    rows = C.clone()
+    got, U, sweeps = binding.calib_eigenvectors(rows, r, torch.float32, max_sweeps=1)
+    torch.cuda.synchronize()
+    assert sweeps == 1
+    # (bounds of one sweep's rotations, as for transformations above)
+    eps = 4 * 60 * np.sqrt(D) * 2.0 ** -53
+    np.testing.assert_allclose(got.cpu().numpy()[:r], lam[:r], rtol=0, atol=eps * lam[0])
+    norm = rows.norm(dim=1)
+    lead = torch.argsort(-norm)[:r]
+    V = rows[lead] / norm[lead, None]
+    assert float((V @ C - norm[lead, None] * V).norm(dim=1).max()) <= (2e-11 + eps) * lam[0]
+
+
 def test_whole_calibration_captures_the_energy_of_the_oracle_basis():
     print("[case] keys -> covariance -> eigenvectors", flush=True)
     D, r, n = 512, 128, 6000
