@@ -1,5 +1,5 @@
-// Calibration eigenvectors: the Newton-Schulz steps that take I + tau E, E skew, to its orthogonal polar factor (host code; the
-// products are in k_calib_all.hpp).
+// Calibration eigenvectors: the Newton-Schulz steps that take I + tau E, E skew, to its orthogonal polar factor, and when the way in
+// floats ends (host code; the products are in k_calib_all.hpp).
 //
 // A step takes every singular value x of X to 3/2 a x - 1/2 (a x)^3, with a^2 = 3 / (1 + l + l^2) for values between l and 1 (J. Chen,
 // E. Chow, "A stable scaling of Newton-Schulz for improving the sign function computation of a Hermitian matrix", 2014).  Those of I +
@@ -45,6 +45,34 @@ inline PolarPlan polar_plan(double a2, double near = kPolarNear)
         low = 0.5 * x * (3.0 - x * x);
     } while (low < near);
     return P;
+}
+
+// The way in floats has come to a stop once transformations no longer bring |E| below 0.97 of the least so far: four in a row, as the rows
+// of wide spectra pass a plateau of up to three (D = 2560, 10^(-12 c / D), r = D: 92, 81, 83, 83, 80, 74 ... 4), or one where V has been
+// polished: fp64 halves small angles and more.  A limit of 0.9 of the one before, and of 0.6 below |E| = 10, left spectra early whose angles fall
+// all the way, for fp64 to do the rest: calls in ms with sweeps first, with that limit and with this one, D = 2560 and r = D, 10^(-8 c / D)
+// 50.7 / 62.9 / 30.4, 10^(-12 c / D) 51.8 / 81.7 / 49.7; D = 1024 and r = D, 10^(-12 c / D) 5.47 / 6.78 / 3.83; D = 256, 10^(-6 c / D) 1.81 / 1.41 /
+// 1.10.  Three in a row: 10^(-13 c / D) at D = 2560 1.66 of the time with sweeps first, now 0.96.  Eigenvalues that repeat, where it does
+// stop: D = 1024, sixteenfold 8.98 / 6.43 / 6.74, two of them 15.9 / 11.4 / 7.27.
+struct FloatWay {
+    double best = 1e300;
+    int slow = 0;
+    bool stuck(double now, bool polished)   // behind every transformation, which started from |E| = now
+    {
+        slow = now < 0.97 * best ? 0 : slow + 1;
+        best = std::min(best, now);
+        return slow >= (polished ? 1 : 4);
+    }
+};
+
+// Rows whose angles the way in floats looks at: the r leading ones, but none of a norm below 4e-6 of the largest (norm: descending).  Their
+// products with leading rows are rounding in fp32, and those among themselves would keep it from its end: a covariance of 4/5 D tokens, D =
+// 512 and r = D, 4.16 ms with all rows, 2.61 so, 3.82 with sweeps first.  (1e-6: 2.43, but half of all eigenvalues zero, r = 5/8 D, 3.13 in
+// place of 2.77.)
+inline int float_lead(const double* norm, int r)
+{
+    while (r > 1 && norm[r - 1] < 4e-6 * norm[0]) --r;
+    return r;
 }
 
 }  // namespace sals

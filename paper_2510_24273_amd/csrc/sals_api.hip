@@ -2331,9 +2331,10 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         hipLaunchKernelGGL(calib_float_rows_kernel, dim3(D), dim3(kCalThreads), 0, st, rows, D, std::ldexp(1.0, -expo), cur);
         Event copied;
         if (hipEventCreateWithFlags(&copied.e, hipEventDisableTiming) != hipSuccess) return SALS_ERR_HIP;
-        double before = 1e300;
+        FloatWay way;
         int steps = 0;   // of the last polar factor
-        bool polished = false, enough = false;
+        bool first = true, polished = false, enough = false;
+        int n_lead = r;
         do {
             near_step(kJacNearEven, std::true_type{});
             near_step(kJacNearOdd, std::false_type{});
@@ -2342,20 +2343,19 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                                reinterpret_cast<double*>(nxt), sorted);
             std::swap(cur, nxt);
             uint32_t *const A = reinterpret_cast<uint32_t*>(nxt), *const E = A + (size_t)D * D;
-            hipLaunchKernelGGL((calib_gram_kernel<float>), sym_grid, prod, kSymLds, st, cur, D, 2 * D, sorted, r, reinterpret_cast<float*>(A), row_off);
+            hipLaunchKernelGGL((calib_gram_kernel<float>), sym_grid, prod, kSymLds, st, cur, D, 2 * D, sorted, n_lead, reinterpret_cast<float*>(A), row_off);
             const bool plain = !polished;   // (large angles)
             if (plain) {
                 hipLaunchKernelGGL((calib_all_angles_kernel<bf16_t>), dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D, sorted,
-                                   r, row_off, kFloatOpen, kFloatDamp, reinterpret_cast<bf16_t*>(E), all_found);
+                                   n_lead, row_off, kFloatOpen, kFloatDamp, reinterpret_cast<bf16_t*>(E), all_found);
                 hipLaunchKernelGGL((calib_polar_plain_kernel<0, true, kOutPlain, false>), tile_grid, prod, kPlainLds, st, reinterpret_cast<const bf16_t*>(E),
                                    reinterpret_cast<const bf16_t*>(E), D, 1.f, 0.f, 0.f, nullptr, 0.f, A, nullptr, square);
             } else {
                 hipLaunchKernelGGL((calib_all_angles_kernel<uint32_t>), dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D,
-                                   sorted, r, row_off, kFloatOpen, kFloatDamp, E, all_found);
+                                   sorted, n_lead, row_off, kFloatOpen, kFloatDamp, E, all_found);
                 hipLaunchKernelGGL((calib_polar_kernel<0, true, false>), tile_grid, prod, kPairLds, st, E, E, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr, A,
                                    square);
             }
-            const bool first = before == 1e300;
             if (!read(h_found, all_found, (size_t)(n_angles + n_tiles) * 8) || (first && !read(h_norm, sorted, (size_t)D * 8))) return SALS_ERR_HIP;
             const bool ahead = plain && steps > 1;   // (not the first time, which may leave C as it is)
             if (ahead) {
@@ -2371,15 +2371,16 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             const double now = std::sqrt(e2);
             const PolarPlan P = polar_plan(a2, now <= kFloatLast && polished ? kPolarNear : kFloatPolar);
             if (!std::isfinite(now) || P.n == 0 || (first && (now <= kFloatFirst || h_norm[D - 1] > kFloatSpread * h_norm[0]))) return SALS_OK;
+            if (first) n_lead = float_lead(h_norm, r);
             steps = P.n + (P.one_more ? 1 : 0);
             const float* const X = plain ? plain_factor(P, ahead, E, A, c0, c1) : polar_factor(P, E, A, A, c0, c1, false);
             hipLaunchKernelGGL(calib_float_apply_kernel, dim3(2 * D / 64, D / 64), prod, (prod_lds<float, float, true>()), st, X, cur, D, 2 * D, 1.f, 0.f, nxt,
                                2 * D);
             std::swap(cur, nxt);
-            const bool stuck = !(now < (now < 10.0 ? 0.6 : 0.9) * before);   // (few large angles are halved and more)
+            const bool stuck = way.stuck(now, polished);
+            first = false;
             enough = stuck || (now <= kFloatLast && polished);
             if ((now <= kFloatPolish || stuck) && !polished) { polish(); polished = true; }
-            before = now;
         } while (!enough);
         float* const O = reinterpret_cast<float*>(c0);
         hipLaunchKernelGGL(calib_polar_square_kernel, sym_grid, prod, kSymLds, st, cur + D, D, 2 * D, O);

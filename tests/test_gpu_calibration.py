@@ -566,6 +566,24 @@ def test_sweep_limit_is_reported():
     assert sweeps == -1
 
 
+@pytest.mark.parametrize("D,r,decades", [(512, 320, 12), (512, 512, 12), (1024, 1024, 12)])
+def test_wide_spectra_need_no_sweep_behind_the_floats(D, r, decades):
+    """Eigenvalues over twelve decades, whose angles fall slowly at first: the way in floats, which counts as one sweep, is gone to its end."""
+    print(f"[case] wide spectrum, D={D} r={r} {decades} decades", flush=True)
+    rng = np.random.default_rng(D + r)
+    lam = 10.0 ** (-decades * np.arange(1, D + 1) / D)
+    Q = torch.linalg.qr(torch.from_numpy(rng.standard_normal((D, D))).to(gu.DEV))[0]
+    C = (Q * gu.to_dev(lam)) @ Q.T.contiguous()
+    C = (0.5 * (C + C.T)).contiguous()
+    rows = C.clone()
+    got, U, sweeps = binding.calib_eigenvectors(rows, r, torch.float32)
+    torch.cuda.synchronize()
+    assert sweeps == 1
+    # (bounds as above)
+    eps = 4 * 60 * np.sqrt(D) * 2.0 ** -53
+    np.testing.assert_allclose(got.cpu().numpy()[:r], lam[:r], rtol=0, atol=eps * lam[0])
+
+
 @pytest.mark.parametrize("D,r,angle", [(256, 256, 0.1), (256, 85, 0.03), (512, 512, 0.01), (1024, 341, 0.03)])
 def test_one_sweep_is_enough_where_it_was(D, r, angle):
     """Channels that mix in pairs far apart, by small angles: one sweep rotates them, so a limit of one sweep does."""

@@ -1,5 +1,5 @@
 """The host's plan of the steps to an orthogonal polar factor (polar_plan.hpp): it ends for whatever sums the device returns, and the
-steps take every singular value to where the last one leaves X X^T - I as small as stated."""
+steps take every singular value to where the last one leaves X X^T - I as small as stated.  And the rule that ends the way in floats."""
 import os
 import subprocess
 
@@ -54,3 +54,72 @@ def test_every_plan_reaches_the_orthogonal_factor(plans):
         if one_more:
             x = 1.5 * x - 0.5 * x ** 3
         assert np.max(np.abs(x * x - 1.0)) <= 7e-6, (bound, P)
+
+
+LEAD = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+#include "polar_plan.hpp"
+// arguments: r, norms in descending order
+int main(int argc, char** argv)
+{
+    std::vector<double> norm;
+    for (int i = 2; i < argc; ++i) norm.push_back(std::strtod(argv[i], nullptr));
+    std::printf("%d\n", sals::float_lead(norm.data(), std::atoi(argv[1])));
+}
+"""
+
+
+@pytest.mark.parametrize("r,norms,lead", [(4, [2, 1, 1e-3, 1e-5], 4), (4, [2, 1, 1e-3, 7.9e-6], 3), (3, [2, 1, 1e-3, 1e-9], 3), (2, [1, 1e-9], 1),
+                                          (1, [0, 0], 1), (2, [0, 0], 2), (3, [1e150, 1e146, 1e144], 2)])
+def test_rows_that_floats_tell_apart(tmp_path, r, norms, lead):
+    (tmp_path / "lead.cpp").write_text(LEAD)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", build.CSRC, "-o", str(tmp_path / "lead"), str(tmp_path / "lead.cpp")], check=True)
+    assert int(subprocess.run([str(tmp_path / "lead"), str(r), *map(repr, norms)], check=True, capture_output=True, text=True, timeout=10).stdout) == lead
+
+
+WAY = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "polar_plan.hpp"
+// arguments: |E| of one transformation after the other, "p" once V has been polished; prints how many were made before it came to a stop
+int main(int argc, char** argv)
+{
+    sals::FloatWay way;
+    bool polished = false;
+    int n = 0;
+    for (int i = 1; i < argc; ++i) {
+        if (argv[i][0] == 'p') { polished = true; continue; }
+        ++n;
+        if (way.stuck(std::strtod(argv[i], nullptr), polished)) { std::printf("%d\n", n); return 0; }
+    }
+    std::printf("0\n");
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def stop(tmp_path_factory):
+    d = tmp_path_factory.mktemp("way")
+    (d / "way.cpp").write_text(WAY)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", build.CSRC, "-o", str(d / "way"), str(d / "way.cpp")], check=True)
+    return lambda norms: int(subprocess.run([str(d / "way"), *map(str, norms)], check=True, capture_output=True, text=True, timeout=10).stdout)
+
+
+@pytest.mark.parametrize("norms", [
+    [15.7, 10.8, 6.4, 3.8, 1.9, "p", 0.48, 0.006],                       # D = 256: a ratio of 0.6 below ten all the way
+    [14.8, 9.0, 5.6, 3.4, "p", 1.2, 0.1],
+    [121, 110, 101, 91, 81, 70, 58, 47, 34, 22, 13, 5.4, 1.2, "p", 0.12, 0.001],   # 1 / c^2, D = 2560: a slow beginning
+    [91.7, 81.1, 83.4, 82.6, 80.3, 73.8, 64, 50, 30, 10, 2, "p", 0.1]])  # twelve decades: a plateau
+def test_the_way_in_floats_goes_on_while_angles_fall(stop, norms):
+    assert stop(norms) == 0
+
+
+@pytest.mark.parametrize("norms,ends", [
+    ([103, 67.8, 44.7, 40.7, 66.9, 57, 64, 60, 62], 8),                  # eigenvalues that repeat
+    ([40, 20, 10, 20, 10, 20, 10, 20], 7),                               # up and down
+    ([30, 10, 3, "p", 1.5, 1.6, 0.1], 5),                                # the rest behind the polish is for fp64
+    ([5] * 9, 5)])
+def test_the_way_in_floats_ends(stop, norms, ends):
+    assert stop(norms) == ends
