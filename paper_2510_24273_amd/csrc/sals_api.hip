@@ -2268,10 +2268,10 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         hipLaunchKernelGGL((calib_apply_kernel<float, false>), tile_grid, prod, (prod_lds<float, double, true>()), st, X, from, nullptr, 1.0, between, D);
         hipLaunchKernelGGL((calib_apply_kernel<double, true>), tile_grid, prod, (prod_lds<double, double, true>()), st, C, between, between, 1.0, to, D);
     };
-    // The long way in floats: an orthogonal matrix times the factor into `rows`, nearly orthogonal rows mostly; *ok false: the factor is still
-    // there (and C, unless a transformation was begun, which takes rows that are not orthogonal).
-    auto float_rows = [&](bool* ok) -> sals_status {
-        *ok = false;
+    // The long way in floats: an orthogonal matrix times the factor into `rows`, nearly orthogonal rows mostly (*near: the last angles were
+    // small); *ok false: the factor is still there (and C, unless a transformation was begun, which takes rows that are not orthogonal).
+    auto float_rows = [&](bool* ok, bool* near) -> sals_status {
+        *ok = *near = false;
         float *cur = reinterpret_cast<float*>(at(off.Y0)), *nxt = reinterpret_cast<float*>(at(off.Y1));
         uint32_t *const c0 = reinterpret_cast<uint32_t*>(C), *const c1 = c0 + (size_t)D * D;
         float* const fpart = reinterpret_cast<float*>(part);
@@ -2379,7 +2379,8 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             std::swap(cur, nxt);
             const bool stuck = way.stuck(now, polished);
             first = false;
-            enough = stuck || (now <= kFloatLast && polished);
+            *near = now <= kFloatLast;
+            enough = stuck || (*near && polished);
             if ((now <= kFloatPolish || stuck) && !polished) { polish(); polished = true; }
         } while (!enough);
         float* const O = reinterpret_cast<float*>(c0);
@@ -2391,10 +2392,10 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         *ok = true;
         return SALS_OK;
     };
-    bool settled = false, fresh = false;
+    bool settled = false, fresh = false, near = false;
     // (A limit of one is that of one sweep in fp64: behind the floats, which would be all that it allows, some angles are always left.)
     if (all && D <= kFloatMaxD && max_sweeps > 1 && !converged) {
-        const sals_status s = float_rows(&fresh);
+        const sals_status s = float_rows(&fresh, &near);
         if (s != SALS_OK) return s;
     }
     if (fresh) {   // (it takes the place of a sweep, and counts as one)
@@ -2416,8 +2417,9 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         if (fresh) {   // behind the floats: their rest is mostly for the series
             worst = 0.1;
             fresh = false;
-        } else if (all && !settled && done >= all_first(D) && last > 0.0) {
-            // One transformation of all rows.
+        } else if (all && !settled && (near || done >= all_first(D)) && last > 0.0) {
+            // One transformation of all rows; at any D where floats left small angles, but too large ones for the series (D = 2304, keys, r =
+            // 5/8 D 23.2 ms with a sweep there, 21.2 so; from |E| = 100 on, 1 / c^2 at D = 2560 55.1 with transformations, 50.2 with sweeps)
             moved = true;
             inside_step();
             block_step(kJacNearEven);

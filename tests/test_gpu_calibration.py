@@ -566,9 +566,10 @@ def test_sweep_limit_is_reported():
     assert sweeps == -1
 
 
-@pytest.mark.parametrize("D,r,decades", [(512, 320, 12), (512, 512, 12), (1024, 1024, 12)])
+@pytest.mark.parametrize("D,r,decades", [(512, 320, 12), (512, 512, 12), (1024, 1024, 12), (2304, 1408, 8), (2560, 1600, 12)])
 def test_wide_spectra_need_no_sweep_behind_the_floats(D, r, decades):
-    """Eigenvalues over twelve decades, whose angles fall slowly at first: the way in floats, which counts as one sweep, is gone to its end."""
+    """Eigenvalues over many decades, whose angles fall slowly at first: the way in floats, which counts as one sweep, is gone to its end, and what
+    it leaves is for transformations at any width."""
     print(f"[case] wide spectrum, D={D} r={r} {decades} decades", flush=True)
     rng = np.random.default_rng(D + r)
     lam = 10.0 ** (-decades * np.arange(1, D + 1) / D)
