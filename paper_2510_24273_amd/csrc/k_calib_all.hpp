@@ -569,18 +569,20 @@ __global__ __launch_bounds__(kProdThreads) void calib_gram_kernel(const T* __res
         off[(size_t)(tile.col + tile.row) * D + j0 + c] = (s_off[1][0][c] + s_off[1][1][c]) + (s_off[1][2][c] + s_off[1][3][c]);
     }
 }
-// ... then E (pairs of bf16, or plain bf16), kAngleRows rows x 256 columns a workgroup, and per workgroup the sum of squares of ab / h over the pairs with
-// a leading row.  (8.9 us at D = 1024; 26.5 with 256 columns
-// after the other in a workgroup.)
+// ... then E (pairs of bf16, or plain bf16), kAngleRows rows x 256 columns a workgroup, and per workgroup the sum of squares of ab / h over
+// the pairs with a leading row; COUNT: also how many these are, behind all sums.  (8.9 us at D = 1024; 26.5 with 256 columns after the
+// other in a workgroup.)
 constexpr int kAngleRows = 8;
-template <typename TE>
+template <typename TE, bool COUNT = false>
 __global__ __launch_bounds__(256) void calib_all_angles_kernel(const float* __restrict__ W, int D, const double* __restrict__ norm, int r,
                                                                const float* __restrict__ off, double open, double damp, TE* __restrict__ E,
                                                                double* __restrict__ found)
 {
     static_assert(kAngleRows == 8 && kCalThreads == 256, "32 lanes a row; D is a multiple of the columns");
     __shared__ double s_sum[4];
+    __shared__ int s_open[4];
     __shared__ float s_off[kAngleRows];
+    int n_open = 0;   // of this wave
     const double unit = all_scale(norm), n_r = norm[r - 1] * unit, lead = 0.999 * n_r * n_r, least = kAllTail * lead;
     const int tid = threadIdx.x, i0 = blockIdx.x * kAngleRows, j = blockIdx.y * 256 + tid, nb = D / 64;
     float w[kAngleRows];
@@ -606,13 +608,18 @@ __global__ __launch_bounds__(256) void calib_all_angles_kernel(const float* __re
         const double s = counts ? ab * rsqrt_f64(fma(damp * o, o, p.h2)) : 0.0;
         const float e = (float)(p.d < 0.0 || (p.d == 0.0 && i > j) ? s : -s);
         E[(size_t)i * D + j] = sizeof(TE) == 2 ? (TE)f32_to_bf16(e) : (TE)pack_pair(e);
-        if (counts && i < j && fmax(ni, nj) * fmax(ni, nj) >= lead) sum += ab * ab / p.h2;
+        const bool leads = counts && i < j && fmax(ni, nj) * fmax(ni, nj) >= lead;
+        if (leads) sum += ab * ab / p.h2;
+        if (COUNT) n_open += __popcll(__ballot(leads));
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, kWave);
-    if ((tid & 63) == 0) s_sum[tid >> 6] = sum;
+    if ((tid & 63) == 0) { s_sum[tid >> 6] = sum; if (COUNT) s_open[tid >> 6] = n_open; }
     __syncthreads();
-    if (tid == 0) found[blockIdx.y * gridDim.x + blockIdx.x] = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
+    if (tid != 0) return;
+    double* const mine_found = found + blockIdx.y * gridDim.x + blockIdx.x;
+    *mine_found = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
+    if (COUNT) mine_found[gridDim.x * gridDim.y] = (s_open[0] + s_open[1]) + (s_open[2] + s_open[3]);
 }
 
 // ---- Polar factor -----------------------------------------------------------------------------------------------------

@@ -65,6 +65,18 @@ struct FloatWay {
     }
 };
 
+// The way in floats is not begun where the rows of the factor are nearly orthogonal as they are, or of nearly equal norms (kFloatSpread of each
+// other): eigenvalues that close are told apart in fp64 only, and the polar factors' rounding would mix them (eigenvalues within 1e-3: 6.3
+// ms, and 4.8).  Nor where fewer pairs of rows than there are rows have an angle: a sweep passes over almost all pairs of blocks then, and turns
+// those (D / 2 planes of two channels turned by 0.1: D = 256 0.37 ms with a sweep, 0.55 with floats, 2048 3.5 and 5.2, 2560 7.0 and 9.8; a
+// covariance of tokens has them all).
+// now: |E| behind the steps next to blocks; open: its angles, counted; norm: of the rows, descending
+constexpr double kFloatFirst = 0.1, kFloatSpread = 0.9;
+inline bool float_begins(double now, double open, const double* norm, int D)
+{
+    return now > kFloatFirst && norm[D - 1] <= kFloatSpread * norm[0] && open >= D;
+}
+
 // Rows whose angles the way in floats looks at: the r leading ones, but none of a norm below 4e-6 of the largest (norm: descending).  Their
 // products with leading rows are rounding in fp32, and those among themselves would keep it from its end: a covariance of 4/5 D tokens, D =
 // 512 and r = D, 4.16 ms with all rows, 2.61 so, 3.82 with sweeps first.  (1e-6: 2.43, but half of all eigenvalues zero, r = 5/8 D, 3.13 in

@@ -2096,9 +2096,7 @@ inline int all_first(int D) { return D <= 2048 ? 1 : D < 3072 ? 3 : 4; }
 // 2048 21.2 / 18.3, 2560 44.4 / 39.4, 3072 66.3 / 65.9, 3584 99.2 / 100.8; D = 1024 with spectra c^-2 5.5 / 4.0, 10^(-6 c / D) 5.1 / 4.1,
 // sixteenfold eigenvalues 9.6 / 8.2.  kFloatLast 0.3 and 0.03: 3.53 and 3.66 at D = 1024; kFloatPolish 1.5 and 6: 3.68 and 3.43, but 4.24 against
 // 4.01 with a spectrum c^-2; steps next to blocks twice: 3.72.
-// Not begun where the rows of the factor are nearly orthogonal as they are, or of nearly equal norms (kFloatSpread of each other): eigenvalues
-// that close are told apart in fp64 only, and the polar factors' rounding would mix them (eigenvalues within 1e-3: 6.3 ms, and 4.8).
-constexpr double kFloatFirst = 0.1, kFloatSpread = 0.9, kFloatLast = 0.1, kFloatPolish = 3.5;
+constexpr double kFloatLast = 0.1, kFloatPolish = 3.5;
 // the series of the exponential: cut behind E^4 it differs from an orthogonal matrix by |E|^6 / 72
 constexpr double kSeriesNorm = 4e-3;
 // the product kernels' dynamic LDS, beyond the default limit
@@ -2166,8 +2164,8 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     const int n_tiles = (D / 64) * (D / 64);   // of the angles, whose results lie where the partial Gram matrices do
     f64x2* const found = reinterpret_cast<f64x2*>(part);
     const int n_angles = D / kAngleRows * (D / 256);
-    double *const all_found = part, *const square = part + n_angles;
-    float* const row_off = reinterpret_cast<float*>(square + n_tiles);
+    double *const square = part, *const all_found = square + n_tiles;   // (read with one copy, squares first)
+    float* const row_off = reinterpret_cast<float*>(all_found + 2 * n_angles);
     double *rows = G, *other = at(off.Y0), *third = at(off.Y1);   // the rows, and room for two more matrices (`series`)
     double* const sorted = diag;                                  // (the factored blocks are in place by then)
     const bool all = series && D <= kAllMaxD;
@@ -2193,7 +2191,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     row_norms(C);
     hipLaunchKernelGGL(calib_scale_kernel, dim3(1), dim3(kCalThreads), 0, st, norm, D, scale);
     const bool begun = factor(1.0);
-    PinnedLease host((size_t)n_blocks + D + std::max(2 * n_tiles, n_angles + n_tiles));
+    PinnedLease host((size_t)n_blocks + D + 2 * n_angles + n_tiles);
     if (!host.p) return SALS_ERR_HIP;
     if (!begun || calib_all_lds(series) != SALS_OK) return SALS_ERR_HIP;
     double *const h_conv = host.p, *const h_norm = h_conv + n_blocks, *const h_found = h_norm + D;
@@ -2346,8 +2344,9 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             hipLaunchKernelGGL((calib_gram_kernel<float>), sym_grid, prod, kSymLds, st, cur, D, 2 * D, sorted, n_lead, reinterpret_cast<float*>(A), row_off);
             const bool plain = !polished;   // (large angles)
             if (plain) {
-                hipLaunchKernelGGL((calib_all_angles_kernel<bf16_t>), dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D, sorted,
-                                   n_lead, row_off, kFloatOpen, kFloatDamp, reinterpret_cast<bf16_t*>(E), all_found);
+                auto angles = first ? calib_all_angles_kernel<bf16_t, true> : calib_all_angles_kernel<bf16_t, false>;
+                hipLaunchKernelGGL(angles, dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D, sorted, n_lead, row_off,
+                                   kFloatOpen, kFloatDamp, reinterpret_cast<bf16_t*>(E), all_found);
                 hipLaunchKernelGGL((calib_polar_plain_kernel<0, true, kOutPlain, false>), tile_grid, prod, kPlainLds, st, reinterpret_cast<const bf16_t*>(E),
                                    reinterpret_cast<const bf16_t*>(E), D, 1.f, 0.f, 0.f, nullptr, 0.f, A, nullptr, square);
             } else {
@@ -2356,7 +2355,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                 hipLaunchKernelGGL((calib_polar_kernel<0, true, false>), tile_grid, prod, kPairLds, st, E, E, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr, A,
                                    square);
             }
-            if (!read(h_found, all_found, (size_t)(n_angles + n_tiles) * 8) || (first && !read(h_norm, sorted, (size_t)D * 8))) return SALS_ERR_HIP;
+            if (!read(h_found, square, (size_t)(n_tiles + (first ? 2 : 1) * n_angles) * 8) || (first && !read(h_norm, sorted, (size_t)D * 8))) return SALS_ERR_HIP;
             const bool ahead = plain && steps > 1;   // (not the first time, which may leave C as it is)
             if (ahead) {
                 if (hipEventRecord(copied.e, st) != hipSuccess) return SALS_ERR_HIP;
@@ -2366,12 +2365,17 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                 return SALS_ERR_HIP;
             }
             double e2 = 0.0, a2 = 0.0;
-            for (int i = 0; i < n_angles; ++i) e2 += h_found[i];
-            for (int i = 0; i < n_tiles; ++i) a2 += h_found[n_angles + i];
+            for (int i = 0; i < n_tiles; ++i) a2 += h_found[i];
+            for (int i = 0; i < n_angles; ++i) e2 += h_found[n_tiles + i];
             const double now = std::sqrt(e2);
             const PolarPlan P = polar_plan(a2, now <= kFloatLast && polished ? kPolarNear : kFloatPolar);
-            if (!std::isfinite(now) || P.n == 0 || (first && (now <= kFloatFirst || h_norm[D - 1] > kFloatSpread * h_norm[0]))) return SALS_OK;
-            if (first) n_lead = float_lead(h_norm, r);
+            if (!std::isfinite(now) || P.n == 0) return SALS_OK;
+            if (first) {
+                double open = 0.0;
+                for (int i = 0; i < n_angles; ++i) open += h_found[n_tiles + n_angles + i];
+                if (!float_begins(now, open, h_norm, D)) return SALS_OK;
+                n_lead = float_lead(h_norm, r);
+            }
             steps = P.n + (P.one_more ? 1 : 0);
             const float* const X = plain ? plain_factor(P, ahead, E, A, c0, c1) : polar_factor(P, E, A, A, c0, c1, false);
             hipLaunchKernelGGL(calib_float_apply_kernel, dim3(2 * D / 64, D / 64), prod, (prod_lds<float, float, true>()), st, X, cur, D, 2 * D, 1.f, 0.f, nxt,
@@ -2434,10 +2438,10 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                                kAllOpen, kAllDamp, E, all_found);
             hipLaunchKernelGGL((calib_polar_kernel<0, true, false>), tile_grid, prod, kPairLds, st, E, E, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr,
                                A, square);
-            if (!read(h_found, all_found, (size_t)(n_angles + n_tiles) * 8) || !wait()) return SALS_ERR_HIP;
+            if (!read(h_found, square, (size_t)(n_tiles + n_angles) * 8) || !wait()) return SALS_ERR_HIP;
             double e2 = 0.0, a2 = 0.0;
-            for (int i = 0; i < n_angles; ++i) e2 += h_found[i];
-            for (int i = 0; i < n_tiles; ++i) a2 += h_found[n_angles + i];
+            for (int i = 0; i < n_tiles; ++i) a2 += h_found[i];
+            for (int i = 0; i < n_angles; ++i) e2 += h_found[n_tiles + i];
             // (a matrix on which the transformations gain little, as with eigenvalues that repeat or rows of very different norms
             // in no order, gets a sweep in between)
             const double now = std::sqrt(e2);

@@ -79,6 +79,37 @@ def test_rows_that_floats_tell_apart(tmp_path, r, norms, lead):
     assert int(subprocess.run([str(tmp_path / "lead"), str(r), *map(repr, norms)], check=True, capture_output=True, text=True, timeout=10).stdout) == lead
 
 
+BEGIN = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+#include "polar_plan.hpp"
+// arguments: |E|, number of angles, norms in descending order
+int main(int argc, char** argv)
+{
+    std::vector<double> norm;
+    for (int i = 3; i < argc; ++i) norm.push_back(std::strtod(argv[i], nullptr));
+    std::printf("%d\n", (int)sals::float_begins(std::strtod(argv[1], nullptr), std::strtod(argv[2], nullptr), norm.data(), (int)norm.size()));
+}
+"""
+
+
+def test_where_the_way_in_floats_begins(tmp_path):
+    """Not from rows that are nearly orthogonal, not among nearly equal norms, not for a handful of angles."""
+    (tmp_path / "begin.cpp").write_text(BEGIN)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", build.CSRC, "-o", str(tmp_path / "begin"), str(tmp_path / "begin.cpp")], check=True)
+
+    def begins(now, angles, norms):
+        return subprocess.run([str(tmp_path / "begin"), repr(now), repr(angles), *map(repr, norms)], check=True, capture_output=True, text=True,
+                              timeout=10).stdout.strip() == "1"
+    norms = [1.0, 0.8, 0.3, 0.1]
+    assert begins(2.0, 6, norms) and begins(2.0, 4, norms)
+    assert not begins(2.0, 3, norms)                        # fewer angles than rows
+    assert not begins(0.1, 6, norms)
+    assert not begins(2.0, 6, [1.0, 0.99, 0.95, 0.91]) and begins(2.0, 6, [1.0, 0.99, 0.95, 0.9])
+    assert not begins(2.0, 6, [1.0, 0.8, 0.3, float("nan")])
+
+
 WAY = r"""
 #include <cstdio>
 #include <cstdlib>
