@@ -14,7 +14,8 @@
 // The polar factor is found by Newton-Schulz steps in pairs of bf16, the last one in fp32 (X <- a X - b (X X^T) X, scaled by the
 // bounds of its singular values: J. Chen, E. Chow, "A stable scaling of Newton-Schulz for improving the sign function computation of
 // a Hermitian matrix", 2014), and only *found* there: what is left, delta = X X^T - I (at most 1e-5: 6.7e-6 where the last step begins
-// with the smallest singular values it may, and the rounding of fp32; measured 5e-7 to 4e-6), is formed in fp64 and taken out to third
+// with the smallest singular values it may, and the rounding of fp32; measured 5e-7 to 4e-6; the product of many factors that floats go
+// by is brought there by as many steps in fp32 as its bound asks for, see FloatDefect), is formed in fp64 and taken out to third
 // order, G <- (I - delta / 2 + 3/8 delta^2) X G, with fp64 products.  The next term, 5/16 delta^3, is below 4e-16, so what a
 // transformation does to G is orthogonal to the rounding of those products (G^T G changed by 2e-15 to 3e-15 of its norm, D = 256 to 1024),
 // and which transformation is made decides nothing but how fast the rows converge.  (D = 1024, r = 640: eigenvalues off by 1.2e-14 of

@@ -2281,12 +2281,14 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             hipLaunchKernelGGL((calib_jacobi_rotate_kernel<float, kInside>), dim3(n_pairs, slices), dim3(kJacThreads), 0, st, cur, D, 2 * D, step,
                                2 * D / slices, fpart, n_part, lead, conv);
         };
+        FloatDefect defect;
         auto polish = [&]() {   // V <- (3 I - V V^T) V / 2, and G with it
             float* const O = reinterpret_cast<float*>(c0);
             hipLaunchKernelGGL(calib_polar_square_kernel, sym_grid, prod, kSymLds, st, cur + D, D, 2 * D, O);
             hipLaunchKernelGGL(calib_float_apply_kernel, dim3(2 * D / 64, D / 64), prod, (prod_lds<float, float, true>()), st, O, cur, D, 2 * D, -0.5f, 1.5f,
                                nxt, 2 * D);
             std::swap(cur, nxt);
+            defect.polish();
         };
         // The polar factor in floats, X or X2, with all steps in plain bf16 (E and A are such matrices, in the lower half of the room of one in
         // pairs).  Its first step and the square that the next one begins with can be launched before the plan is known; they are `ahead`, and made
@@ -2381,12 +2383,14 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             hipLaunchKernelGGL(calib_float_apply_kernel, dim3(2 * D / 64, D / 64), prod, (prod_lds<float, float, true>()), st, X, cur, D, 2 * D, 1.f, 0.f, nxt,
                                2 * D);
             std::swap(cur, nxt);
+            defect.factor(P, plain);
             const bool stuck = way.stuck(now, polished);
             first = false;
             *near = now <= kFloatLast;
             enough = stuck || (*near && polished);
             if ((now <= kFloatPolish || stuck) && !polished) { polish(); polished = true; }
         } while (!enough);
+        for (int k = 0; k < 8 && !defect.correctable(); ++k) polish();   // (mostly none)
         float* const O = reinterpret_cast<float*>(c0);
         hipLaunchKernelGGL(calib_polar_square_kernel, sym_grid, prod, kSymLds, st, cur + D, D, 2 * D, O);
         hipLaunchKernelGGL(calib_float_apply_kernel, tile_grid, prod, (prod_lds<float, float, true>()), st, O, cur + D, D, 2 * D, -0.5f, 1.5f, nxt, D);

@@ -12,10 +12,13 @@ PROGRAM = r"""
 #include <cstdio>
 #include <cstdlib>
 #include "polar_plan.hpp"
+#ifndef NEAR
+#define NEAR sals::kPolarNear
+#endif
 int main(int argc, char** argv)
 {
     for (int i = 1; i < argc; ++i) {
-        const sals::PolarPlan P = sals::polar_plan(std::strtod(argv[i], nullptr));
+        const sals::PolarPlan P = sals::polar_plan(std::strtod(argv[i], nullptr), NEAR);
         std::printf("%d %d %.17g %.17g", P.n, (int)P.one_more, P.tau, P.top);
         for (int k = 0; k < P.n; ++k) std::printf(" %.17g", P.a[k]);
         std::printf("\n");
@@ -54,6 +57,70 @@ def test_every_plan_reaches_the_orthogonal_factor(plans):
         if one_more:
             x = 1.5 * x - 0.5 * x ** 3
         assert np.max(np.abs(x * x - 1.0)) <= 7e-6, (bound, P)
+
+
+DEFECT = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "polar_plan.hpp"
+// arguments: bounds of |E|, one factor each ("p": a step in fp32 behind it); prints what their plans leave, and the bound of them all and whether it can
+// be corrected, then the same behind one more step
+int main(int argc, char** argv)
+{
+    sals::FloatDefect d;
+    bool plain = true;
+    for (int i = 1; i < argc; ++i) {
+        if (argv[i][0] == 'p') { d.polish(); plain = false; continue; }
+        const double b = std::strtod(argv[i], nullptr);
+        const sals::PolarPlan P = sals::polar_plan(b * b * b * b, sals::kFloatPolar);
+        std::printf("%.17g ", P.left);
+        d.factor(P, plain);
+    }
+    std::printf("%.17g %d ", d.u, (int)d.correctable());
+    d.polish();
+    std::printf("%.17g %d\n", d.u, (int)d.correctable());
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def defect(tmp_path_factory):
+    d = tmp_path_factory.mktemp("defect")
+    (d / "defect.cpp").write_text(DEFECT)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", build.CSRC, "-o", str(d / "defect"), str(d / "defect.cpp")], check=True)
+    return lambda *a: [float(x) for x in subprocess.run([str(d / "defect"), *map(str, a)], check=True, capture_output=True, text=True,
+                                                        timeout=10).stdout.split()]
+
+
+def test_plans_of_the_way_in_floats_leave_what_they_say(tmp_path, defect):
+    """The plans that steer: singular values of every size end within the stated bound of one, at most 3/4 (1 - 0.97^2)^2 and its cube."""
+    (tmp_path / "plan.cpp").write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-DNEAR=sals::kFloatPolar", "-I", build.CSRC, "-o", str(tmp_path / "plan"), str(tmp_path / "plan.cpp")],
+                   check=True)
+    worst = 0.0
+    for bound in np.concatenate([np.geomspace(1e-6, 50.0, 200), np.linspace(0.1, 6.1, 200)]):
+        out = subprocess.run([str(tmp_path / "plan"), repr(float(bound) ** 4)], check=True, capture_output=True, text=True, timeout=10).stdout.split()
+        n, one_more, tau, top, a = int(out[0]), out[1] == "1", float(out[2]), float(out[3]), [float(x) for x in out[4:]]
+        assert 1 <= n <= 6
+        x = np.sqrt(1.0 + np.linspace(0.0, tau * bound, 1001) ** 2) / top
+        for s in a + [1.0] * one_more:
+            x = 1.5 * s * x - 0.5 * (s * x) ** 3
+        left = defect(float(bound))[0]
+        assert np.max(np.abs(x * x - 1.0)) <= left * (1 + 1e-9) + 1e-15, bound
+        worst = max(worst, left)
+    u = 1 - 0.97 ** 2
+    assert 1e-3 < worst <= 0.75 * u * u + 0.25 * u ** 3
+
+
+def test_what_adds_up_in_floats_is_taken_out_before_the_correction(defect):
+    near_one = 2.263                                  # (a plan that leaves about as much as any)
+    one = defect(near_one)
+    assert one[0] > 1.5e-3 and one[-3] == 1.0         # a single factor can be corrected behind one step in fp32
+    *_, u, fine, u1, fine1 = defect("p", near_one, near_one, near_one)
+    assert u >= 3 * one[0] and fine == 0.0            # three that line up cannot
+    assert u1 <= 0.8 * u * u + 3e-6 and fine1 == 1.0
+    *_, u, fine, u1, fine1 = defect(*[near_one] * 40)  # a long way
+    assert u >= 40 * one[0] and fine == 0.0 and u1 < 0.2 * u
 
 
 LEAD = r"""
