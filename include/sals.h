@@ -19,6 +19,8 @@
  *   workspace and the packed weights.  The library never allocates or frees
  *   device memory and keeps no device pointer beyond a call, except the workspace
  *   handed to sals_create, which must stay valid until sals_destroy.
+ *   sals_calib_eigenvectors reads back into pinned host memory, of which up to four blocks of 330 KB stay with the
+ *   library for its later calls (none where pinned memory is refused: the call then takes ordinary memory).
  * Layout.  All arrays are dense and row-major.  Element type `T` is the
  *   descriptor's storage type: 32-bit float, or bfloat16 (upper 16 bits of a
  *   float, round-to-nearest-even).  Token t of a sequence has RoPE position t.

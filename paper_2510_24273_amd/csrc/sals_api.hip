@@ -29,6 +29,7 @@
 #include "k_qvalue.hpp"
 #include "k_value.hpp"
 #include "k_window.hpp"
+#include "host_block.hpp"
 #include "polar_plan.hpp"
 
 using namespace sals;
@@ -2003,42 +2004,24 @@ int jac_slices(int D)
     while (D % (32 * s) == 0 && D / (2 * s) >= 64 && D / (2 * kJacBig) * (2 * s) <= 256) s *= 2;
     return s;
 }
-// Pinned host memory for what a call reads back (a wait for the device and 8 KB from it take 11 us, into other memory 22), for one call at
-// a time.  Making and freeing it takes 25 us and waits for every stream of the process, so up to four blocks are kept from call to call.
-struct PinnedLease {
-    double* p = nullptr;
-    bool idle = false;   // no copy into it is under way
-    explicit PinnedLease(size_t n_) : n(n_)
+constexpr int kAllMaxD = 3584;   // of transformations of all rows at once (see all_first)
+struct PinnedAlloc {
+    static void* pin(size_t bytes)
     {
-        {
-            const std::lock_guard<std::mutex> hold(lock());
-            for (Block& b : kept())
-                if (b.p && b.n >= n) { p = b.p; n = b.n; b.p = nullptr; return; }
-        }
-        void* q = nullptr;
-        if (hipHostMalloc(&q, n * 8, hipHostMallocPortable) == hipSuccess) p = static_cast<double*>(q);
-        else (void)hipGetLastError();
+        void* p = nullptr;
+        if (hipHostMalloc(&p, bytes, hipHostMallocPortable) == hipSuccess) return p;
+        (void)hipGetLastError();
+        return nullptr;
     }
-    ~PinnedLease()
-    {
-        if (!p) return;
-        if (idle) {
-            const std::lock_guard<std::mutex> hold(lock());
-            for (Block& b : kept())
-                if (!b.p) { b = Block{p, n}; return; }
-        }
-        (void)hipHostFree(p);
-    }
-    PinnedLease(const PinnedLease&) = delete;
-    PinnedLease& operator=(const PinnedLease&) = delete;
-
-private:
-    struct Block { double* p; size_t n; };
-    typedef Block Blocks[4];
-    static std::mutex& lock() { static std::mutex m; return m; }
-    static Blocks& kept() { static Blocks b = {}; return b; }
-    size_t n;
+    static void unpin(void* p) { (void)hipHostFree(p); }
 };
+// doubles that a call reads back: convergence slots, norms, what is found of angles (their sums, counts and squares, or two values a tile)
+constexpr size_t eig_host_doubles(int D)
+{
+    const size_t n = D, tiles = n * n / 4096, angles = n * n / 2048;
+    return n / kJacBig + n + (D <= kAllMaxD ? tiles + 2 * angles : 2 * tiles);
+}
+typedef HostBlock<PinnedAlloc, std::max(eig_host_doubles(kCalMaxD), eig_host_doubles(kAllMaxD)) * 8, 4> EigHost;
 struct Event {
     hipEvent_t e = nullptr;
     ~Event() { if (e) (void)hipEventDestroy(e); }
@@ -2088,7 +2071,6 @@ namespace {
 // transformations behind one, two, three and four sweeps (and with sweeps alone): D = 256 1.8 / 1.9 / 2.0 / 2.0 (2.1), 512 2.8 / 2.8 /
 // 3.0 / 3.2 (4.1), 1024 4.9 / 5.3 / 5.7 / 6.3 (9.4), 1536 12.9 / 13.3 / 13.8 / 14.3 (19.1), 2048 21.2 / 21.5 / 21.8 / 22.5 (28.7), 2560 45.6 /
 // 43.8 / 43.0 / 44.1 (58.9), 3072 67.9 / 68.0 / 66.9 / 63.9 (80.3), 3584 111 / 104 / 102 / 98.6 (109), 4096 159 / 149 / 142 / 140 (141).
-constexpr int kAllMaxD = 3584;
 inline int all_first(int D) { return D <= 2048 ? 1 : D < 3072 ? 3 : 4; }
 // Up to kFloatMaxD the long way, in place of the first sweep and of the transformations that follow it, is gone in floats (k_calib_all.hpp):
 // transformations until one has started from |E| <= kFloatLast, V made orthogonal once, in fp32, behind the first one that starts from
@@ -2187,14 +2169,13 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         hipLaunchKernelGGL(calib_chol_finish_kernel, dim3(D), dim3(256), 0, st, G, D, diag);
         return launch_status() == SALS_OK;
     };
+    EigHost host;   // (behind the first launch a lack of memory would leave kernels at work in the caller's)
+    if (!host.p) return SALS_ERR_HIP;
     // G = Cholesky factor of C + shift I, the shift from C's scale, which the host learns with what came of it.
     row_norms(C);
     hipLaunchKernelGGL(calib_scale_kernel, dim3(1), dim3(kCalThreads), 0, st, norm, D, scale);
-    const bool begun = factor(1.0);
-    PinnedLease host((size_t)n_blocks + D + 2 * n_angles + n_tiles);
-    if (!host.p) return SALS_ERR_HIP;
-    if (!begun || calib_all_lds(series) != SALS_OK) return SALS_ERR_HIP;
-    double *const h_conv = host.p, *const h_norm = h_conv + n_blocks, *const h_found = h_norm + D;
+    if (!factor(1.0) || calib_all_lds(series) != SALS_OK) return SALS_ERR_HIP;
+    double *const h_conv = static_cast<double*>(host.p), *const h_norm = h_conv + n_blocks, *const h_found = h_norm + D;
     auto read = [&](void* to, const void* from, size_t bytes) { return hipMemcpyAsync(to, from, bytes, hipMemcpyDeviceToHost, st) == hipSuccess; };
     auto wait = [&]() { return launch_status() == SALS_OK && hipStreamSynchronize(st) == hipSuccess; };
     if (!read(h_norm, scale, 8) || !read(h_conv, fail, sizeof(int)) || !wait()) return SALS_ERR_HIP;
