@@ -225,6 +225,38 @@ def test_the_way_in_floats_leaves_no_trace(D, r, kind):
     assert float((V @ C - L[:, None] * V).norm(dim=1).max()) <= (2e-11 + eps) * lam[0]
 
 
+def _rotated(lam, seed):
+    rng = np.random.default_rng(seed)
+    Q = torch.linalg.qr(torch.from_numpy(rng.standard_normal((len(lam), len(lam)))).to(gu.DEV))[0]
+    C = (Q * gu.to_dev(lam)) @ Q.T.contiguous()
+    return (0.5 * (C + C.T)).contiguous()
+
+
+@pytest.mark.parametrize("D,r", [(512, 320), (1024, 640)])
+def test_the_way_in_floats_is_gone(D, r):
+    """A covariance of half the full rank and more eigenvectors than that: from the Cholesky factor on fp64 takes a sweep, its transformations and a
+    second sweep; behind the way in floats, which counts as the first, there is none.  (Results alone would not tell whether it was gone.)"""
+    print(f"[case] one sweep or two, D={D} r={r}", flush=True)
+    C = _rotated(np.where(np.arange(D) < D // 2, 1.0 / (1.0 + np.arange(D)), 0.0), D + r)
+    assert binding.calib_eigenvectors(C, r, torch.float32)[2] == 1
+
+
+@pytest.mark.parametrize("D,kind", [(256, "wide"), (256, "geometric"), (512, "power"), (512, "six decades"), (1024, "geometric"), (1024, "twelve decades")])
+def test_eigenvalues_beside_a_64_bit_eigensolver(D, kind):
+    """The whole call against LAPACK on the same matrix.  Either is off by what fp64 sums of D products are, sqrt(D) 2^-53 of the largest
+    eigenvalue, for each of the few products that the rows go through behind the floats: eight of them here (measured 2e-15 on average and 1e-14 at
+    most, D = 256 to 1024).  A V that came out of the floats orthogonal to 5e-5 only, corrected to third order, leaves 4e-14."""
+    print(f"[case] 64-bit eigensolver, D={D} {kind}", flush=True)
+    c = np.arange(1, D + 1)
+    lam = {"wide": 2.0 - 1.99 * c / D, "geometric": 10.0 ** (-2.0 * c / D), "power": c ** -2.0, "six decades": 10.0 ** (-6.0 * c / D),
+           "twelve decades": 10.0 ** (-12.0 * c / D)}[kind]
+    C = _rotated(lam, D)
+    want = np.linalg.eigvalsh(C.cpu().numpy())[::-1]
+    got, _, sweeps = binding.calib_eigenvectors(C, D, torch.float32)
+    assert 0 < sweeps <= 20
+    np.testing.assert_allclose(got.cpu().numpy(), want, rtol=0, atol=8 * np.sqrt(D) * 2.0 ** -53 * want[0])
+
+
 @pytest.mark.parametrize("D,r,width", [(256, 256, 16), (512, 200, 32), (768, 768, 64), (768, 480, 96), (1024, 640, 128)])
 def test_coupled_groups_of_neighbouring_rows(D, r, width):
     """Groups of `width` neighbouring channels that mix among themselves alone: rotations inside the small blocks of rows, inside blocks, inside
@@ -571,13 +603,8 @@ def test_wide_spectra_need_no_sweep_behind_the_floats(D, r, decades):
     """Eigenvalues over many decades, whose angles fall slowly at first: the way in floats, which counts as one sweep, is gone to its end, and what
     it leaves is for transformations at any width."""
     print(f"[case] wide spectrum, D={D} r={r} {decades} decades", flush=True)
-    rng = np.random.default_rng(D + r)
     lam = 10.0 ** (-decades * np.arange(1, D + 1) / D)
-    Q = torch.linalg.qr(torch.from_numpy(rng.standard_normal((D, D))).to(gu.DEV))[0]
-    C = (Q * gu.to_dev(lam)) @ Q.T.contiguous()
-    C = (0.5 * (C + C.T)).contiguous()
-    rows = C.clone()
-    got, U, sweeps = binding.calib_eigenvectors(rows, r, torch.float32)
+    got, _, sweeps = binding.calib_eigenvectors(_rotated(lam, D + r), r, torch.float32)
     torch.cuda.synchronize()
     assert sweeps == 1
     # (bounds as above)

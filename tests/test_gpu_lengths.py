@@ -1,6 +1,7 @@
 """Lengths advanced by the last workgroup of an append or a prompt compression: rows, codes and lengths against a context that was
 never prepared, whose lengths a second launch advances, bit for bit, call after call and in replays of a captured graph.  Shapes: batches at the edges of a
-wave's lanes, full caches, sequences without new tokens, grids with workgroups that have nothing to do."""
+wave's lanes, full caches, sequences without new tokens, grids with workgroups that have nothing to do.  (Batches of 64 and 128 sequences have no room for
+a count of arrivals: there a second launch advances the lengths of either context.)"""
 import ctypes
 
 import pytest
@@ -36,7 +37,7 @@ def _rand(gen, dtype, *shape):
 
 
 @pytest.mark.parametrize("dtype,B,bits", [("bf16", 1, 0), ("bf16", 64, 0), ("bf16", 65, 4), ("bf16", 128, 0), ("bf16", 12, 2),
-                                          ("f32", 17, 0), ("f32", 128, 4)])
+                                          ("f32", 17, 0), ("f32", 128, 4), ("bf16", 63, 0), ("bf16", 127, 2), ("f32", 127, 4), ("f32", 63, 0)])
 def test_append(dtype, B, bits):
     print(f"[case] append {dtype} B={B} bits={bits}", flush=True)
     S, H_kv, r = 9, 4, 128
@@ -67,7 +68,9 @@ def test_append(dtype, B, bits):
 
 @pytest.mark.parametrize("dtype,B,n_tok,r,counts", [
     ("bf16", 3, 130, 192, [130, 0, 77]), ("bf16", 2, 64, 64, None), ("bf16", 65, 40, 64, [(7 * b) % 41 for b in range(65)]),
-    ("bf16", 6, 1001, 640, [1001, 900, 0, 513, 256, 1]), ("bf16", 4, 2600, 640, None), ("f32", 3, 300, 128, [300, 0, 129])])
+    ("bf16", 6, 1001, 640, [1001, 900, 0, 513, 256, 1]), ("bf16", 4, 2600, 640, None), ("f32", 3, 300, 128, [300, 0, 129]),
+    ("bf16", 63, 40, 64, [(7 * b) % 41 for b in range(63)]), ("bf16", 127, 33, 64, [(5 * b) % 34 for b in range(127)]),
+    ("f32", 127, 20, 64, [(3 * b) % 21 for b in range(127)])])
 def test_prompt(dtype, B, n_tok, r, counts):
     print(f"[case] prompt {dtype} B={B} n_tok={n_tok} r={r} counts={counts}", flush=True)
     H_kv = 4

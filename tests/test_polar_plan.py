@@ -97,15 +97,15 @@ def test_plans_of_the_way_in_floats_leave_what_they_say(tmp_path, defect):
     (tmp_path / "plan.cpp").write_text(PROGRAM)
     subprocess.run(["g++", "-std=c++17", "-O1", "-DNEAR=sals::kFloatPolar", "-I", build.CSRC, "-o", str(tmp_path / "plan"), str(tmp_path / "plan.cpp")],
                    check=True)
+    bounds = [float(b) for b in np.concatenate([np.geomspace(1e-6, 50.0, 200), np.linspace(0.1, 6.1, 200)])]
+    plans = subprocess.run([str(tmp_path / "plan"), *(repr(b ** 4) for b in bounds)], check=True, capture_output=True, text=True, timeout=10).stdout
     worst = 0.0
-    for bound in np.concatenate([np.geomspace(1e-6, 50.0, 200), np.linspace(0.1, 6.1, 200)]):
-        out = subprocess.run([str(tmp_path / "plan"), repr(float(bound) ** 4)], check=True, capture_output=True, text=True, timeout=10).stdout.split()
-        n, one_more, tau, top, a = int(out[0]), out[1] == "1", float(out[2]), float(out[3]), [float(x) for x in out[4:]]
+    for bound, plan, left in zip(bounds, plans.splitlines(), defect(*bounds)):
+        n, one_more, tau, top, *a = map(float, plan.split())
         assert 1 <= n <= 6
         x = np.sqrt(1.0 + np.linspace(0.0, tau * bound, 1001) ** 2) / top
-        for s in a + [1.0] * one_more:
+        for s in a + [1.0] * int(one_more):
             x = 1.5 * s * x - 0.5 * (s * x) ** 3
-        left = defect(float(bound))[0]
         assert np.max(np.abs(x * x - 1.0)) <= left * (1 + 1e-9) + 1e-15, bound
         worst = max(worst, left)
     u = 1 - 0.97 ** 2
