@@ -35,7 +35,9 @@
  *   passed as void*, NULL = the default stream) and returns; nothing synchronises
  *   and no device data is read on the host, except where a call says so
  *   (sals_prepare, sals_calib_eigenvectors, sals_profile_collect).  Calls that share one context must be
- *   ordered on one stream (they share the workspace).
+ *   ordered, on one stream or by events: they share the workspace.  That holds for appends and prompt
+ *   compressions too, which count their workgroups there to advance the lengths: two that overlap leave wrong
+ *   lengths, and a count that is off from then on.
  * Errors.  Every call returns a sals_status; nothing throws or aborts.  Argument
  *   and descriptor errors are detected on the host before anything is enqueued.
  *   A failed launch returns SALS_ERR_HIP.
@@ -106,7 +108,8 @@ void sals_destroy(sals_ctx* ctx);
 /* One-time device set-up of a context: fills the cos/sin table of the workspace with one
  * kernel on `hip_stream`, WAITS for it (only this call, sals_calib_eigenvectors and
  * sals_profile_collect block the host), and raises the LDS limit of the kernels the
- * context will launch.  Afterwards calls on the context may come from any stream and may be captured into HIP graphs.
+ * context will launch.  Afterwards calls on the context may come from any stream, ordered with each other as all
+ * calls of a context, and may be captured into HIP graphs.
  * A context that was never prepared still works: the first call that needs the table
  * enqueues the fill on its own stream, calls on the same stream follow by stream order and
  * calls on other streams wait for an event; but such a context must not be used under
@@ -390,8 +393,9 @@ sals_status sals_overlap_score(sals_ctx* ctx, const void* q, const int32_t* q_po
  *
  * sals_calib_eigenvectors computes the eigen-decomposition of C (symmetric, positive semi-definite up to the rounding
  * of its sums) by one-sided Jacobi rotations in fp64, of the rows of the Cholesky factor of C plus a small multiple of
- * the identity (with a workspace of the full size and D up to 3584 also by orthogonal transformations of all rows at once;
- * up to D = 2560 the first of these are found in fp32 and applied together, as one matrix that is orthogonal to fp64 rounding), and returns all eigenvalues in descending order and the r leading eigenvectors:
+ * the identity (with a workspace of the full size and D up to 3584 also by orthogonal transformations of all rows at
+ * once; up to D = 2560 the first of these are found in fp32 and applied together, as one matrix that is orthogonal to
+ * fp64 rounding), and returns all eigenvalues in descending order and the r leading eigenvectors:
  *   C          [D, D] fp64 (device)    in; OVERWRITTEN (its rows become eigenvalue times eigenvector)
  *   D          multiple of 256, at most 8192;  r  1 .. D
  *   dtype      storage type T of U
@@ -405,8 +409,8 @@ sals_status sals_overlap_score(sals_ctx* ctx, const void* q, const int32_t* q_po
  *   workspace  device, 256-byte aligned, sals_calib_eigenvectors_workspace_bytes(D) bytes (the factor and two partial
  *              sums of a series, 8 D^2 bytes each, and some D of scratch).  Fewer are taken from 8 D^2 + 900 D on
  *              (SALS_ERR_WORKSPACE below what the sweeps need): all rotations are then made by sweeps, whose
- *              sums are spread over as much of the device as the scratch allows (D = 1024: 3.2 ms with the full size,
- *              10.2 with 8 D^2 + 4000 D bytes, 15.4 with the least)
+ *              sums are spread over as much of the device as the scratch allows (D = 1024: 2.7 ms with the full size,
+ *              10.3 with 8 D^2 + 4000 D bytes, 14.9 with the least)
  *   max_sweeps at least 1 (host): a sweep rotates every pair of rows once (transformations of all rows, which come
  *              between sweeps, are not counted; where they take the place of the first sweep, which they do if the
  *              limit is more than one, they count as one); the call stops when no rotation that involves one of the r

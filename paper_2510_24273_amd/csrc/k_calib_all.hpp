@@ -14,9 +14,9 @@
 // The polar factor is found by Newton-Schulz steps in pairs of bf16, the last one in fp32 (X <- a X - b (X X^T) X, scaled by the
 // bounds of its singular values: J. Chen, E. Chow, "A stable scaling of Newton-Schulz for improving the sign function computation of
 // a Hermitian matrix", 2014), and only *found* there: what is left, delta = X X^T - I (at most 1e-5: 6.7e-6 where the last step begins
-// with the smallest singular values it may, and the rounding of fp32; measured 5e-7 to 4e-6; the product of many factors that floats go
-// by is brought there by as many steps in fp32 as its bound asks for, see FloatDefect), is formed in fp64 and taken out to third
-// order, G <- (I - delta / 2 + 3/8 delta^2) X G, with fp64 products.  The next term, 5/16 delta^3, is below 4e-16, so what a
+// with the smallest singular values it may, and the rounding of fp32; measured 5e-7 to 4e-6; where rows go in floats, below, it is the
+// product of many coarser factors, brought there by steps in fp32, see FloatDefect), is formed in fp64 and taken out to third order,
+// G <- (I - delta / 2 + 3/8 delta^2) X G, with fp64 products.  The next term, 5/16 delta^3, is below 4e-16, so what a
 // transformation does to G is orthogonal to the rounding of those products (G^T G changed by 2e-15 to 3e-15 of its norm, D = 256 to 1024),
 // and which transformation is made decides nothing but how fast the rows converge.  (D = 1024, r = 640: eigenvalues off by 1.2e-14 of
 // themselves against a 64-bit eigensolver, by 2.4e-14 with sweeps alone.)  With X (X X^T) in the place of (X X^T) X, which is the same
@@ -30,9 +30,9 @@
 namespace sals {
 
 // ---- 64 x 64 tiles of products of [D, D] matrices --------------------------------------------------------------------
-// Tile (blockIdx.y, blockIdx.x) of A B^T (NN: of A B), summed in ACC; rows of A are D apart, those of B ldb.  A step is 128 bytes of a row: 32 floats or 16 doubles
-// of the contraction.  Both operands go from memory straight into LDS, three steps ahead in four stages; eight waves, each half
-// of a step's contraction for a quarter of the tile.  16-byte piece p of row r lies at piece p ^ ((r >> 1) & 7): no bank conflicts.
+// Tile (blockIdx.y, blockIdx.x) of A B^T (NN: of A B), summed in ACC; rows of A are D apart, those of B ldb.  A step is 128 bytes of a row:
+// 32 floats or 16 doubles of the contraction.  Both operands go from memory straight into LDS, three steps ahead in four stages;
+// eight waves, each half of a step's contraction for a quarter of the tile.  16-byte piece p of row r lies at piece p ^ ((r >> 1) & 7): no bank conflicts.
 // Bound by the matrix cores from D = 2048 on (131 TFLOP/s in fp32, 66 in fp64); at D = 1024, one tile per compute unit, 22 and 38 us
 // a product, where operands straight from memory took 33 and 47 (rows a power of two apart, and four waves asking for each).
 // finish(part, row, col, e, value): called by the first four waves, element e = 0 .. 15 of lane's sixteen.
@@ -45,7 +45,8 @@ template <typename TA, typename TB, bool NN, typename ACC, typename Finish>
 __device__ __forceinline__ void calib_product(const TA* A, const TB* B, int D, int ldb, Finish finish)
 {
     static_assert(NN || sizeof(TA) == sizeof(TB), "operand layout");
-    constexpr int KS = 128 / (int)sizeof(TA), EPV = 16 / (int)sizeof(TA), RB = 64 * (int)sizeof(TB), B_BYTES = NN ? KS * RB : 8192, STAGE = 8192 + B_BYTES, ST = kProdStages;
+    constexpr int KS = 128 / (int)sizeof(TA), EPV = 16 / (int)sizeof(TA), RB = 64 * (int)sizeof(TB);
+    constexpr int B_BYTES = NN ? KS * RB : 8192, STAGE = 8192 + B_BYTES, ST = kProdStages;
     constexpr int NB = B_BYTES / 8192, NL = 1 + NB;   // loads of a wave per step
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kg = lane >> 4;
@@ -430,9 +431,10 @@ __global__ __launch_bounds__(kProdThreads) void calib_apply_kernel(const TA* A, 
     });
 }
 
-// exp(E) - I for a small skew E, so that one product with G takes all its terms: X = E - P / 2 with P = E E^T = -E^2 summed in fp64 and, LONG, the
-// terms of third and fourth order, (P / 24 - E / 6) P, by a product in fp32 behind it: with |E|_F at most 5.7e-3 (the limit is one of the pairs)
-// they are 3e-8, and fp32 leaves 2e-15 of them, in the Frobenius norm.  At D = 1024 28 + 22 + 44 us for four terms, and 28 + 44 for two, where a product with G took 44 for each term.
+// exp(E) - I for a small skew E, so that one product with G takes all its terms: X = E - P / 2 with P = E E^T = -E^2 summed in fp64 and,
+// LONG, the terms of third and fourth order, (P / 24 - E / 6) P, by a product in fp32 behind it: with |E|_F at most 5.7e-3 (the limit is
+// one of the pairs) they are 3e-8, and fp32 leaves 2e-15 of them, in the Frobenius norm.  At D = 1024 28 + 22 + 44 us for four terms,
+// and 28 + 44 for two, where a product with G took 44 for each term.
 template <bool LONG>
 __global__ __launch_bounds__(kProdThreads) void calib_series_kernel(const double* __restrict__ E, int D, double* __restrict__ X, float* __restrict__ P,
                                                                     float* __restrict__ L)
@@ -457,7 +459,8 @@ __global__ __launch_bounds__(kProdThreads) void calib_series_kernel(const double
     });
 }
 // X += L P, P symmetric
-__global__ __launch_bounds__(kProdThreads) void calib_series_rest_kernel(const float* __restrict__ L, const float* __restrict__ P, int D, double* __restrict__ X)
+__global__ __launch_bounds__(kProdThreads) void calib_series_rest_kernel(const float* __restrict__ L, const float* __restrict__ P, int D,
+                                                                         double* __restrict__ X)
 {
     calib_product<float, float, false, float>(L, P, D, D, [&](int i, int j, float v) { X[(size_t)i * D + j] += (double)v; });
 }
@@ -663,12 +666,13 @@ static_assert((kFloatMaxD / 64) * (kFloatMaxD / 64) <= kPolarFound * kProdThread
 // d I + s E + t A + f A E^T (N == 2, B = S = E, which is skew).  What is symmetric or skew is read and written by rows for columns, four
 // elements a lane; of what is neither, S and OT are the transposes.  Left as plain bf16 or in fp32.
 //
-// Bound by what a compute unit draws, of which a pair's half is half: 7 us a product at D = 1024 where pairs take 12 to 15, a call 3300 -> 3110 us
-// (D = 2048 18.5 -> 15.4 ms) with all steps but the last one so, and 2824 -> 2667 (13.4 -> 12.4) with that one too.  Rounding X to 2^-9 turns the
+// Bound by what a compute unit draws, of which a pair's half is half: 7 us a product at D = 1024 where pairs take 12 to 15, a call when
+// this was made 3300 -> 3110 us (D = 2048 18.5 -> 15.4 ms) with all steps but the last one so, and 2824 -> 2667 (13.4 -> 12.4) with that
+// one too.  Rounding X to 2^-9 turns the
 // rows by 2^-9 of the angles that are taken out, while these are still large, and moves its singular values by 2e-3 (noise of 2^-9 / sqrt(3 D) an
 // element), which the last step, the one that leaves fp32, takes to the square of that.  The steps multiply with X X^T - I, whose rounding is a
-// small part of what is still to be made good; the diagonal of X X^T alone would be off by 4e-3.  X X^T - I stays within 4e-3.  Not once V is
-// polished: the last angles are told in pairs.
+// small part of what is still to be made good; the diagonal of X X^T alone would be off by 4e-3.  (FloatDefect has what is left.)  Not once V
+// is polished: the last angles are told in pairs.
 enum PolarOut { kOutPlain, kOutFloat };
 //
 // FIND: the scalars of the first step (N == 2) from the sums of squares of A's tiles, as polar_plan has them, so that the step need not wait for the
@@ -783,13 +787,15 @@ __global__ __launch_bounds__(kProdThreads) void calib_correction_kernel(const ui
 // From the factor to nearly orthogonal rows it is as far in floats as in doubles, and most of what is computed on the way only steers.
 // So the rows are taken there in floats, [G | V], D rows of 2 D floats: G = V times the factor (scaled so that its largest norm is about
 // one) and V the orthogonal matrix that all transformations so far amount to.  A transformation is that of above: steps inside and next to
-// blocks (calib_jacobi_*<float>), a polar factor, and one product, of [G | V].  Its polar factor is sloppier (pairs of bf16 to the end, see
-// kFloatPolar): V is made orthogonal behind one of the last transformations and at the end, by one Newton-Schulz step each in fp32, and at
-// last to rounding, in fp64, as it is applied to the factor's doubles: what it cost in bits is some angles of the size of fp32 rounding over the
-// relative distance of two eigenvalues, which the fp64 steps that follow take out.  Fewer fp64 products round the result: eigenvalues off by
-// 1e-15 of the largest one where they were by 3e-15, D = 1024, r = 640.
-// At D = 1024 a transformation takes 0.24 ms (fp64: 0.38), of which the product takes 37 us (131 TFLOP/s, the fp32 matrix cores' rate), the polar
-// factor up to 70, the steps in blocks 65, the Gram matrix and the angles 26; and no sweep (0.85 ms) comes before them.
+// blocks (calib_jacobi_*<float>), a polar factor, and one product, of [G | V].  Its polar factor is sloppier (plain bf16 up to where V is
+// polished, pairs of bf16 behind that; see kFloatPolar): V is made orthogonal behind one of the last transformations and at the end, by one
+// Newton-Schulz step each in fp32 (or more, see FloatDefect), and at last to rounding, in fp64, as it is applied to the factor's doubles:
+// what it cost in bits is some angles of the size of fp32 rounding over the relative distance of two eigenvalues, which the fp64 steps that
+// follow take out.  Fewer fp64 products round the result: eigenvalues off by 1e-15 of the largest one where they were by 3e-15, D = 1024,
+// r = 640.
+// At D = 1024 a transformation takes 0.18 ms (fp64: 0.38), of which the product takes 41 us (105 of the 131 TFLOP/s of the fp32 matrix cores), the
+// polar factor six to eight products of 7 to 9, the steps in blocks 33 + 16 and 5 for each Gram matrix, the Gram matrix of all rows and the
+// angles 26, norms and order 11; and no sweep (0.85 ms) comes before them.
 __global__ __launch_bounds__(kCalThreads) void calib_float_rows_kernel(const double* __restrict__ G, int D, double scale, float* __restrict__ GV)
 {
     const int i = blockIdx.x;

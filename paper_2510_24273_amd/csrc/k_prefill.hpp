@@ -43,7 +43,7 @@ __device__ __forceinline__ void pf_advance(int32_t* seq_len, const int32_t* n_ne
     if (s >= 0) seq_len[b] = (int)min((long long)s + n, (long long)S_max);
 }
 // thread 0 of a workgroup arrives behind every read of the lengths; the last workgroup advances them before it ends (6 ragged prompts
-// of up to 4001 tokens, D = 1024, r = 640 63.1 us a call with a launch for that behind the stores, 61.8 so)
+// of up to 4001 tokens, D = 1024, r = 640 62.9 us a call with a launch for that behind the stores, 61.8 so)
 __device__ __forceinline__ uint32_t pf_arrive(const PrefillArgs& a) { return a.arrived && threadIdx.x == 0 ? arrive(a.arrived, a.n_wg) : 0u; }
 __device__ __forceinline__ void pf_leave(const PrefillArgs& a, uint32_t order)
 {

@@ -88,12 +88,12 @@ __device__ __forceinline__ void qv_quantize_group(const QuantArgs& qa, const int
 
 // The append of a token.  Where the D axis is not sliced the last workgroup to arrive advances the lengths, on the way: every
 // workgroup arrives as soon as it has read them and looks at the answer behind its stores (arriving behind the stores cost 1 us more
-// than a launch that advances them; a step of 12 sequences of 8 KV heads with that launch 61.8 us, now 60.6).  blockIdx.z: projection of the new key (and value) into the latent caches, 16
-// coordinates per workgroup, blockIdx.y: slice of the D axis; QUANT: z = 0 projects the key, z = 1 quantises the new values,
-// 2 NW groups per workgroup.  What binds it is the bytes a compute unit draws: 16 coordinates over the whole axis are 128 KB of
-// the projector and as much of the inputs at D = 4096.  So where a second launch follows anyway the axis is sliced and that
-// launch adds the slices up (append_finish_kernel), and where none does (a recent window) eight waves have all their pieces in
-// flight.  (Batch 16, D = 4096, r = 512, 2-bit values, with the advance: 12.4 + 3.9 + 1.4 us as three launches of four waves,
+// than a launch that advances them; a step of 12 sequences of 8 KV heads with that launch 61.4 us, now 60.2).  blockIdx.z: projection
+// of the new key (and value) into the latent caches, 16 coordinates per workgroup, blockIdx.y: slice of the D axis; QUANT: z = 0
+// projects the key, z = 1 quantises the new values, 2 NW groups per workgroup.  What binds it is the bytes a compute unit draws: 16
+// coordinates over the whole axis are 128 KB of the projector and as much of the inputs at D = 4096.  So where a second launch
+// follows anyway the axis is sliced and that launch adds the slices up (append_finish_kernel), and where none does (a recent
+// window) eight waves have all their pieces in flight.  (Batch 16, D = 4096, r = 512, 2-bit values, with the advance: 12.4 + 3.9 + 1.4 us as three launches of four waves,
 // 10.2 + 1.4 with eight waves over the whole axis, 5.3 + 2.8 sliced.)
 // HB: column blocks in a round, as many as there are.  Eight of them, whose registers would leave a SIMD one wave, take their loads in
 // pairs (four waves) or one by one (eight waves, 16 pieces each), with the sums folded once.  Appends alone, D = 4096,

@@ -2074,10 +2074,10 @@ namespace {
 inline int all_first(int D) { return D <= 2048 ? 1 : D < 3072 ? 3 : 4; }
 // Up to kFloatMaxD the long way, in place of the first sweep and of the transformations that follow it, is gone in floats (k_calib_all.hpp):
 // transformations until one has started from |E| <= kFloatLast, V made orthogonal once, in fp32, behind the first one that starts from
-// kFloatPolish or less.  A call, r = 5/8 D, in ms without and with it, D = 256 1.77 / 1.50, 512 2.73 / 2.10, 1024 4.75 / 3.48, 1536 12.8 / 10.6,
-// 2048 21.2 / 18.3, 2560 44.4 / 39.4, 3072 66.3 / 65.9, 3584 99.2 / 100.8; D = 1024 with spectra c^-2 5.5 / 4.0, 10^(-6 c / D) 5.1 / 4.1,
-// sixteenfold eigenvalues 9.6 / 8.2.  kFloatLast 0.3 and 0.03: 3.53 and 3.66 at D = 1024; kFloatPolish 1.5 and 6: 3.68 and 3.43, but 4.24 against
-// 4.01 with a spectrum c^-2; steps next to blocks twice: 3.72.
+// kFloatPolish or less.  A call, r = 5/8 D, in ms without and with it, D = 256 1.44 / 1.06, 512 2.34 / 1.49, 1024 4.30 / 2.63, 1536 12.2 / 6.75,
+// 2048 20.5 / 12.2, 2560 42.3 / 23.4 (beyond, with all polar factors in pairs, 3072 66.3 / 65.9, 3584 99.2 / 100.8); D = 1024 with
+// spectra c^-2 5.03 / 2.89, 10^(-6 c / D) 4.51 / 2.78, sixteenfold eigenvalues 8.18 / 6.70.  kFloatLast 0.3 and 0.03: 2.70 and 2.65 at D = 1024 where
+// 0.1 takes 2.65, and 1.55 and 1.63 with a linear spectrum at D = 512, where it takes 1.55; kFloatPolish 1.5 and 6: 2.65 and 2.68, 1.62 and 1.55.
 constexpr double kFloatLast = 0.1, kFloatPolish = 3.5;
 // the series of the exponential: cut behind E^4 it differs from an orthogonal matrix by |E|^6 / 72
 constexpr double kSeriesNorm = 4e-3;
@@ -2277,8 +2277,8 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
         auto low = [](uint32_t* M) { return reinterpret_cast<bf16_t*>(M); };
         auto high = [&](uint32_t* M) { return reinterpret_cast<bf16_t*>(M) + (size_t)D * D; };
         auto plain_square = [&](uint32_t* X, uint32_t* A) {
-            hipLaunchKernelGGL((calib_polar_plain_kernel<0, false, kOutPlain, false>), tile_grid, prod, kPlainLds, st, low(X), low(X), D, 1.f, -1.f, 0.f, nullptr,
-                               0.f, high(A), nullptr, nullptr);
+            hipLaunchKernelGGL((calib_polar_plain_kernel<0, false, kOutPlain, false>), tile_grid, prod, kPlainLds, st, low(X), low(X), D, 1.f, -1.f, 0.f,
+                               nullptr, 0.f, high(A), nullptr, nullptr);
         };
         auto begin_plain = [&](uint32_t* E, uint32_t* A, uint32_t* X) {
             hipLaunchKernelGGL((calib_polar_plain_kernel<2, false, kOutPlain, true>), tile_grid, prod, kPlainLds, st, low(A), low(E), D, 0.f, 0.f, 0.f, low(E),
@@ -2291,7 +2291,8 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             ahead = ahead && n > 1;
             auto first = [&](auto out) {
                 hipLaunchKernelGGL((calib_polar_plain_kernel<2, false, (PolarOut)decltype(out)::value, false>), tile_grid, prod, kPlainLds, st, low(A), low(E),
-                                   D, (float)(w * P.tau * P.tau * P.tau), (float)c1, (float)(c1 * P.tau), low(E), (float)(-w * P.tau * P.tau), X, high(X), nullptr);
+                                   D, (float)(w * P.tau * P.tau * P.tau), (float)c1, (float)(c1 * P.tau), low(E), (float)(-w * P.tau * P.tau), X,
+                                   high(X), nullptr);
             };
             if (n == 1) first(std::integral_constant<int, kOutFloat>{});
             else if (!ahead) first(std::integral_constant<int, kOutPlain>{});
@@ -2338,7 +2339,8 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
                 hipLaunchKernelGGL((calib_polar_kernel<0, true, false>), tile_grid, prod, kPairLds, st, E, E, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr, A,
                                    square);
             }
-            if (!read(h_found, square, (size_t)(n_tiles + (first ? 2 : 1) * n_angles) * 8) || (first && !read(h_norm, sorted, (size_t)D * 8))) return SALS_ERR_HIP;
+            if (!read(h_found, square, (size_t)(n_tiles + (first ? 2 : 1) * n_angles) * 8) || (first && !read(h_norm, sorted, (size_t)D * 8)))
+                return SALS_ERR_HIP;
             const bool ahead = plain && steps > 1;   // (not the first time, which may leave C as it is)
             if (ahead) {
                 if (hipEventRecord(copied.e, st) != hipSuccess) return SALS_ERR_HIP;
@@ -2419,8 +2421,8 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
             uint32_t *const E = reinterpret_cast<uint32_t*>(third), *const A = E + (size_t)D * D;
             hipLaunchKernelGGL((calib_gram_kernel<double>), sym_grid, prod, kSymLds, st, rows, D, D, sorted, r,
                                reinterpret_cast<float*>(A), row_off);
-            hipLaunchKernelGGL((calib_all_angles_kernel<uint32_t>), dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D, sorted, r, row_off,
-                               kAllOpen, kAllDamp, E, all_found);
+            hipLaunchKernelGGL((calib_all_angles_kernel<uint32_t>), dim3(D / kAngleRows, D / 256), dim3(256), 0, st, reinterpret_cast<const float*>(A), D,
+                               sorted, r, row_off, kAllOpen, kAllDamp, E, all_found);
             hipLaunchKernelGGL((calib_polar_kernel<0, true, false>), tile_grid, prod, kPairLds, st, E, E, D, 1.f, 0.f, 0.f, nullptr, 0.f, nullptr,
                                A, square);
             if (!read(h_found, square, (size_t)(n_tiles + n_angles) * 8) || !wait()) return SALS_ERR_HIP;
