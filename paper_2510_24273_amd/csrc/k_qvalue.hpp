@@ -93,8 +93,8 @@ __device__ __forceinline__ void qv_quantize_group(const QuantArgs& qa, const int
 // projects the key, z = 1 quantises the new values, 2 NW groups per workgroup.  What binds it is the bytes a compute unit draws: 16
 // coordinates over the whole axis are 128 KB of the projector and as much of the inputs at D = 4096.  So where a second launch
 // follows anyway the axis is sliced and that launch adds the slices up (append_finish_kernel), and where none does (a recent
-// window) eight waves have all their pieces in flight.  (Batch 16, D = 4096, r = 512, 2-bit values, with the advance: 12.4 + 3.9 + 1.4 us as three launches of four waves,
-// 10.2 + 1.4 with eight waves over the whole axis, 5.3 + 2.8 sliced.)
+// window) eight waves have all their pieces in flight.  (Batch 16, D = 4096, r = 512, 2-bit values, with the advance: 12.4 + 3.9 + 1.4 us
+// as three launches of four waves, 10.2 + 1.4 with eight waves over the whole axis, 5.3 + 2.8 sliced.)
 // HB: column blocks in a round, as many as there are.  Eight of them, whose registers would leave a SIMD one wave, take their loads in
 // pairs (four waves) or one by one (eight waves, 16 pieces each), with the sums folded once.  Appends alone, D = 4096,
 // in us: 128 sequences, r = 640 (eight waves) 25.7 in rounds of two blocks, 23.5 in one of eight (24.0 unrolled over all blocks, each

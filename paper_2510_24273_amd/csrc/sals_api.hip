@@ -2388,6 +2388,7 @@ sals_status sals_calib_eigenvectors(double* C, int32_t D, int32_t r, int32_t dty
     if (all && D <= kFloatMaxD && max_sweeps > 1 && !converged) {
         const sals_status s = float_rows(&fresh, &near);
         if (s != SALS_OK) return s;
+        near = near && fresh;
     }
     if (fresh) {   // (it takes the place of a sweep, and counts as one)
         rotated = true;
