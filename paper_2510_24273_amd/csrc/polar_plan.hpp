@@ -57,7 +57,7 @@ inline PolarPlan polar_plan(double a2, double near = kPolarNear)
 // polished: fp64 halves small angles and more.  A limit of 0.9 of the one before, and of 0.6 below |E| = 10, left spectra early whose angles fall
 // all the way, for fp64 to do the rest: calls in ms with sweeps first, with that limit and with this one, D = 2560 and r = D, 10^(-8 c / D)
 // 50.7 / 62.9 / 30.4, 10^(-12 c / D) 51.8 / 81.7 / 49.7; D = 1024 and r = D, 10^(-12 c / D) 5.47 / 6.78 / 3.83; D = 256, 10^(-6 c / D) 1.81 / 1.41 /
-// 1.10.  Three in a row: 10^(-13 c / D) at D = 2560 1.66 of the time with sweeps first, now 0.96.  Eigenvalues that repeat, where it does
+// 1.10.  Three in a row: 10^(-13 c / D) at D = 2560 1.66 of the time with sweeps first, now 0.92.  Eigenvalues that repeat, where it does
 // stop: D = 1024, sixteenfold 8.98 / 6.43 / 6.74, two of them 15.9 / 11.4 / 7.27.
 struct FloatWay {
     double best = 1e300;
